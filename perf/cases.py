@@ -33,26 +33,26 @@ def blocks(name, M, hidden, qkv, ff, group=128, layers=1, graph=False, vocab=0, 
 def listed():
     return [
         # the smallest call: one projection of the smallest model for one token, launched by itself
-        {"name": "projection, one token", "kind": "linear", "format": "e0m4", "M": 1, "N": 2048, "K": 2048, "group": 128},
+        {"name": "projection one token", "kind": "linear", "format": "e0m4", "M": 1, "N": 2048, "K": 2048, "group": 128},
         # the headline workload: one decoding step of the 28-layer 6B model for a single user
-        blocks("decode 6B, batch 1", 1, 4096, 4608, 13696, layers=28, graph=True),
+        blocks("decode 6B b1", 1, 4096, 4608, 13696, layers=28, graph=True),
         # a few users on the 14B model with the finer group of 64 (six of its layers)
-        blocks("decode 14B g64, batch 6", 6, 5120, 15360, 13696, group=64, layers=6, graph=True),
+        blocks("decode 14B g64 b6", 6, 5120, 15360, 13696, group=64, layers=6, graph=True),
         # a full small batch on the 2B model with its vocabulary projection
-        blocks("decode 2B, batch 16", 16, 2048, 2560, 16384, layers=18, graph=True, vocab=256000),
+        blocks("decode 2B b16", 16, 2048, 2560, 16384, layers=18, graph=True, vocab=256000),
         # 8-bit weights where 4 bits lose too much, three users (eight layers)
-        blocks("decode 6B 8-bit, batch 3", 3, 4096, 4608, 13696, layers=8, graph=True, format="e0m8"),
+        blocks("decode 6B 8-bit b3", 3, 4096, 4608, 13696, layers=8, graph=True, format="e0m8"),
         # bfloat16 models, decoded for a handful of users
-        blocks("decode 6B bf16, batch 5", 5, 4096, 4608, 13696, layers=4, graph=True, format="bf16", kind="plain"),
+        blocks("decode 6B bf16 b5", 5, 4096, 4608, 13696, layers=4, graph=True, format="bf16", kind="plain"),
         # a chat turn: a prompt of a few dozen tokens
-        blocks("prompt 45, 6B", 45, 4096, 4608, 13696, layers=4),
+        blocks("prompt 45 6B", 45, 4096, 4608, 13696, layers=4),
         # a ragged prompt of ordinary length with the finest group
-        blocks("prompt 317, 2B g32", 317, 2048, 2560, 16384, group=32, layers=2),
+        blocks("prompt 317 2B g32", 317, 2048, 2560, 16384, group=32, layers=2),
         # the benchmark's prompts
-        blocks("prompt 1024, 6B", 1024, 4096, 4608, 13696, layers=2),
-        blocks("prompt 2048, 14B g64", 2048, 5120, 15360, 13696, group=64),
+        blocks("prompt 1024 6B", 1024, 4096, 4608, 13696, layers=2),
+        blocks("prompt 2048 14B g64", 2048, 5120, 15360, 13696, group=64),
         # a bfloat16 prompt of odd length
-        blocks("prompt 700 bf16, 6B", 700, 4096, 4608, 13696, format="bf16", kind="plain"),
+        blocks("prompt 700 6B bf16", 700, 4096, 4608, 13696, format="bf16", kind="plain"),
         # preparing a model: its largest matrix
         {"name": "pack 27392 x 4096", "kind": "pack", "format": "e0m4", "N": 27392, "K": 4096, "group": 128},
     ]
