@@ -501,6 +501,73 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_pipe_kernel(const half
             }
         }
     };
+    // Results to Y in whole 16-byte pieces of its rows, for row lengths that are a multiple of 8: the accumulators hold
+    // single elements of 32 different columns, so a wavefront turns 4 KiB of them at a time around in a piece of LDS of its
+    // own (the K loop's stages are free by then) and reads back eight neighbouring columns per lane.  The residual comes in
+    // the same way, the next piece's while this one's is used.  Element by element, the residual's loads -- one 2-byte load
+    // and one 2-byte store after the other, each masked by itself -- were a serial
+    // chain of 128 round trips to memory: 2048 x 5120 x 5120 with a residual (160 large tiles) 198 us, now 144; without a
+    // residual the stores alone: 2048 x 15360 x 5120 300 -> 291, gated 2048 x 27392 x 5120 538 -> 514.
+    constexpr uint32_t kTurnBytes = 32 * (32 + 4) * 4;  // per wavefront: 32 x 32 or 16 x 64 sums, rows padded by 16 bytes
+    static_assert(kTurnBytes >= 16 * (64 + 4) * 4 && kTurnBytes * WGM * WGN <= (uint32_t)kStages * kStageBytes, "fits the stages");
+    // COLS: columns of the wavefront's results (64, or 32 gated); value(i, r, j): accumulator register r of block i (j)
+    auto write_rows = [&](auto cols_c, auto value, auto* dst, const half_t* res, uint32_t ld, int wcol, int cols_valid) {
+        using out_t = std::remove_reference_t<decltype(*dst)>;
+        typedef out_t out8_t __attribute__((ext_vector_type(8)));
+        constexpr int COLS = decltype(cols_c)::value, ROWS = 1024 / COLS, kChunks = TM * 32 / ROWS;
+        constexpr int PPR = COLS / 8, RPP = 64 / PPR;   // 16-byte pieces per row, rows per pass (two passes per chunk)
+        constexpr int kStride = COLS + 4, NJ = COLS / 32, NR = 16 / NJ;
+        float* turn = reinterpret_cast<float*>(smem + wave * kTurnBytes);
+        const int prow = lane / PPR, pcol = (lane % PPR) * 8;
+        const bool col_ok = wcol + pcol < cols_valid;
+        const uint32_t o0 = (uint32_t)(wm + prow) * ld + (uint32_t)(wcol + pcol);
+        const int my_rows = col_ok ? rows_left - wm - prow : 0;     // rows from this lane's first on that exist
+        half8_t rs[2][2];
+        auto load_res = [&](int ch) {
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                const int dr = ch * ROWS + p * RPP;
+                rs[ch & 1][p] = half8_t{0, 0, 0, 0, 0, 0, 0, 0};
+                if (dr < my_rows) rs[ch & 1][p] = *reinterpret_cast<const half8_t*>(res + (o0 + (uint32_t)dr * ld));
+            }
+        };
+        __syncthreads();                                // every wavefront has left the K loop's stages
+        if (res) load_res(0);
+#pragma unroll
+        for (int ch = 0; ch < kChunks; ++ch) {
+            if (res && ch + 1 < kChunks) load_res(ch + 1);
+#pragma unroll
+            for (int j = 0; j < NJ; ++j)
+#pragma unroll
+                for (int rr = 0; rr < NR; ++rr)
+                    turn[(8 * (rr >> 2) + 4 * (lane >> 5) + (rr & 3)) * kStride + 32 * j + (lane & 31)] =
+                        value(ch * ROWS / 32, (ch * ROWS % 32) / 2 + rr, j);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                const int dr = ch * ROWS + p * RPP;
+                const float* src = turn + (p * RPP + prow) * kStride + pcol;
+                floatx4 lo = *reinterpret_cast<const floatx4*>(src), hi = *reinterpret_cast<const floatx4*>(src + 4);
+                if (res) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        lo[e] += (float)rs[ch & 1][p][e];
+                        hi[e] += (float)rs[ch & 1][p][4 + e];
+                    }
+                }
+                out8_t o;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    o[e] = out_value<out_t>(lo[e]);
+                    o[4 + e] = out_value<out_t>(hi[e]);
+                }
+                if (dr < my_rows) *reinterpret_cast<out8_t*>(dst + (o0 + (uint32_t)dr * ld)) = o;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();            // the piece of LDS is read before it is written again
+        }
+    };
     // A shared-out K range (even scheduling): this sharer's sums go to its slab, in the order the registers hold
     // them (16 bytes per lane and store, a wavefront's stores contiguous); the sharer that arrives last adds all
     // slabs of the tile in K order and goes on to write the tile like an unshared one.
@@ -594,28 +661,19 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_pipe_kernel(const half
                                 pu[o0 + (uint32_t)dr * n32] = acc[i][1][r];
                             }
                         }
-                } else {
-                    uint32_t nh32 = (uint32_t)fu.n_half;
-                    asm volatile("" : "+s"(nh32));             // (opaque, like n32)
-                    half_t* __restrict__ yt = Y + m0 * fu.n_half + n0;
-                    const half_t* __restrict__ rt = fu.residual ? fu.residual + m0 * fu.n_half + n0 : nullptr;
-                    const uint32_t o0 = (uint32_t)row0 * nh32 + (uint32_t)ocol;
-#pragma unroll
-                    for (int i = 0; i < TM; ++i)
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) {
-                            const int dr = 32 * i + 8 * (r >> 2) + (r & 3);
-                            if (row0 + dr < rows_left) {
-                                float v = silu_f32(acc[i][0][r]) * acc[i][1][r];
-                                if (rt) v += (float)rt[o0 + (uint32_t)dr * nh32];
-                                yt[o0 + (uint32_t)dr * nh32] = (half_t)v;
-                            }
-                        }
                 }
+            }
+            if (out_mode != 1) {
+                uint32_t nh32 = (uint32_t)fu.n_half;    // (a multiple of 32)
+                asm volatile("" : "+s"(nh32));          // (opaque, like n32)
+                write_rows(std::integral_constant<int, 32>{},
+                           [&](int i, int r, int) { return silu_f32(acc[i][0][r]) * acc[i][1][r]; },
+                           Y + m0 * fu.n_half + n0, fu.residual ? fu.residual + m0 * fu.n_half + n0 : nullptr, nh32,
+                           (wave % WGN) * 32, ocols_left);
             }
             continue;
         }
-        if (out_mode != 1 && fu.residual) {
+        if (out_mode != 1 && fu.residual && (n32 & 7u) != 0) {
             const half_t* __restrict__ rt = fu.residual + m0 * N + n0;
             half_t* __restrict__ yt = Y + m0 * N + n0;
 #pragma unroll
@@ -634,11 +692,15 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_pipe_kernel(const half
             continue;
         }
     }
+    using out_t = std::conditional_t<BF, __bf16, half_t>;
+    out_t* yt = reinterpret_cast<out_t*>(Y) + m0 * N + n0;
     if (out_mode == 1)
         store_tile(partial + ((size_t)split * (size_t)M + (size_t)m0) * (size_t)N + (size_t)n0);
+    else if ((n32 & 7u) == 0)
+        write_rows(std::integral_constant<int, 64>{}, [&](int i, int r, int j) { return acc[i][j][r]; }, yt,
+                   FUSED && fu.residual ? fu.residual + m0 * N + n0 : nullptr, n32, wn, cols_left);
     else
-        if (BF) store_tile(reinterpret_cast<__bf16*>(Y) + m0 * N + n0);
-        else store_tile(Y + m0 * N + n0);
+        store_tile(yt);
   }
 }
 

@@ -461,3 +461,20 @@ def test_fused_layer_in_a_hip_graph_matches_eager(e0m4):
             graph.replay()
         stream.synchronize()
         assert torch.equal(y, want), "replay %d" % replay
+
+
+@pytest.mark.parametrize("variant", [2, 3, 4, 5])
+@pytest.mark.parametrize("M,N,swiglu,in_place", [(257, 520, False, True), (190, 516, False, True), (63, 264, False, False),
+                                                 (130, 576, True, True), (31, 320, True, False)])
+def test_gemm_epilogue_edges(e0m4, oracle, variant, M, N, swiglu, in_place):
+    # results written in whole 16-byte pieces of rows (N a multiple of 8) or element by element (516), with the residual
+    # in place or not, on every tile: rows and columns that end inside a tile, a wavefront's block and a piece of LDS
+    e0m4.e0m4_set_knob("gemm_variant", variant)
+    e0m4.e0m4_set_knob("gemm_splits", 1)
+    try:
+        for bits in (4, 8):
+            run_fused(e0m4, oracle, M, N, 256, 128, seed=700 + M + bits, swiglu=swiglu, res=True, in_place=in_place, bits=bits)
+            run_fused(e0m4, oracle, M, N, 256, 128, seed=710 + M + bits, swiglu=swiglu, bits=bits)
+    finally:
+        e0m4.e0m4_set_knob("gemm_variant", 0)
+        e0m4.e0m4_set_knob("gemm_splits", 0)
