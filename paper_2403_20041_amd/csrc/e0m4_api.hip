@@ -69,29 +69,22 @@ __global__ void zero_fill_kernel(half_t* y, int64_t count)
 }
 
 bool group_ok(int group) { return group == 32 || group == 64 || group == 128; }
-// (gemv_mfma 1: off; 6: also for groups of 64 and 32 wherever it can run, which by default it does where it pays)
+// The small-batch kernel that stages X in LDS, for plain matmuls (gemv_mfma 1: off; 6: also for groups of 64 and 32).
 bool use_gemv_mfma(int64_t M, int64_t N, int64_t K, int group)
 {
     const int k = knob("gemv_mfma");
-    if (k == 1 || !gemv_mfma_supported(M, N, K, group)) return false;
-    return group == 128 || k == 6 || gemv_mfma_groups_pay(M, N, K, group);
+    return k != 1 && (group == 128 || k == 6) && gemv_mfma_supported(M, N, K, group);
 }
-// The small-batch kernel with dequantised weight operands serves groups of 32 and 64 at 3 <= M <= 16 where the
-// kernel above does not run (more than 8 or 4 rows) or does not pay: measured against the vector kernel and the GEMM on layer shapes of 6B and 14B
-// models it is 20 - 45 % faster for 4 <= M <= 8 whatever K is, and for 9 <= M <= 16 when all of X fits the LDS
-// (4608 x 4096 at M = 16: 8.9 against 13.2 us); with K in phases at those M it equals or loses to the GEMM
-// (15360 x 5120 at M = 16: 22.9 against 20.2 us), and at M = 2 the vector kernel is faster.  It runs up to 64
-// rows (two to four row tiles per weight operand), but from 17 rows on every workgroup stages more of X than it
-// reads weights and it measured 1.3 - 5 x slower than the GEMM, so those M are not sent to it by default.
-// gemv_mfma 4 forces it wherever it can run (2 <= M <= 64), 5 switches it off.
-bool use_gemv_dq(int64_t M, int64_t N, int64_t K, int group)
+// The small-batch kernel with dequantised weight operands, for plain matmuls: where it pays; gemv_mfma 4 forces it wherever it
+// can run (2 <= M <= 64), 1 and 5 switch it off, 2, 3 and 6 prefer the kernel above.
+bool use_gemv_dq(int64_t M, int64_t N, int64_t K, int group, DqFormat format)
 {
     const int k = knob("gemv_mfma");
-    if (k == 1 || k == 5 || M < 2) return false;
-    if (k == 4) return gemv_dq_supported(M, N, K, group);
-    if (group == 128 || M < 3 || M > 16) return false;
-    bool whole = false;
-    return gemv_dq_supported(M, N, K, group, &whole) && (whole || M <= 8);
+    if (k == 1 || k == 5 || !gemv_dq_supported(M, N, K, group)) return false;
+    if (k == 4) return true;
+    if (k != 0 && format == kDqFormatFp16 && use_gemv_mfma(M, N, K, group)) return false;
+    if (k != 0 && format == kDqFormatE8 && gemv_mfma8_supported(M, N, K)) return false;
+    return gemv_dq_pays(M, N, K, group, format);
 }
 // M <= kGemvMaxM rows take the vector decode kernel, whose time grows with M, unless the matrix-core GEMM
 // (64 x 256 tile, time nearly independent of M) is faster: measured crossover at about M * N * K = 3.8e8
@@ -102,8 +95,8 @@ bool small_m_on_vector(int64_t M, int64_t N, int64_t K)
     if (M < 2 || !gemm_pipe_supported(K) || N > (int64_t)1 << 24) return true;
     return (double)M * (double)N * (double)K < 3.8e8;
 }
-// 17 <= M <= kChunkedMaxM on small weights: the small-batch matrix-core kernel on equal chunks of at most 16 rows,
-// dealt to the y dimension of one launch (the chunks of a workgroup's row blocks follow each other on a compute unit
+// Fused matmuls with 17 <= M <= kChunkedMaxM on small weights: the small-batch matrix-core kernel on equal chunks of at
+// most 16 rows, dealt to the y dimension of one launch (the chunks of a workgroup's row blocks follow each other on a compute unit
 // or run side by side on the same XCD: the weights come from HBM once), instead of the GEMM, whose 64 x 256 tile with
 // its split along K costs 12 - 20 us whatever M is.  The launch takes about as long as one chunk times the rounds its
 // workgroups make on the 256 compute units (staging a chunk of X costs a workgroup more than its weights do):
@@ -192,8 +185,7 @@ size_t e0m4_workspace_bytes(int64_t M, int64_t N, int64_t K, int group)
 {
     if (check_shape(N, K, group) != E0M4_OK || M <= 0 || N == 0 || K == 0) return 0;             // invalid or empty: nothing runs
     if (small_m_on_vector(M, N, K)) return 0;           // the small-M kernels need none
-    if (use_gemv_dq(M, N, K, group)) return 0;
-    if (use_gemv_mfma(M, N, K, group) || small_batch_in_chunks(Fusion{}, M, N, K, group)) return 0;
+    if (use_gemv_dq(M, N, K, group, kDqFormatFp16) || use_gemv_mfma(M, N, K, group)) return 0;
     return gemm_workspace_bytes(M, N, K);       // partial tiles of the split-K GEMM, if it splits
 }
 
@@ -335,13 +327,10 @@ int e0m4_matmul(const void* X, int64_t M, const void* codes, const void* scales,
     }
     if (!X || !codes) return E0M4_ERR_NULL;
     if (!aligned16(X) || !aligned16(codes)) return E0M4_ERR_ALIGN;
-    if (knob("gemv_mfma") == 4 && use_gemv_dq(M, N, K, group))
-        return launch_gemv_dq(X, M, codes, N, K, group, Y, (hipStream_t)stream);
-    if (use_gemv_mfma(M, N, K, group)) return launch_gemv_mfma(X, M, codes, N, K, Y, (hipStream_t)stream, 1, group);
-    if (use_gemv_dq(M, N, K, group)) return launch_gemv_dq(X, M, codes, N, K, group, Y, (hipStream_t)stream);
+    if (use_gemv_dq(M, N, K, group, kDqFormatFp16))
+        return launch_gemv_dq(X, M, codes, N, K, group, kDqFormatFp16, Y, (hipStream_t)stream);
+    if (use_gemv_mfma(M, N, K, group)) return launch_gemv_mfma(X, M, codes, N, K, Y, (hipStream_t)stream, group);
     if (small_m_on_vector(M, N, K)) return launch_gemv(X, M, codes, N, K, group, Y, (hipStream_t)stream);
-    if (small_batch_in_chunks(Fusion{}, M, N, K, group))
-        return launch_gemv_mfma(X, M, codes, N, K, Y, (hipStream_t)stream, row_chunks(M), group);
     if (N > (int64_t)1 << 24) return E0M4_ERR_SHAPE;    // the GEMM epilogue forms 32-bit offsets of up to 256 rows of Y
     if (workspace_bytes > 0 && (!workspace || !aligned16(workspace))) return workspace ? E0M4_ERR_ALIGN : E0M4_ERR_NULL;
     return launch_gemm(X, M, codes, N, K, group, Y, workspace, workspace_bytes, (hipStream_t)stream);
@@ -382,6 +371,8 @@ int e0m4_matmul_fused(const void* X, int64_t M, const void* rms_gamma, float rms
         (residual && !aligned16(residual)))
         return E0M4_ERR_ALIGN;
     hipStream_t st = (hipStream_t)stream;
+    if (!f.any() && use_gemv_dq(M, N, K, group, kDqFormatFp16))         // nothing to fuse: the bits of e0m4_matmul
+        return launch_gemv_dq(X, M, codes, N, K, group, kDqFormatFp16, Y, st);
     const int path = fused_path(f, M, N, K, group);
     if (path == 2) return launch_gemv_mfma_fused(f, X, M, codes, N, K, Y, st, 1, group);
     if (path == 0) return launch_gemv_fused(f, X, M, codes, N, K, group, Y, st);
@@ -475,6 +466,8 @@ int e0m4_bf16_matmul(const void* X, int64_t M, const void* codes, int64_t N, int
     }
     if (!X || !codes) return E0M4_ERR_NULL;
     if (!aligned16(X) || !aligned16(codes)) return E0M4_ERR_ALIGN;
+    if (use_gemv_dq(M, N, K, group, kDqFormatBf16))
+        return launch_gemv_dq(X, M, codes, N, K, group, kDqFormatBf16, Y, (hipStream_t)stream);
     if (M <= kGemvMaxM) return launch_gemv_bf16(X, M, codes, N, K, group, Y, (hipStream_t)stream);
     if (N > (int64_t)1 << 24) return E0M4_ERR_SHAPE;    // 32-bit offsets in the GEMM epilogue
     return launch_gemm_bf16(X, M, codes, N, K, group, Y, (hipStream_t)stream);
@@ -542,7 +535,7 @@ static bool small_batch8_in_chunks(const Fusion& f, int64_t M, int64_t N, int64_
 
 static bool e0m8_use_gemm(int64_t M, int64_t N, int64_t K)
 {
-    return !e0m8_use_mfma_decode(M, N, K) && !small_batch8_in_chunks(Fusion{}, M, N, K) && !small_m_on_vector(M, N, K) &&
+    return !use_gemv_dq(M, N, K, 128, kDqFormatE8) && !e0m8_use_mfma_decode(M, N, K) && !small_m_on_vector(M, N, K) &&
            gemm_pipe_supported(K) && N <= (int64_t)1 << 24;
 }
 
@@ -569,9 +562,9 @@ int e0m8_matmul(const void* X, int64_t M, const void* codes, int64_t N, int64_t 
     }
     if (!X || !codes) return E0M4_ERR_NULL;
     if (!aligned16(X) || !aligned16(codes)) return E0M4_ERR_ALIGN;
+    if (use_gemv_dq(M, N, K, 128, kDqFormatE8))
+        return launch_gemv_dq(X, M, codes, N, K, 128, kDqFormatE8, Y, (hipStream_t)stream);
     if (e0m8_use_mfma_decode(M, N, K)) return launch_gemv_mfma8(X, M, codes, N, K, Y, (hipStream_t)stream);
-    if (small_batch8_in_chunks(Fusion{}, M, N, K))
-        return launch_gemv_mfma8(X, M, codes, N, K, Y, (hipStream_t)stream, row_chunks(M));
     if (e0m8_use_gemm(M, N, K)) {
         if (workspace_bytes > 0 && (!workspace || !aligned16(workspace))) return workspace ? E0M4_ERR_ALIGN : E0M4_ERR_NULL;
         return launch_gemm_pipe8(X, M, codes, N, K, Y, workspace, workspace_bytes, (hipStream_t)stream);
@@ -627,6 +620,8 @@ int e0m8_matmul_fused(const void* X, int64_t M, const void* rms_gamma, float rms
         (residual && !aligned16(residual)))
         return E0M4_ERR_ALIGN;
     hipStream_t st = (hipStream_t)stream;
+    if (!f.any() && use_gemv_dq(M, N, K, 128, kDqFormatE8))             // nothing to fuse: the bits of e0m8_matmul
+        return launch_gemv_dq(X, M, codes, N, K, 128, kDqFormatE8, Y, st);
     const int path = fused_path8(f, M, N, K);
     if (path == 2) return launch_gemv_mfma8_fused(f, X, M, codes, N, K, Y, st);
     if (path == 0) return launch_gemv8_fused(f, X, M, codes, N, K, Y, st);

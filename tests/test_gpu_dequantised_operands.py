@@ -1,0 +1,69 @@
+"""The small-batch kernel with dequantised weight operands (plain matmuls, 2 <= M <= 64) against the CPU oracle, in the three
+formats it serves: last tiles of 16 rows of X and 16 weight rows, k blocks that K does not fill, fewer k blocks than
+wavefronts and remainders of the unrolled loop, one to sixteen row blocks per workgroup."""
+import numpy as np
+import pytest
+
+import synth_inputs
+from test_gpu_bf16_e0m3 import assert_bf16_quantize_exact, bf_bits, bf_dev, check_bf16_matmul
+from test_gpu_parity import assert_quantize_exact, check_matmul, e0m4, to_dev, torch  # noqa: F401
+import test_gpu_e0m8
+
+pytestmark = pytest.mark.gpu
+
+# N, K, group, workgroups aimed at: 1, 2, 3 and 4 row blocks per wavefront, one, two and four groups of wavefronts
+SHAPES = [(17, 128, 64, 0), (203, 1152, 64, 0), (333, 2176, 128, 12), (520, 1664, 128, 4), (260, 640, 64, 1), (1000, 4224, 128, 9)]
+
+
+@pytest.mark.parametrize("fmt", ["e0m4", "e0m8", "bf16"])
+@pytest.mark.parametrize("N,K,G,workgroups", SHAPES + [(203, 416, 32, 3), (48, 96, 32, 0)])
+@pytest.mark.parametrize("M", [2, 9, 16, 17, 33, 48, 64])
+def test_forced(e0m4, oracle, fmt, N, K, G, workgroups, M):
+    if fmt == "e0m8" and G == 32:
+        pytest.skip("8-bit codes have groups of 64 and 128")
+    seed = 4000 + N + K
+    e0m4.e0m4_set_knob("gemv_mfma", 4)
+    e0m4.e0m4_set_knob("gemv_workgroups", workgroups)
+    try:
+        if fmt == "bf16":
+            codes, What, _ = assert_bf16_quantize_exact(e0m4, oracle, synth_inputs.weights_bf16(N, K, seed=seed), G)
+            X = synth_inputs.activations_bf16(M, K, seed=seed + M)
+            Y, Y2 = (e0m4.e0m4_bf16_matmul(bf_dev(X), codes, N, K, G) for _ in range(2))
+            Yref, absdot = oracle.bf16_matmul(X, What)
+            check_bf16_matmul(oracle, Y, Yref, absdot, "bf16")
+            assert np.array_equal(bf_bits(Y), bf_bits(Y2))
+            return
+        X = synth_inputs.activations(M, K, seed=seed + M, outlier_frac=0.01)
+        W = synth_inputs.weights(N, K, seed=seed)
+        if fmt == "e0m8":
+            codes, What = test_gpu_e0m8.assert_quantize_exact(e0m4, oracle, W, G)
+            Y, Y2 = (e0m4.e0m8_matmul(to_dev(X), codes, N, K, G) for _ in range(2))
+        else:
+            (codes, _, _), What = assert_quantize_exact(e0m4, oracle, W, G)
+            Y, Y2 = (e0m4.e0m4_matmul(to_dev(X), codes, None, None, N, K, G) for _ in range(2))
+        Yref, absdot = oracle.matmul(X, What)
+        check_matmul(Y, Yref, absdot, fmt)
+        assert torch.equal(Y, Y2)
+    finally:
+        e0m4.e0m4_set_knob("gemv_mfma", 0)
+        e0m4.e0m4_set_knob("gemv_workgroups", 0)
+
+
+@pytest.mark.parametrize("M", [3, 20])
+def test_infinite_activation_stays_in_its_row(e0m4, oracle, M):
+    # a k block that K does not fill: what stands in for the missing activations is zero, whatever the row holds
+    N, K, G = 70, 160, 32
+    (codes, _, _), What = assert_quantize_exact(e0m4, oracle, synth_inputs.weights(N, K, seed=4900), G)
+    X = synth_inputs.activations(M, K, seed=4901)
+    X[1, 130] = np.inf
+    e0m4.e0m4_set_knob("gemv_mfma", 4)
+    try:
+        Y = e0m4.e0m4_matmul(to_dev(X), codes, None, None, N, K, G).cpu().numpy()
+    finally:
+        e0m4.e0m4_set_knob("gemv_mfma", 0)
+    X[1, 130] = 0
+    keep = np.arange(M) != 1
+    Yref, absdot = oracle.matmul(X, What)
+    check_matmul(torch.from_numpy(Y[keep]), Yref[keep], absdot[keep], "rows without the infinity")
+    w = What[:, 130].astype(np.float64)
+    assert np.array_equal(Y[1][w != 0], (np.sign(w[w != 0]) * np.inf).astype(np.float16)) and np.isnan(Y[1][w == 0]).all()
