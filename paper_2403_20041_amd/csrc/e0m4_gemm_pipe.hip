@@ -105,15 +105,20 @@ struct SkArgs {
 // of 64 is one block, a lane reads two 16-byte chunks of 16 weights per slice, and MFMA number s takes
 // words 2(s%2) and 2(s%2)+1 of chunk s/2, each of which one mask-or (and one more after a rotation) turns
 // into four binade values.
-template <int G, int WGM, int WGN, bool FUSED, int BM, int BN, bool E8 = false, bool BF = false>
-__global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_pipe_kernel(const half_t* __restrict__ X, int64_t M,
+template <int G, int WGM, int WGN, bool FUSED, int BM, int BN, bool E8 = false, bool BF = false, int KS = 1>
+__global__ __launch_bounds__(64 * WGM * WGN * KS, 2) void gemm_pipe_kernel(const half_t* __restrict__ X, int64_t M,
                                                              const uint4* __restrict__ packed, int64_t N, int64_t K,
                                                              half_t* __restrict__ Y, int m_tiles, int n_tiles,
                                                              int splits, float* __restrict__ partial, PipeFusion fu,
                                                              SkArgs sk)
 {
-    constexpr int kThreads = 64 * WGM * WGN;
+    constexpr int kThreads = 64 * WGM * WGN;            // per K half
     constexpr int kStageBytes = BM * kRowBytes;
+    // K slices of weights in flight, and of activations in registers.  Twice as many for the flat bfloat16 tile, which has no
+    // K split to put a second workgroup on a compute unit: 4096 x 13696 at M = 300 165 -> 144 us.  With the K split the
+    // longer start costs more than it gives (fp16 4096 x 13696 at M = 128 29.4 -> 31.4).  With K halves 112 -> 103.
+    constexpr int PD = BF && BM == 64 ? 4 : 2;
+    constexpr int AD = BF && BM == 64 ? 2 : 1;
     constexpr int TM = BM / (32 * WGM), TN = BN / (32 * WGN);      // 32x32 MFMA blocks per wavefront
     constexpr int RP = kThreads / 8;                    // rows covered by one activation loader pass
     constexpr int PA = BM / RP;                         // activation loader passes
@@ -124,6 +129,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_pipe_kernel(const half
     // neighbouring tiles and share operands in its L2; each XCD takes a contiguous run.
     // (even scheduling exists in the instance the launcher uses it with; elsewhere the segment loop below folds away)
     static_assert(!BF || (!FUSED && !E8), "the bfloat16 member has the plain 4-bit kernel only");
+    static_assert(KS == 1 || (KS == 2 && BM == 64 && !FUSED), "K halves inside a workgroup: the flat tile, unfused");
     constexpr bool kSk = !FUSED && !E8 && !BF && BM == 256 && BN == 256;
     const bool sk_on = kSk && sk.enabled;
     const int total = m_tiles * n_tiles * splits;
@@ -162,8 +168,11 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_pipe_kernel(const half
     const int all_tiles = m_tiles * n_tiles;
     const int plain_tile = __builtin_amdgcn_readfirstlane(fu.split_major ? item % all_tiles : item / splits);
     const int plain_split = __builtin_amdgcn_readfirstlane(fu.split_major ? item / all_tiles : item % splits);
-    const int plain_kb = __builtin_amdgcn_readfirstlane(2 * (int)((int64_t)(KT_all / 2) * plain_split / splits));
-    const int plain_ke = __builtin_amdgcn_readfirstlane(2 * (int)((int64_t)(KT_all / 2) * (plain_split + 1) / splits));
+    // (KS = 2: no K split of the launch; the two halves of the workgroup's wavefronts take one half of K each)
+    const int half = KS == 2 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / kThreads) : 0;
+    const int k_part = KS == 2 ? half : plain_split, k_parts = KS == 2 ? 2 : splits;
+    const int plain_kb = __builtin_amdgcn_readfirstlane(2 * (int)((int64_t)(KT_all / 2) * k_part / k_parts));
+    const int plain_ke = __builtin_amdgcn_readfirstlane(2 * (int)((int64_t)(KT_all / 2) * (k_part + 1) / k_parts));
   for (int seg = 0; seg < n_segments; ++seg) {
     if (seg > 0) __syncthreads();                       // every wavefront has left the previous segment's LDS stages
     // what this segment computes: a tile, a range of its K slices, and where the sums go
@@ -237,7 +246,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_pipe_kernel(const half
     // (the thread number is made opaque to the optimiser in every segment: what is derived from it -- loader
     // offsets, epilogue rows and masks -- is then computed where it is used, not ahead of the segment loop, where it
     // would hold registers through the K loop)
-    int t = threadIdx.x;
+    int t = KS == 2 ? (int)threadIdx.x % kThreads : (int)threadIdx.x;
     asm volatile("" : "+v"(t));
     const int lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -290,17 +299,17 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_pipe_kernel(const half
     for (int s = 0; s < 4; ++s)
         frag_off[s] = (uint32_t)((wm + (lane & 31)) * kRowBytes + (((4 * b_h + s) ^ ((lane >> 1) & 7)) << 4));
 
-    u32x4 a_reg[PA];
+    u32x4 a_reg[AD][PA];
     constexpr int NCH = E8 ? 2 : 1;                     // 16-byte chunks per lane, slice and operand block
-    u32x4 bset[2][TN][NCH];
-    uint32_t pwset[2][TN];
+    u32x4 bset[PD][TN][NCH];
+    uint32_t pwset[PD][TN];
     half8_t fa[2][TM], fb[2][TN];
 
-    auto load_a = [&](int kt) {
+    auto load_a = [&](int kt, int set) {
         const uint32_t k0 = (uint32_t)min(kt, KT - 1) * BK;
 #pragma unroll
         for (int p = 0; p < PA; ++p)
-            a_reg[p] = __builtin_amdgcn_raw_buffer_load_b128(a_rsrc, (int)a_pass_off[p], (int)(k0 * 2), 0);
+            a_reg[set][p] = __builtin_amdgcn_raw_buffer_load_b128(a_rsrc, (int)a_pass_off[p], (int)(k0 * 2), 0);
     };
     auto load_b = [&](int kt, int set) {
         const uint32_t k0 = (uint32_t)min(kt, KT - 1) * BK;
@@ -318,10 +327,10 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_pipe_kernel(const half
             pwset[set][j] = __builtin_amdgcn_raw_buffer_load_b32(b_param_rsrc, (int)b_param_off[j], param_soff, 0);
         }
     };
-    auto store_a = [&](uint32_t stage_off) {
+    auto store_a = [&](uint32_t stage_off, int set) {
 #pragma unroll
         for (int p = 0; p < PA; ++p)
-            *reinterpret_cast<u32x4*>(smem + stage_off + a_lds_off + p * RP * kRowBytes) = a_reg[p];
+            *reinterpret_cast<u32x4*>(smem + stage_off + a_lds_off + p * RP * kRowBytes) = a_reg[set][p];
     };
     auto read_frags = [&](uint32_t stage_off, int s, half8_t (&dst)[TM]) {
         const unsigned char* base = smem + stage_off + frag_off[s];
@@ -410,14 +419,14 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_pipe_kernel(const half
     using ITN2 = std::integral_constant<int, (1 + NCH) * TN>;      // loads issued by load_b
 
     // One K slice.  On entry: stage `cur` holds slice kt; fa[0], fb[0] hold its sub-step 0 operands;
-    // bset[set] holds its codes; bset[set^1] and a_reg are in flight for slice kt+1.
+    // bset[set] holds its codes; the next PD - 1 slices' codes and the next AD slices' activations are in flight.
     auto step = [&](int kt, int set, uint32_t cur, uint32_t nxt) {
         // sub-step 0: operands of sub-step 1; publish slice kt+1's activations and, the staging
         // registers being free again, request those of slice kt+2 at once
         read_frags(cur, 1, fa[1]);
         dequant_frags(set, 1, fb[1]);
-        store_a(nxt);
-        load_a(kt + 2);
+        store_a(nxt, (set + 1) % AD);
+        load_a(kt + 1 + AD, (set + 1) % AD);
         mfma_block(fa[0], fb[0]);
         interleave(IPA{}, IPA{});
         __builtin_amdgcn_sched_barrier(0);
@@ -436,33 +445,77 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_pipe_kernel(const half
         interleave(I0{}, I0{});
         __builtin_amdgcn_sched_barrier(0);
         // sub-step 3: operands of the next slice's sub-step 0; this slice's code registers are free,
-        // so the codes of slice kt+2 are requested into them
-        load_b(kt + 2, set);
+        // so the codes of slice kt+PD are requested into them
+        load_b(kt + PD, set);
         read_frags(nxt, 0, fa[0]);
-        dequant_frags(set ^ 1, 0, fb[0]);
+        dequant_frags((set + 1) % PD, 0, fb[0]);
         mfma_block(fa[1], fb[1]);
         interleave(I0{}, ITN2{});
         __builtin_amdgcn_sched_barrier(0);
     };
 
     // ---- prologue
-    load_a(kt_begin);
-    load_b(kt_begin, 0);
-    load_b(kt_begin + 1, 1);
-    store_a(0);
-    load_a(kt_begin + 1);
+    load_a(kt_begin, 0);
+#pragma unroll
+    for (int d = 0; d < PD; ++d) load_b(kt_begin + d, d);
+    const uint32_t ring = KS == 2 ? (uint32_t)half * kStages * kStageBytes : 0u;
+    store_a(ring, 0);
+#pragma unroll
+    for (int d = 1; d <= AD; ++d) load_a(kt_begin + d, d % AD);
     __syncthreads();
-    read_frags(0, 0, fa[0]);
+    read_frags(ring, 0, fa[0]);
     dequant_frags(0, 0, fb[0]);
 
-    uint32_t s0 = 0, s1 = kStageBytes, s2 = 2 * kStageBytes;      // ring: current, next, the one after
-    for (int kt = kt_begin; kt < kt_end; kt += 2) {
-        step(kt, 0, s0, s1);
-        step(kt + 1, 1, s1, s2);
-        const uint32_t tmp = s0;                        // advance the ring by two slices
+    uint32_t s0 = ring, s1 = ring + kStageBytes, s2 = ring + 2 * kStageBytes;     // current, next, the one after
+    auto advance_ring = [&]() {                         // by two slices
+        const uint32_t tmp = s0;
         s0 = s2;
         s2 = s1;
         s1 = tmp;
+    };
+    for (int kt = kt_begin; kt < kt_end; kt += PD) {
+        step(kt, 0, s0, s1);
+        step(kt + 1, 1, s1, s2);
+        advance_ring();
+        if (PD == 4) {                                  // (K ranges are whole pairs of slices)
+            if (kt + 2 >= kt_end) break;
+            step(kt + 2, 2 % PD, s0, s1);
+            step(kt + 3, 3 % PD, s1, s2);
+            advance_ring();
+        }
+    }
+    if (KS == 2) {
+        // The upper half's sums are added to the lower half's, through LDS.  An odd number of pairs of slices gives the
+        // upper half one more, so the lower half waits at the barriers of its last two steps.
+        if (half == 0 && ((KT_all / 2) & 1)) {
+            __syncthreads();
+            __syncthreads();
+        }
+        __syncthreads();                                // every wavefront has left the K loop's stages
+        floatx4* sums = reinterpret_cast<floatx4*>(smem);
+        if (half == 1) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        sums[((i * TN + j) * 4 + q) * kThreads + t] =
+                            floatx4{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+        }
+        __syncthreads();
+        if (half == 0) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const floatx4 v = sums[((i * TN + j) * 4 + q) * kThreads + t];
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) acc[i][j][4 * q + e] += v[e];
+                    }
+        }
     }
 
     // accumulator layout of a 32x32 block: register r of lane l is row 8*(r/4) + 4*(l/32) + r%4, column l%32
@@ -471,7 +524,8 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_pipe_kernel(const half
     // through the K loop: a hundred registers more, and spills in the large tile)
     uint32_t n32 = (uint32_t)N;
     asm volatile("" : "+s"(n32));
-    const int rows_left = (int)min((int64_t)BM, M - m0), cols_left = (int)min((int64_t)BN, N - n0);
+    // (KS = 2: the upper half has no rows to write)
+    const int rows_left = KS == 2 && half == 1 ? 0 : (int)min((int64_t)BM, M - m0), cols_left = (int)min((int64_t)BN, N - n0);
     const int row0 = wm + 4 * (lane >> 5), col0 = wn + (lane & 31);
     const uint32_t off0 = (uint32_t)row0 * n32 + (uint32_t)col0;
     auto store_tile = [&](auto* __restrict__ dst) {     // dst: element (m0, n0) of a row-major [M, N] array
@@ -517,7 +571,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_pipe_kernel(const half
         constexpr int COLS = decltype(cols_c)::value, ROWS = 1024 / COLS, kChunks = TM * 32 / ROWS;
         constexpr int PPR = COLS / 8, RPP = 64 / PPR;   // 16-byte pieces per row, rows per pass (two passes per chunk)
         constexpr int kStride = COLS + 4, NJ = COLS / 32, NR = 16 / NJ;
-        float* turn = reinterpret_cast<float*>(smem + wave * kTurnBytes);
+        float* turn = reinterpret_cast<float*>(smem + (half * WGM * WGN + wave) * kTurnBytes);
         const int prow = lane / PPR, pcol = (lane % PPR) * 8;
         const bool col_ok = wcol + pcol < cols_valid;
         const uint32_t o0 = (uint32_t)(wm + prow) * ld + (uint32_t)(wcol + pcol);
@@ -907,6 +961,18 @@ SkPlan sk_plan(int64_t tiles, int64_t K, int bm, int bn, bool allowed)
     return p;
 }
 
+// Whole flat tiles (the bfloat16 member: no workspace, hence no K split) that leave compute units with one workgroup of four
+// wavefronts or none run as workgroups of eight, whose halves take one half of K each and add their sums in LDS: two
+// wavefronts per SIMD hide each other's waits.  M = 700: 4096 x 13696 (176 tiles) 151 -> 114 us, 4608 x 4096 (198) 50 -> 42;
+// M = 100: 27392 x 4096 (214) 54 -> 44, 4096 x 4096 (32) 46 -> 35.  With more tiles than compute units there are two
+// workgroups per unit anyway, and two of the larger ones do not fit: M = 700, 27392 x 4096 (1177) 205 -> 219.
+bool k_halves(const PipeTile& t, int64_t M, int64_t N, int64_t K)
+{
+    return t.bm == 64 && K >= 4 * BK && ((M + 63) / 64) * ((N + 255) / 256) <= kComputeUnits;
+}
+// (the seven cases above and below within 10 %, for any number of tiles: a compute unit has two wavefronts per SIMD or none)
+constexpr double kHalvesUsPerPair = 1.1;                // us per pair of K slices of the whole K
+
 // Up to 64 rows the flat tile; above, the tile with the shortest estimate.
 // (`sk_allowed`: the launch may use even scheduling; `whole_tiles`: it has no workspace, so neither that nor a K split)
 PipeTile pipe_tile(int64_t M, int64_t N, int64_t K, bool sk_allowed, bool whole_tiles = false)
@@ -917,7 +983,8 @@ PipeTile pipe_tile(int64_t M, int64_t N, int64_t K, bool sk_allowed, bool whole_
     if (v == 2) return kBigTile;
     if (v == 5) return kHalfTile;
     if (M <= kFlatOnlyMaxM || N <= 0 || K < 2 * BK) return kFlatTile;
-    const double flat_us = tile_launch_us(kFlatTile, kFlatCost, M, N, K, whole_tiles);
+    const double flat_us = whole_tiles && k_halves(kFlatTile, M, N, K) ? (double)(K / (2 * BK)) * kHalvesUsPerPair + kFlatCost.b
+                                                                       : tile_launch_us(kFlatTile, kFlatCost, M, N, K, whole_tiles);
     const double half_us = tile_launch_us(kHalfTile, kHalfCost, M, N, K, whole_tiles);
     double big_us = tile_launch_us(kBigTile, kBigCost, M, N, K, whole_tiles);
     const SkPlan skp = sk_plan(((M + 255) / 256) * ((N + 255) / 256), K, 256, 256, sk_allowed && !whole_tiles);
@@ -943,7 +1010,7 @@ int64_t pipe_tiles(const PipeTile& t, int64_t M, int64_t N, bool swiglu)
 }
 
 // (`whole_tiles`: neither a K split nor the even scheduling, hence no workspace)
-template <int G, int WGM, int WGN, bool FUSED, int BM, int BN, bool E8 = false, bool BF = false>
+template <int G, int WGM, int WGN, bool FUSED, int BM, int BN, bool E8 = false, bool BF = false, int KS = 1>
 int launch_pipe(const half_t* x, int64_t M, const uint4* c, int64_t N, int64_t K, half_t* y, void* workspace,
                 size_t workspace_bytes, hipStream_t stream, const Fusion& f, bool whole_tiles = false)
 {
@@ -991,12 +1058,13 @@ int launch_pipe(const half_t* x, int64_t M, const uint4* c, int64_t N, int64_t K
         const int zrc = check_launch();
         if (zrc != E0M4_OK) return zrc;
     }
-    constexpr size_t lds = (size_t)kStages * BM * kRowBytes;       // 96 KiB for the large tile: above the default limit
+    // 96 KiB for the large tile: above the default limit.  (KS = 2: two rings; one half's sums, afterwards.)
+    constexpr size_t lds = std::max((size_t)KS * kStages * BM * kRowBytes, KS == 2 ? (size_t)BM * BN * sizeof(float) : 0);
     static std::atomic<uint64_t> lds_allowed{0};
-    const int arc = allow_dynamic_lds(reinterpret_cast<const void*>(&gemm_pipe_kernel<G, WGM, WGN, FUSED, BM, BN, E8, BF>),
+    const int arc = allow_dynamic_lds(reinterpret_cast<const void*>(&gemm_pipe_kernel<G, WGM, WGN, FUSED, BM, BN, E8, BF, KS>),
                                       (int)lds, lds_allowed);
     if (arc != E0M4_OK) return arc;
-    hipLaunchKernelGGL((gemm_pipe_kernel<G, WGM, WGN, FUSED, BM, BN, E8, BF>), dim3(grid), dim3(64 * WGM * WGN), lds, stream, x,
+    hipLaunchKernelGGL((gemm_pipe_kernel<G, WGM, WGN, FUSED, BM, BN, E8, BF, KS>), dim3(grid), dim3(64 * WGM * WGN * KS), lds, stream, x,
                        M, c, N, K, y, (int)m_tiles, (int)n_tiles, splits, partial, fu, sk);
     int rc = check_launch();
     if (rc != E0M4_OK || splits == 1) return rc;
@@ -1043,6 +1111,10 @@ template <int G, bool FUSED, bool E8 = false, bool BF = false>
 int launch_pipe_as(const PipeTile& t, const half_t* x, int64_t M, const uint4* c, int64_t N, int64_t K, half_t* y,
                    void* workspace, size_t workspace_bytes, hipStream_t stream, const Fusion& f, bool whole_tiles = false)
 {
+    if constexpr (BF) {
+        if (k_halves(t, M, N, K))
+            return launch_pipe<G, 1, 4, FUSED, 64, 256, E8, BF, 2>(x, M, c, N, K, y, workspace, workspace_bytes, stream, f, whole_tiles);
+    }
     if (t.bm == 64)
         return launch_pipe<G, 1, 4, FUSED, 64, 256, E8, BF>(x, M, c, N, K, y, workspace, workspace_bytes, stream, f, whole_tiles);
     if (t.bm == 128 && t.bn == 256)

@@ -132,6 +132,25 @@ def test_bf16_gemm_every_kernel_and_tile(e0m4, oracle, variant, M, N, K, G):
     assert torch.equal(Y.view(torch.int16), Y2.view(torch.int16))
 
 
+@pytest.mark.parametrize("M,N,K,G", [(129, 203, 256, 64), (191, 520, 384, 128), (300, 260, 640, 32), (64, 256, 1152, 128), (257, 16, 4224, 64)])
+def test_bf16_gemm_k_halves(e0m4, oracle, M, N, K, G):
+    # few flat tiles: a workgroup's two halves take one half of K each; even and odd numbers of pairs of K slices, numbers
+    # of pairs that do not fill the unrolled loop, ragged rows and columns, row lengths that are no multiple of 8
+    codes, What, _ = assert_bf16_quantize_exact(e0m4, oracle, synth_inputs.weights_bf16(N, K, seed=3680 + N + K), G)
+    X = synth_inputs.activations_bf16(M, K, seed=3690 + M)
+    e0m4.e0m4_set_knob("gemv_mfma", 5)
+    e0m4.e0m4_set_knob("gemm_variant", 4)
+    try:
+        Y = e0m4.e0m4_bf16_matmul(bf_dev(X), codes, N, K, G)
+        Y2 = e0m4.e0m4_bf16_matmul(bf_dev(X), codes, N, K, G)
+    finally:
+        e0m4.e0m4_set_knob("gemv_mfma", 0)
+        e0m4.e0m4_set_knob("gemm_variant", 0)
+    Yref, absdot = oracle.bf16_matmul(X, What)
+    check_bf16_matmul(oracle, Y, Yref, absdot, "bf16 K halves M=%d N=%d K=%d" % (M, N, K))
+    assert torch.equal(Y.view(torch.int16), Y2.view(torch.int16))
+
+
 def test_bf16_gemm_default_choice_with_many_tiles(e0m4, oracle):
     # 5 x 26 tiles of 64 x 256: enough to fill the chip in whole tiles, so the pipelined kernel is the default;
     # all of N on sampled rows, and one-hot rows that must reproduce the weights through the MFMA path
