@@ -76,7 +76,7 @@ bool use_gemv_mfma(int64_t M, int64_t N, int64_t K, int group)
     return k != 1 && (group == 128 || k == 6) && gemv_mfma_supported(M, N, K, group);
 }
 // The small-batch kernel with dequantised weight operands, for plain matmuls: where it pays; gemv_mfma 4 forces it wherever it
-// can run (2 <= M <= 64), 1 and 5 switch it off, 2, 3 and 6 prefer the kernel above.
+// can run (2 <= M <= 128), 1 and 5 switch it off, 2, 3 and 6 prefer the kernel above.
 bool use_gemv_dq(int64_t M, int64_t N, int64_t K, int group, DqFormat format)
 {
     const int k = knob("gemv_mfma");

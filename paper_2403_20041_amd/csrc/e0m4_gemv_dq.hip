@@ -1,5 +1,5 @@
 // Small-batch path with the weight operand dequantised in registers: Y[M,N] = X[M,K] * dequant(packed)^T for
-// 2 <= M <= 64, any group size, 4-bit codes on fp16 or bfloat16 activations and 8-bit codes on fp16.  Paper: section
+// 2 <= M <= 128, any group size, 4-bit codes on fp16 or bfloat16 activations and 8-bit codes on fp16.  Paper: section
 // "Operator and lagging optimizations" (vector-matrix product of the decoding stage, bound by memory bandwidth) with
 // the dequantisation of section "E0M4 FP4 quantization" fused in registers.
 //
@@ -37,12 +37,14 @@ constexpr int kDqWaves = 8;
 constexpr int kDqThreads = kDqWaves * 64;
 constexpr int kDqMaxR = 4;                      // row blocks per wavefront
 constexpr int kDqMaxSlots = 16;                 // row blocks per workgroup (so that at least two wavefronts share a row block)
-constexpr int kDqMaxM = 64;
+constexpr int kDqMaxM = 64;                     // rows of X per workgroup
+constexpr int kDqMaxParts = 2;
 constexpr int kTargetWorkgroups = 256;          // one workgroup per compute unit
 
 struct DqPlan {
     int64_t grid;
     int rb_base, rb_rem;                        // even deal of row blocks
+    int parts;                                  // of the rows of X
     int wr, r;                                  // groups of wavefronts, row blocks per group
 };
 
@@ -63,7 +65,7 @@ __device__ inline __amdgpu_buffer_rsrc_t rsrc_if(const void* p, bool in)
 
 template <DqFormat FMT, int MT, int R>
 __global__ __launch_bounds__(kDqThreads, 2) void gemv_dq_kernel(const half_t* __restrict__ X, const uint4* __restrict__ packed,
-                                                                half_t* __restrict__ Y, int M, uint32_t N32, uint32_t K32,
+                                                                half_t* __restrict__ Y, int m_total, uint32_t N32, uint32_t K32,
                                                                 int rb_base, int rb_rem, int wk_shift, int group_shift)
 {
     constexpr int NP = FMT == kDqFormatE8 ? 2 : 4;            // pieces of X (and MFMAs) per k block
@@ -74,6 +76,11 @@ __global__ __launch_bounds__(kDqThreads, 2) void gemv_dq_kernel(const half_t* __
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int64_t N = N32;
     const int K = (int)K32;
+    // (more than 64 rows: equal parts of them in the y dimension of the grid)
+    const int m_part = (m_total + (int)gridDim.y - 1) / (int)gridDim.y, m0 = (int)blockIdx.y * m_part;
+    const int M = min(m_part, m_total - m0);
+    X += (int64_t)m0 * K;
+    Y += (int64_t)m0 * N;
     const int nkb = (K + BLK - 1) / BLK;
     const int pw = kBlockRows << (7 - group_shift);     // parameter words per k block (8-bit codes: 16)
     const uint32_t rb_stride = (uint32_t)nkb * (uint32_t)(kBlockCodeBytes + 4 * pw);
@@ -265,7 +272,8 @@ __global__ __launch_bounds__(kDqThreads, 2) void gemv_dq_kernel(const half_t* __
 // than 256 x 16 of them, as few whole rounds as possible.
 bool make_dq_plan(int64_t M, int64_t N, int64_t K, DqPlan& p)
 {
-    if (M < 2 || M > kDqMaxM || N <= 0 || K <= 0) return false;
+    if (M < 2 || M > kDqMaxParts * kDqMaxM || N <= 0 || K <= 0) return false;
+    p.parts = M > kDqMaxM ? kDqMaxParts : 1;
     const int64_t nrb = row_blocks(N);
     int target = knob("gemv_workgroups");
     if (target <= 0) target = kTargetWorkgroups;
@@ -291,7 +299,7 @@ int launch_dq(const DqPlan& p, const void* X, int64_t M, const void* packed, int
     int wk_shift = 0;                                   // log2 of the wavefronts in a group
     while ((p.wr << (wk_shift + 1)) <= kDqWaves) ++wk_shift;
     const int group_shift = FMT == kDqFormatE8 || group == 128 ? 7 : group == 64 ? 6 : 5;
-    hipLaunchKernelGGL((gemv_dq_kernel<FMT, MT, R>), dim3((unsigned)p.grid), dim3(kDqWaves * 64), lds, stream,
+    hipLaunchKernelGGL((gemv_dq_kernel<FMT, MT, R>), dim3((unsigned)p.grid, (unsigned)p.parts), dim3(kDqThreads), lds, stream,
                        static_cast<const half_t*>(X), static_cast<const uint4*>(packed), static_cast<half_t*>(Y), (int)M,
                        (uint32_t)N, (uint32_t)K, p.rb_base, p.rb_rem, wk_shift, group_shift);
     return check_launch();
@@ -314,7 +322,7 @@ template <DqFormat FMT>
 int launch_dq_m(const DqPlan& p, const void* X, int64_t M, const void* packed, int64_t N, int64_t K,
                 int group, void* Y, hipStream_t stream)
 {
-    switch ((M + 15) / 16) {
+    switch (((M + p.parts - 1) / p.parts + 15) / 16) {
         case 1: return launch_dq_r<FMT, 1>(p, X, M, packed, N, K, group, Y, stream);
         case 2: return launch_dq_r<FMT, 2>(p, X, M, packed, N, K, group, Y, stream);
         case 3: return launch_dq_r<FMT, 3>(p, X, M, packed, N, K, group, Y, stream);
@@ -334,7 +342,10 @@ bool gemv_dq_supported(int64_t M, int64_t N, int64_t K, int group)
 
 // Where this kernel is the faster one; 2400 timings on random problems (M = 2 ... 64, N = 1500 ... 40000, K = 1536 ... 16384,
 // cold weights, in a graph), quoted as the time of the kernel it replaces over its own.
-//   bfloat16: from 3 rows on, always (the vector kernel and the GEMM in whole tiles: 1.1 - 12; at 2 rows 0.90 - 1.07).
+//   bfloat16: from 3 rows on, always (the vector kernel and the GEMM in whole tiles: 1.1 - 12; at 2 rows 0.90 - 1.07).  65 to
+//     128 rows in two parts, against the GEMM's 64 x 256 tiles with K halves, where a workgroup has few row blocks: at M =
+//     100 4096 x 4096 35 -> 22 us, 4096 x 13696 103 -> 56, but 32768 x 2048 (8 row blocks) 27 -> 37, 27392 x 4096 44 -> 67;
+//     three parts are no faster (4096 x 4096 at M = 192 38).
 //   Groups of 32 and 64: from 3 rows on up to 16, always (0.97 - 1.8).
 //   Group 128 and 8-bit codes up to 16 rows, against the kernel that stages X in LDS once per workgroup: that one costs a
 //     compute unit M K bytes of staging before its first product, this one more arithmetic per weight.  From 9 rows on
@@ -349,8 +360,9 @@ bool gemv_dq_pays(int64_t M, int64_t N, int64_t K, int group, DqFormat format)
     if (M < 3 || !make_dq_plan(M, N, K, p)) return false;
     // (what the GEMM refuses stays refused: more than 2^24 columns, 8-bit rows that are not a multiple of 128 long unless the
     // weights are small)
-    if (format == kDqFormatBf16) return M <= 8 || N <= (int64_t)1 << 24;
     const double NK = (double)N * (double)K;
+    if (format == kDqFormatBf16) return M <= 8 || (N <= (int64_t)1 << 24 && (M <= kDqMaxM || (NK <= 7e7 && p.wr * p.r <= 2)));
+    if (M > kDqMaxM) return false;
     if (format == kDqFormatE8 && M > 16 && K % 128 != 0 && !(M <= 32 && K <= 2048 && NK <= 1e7)) return false;
     if (M > 16) return NK <= (format == kDqFormatE8 ? 1e8 : 7e7) && (M <= 48 || K <= 9216);
     if (format == kDqFormatFp16 && group != 128) return true;

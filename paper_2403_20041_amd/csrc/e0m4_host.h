@@ -77,7 +77,7 @@ bool gemv_mfma8_whole_rows(const Fusion& f, int64_t M, int64_t N, int64_t K);
 // (`chunks` > 1: M (17 ... 64) rows in that many equal chunks of at most 16 rows, dealt to the y dimension of one launch)
 int launch_gemv_mfma_fused(const Fusion& f, const void* X, int64_t M, const void* packed, int64_t N, int64_t K, void* Y,
                            hipStream_t stream, int chunks = 1, int group = 128);
-// Small-batch path with the weight operand dequantised in registers: 2 <= M <= 64, any group (e0m4_gemv_dq.hip).
+// Small-batch path with the weight operand dequantised in registers: 2 <= M <= 128, any group (e0m4_gemv_dq.hip).
 // (`pays`: it is expected to beat the other kernels)
 enum DqFormat { kDqFormatFp16 = 0, kDqFormatE8 = 1, kDqFormatBf16 = 2 };     // 4-bit codes, 8-bit codes, 4-bit codes on bfloat16
 bool gemv_dq_supported(int64_t M, int64_t N, int64_t K, int group);

@@ -1,4 +1,4 @@
-"""The small-batch kernel with dequantised weight operands (plain matmuls, 2 <= M <= 64) against the CPU oracle, in the three
+"""The small-batch kernel with dequantised weight operands (plain matmuls, 2 <= M <= 128) against the CPU oracle, in the three
 formats it serves: last tiles of 16 rows of X and 16 weight rows, k blocks that K does not fill, fewer k blocks than
 wavefronts and remainders of the unrolled loop, one to sixteen row blocks per workgroup."""
 import numpy as np
@@ -17,7 +17,7 @@ SHAPES = [(17, 128, 64, 0), (203, 1152, 64, 0), (333, 2176, 128, 12), (520, 1664
 
 @pytest.mark.parametrize("fmt", ["e0m4", "e0m8", "bf16"])
 @pytest.mark.parametrize("N,K,G,workgroups", SHAPES + [(203, 416, 32, 3), (48, 96, 32, 0)])
-@pytest.mark.parametrize("M", [2, 9, 16, 17, 33, 48, 64])
+@pytest.mark.parametrize("M", [2, 9, 16, 17, 33, 48, 64, 65, 127])
 def test_forced(e0m4, oracle, fmt, N, K, G, workgroups, M):
     if fmt == "e0m8" and G == 32:
         pytest.skip("8-bit codes have groups of 64 and 128")
