@@ -139,6 +139,46 @@ __device__ inline uint32_t frac_mask_low_vgpr()
     return m;
 }
 
+// Quotients by one divisor, correctly rounded like w / d: with r the correctly rounded reciprocal and q0 = r w, the remainder
+// w - q0 d is exact and q0 + r (w - q0 d), rounded once, is the rounded quotient (Markstein, "Computation of elementary
+// functions on the IBM RISC System/6000 processor", 1990), as long as nothing leaves the normal range: fp16 numerators and
+// normal fp16 divisors stay between 2^-65 and 2^31.  An infinite or not-a-number numerator gives what it divides to.
+struct Divisor {
+    float d, r;
+};
+__device__ inline Divisor make_divisor(float d) { return Divisor{d, 1.0f / d}; }
+__device__ inline float quotient(float w, const Divisor& v)
+{
+    const float q0 = w * v.r;
+    const float q = __builtin_fmaf(__builtin_fmaf(-q0, v.d, w), v.r, q0);
+    return q == q ? q : q0;
+}
+
+// Smallest and largest value of LANES (4, 8 or 16) neighbouring lanes, in all of them; the pattern reaches the neighbour, the
+// other pair of a quad, the other quad and the other eight.
+template <int CTRL>
+__device__ inline float other_lane(float v)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
+}
+template <int LANES>
+__device__ inline void group_range(float& mn, float& mx)
+{
+    static_assert(LANES == 4 || LANES == 8 || LANES == 16, "lanes of a group");
+    mn = fminf(mn, other_lane<0xB1>(mn));
+    mx = fmaxf(mx, other_lane<0xB1>(mx));
+    mn = fminf(mn, other_lane<0x4E>(mn));
+    mx = fmaxf(mx, other_lane<0x4E>(mx));
+    if (LANES >= 8) {
+        mn = fminf(mn, other_lane<0x141>(mn));
+        mx = fmaxf(mx, other_lane<0x141>(mx));
+    }
+    if (LANES == 16) {
+        mn = fminf(mn, other_lane<0x140>(mn));
+        mx = fmaxf(mx, other_lane<0x140>(mx));
+    }
+}
+
 // Buffer resource over [p, p + 2 GiB): raw (stride 0), 32-bit data format word of gfx9-class targets.
 // p must be wavefront-uniform; passing its halves through readfirstlane pins the resource to scalar
 // registers (otherwise every buffer load is wrapped in a per-lane "waterfall" loop).

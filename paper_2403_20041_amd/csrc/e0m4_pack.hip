@@ -26,24 +26,23 @@ __device__ inline half_t bits_half(uint16_t b) { return __builtin_bit_cast(half_
 
 // code = min(y1 + y2, 15): y1 = four highest fraction bits of the mapped fp16
 // value, y2 = the bit below them (paper: quantization paragraph).
-__device__ inline uint32_t encode_value(float w0, float sf, float bf)
+// (y1 + y2 is the five bits above bit 5, plus one, halved; every value here lies in [2, 4))
+__device__ inline uint32_t encode_value(float w0, const Divisor& sf, float bf)
 {
-    float q = w0 / sf;
+    float q = quotient(w0, sf);
     float t = q + bf;
     t = t < kLo ? kLo : t;
     t = t > kHi ? kHi : t;
-    uint32_t bits = half_bits((half_t)t);
-    uint32_t y1 = (bits >> 6) & 15u;
-    uint32_t y2 = (bits >> 5) & 1u;
-    uint32_t c = y1 + y2;
+    const uint32_t bits = half_bits((half_t)t);
+    const uint32_t c = (((bits >> 5) & 31u) + 1u) >> 1;
     return c > 15u ? 15u : c;
 }
 
 // INT4 comparison format (paper: section "Evaluation of FP4 quantization"): q = clamp(rne(w / scale)
 // + zero, 0, 15) with an integer zero point kept as an fp16 number.
-__device__ inline uint32_t encode_value_int4(float w0, float sf, float zf)
+__device__ inline uint32_t encode_value_int4(float w0, const Divisor& sf, float zf)
 {
-    float q = w0 / sf;
+    float q = quotient(w0, sf);
     float t = rintf(q) + zf;
     t = t < 0.0f ? 0.0f : t;
     t = t > 15.0f ? 15.0f : t;
@@ -72,13 +71,13 @@ __device__ inline uint16_t float_to_bf16_bits(float f)
 
 // The general form of encode_value: CODE_SHIFT = fraction bits below the code, TOP = largest code.
 template <int FMT>
-__device__ inline uint32_t encode_value_fmt(float w0, float sf, float bf)
+__device__ inline uint32_t encode_value_fmt(float w0, const Divisor& sf, float bf)
 {
     constexpr bool BF = FMT == kBf16;
     constexpr int SHIFT = BF ? 3 : (FMT == kE0M3 ? 7 : 6);
     constexpr uint32_t TOP = FMT == kE0M3 ? 7u : 15u;
     const float hi = BF ? kHiBf16 : kHi;
-    float q = w0 / sf;
+    const float q = quotient(w0, sf);
     float t = q + bf;
     t = t < kLo ? kLo : t;
     t = t > hi ? hi : t;
@@ -125,7 +124,8 @@ __global__ __launch_bounds__(kThreads) void quantize_kernel(const half_t* __rest
 #pragma unroll
         for (int j = 0; j < 8; ++j) v[j] = BF ? bf16_bits_to_float(half_bits(v8[j])) : (float)v8[j];
 
-        float sf, bf;
+        Divisor sf;
+        float bf;
         half_t sh, bh;                                  // 16-bit patterns of the group's parameters (fp16, or bfloat16)
         if (FIT) {
             float mn = 0.0f, mx = 0.0f;                 // the range always contains 0
@@ -134,18 +134,14 @@ __global__ __launch_bounds__(kThreads) void quantize_kernel(const half_t* __rest
                 mn = fminf(mn, v[j]);
                 mx = fmaxf(mx, v[j]);
             }
-#pragma unroll
-            for (int d = G / 16; d >= 1; d >>= 1) {     // G/8 adjacent lanes form the group
-                mn = fminf(mn, __shfl_xor(mn, d));
-                mx = fmaxf(mx, __shfl_xor(mx, d));
-            }
+            group_range<G / 8>(mn, mx);                 // G/8 adjacent lanes form the group
             float range = mx - mn;
             float s = range / (FMT == kInt4 ? 15.0f : (BF ? kSpanBf16 : kSpan));
             s = s < (BF ? kMinScaleBf16 : kMinScale) ? (BF ? kMinScaleBf16 : kMinScale) : s;
             s = s > (BF ? kMaxScaleBf16 : kMaxScale) ? (BF ? kMaxScaleBf16 : kMaxScale) : s;
             sh = BF ? bits_half(float_to_bf16_bits(s)) : (half_t)s;
-            sf = BF ? bf16_bits_to_float(half_bits(sh)) : (float)sh;     // encode with the stored scale
-            float q = mn / sf;
+            sf = make_divisor(BF ? bf16_bits_to_float(half_bits(sh)) : (float)sh);       // encode with the stored scale
+            const float q = BF ? mn / sf.d : quotient(mn, sf);
             if (BF) {
                 float b = kLo - q;
                 b = b < kLo ? kLo : b;
@@ -175,12 +171,22 @@ __global__ __launch_bounds__(kThreads) void quantize_kernel(const half_t* __rest
                 sh = scales_in[n * ng + g];
                 bh = bias_in[n * ng + g];
             }
-            sf = BF ? bf16_bits_to_float(half_bits(sh)) : (float)sh;
+            sf = make_divisor(BF ? bf16_bits_to_float(half_bits(sh)) : (float)sh);
             bf = BF ? bf16_bits_to_float(half_bits(bh)) : (float)bh;
         }
 
         uint32_t word = 0;
-        if (ok) {
+        // bfloat16: with a scale between 2^-60 and 2^60 a quotient of 2^-40 or more keeps its remainder in the normal range,
+        // and a smaller one vanishes against the bias; other scales divide
+        const bool divide = BF && !(sf.d >= 0x1p-60f && sf.d <= 0x1p60f);
+        if (ok && divide) {
+#pragma unroll 1
+            for (int j = 0; j < 8; ++j) {
+                const float w0 = bf16_bits_to_float(half_bits(v8[j]));
+                const Divisor one{1.0f, 1.0f};
+                word |= place_code(encode_value_fmt<kBf16>(w0 / sf.d, one, bf), j);
+            }
+        } else if (ok) {
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 uint32_t c;

@@ -33,14 +33,14 @@ constexpr int kBlockK8 = 64;            // weights per block
 __device__ inline uint16_t half_bits(half_t h) { return __builtin_bit_cast(uint16_t, h); }
 __device__ inline half_t bits_half(uint16_t b) { return __builtin_bit_cast(half_t, b); }
 
-__device__ inline uint32_t encode8(float w0, float sf, float bf)
+__device__ inline uint32_t encode8(float w0, const Divisor& sf, float bf)
 {
-    float q = w0 / sf;
+    float q = quotient(w0, sf);
     float t = q + bf;
     t = t < kLo ? kLo : t;
     t = t > kHi ? kHi : t;
     const uint32_t bits = half_bits((half_t)t);
-    const uint32_t c = ((bits >> 2) & 255u) + ((bits >> 1) & 1u);
+    const uint32_t c = (((bits >> 1) & 511u) + 1u) >> 1;        // the eight bits and the one below, for rounding
     return c > 255u ? 255u : c;
 }
 
@@ -92,17 +92,13 @@ __global__ __launch_bounds__(kThreads) void quantize8_kernel(const half_t* __res
             mn = fminf(mn, v[j]);
             mx = fmaxf(mx, v[j]);
         }
-#pragma unroll
-        for (int d = G / 16; d >= 1; d >>= 1) {
-            mn = fminf(mn, __shfl_xor(mn, d));
-            mx = fmaxf(mx, __shfl_xor(mx, d));
-        }
+        group_range<G / 8>(mn, mx);
         float s = (mx - mn) / kSpan;
         s = s < kMinScale ? kMinScale : s;
         s = s > kMaxScale ? kMaxScale : s;
         const half_t sh = (half_t)s;
-        const float sf = (float)sh;                     // encode with the stored scale
-        float b = kLo - mn / sf;                        // image of zero in the binade
+        const Divisor sf = make_divisor((float)sh);     // encode with the stored scale
+        float b = kLo - quotient(mn, sf);                        // image of zero in the binade
         b = b < kLo ? kLo : b;
         b = b > kHi ? kHi : b;
         const half_t bh = bits_half(half_bits((half_t)b) & 0xFFFCu);    // keep the eight highest fraction bits

@@ -694,3 +694,50 @@ def test_small_batch_dequantised_operands_few_workgroups(e0m4, oracle):
             e0m4.e0m4_set_knob("gemv_mfma", 0)
             e0m4.e0m4_set_knob("gemv_workgroups", 0)
         check_matmul(Y, Yref, absdot, "dq target=%d" % target)
+
+
+# ------------------------------------------------------------------ quotients of the quantiser
+
+@pytest.mark.parametrize("fmt", ["e0m4", "e0m3", "e0m8", "int4"])
+def test_quantize_every_fp16_numerator(e0m4, oracle, fmt):
+    """All finite fp16 values as weights, in groups whose scales run over many mantissas: the quotients, computed through
+    the scale's reciprocal, have to be the rounded ones wherever a code depends on it."""
+    G = 64
+    values = np.arange(1 << 16, dtype=np.uint32).astype(np.uint16).view(np.float16)
+    values = values[np.isfinite(values)]
+    rng = np.random.default_rng(77)
+    rows = []
+    for kind in range(3):                               # neighbours in value together, at random, and scaled down
+        v = np.sort(values) if kind == 0 else rng.permutation(values)
+        if kind == 2:
+            v = (v.astype(np.float32) * np.float32(2.0 ** -11)).astype(np.float16)
+        rows.append(np.resize(v, (64, 1024)))
+    W = np.concatenate(rows)
+    with np.errstate(over="ignore"):
+        if fmt == "int4":
+            codes, scales, zeros = e0m4.e0m4_int4_quantize(to_dev(W), G)
+            oc, os_, oz = oracle.int4_quantize(W, G)
+            assert np.array_equal(bits(zeros), oz.view(np.uint16))
+        else:
+            quantize = {"e0m4": e0m4.e0m4_quantize, "e0m3": e0m4.e0m3_quantize, "e0m8": e0m4.e0m8_quantize}[fmt]
+            codes, scales, bias = quantize(to_dev(W), G)
+            oc, os_, ob = oracle.quantize(W, G) if fmt == "e0m4" else oracle.quantize_k(W, G, 3 if fmt == "e0m3" else 8)
+            assert np.array_equal(bits(bias), ob.view(np.uint16))
+    unpack = {"e0m3": e0m4.e0m3_unpack_codes, "e0m8": e0m4.e0m8_unpack_codes}.get(fmt, e0m4.e0m4_unpack_codes)
+    assert np.array_equal(bits(scales), os_.view(np.uint16))
+    assert np.array_equal(bits(unpack(codes, W.shape[0], W.shape[1], G)), oc)
+
+
+def test_encode_with_extreme_scales(e0m4, oracle):
+    # given scales of any size, subnormal ones among them, and infinite weights
+    N, K, G = 64, 512, 32
+    rng = np.random.default_rng(78)
+    W = (rng.standard_normal((N, K)) * 4.0 ** rng.integers(-8, 8, (N, 1))).astype(np.float16)
+    W[3, 5], W[4, 70], W[5, 200:220] = np.inf, -np.inf, np.inf
+    scales = (2.0 ** rng.uniform(-24, 15, (N, K // G))).astype(np.float16)
+    bias = np.full((N, K // G), 2.5, dtype=np.float16)
+    codes = e0m4.e0m4_encode(to_dev(W), to_dev(scales), to_dev(bias), G)
+    q = W.astype(np.float32) / np.repeat(scales.astype(np.float32), G, axis=1) + np.float32(2.5)
+    t = np.clip(q, np.float32(2.0), np.float32(3.998046875)).astype(np.float16).view(np.uint16)
+    want = np.minimum(((t >> 6) & 15) + ((t >> 5) & 1), 15)
+    assert np.array_equal(bits(e0m4.e0m4_unpack_codes(codes, N, K, G)), want.astype(np.uint8))
