@@ -108,8 +108,15 @@ def lib() -> ctypes.CDLL:
     return L
 
 
+# The handle of the current device's current stream, without the Stream object that torch.cuda.current_stream() makes.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream(stream) -> int:
     if stream is None:
+        if _raw_stream is not None and _current_device is not None:
+            return _raw_stream(_current_device())
         stream = torch.cuda.current_stream()
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
@@ -140,7 +147,7 @@ def _check(rc: int, where: str):
 
 
 def _need(t: torch.Tensor, dtype, shape, name: str):
-    if t.dtype != dtype or tuple(t.shape) != tuple(shape) or not t.is_contiguous() or not t.is_cuda:
+    if t.dtype != dtype or t.shape != shape or not t.is_contiguous() or not t.is_cuda:
         raise ValueError("%s must be a contiguous cuda %s tensor of shape %s, got %s %s on %s"
                          % (name, dtype, tuple(shape), t.dtype, tuple(t.shape), t.device))
 
@@ -214,10 +221,13 @@ def e0m4_matmul(X, codes, scales, bias, N: int, K: int, group: int, out=None, wo
     _need(X, torch.float16, (M, K), "X")
     if out is None:
         out = _empty((M, N), torch.float16, X.device, stream, "out")
-    _need(out, torch.float16, (M, N), "out")
-    need = e0m4_workspace_bytes(M, N, K, group)
-    if workspace is None and need > 0:
-        workspace = _empty(need, torch.uint8, X.device, stream, "workspace")
+    else:
+        _need(out, torch.float16, (M, N), "out")
+    # (one row never needs a workspace; two or more may)
+    if workspace is None and M > 1:
+        need = e0m4_workspace_bytes(M, N, K, group)
+        if need > 0:
+            workspace = _empty(need, torch.uint8, X.device, stream, "workspace")
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     _check(lib().e0m4_matmul(_ptr(X), M, _ptr(codes), _ptr(scales), _ptr(bias), N, K, group, _ptr(out),
                              _ptr(workspace), ws_bytes, _stream(stream)), "e0m4_matmul")
@@ -259,7 +269,8 @@ def e0m4_matmul_fused(X, codes, N: int, K: int, group: int, rms_gamma=None, rms_
         _need(residual, torch.float16, (M, n_out), "residual")
     if out is None:
         out = _empty((M, n_out), torch.float16, X.device, stream, "out")
-    _need(out, torch.float16, (M, n_out), "out")
+    else:
+        _need(out, torch.float16, (M, n_out), "out")
     need = e0m4_fused_workspace_bytes(M, N, K, group, rms_gamma is not None, epilogue)
     if workspace is None and need > 0:
         workspace = _empty(need, torch.uint8, X.device, stream, "workspace")
@@ -330,7 +341,8 @@ def e0m8_matmul(X, codes, N: int, K: int, group: int, out=None, workspace=None, 
     _need(X, torch.float16, (M, K), "X")
     if out is None:
         out = _empty((M, N), torch.float16, X.device, stream, "out")
-    _need(out, torch.float16, (M, N), "out")
+    else:
+        _need(out, torch.float16, (M, N), "out")
     need = e0m8_workspace_bytes(M, N, K, group)
     if workspace is None and need > 0:
         workspace = _empty(need, torch.uint8, X.device, stream, "workspace")
@@ -352,7 +364,8 @@ def e0m8_matmul_fused(X, codes, N: int, K: int, group: int, rms_gamma=None, rms_
         _need(residual, torch.float16, (M, n_out), "residual")
     if out is None:
         out = _empty((M, n_out), torch.float16, X.device, stream, "out")
-    _need(out, torch.float16, (M, n_out), "out")
+    else:
+        _need(out, torch.float16, (M, n_out), "out")
     need = lib().e0m8_fused_workspace_bytes(M, N, K, group, 1 if rms_gamma is not None else 0, epilogue)
     if workspace is None and need > 0:
         workspace = _empty(need, torch.uint8, X.device, stream, "workspace")
@@ -448,6 +461,7 @@ def e0m4_bf16_matmul(X, codes, N: int, K: int, group: int, out=None, stream=None
     _need(X, torch.bfloat16, (M, K), "X")
     if out is None:
         out = _empty((M, N), torch.bfloat16, X.device, stream, "out")
-    _need(out, torch.bfloat16, (M, N), "out")
+    else:
+        _need(out, torch.bfloat16, (M, N), "out")
     _check(lib().e0m4_bf16_matmul(_ptr(X), M, _ptr(codes), N, K, group, _ptr(out), _stream(stream)), "e0m4_bf16_matmul")
     return out
