@@ -139,6 +139,19 @@ __device__ inline uint32_t frac_mask_low_vgpr()
     return m;
 }
 
+// Grid of the kernels that walk a row-major matrix in tiles: eight strips of tile rows side by side, column after column, so
+// that each XCD (workgroup b runs on XCD b % 8) walks along one strip: what neighbouring tiles write to the same cache line,
+// the two-byte parameters above all, meets in one L2.  Groups of strips in y and, beyond what y holds, z.  27392 x 4096
+// quantised and dequantised at group 128 in 124 us, 143 with tile rows in x; 8-bit codes of 8000 x 11008 in 70, 80.
+constexpr unsigned kTileGridY = 32768, kTileStrips = 8;
+__host__ inline dim3 tile_grid(int64_t tile_rows, int64_t tile_cols)
+{
+    const int64_t y = (tile_rows + kTileStrips - 1) / kTileStrips, z = (y + kTileGridY - 1) / kTileGridY;
+    return dim3((unsigned)tile_cols * kTileStrips, (unsigned)(z > 1 ? kTileGridY : y), (unsigned)z);
+}
+__device__ inline int64_t tile_row() { return ((int64_t)blockIdx.z * kTileGridY + blockIdx.y) * kTileStrips + blockIdx.x % kTileStrips; }
+__device__ inline int64_t tile_col() { return blockIdx.x / kTileStrips; }
+
 // Quotients by one divisor, correctly rounded like w / d: with r the correctly rounded reciprocal and q0 = r w, the remainder
 // w - q0 d is exact and q0 + r (w - q0 d), rounded once, is the rounded quotient (Markstein, "Computation of elementary
 // functions on the IBM RISC System/6000 processor", 1990), as long as nothing leaves the normal range: fp16 numerators and

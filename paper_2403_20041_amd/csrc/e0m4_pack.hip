@@ -104,8 +104,8 @@ __global__ __launch_bounds__(kThreads) void quantize_kernel(const half_t* __rest
     constexpr int PPB = block_bytes(G) / 16;            // 16-byte pieces per block
     __shared__ __attribute__((aligned(16))) uint32_t stage[4 * BW];
     const int t = threadIdx.x;
-    const int64_t rb64 = blockIdx.x;
-    const int64_t kb = blockIdx.y;
+    const int64_t rb64 = tile_row();
+    const int64_t kb = tile_col();
     const int piece = t & 15;
     const int r = t >> 4;
     const int64_t k = kb * kBlockK + piece * 8;
@@ -227,8 +227,8 @@ __global__ __launch_bounds__(kThreads) void dequant_kernel(const uint4* __restri
     constexpr int kStride = kBlockK + 8;                // halves; +16 bytes keeps ds_write_b128 conflict-free
     __shared__ __attribute__((aligned(16))) half_t tile[kTileRows * kStride];
     const int t = threadIdx.x;
-    const int64_t rb64 = blockIdx.x;
-    const int64_t kb = blockIdx.y;
+    const int64_t rb64 = tile_row();
+    const int64_t kb = tile_col();
     const int64_t nrb = row_blocks(N);
     const PackedLayout<G> lay(K);
     {
@@ -286,8 +286,8 @@ __global__ __launch_bounds__(kThreads) void unpack_kernel(const uint4* __restric
     constexpr int kStride = kBlockK + 16;               // bytes per row in LDS
     __shared__ __attribute__((aligned(16))) uint8_t tile[kTileRows * kStride];
     const int t = threadIdx.x;
-    const int64_t rb64 = blockIdx.x;
-    const int64_t kb = blockIdx.y;
+    const int64_t rb64 = tile_row();
+    const int64_t kb = tile_col();
     const int64_t nrb = row_blocks(N);
     const PackedLayout<G> lay(K);
     {
@@ -321,18 +321,13 @@ __global__ __launch_bounds__(kThreads) void unpack_kernel(const uint4* __restric
     }
 }
 
-dim3 tile_grid(int64_t N, int64_t K)
-{
-    return dim3((unsigned)((N + kTileRows - 1) / kTileRows), (unsigned)k_blocks(K), 1);
-}
-
 }  // namespace
 
 int launch_quantize(const void* W, int64_t N, int64_t K, int group, void* packed, void* scales, void* bias,
                     const void* scales_in, const void* bias_in, bool fit, int format, hipStream_t stream)
 {
     const bool int4 = format == kInt4;
-    const dim3 grid = tile_grid(N, K), block(kThreads);
+    const dim3 grid = tile_grid((N + kTileRows - 1) / kTileRows, k_blocks(K)), block(kThreads);
     const half_t* w = static_cast<const half_t*>(W);
     uint4* c = static_cast<uint4*>(packed);
     half_t* so = static_cast<half_t*>(scales);
@@ -360,7 +355,7 @@ int launch_quantize(const void* W, int64_t N, int64_t K, int group, void* packed
 
 int launch_dequant(const void* packed, int64_t N, int64_t K, int group, void* W_out, int format, hipStream_t stream)
 {
-    const dim3 grid = tile_grid(N, K), block(kThreads);
+    const dim3 grid = tile_grid((N + kTileRows - 1) / kTileRows, k_blocks(K)), block(kThreads);
     const uint4* c = static_cast<const uint4*>(packed);
     half_t* o = static_cast<half_t*>(W_out);
     const bool int4 = format == kInt4;
@@ -393,7 +388,7 @@ int launch_dequant(const void* packed, int64_t N, int64_t K, int group, void* W_
 
 int launch_unpack(const void* packed, int64_t N, int64_t K, int group, void* out, hipStream_t stream, int shift)
 {
-    const dim3 grid = tile_grid(N, K), block(kThreads);
+    const dim3 grid = tile_grid((N + kTileRows - 1) / kTileRows, k_blocks(K)), block(kThreads);
     const uint4* c = static_cast<const uint4*>(packed);
     uint8_t* o = static_cast<uint8_t*>(out);
     switch (group) {

@@ -68,8 +68,8 @@ __global__ __launch_bounds__(kThreads) void quantize8_kernel(const half_t* __res
     constexpr int PPB = block_bytes(128) / 16;
     __shared__ __attribute__((aligned(16))) uint32_t stage[8 * BW];     // [row block i][block half h]
     const int t = threadIdx.x;
-    const int64_t rb64 = blockIdx.x;
-    const int64_t kb2 = blockIdx.y;                     // pair of blocks
+    const int64_t rb64 = tile_row();
+    const int64_t kb2 = tile_col();                     // pair of blocks
     const int piece = t & 15, r = t >> 4;
     const int h = piece >> 3, p8 = piece & 7;           // block of the pair, piece inside the block
     const int q = p8 >> 1, w0 = (p8 & 1) * 2;           // chunk, first of the two words
@@ -168,7 +168,7 @@ __global__ __launch_bounds__(kThreads) void dequant8_kernel(const uint4* __restr
 int launch_quantize8(const void* W, int64_t N, int64_t K, int group, void* packed, void* scales, void* bias,
                      hipStream_t stream)
 {
-    const dim3 grid((unsigned)((N + 63) / 64), (unsigned)((K + 127) / 128)), block(kThreads);
+    const dim3 grid = tile_grid((N + 63) / 64, (K + 127) / 128), block(kThreads);
     const half_t* w = static_cast<const half_t*>(W);
     uint4* c = static_cast<uint4*>(packed);
     half_t* so = static_cast<half_t*>(scales);
