@@ -38,6 +38,7 @@
 #include "e0m4_host.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace e0m4 {
 
@@ -229,7 +230,8 @@ __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restr
     // The pieces (one per lane and row of X) stay in registers until the row scales are known.
     constexpr int kItemPieces = kSuper * XBB / 16;      // pieces of one row of X per work item: 64 (32 for 8-bit codes)
     // (not with sixteen wavefronts: 64 more registers do not fit their budget of 128)
-    const bool own_norm = W <= 8 && normed && XREG && step_slots == 1;
+    constexpr bool kOwn = W <= 8 && XREG && E8, kKeep = W <= 8 && FUSED && !PHASED && GS == 1 && !kOwn, kKeepTwo = kKeep && !XREG;
+    const bool own_norm = kOwn && normed && step_slots == 1;
     const int pc_own = si * kItemPieces + lane;
     const bool own_ok = lane < kItemPieces && pc_own < pieces;      // (a last work item may reach beyond the row's blocks)
     half8_t keep[kMaxM], g_own = zero8;
@@ -265,7 +267,59 @@ __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restr
             }
         }
     }
-    if (normed && !own_norm) {
+    // Otherwise, with at most sixteen pieces per thread -- one per row of X, or two of up to eight rows -- every thread keeps
+    // its pieces from the first pass, and X is read once: 4608 x 4096 in 8-bit codes at M = 16 17.0 -> 14.7 us, gated 27392 x
+    // 4096 36.5 -> 33.2; 15360 x 5120 at M = 8 18.4 -> 16.6.  (Not with K in phases or several groups per block, where it
+    // gained nothing.)  4-bit codes with XREG and step_slots == 1: thread t's piece is one of its own wavefront's four blocks.
+    const bool keep_norm = kKeep && normed && (cpr == 1 || (kKeepTwo && cpr == 2 && M <= 8));
+    const bool keep_own = XREG && step_slots == 1;
+    half8_t g_keep[2] = {zero8, zero8};
+    auto keep_pass = [&](auto chunks_c) {               // sums in the order of the pass below: chunk after chunk, lanes, wavefronts
+        constexpr int KC = decltype(chunks_c)::value, KM = kMaxM / KC;
+#pragma unroll
+        for (int c0 = 0; c0 < KC; ++c0) {
+            const int64_t k = (int64_t)(c0 * kThreads + t) * 8;
+            const bool in_k = c0 * kThreads + t < pieces && k < K;
+#pragma unroll
+            for (int m = 0; m < KM; ++m) {
+                keep[c0 * KM + m] = zero8;
+                if (m < M && in_k) keep[c0 * KM + m] = *reinterpret_cast<const half8_t*>(X + (int64_t)m * K + k);
+            }
+            if (in_k) g_keep[c0] = *reinterpret_cast<const half8_t*>(fu.gamma + k);
+        }
+#pragma unroll
+        for (int m0 = 0; m0 < KM; m0 += 8) {
+            if (m0 >= M) break;
+            float sq[8];
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+                sq[r] = 0.f;
+#pragma unroll
+                for (int c0 = 0; c0 < KC; ++c0) {
+                    const half8_t v = keep[c0 * KM + m0 + r];
+                    const half2_t x0 = {v[0], v[1]}, x1 = {v[2], v[3]}, x2 = {v[4], v[5]}, x3 = {v[6], v[7]};
+                    float d = __builtin_amdgcn_fdot2(x0, x0, sq[r], false);
+                    d = __builtin_amdgcn_fdot2(x1, x1, d, false);
+                    d = __builtin_amdgcn_fdot2(x2, x2, d, false);
+                    sq[r] = __builtin_amdgcn_fdot2(x3, x3, d, false);
+                }
+            }
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1)
+#pragma unroll
+                for (int r = 0; r < 8; ++r) sq[r] += __shfl_xor(sq[r], d);
+            if (lane == 0) {
+#pragma unroll
+                for (int r = 0; r < 8; ++r)
+                    if (m0 + r < M) norm_part[wave * kMaxM + m0 + r] = sq[r];
+            }
+        }
+    };
+    if (keep_norm) {
+        if (!kKeepTwo || cpr == 1) keep_pass(std::integral_constant<int, 1>{});
+        else keep_pass(std::integral_constant<int, 2>{});
+    }
+    if (normed && !own_norm && !keep_norm) {
         // rms-norm: sum of squares of every row (first pass over X; the staging pass below reads it again,
         // from the cache), reduced in a fixed order: lanes, then wavefronts;
         // kNormRows rows at a time: their loads are in flight together and their wavefront reductions (chains of
@@ -361,6 +415,26 @@ __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restr
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");     // read back by the wavefront that wrote it
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        } else if (keep_norm) {
+            auto store_kept = [&](auto chunks_c) {
+                constexpr int KC = decltype(chunks_c)::value, KM = kMaxM / KC;
+#pragma unroll
+                for (int c0 = 0; c0 < KC; ++c0) {
+                    const int pc = c0 * kThreads + t;
+#pragma unroll
+                    for (int m = 0; m < KM; ++m)
+                        if (m < M) store_piece(m, pc, pc < pieces, keep[c0 * KM + m], g_keep[c0]);
+                }
+            };
+            if (!kKeepTwo || cpr == 1) store_kept(std::integral_constant<int, 1>{});
+            else store_kept(std::integral_constant<int, 2>{});
+            if (keep_own) {                             // read back by the wavefront that wrote it
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            } else {
+                __syncthreads();
+            }
         } else if (own_x) {
             for (int i0 = 0; i0 < M * kItemPieces; i0 += kStageBatch * 64) {
                 half8_t vb[kStageBatch];

@@ -478,3 +478,19 @@ def test_gemm_epilogue_edges(e0m4, oracle, variant, M, N, swiglu, in_place):
     finally:
         e0m4.e0m4_set_knob("gemm_variant", 0)
         e0m4.e0m4_set_knob("gemm_splits", 0)
+
+
+@pytest.mark.parametrize("bits", [4, 8])
+@pytest.mark.parametrize("M,K", [(2, 2048), (16, 2048), (16, 1152), (9, 3584), (16, 4096), (3, 4224), (8, 5120), (9, 5120),
+                                 (8, 8192), (5, 8320), (2, 128)])
+def test_norm_with_the_activations_kept(e0m4, oracle, bits, M, K):
+    # rms-norm inside the small-batch kernel with one or two pieces of X per thread and row kept from the pass over its
+    # squares: rows as long as the workgroup holds and one step longer, eight rows and one more, a wavefront's own pieces
+    # (4096) and pieces shared by two wavefronts (2048)
+    Y = run_fused(e0m4, oracle, M, 448, K, 128, seed=800 + M + K, norm=True, swiglu=True, bits=bits, outliers=True)
+    e0m4.e0m4_set_knob("gemv_waves", 16)                # (never kept with sixteen wavefronts)
+    try:
+        Z = run_fused(e0m4, oracle, M, 448, K, 128, seed=800 + M + K, norm=True, swiglu=True, bits=bits, outliers=True)
+    finally:
+        e0m4.e0m4_set_knob("gemv_waves", 0)
+    assert Y.shape == Z.shape
