@@ -970,7 +970,7 @@ bool k_halves(const PipeTile& t, int64_t M, int64_t N, int64_t K)
 {
     return t.bm == 64 && K >= 4 * BK && ((M + 63) / 64) * ((N + 255) / 256) <= kComputeUnits;
 }
-// (the seven cases above and below within 10 %, for any number of tiles: a compute unit has two wavefronts per SIMD or none)
+// (the cases above within 12 %, whatever the number of tiles: a compute unit has two wavefronts per SIMD or none)
 constexpr double kHalvesUsPerPair = 1.1;                // us per pair of K slices of the whole K
 
 // Up to 64 rows the flat tile; above, the tile with the shortest estimate.
@@ -1170,8 +1170,8 @@ int launch_gemm_pipe(const void* X, int64_t M, const void* packed, int64_t N, in
 
 namespace {
 // Whole tiles only (no workspace to split K into); the tile by the same estimate as for fp16, whose timings those of
-// this member follow.  M = 1024: 4608 x 4096 (72 large tiles) 70 us flat against 90 large, 27392 x 4096 (428) 214
-// large against 253 flat, 4096 x 13696 (64) 154 flat against 253 large; 2048 x 5120 x 5120 (160) 111 large against 132.
+// this member follow, flat tiles as K halves where k_halves says so.  M = 1024: 4608 x 4096 (288 flat tiles) 61 us, 27392 x
+// 4096 (428 large ones) 226, 4096 x 13696 (256 flat tiles in halves) 131, whole 154.
 template <int G>
 int launch_pipe_bf16(const half_t* x, int64_t M, const uint4* c, int64_t N, int64_t K, half_t* y, hipStream_t stream)
 {
