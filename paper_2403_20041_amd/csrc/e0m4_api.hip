@@ -69,11 +69,12 @@ __global__ void zero_fill_kernel(half_t* y, int64_t count)
 }
 
 bool group_ok(int group) { return group == 32 || group == 64 || group == 128; }
-// The small-batch kernel that stages X in LDS, for plain matmuls (gemv_mfma 1: off; 6: also for groups of 64 and 32).
+// The small-batch kernel that stages X in LDS, for plain matmuls (gemv_mfma 1: off; 6: groups of 64 and 32 at two rows too,
+// where the vector kernel is the faster one).
 bool use_gemv_mfma(int64_t M, int64_t N, int64_t K, int group)
 {
     const int k = knob("gemv_mfma");
-    return k != 1 && (group == 128 || k == 6) && gemv_mfma_supported(M, N, K, group);
+    return k != 1 && (group == 128 || M >= 3 || k == 6) && gemv_mfma_supported(M, N, K, group);
 }
 // The small-batch kernel with dequantised weight operands, for plain matmuls: where it pays; gemv_mfma 4 forces it wherever it
 // can run (2 <= M <= 128), 1 and 5 switch it off, 2, 3 and 6 prefer the kernel above.

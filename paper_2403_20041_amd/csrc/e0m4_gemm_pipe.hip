@@ -114,11 +114,11 @@ __global__ __launch_bounds__(64 * WGM * WGN * KS, 2) void gemm_pipe_kernel(const
 {
     constexpr int kThreads = 64 * WGM * WGN;            // per K half
     constexpr int kStageBytes = BM * kRowBytes;
-    // K slices of weights in flight, and of activations in registers.  Twice as many for the flat bfloat16 tile, which has no
-    // K split to put a second workgroup on a compute unit: 4096 x 13696 at M = 300 165 -> 144 us.  With the K split the
-    // longer start costs more than it gives (fp16 4096 x 13696 at M = 128 29.4 -> 31.4).  With K halves 112 -> 103.
-    constexpr int PD = BF && BM == 64 ? 4 : 2;
-    constexpr int AD = BF && BM == 64 ? 2 : 1;
+    // K slices of weights in flight, and of activations in registers.  Twice as many where one workgroup has a compute unit to
+    // itself (K halves: 4096 x 13696 at M = 300 112 -> 103 us); with a second one beside it the longer start costs more than it
+    // gives (fp16 4096 x 13696 at M = 128 in K splits 29.4 -> 31.4, bfloat16 22784 x 5120 at M = 180, 267 tiles, 77 -> 79).
+    constexpr int PD = KS == 2 ? 4 : 2;
+    constexpr int AD = KS == 2 ? 2 : 1;
     constexpr int TM = BM / (32 * WGM), TN = BN / (32 * WGN);      // 32x32 MFMA blocks per wavefront
     constexpr int RP = kThreads / 8;                    // rows covered by one activation loader pass
     constexpr int PA = BM / RP;                         // activation loader passes

@@ -346,7 +346,8 @@ bool gemv_dq_supported(int64_t M, int64_t N, int64_t K, int group)
 //     128 rows in two parts, against the GEMM's 64 x 256 tiles with K halves, where a workgroup has few row blocks: at M =
 //     100 4096 x 4096 35 -> 22 us, 4096 x 13696 103 -> 56, but 32768 x 2048 (8 row blocks) 27 -> 37, 27392 x 4096 44 -> 67;
 //     three parts are no faster (4096 x 4096 at M = 192 38).
-//   Groups of 32 and 64: from 3 rows on up to 16, always (0.97 - 1.8).
+//   Groups of 32 and 64: from 3 rows on up to 16 (0.97 - 1.8), but not where the kernel that stages X can run (8 and 4 rows)
+//     and a workgroup has three row blocks or more to spend its staging on (0.97 - 1.02, with weights in cache 0.93).
 //   Group 128 and 8-bit codes up to 16 rows, against the kernel that stages X in LDS once per workgroup: that one costs a
 //     compute unit M K bytes of staging before its first product, this one more arithmetic per weight.  From 9 rows on
 //     1.06 - 1.67 (more than 8 row blocks per workgroup: 0.78 - 0.96), below that where a workgroup has one or two row
@@ -365,8 +366,8 @@ bool gemv_dq_pays(int64_t M, int64_t N, int64_t K, int group, DqFormat format)
     if (M > kDqMaxM) return false;
     if (format == kDqFormatE8 && M > 16 && K % 128 != 0 && !(M <= 32 && K <= 2048 && NK <= 1e7)) return false;
     if (M > 16) return NK <= (format == kDqFormatE8 ? 1e8 : 7e7) && (M <= 48 || K <= 9216);
-    if (format == kDqFormatFp16 && group != 128) return true;
     const int row_blocks_wg = p.wr * p.r;
+    if (format == kDqFormatFp16 && group != 128) return row_blocks_wg <= 2 || !gemv_mfma_supported(M, N, K, group);
     if (M >= 9 || format == kDqFormatE8) return row_blocks_wg <= 8;
     return row_blocks_wg <= 2 && (M >= 5 || K <= 4608);
 }

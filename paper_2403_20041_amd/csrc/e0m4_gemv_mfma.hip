@@ -270,8 +270,9 @@ __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restr
     // Otherwise, with at most sixteen pieces per thread -- one per row of X, or two of up to eight rows -- every thread keeps
     // its pieces from the first pass, and X is read once: 4608 x 4096 in 8-bit codes at M = 16 17.0 -> 14.7 us, gated 27392 x
     // 4096 36.5 -> 33.2; 15360 x 5120 at M = 8 18.4 -> 16.6.  (Not with K in phases or several groups per block, where it
-    // gained nothing.)  4-bit codes with XREG and step_slots == 1: thread t's piece is one of its own wavefront's four blocks.
-    const bool keep_norm = kKeep && normed && (cpr == 1 || (kKeepTwo && cpr == 2 && M <= 8));
+    // gained nothing, nor where the pieces leave more than three threads in eight without one: 2944 x 2176 lost 3 %.)  4-bit
+    // codes with XREG and step_slots == 1: thread t's piece is one of its own wavefront's four blocks.
+    const bool keep_norm = kKeep && normed && (cpr == 1 || (kKeepTwo && cpr == 2 && M <= 8)) && (XREG || pieces * 8 >= cpr * kThreads * 5);
     const bool keep_own = XREG && step_slots == 1;
     half8_t g_keep[2] = {zero8, zero8};
     auto keep_pass = [&](auto chunks_c) {               // sums in the order of the pass below: chunk after chunk, lanes, wavefronts
