@@ -17,7 +17,7 @@
 // is the arithmetic of the dequantisation, 15 vector instructions per word of eight weights (bfloat16: 19), which is why
 // one operand should serve many rows.  Two k blocks in flight per wavefront are enough: four take 5 - 15 % longer, and so
 // do sixteen wavefronts.  Against the kernels used before, at 4096 x 4096, 27392 x 4096, 4096 x 13696 (us): bfloat16 at
-// M = 5 7.9 -> 6.0, 28.7 -> 19.4, 19.2 -> 11.8, at M = 16 53 -> 6.6, 55 -> 19.7, 171 -> 13.7; fp16 at M = 16 7.6 -> 7.3,
+// M = 16 53 -> 6.6, 55 -> 19.7, 171 -> 13.7; fp16 at M = 16 7.6 -> 7.3,
 // (not used), 21.6 -> 13.9, at M = 45 17.2 -> 12.3, (not used), 27.4 -> 26.4.
 #include "e0m4_device.h"
 #include "e0m4_host.h"
@@ -342,8 +342,9 @@ bool gemv_dq_supported(int64_t M, int64_t N, int64_t K, int group)
 
 // Where this kernel is the faster one; 2400 timings on random problems (M = 2 ... 64, N = 1500 ... 40000, K = 1536 ... 16384,
 // cold weights, in a graph), quoted as the time of the kernel it replaces over its own.
-//   bfloat16: from 3 rows on, always (the vector kernel and the GEMM in whole tiles: 1.1 - 12; at 2 rows 0.90 - 1.07).  65 to
-//     128 rows in two parts, against the GEMM's 64 x 256 tiles with K halves, where a workgroup has few row blocks: at M =
+//   bfloat16: from 9 rows on, always (the GEMM in whole tiles: 1.1 - 12).  Up to 8 rows the vector kernel keeps the call
+//     although it is the slower one from 3 on (4096 x 13696 at M = 5 19.2 us, here 11.8): it multiplies the weights unrounded,
+//     this one rounds each to bfloat16 first.  65 to 128 rows in two parts, against the GEMM's 64 x 256 tiles with K halves, where a workgroup has few row blocks: at M =
 //     100 4096 x 4096 35 -> 22 us, 4096 x 13696 103 -> 56, but 32768 x 2048 (8 row blocks) 27 -> 37, 27392 x 4096 44 -> 67;
 //     three parts are no faster (4096 x 4096 at M = 192 38).
 //   Groups of 32 and 64: from 3 rows on up to 16 (0.97 - 1.8), but not where the kernel that stages X can run (8 and 4 rows)
@@ -362,7 +363,8 @@ bool gemv_dq_pays(int64_t M, int64_t N, int64_t K, int group, DqFormat format)
     // (what the GEMM refuses stays refused: more than 2^24 columns, 8-bit rows that are not a multiple of 128 long unless the
     // weights are small)
     const double NK = (double)N * (double)K;
-    if (format == kDqFormatBf16) return M <= 8 || (N <= (int64_t)1 << 24 && (M <= kDqMaxM || (NK <= 7e7 && p.wr * p.r <= 2)));
+    if (format == kDqFormatBf16)
+        return M > kGemvMaxM && N <= (int64_t)1 << 24 && (M <= kDqMaxM || (NK <= 7e7 && p.wr * p.r <= 2));
     if (M > kDqMaxM) return false;
     if (format == kDqFormatE8 && M > 16 && K % 128 != 0 && !(M <= 32 && K <= 2048 && NK <= 1e7)) return false;
     if (M > 16) return NK <= (format == kDqFormatE8 ? 1e8 : 7e7) && (M <= 48 || K <= 9216);

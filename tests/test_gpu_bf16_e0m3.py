@@ -87,6 +87,24 @@ def test_bf16_decode_matmul(e0m4, oracle, M, G):
     check_bf16_matmul(oracle, Y, Yref, absdot, "bf16 decode M=%d G=%d" % (M, G))
 
 
+@pytest.mark.parametrize("G", [32, 64, 128])
+@pytest.mark.parametrize("M", [1, 2, 3, 5, 8])
+def test_bf16_decode_multiplies_unrounded_weights(e0m4, oracle, M, G):
+    # up to 8 rows a weight is its code's value under scale and bias, with no rounding to bfloat16 before the product: a row
+    # with a single 1.5 gives 1.5 scale (w1 - bias), which fp32 holds exactly, rounded once
+    N, K = 203, 1664
+    codes, _, (oc, os_, ob) = assert_bf16_quantize_exact(e0m4, oracle, synth_inputs.weights_bf16(N, K, seed=3250 + G), G)
+    ks = [(389 * m + 77) % K for m in range(M)]
+    X = np.zeros((M, K), dtype=np.uint16)
+    X[np.arange(M), ks] = 0x3FC0
+    Y = bf_bits(e0m4.e0m4_bf16_matmul(bf_dev(X), codes, N, K, G))
+    for m, k in enumerate(ks):
+        exact = 1.5 * oracle.bf16_to_float64(os_[:, k // G]) * (2 + oc[:, k] / 8.0 - oracle.bf16_to_float64(ob[:, k // G]))
+        want = synth_inputs.to_bf16_bits(exact.astype(np.float32))
+        assert np.array_equal(exact, exact.astype(np.float32).astype(np.float64))
+        assert np.array_equal(Y[m] & 0x7FFF, want & 0x7FFF), "row %d" % m
+
+
 @pytest.mark.parametrize("N,K,G", [(4096, 4096, 128), (1040, 2048, 64), (64, 128, 128), (1, 32, 32), (530, 13696, 128),
                                    (4608, 5120, 64)])
 @pytest.mark.parametrize("waves", [0, 4, 16])
