@@ -69,23 +69,13 @@ __global__ void zero_fill_kernel(half_t* y, int64_t count)
 }
 
 bool group_ok(int group) { return group == 32 || group == 64 || group == 128; }
-// The small-batch kernel that stages X in LDS, for plain matmuls (gemv_mfma 1: off; 6: groups of 64 and 32 at two rows too,
-// where the vector kernel is the faster one).
+// The small-batch kernel that stages X in LDS, for plain matmuls (gemv_mfma 1: off; 6: also for groups of 64 and 32 wherever
+// it can run, which by default it does where it pays).
 bool use_gemv_mfma(int64_t M, int64_t N, int64_t K, int group)
 {
     const int k = knob("gemv_mfma");
-    return k != 1 && (group == 128 || M >= 3 || k == 6) && gemv_mfma_supported(M, N, K, group);
-}
-// The small-batch kernel with dequantised weight operands, for plain matmuls: where it pays; gemv_mfma 4 forces it wherever it
-// can run (2 <= M <= 128), 1 and 5 switch it off, 2, 3 and 6 prefer the kernel above.
-bool use_gemv_dq(int64_t M, int64_t N, int64_t K, int group, DqFormat format)
-{
-    const int k = knob("gemv_mfma");
-    if (k == 1 || k == 5 || !gemv_dq_supported(M, N, K, group)) return false;
-    if (k == 4) return true;
-    if (k != 0 && format == kDqFormatFp16 && use_gemv_mfma(M, N, K, group)) return false;
-    if (k != 0 && format == kDqFormatE8 && gemv_mfma8_supported(M, N, K)) return false;
-    return gemv_dq_pays(M, N, K, group, format);
+    if (k == 1 || !gemv_mfma_supported(M, N, K, group)) return false;
+    return group == 128 || k == 6 || gemv_mfma_groups_pay(M, N, K, group);
 }
 // M <= kGemvMaxM rows take the vector decode kernel, whose time grows with M, unless the matrix-core GEMM
 // (64 x 256 tile, time nearly independent of M) is faster: measured crossover at about M * N * K = 3.8e8
@@ -96,8 +86,8 @@ bool small_m_on_vector(int64_t M, int64_t N, int64_t K)
     if (M < 2 || !gemm_pipe_supported(K) || N > (int64_t)1 << 24) return true;
     return (double)M * (double)N * (double)K < 3.8e8;
 }
-// Fused matmuls with 17 <= M <= kChunkedMaxM on small weights: the small-batch matrix-core kernel on equal chunks of at
-// most 16 rows, dealt to the y dimension of one launch (the chunks of a workgroup's row blocks follow each other on a compute unit
+// 17 <= M <= kChunkedMaxM on small weights: the small-batch matrix-core kernel on equal chunks of at most 16 rows,
+// dealt to the y dimension of one launch (the chunks of a workgroup's row blocks follow each other on a compute unit
 // or run side by side on the same XCD: the weights come from HBM once), instead of the GEMM, whose 64 x 256 tile with
 // its split along K costs 12 - 20 us whatever M is.  The launch takes about as long as one chunk times the rounds its
 // workgroups make on the 256 compute units (staging a chunk of X costs a workgroup more than its weights do):
@@ -115,6 +105,24 @@ bool small_batch_in_chunks(const Fusion& f, int64_t M, int64_t N, int64_t K, int
     if (!gemv_mfma_whole_rows(f, rows_per_chunk(M), N, K, group, &wgs)) return false;
     const int64_t rounds = (row_chunks(M) * wgs + 255) / 256;
     return rounds <= 2 || (rounds == 3 && (double)N * (double)K <= 2e7);
+}
+// The small-batch kernel with dequantised weight operands, for plain matmuls.  It rounds every weight to 16 bits before the
+// product, as the GEMM does; the kernels above work on the codes' exact values and apply scale and bias in fp32.  So it never
+// takes a call from one of those, only, where it is the faster one, from the GEMM -- and, at 3 <= M <= 16 in groups of 32 and
+// 64, what use_gemv_mfma leaves.  gemv_mfma 4 forces it wherever it can run (2 <= M <= 128), 1 and 5 switch it off.
+bool use_gemv_dq(int64_t M, int64_t N, int64_t K, int group, DqFormat format)
+{
+    const int k = knob("gemv_mfma");
+    if (k == 1 || k == 5 || !gemv_dq_supported(M, N, K, group)) return false;
+    return k == 4 || gemv_dq_pays(M, N, K, group, format);
+}
+bool use_gemv_dq4(int64_t M, int64_t N, int64_t K, int group)
+{
+    if (knob("gemv_mfma") != 4) {
+        if (use_gemv_mfma(M, N, K, group) || small_batch_in_chunks(Fusion{}, M, N, K, group)) return false;
+        if ((group == 128 || M < 3) && small_m_on_vector(M, N, K)) return false;
+    }
+    return use_gemv_dq(M, N, K, group, kDqFormatFp16);
 }
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
@@ -186,7 +194,8 @@ size_t e0m4_workspace_bytes(int64_t M, int64_t N, int64_t K, int group)
 {
     if (check_shape(N, K, group) != E0M4_OK || M <= 0 || N == 0 || K == 0) return 0;             // invalid or empty: nothing runs
     if (small_m_on_vector(M, N, K)) return 0;           // the small-M kernels need none
-    if (use_gemv_dq(M, N, K, group, kDqFormatFp16) || use_gemv_mfma(M, N, K, group)) return 0;
+    if (use_gemv_dq4(M, N, K, group)) return 0;
+    if (use_gemv_mfma(M, N, K, group) || small_batch_in_chunks(Fusion{}, M, N, K, group)) return 0;
     return gemm_workspace_bytes(M, N, K);       // partial tiles of the split-K GEMM, if it splits
 }
 
@@ -328,10 +337,12 @@ int e0m4_matmul(const void* X, int64_t M, const void* codes, const void* scales,
     }
     if (!X || !codes) return E0M4_ERR_NULL;
     if (!aligned16(X) || !aligned16(codes)) return E0M4_ERR_ALIGN;
-    if (use_gemv_dq(M, N, K, group, kDqFormatFp16))
+    if (use_gemv_dq4(M, N, K, group))
         return launch_gemv_dq(X, M, codes, N, K, group, kDqFormatFp16, Y, (hipStream_t)stream);
-    if (use_gemv_mfma(M, N, K, group)) return launch_gemv_mfma(X, M, codes, N, K, Y, (hipStream_t)stream, group);
+    if (use_gemv_mfma(M, N, K, group)) return launch_gemv_mfma(X, M, codes, N, K, Y, (hipStream_t)stream, 1, group);
     if (small_m_on_vector(M, N, K)) return launch_gemv(X, M, codes, N, K, group, Y, (hipStream_t)stream);
+    if (small_batch_in_chunks(Fusion{}, M, N, K, group))
+        return launch_gemv_mfma(X, M, codes, N, K, Y, (hipStream_t)stream, row_chunks(M), group);
     if (N > (int64_t)1 << 24) return E0M4_ERR_SHAPE;    // the GEMM epilogue forms 32-bit offsets of up to 256 rows of Y
     if (workspace_bytes > 0 && (!workspace || !aligned16(workspace))) return workspace ? E0M4_ERR_ALIGN : E0M4_ERR_NULL;
     return launch_gemm(X, M, codes, N, K, group, Y, workspace, workspace_bytes, (hipStream_t)stream);
@@ -372,8 +383,6 @@ int e0m4_matmul_fused(const void* X, int64_t M, const void* rms_gamma, float rms
         (residual && !aligned16(residual)))
         return E0M4_ERR_ALIGN;
     hipStream_t st = (hipStream_t)stream;
-    if (!f.any() && use_gemv_dq(M, N, K, group, kDqFormatFp16))         // nothing to fuse: the bits of e0m4_matmul
-        return launch_gemv_dq(X, M, codes, N, K, group, kDqFormatFp16, Y, st);
     const int path = fused_path(f, M, N, K, group);
     if (path == 2) return launch_gemv_mfma_fused(f, X, M, codes, N, K, Y, st, 1, group);
     if (path == 0) return launch_gemv_fused(f, X, M, codes, N, K, group, Y, st);
@@ -534,11 +543,17 @@ static bool small_batch8_in_chunks(const Fusion& f, int64_t M, int64_t N, int64_
            gemv_mfma8_whole_rows(f, rows_per_chunk(M), N, K);
 }
 
-static bool e0m8_use_gemm(int64_t M, int64_t N, int64_t K)
+// the GEMM's calls, of which the kernel with dequantised operands takes those where it pays
+static bool e0m8_gemm_or_dq(int64_t M, int64_t N, int64_t K)
 {
-    return !use_gemv_dq(M, N, K, 128, kDqFormatE8) && !e0m8_use_mfma_decode(M, N, K) && !small_m_on_vector(M, N, K) &&
+    return !e0m8_use_mfma_decode(M, N, K) && !small_batch8_in_chunks(Fusion{}, M, N, K) && !small_m_on_vector(M, N, K) &&
            gemm_pipe_supported(K) && N <= (int64_t)1 << 24;
 }
+static bool e0m8_use_gemv_dq(int64_t M, int64_t N, int64_t K)
+{
+    return (knob("gemv_mfma") == 4 || e0m8_gemm_or_dq(M, N, K)) && use_gemv_dq(M, N, K, 128, kDqFormatE8);
+}
+static bool e0m8_use_gemm(int64_t M, int64_t N, int64_t K) { return e0m8_gemm_or_dq(M, N, K) && !e0m8_use_gemv_dq(M, N, K); }
 
 size_t e0m8_workspace_bytes(int64_t M, int64_t N, int64_t K, int group)
 {
@@ -563,9 +578,10 @@ int e0m8_matmul(const void* X, int64_t M, const void* codes, int64_t N, int64_t 
     }
     if (!X || !codes) return E0M4_ERR_NULL;
     if (!aligned16(X) || !aligned16(codes)) return E0M4_ERR_ALIGN;
-    if (use_gemv_dq(M, N, K, 128, kDqFormatE8))
-        return launch_gemv_dq(X, M, codes, N, K, 128, kDqFormatE8, Y, (hipStream_t)stream);
+    if (e0m8_use_gemv_dq(M, N, K)) return launch_gemv_dq(X, M, codes, N, K, 128, kDqFormatE8, Y, (hipStream_t)stream);
     if (e0m8_use_mfma_decode(M, N, K)) return launch_gemv_mfma8(X, M, codes, N, K, Y, (hipStream_t)stream);
+    if (small_batch8_in_chunks(Fusion{}, M, N, K))
+        return launch_gemv_mfma8(X, M, codes, N, K, Y, (hipStream_t)stream, row_chunks(M));
     if (e0m8_use_gemm(M, N, K)) {
         if (workspace_bytes > 0 && (!workspace || !aligned16(workspace))) return workspace ? E0M4_ERR_ALIGN : E0M4_ERR_NULL;
         return launch_gemm_pipe8(X, M, codes, N, K, Y, workspace, workspace_bytes, (hipStream_t)stream);
@@ -621,8 +637,6 @@ int e0m8_matmul_fused(const void* X, int64_t M, const void* rms_gamma, float rms
         (residual && !aligned16(residual)))
         return E0M4_ERR_ALIGN;
     hipStream_t st = (hipStream_t)stream;
-    if (!f.any() && use_gemv_dq(M, N, K, 128, kDqFormatE8))             // nothing to fuse: the bits of e0m8_matmul
-        return launch_gemv_dq(X, M, codes, N, K, 128, kDqFormatE8, Y, st);
     const int path = fused_path8(f, M, N, K);
     if (path == 2) return launch_gemv_mfma8_fused(f, X, M, codes, N, K, Y, st);
     if (path == 0) return launch_gemv8_fused(f, X, M, codes, N, K, Y, st);

@@ -17,8 +17,7 @@
 // is the arithmetic of the dequantisation, 15 vector instructions per word of eight weights (bfloat16: 19), which is why
 // one operand should serve many rows.  Two k blocks in flight per wavefront are enough: four take 5 - 15 % longer, and so
 // do sixteen wavefronts.  Against the kernels used before, at 4096 x 4096, 27392 x 4096, 4096 x 13696 (us): bfloat16 at
-// M = 16 53 -> 6.6, 55 -> 19.7, 171 -> 13.7; fp16 at M = 16 7.6 -> 7.3,
-// (not used), 21.6 -> 13.9, at M = 45 17.2 -> 12.3, (not used), 27.4 -> 26.4.
+// M = 16 53 -> 6.6, 55 -> 19.7, 171 -> 13.7; fp16 at M = 45 17.2 -> 12.3, (not used), 27.4 -> 26.4.
 #include "e0m4_device.h"
 #include "e0m4_host.h"
 
@@ -340,38 +339,27 @@ bool gemv_dq_supported(int64_t M, int64_t N, int64_t K, int group)
     return (group == 32 || group == 64 || group == 128) && make_dq_plan(M, N, K, p);
 }
 
-// Where this kernel is the faster one; 2400 timings on random problems (M = 2 ... 64, N = 1500 ... 40000, K = 1536 ... 16384,
-// cold weights, in a graph), quoted as the time of the kernel it replaces over its own.
-//   bfloat16: from 9 rows on, always (the GEMM in whole tiles: 1.1 - 12).  Up to 8 rows the vector kernel keeps the call
-//     although it is the slower one from 3 on (4096 x 13696 at M = 5 19.2 us, here 11.8): it multiplies the weights unrounded,
-//     this one rounds each to bfloat16 first.  65 to 128 rows in two parts, against the GEMM's 64 x 256 tiles with K halves, where a workgroup has few row blocks: at M =
-//     100 4096 x 4096 35 -> 22 us, 4096 x 13696 103 -> 56, but 32768 x 2048 (8 row blocks) 27 -> 37, 27392 x 4096 44 -> 67;
-//     three parts are no faster (4096 x 4096 at M = 192 38).
-//   Groups of 32 and 64: from 3 rows on up to 16 (0.97 - 1.8), but not where the kernel that stages X can run (8 and 4 rows)
-//     and a workgroup has three row blocks or more to spend its staging on (0.97 - 1.02, with weights in cache 0.93).
-//   Group 128 and 8-bit codes up to 16 rows, against the kernel that stages X in LDS once per workgroup: that one costs a
-//     compute unit M K bytes of staging before its first product, this one more arithmetic per weight.  From 9 rows on
-//     1.06 - 1.67 (more than 8 row blocks per workgroup: 0.78 - 0.96), below that where a workgroup has one or two row
-//     blocks: 1.07 - 1.22 from 5 rows on, 1.10 from 3 on up to K = 4608 (longer rows 0.92 - 1.04); 8-bit codes, whose
-//     arithmetic is the cheaper, 1.00 - 1.22 from 3 rows on.
-//   17 to 64 rows, against the GEMM and its K splits: 1.05 - 1.8 while the weights are few enough that reading X again in
-//     every workgroup is the smaller part (0.80 - 1.0 beyond the lines below).
+// Where this kernel is faster than the GEMM, which rounds the weights as it does.  (The callers keep the calls of the kernels
+// that multiply unrounded weights away from here, faster or not: bfloat16 4096 x 13696 at M = 5 takes the vector kernel 19.2 us
+// and this one 11.8.)  Timings on random problems (N = 1500 ... 40000, K = 1536 ... 16384, cold weights, in a graph), quoted
+// as the GEMM's time over this kernel's:
+//   bfloat16: up to 64 rows always (whole tiles only on the other side: 1.1 - 12).  65 to 128 rows in two parts, against 64 x
+//     256 tiles with K halves, where a workgroup has few row blocks: at M = 100 4096 x 4096 35 -> 22 us, 4096 x 13696 103 ->
+//     56, but 32768 x 2048 (8 row blocks) 27 -> 37, 27392 x 4096 44 -> 67; three parts are no faster (4096 x 4096 at M = 192
+//     38).
+//   Groups of 32 and 64 up to 16 rows: always (0.97 - 1.8).
+//   17 to 64 rows, against K splits: 1.05 - 1.8 while the weights are few enough that reading X again in every workgroup is
+//     the smaller part (0.80 - 1.0 beyond the lines below).
 bool gemv_dq_pays(int64_t M, int64_t N, int64_t K, int group, DqFormat format)
 {
     DqPlan p;
     if (M < 3 || !make_dq_plan(M, N, K, p)) return false;
-    // (what the GEMM refuses stays refused: more than 2^24 columns, 8-bit rows that are not a multiple of 128 long unless the
-    // weights are small)
     const double NK = (double)N * (double)K;
     if (format == kDqFormatBf16)
         return M > kGemvMaxM && N <= (int64_t)1 << 24 && (M <= kDqMaxM || (NK <= 7e7 && p.wr * p.r <= 2));
     if (M > kDqMaxM) return false;
-    if (format == kDqFormatE8 && M > 16 && K % 128 != 0 && !(M <= 32 && K <= 2048 && NK <= 1e7)) return false;
     if (M > 16) return NK <= (format == kDqFormatE8 ? 1e8 : 7e7) && (M <= 48 || K <= 9216);
-    const int row_blocks_wg = p.wr * p.r;
-    if (format == kDqFormatFp16 && group != 128) return row_blocks_wg <= 2 || !gemv_mfma_supported(M, N, K, group);
-    if (M >= 9 || format == kDqFormatE8) return row_blocks_wg <= 8;
-    return row_blocks_wg <= 2 && (M >= 5 || K <= 4608);
+    return format == kDqFormatFp16 && group != 128;
 }
 
 int launch_gemv_dq(const void* X, int64_t M, const void* packed, int64_t N, int64_t K, int group, DqFormat format, void* Y,

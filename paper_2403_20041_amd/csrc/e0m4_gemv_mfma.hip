@@ -844,15 +844,35 @@ bool gemv_mfma_supported(int64_t M, int64_t N, int64_t K, int group)
 // the M and chunk counts the callers use: 17 ... 64 rows in ceil(M / 16) chunks).
 int64_t chunk_rows(int64_t M, int chunks) { return (M + chunks - 1) / chunks; }
 
-int launch_gemv_mfma(const void* X, int64_t M, const void* packed, int64_t N, int64_t K, void* Y, hipStream_t stream, int group)
+// Groups of 64 and 32 stage every row of X two or four times (16 rows of LDS traffic whatever M is), which the
+// kernel with dequantised operands (e0m4_gemv_dq.hip) does not.  This one takes the calls where a workgroup has several
+// row blocks to spend its staging on, or (group 64) the staged rows fit the LDS at once: 15360 x 5120 at M = 4 12.4 us,
+// 27392 x 5120 at M = 8 22.6, 5120 x 5120 at M = 4 7.5; in phases 5120 x 5120 at M = 8 11.1, 5120 x 13696 at M = 4 18.9.
+// It works with unrounded weights, the other kernel with weights rounded to fp16: the line stays where it is, also where
+// the other kernel is by now the faster one.  At M = 2 the vector kernel is as fast or faster.
+bool gemv_mfma_groups_pay(int64_t M, int64_t N, int64_t K, int group)
+{
+    const int gs = groups_per_block(group);
+    MfmaPlan p;
+    if (gs == 1 || M < 3 || !gemv_mfma_supported(M, N, K, group) || !make_mfma_plan(M, N, K, p, 1, false, gs)) return false;
+    return p.rb_base >= 3 || (gs == 2 && p.kb_phase == 0);
+}
+
+int launch_gemv_mfma(const void* X, int64_t M, const void* packed, int64_t N, int64_t K, void* Y, hipStream_t stream,
+                     int chunks, int group)
 {
     MfmaPlan p;
+    const int64_t mc = chunk_rows(M, chunks);
     const int gs = groups_per_block(group);
-    if (!gemv_mfma_supported(M, N, K, group) || !make_mfma_plan(M, N, K, p, 1, false, gs)) return E0M4_ERR_SHAPE;
+    if (chunks < 1 || M - (chunks - 1) * mc < kMinM || !gemv_mfma_supported(mc, N, K, group) ||
+        !make_mfma_plan(mc, N, K, p, 1, false, gs))
+        return E0M4_ERR_SHAPE;
+    GemvFusion fu{};
+    fu.m_total = chunks > 1 ? (int)M : 0;
     switch (p.waves) {
-        case 4: return launch_mfma<4, false>(p, X, M, packed, N, K, Y, stream, GemvFusion{}, gs);
-        case 8: return launch_mfma<8, false>(p, X, M, packed, N, K, Y, stream, GemvFusion{}, gs);
-        default: return launch_mfma<16, false>(p, X, M, packed, N, K, Y, stream, GemvFusion{}, gs);
+        case 4: return launch_mfma<4, false>(p, X, mc, packed, N, K, Y, stream, fu, gs);
+        case 8: return launch_mfma<8, false>(p, X, mc, packed, N, K, Y, stream, fu, gs);
+        default: return launch_mfma<16, false>(p, X, mc, packed, N, K, Y, stream, fu, gs);
     }
 }
 
@@ -887,11 +907,15 @@ int launch_mfma8(const MfmaPlan& p, const GemvFusion& fu, const void* X, int64_t
 }
 }  // namespace
 
-int launch_gemv_mfma8(const void* X, int64_t M, const void* packed, int64_t N, int64_t K, void* Y, hipStream_t stream)
+int launch_gemv_mfma8(const void* X, int64_t M, const void* packed, int64_t N, int64_t K, void* Y, hipStream_t stream,
+                      int chunks)
 {
     MfmaPlan p;
-    if (!gemv_mfma8_supported(M, N, K) || !make_mfma_plan(M, N, 2 * K, p, 1, true)) return E0M4_ERR_SHAPE;
-    return launch_mfma8<false>(p, GemvFusion{}, X, M, packed, N, K, Y, stream);
+    const int64_t mc = chunk_rows(M, chunks);
+    if (chunks < 1 || M - (chunks - 1) * mc < kMinM || !make_mfma_plan(mc, N, 2 * K, p, 1, true)) return E0M4_ERR_SHAPE;
+    GemvFusion fu{};
+    fu.m_total = chunks > 1 ? (int)M : 0;
+    return launch_mfma8<false>(p, fu, X, mc, packed, N, K, Y, stream);
 }
 
 bool gemv_mfma8_fused_supported(const Fusion& f, int64_t M, int64_t N, int64_t K)

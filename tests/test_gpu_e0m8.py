@@ -209,6 +209,24 @@ def test_one_hot_activations_reproduce_weights_bit_exactly(e0m4, oracle):
         assert np.array_equal(Y[0].view(np.uint16), What[:, k].view(np.uint16)), k
 
 
+@pytest.mark.parametrize("M,N,K,G", [(1, 203, 1088, 64), (2, 203, 1088, 64), (3, 203, 1088, 64), (16, 203, 2048, 128),
+                                     (16, 448, 5184, 64), (17, 333, 1152, 128), (32, 203, 1088, 64)])
+def test_few_rows_multiply_unrounded_weights(e0m4, oracle, M, N, K, G):
+    # up to 16 rows, and up to 32 in chunks, no weight is rounded to fp16 before the product: a row with a single 1.5 gives
+    # 1.5 scale (w1 - bias), which fp32 holds exactly, rounded once
+    W = synth_inputs.weights(N, K, seed=735 + G)
+    codes, _ = assert_quantize_exact(e0m4, oracle, W, G)
+    oc, os_, ob = oracle.quantize_k(W, G, 8)
+    ks = [(389 * m + 77) % K for m in range(M)]
+    X = np.zeros((M, K), np.float16)
+    X[np.arange(M), ks] = 1.5
+    Y = bits(e0m4.e0m8_matmul(to_dev(X), codes, N, K, G))
+    for m, k in enumerate(ks):
+        exact = 1.5 * os_.view(np.float16)[:, k // G].astype(np.float64) * (2 + oc[:, k] / 128.0 - ob.view(np.float16)[:, k // G])
+        want = exact.astype(np.float16).view(np.uint16)
+        assert np.array_equal(Y[m] & 0x7FFF, want & 0x7FFF), "row %d" % m
+
+
 def test_argument_errors(e0m4):
     x = torch.zeros((1, 128), dtype=torch.float16, device=DEV)
     w = torch.zeros((64, 128), dtype=torch.float16, device=DEV)

@@ -573,6 +573,28 @@ def test_one_hot_activations_reproduce_weights_bit_exactly(e0m4, oracle, M):
     assert np.array_equal(Y, What.view(np.uint16)[:, ks].T)
 
 
+@pytest.mark.parametrize("M,N,K,G", [
+    (1, 203, 1664, 64), (2, 203, 1664, 32), (2, 203, 1664, 64),                 # vector kernel
+    (2, 203, 1664, 128), (3, 203, 1664, 128), (9, 203, 1664, 128), (16, 1000, 5248, 128),       # X staged in LDS; in phases
+    (3, 203, 1664, 64), (8, 333, 2048, 64), (4, 12400, 640, 32),                # ... once per group
+    (17, 203, 1664, 128), (33, 203, 1664, 128), (64, 333, 1152, 128),           # ... in chunks of rows
+])
+def test_few_rows_multiply_unrounded_weights(e0m4, oracle, M, N, K, G):
+    # the kernels of few rows take a weight as its code's value under scale and bias, with no rounding to fp16 before the
+    # product: a row with a single 1.5 gives 1.5 scale (w1 - bias), which fp32 holds exactly, rounded once
+    W = synth_inputs.weights(N, K, seed=65 + G)
+    (codes, scales, bias), _ = assert_quantize_exact(e0m4, oracle, W, G)
+    oc, os_, ob = oracle.quantize(W, G)
+    ks = [(389 * m + 77) % K for m in range(M)]
+    X = np.zeros((M, K), dtype=np.float16)
+    X[np.arange(M), ks] = 1.5
+    Y = bits(e0m4.e0m4_matmul(to_dev(X), codes, scales, bias, N, K, G))
+    for m, k in enumerate(ks):
+        exact = 1.5 * os_.view(np.float16)[:, k // G].astype(np.float64) * (2 + oc[:, k] / 8.0 - ob.view(np.float16)[:, k // G])
+        want = exact.astype(np.float16).view(np.uint16)
+        assert np.array_equal(Y[m] & 0x7FFF, want & 0x7FFF), "row %d" % m
+
+
 @pytest.mark.parametrize("M", [1, 64])
 def test_all_ones_activations_give_row_sums(e0m4, oracle, M):
     N, K, G = 192, 1024, 64
