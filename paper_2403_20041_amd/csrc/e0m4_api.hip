@@ -121,6 +121,9 @@ bool use_gemv_dq4(int64_t M, int64_t N, int64_t K, int group)
     if (knob("gemv_mfma") != 4) {
         if (use_gemv_mfma(M, N, K, group) || small_batch_in_chunks(Fusion{}, M, N, K, group)) return false;
         if ((group == 128 || M < 3) && small_m_on_vector(M, N, K)) return false;
+        // (beyond 2^24 columns more than 8 rows are refused like the GEMM's, but for those whose X fits 140 KiB, which never
+        // were)
+        if (N > (int64_t)1 << 24 && M > kGemvMaxM && M * (k_blocks(K) * 256 + 16) > 140 * 1024) return false;
     }
     return use_gemv_dq(M, N, K, group, kDqFormatFp16);
 }

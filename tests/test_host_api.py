@@ -109,6 +109,14 @@ def test_knobs_belong_to_the_calling_thread(L):
     assert L.e0m4_workspace_bytes(*shape) == base
 
 
+def test_more_columns_than_the_gemm_serves_are_refused(L):
+    p, N = ctypes.c_void_p(0x1000), (1 << 24) + 16
+    for M, K, group in ((9, 16384, 64), (16, 8192, 32), (16, 16384, 64), (20, 4096, 32), (64, 4096, 64), (100, 4096, 128)):
+        assert L.e0m4_matmul(p, M, p, p, p, N, K, group, p, None, 0, None) == -2, (M, K, group)
+        assert L.e0m4_matmul_fused(p, M, None, ctypes.c_float(0), p, N, K, group, 0, None, p, None, 0, None) == -2, (M, K, group)
+        assert L.e0m4_bf16_matmul(p, M, p, N, K, group, p, None) == -2, (M, K, group)
+
+
 def test_error_codes_before_any_launch(L):
     p = ctypes.c_void_p(0x1000)         # aligned, never dereferenced: every call below fails validation first
     odd = ctypes.c_void_p(0x1008)
