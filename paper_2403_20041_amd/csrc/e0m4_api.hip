@@ -106,6 +106,11 @@ bool small_batch_in_chunks(const Fusion& f, int64_t M, int64_t N, int64_t K, int
     const int64_t rounds = (row_chunks(M) * wgs + 255) / 256;
     return rounds <= 2 || (rounds == 3 && (double)N * (double)K <= 2e7);
 }
+// Any of the GEMM's knobs is set: it keeps the calls that are its own without the kernel below.
+bool gemm_steered()
+{
+    return knob("gemm_variant") || knob("gemm_splits") || knob("gemm_sk") || knob("gemm_panel") || knob("gemm_split_order");
+}
 // The small-batch kernel with dequantised weight operands, for plain matmuls.  It rounds every weight to 16 bits before the
 // product, as the GEMM does; the kernels above work on the codes' exact values and apply scale and bias in fp32.  So it never
 // takes a call from one of those, only, where it is the faster one, from the GEMM -- and, at 3 <= M <= 16 in groups of 32 and
@@ -118,12 +123,13 @@ bool use_gemv_dq(int64_t M, int64_t N, int64_t K, int group, DqFormat format)
 }
 bool use_gemv_dq4(int64_t M, int64_t N, int64_t K, int group)
 {
+    if (M < 2) return false;
     if (knob("gemv_mfma") != 4) {
         if (use_gemv_mfma(M, N, K, group) || small_batch_in_chunks(Fusion{}, M, N, K, group)) return false;
-        if ((group == 128 || M < 3) && small_m_on_vector(M, N, K)) return false;
-        // (beyond 2^24 columns more than 8 rows are refused like the GEMM's, but for those whose X fits 140 KiB, which never
-        // were)
-        if (N > (int64_t)1 << 24 && M > kGemvMaxM && M * (k_blocks(K) * 256 + 16) > 140 * 1024) return false;
+        const bool fits = M <= kGemvMaxM || (M <= 16 && M * (k_blocks(K) * 256 + 16) <= 140 * 1024);
+        if (group != 128 && M >= 3 && fits) return use_gemv_dq(M, N, K, group, kDqFormatFp16);
+        // what is left is the GEMM's, with its limit of 2^24 columns
+        if (gemm_steered() || small_m_on_vector(M, N, K) || N > (int64_t)1 << 24) return false;
     }
     return use_gemv_dq(M, N, K, group, kDqFormatFp16);
 }
@@ -479,7 +485,7 @@ int e0m4_bf16_matmul(const void* X, int64_t M, const void* codes, int64_t N, int
     }
     if (!X || !codes) return E0M4_ERR_NULL;
     if (!aligned16(X) || !aligned16(codes)) return E0M4_ERR_ALIGN;
-    if (use_gemv_dq(M, N, K, group, kDqFormatBf16))
+    if ((knob("gemv_mfma") == 4 || !gemm_steered()) && use_gemv_dq(M, N, K, group, kDqFormatBf16))
         return launch_gemv_dq(X, M, codes, N, K, group, kDqFormatBf16, Y, (hipStream_t)stream);
     if (M <= kGemvMaxM) return launch_gemv_bf16(X, M, codes, N, K, group, Y, (hipStream_t)stream);
     if (N > (int64_t)1 << 24) return E0M4_ERR_SHAPE;    // 32-bit offsets in the GEMM epilogue
@@ -554,7 +560,7 @@ static bool e0m8_gemm_or_dq(int64_t M, int64_t N, int64_t K)
 }
 static bool e0m8_use_gemv_dq(int64_t M, int64_t N, int64_t K)
 {
-    return (knob("gemv_mfma") == 4 || e0m8_gemm_or_dq(M, N, K)) && use_gemv_dq(M, N, K, 128, kDqFormatE8);
+    return (knob("gemv_mfma") == 4 || (e0m8_gemm_or_dq(M, N, K) && !gemm_steered())) && use_gemv_dq(M, N, K, 128, kDqFormatE8);
 }
 static bool e0m8_use_gemm(int64_t M, int64_t N, int64_t K) { return e0m8_gemm_or_dq(M, N, K) && !e0m8_use_gemv_dq(M, N, K); }
 

@@ -109,6 +109,21 @@ def test_knobs_belong_to_the_calling_thread(L):
     assert L.e0m4_workspace_bytes(*shape) == base
 
 
+def test_knobs_of_the_gemm_reach_calls_of_few_rows(L):
+    """A forced number of K splits shows in the size query of every call that is the GEMM's without the small-batch kernel."""
+    L.e0m8_workspace_bytes.restype = ctypes.c_size_t
+    L.e0m8_workspace_bytes.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int]
+    cases = [(L.e0m4_workspace_bytes, (64, 4096, 4096, 64)), (L.e0m4_workspace_bytes, (16, 4608, 8192, 32)),
+             (L.e0m8_workspace_bytes, (48, 4096, 4096, 128))]
+    for query, shape in cases:
+        assert query(*shape) == 0                       # by default the small-batch kernel's
+        assert L.e0m4_set_knob(b"gemm_splits", 3) == 0
+        try:
+            assert query(*shape) == 3 * 4 * shape[0] * shape[1], shape
+        finally:
+            assert L.e0m4_set_knob(b"gemm_splits", 0) == 0
+
+
 def test_more_columns_than_the_gemm_serves_are_refused(L):
     p, N = ctypes.c_void_p(0x1000), (1 << 24) + 16
     for M, K, group in ((9, 16384, 64), (16, 8192, 32), (16, 16384, 64), (20, 4096, 32), (64, 4096, 64), (100, 4096, 128)):
