@@ -125,11 +125,17 @@ def test_bf16_decode_shapes_and_wavefront_counts(e0m4, oracle, N, K, G, waves):
 @pytest.mark.parametrize("M,N,K,G", [(9, 203, 1664, 128), (64, 256, 512, 32), (200, 520, 1024, 64), (300, 1040, 2080, 32),
                                      (1024, 1280, 4096, 128), (130, 64, 128, 128), (17, 4608, 416, 32)])
 def test_bf16_gemm(e0m4, oracle, M, N, K, G):
+    # by default, where up to 64 rows take the kernel with dequantised operands, and with that kernel off (5)
     codes, What, _ = assert_bf16_quantize_exact(e0m4, oracle, synth_inputs.weights_bf16(N, K, seed=3600 + N + K), G)
     X = synth_inputs.activations_bf16(M, K, seed=3700 + M)
-    Y = e0m4.e0m4_bf16_matmul(bf_dev(X), codes, N, K, G)
     Yref, absdot = oracle.bf16_matmul(X, What)
-    check_bf16_matmul(oracle, Y, Yref, absdot, "bf16 gemm M=%d N=%d K=%d" % (M, N, K))
+    for mode in (0, 5):
+        e0m4.e0m4_set_knob("gemv_mfma", mode)
+        try:
+            Y = e0m4.e0m4_bf16_matmul(bf_dev(X), codes, N, K, G)
+        finally:
+            e0m4.e0m4_set_knob("gemv_mfma", 0)
+        check_bf16_matmul(oracle, Y, Yref, absdot, "bf16 gemm M=%d N=%d K=%d mode %d" % (M, N, K, mode))
 
 
 @pytest.mark.parametrize("variant", [1, 2, 3, 4, 5])

@@ -162,6 +162,7 @@ def test_small_batch_other_kernels_when_the_matrix_core_kernel_is_off(e0m4, orac
 @pytest.mark.parametrize("variant", [2, 3, 4, 5])     # pipelined kernel with tiles of 2: 256 x 256, 3: 128 x 128, 4: 64 x 256, 5: 128 x 256
 @pytest.mark.parametrize("splits", [0, 2, 3])
 def test_gemm_kernels(e0m4, oracle, variant, splits):
+    e0m4.e0m4_set_knob("gemv_mfma", 1)                  # 9 rows would take the small-batch kernel
     e0m4.e0m4_set_knob("gemm_variant", variant)
     e0m4.e0m4_set_knob("gemm_splits", splits)
     try:
@@ -169,6 +170,7 @@ def test_gemm_kernels(e0m4, oracle, variant, splits):
         run_matmul_case(e0m4, oracle, 9, 200, 384, 64, seed=741 + variant)
         run_matmul_case(e0m4, oracle, 257, 1040, 512, 64, seed=742 + variant)
     finally:
+        e0m4.e0m4_set_knob("gemv_mfma", 0)
         e0m4.e0m4_set_knob("gemm_variant", 0)
         e0m4.e0m4_set_knob("gemm_splits", 0)
 
@@ -190,12 +192,17 @@ def test_small_batch_chunks_of_rows(e0m4, oracle, M):
     for N, K, G, seed in ((333, 1152, 128, 770), (1000, 2048, 64, 771), (68, 192, 64, 772)):
         assert e0m4.e0m8_workspace_bytes(M, N, K, G) == 0
         run_matmul_case(e0m4, oracle, M, N, K, G, seed=seed + M, outliers=True)
-    run_matmul_case(e0m4, oracle, 33, 336, 1152, 128, seed=773)         # beyond 32 rows: the GEMM
+    run_matmul_case(e0m4, oracle, 33, 336, 1152, 128, seed=773)         # beyond 32 rows: dequantised operands
 
 
+@pytest.mark.parametrize("mode", [0, 5])                # 5: 20 rows on the GEMM
 @pytest.mark.parametrize("M", [1, 20])
-def test_longest_rows(e0m4, oracle, M):
-    run_matmul_case(e0m4, oracle, M, 24, 1 << 19, 128, seed=760 + M)   # K at its limit
+def test_longest_rows(e0m4, oracle, M, mode):
+    e0m4.e0m4_set_knob("gemv_mfma", mode)
+    try:
+        run_matmul_case(e0m4, oracle, M, 24, 1 << 19, 128, seed=760 + M)   # K at its limit
+    finally:
+        e0m4.e0m4_set_knob("gemv_mfma", 0)
 
 
 def test_one_hot_activations_reproduce_weights_bit_exactly(e0m4, oracle):

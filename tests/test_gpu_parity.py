@@ -356,7 +356,11 @@ def test_small_batch_long_rows_without_the_late_reduction_take_another_kernel(e0
     (512, 512, 1024, 128), (300, 1000, 2048, 64), (1024, 256, 4096, 128),
 ])
 def test_gemm_small(e0m4, oracle, M, N, K, G):
-    run_matmul_case(e0m4, oracle, M, N, K, G, seed=M + N + K, outliers=True, row_std=(0.5, 2.0))
+    e0m4.e0m4_set_knob("gemv_mfma", 1)                  # 9 rows would take the small-batch kernel
+    try:
+        run_matmul_case(e0m4, oracle, M, N, K, G, seed=M + N + K, outliers=True, row_std=(0.5, 2.0))
+    finally:
+        e0m4.e0m4_set_knob("gemv_mfma", 0)
 
 
 # 1: small-tile kernel; pipelined kernel with tiles of 2: 256 x 256, 3: 128 x 128, 4: 64 x 256, 5: 128 x 256
@@ -368,10 +372,12 @@ def test_gemm_small(e0m4, oracle, M, N, K, G):
     (40, 1040, 2048, 128),      # fewer rows than any tile
 ])
 def test_gemm_both_kernels(e0m4, oracle, variant, M, N, K, G):
+    e0m4.e0m4_set_knob("gemv_mfma", 1)                  # 40 rows would take the small-batch kernel in chunks of rows
     e0m4.e0m4_set_knob("gemm_variant", variant)
     try:
         run_matmul_case(e0m4, oracle, M, N, K, G, seed=variant + M + N, outliers=True, row_std=(0.5, 2.0))
     finally:
+        e0m4.e0m4_set_knob("gemv_mfma", 0)
         e0m4.e0m4_set_knob("gemm_variant", 0)
 
 
@@ -620,22 +626,28 @@ def test_matmul_is_deterministic(e0m4, M):
 
 @pytest.mark.parametrize("M,G", [(8, 64), (5, 32), (8, 128)])
 def test_few_rows_with_large_weights_take_the_gemm(e0m4, oracle, M, G):
-    # M * N * K above 3.8e8 and no small-batch matrix-core kernel (other groups; at G = 128, that kernel switched
-    # off): the 64 x 256 GEMM tile instead of the vector kernel
-    if G == 128:
-        e0m4.e0m4_set_knob("gemv_mfma", 1)
-        try:
+    # M * N * K above 3.8e8 and the small-batch matrix-core kernels switched off: the 64 x 256 GEMM tile instead of the
+    # vector kernel
+    e0m4.e0m4_set_knob("gemv_mfma", 1)
+    try:
+        if G == 128:
             run_matmul_case(e0m4, oracle, M, 1600, 32768, G, seed=611)
-        finally:
-            e0m4.e0m4_set_knob("gemv_mfma", 0)
-    else:
-        run_matmul_case(e0m4, oracle, M, 24000 if M == 5 else 12288, 4096, G, seed=610 + M, outliers=True)
+        else:
+            run_matmul_case(e0m4, oracle, M, 24000 if M == 5 else 12288, 4096, G, seed=610 + M, outliers=True)
+    finally:
+        e0m4.e0m4_set_knob("gemv_mfma", 0)
 
 
+@pytest.mark.parametrize("mode", [0, 5])
 @pytest.mark.parametrize("M", [1, 3, 20])
-def test_longest_rows(e0m4, oracle, M):
-    # K at its limit of 2^20: the decode kernel stages X in many segments, the GEMM runs 16384 K slices in 8 splits
-    run_matmul_case(e0m4, oracle, M, 24, 1 << 20, 128, seed=600 + M)
+def test_longest_rows(e0m4, oracle, M, mode):
+    # K at its limit of 2^20: the decode kernel stages X in many segments, 20 rows take the kernel with dequantised
+    # operands and, without it (5), the GEMM, which runs 16384 K slices in 8 splits
+    e0m4.e0m4_set_knob("gemv_mfma", mode)
+    try:
+        run_matmul_case(e0m4, oracle, M, 24, 1 << 20, 128, seed=600 + M)
+    finally:
+        e0m4.e0m4_set_knob("gemv_mfma", 0)
 
 
 def test_empty_problems(e0m4):
@@ -655,8 +667,8 @@ def test_empty_problems(e0m4):
 
 
 # ------------------------------------------------------------------ small batches with dequantised weight operands
-# (2 <= M <= 64, any group; by default it serves groups of 32 and 64 at 3 <= M <= 16; knob gemv_mfma = 4 forces the
-# kernel wherever it can run)
+# (2 <= M <= 128, any group; by default it serves groups of 32 and 64 at 3 <= M <= 16 where the kernel that stages X does not
+# run or pay, and at M > 16 what it takes from the GEMM; knob gemv_mfma = 4 forces the kernel wherever it can run)
 
 DQ_SHAPES = [(203, 1664, 32), (203, 1664, 64), (203, 1664, 128), (1040, 4096, 64), (64, 128, 128), (17, 32, 32),
              (530, 13696, 64), (300, 8192, 128), (4608, 416, 32)]
@@ -701,7 +713,7 @@ def test_small_batch_default_dispatch_and_one_hot(e0m4, oracle, M, G):
 
 
 def test_small_batch_dequantised_operands_few_workgroups(e0m4, oracle):
-    """Many row blocks per workgroup, K in several phases (the sums wait in LDS between phases)."""
+    """One row block per workgroup, nine (two rounds of seven workgroups), four."""
     N, K, G, M = 2000, 6144, 64, 40
     W = synth_inputs.weights(N, K, seed=990)
     (codes, scales, bias), What = assert_quantize_exact(e0m4, oracle, W, G)
