@@ -126,12 +126,13 @@ int e0m4_unpack_codes(const void* codes, int64_t N, int64_t K, int group, void* 
  *   3 <= M <= 16, group 32 or 64: the same kernel with every row of X staged
  *            once per group of a block (M <= 8 at group 64, M <= 4 at group 32,
  *            where a workgroup has several row blocks or the staged rows fit
- *            the LDS), else a kernel that dequantises the weight operand in
- *            registers (when all of X fits the LDS, or M <= 8).
+ *            the LDS), else a matrix-core kernel that dequantises the weight
+ *            operand in registers.
  *   17 <= M <= 64, group 128, N * K <= 7e7, a chunk of X within the LDS:
  *            that kernel on equal chunks of at most 16 rows in one launch,
  *            when its workgroups make at most two rounds on the compute
- *            units (three on small weights).
+ *            units (three on small weights); otherwise, any group, N * K <= 7e7 (and
+ *            K <= 9216 for M > 48), the dequantising kernel.
  *   M >= 9 otherwise, and 2 <= M <= 8 when M * N * K is about 3.8e8 or
  *            more (the vector kernel's time grows with M): MFMA GEMM path
  *            (tiles of 64 x 256, 128 x 256 or 256 x 256 outputs, whichever
@@ -139,6 +140,9 @@ int e0m4_unpack_codes(const void* codes, int64_t N, int64_t K, int group, void* 
  *            K when tiles are few, a partly filled last round of many large
  *            tiles shared out evenly when the estimate favours that).
  *            e0m4_workspace_bytes() tells when a workspace is needed.
+ * The dequantising kernel and the GEMM round every weight to fp16 as
+ * e0m4_dequant does; the other kernels work on the codes' exact values and
+ * apply scale and bias in fp32.
  * `scales_f16`/`bias_f16` may be NULL (see `codes` above); `workspace` may be
  * NULL when e0m4_workspace_bytes() is 0, else it is device memory of at least
  * that many bytes, 16-byte aligned, owned by the caller, overwritten by the
@@ -199,7 +203,8 @@ int e0m4_matmul_static(const void* X_f16, int64_t M, const void* codes, int64_t 
  * rms-norm is a launch of its own that writes x' to the workspace.
  * Workspace: e0m4_fused_workspace_bytes() bytes, same rules as e0m4_matmul.
  * With no operator selected the result is that of e0m4_matmul (up to the order of
- * the fp32 additions, which the two may choose differently for a large problem).  K == 0 is
+ * the fp32 additions and the rounding of the weights: the two may choose different
+ * kernels).  K == 0 is
  * rejected (E0M4_ERR_SHAPE); other shape, pointer and error rules as above.
  */
 #define E0M4_EPILOGUE_NONE   0
@@ -252,7 +257,8 @@ int e0m4_kv_append(void* cache_f16, int64_t max_seq, int64_t row_elems,
  *     (and N <= 2^24): the MFMA GEMM kernels, workspace of
  *     e0m8_workspace_bytes() bytes under the rules of e0m4_matmul (17 <= M <=
  *     32 with K <= 2048 and N * K <= 1e7: the matrix-core variant on two
- *     chunks of rows in one launch instead).  Other M > 16:
+ *     chunks of rows in one launch instead; otherwise M <= 64 with N * K <= 1e8,
+ *     and K <= 9216 for M > 48: the dequantising kernel of e0m4_matmul).  Other M > 16:
  *     the decode kernel on 8 rows of X at a time (needs N % 8 == 0).
  * Pointer, alignment, stream and error rules as for the E0M4 entry points.
  */
@@ -297,10 +303,12 @@ int e0m3_unpack_codes(const void* codes, int64_t N, int64_t K, int group, void* 
  * `codes` has the E0M4 layout and size (e0m4_codes_bytes; e0m4_unpack_codes
  * reads it), its embedded parameter words hold bfloat16 pairs.
  *   e0m4_bf16_matmul: M <= 8 the decode kernel with bfloat16 dot products
- *   (a shift and a mask-or per pair of codes), larger M the pipelined MFMA
- *   kernel of e0m4_matmul with the weights dequantised in registers (fp32 fused
- *   multiply-add, one rounding to bfloat16), in whole tiles (no workspace, so
- *   no split along K); when K is not a multiple of 128 an MFMA kernel with
+ *   (a shift and a mask-or per pair of codes; scale and bias in fp32); larger M
+ *   with the weights dequantised in registers (fp32 fused multiply-add, one
+ *   rounding to bfloat16): up to 64 rows, and 128 on small weights, the
+ *   dequantising kernel of e0m4_matmul, beyond that its pipelined MFMA kernel
+ *   in whole tiles (no workspace, so no split along K but for two halves inside
+ *   a workgroup); when K is not a multiple of 128 an MFMA kernel with
  *   128 x 128 tiles that dequantises into LDS.
  * Shape, pointer, stream and error rules as for the E0M4 entry points.
  */

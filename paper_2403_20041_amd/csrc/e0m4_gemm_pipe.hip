@@ -422,7 +422,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KS, 2) void gemm_pipe_kernel(const
     // bset[set] holds its codes; the next PD - 1 slices' codes and the next AD slices' activations are in flight.
     auto step = [&](int kt, int set, uint32_t cur, uint32_t nxt) {
         // sub-step 0: operands of sub-step 1; publish slice kt+1's activations and, the staging
-        // registers being free again, request those of slice kt+2 at once
+        // registers being free again, request those of slice kt+1+AD at once
         read_frags(cur, 1, fa[1]);
         dequant_frags(set, 1, fb[1]);
         store_a(nxt, (set + 1) % AD);

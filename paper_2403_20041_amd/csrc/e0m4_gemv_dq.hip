@@ -15,9 +15,13 @@
 // matrix core takes it, 16 rows at a stride of 2 K bytes per load, comes at 13 bytes per clock and compute unit (4096 x
 // 13696 at M = 16: 21.7 us); loads of whole rows of a k block, turned around in LDS, bring that to 13.9 us.  After that it
 // is the arithmetic of the dequantisation, 15 vector instructions per word of eight weights (bfloat16: 19), which is why
-// one operand should serve many rows.  Two k blocks in flight per wavefront are enough: four take 5 - 15 % longer, and so
-// do sixteen wavefronts.  Against the kernels used before, at 4096 x 4096, 27392 x 4096, 4096 x 13696 (us): bfloat16 at
-// M = 16 53 -> 6.6, 55 -> 19.7, 171 -> 13.7; fp16 at M = 45 17.2 -> 12.3, (not used), 27.4 -> 26.4.
+// one operand should serve many rows.  In flight per wavefront are two k blocks of weights (four where it has a single row
+// block) and two of X, or one where registers are short (XD); four of both, and sixteen wavefronts, took up to 15 % longer.
+// Against the GEMM at 4096 x 4096, 27392 x 4096, 4096 x 13696 (us): bfloat16 at M = 16 35.0 -> 6.5, 38.6 -> 19.6, 102 -> 13.7;
+// groups of 64 at M = 16 15.1 -> 6.3, 27.3 -> 18.0, 30.7 -> 13.4; 8-bit codes at M = 45 17.6 -> 11.0, (not used), 33.3 -> 28.4.
+//
+// Every weight is rounded to 16 bits before the product, as it is in the GEMM.  The kernels that keep code values exact and
+// apply scale and bias in fp32 (e0m4_gemv.hip, e0m4_gemv_mfma.hip) are not replaced by this one.
 #include "e0m4_device.h"
 #include "e0m4_host.h"
 
@@ -341,15 +345,14 @@ bool gemv_dq_supported(int64_t M, int64_t N, int64_t K, int group)
 
 // Where this kernel is faster than the GEMM, which rounds the weights as it does.  (The callers keep the calls of the kernels
 // that multiply unrounded weights away from here, faster or not: bfloat16 4096 x 13696 at M = 5 takes the vector kernel 19.2 us
-// and this one 11.8.)  Timings on random problems (N = 1500 ... 40000, K = 1536 ... 16384, cold weights, in a graph), quoted
-// as the GEMM's time over this kernel's:
-//   bfloat16: up to 64 rows always (whole tiles only on the other side: 1.1 - 12).  65 to 128 rows in two parts, against 64 x
-//     256 tiles with K halves, where a workgroup has few row blocks: at M = 100 4096 x 4096 35 -> 22 us, 4096 x 13696 103 ->
-//     56, but 32768 x 2048 (8 row blocks) 27 -> 37, 27392 x 4096 44 -> 67; three parts are no faster (4096 x 4096 at M = 192
-//     38).
-//   Groups of 32 and 64 up to 16 rows: always (0.97 - 1.8).
-//   17 to 64 rows, against K splits: 1.05 - 1.8 while the weights are few enough that reading X again in every workgroup is
-//     the smaller part (0.80 - 1.0 beyond the lines below).
+// and this one 11.8.)  The other side's time over this kernel's, on 166 problems with cold weights
+// (profiles/small_batch_dequantised_operands_vs_gemm.txt):
+//   bfloat16: up to 64 rows always (1.1 - 8.2: the GEMM has whole tiles only).  65 to 128 rows in two parts, against 64 x 256
+//     tiles with K halves, where a workgroup has few row blocks: 1.2 - 3.1; at M = 100 4096 x 4096 34.8 -> 21.1 us, 4096 x 13696
+//     102 -> 52, but 32768 x 2048 (8 row blocks) 25 -> 37, 27392 x 4096 43 -> 63.
+//   Groups of 32 and 64 up to 16 rows: always (1.1 - 3.1, the vector kernel's calls among them).
+//   17 to 64 rows, against K splits: 1.1 - 2.7 while the weights are few enough that reading X again in every workgroup is
+//     the smaller part; beyond the lines below 0.9 - 1.4, the more the fewer the rows.
 bool gemv_dq_pays(int64_t M, int64_t N, int64_t K, int group, DqFormat format)
 {
     DqPlan p;
