@@ -66,12 +66,16 @@ __device__ inline __amdgpu_buffer_rsrc_t rsrc_if(const void* p, bool in)
     return __builtin_amdgcn_make_buffer_rsrc(q, 0, __builtin_amdgcn_readfirstlane(in ? 0x7fffffff : 0), 0x00020000);
 }
 
-template <DqFormat FMT, int MT, int R>
+// XE: loads of X per tile and k block.  A load brings a quarter of the tile's rows (8-bit codes: half); calls of up to 4 and 8
+// rows make one and two of them, the other rows of the tile stay what LDS held and so do their sums, which nobody stores.
+// Groups of 32 at 4096 x 4096: M = 3 6.0 -> 5.3 us with one load for four, M = 8 6.1 -> 5.5 with two.
+template <DqFormat FMT, int MT, int R, int XE>
 __global__ __launch_bounds__(kDqThreads, 2) void gemv_dq_kernel(const half_t* __restrict__ X, const uint4* __restrict__ packed,
                                                                 half_t* __restrict__ Y, int m_total, uint32_t N32, uint32_t K32,
                                                                 int rb_base, int rb_rem, int wk_shift, int group_shift)
 {
     constexpr int NP = FMT == kDqFormatE8 ? 2 : 4;            // pieces of X (and MFMAs) per k block
+    static_assert(XE == NP || (XE < NP && MT == 1), "a part of the rows: of a single tile");
     constexpr int BLK = NP * 32;                        // weights of a row per k block
     constexpr int DW = R == 1 ? 4 : 2;
     constexpr int XD = MT <= 2 || (MT == 3 && R <= 2) || FMT == kDqFormatE8 ? 2 : 1;
@@ -119,20 +123,21 @@ __global__ __launch_bounds__(kDqThreads, 2) void gemv_dq_kernel(const half_t* __
     const int tail_kb = (K % BLK) != 0 ? nkb - 1 : -1;
     const bool in_tail = (nkb - 1) * BLK + x_j * 8 < K;
     const uint32_t x_tail_back = in_tail ? 0u : (uint32_t)((x_j / NP) * NP * 16);
-    uint32_t x_voff[MT][NP];
-    uint32_t x_wr[NP], x_rd[NP];
+    uint32_t x_voff[MT][XE];
+    uint32_t x_wr[XE], x_rd[NP];
 #pragma unroll
-    for (int e = 0; e < NP; ++e) {
+    for (int e = 0; e < XE; ++e) {
         const int row = e * RPI + x_a;
 #pragma unroll
         for (int i = 0; i < MT; ++i) x_voff[i][e] = ((uint32_t)min(16 * i + row, M - 1) * K32 + (uint32_t)(x_j * 8)) * 2;
         x_wr[e] = (uint32_t)(row * RB + ((x_j ^ swizzle(row)) << 4));
-        x_rd[e] = (uint32_t)(n_l * RB + (((g_l * NP + e) ^ swizzle(n_l)) << 4));
     }
+#pragma unroll
+    for (int e = 0; e < NP; ++e) x_rd[e] = (uint32_t)(n_l * RB + (((g_l * NP + e) ^ swizzle(n_l)) << 4));
 
     u32x4 c[DW][R];
     uint32_t pwd[DW][R];
-    u32x4 xr[XD][MT][NP];
+    u32x4 xr[XD][MT][XE];
     // (a k block beyond the last is requested through a resource of no bytes: zeros, without an access to memory)
     auto load_w = [&](int kb, int d) {
         const __amdgpu_buffer_rsrc_t rsrc = rsrc_if(wg_base, kb < nkb);
@@ -148,7 +153,7 @@ __global__ __launch_bounds__(kDqThreads, 2) void gemv_dq_kernel(const half_t* __
 #pragma unroll
         for (int i = 0; i < MT; ++i)
 #pragma unroll
-            for (int e = 0; e < NP; ++e)
+            for (int e = 0; e < XE; ++e)
                 xr[d][i][e] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)(x_voff[i][e] - back), kb * RB, 0);
     };
     // (in the order of use: a wait for one request is a wait for all before it)
@@ -207,7 +212,7 @@ __global__ __launch_bounds__(kDqThreads, 2) void gemv_dq_kernel(const half_t* __
 #pragma unroll
         for (int i = 0; i < MT; ++i)
 #pragma unroll
-            for (int e = 0; e < NP; ++e) {
+            for (int e = 0; e < XE; ++e) {
                 half8_t v = __builtin_bit_cast(half8_t, xr[xd][i][e]);
                 if (none) v = half8_t{0, 0, 0, 0, 0, 0, 0, 0};
                 *reinterpret_cast<half8_t*>(xl + i * (16 * RB) + x_wr[e]) = v;
@@ -291,32 +296,32 @@ bool make_dq_plan(int64_t M, int64_t N, int64_t K, DqPlan& p)
     return true;
 }
 
-template <DqFormat FMT, int MT, int R>
+template <DqFormat FMT, int MT, int R, int XE>
 int launch_dq(const DqPlan& p, const void* X, int64_t M, const void* packed, int64_t N, int64_t K,
               int group, void* Y, hipStream_t stream)
 {
     constexpr int lds = std::max(kDqWaves * R * MT * 64 * 16, kDqWaves * MT * 16 * (FMT == kDqFormatE8 ? 128 : 256));
     static std::atomic<uint64_t> lds_allowed{0};
-    const int arc = allow_dynamic_lds(reinterpret_cast<const void*>(&gemv_dq_kernel<FMT, MT, R>), lds, lds_allowed);
+    const int arc = allow_dynamic_lds(reinterpret_cast<const void*>(&gemv_dq_kernel<FMT, MT, R, XE>), lds, lds_allowed);
     if (arc != E0M4_OK) return arc;
     int wk_shift = 0;                                   // log2 of the wavefronts in a group
     while ((p.wr << (wk_shift + 1)) <= kDqWaves) ++wk_shift;
     const int group_shift = FMT == kDqFormatE8 || group == 128 ? 7 : group == 64 ? 6 : 5;
-    hipLaunchKernelGGL((gemv_dq_kernel<FMT, MT, R>), dim3((unsigned)p.grid, (unsigned)p.parts), dim3(kDqThreads), lds, stream,
+    hipLaunchKernelGGL((gemv_dq_kernel<FMT, MT, R, XE>), dim3((unsigned)p.grid, (unsigned)p.parts), dim3(kDqThreads), lds, stream,
                        static_cast<const half_t*>(X), static_cast<const uint4*>(packed), static_cast<half_t*>(Y), (int)M,
                        (uint32_t)N, (uint32_t)K, p.rb_base, p.rb_rem, wk_shift, group_shift);
     return check_launch();
 }
 
-template <DqFormat FMT, int MT>
+template <DqFormat FMT, int MT, int XE = FMT == kDqFormatE8 ? 2 : 4>
 int launch_dq_r(const DqPlan& p, const void* X, int64_t M, const void* packed, int64_t N, int64_t K,
                 int group, void* Y, hipStream_t stream)
 {
     switch (p.r) {
-        case 1: return launch_dq<FMT, MT, 1>(p, X, M, packed, N, K, group, Y, stream);
-        case 2: return launch_dq<FMT, MT, 2>(p, X, M, packed, N, K, group, Y, stream);
-        case 3: return launch_dq<FMT, MT, 3>(p, X, M, packed, N, K, group, Y, stream);
-        case 4: return launch_dq<FMT, MT, 4>(p, X, M, packed, N, K, group, Y, stream);
+        case 1: return launch_dq<FMT, MT, 1, XE>(p, X, M, packed, N, K, group, Y, stream);
+        case 2: return launch_dq<FMT, MT, 2, XE>(p, X, M, packed, N, K, group, Y, stream);
+        case 3: return launch_dq<FMT, MT, 3, XE>(p, X, M, packed, N, K, group, Y, stream);
+        case 4: return launch_dq<FMT, MT, 4, XE>(p, X, M, packed, N, K, group, Y, stream);
         default: return E0M4_ERR_SHAPE;
     }
 }
@@ -325,6 +330,10 @@ template <DqFormat FMT>
 int launch_dq_m(const DqPlan& p, const void* X, int64_t M, const void* packed, int64_t N, int64_t K,
                 int group, void* Y, hipStream_t stream)
 {
+    if constexpr (FMT == kDqFormatFp16) {               // (the other formats come here with nine rows or more)
+        if (M <= 4) return launch_dq_r<FMT, 1, 1>(p, X, M, packed, N, K, group, Y, stream);
+        if (M <= 8) return launch_dq_r<FMT, 1, 2>(p, X, M, packed, N, K, group, Y, stream);
+    }
     switch (((M + p.parts - 1) / p.parts + 15) / 16) {
         case 1: return launch_dq_r<FMT, 1>(p, X, M, packed, N, K, group, Y, stream);
         case 2: return launch_dq_r<FMT, 2>(p, X, M, packed, N, K, group, Y, stream);

@@ -67,3 +67,22 @@ def test_infinite_activation_stays_in_its_row(e0m4, oracle, M):
     check_matmul(torch.from_numpy(Y[keep]), Yref[keep], absdot[keep], "rows without the infinity")
     w = What[:, 130].astype(np.float64)
     assert np.array_equal(Y[1][w != 0], (np.sign(w[w != 0]) * np.inf).astype(np.float16)) and np.isnan(Y[1][w == 0]).all()
+
+
+@pytest.mark.parametrize("N,K,G,workgroups", SHAPES + [(203, 416, 32, 3), (48, 96, 32, 0)])
+@pytest.mark.parametrize("M", [3, 4, 5, 8])
+def test_few_rows_of_a_tile(e0m4, oracle, M, N, K, G, workgroups):
+    # up to four and up to eight rows only these are loaded: the bits of the same rows among sixteen, which add in one order
+    (codes, _, _), What = assert_quantize_exact(e0m4, oracle, synth_inputs.weights(N, K, seed=4950 + N), G)
+    X = synth_inputs.activations(16, K, seed=4960 + K, outlier_frac=0.01)
+    e0m4.e0m4_set_knob("gemv_mfma", 4)
+    e0m4.e0m4_set_knob("gemv_workgroups", workgroups)
+    try:
+        Y16 = e0m4.e0m4_matmul(to_dev(X), codes, None, None, N, K, G)
+        Y = e0m4.e0m4_matmul(to_dev(X[:M]), codes, None, None, N, K, G)
+    finally:
+        e0m4.e0m4_set_knob("gemv_mfma", 0)
+        e0m4.e0m4_set_knob("gemv_workgroups", 0)
+    Yref, absdot = oracle.matmul(X[:M], What)
+    check_matmul(Y, Yref, absdot, "M=%d" % M)
+    assert torch.equal(Y, Y16[:M])
