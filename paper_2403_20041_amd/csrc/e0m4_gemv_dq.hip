@@ -356,10 +356,10 @@ bool gemv_dq_supported(int64_t M, int64_t N, int64_t K, int group)
 // that multiply unrounded weights away from here, faster or not: bfloat16 4096 x 13696 at M = 5 takes the vector kernel 19.2 us
 // and this one 11.8.)  The other side's time over this kernel's, on 166 problems with cold weights
 // (profiles/small_batch_dequantised_operands_vs_gemm.txt):
-//   bfloat16: up to 64 rows always (1.1 - 8.2: the GEMM has whole tiles only).  65 to 128 rows in two parts, against 64 x 256
+//   bfloat16: up to 64 rows always (1.1 - 7.8: the GEMM has whole tiles only).  65 to 128 rows in two parts, against 64 x 256
 //     tiles with K halves, where a workgroup has few row blocks: 1.2 - 3.1; at M = 100 4096 x 4096 34.8 -> 21.1 us, 4096 x 13696
 //     102 -> 52, but 32768 x 2048 (8 row blocks) 25 -> 37, 27392 x 4096 43 -> 63.
-//   Groups of 32 and 64 up to 16 rows: always (1.1 - 3.1, the vector kernel's calls among them).
+//   Groups of 32 and 64 up to 16 rows: always (1.3 - 3.1, the vector kernel's calls among them).
 //   17 to 64 rows, against K splits: 1.1 - 2.7 while the weights are few enough that reading X again in every workgroup is
 //     the smaller part; beyond the lines below 0.9 - 1.4, the more the fewer the rows.
 bool gemv_dq_pays(int64_t M, int64_t N, int64_t K, int group, DqFormat format)
