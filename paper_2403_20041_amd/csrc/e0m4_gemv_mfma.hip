@@ -825,8 +825,10 @@ int launch_mfma(const MfmaPlan& p, const void* X, int64_t M, const void* packed,
     if (gs == 2) return launch_mfma_groups<W, FUSED, 2>(p, X, M, packed, N, K, Y, stream, fu);
     if (gs == 4) return launch_mfma_groups<W, FUSED, 4>(p, X, M, packed, N, K, Y, stream, fu);
     if (p.kb_phase > 0) return launch_mfma_phased<W, FUSED, false>(p, X, M, packed, N, K, Y, stream, fu);
-    if (p.step_item == 0 && W <= 8 && knob("gemv_mfma") != 2)
-        return launch_mfma_x<W, FUSED, true>(p, X, M, packed, N, K, Y, stream, fu);
+    if constexpr (W <= 8) {
+        if (p.step_item == 0 && knob("gemv_mfma") != 2)
+            return launch_mfma_x<W, FUSED, true>(p, X, M, packed, N, K, Y, stream, fu);
+    }
     return launch_mfma_x<W, FUSED, false>(p, X, M, packed, N, K, Y, stream, fu);
 }
 
