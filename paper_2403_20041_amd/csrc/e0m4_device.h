@@ -139,18 +139,57 @@ __device__ inline uint32_t frac_mask_low_vgpr()
     return m;
 }
 
-// Grid of the kernels that walk a row-major matrix in tiles: eight strips of tile rows side by side, column after column, so
-// that each XCD (workgroup b runs on XCD b % 8) walks along one strip: what neighbouring tiles write to the same cache line,
-// the two-byte parameters above all, meets in one L2.  Groups of strips in y and, beyond what y holds, z.  27392 x 4096
-// quantised and dequantised at group 128 in 124 us, 143 with tile rows in x; 8-bit codes of 8000 x 11008 in 70, 80.
-constexpr unsigned kTileGridY = 32768, kTileStrips = 8;
-__host__ inline dim3 tile_grid(int64_t tile_rows, int64_t tile_cols)
+// Orders in which the kernels that walk a row-major matrix in tiles visit them; workgroup b runs on XCD b % 8.
+//   Strips: eight tile rows side by side, column after column, so that each XCD walks along a strip: what neighbouring tiles
+//     write to the same cache line, the quantisers' two-byte parameters above all, meets in one L2.  27392 x 4096 quantised at
+//     group 128 in 88 us, with tile rows in x 105.  Groups of eight tile rows in y and, beyond what y holds, z; in a last group
+//     of fewer, the rows go round the XCDs from column to column, or some XCDs would wait for the others.
+//   Dealt, with fewer than eight groups, where the idle workgroups of the last one cost too much (600 x 12800 quantised: 14.6
+//     us, dealt 10.2): the same with all tiles in x, those of the last group one by one, rows first.
+//   Plain: tile rows in x, columns in y.
+constexpr unsigned kTileGridY = 32768;
+struct TileGrid {
+    dim3 grid;
+    uint32_t dealt;                                     // 0, or 2^32 / columns rounded up
+    bool plain;
+};
+__host__ inline TileGrid tile_plain(int64_t tile_rows, int64_t tile_cols)
 {
-    const int64_t y = (tile_rows + kTileStrips - 1) / kTileStrips, z = (y + kTileGridY - 1) / kTileGridY;
-    return dim3((unsigned)tile_cols * kTileStrips, (unsigned)(z > 1 ? kTileGridY : y), (unsigned)z);
+    return TileGrid{dim3((unsigned)tile_rows, (unsigned)tile_cols, 1), 0, true};
 }
-__device__ inline int64_t tile_row() { return ((int64_t)blockIdx.z * kTileGridY + blockIdx.y) * kTileStrips + blockIdx.x % kTileStrips; }
-__device__ inline int64_t tile_col() { return blockIdx.x / kTileStrips; }
+__host__ inline TileGrid tile_strips(int64_t tile_rows, int64_t tile_cols)
+{
+    const int64_t groups = (tile_rows + 7) / 8, z = (groups + kTileGridY - 1) / kTileGridY;
+    return TileGrid{dim3((unsigned)tile_cols * 8, (unsigned)(z > 1 ? kTileGridY : groups), (unsigned)z), 0, false};
+}
+__host__ inline TileGrid tile_quantise(int64_t tile_rows, int64_t tile_cols)
+{
+    if (tile_rows > 56 || tile_cols < 2) return tile_strips(tile_rows, tile_cols);
+    return TileGrid{dim3((unsigned)(tile_rows * tile_cols)), (uint32_t)((((uint64_t)1 << 32) + tile_cols - 1) / tile_cols), false};
+}
+// Dequantisation has no parameters of its own to write and gains from strips only when its output leaves the caches (11008 x
+// 12800 75 us plain, 65 in strips, 6700 x 12800 34 and 32; 1600 x 4096 5.1 and 5.7).
+__host__ inline TileGrid tile_dequant(int64_t tile_rows, int64_t tile_cols)
+{
+    return tile_rows <= 56 || tile_rows * tile_cols < 8192 ? tile_plain(tile_rows, tile_cols) : tile_strips(tile_rows, tile_cols);
+}
+struct Tile {
+    int64_t row, col;
+};
+// (a workgroup without a tile gets a row behind the last one)
+__device__ inline Tile tile_in_strips(int64_t tile_rows)
+{
+    const uint32_t first = (blockIdx.z * kTileGridY + blockIdx.y) * 8, col = blockIdx.x / 8;
+    return Tile{first + (blockIdx.x + (first + 8 > (uint32_t)tile_rows ? col : 0)) % 8, col};
+}
+__device__ inline Tile tile_dealt(int64_t tile_rows, int64_t tile_cols, uint32_t dealt)
+{
+    // (the reciprocal is exact: x / 8 < 2^19, at most 2^13 columns)
+    const uint32_t first = __umulhi(blockIdx.x / 8, dealt) * 8, r = blockIdx.x - first * (uint32_t)tile_cols;
+    const uint32_t left = (uint32_t)tile_rows - first;
+    if (left >= 8) return Tile{first + r % 8, r / 8};
+    return Tile{first + r % left, r / left};
+}
 
 // Quotients by one divisor, correctly rounded like w / d: with r the correctly rounded reciprocal and q0 = r w, the remainder
 // w - q0 d is exact and q0 + r (w - q0 d), rounded once, is the rounded quotient (Markstein, "Computation of elementary

@@ -93,7 +93,7 @@ __device__ inline uint32_t encode_value_fmt(float w0, const Divisor& sf, float b
 // weights is G/8 adjacent lanes.  The four finished blocks are staged in LDS and
 // written out in 16-byte pieces.
 template <int G, bool FIT, int FMT = kE0M4>
-__global__ __launch_bounds__(kThreads) void quantize_kernel(const half_t* __restrict__ W, int64_t N, int64_t K,
+__global__ __launch_bounds__(kThreads) void quantize_kernel(const half_t* __restrict__ W, int64_t N, int64_t K, uint32_t dealt,
                                                             uint4* __restrict__ packed,
                                                             half_t* __restrict__ scales_out,
                                                             half_t* __restrict__ bias_out,
@@ -104,8 +104,9 @@ __global__ __launch_bounds__(kThreads) void quantize_kernel(const half_t* __rest
     constexpr int PPB = block_bytes(G) / 16;            // 16-byte pieces per block
     __shared__ __attribute__((aligned(16))) uint32_t stage[4 * BW];
     const int t = threadIdx.x;
-    const int64_t rb64 = tile_row();
-    const int64_t kb = tile_col();
+    const int64_t tile_rows = (N + kTileRows - 1) / kTileRows;
+    const Tile own = dealt ? tile_dealt(tile_rows, k_blocks(K), dealt) : tile_in_strips(tile_rows);
+    const int64_t rb64 = own.row, kb = own.col;
     const int piece = t & 15;
     const int r = t >> 4;
     const int64_t k = kb * kBlockK + piece * 8;
@@ -221,14 +222,14 @@ __global__ __launch_bounds__(kThreads) void quantize_kernel(const half_t* __rest
 // block's parameter words; the 64 x 128 tile goes through LDS so that rows are
 // written out in 256-byte runs.
 template <int G, int FMT = kE0M4>
-__global__ __launch_bounds__(kThreads) void dequant_kernel(const uint4* __restrict__ packed, int64_t N, int64_t K,
+__global__ __launch_bounds__(kThreads) void dequant_kernel(const uint4* __restrict__ packed, int64_t N, int64_t K, bool plain,
                                                            half_t* __restrict__ W_out)
 {
     constexpr int kStride = kBlockK + 8;                // halves; +16 bytes keeps ds_write_b128 conflict-free
     __shared__ __attribute__((aligned(16))) half_t tile[kTileRows * kStride];
     const int t = threadIdx.x;
-    const int64_t rb64 = tile_row();
-    const int64_t kb = tile_col();
+    const Tile own = plain ? Tile{blockIdx.x, blockIdx.y} : tile_in_strips((N + kTileRows - 1) / kTileRows);
+    const int64_t rb64 = own.row, kb = own.col;
     const int64_t nrb = row_blocks(N);
     const PackedLayout<G> lay(K);
     {
@@ -280,14 +281,14 @@ __global__ __launch_bounds__(kThreads) void dequant_kernel(const uint4* __restri
 }
 
 template <int G>
-__global__ __launch_bounds__(kThreads) void unpack_kernel(const uint4* __restrict__ packed, int64_t N, int64_t K,
+__global__ __launch_bounds__(kThreads) void unpack_kernel(const uint4* __restrict__ packed, int64_t N, int64_t K, bool plain,
                                                           uint8_t* __restrict__ out, int shift)
 {
     constexpr int kStride = kBlockK + 16;               // bytes per row in LDS
     __shared__ __attribute__((aligned(16))) uint8_t tile[kTileRows * kStride];
     const int t = threadIdx.x;
-    const int64_t rb64 = tile_row();
-    const int64_t kb = tile_col();
+    const Tile own = plain ? Tile{blockIdx.x, blockIdx.y} : tile_in_strips((N + kTileRows - 1) / kTileRows);
+    const int64_t rb64 = own.row, kb = own.col;
     const int64_t nrb = row_blocks(N);
     const PackedLayout<G> lay(K);
     {
@@ -327,7 +328,8 @@ int launch_quantize(const void* W, int64_t N, int64_t K, int group, void* packed
                     const void* scales_in, const void* bias_in, bool fit, int format, hipStream_t stream)
 {
     const bool int4 = format == kInt4;
-    const dim3 grid = tile_grid((N + kTileRows - 1) / kTileRows, k_blocks(K)), block(kThreads);
+    const TileGrid tiles = tile_quantise((N + kTileRows - 1) / kTileRows, k_blocks(K));
+    const dim3 block(kThreads);
     const half_t* w = static_cast<const half_t*>(W);
     uint4* c = static_cast<uint4*>(packed);
     half_t* so = static_cast<half_t*>(scales);
@@ -336,12 +338,12 @@ int launch_quantize(const void* W, int64_t N, int64_t K, int group, void* packed
     const half_t* bi = static_cast<const half_t*>(bias_in);
 #define E0M4_LAUNCH_Q(G)                                                                              \
     do {                                                                                              \
-        if (int4) hipLaunchKernelGGL((quantize_kernel<G, true, kInt4>), grid, block, 0, stream, w, N, K, c, so, bo, si, bi); \
-        else if (format == kE0M3) hipLaunchKernelGGL((quantize_kernel<G, true, kE0M3>), grid, block, 0, stream, w, N, K, c, so, bo, si, bi); \
-        else if (format == kBf16 && fit) hipLaunchKernelGGL((quantize_kernel<G, true, kBf16>), grid, block, 0, stream, w, N, K, c, so, bo, si, bi); \
-        else if (format == kBf16) hipLaunchKernelGGL((quantize_kernel<G, false, kBf16>), grid, block, 0, stream, w, N, K, c, so, bo, si, bi); \
-        else if (fit) hipLaunchKernelGGL((quantize_kernel<G, true>), grid, block, 0, stream, w, N, K, c, so, bo, si, bi); \
-        else hipLaunchKernelGGL((quantize_kernel<G, false>), grid, block, 0, stream, w, N, K, c, so, bo, si, bi);    \
+        if (int4) hipLaunchKernelGGL((quantize_kernel<G, true, kInt4>), tiles.grid, block, 0, stream, w, N, K, tiles.dealt, c, so, bo, si, bi); \
+        else if (format == kE0M3) hipLaunchKernelGGL((quantize_kernel<G, true, kE0M3>), tiles.grid, block, 0, stream, w, N, K, tiles.dealt, c, so, bo, si, bi); \
+        else if (format == kBf16 && fit) hipLaunchKernelGGL((quantize_kernel<G, true, kBf16>), tiles.grid, block, 0, stream, w, N, K, tiles.dealt, c, so, bo, si, bi); \
+        else if (format == kBf16) hipLaunchKernelGGL((quantize_kernel<G, false, kBf16>), tiles.grid, block, 0, stream, w, N, K, tiles.dealt, c, so, bo, si, bi); \
+        else if (fit) hipLaunchKernelGGL((quantize_kernel<G, true>), tiles.grid, block, 0, stream, w, N, K, tiles.dealt, c, so, bo, si, bi); \
+        else hipLaunchKernelGGL((quantize_kernel<G, false>), tiles.grid, block, 0, stream, w, N, K, tiles.dealt, c, so, bo, si, bi);    \
     } while (0)
     switch (group) {
         case 32: E0M4_LAUNCH_Q(32); break;
@@ -355,32 +357,33 @@ int launch_quantize(const void* W, int64_t N, int64_t K, int group, void* packed
 
 int launch_dequant(const void* packed, int64_t N, int64_t K, int group, void* W_out, int format, hipStream_t stream)
 {
-    const dim3 grid = tile_grid((N + kTileRows - 1) / kTileRows, k_blocks(K)), block(kThreads);
+    const TileGrid tiles = tile_dequant((N + kTileRows - 1) / kTileRows, k_blocks(K));
+    const dim3 block(kThreads);
     const uint4* c = static_cast<const uint4*>(packed);
     half_t* o = static_cast<half_t*>(W_out);
     const bool int4 = format == kInt4;
     if (format == kBf16) {
         switch (group) {
-            case 32: hipLaunchKernelGGL((dequant_kernel<32, kBf16>), grid, block, 0, stream, c, N, K, o); break;
-            case 64: hipLaunchKernelGGL((dequant_kernel<64, kBf16>), grid, block, 0, stream, c, N, K, o); break;
-            case 128: hipLaunchKernelGGL((dequant_kernel<128, kBf16>), grid, block, 0, stream, c, N, K, o); break;
+            case 32: hipLaunchKernelGGL((dequant_kernel<32, kBf16>), tiles.grid, block, 0, stream, c, N, K, tiles.plain, o); break;
+            case 64: hipLaunchKernelGGL((dequant_kernel<64, kBf16>), tiles.grid, block, 0, stream, c, N, K, tiles.plain, o); break;
+            case 128: hipLaunchKernelGGL((dequant_kernel<128, kBf16>), tiles.grid, block, 0, stream, c, N, K, tiles.plain, o); break;
             default: return E0M4_ERR_GROUP;
         }
         return check_launch();
     }
     if (int4) {
         switch (group) {
-            case 32: hipLaunchKernelGGL((dequant_kernel<32, kInt4>), grid, block, 0, stream, c, N, K, o); break;
-            case 64: hipLaunchKernelGGL((dequant_kernel<64, kInt4>), grid, block, 0, stream, c, N, K, o); break;
-            case 128: hipLaunchKernelGGL((dequant_kernel<128, kInt4>), grid, block, 0, stream, c, N, K, o); break;
+            case 32: hipLaunchKernelGGL((dequant_kernel<32, kInt4>), tiles.grid, block, 0, stream, c, N, K, tiles.plain, o); break;
+            case 64: hipLaunchKernelGGL((dequant_kernel<64, kInt4>), tiles.grid, block, 0, stream, c, N, K, tiles.plain, o); break;
+            case 128: hipLaunchKernelGGL((dequant_kernel<128, kInt4>), tiles.grid, block, 0, stream, c, N, K, tiles.plain, o); break;
             default: return E0M4_ERR_GROUP;
         }
         return check_launch();
     }
     switch (group) {
-        case 32: hipLaunchKernelGGL(dequant_kernel<32>, grid, block, 0, stream, c, N, K, o); break;
-        case 64: hipLaunchKernelGGL(dequant_kernel<64>, grid, block, 0, stream, c, N, K, o); break;
-        case 128: hipLaunchKernelGGL(dequant_kernel<128>, grid, block, 0, stream, c, N, K, o); break;
+        case 32: hipLaunchKernelGGL(dequant_kernel<32>, tiles.grid, block, 0, stream, c, N, K, tiles.plain, o); break;
+        case 64: hipLaunchKernelGGL(dequant_kernel<64>, tiles.grid, block, 0, stream, c, N, K, tiles.plain, o); break;
+        case 128: hipLaunchKernelGGL(dequant_kernel<128>, tiles.grid, block, 0, stream, c, N, K, tiles.plain, o); break;
         default: return E0M4_ERR_GROUP;
     }
     return check_launch();
@@ -388,13 +391,15 @@ int launch_dequant(const void* packed, int64_t N, int64_t K, int group, void* W_
 
 int launch_unpack(const void* packed, int64_t N, int64_t K, int group, void* out, hipStream_t stream, int shift)
 {
-    const dim3 grid = tile_grid((N + kTileRows - 1) / kTileRows, k_blocks(K)), block(kThreads);
+    const int64_t tile_rows = (N + kTileRows - 1) / kTileRows;
+    const TileGrid tiles = tile_rows < 1 << 23 ? tile_plain(tile_rows, k_blocks(K)) : tile_strips(tile_rows, k_blocks(K));    // (a grid's x holds 2^24)
+    const dim3 block(kThreads);
     const uint4* c = static_cast<const uint4*>(packed);
     uint8_t* o = static_cast<uint8_t*>(out);
     switch (group) {
-        case 32: hipLaunchKernelGGL(unpack_kernel<32>, grid, block, 0, stream, c, N, K, o, shift); break;
-        case 64: hipLaunchKernelGGL(unpack_kernel<64>, grid, block, 0, stream, c, N, K, o, shift); break;
-        case 128: hipLaunchKernelGGL(unpack_kernel<128>, grid, block, 0, stream, c, N, K, o, shift); break;
+        case 32: hipLaunchKernelGGL(unpack_kernel<32>, tiles.grid, block, 0, stream, c, N, K, tiles.plain, o, shift); break;
+        case 64: hipLaunchKernelGGL(unpack_kernel<64>, tiles.grid, block, 0, stream, c, N, K, tiles.plain, o, shift); break;
+        case 128: hipLaunchKernelGGL(unpack_kernel<128>, tiles.grid, block, 0, stream, c, N, K, tiles.plain, o, shift); break;
         default: return E0M4_ERR_GROUP;
     }
     return check_launch();

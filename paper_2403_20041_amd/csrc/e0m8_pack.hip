@@ -59,7 +59,7 @@ __host__ __device__ inline uint32_t code_of(uint32_t word, int i)
 // k = 8 * (t % 16) .. of row t / 16 of row block i (i = 0..3): two packed words.  A group of G weights is
 // G/8 adjacent lanes.
 template <int G>
-__global__ __launch_bounds__(kThreads) void quantize8_kernel(const half_t* __restrict__ W, int64_t N, int64_t K,
+__global__ __launch_bounds__(kThreads) void quantize8_kernel(const half_t* __restrict__ W, int64_t N, int64_t K, uint32_t dealt,
                                                              uint4* __restrict__ packed,
                                                              half_t* __restrict__ scales_out,
                                                              half_t* __restrict__ bias_out)
@@ -68,8 +68,8 @@ __global__ __launch_bounds__(kThreads) void quantize8_kernel(const half_t* __res
     constexpr int PPB = block_bytes(128) / 16;
     __shared__ __attribute__((aligned(16))) uint32_t stage[8 * BW];     // [row block i][block half h]
     const int t = threadIdx.x;
-    const int64_t rb64 = tile_row();
-    const int64_t kb2 = tile_col();                     // pair of blocks
+    const Tile own = dealt ? tile_dealt((N + 63) / 64, (K + 127) / 128, dealt) : tile_in_strips((N + 63) / 64);
+    const int64_t rb64 = own.row, kb2 = own.col;        // (kb2: pair of blocks)
     const int piece = t & 15, r = t >> 4;
     const int h = piece >> 3, p8 = piece & 7;           // block of the pair, piece inside the block
     const int q = p8 >> 1, w0 = (p8 & 1) * 2;           // chunk, first of the two words
@@ -154,13 +154,14 @@ __global__ __launch_bounds__(kThreads) void unpack8_kernel(const uint4* __restri
 // One workgroup: 64 rows x 128 weights.  Wavefront i dequantises the two blocks of row block 4 rb64 + i; the tile goes
 // through LDS so that rows are written out in 256-byte runs (32-byte pieces straight from the lanes: 27392 x 4096 128 us,
 // now 62; 8000 x 11008 67 and 43).
-__global__ __launch_bounds__(kThreads) void dequant8_kernel(const uint4* __restrict__ packed, int64_t N, int64_t K,
+__global__ __launch_bounds__(kThreads) void dequant8_kernel(const uint4* __restrict__ packed, int64_t N, int64_t K, bool plain,
                                                             half_t* __restrict__ W_out)
 {
     constexpr int kStride = 128 + 8;                    // halves; +16 bytes keeps the 16-byte writes conflict-free
     __shared__ __attribute__((aligned(16))) half_t tile[64 * kStride];
     const int t = threadIdx.x;
-    const int64_t rb64 = tile_row(), kb2 = tile_col();
+    const Tile own = plain ? Tile{blockIdx.x, blockIdx.y} : tile_in_strips((N + 63) / 64);
+    const int64_t rb64 = own.row, kb2 = own.col;
     const PackedLayout<128> lay(2 * K);
     const int i = t >> 6, lane = t & 63, q = lane >> 4, r = lane & 15;
     const int64_t rb = rb64 * 4 + i;
@@ -202,13 +203,14 @@ __global__ __launch_bounds__(kThreads) void dequant8_kernel(const uint4* __restr
 int launch_quantize8(const void* W, int64_t N, int64_t K, int group, void* packed, void* scales, void* bias,
                      hipStream_t stream)
 {
-    const dim3 grid = tile_grid((N + 63) / 64, (K + 127) / 128), block(kThreads);
+    const TileGrid tiles = tile_quantise((N + 63) / 64, (K + 127) / 128);
+    const dim3 block(kThreads);
     const half_t* w = static_cast<const half_t*>(W);
     uint4* c = static_cast<uint4*>(packed);
     half_t* so = static_cast<half_t*>(scales);
     half_t* bo = static_cast<half_t*>(bias);
-    if (group == 64) hipLaunchKernelGGL(quantize8_kernel<64>, grid, block, 0, stream, w, N, K, c, so, bo);
-    else if (group == 128) hipLaunchKernelGGL(quantize8_kernel<128>, grid, block, 0, stream, w, N, K, c, so, bo);
+    if (group == 64) hipLaunchKernelGGL(quantize8_kernel<64>, tiles.grid, block, 0, stream, w, N, K, tiles.dealt, c, so, bo);
+    else if (group == 128) hipLaunchKernelGGL(quantize8_kernel<128>, tiles.grid, block, 0, stream, w, N, K, tiles.dealt, c, so, bo);
     else return E0M4_ERR_GROUP;
     return check_launch();
 }
@@ -219,11 +221,12 @@ int launch_dequant8(const void* packed, int64_t N, int64_t K, void* W_out, void*
     const int64_t blocks = (words + kThreads - 1) / kThreads;
     if (blocks > 0x7fffffffLL) return E0M4_ERR_SHAPE;
     const uint4* c = static_cast<const uint4*>(packed);
+    const TileGrid tiles = tile_dequant((N + 63) / 64, (K + 127) / 128);
     if (codes_out)
         hipLaunchKernelGGL(unpack8_kernel, dim3((unsigned)blocks), dim3(kThreads), 0, stream, c, N, K,
                            static_cast<uint8_t*>(codes_out));
     else
-        hipLaunchKernelGGL(dequant8_kernel, tile_grid((N + 63) / 64, (K + 127) / 128), dim3(kThreads), 0, stream, c, N, K,
+        hipLaunchKernelGGL(dequant8_kernel, tiles.grid, dim3(kThreads), 0, stream, c, N, K, tiles.plain,
                            static_cast<half_t*>(W_out));
     return check_launch();
 }

@@ -263,3 +263,15 @@ def test_full_size_layer_shapes(e0m4, oracle):
         cols = np.array([0, 15, 16, 255, 256, N // 2, N - 257, N - 1])
         Yc, adc = oracle.matmul(X, What[cols])
         check_matmul(torch.from_numpy(np.ascontiguousarray(Y[:, cols])), Yc, adc, name + " prefill cols")
+
+
+@pytest.mark.parametrize("tile_rows", [1, 2, 3, 5, 6, 7, 8, 9, 11, 12, 14, 15, 16, 17])
+def test_offline_kernels_visit_every_tile(e0m4, oracle, tile_rows):
+    # the quantisers go through 64 x 128 tiles in strips of tile rows, which end in an incomplete group here; 4-bit and 8-bit
+    # codes, parameters and dequantised weights bit for bit
+    from test_gpu_parity import assert_quantize_exact as assert_quantize4_exact
+
+    for N, K, G in ((64 * tile_rows - 3, 640, 64), (64 * tile_rows, 128, 128), (64 * tile_rows - 63, 1216, 64)):
+        W = synth_inputs.weights(N, K, seed=790 + N + K)
+        assert_quantize_exact(e0m4, oracle, W, G)
+        assert_quantize4_exact(e0m4, oracle, W, G)
