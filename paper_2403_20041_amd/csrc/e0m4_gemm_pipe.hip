@@ -560,8 +560,10 @@ __global__ __launch_bounds__(64 * WGM * WGN * KS, 2) void gemm_pipe_kernel(const
     // own (the K loop's stages are free by then) and reads back eight neighbouring columns per lane.  The residual comes in
     // the same way, the next piece's while this one's is used.  Element by element, the residual's loads -- one 2-byte load
     // and one 2-byte store after the other, each masked by itself -- were a serial
-    // chain of 128 round trips to memory: 2048 x 5120 x 5120 with a residual (160 large tiles) 198 us, now 144; without a
-    // residual the stores alone: 2048 x 15360 x 5120 300 -> 291, gated 2048 x 27392 x 5120 538 -> 514.
+    // chain of 128 round trips to memory: 2048 x 5120 x 5120 with a residual (160 large tiles) 198 us, now 144; gated 2048 x
+    // 27392 x 5120 538 -> 514.  Whole tiles without a residual are stored element by element: nothing waits for those stores,
+    // and turning the sums around costs 0.3 - 0.5 us at the end of a launch (1024 x 8192 x 256 10.9 us, element by element 10.5);
+    // tiles that the matrix ends in need a mask per element there (1000 x 4096 x 512 10.4 us, in pieces 9.8).
     constexpr uint32_t kTurnBytes = 32 * (32 + 4) * 4;  // per wavefront: 32 x 32 or 16 x 64 sums, rows padded by 16 bytes
     static_assert(kTurnBytes >= 16 * (64 + 4) * 4 && kTurnBytes * WGM * WGN <= (uint32_t)kStages * kStageBytes, "fits the stages");
     // COLS: columns of the wavefront's results (64, or 32 gated); value(i, r, j): accumulator register r of block i (j)
@@ -750,7 +752,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KS, 2) void gemm_pipe_kernel(const
     out_t* yt = reinterpret_cast<out_t*>(Y) + m0 * N + n0;
     if (out_mode == 1)
         store_tile(partial + ((size_t)split * (size_t)M + (size_t)m0) * (size_t)N + (size_t)n0);
-    else if ((n32 & 7u) == 0)
+    else if ((n32 & 7u) == 0 && (KS == 2 || (FUSED && fu.residual) || M - m0 < BM || N - n0 < BN))
         write_rows(std::integral_constant<int, 64>{}, [&](int i, int r, int j) { return acc[i][j][r]; }, yt,
                    FUSED && fu.residual ? fu.residual + m0 * N + n0 : nullptr, n32, wn, cols_left);
     else
