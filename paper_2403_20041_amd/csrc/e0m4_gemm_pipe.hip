@@ -968,9 +968,12 @@ SkPlan sk_plan(int64_t tiles, int64_t K, int bm, int bn, bool allowed)
 // wavefronts per SIMD hide each other's waits.  M = 700: 4096 x 13696 (176 tiles) 151 -> 114 us, 4608 x 4096 (198) 50 -> 42;
 // M = 100: 27392 x 4096 (214) 54 -> 44, 4096 x 4096 (32) 46 -> 35.  With more tiles than compute units there are two
 // workgroups per unit anyway, and two of the larger ones do not fit: M = 700, 27392 x 4096 (1177) 205 -> 219.
+// On shorter rows the longer start and the exchange of the sums cost more than they give: M = 512, N = 8192 (256 tiles) at K =
+// 256 8.8 us against 7.5, at 768 12.6 against 12.5, at 1024 15.1 against 14.9, but at 1536 19.0 against 20.2.
+constexpr int64_t kHalvesMinK = 18 * BK;
 bool k_halves(const PipeTile& t, int64_t M, int64_t N, int64_t K)
 {
-    return t.bm == 64 && K >= 4 * BK && ((M + 63) / 64) * ((N + 255) / 256) <= kComputeUnits;
+    return t.bm == 64 && K >= kHalvesMinK && ((M + 63) / 64) * ((N + 255) / 256) <= kComputeUnits;
 }
 // (the cases above within 12 %, whatever the number of tiles: a compute unit has two wavefronts per SIMD or none)
 constexpr double kHalvesUsPerPair = 1.1;                // us per pair of K slices of the whole K

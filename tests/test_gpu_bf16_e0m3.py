@@ -156,9 +156,10 @@ def test_bf16_gemm_every_kernel_and_tile(e0m4, oracle, variant, M, N, K, G):
     assert torch.equal(Y.view(torch.int16), Y2.view(torch.int16))
 
 
-@pytest.mark.parametrize("M,N,K,G", [(129, 203, 256, 64), (191, 520, 384, 128), (300, 260, 640, 32), (64, 256, 1152, 128), (257, 16, 4224, 64)])
+@pytest.mark.parametrize("M,N,K,G", [(129, 203, 256, 64), (191, 520, 384, 128), (300, 260, 640, 32), (64, 256, 1152, 128), (257, 16, 4224, 64),
+                                     (129, 203, 1280, 64), (191, 520, 1408, 128), (300, 260, 1664, 32), (65, 264, 1536, 128)])
 def test_bf16_gemm_k_halves(e0m4, oracle, M, N, K, G):
-    # few flat tiles: a workgroup's two halves take one half of K each; even and odd numbers of pairs of K slices, numbers
+    # few flat tiles: a workgroup's two halves take one half of K each (from K = 1152 on); even and odd numbers of pairs of K slices, numbers
     # of pairs that do not fill the unrolled loop, ragged rows and columns, row lengths that are no multiple of 8
     codes, What, _ = assert_bf16_quantize_exact(e0m4, oracle, synth_inputs.weights_bf16(N, K, seed=3680 + N + K), G)
     X = synth_inputs.activations_bf16(M, K, seed=3690 + M)
