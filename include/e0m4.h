@@ -132,7 +132,7 @@ int e0m4_unpack_codes(const void* codes, int64_t N, int64_t K, int group, void* 
  *            that kernel on equal chunks of at most 16 rows in one launch,
  *            when its workgroups make at most two rounds on the compute
  *            units (three on small weights); otherwise, any group, N * K <= 7e7 (and
- *            K <= 9216 for M > 48), the dequantising kernel.
+ *            256 <= K <= 9216 for M > 48), the dequantising kernel.
  *   M >= 9 otherwise, and 2 <= M <= 8 when M * N * K is about 3.8e8 or
  *            more (the vector kernel's time grows with M): MFMA GEMM path
  *            (tiles of 64 x 256, 128 x 256 or 256 x 256 outputs, whichever
@@ -258,7 +258,7 @@ int e0m4_kv_append(void* cache_f16, int64_t max_seq, int64_t row_elems,
  *     e0m8_workspace_bytes() bytes under the rules of e0m4_matmul (17 <= M <=
  *     32 with K <= 2048 and N * K <= 1e7: the matrix-core variant on two
  *     chunks of rows in one launch instead; otherwise M <= 64 with N * K <= 1e8,
- *     and K <= 9216 for M > 48: the dequantising kernel of e0m4_matmul).  Other M > 16:
+ *     and 256 <= K <= 9216 for M > 48: the dequantising kernel of e0m4_matmul).  Other M > 16:
  *     the decode kernel on 8 rows of X at a time (needs N % 8 == 0).
  * Pointer, alignment, stream and error rules as for the E0M4 entry points.
  */
@@ -305,8 +305,8 @@ int e0m3_unpack_codes(const void* codes, int64_t N, int64_t K, int group, void* 
  *   e0m4_bf16_matmul: M <= 8 the decode kernel with bfloat16 dot products
  *   (a shift and a mask-or per pair of codes; scale and bias in fp32); larger M
  *   with the weights dequantised in registers (fp32 fused multiply-add, one
- *   rounding to bfloat16): up to 64 rows, and 128 on small weights, the
- *   dequantising kernel of e0m4_matmul, beyond that its pipelined MFMA kernel
+ *   rounding to bfloat16): up to 64 rows, and 128 on small weights (not on the
+ *   shortest rows), the dequantising kernel of e0m4_matmul, beyond that its pipelined MFMA kernel
  *   in whole tiles (no workspace, so no split along K but for two halves inside
  *   a workgroup); when K is not a multiple of 128 an MFMA kernel with
  *   128 x 128 tiles that dequantises into LDS.

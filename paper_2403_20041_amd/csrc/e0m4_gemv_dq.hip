@@ -359,6 +359,8 @@ bool gemv_dq_supported(int64_t M, int64_t N, int64_t K, int group)
 //   bfloat16: up to 64 rows always (1.1 - 7.8: the GEMM has whole tiles only).  65 to 128 rows in two parts, against 64 x 256
 //     tiles with K halves, where a workgroup has few row blocks: 1.2 - 3.1; at M = 100 4096 x 4096 34.8 -> 21.1 us, 4096 x 13696
 //     102 -> 52, but 32768 x 2048 (8 row blocks) 25 -> 37, 27392 x 4096 43 -> 63.
+//   On the shortest rows most wavefronts have no k block of their own, and many rows of X cost the others time: M = 64, 16384 x
+//     128 6.0 us against 4.9; in two parts M = 128, 8192 x 256 7.7 against 6.2, 8192 x 512 7.9 against 8.3.
 //   Groups of 32 and 64 up to 16 rows: always (1.3 - 3.1, the vector kernel's calls among them).
 //   17 to 64 rows, against K splits: 1.1 - 2.7 while the weights are few enough that reading X again in every workgroup is
 //     the smaller part; beyond the lines below 0.9 - 1.4, the more the fewer the rows.
@@ -368,9 +370,10 @@ bool gemv_dq_pays(int64_t M, int64_t N, int64_t K, int group, DqFormat format)
     if (M < 3 || !make_dq_plan(M, N, K, p)) return false;
     const double NK = (double)N * (double)K;
     if (format == kDqFormatBf16)
-        return M > kGemvMaxM && N <= (int64_t)1 << 24 && (M <= kDqMaxM || (NK <= 7e7 && p.wr * p.r <= 2));
+        return M > kGemvMaxM && N <= (int64_t)1 << 24 &&
+               (M <= 48 || (M <= kDqMaxM ? K >= 256 : K >= 512 && NK <= 7e7 && p.wr * p.r <= 2));
     if (M > kDqMaxM) return false;
-    if (M > 16) return NK <= (format == kDqFormatE8 ? 1e8 : 7e7) && (M <= 48 || K <= 9216);
+    if (M > 16) return NK <= (format == kDqFormatE8 ? 1e8 : 7e7) && (M <= 48 || (K >= 256 && K <= 9216));
     return format == kDqFormatFp16 && group != 128;
 }
 

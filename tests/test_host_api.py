@@ -300,3 +300,14 @@ def test_e0m8_validation_and_sizes(L):
     assert (L.e0m8_fused_workspace_bytes(1024, 4096, 4096, 128, 1, 0) - L.e0m8_fused_workspace_bytes(1024, 4096, 4096, 128, 0, 0)
             == 1024 * 4096 * 2)                                                         # the normalised copy of X
     assert L.e0m8_fused_workspace_bytes(1024, 4096, 13696, 128, 0, 0) == L.e0m4_fused_workspace_bytes(1024, 4096, 13696, 128, 0, 0) > 0
+
+
+def test_workspace_on_either_side_of_the_small_batch_rules(L):
+    """The dequantising small-batch kernel needs no workspace; past its lines the GEMM splits K and does."""
+    L.e0m8_workspace_bytes.restype = ctypes.c_size_t
+    L.e0m8_workspace_bytes.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int]
+    assert L.e0m4_workspace_bytes(64, 4096, 9216, 64) == 0 and L.e0m4_workspace_bytes(64, 4096, 9344, 64) > 0      # K
+    assert L.e0m4_workspace_bytes(48, 4096, 13696, 64) == 0 and L.e0m4_workspace_bytes(49, 4096, 13696, 64) > 0    # rows
+    assert L.e0m4_workspace_bytes(32, 8544, 8192, 64) == 0 and L.e0m4_workspace_bytes(32, 8560, 8192, 64) > 0      # N * K
+    assert L.e0m8_workspace_bytes(40, 12200, 8192, 128) == 0 and L.e0m8_workspace_bytes(40, 12216, 8192, 128) > 0
+    assert L.e0m4_workspace_bytes(64, 4096, 4096, 64) == 0 and L.e0m4_workspace_bytes(65, 4096, 4096, 64) > 0
