@@ -100,7 +100,8 @@ __device__ inline int x_unit_off(int q, int w, int hl) { return ((q * 4 + (w >> 
 // PHASED: M rows of X do not fit the LDS.  K is walked in phases of kb_phase blocks: every phase stages its
 // part of X, visits all row blocks of the workgroup and adds to the wavefront sums, which stay in LDS
 // (`late`) until the last phase.  The weights are still read exactly once.
-template <int W, bool FUSED, bool XREG, bool E8 = false, bool PHASED = false, int GS = 1>
+// KEEP: with an rms-norm, X stays in registers from the pass over its squares (keeps_x below).
+template <int W, bool FUSED, bool XREG, bool E8 = false, bool PHASED = false, int GS = 1, bool KEEP = false>
 __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restrict__ X,
                                                            const uint4* __restrict__ packed, half_t* __restrict__ Y,
                                                            int M, uint32_t N32, uint32_t K32, int step_slots_arg,
@@ -122,6 +123,7 @@ __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restr
         M = min(M, fu.m_total - row0);
     }
     static_assert(!(PHASED && XREG), "a wavefront meets other k blocks in every phase");
+    static_assert(!KEEP || (FUSED && W <= 8 && !PHASED && GS == 1 && !(XREG && E8)), "instances that keep X");
     static_assert(GS == 1 || ((GS == 2 || GS == 4) && !E8 && !XREG), "several groups per block: 4-bit codes, X from LDS");
     constexpr int kThreads = W * 64;
     constexpr int G = kG / GS;                          // group size
@@ -230,7 +232,7 @@ __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restr
     // The pieces (one per lane and row of X) stay in registers until the row scales are known.
     constexpr int kItemPieces = kSuper * XBB / 16;      // pieces of one row of X per work item: 64 (32 for 8-bit codes)
     // (not with sixteen wavefronts: 64 more registers do not fit their budget of 128)
-    constexpr bool kOwn = W <= 8 && XREG && E8, kKeep = W <= 8 && FUSED && !PHASED && GS == 1 && !kOwn, kKeepTwo = kKeep && !XREG;
+    constexpr bool kOwn = W <= 8 && XREG && E8, kKeepTwo = KEEP && !XREG;
     const bool own_norm = kOwn && normed && step_slots == 1;
     const int pc_own = si * kItemPieces + lane;
     const bool own_ok = lane < kItemPieces && pc_own < pieces;      // (a last work item may reach beyond the row's blocks)
@@ -267,12 +269,10 @@ __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restr
             }
         }
     }
-    // Otherwise, with at most sixteen pieces per thread -- one per row of X, or two of up to eight rows -- every thread keeps
-    // its pieces from the first pass, and X is read once: 4608 x 4096 in 8-bit codes at M = 16 17.0 -> 14.7 us, gated 27392 x
-    // 4096 36.5 -> 33.2; 15360 x 5120 at M = 8 18.4 -> 16.6.  (Not with K in phases or several groups per block, where it
-    // gained nothing, nor where the pieces leave more than three threads in eight without one: 2944 x 2176 lost 3 %.)  4-bit
-    // codes with XREG and step_slots == 1: thread t's piece is one of its own wavefront's four blocks.
-    const bool keep_norm = kKeep && normed && (cpr == 1 || (kKeepTwo && cpr == 2 && M <= 8)) && (XREG || pieces * 8 >= cpr * kThreads * 5);
+    // KEEP: at most sixteen pieces per thread -- one per row of X, or two of up to eight rows -- and every thread keeps its
+    // pieces from the first pass, so that X is read once.  4-bit codes with XREG and step_slots == 1: thread t's piece is one of
+    // its own wavefront's four blocks.
+    const bool keep_norm = KEEP && (!XREG || (normed && cpr == 1));
     const bool keep_own = XREG && step_slots == 1;
     half8_t g_keep[2] = {zero8, zero8};
     auto keep_pass = [&](auto chunks_c) {               // sums in the order of the pass below: chunk after chunk, lanes, wavefronts
@@ -778,22 +778,47 @@ bool make_mfma_plan(int64_t M_rows, int64_t N, int64_t K, MfmaPlan& p, int unit 
     return true;
 }
 
-template <int W, bool FUSED, bool XREG, bool E8 = false, bool PHASED = false, int GS = 1>
-int launch_mfma_x(const MfmaPlan& p, const void* X, int64_t M, const void* packed, int64_t N, int64_t K, void* Y,
+template <int W, bool FUSED, bool XREG, bool E8, bool PHASED, int GS, bool KEEP>
+int launch_mfma_keep(const MfmaPlan& p, const void* X, int64_t M, const void* packed, int64_t N, int64_t K, void* Y,
                   hipStream_t stream, const GemvFusion& fu)
 {
     if (PHASED != (p.kb_phase > 0) || (PHASED && !p.late) || p.lds_bytes > (size_t)kLdsLimitBytes) return E0M4_ERR_SHAPE;
     static std::atomic<uint64_t> lds_allowed{0};
-    const int arc = allow_dynamic_lds(reinterpret_cast<const void*>(&gemv_mfma_kernel<W, FUSED, XREG, E8, PHASED, GS>),
+    const int arc = allow_dynamic_lds(reinterpret_cast<const void*>(&gemv_mfma_kernel<W, FUSED, XREG, E8, PHASED, GS, KEEP>),
                                       kLdsLimitBytes, lds_allowed);
     if (arc != E0M4_OK) return arc;
     // (M: rows per chunk; fu.m_total: all rows, when there are several chunks)
     const unsigned chunks = fu.m_total > 0 ? (unsigned)((fu.m_total + M - 1) / M) : 1u;
-    hipLaunchKernelGGL((gemv_mfma_kernel<W, FUSED, XREG, E8, PHASED, GS>), dim3((unsigned)p.grid, chunks), dim3(W * 64),
+    hipLaunchKernelGGL((gemv_mfma_kernel<W, FUSED, XREG, E8, PHASED, GS, KEEP>), dim3((unsigned)p.grid, chunks), dim3(W * 64),
                        p.lds_bytes, stream, static_cast<const half_t*>(X), static_cast<const uint4*>(packed),
                        static_cast<half_t*>(Y), (int)M, (uint32_t)N, (uint32_t)K, p.step_slots, p.step_item, p.rb_base,
                        p.rb_rem, p.late, p.pieces_magic, p.kb_phase, p.pieces_magic_last, fu);
     return check_launch();
+}
+
+// Whether X is kept from the norm's first pass: one piece of eight elements per thread and row, or two of up to eight rows.
+// 4608 x 4096 in 8-bit codes at M = 16 17.0 -> 14.7 us, gated 27392 x 4096 36.5 -> 33.2; 15360 x 5120 at M = 8 18.4 -> 16.6.
+// Not with K in phases or several groups per block, where it gained nothing, nor where the pieces leave more than three
+// threads in eight without one: 2944 x 2176 lost 3 %.  In instances of its own, since the registers it takes cost the other
+// launches 0.1 - 0.2 us; but with XREG, where they fit, decided in the kernel (two instances: 4096 x 4096 at M = 16 9.5 ->
+// 9.9 us).
+bool keeps_x(const GemvFusion& fu, int threads, bool e8, int64_t M, int64_t K)
+{
+    const int64_t pieces = e8 ? k_blocks(2 * K) * 8 : k_blocks(K) * 16, per_row = (pieces + threads - 1) / threads;
+    return fu.gamma && (per_row == 1 || (per_row == 2 && M <= 8)) && pieces * 8 >= per_row * threads * 5;
+}
+
+template <int W, bool FUSED, bool XREG, bool E8 = false, bool PHASED = false, int GS = 1>
+int launch_mfma_x(const MfmaPlan& p, const void* X, int64_t M, const void* packed, int64_t N, int64_t K, void* Y,
+                  hipStream_t stream, const GemvFusion& fu)
+{
+    if constexpr (FUSED && W <= 8 && !PHASED && GS == 1 && !(XREG && E8)) {
+        if (XREG || keeps_x(fu, W * 64, E8, M, K))
+            return launch_mfma_keep<W, FUSED, XREG, E8, PHASED, GS, true>(p, X, M, packed, N, K, Y, stream, fu);
+    }
+    if constexpr (!(FUSED && W <= 8 && !PHASED && GS == 1 && XREG && !E8))
+        return launch_mfma_keep<W, FUSED, XREG, E8, PHASED, GS, false>(p, X, M, packed, N, K, Y, stream, fu);
+    return E0M4_ERR_SHAPE;                              // (not reached)
 }
 
 // K in phases (plans with kb_phase > 0; they have eight or sixteen wavefronts)
