@@ -24,16 +24,21 @@
 //
 // Groups of 64 and 32 (GS = 2 or 4 groups per block; at most 8 or 4 rows of X).  A lane's 32 codes lie inside one
 // group (k-groups 2g and 2g + 1 of the block belong to group g of two, k-group g to group g of four), but an MFMA
-// adds all four k-groups.  So every row m of X is staged GS times, as row m + (16 / GS) * g with everything but the
-// k-groups of group g set to zero: the sixteen rows of the MFMA then hold, per group, the sums over that group
-// alone (the all-ones MFMAs likewise), the four output rows of a lane belong to one group, whose parameters the
-// lane picks, and the GS rows of a row of X are added when the wavefront sums are.  The loop over the weights is
-// the same as for one group per block.
+// adds all four k-groups.  So every row m of X is GS rows of the MFMA, m + (16 / GS) * g, with everything but the
+// k-groups of group g zero: the sixteen rows then hold, per group, the sums over that group alone (the all-ones MFMAs
+// likewise), the four output rows of a lane belong to one group, whose parameters the lane picks, and the GS rows of
+// a row of X are added when the wavefront sums are.  The zeros are no part of the staged X: a lane whose k-group is
+// not its row's reads the same 64 zero bytes for every block (all such lanes at once, one broadcast).  LDS then holds
+// M rows, not GS times as many, and staging moves half or a quarter of the bytes (groups of 64, M = 6: 5120 x 13696 with a
+// residual 19.7 -> 18.8 us, 15360 x 5120 with rms-norm 18.8 -> 18.2).  The loop over the weights is the same as for one group
+// per block.
 //
-// Long rows.  When M rows of X exceed the LDS, K is walked in phases: a phase stages its part of X,
-// visits that part of every row block of the workgroup and adds to the wavefront sums, which stay in
-// LDS until the last phase.  The weight stream is the same, each byte once; what a phase costs is
-// the barrier before X is replaced and the restart of the wavefronts' prefetch.
+// Long rows.  When M rows of X exceed the LDS, K is walked in phases: a phase visits its part of every row
+// block of the workgroup and adds to the wavefront sums, which stay in LDS until the last phase.  X is staged
+// for as many phases at a time as fit (ph_stage: one, but with several groups per block, whose phases are cut as
+// if LDS held GS times the rows, so that the order of the sums does not depend on what it does hold).  The weight
+// stream is the same, each byte once, and runs on from phase to phase: replacing X costs a barrier and the loads (2048 x
+// 16384 at M = 16, four phases: 20.6 us with the weights' prefetch started anew in every phase, now 19.8).
 #include "e0m4_device.h"
 #include "e0m4_host.h"
 
@@ -53,6 +58,7 @@ constexpr int kMaxM = 16;
 constexpr int kPW = block_param_words(kG);      // 16 parameter words per block
 constexpr int kXBlockBytes = kBlockK * 2;       // one row of X, one block: 256 bytes
 constexpr int kRowPadBytes = 16;                // keeps the 16 rows of X in different LDS bank groups
+constexpr int kZeroBytes = 64;                  // several groups per block: the zeros of a k-group that is not the row's
 constexpr int kLdsLimitBytes = 156 * 1024;      // of the 160 KiB of a compute unit
 constexpr int kTargetWorkgroups = 256;          // one workgroup per compute unit
 
@@ -64,22 +70,22 @@ struct MfmaPlan {
     int64_t grid;
     size_t lds_bytes;
     uint32_t pieces_magic;                      // ceil(2^32 / pieces of 8 activations per row): row of a piece by multiplication
-    // X longer than the LDS holds: K is walked in phases of kb_phase blocks (a multiple of kSuper; 0: one phase),
-    // each phase stages its part of X and visits all row blocks of the workgroup
-    int kb_phase;
-    uint32_t pieces_magic_last;                 // the same for the (shorter) last phase
+    // X longer than the LDS holds: K is walked in phases of kb_phase blocks (a multiple of kSuper; 0: one phase), each of
+    // which visits all row blocks of the workgroup; X is staged for ph_stage phases at a time
+    int kb_phase, ph_stage;
+    uint32_t pieces_magic_last;                 // the same for the (shorter) last stage
 };
 
 constexpr int kNormBytes = (16 + 1) * kMaxM * 4;        // rms-norm: per-wavefront sums of squares and the row scales
 
 // (nkb blocks of 128 4-bit codes or of 64 8-bit codes: 256 or 128 bytes of X per row and block)
-size_t lds_need(int64_t M, int64_t nkb, int waves, bool e8 = false)
+size_t lds_need(int64_t M, int64_t nkb, int waves, bool e8 = false, int gs = 1)
 {
-    return (size_t)M * (nkb * (e8 ? kXBlockBytes / 2 : kXBlockBytes) + kRowPadBytes) +
+    return (gs > 1 ? kZeroBytes : 0) + (size_t)M * (nkb * (e8 ? kXBlockBytes / 2 : kXBlockBytes) + kRowPadBytes) +
            2 * (size_t)waves * kMaxM * kBlockRows * sizeof(float) + kNormBytes;
 }
 
-// LDS for the wavefront sums of all `slots` row blocks of a workgroup at once
+// LDS for the wavefront sums of all `slots` row blocks of a workgroup at once (M: rows of the MFMA, mfma_rows below)
 size_t late_red_bytes(int64_t M, int slots, int waves)
 {
     return (size_t)slots * waves * M * kBlockRows * sizeof(float);
@@ -97,16 +103,16 @@ __device__ inline int x_unit_off(int q, int w, int hl) { return ((q * 4 + (w >> 
 // E8: the 8-bit format E0M8 (e0m8_pack.hip).  A block holds 64 weights, a lane's chunk 16, and one MFMA
 // takes the eight weights of two words per lane, each word turned into two pairs of binade values by a
 // mask-or and a rotation; there is only one kind of code slot, so one accumulator and the plain sum of X.
-// PHASED: M rows of X do not fit the LDS.  K is walked in phases of kb_phase blocks: every phase stages its
-// part of X, visits all row blocks of the workgroup and adds to the wavefront sums, which stay in LDS
-// (`late`) until the last phase.  The weights are still read exactly once.
+// PHASED: M rows of X do not fit the LDS.  K is walked in phases of kb_phase blocks: every phase visits all row blocks of
+// the workgroup and adds to the wavefront sums, which stay in LDS (`late`) until the last phase; X is staged for ph_stage
+// phases at a time.  The weights are still read exactly once.
 // KEEP: with an rms-norm, X stays in registers from the pass over its squares (keeps_x below).
 template <int W, bool FUSED, bool XREG, bool E8 = false, bool PHASED = false, int GS = 1, bool KEEP = false>
 __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restrict__ X,
                                                            const uint4* __restrict__ packed, half_t* __restrict__ Y,
                                                            int M, uint32_t N32, uint32_t K32, int step_slots_arg,
                                                            int step_item_arg, int rb_base, int rb_rem, int late,
-                                                           uint32_t pieces_magic_arg, int kb_phase,
+                                                           uint32_t pieces_magic_arg, int kb_phase, int ph_stage,
                                                            uint32_t pieces_magic_last, GemvFusion fu)
 {
     // (the arguments up to `late` fill the 14 scalar registers the launch can preload; N <= 2^31, K <= 2^20)
@@ -129,17 +135,17 @@ __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restr
     constexpr int G = kG / GS;                          // group size
     constexpr int PW = kPW * GS;                        // parameter words per block
     constexpr int SLOT = kMaxM / GS;                    // MFMA rows per group (GS > 1): row m of X is rows m + SLOT * g
-    const int Ms = GS == 1 ? M : (GS - 1) * SLOT + M;   // staged rows of X
+    const int Ms = GS == 1 ? M : (GS - 1) * SLOT + M;   // rows of the MFMA that a wavefront's sums are kept of
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     constexpr int XBB = E8 ? kXBlockBytes / 2 : kXBlockBytes;   // bytes of X per row and block
     constexpr int UB = E8 ? 16 : 32;                            // bytes per (k-group, MFMA pair) unit of a block
     const PackedLayout<G> lay(E8 ? 2 * K : K);
     const int nkb = (int)lay.nkb;
-    const int nkb_lds = PHASED ? kb_phase : nkb;        // k blocks of X that the LDS holds at a time
+    const int nkb_lds = PHASED ? kb_phase * ph_stage : nkb;     // k blocks of X that the LDS holds at a time
     const int n_ph = PHASED ? (nkb + kb_phase - 1) / kb_phase : 1;
     const int row_stride = nkb_lds * XBB + kRowPadBytes;
-    unsigned char* xs = smem;                                                   // [M] rows of X in MFMA order
-    float* norm_part = reinterpret_cast<float*>(smem + (size_t)Ms * row_stride); // [W][16] sums of squares, then [16] row scales
+    unsigned char* xs = smem + (GS > 1 ? kZeroBytes : 0);                       // [M] rows of X in MFMA order
+    float* norm_part = reinterpret_cast<float*>(xs + (size_t)M * row_stride);   // [W][16] sums of squares, then [16] row scales
     // wavefront sums: [2][W][16 m][16 n], reduced row block by row block; or, when `late` (LDS permitting),
     // [row blocks][W][M][16 n], reduced once at the end without a barrier per row block
     float* red = norm_part + kNormBytes / 4;
@@ -164,62 +170,61 @@ __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restr
         return s_ * rb_stride;
     };
 
-    // ---- per phase: the k blocks [kb_lo, kb_lo + nkb_ph) of every row block, as nsi work items per row block
-    int kb_lo = 0, nkb_ph = nkb, nsi = (nkb + kSuper - 1) / kSuper;
-    int step_slots = step_slots_arg, step_item = step_item_arg;
-    auto advance = [&](int& s_, int& i_) {              // W work items ahead
-        s_ += step_slots;
-        i_ += step_item;
-        if (i_ >= nsi) {
-            i_ -= nsi;
+    // ---- phase p: the k blocks [p * kb_phase, ...) of every row block, as nsi_of(p) work items per row block
+    const int nsi_all = PHASED ? kb_phase / kSuper : (nkb + kSuper - 1) / kSuper;
+    const int nsi_end = PHASED ? (nkb - (n_ph - 1) * kb_phase + kSuper - 1) / kSuper : nsi_all;
+    const int step_slots = PHASED ? W / nsi_all : step_slots_arg, step_item = PHASED ? W % nsi_all : step_item_arg;
+    const int step_slots_end = PHASED ? W / nsi_end : 0, step_item_end = PHASED ? W % nsi_end : 0;
+    auto nsi_of = [&](int p_) -> int { return PHASED && p_ == n_ph - 1 ? nsi_end : nsi_all; };
+    auto start = [&](int p_, int& s_, int& i_) {        // where this wavefront starts in a phase
+        s_ = 0;
+        i_ = wave;
+        while (i_ >= nsi_of(p_)) {
+            i_ -= nsi_of(p_);
             ++s_;
         }
     };
-    int slot = 0, si = 0;                               // current work item: row block slot, item inside the row block
-    int nslot = 0, nitem = 0;                           // the one after it (in flight)
+    auto advance = [&](int& p_, int& s_, int& i_) {     // W work items ahead, or on to the next phase
+        const bool end = PHASED && p_ == n_ph - 1;
+        s_ += end ? step_slots_end : step_slots;
+        i_ += end ? step_item_end : step_item;
+        if (i_ >= nsi_of(p_)) {
+            i_ -= nsi_of(p_);
+            ++s_;
+        }
+        if (PHASED && s_ >= n_rb && !end) start(++p_, s_, i_);
+    };
+    int cph = 0, slot = 0, si = 0;                      // current work item: phase, row block slot, item inside the row block
+    int nph = 0, nslot = 0, nitem = 0;                  // the one after it (in flight)
 
     // ---- the work item in flight: four code blocks and their 64 parameter words (one per lane)
     uint4 c[kSuper];
     uint32_t pwraw[GS];                                 // the item's 64 * GS parameter words: word 64 n + lane in pwraw[n]
-    auto fetch_params = [&](int fs, int fi) {           // past the end the last item is read again
+    auto fetch_params = [&](int fp, int fs, int fi) {   // past the end the last item is read again
         const bool in = fs < n_rb;
-        const uint32_t s_ = in ? fs : n_rb - 1, i_ = in ? fi : nsi - 1;
-        const uint32_t first = (uint32_t)kb_lo * PW + i_ * (kSuper * PW);       // the item's first parameter word
+        const uint32_t s_ = in ? fs : n_rb - 1, i_ = in ? fi : nsi_of(fp) - 1;
+        const uint32_t first = (uint32_t)(PHASED ? fp * kb_phase : 0) * PW + i_ * (kSuper * PW);    // the item's first parameter word
         const uint32_t soff = __builtin_amdgcn_readfirstlane(slot_off(s_) + first * 4);
         const int last = param_words_rb - 1 - (int)first;
 #pragma unroll
         for (int n = 0; n < GS; ++n)
             pwraw[n] = __builtin_amdgcn_raw_buffer_load_b32(wg_params, min(n * 64 + lane, last) * 4, (int)soff, 0);
     };
-    auto fetch_code = [&](int j, int fs, int fi) {      // k blocks beyond K: the last block again (left out of the sums)
+    auto fetch_code = [&](int j, int fp, int fs, int fi) {      // k blocks beyond K: the last block again (left out of the sums)
         const bool in = fs < n_rb;
-        const uint32_t s_ = in ? fs : n_rb - 1, i_ = in ? fi : nsi - 1;
-        const uint32_t kb = min((uint32_t)kb_lo + i_ * kSuper + j, (uint32_t)nkb - 1);
+        const uint32_t s_ = in ? fs : n_rb - 1, i_ = in ? fi : nsi_of(fp) - 1;
+        const uint32_t kb = min((uint32_t)(PHASED ? fp * kb_phase : 0) + i_ * kSuper + j, (uint32_t)nkb - 1);
         const uint32_t soff = __builtin_amdgcn_readfirstlane(slot_off(s_) + kb * kBlockCodeBytes);
         const u32x4 cv = __builtin_amdgcn_raw_buffer_load_b128(wg_codes, (int)lane_code_off, (int)soff, 0);
         c[j] = make_uint4(cv.x, cv.y, cv.z, cv.w);
     };
-    auto first_item = [&]() {                           // of a phase: where this wavefront starts, and its first requests
-        slot = 0;
-        si = wave;
-        while (si >= nsi) {
-            si -= nsi;
-            ++slot;
-        }
-        nslot = slot;
-        nitem = si;
-        advance(nslot, nitem);
-        fetch_params(slot, si);
+    start(0, slot, si);
+    nslot = slot;
+    nitem = si;
+    advance(nph, nslot, nitem);
+    fetch_params(0, slot, si);
 #pragma unroll
-        for (int j = 0; j < kSuper; ++j) fetch_code(j, slot, si);
-    };
-    if (PHASED) {
-        nkb_ph = min(kb_phase, nkb);
-        nsi = (nkb_ph + kSuper - 1) / kSuper;
-        step_slots = W / nsi;
-        step_item = W % nsi;
-    }
-    first_item();
+    for (int j = 0; j < kSuper; ++j) fetch_code(j, 0, slot, si);
 
     // ---- stage X in pieces of 8 elements (k = 8*pc .. 8*pc+7 of row m); no piece index needs a division
     const int pieces = nkb * (XBB / 16);
@@ -385,26 +390,17 @@ __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restr
         } else {
             const int kb = pc >> 4, q = (pc >> 2) & 3, w = pc & 3;
             const half4_t hpart = {v[0], v[1], v[6], v[7]}, lpart = {v[2], v[3], v[4], v[5]};
-            const half4_t none = {0, 0, 0, 0};
-#pragma unroll
-            for (int g = 0; g < GS; ++g) {              // (GS > 1: the piece in the row of its own group, zeros in the others)
-                const bool own = GS == 1 || g == q * GS / 4;
-                unsigned char* blk = xs + (size_t)(m + SLOT * g) * row_stride + kb * XBB;
-                *reinterpret_cast<half4_t*>(blk + x_unit_off(q, w, 0)) = own ? hpart : none;
-                *reinterpret_cast<half4_t*>(blk + x_unit_off(q, w, 1)) = own ? lpart : none;
-            }
+            unsigned char* blk = xs + (size_t)m * row_stride + kb * XBB;
+            *reinterpret_cast<half4_t*>(blk + x_unit_off(q, w, 0)) = hpart;
+            *reinterpret_cast<half4_t*>(blk + x_unit_off(q, w, 1)) = lpart;
         }
     };
+    if (GS > 1 && t < kZeroBytes / 4) reinterpret_cast<uint32_t*>(smem)[t] = 0;     // (read after the barrier that ends the staging)
     for (int ph = 0; ph < n_ph; ++ph) {
-        if (PHASED && ph > 0) {
-            kb_lo = ph * kb_phase;
-            nkb_ph = min(kb_phase, nkb - kb_lo);
-            nsi = (nkb_ph + kSuper - 1) / kSuper;
-            step_slots = W / nsi;
-            step_item = W % nsi;
-            first_item();                               // its requests are in flight while X is staged
-            __syncthreads();                            // every wavefront has finished with the previous part of X
-        }
+        const int kb_lo = PHASED ? ph * kb_phase : 0, nkb_ph = PHASED ? min(kb_phase, nkb - kb_lo) : nkb;
+        const int st_ph = PHASED ? ph % ph_stage : 0;   // phases of the staged part before this one
+        const bool stage = !PHASED || st_ph == 0;
+        if (PHASED && stage && ph > 0) __syncthreads();     // every wavefront has finished with the previous part of X
         // XREG without rms-norm: a wavefront needs nothing but the activations of its own four k blocks, so it
         // stages exactly those and waits for no other wavefront before it starts.  (Wavefronts on the same k
         // blocks write the same bytes; not done when they would each load many rows twice.)
@@ -456,13 +452,13 @@ __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restr
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");     // read back by the wavefront that wrote it
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        } else {
-            // all M * ph_pieces pieces (of this phase: all of them unless PHASED), kThreads at a time; the row of
+        } else if (stage) {
+            // all M * ph_pieces pieces (of ph_stage phases: all of them unless PHASED), kThreads at a time; the row of
             // piece idx is idx / ph_pieces, taken as the high half of idx * ceil(2^32 / ph_pieces) (exact while
             // M * ph_pieces^2 < 2^32, which the LDS limit implies)
-            const int ph_pieces = PHASED ? nkb_ph * (XBB / 16) : pieces;
+            const int ph_pieces = PHASED ? min(nkb_lds, nkb - kb_lo) * (XBB / 16) : pieces;
             const int pc_lo = PHASED ? kb_lo * (XBB / 16) : 0;
-            const uint32_t pieces_magic = PHASED && ph == n_ph - 1 ? pieces_magic_last : pieces_magic_arg;
+            const uint32_t pieces_magic = PHASED && kb_lo + nkb_lds >= nkb ? pieces_magic_last : pieces_magic_arg;
             for (int base = 0; base < M * ph_pieces; base += kStageBatch * kThreads) {
                 half8_t vb[kStageBatch], gb[kStageBatch];
 #pragma unroll
@@ -488,9 +484,11 @@ __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restr
         }
 
         // X operand address of this lane: row min(l%16, M-1) (rows beyond M repeat the last one; their
-        // results are never stored), k-group l/16
-        const int x_row = GS == 1 ? min(n_l, M - 1) : (n_l / SLOT) * SLOT + min(n_l % SLOT, M - 1);
-        const unsigned char* x_lane = xs + (size_t)x_row * row_stride + g_l * 2 * UB;
+        // results are never stored), k-group l/16; the zeros where that is not of the group of row l%16 of the MFMA
+        const bool x_own = GS == 1 || n_l / SLOT == g_l * GS / 4;
+        const unsigned char* x_lane =
+            x_own ? xs + (size_t)min(n_l % SLOT, M - 1) * row_stride + g_l * 2 * UB + (PHASED ? st_ph * kb_phase * XBB : 0) : smem;
+        const int x_blk = x_own ? XBB : 0;
 
         half8_t xreg_h[XREG ? kSuper : 1][2], xreg_l[XREG ? kSuper : 1][2];
         if (XREG) {
@@ -527,7 +525,7 @@ __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restr
 
         for (int s_rb = 0; s_rb < n_rb; ++s_rb) {
             floatx4 ysum = zero4;                           // this wavefront's share of Y[4*g_l .. 4*g_l+3][row n_l] of row block s_rb
-            while (slot == s_rb) {
+            while (slot == s_rb && (!PHASED || cph == ph)) {
                 // parameter word of (block j, weight row n_l): lane 16 j + n_l of the item's 64 words
                 uint32_t pwj[kSuper];
 #pragma unroll
@@ -535,7 +533,7 @@ __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restr
                     const int word = j * PW + (g_l * GS / 4) * kBlockRows + n_l;
                     pwj[j] = (uint32_t)__builtin_amdgcn_ds_bpermute((word & 63) * 4, (int)pwraw[GS == 1 ? 0 : (j * PW) / 64]);
                 }
-                fetch_params(nslot, nitem);
+                fetch_params(nph, nslot, nitem);
 #pragma unroll
                 for (int j = 0; j < kSuper; ++j) {
                     const int kb = si * kSuper + j;         // (inside the phase) may lie beyond K in the last item: such a block is left out below
@@ -553,9 +551,9 @@ __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restr
                             w1_pairs_mixed(words[w], fmask, fmask_low, p[w]);
                         }
                     }
-                    fetch_code(j, nslot, nitem);            // the block's registers are free: request the next item's
+                    fetch_code(j, nph, nslot, nitem);            // the block's registers are free: request the next item's
                     floatx4 acc_h = zero4, acc_l = zero4;
-                    const unsigned char* xb = x_lane + (size_t)min(kb, nkb_ph - 1) * XBB;
+                    const unsigned char* xb = x_lane + min(kb, nkb_ph - 1) * (GS == 1 ? XBB : x_blk);
                     half8_t xh2[2], xl2[2];
 #pragma unroll
                     for (int wp = 0; wp < 2; ++wp) {
@@ -592,9 +590,10 @@ __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restr
                             ysum[r] += sc * ((acc_h[r] + 16.f * acc_l[r] - sx30[r]) - bi * sx[r]);
                     }
                 }
+                cph = nph;
                 slot = nslot;
                 si = nitem;
-                advance(nslot, nitem);
+                advance(nph, nslot, nitem);
             }
             if (late) {                                 // (a cell belongs to one wavefront, which adds later phases to it)
 #pragma unroll
@@ -688,18 +687,18 @@ __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restr
 // remainder.  One round of workgroups as long as that leaves room for kPhasedMinItems work items of X per
 // phase, more workgroups with fewer row blocks each otherwise.
 constexpr int kPhasedMinItems = 4;
-bool make_phased_plan(int64_t M, int64_t nrb, int64_t nkb, MfmaPlan& p, int unit, bool e8, int w_knob, int target)
+bool make_phased_plan(int64_t M, int64_t mfma_rows, int64_t nrb, int64_t nkb, MfmaPlan& p, int unit, bool e8, int w_knob, int target)
 {
     const int64_t nsi = (nkb + kSuper - 1) / kSuper;
     const size_t xbb = e8 ? kXBlockBytes / 2 : kXBlockBytes;
     auto plan = [&](int w) -> bool {
         int64_t most = (nrb + std::min<int64_t>(nrb, target) - 1) / std::min<int64_t>(nrb, target);    // row blocks (or pairs) of a workgroup
-        const size_t per_item = (size_t)M * kSuper * xbb, other = kNormBytes + (size_t)M * kRowPadBytes;
+        const size_t per_item = (size_t)mfma_rows * kSuper * xbb, other = kNormBytes + (size_t)mfma_rows * kRowPadBytes;
         const size_t min_x = other + (size_t)std::min<int64_t>(kPhasedMinItems, nsi) * per_item;
         const size_t room = (size_t)kLdsLimitBytes > min_x ? (size_t)kLdsLimitBytes - min_x : 0;    // for the sums
-        most = std::min<int64_t>(most, std::max<int64_t>(1, (int64_t)(room / late_red_bytes(M, unit, w))));
+        most = std::min<int64_t>(most, std::max<int64_t>(1, (int64_t)(room / late_red_bytes(mfma_rows, unit, w))));
         p.grid = (nrb + most - 1) / most;
-        const size_t fixed = late_red_bytes(M, (int)most * unit, w) + other;
+        const size_t fixed = late_red_bytes(mfma_rows, (int)most * unit, w) + other;
         if (fixed + per_item > (size_t)kLdsLimitBytes) return false;
         const int64_t fit = (int64_t)(((size_t)kLdsLimitBytes - fixed) / per_item);     // work items of X at a time
         const int64_t phases = (nsi + fit - 1) / fit;
@@ -711,9 +710,16 @@ bool make_phased_plan(int64_t M, int64_t nrb, int64_t nkb, MfmaPlan& p, int unit
         p.rb_base = (int)(nrb / p.grid);
         p.rb_rem = (int)(nrb % p.grid);
         p.late = 1;
-        p.lds_bytes = fixed + (size_t)nsi_ph * per_item;
-        const uint64_t pieces = (uint64_t)p.kb_phase * (xbb / 16);
-        const uint64_t pieces_last = (uint64_t)(nkb - (nkb - 1) / p.kb_phase * p.kb_phase) * (xbb / 16);
+        // (mfma_rows >= M: with several groups per block LDS holds more than a phase)
+        const int64_t n_ph = (nkb + p.kb_phase - 1) / p.kb_phase;
+        const size_t ph_bytes = (size_t)M * nsi_ph * kSuper * xbb, zeros = mfma_rows > M ? kZeroBytes : 0;
+        const int64_t fit_ph = std::max<int64_t>(1, (int64_t)(((size_t)kLdsLimitBytes - fixed - zeros) / ph_bytes));
+        const int64_t stages = (n_ph + fit_ph - 1) / fit_ph;
+        p.ph_stage = (int)((n_ph + stages - 1) / stages);
+        p.lds_bytes = fixed + zeros + (size_t)p.ph_stage * ph_bytes;
+        const int64_t st_blocks = (int64_t)p.ph_stage * p.kb_phase;
+        const uint64_t pieces = (uint64_t)st_blocks * (xbb / 16);
+        const uint64_t pieces_last = (uint64_t)(nkb - (nkb - 1) / st_blocks * st_blocks) * (xbb / 16);
         p.pieces_magic = (uint32_t)(((1ull << 32) + pieces - 1) / pieces);      // (M * pieces^2 < 2^32: M * pieces * 16 bytes fit the LDS)
         p.pieces_magic_last = (uint32_t)(((1ull << 32) + pieces_last - 1) / pieces_last);
         return true;
@@ -731,14 +737,13 @@ bool make_phased_plan(int64_t M, int64_t nrb, int64_t nkb, MfmaPlan& p, int unit
 
 // `unit`: 2 when row blocks are dealt in (gate, up) pairs; rb_base and rb_rem then count pairs
 // (e8: K counts 4-bit slots, two per weight, and a block of X is half as long)
-// Groups per block of a group size, and the rows of X the kernel stages for M rows (see the kernel's header).
+// Groups per block of a group size, and the rows of the MFMA that M rows of X take (see the kernel's header).
 int groups_per_block(int group) { return kG / group; }
-int64_t staged_rows(int64_t M, int gs) { return gs == 1 ? M : (gs - 1) * (kMaxM / gs) + M; }
+int64_t mfma_rows(int64_t M, int gs) { return gs == 1 ? M : (gs - 1) * (kMaxM / gs) + M; }
 
-// (`gs`: groups per block; every LDS size below is for the staged rows)
-bool make_mfma_plan(int64_t M_rows, int64_t N, int64_t K, MfmaPlan& p, int unit = 1, bool e8 = false, int gs = 1)
+// (`gs`: groups per block)
+bool make_mfma_plan(int64_t M, int64_t N, int64_t K, MfmaPlan& p, int unit = 1, bool e8 = false, int gs = 1)
 {
-    const int64_t M = staged_rows(M_rows, gs);
     const int64_t nrb = row_blocks(N) / unit, nkb = k_blocks(K);
     const int64_t nsi = (nkb + kSuper - 1) / kSuper;
     int w = knob("gemv_waves");
@@ -747,16 +752,18 @@ bool make_mfma_plan(int64_t M_rows, int64_t N, int64_t K, MfmaPlan& p, int unit 
     const int w_knob = (w == 4 || w == 8 || w == 16) ? w : 0;
     if (!w_knob) w = nsi > 16 ? 16 : 8;
     const int w_wanted = w;
-    while (w > 4 && lds_need(M, nkb, w, e8) > (size_t)kLdsLimitBytes) w /= 2;   // (smaller buffers for the wavefront sums)
+    // (several groups per block: plans are made for the rows of the MFMA, of which LDS holds a part)
+    const int64_t rows = mfma_rows(M, gs);
+    while (w > 4 && lds_need(rows, nkb, w, e8) > (size_t)kLdsLimitBytes) w /= 2;    // (smaller buffers for the wavefront sums)
     int target = knob("gemv_workgroups");
     if (target <= 0) target = kTargetWorkgroups;
-    p.kb_phase = 0;
+    p.kb_phase = p.ph_stage = 0;
     p.pieces_magic_last = 0;
     // X does not fit beside the sums of eight wavefronts: K in phases rather than all of X with four wavefronts
     // (36864 x 7168 at M = 10: 33 us against 52)
-    if (w < 8 && w_wanted >= 8 && knob("gemv_mfma") != 3 && make_phased_plan(M, nrb, nkb, p, unit, e8, w_knob, target))
+    if (w < 8 && w_wanted >= 8 && knob("gemv_mfma") != 3 && make_phased_plan(M, rows, nrb, nkb, p, unit, e8, w_knob, target))
         return true;
-    if (lds_need(M, nkb, w, e8) > (size_t)kLdsLimitBytes) return false;
+    if (lds_need(rows, nkb, w, e8) > (size_t)kLdsLimitBytes) return false;
     p.grid = std::min<int64_t>(nrb, target);
     if (nrb > target) {                                 // the fewest workgroups with the same largest share of row
         const int64_t most = (nrb + target - 1) / target;   // blocks (or pairs), so that (nearly) all of them end together
@@ -767,12 +774,12 @@ bool make_mfma_plan(int64_t M_rows, int64_t N, int64_t K, MfmaPlan& p, int unit 
     p.step_item = (int)(w % nsi);
     p.rb_base = (int)(nrb / p.grid);
     p.rb_rem = (int)(nrb % p.grid);
-    p.lds_bytes = lds_need(M, nkb, w, e8);
+    p.lds_bytes = lds_need(M, nkb, w, e8, gs);
     const uint64_t row_pieces = (uint64_t)nkb * (e8 ? 8 : 16);
     if ((uint64_t)M * row_pieces * row_pieces >= (1ull << 32)) return false;    // (never within the LDS limit)
     p.pieces_magic = (uint32_t)(((1ull << 32) + row_pieces - 1) / row_pieces);
     const size_t per_rb = 2 * (size_t)w * kMaxM * kBlockRows * sizeof(float);
-    const size_t late_bytes = late_red_bytes(M, (p.rb_base + 1) * unit, w);
+    const size_t late_bytes = late_red_bytes(rows, (p.rb_base + 1) * unit, w);
     p.late = knob("gemv_mfma") != 3 && p.lds_bytes - per_rb + late_bytes <= (size_t)kLdsLimitBytes;
     if (p.late) p.lds_bytes = p.lds_bytes - per_rb + std::max(late_bytes, (size_t)16);
     return true;
@@ -792,7 +799,7 @@ int launch_mfma_keep(const MfmaPlan& p, const void* X, int64_t M, const void* pa
     hipLaunchKernelGGL((gemv_mfma_kernel<W, FUSED, XREG, E8, PHASED, GS, KEEP>), dim3((unsigned)p.grid, chunks), dim3(W * 64),
                        p.lds_bytes, stream, static_cast<const half_t*>(X), static_cast<const uint4*>(packed),
                        static_cast<half_t*>(Y), (int)M, (uint32_t)N, (uint32_t)K, p.step_slots, p.step_item, p.rb_base,
-                       p.rb_rem, p.late, p.pieces_magic, p.kb_phase, p.pieces_magic_last, fu);
+                       p.rb_rem, p.late, p.pieces_magic, p.kb_phase, p.ph_stage, p.pieces_magic_last, fu);
     return check_launch();
 }
 
