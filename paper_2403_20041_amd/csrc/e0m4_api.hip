@@ -136,6 +136,15 @@ bool use_gemv_dq4(int64_t M, int64_t N, int64_t K, int group)
     }
     return use_gemv_dq(M, N, K, group, kDqFormatFp16);
 }
+// bfloat16 of up to eight rows: the small-batch kernel, which multiplies the codes' exact values as the vector kernel does but
+// whose time hardly grows with the rows (27392 x 5120 at M = 5 32 -> 18.3 us; M = 2 21.5 -> 18.4, 4096 x 4096 5.8 -> 5.7, 2560 x
+// 2048 4.4 and 4.5).  In groups of 64 and 32 from three rows on: 2560 x 2048 at M = 2 4.4 against 4.8, at M = 3 5.6 against 4.8.
+// (gemv_mfma 1: the vector kernel, 6: this one from two rows on)
+bool use_gemv_mfma_bf16(int64_t M, int64_t N, int64_t K, int group)
+{
+    const int k = knob("gemv_mfma");
+    return M <= kGemvMaxM && k != 1 && (group == 128 || M >= 3 || k == 6) && gemv_mfma_supported(M, N, K, group);
+}
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 // Shape rules shared by all entry points.
@@ -490,6 +499,7 @@ int e0m4_bf16_matmul(const void* X, int64_t M, const void* codes, int64_t N, int
     if (!aligned16(X) || !aligned16(codes)) return E0M4_ERR_ALIGN;
     if ((knob("gemv_mfma") == 4 || !gemm_steered()) && use_gemv_dq(M, N, K, group, kDqFormatBf16))
         return launch_gemv_dq(X, M, codes, N, K, group, kDqFormatBf16, Y, (hipStream_t)stream);
+    if (use_gemv_mfma_bf16(M, N, K, group)) return launch_gemv_mfma_bf16(X, M, codes, N, K, group, Y, (hipStream_t)stream);
     if (M <= kGemvMaxM) return launch_gemv_bf16(X, M, codes, N, K, group, Y, (hipStream_t)stream);
     if (N > (int64_t)1 << 24) return E0M4_ERR_SHAPE;    // 32-bit offsets in the GEMM epilogue
     return launch_gemm_bf16(X, M, codes, N, K, group, Y, (hipStream_t)stream);

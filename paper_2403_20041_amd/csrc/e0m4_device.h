@@ -139,6 +139,15 @@ __device__ inline uint32_t frac_mask_low_vgpr()
     return m;
 }
 
+// Fraction bits 6..3 of both bfloat16 halves: a code there reads 2 + code/8 with the exponent of [2,4) (kExpBits2 in this format too).
+constexpr uint32_t kBf16CodeMask2 = 0x00780078u;
+__device__ inline uint32_t frac_mask_bf16_vgpr()
+{
+    uint32_t m = kBf16CodeMask2;
+    asm volatile("" : "+v"(m));
+    return m;
+}
+
 // Orders in which the kernels that walk a row-major matrix in tiles visit them; workgroup b runs on XCD b % 8.
 //   Strips: eight tile rows side by side, column after column, so that each XCD walks along a strip: what neighbouring tiles
 //     write to the same cache line, the quantisers' two-byte parameters above all, meets in one L2.  27392 x 4096 quantised at

@@ -134,7 +134,6 @@ GemvPlan make_plan(int64_t M, int64_t N, int64_t K, int unit = 1, bool* single_s
 enum { kDeqE0M4 = 0, kDeqInt4Convert = 1, kDeqE0M8 = 2, kDeqBf16 = 3 };
 
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-constexpr uint32_t kBf16CodeMask2 = 0x00780078u;       // fraction bits 6..3 of both bfloat16 halves
 constexpr uint32_t kBf16Ones2 = 0x3F803F80u;           // (1.0, 1.0)
 __device__ inline bf16x2_t as_bf16x2(uint32_t v) { return __builtin_bit_cast(bf16x2_t, v); }
 __device__ inline float bf16_lo(uint32_t word) { return __builtin_bit_cast(float, word << 16); }

@@ -50,6 +50,7 @@ namespace e0m4 {
 namespace {
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 
 constexpr int kSuper = 4;                       // weight blocks (of 128 k) per work item
 constexpr int kG = 128;                         // group size: one group per block
@@ -107,7 +108,9 @@ __device__ inline int x_unit_off(int q, int w, int hl) { return ((q * 4 + (w >> 
 // the workgroup and adds to the wavefront sums, which stay in LDS (`late`) until the last phase; X is staged for ph_stage
 // phases at a time.  The weights are still read exactly once.
 // KEEP: with an rms-norm, X stays in registers from the pass over its squares (keeps_x below).
-template <int W, bool FUSED, bool XREG, bool E8 = false, bool PHASED = false, int GS = 1, bool KEEP = false>
+// BF: 4-bit codes on bfloat16 (no fused operators).  Brought to fraction bits 6..3 by one shift or rotation per pair, all eight
+// codes of a word read 2 + c/8, so one MFMA takes one word and X as it lies in memory, and a block needs the plain sum of X only.
+template <int W, bool FUSED, bool XREG, bool E8 = false, bool PHASED = false, int GS = 1, bool KEEP = false, bool BF = false>
 __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restrict__ X,
                                                            const uint4* __restrict__ packed, half_t* __restrict__ Y,
                                                            int M, uint32_t N32, uint32_t K32, int step_slots_arg,
@@ -130,6 +133,7 @@ __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restr
     }
     static_assert(!(PHASED && XREG), "a wavefront meets other k blocks in every phase");
     static_assert(!KEEP || (FUSED && W <= 8 && !PHASED && GS == 1 && !(XREG && E8)), "instances that keep X");
+    static_assert(!BF || (!FUSED && !E8), "bfloat16: 4-bit codes, plain matmuls");
     static_assert(GS == 1 || ((GS == 2 || GS == 4) && !E8 && !XREG), "several groups per block: 4-bit codes, X from LDS");
     constexpr int kThreads = W * 64;
     constexpr int G = kG / GS;                          // group size
@@ -155,7 +159,15 @@ __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restr
     const int lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int n_l = lane & 15, g_l = lane >> 4;         // weight row / k-group of this lane; also (row of X, k-group)
-    const uint32_t fmask = frac_mask_vgpr(), fmask_low = frac_mask_low_vgpr();
+    const uint32_t fmask = BF ? frac_mask_bf16_vgpr() : frac_mask_vgpr(), fmask_low = frac_mask_low_vgpr();
+    auto mfma = [](const half8_t& a, const half8_t& b, const floatx4& c_) -> floatx4 {
+        if constexpr (BF) return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c_, 0, 0, 0);
+        else return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c_, 0, 0, 0);
+    };
+    auto out_value = [](float v) -> half_t {
+        if constexpr (BF) return __builtin_bit_cast(half_t, (__bf16)v);
+        else return (half_t)v;
+    };
     // even deal of row blocks; gated: of pairs of row blocks (rb0 is then the pair, i.e. its gate row block)
     const bool gated = FUSED && fu.swiglu;
     const int64_t rb0 = (int64_t)blockIdx.x * rb_base + min((int)blockIdx.x, rb_rem);
@@ -391,6 +403,10 @@ __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restr
             const int kb = pc >> 4, q = (pc >> 2) & 3, w = pc & 3;
             const half4_t hpart = {v[0], v[1], v[6], v[7]}, lpart = {v[2], v[3], v[4], v[5]};
             unsigned char* blk = xs + (size_t)m * row_stride + kb * XBB;
+            if (BF) {                                   // piece = the 8 weights of (k-group q, MFMA w)
+                *reinterpret_cast<half8_t*>(blk + (q * 4 + w) * 16) = v;
+                return;
+            }
             *reinterpret_cast<half4_t*>(blk + x_unit_off(q, w, 0)) = hpart;
             *reinterpret_cast<half4_t*>(blk + x_unit_off(q, w, 1)) = lpart;
         }
@@ -506,13 +522,14 @@ __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restr
         // The two sums of a block's activations per row of X (all of them, and those that meet the code pairs
         // read at 1/128 scale) come from the matrix cores as well: products with an all-ones weight operand.
         const floatx4 zero4 = {0.f, 0.f, 0.f, 0.f};
-        const half8_t ones8 = {(half_t)1.f, (half_t)1.f, (half_t)1.f, (half_t)1.f, (half_t)1.f, (half_t)1.f, (half_t)1.f, (half_t)1.f};
+        const half_t one = out_value(1.f);
+        const half8_t ones8 = {one, one, one, one, one, one, one, one};
         auto block_sums = [&](const half8_t (&xh)[2], const half8_t (&xl)[2], floatx4& sx, floatx4& sx30) {
             floatx4 sh = zero4, sl = zero4;
 #pragma unroll
             for (int wp = 0; wp < 2; ++wp) {
-                sh = __builtin_amdgcn_mfma_f32_16x16x32_f16(xh[wp], ones8, sh, 0, 0, 0);
-                if (!E8) sl = __builtin_amdgcn_mfma_f32_16x16x32_f16(xl[wp], ones8, sl, 0, 0, 0);
+                sh = mfma(xh[wp], ones8, sh);
+                if (!E8) sl = mfma(xl[wp], ones8, sl);
             }
             sx = sh + sl;
             sx30 = 30.f * sl;
@@ -537,8 +554,8 @@ __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restr
 #pragma unroll
                 for (int j = 0; j < kSuper; ++j) {
                     const int kb = si * kSuper + j;         // (inside the phase) may lie beyond K in the last item: such a block is left out below
-                    const float sc = (float)param_scale(pwj[j]);
-                    const float bi = (float)param_bias(pwj[j]);
+                    const float sc = BF ? __builtin_bit_cast(float, pwj[j] << 16) : (float)param_scale(pwj[j]);
+                    const float bi = BF ? __builtin_bit_cast(float, pwj[j] & 0xFFFF0000u) : (float)param_bias(pwj[j]);
                     const uint32_t words[4] = {c[j].x, c[j].y, c[j].z, c[j].w};
                     half2_t p[4][4];
 #pragma unroll
@@ -547,6 +564,11 @@ __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restr
                             const uint32_t m8 = fmask | fmask_low;
                             p[w][0] = __builtin_bit_cast(half2_t, (words[w] & m8) | kExpBits2);
                             p[w][1] = __builtin_bit_cast(half2_t, (__builtin_amdgcn_alignbit(words[w], words[w], 8) & m8) | kExpBits2);
+                        } else if (BF) {
+                            p[w][0] = __builtin_bit_cast(half2_t, ((words[w] >> 3) & fmask) | kExpBits2);
+                            p[w][1] = __builtin_bit_cast(half2_t, ((words[w] << 1) & fmask) | kExpBits2);
+                            p[w][2] = __builtin_bit_cast(half2_t, ((words[w] >> 7) & fmask) | kExpBits2);
+                            p[w][3] = __builtin_bit_cast(half2_t, (__builtin_amdgcn_alignbit(words[w], words[w], 11) & fmask) | kExpBits2);
                         } else {
                             w1_pairs_mixed(words[w], fmask, fmask_low, p[w]);
                         }
@@ -566,16 +588,23 @@ __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restr
                             const half2_t* w0 = p[2 * wp];
                             const half2_t* w1 = p[2 * wp + 1];
                             const half8_t w8 = {w0[0][0], w0[0][1], w0[1][0], w0[1][1], w1[0][0], w1[0][1], w1[1][0], w1[1][1]};
-                            acc_h = __builtin_amdgcn_mfma_f32_16x16x32_f16(xh2[wp], w8, acc_h, 0, 0, 0);
+                            acc_h = mfma(xh2[wp], w8, acc_h);
                             continue;
                         }
                         const half8_t xh = xh2[wp], xl = xl2[wp];
                         const half2_t* w0 = p[2 * wp];
                         const half2_t* w1 = p[2 * wp + 1];
+                        if (BF) {
+                            const half8_t wa = {w0[0][0], w0[0][1], w0[1][0], w0[1][1], w0[2][0], w0[2][1], w0[3][0], w0[3][1]};
+                            const half8_t wb = {w1[0][0], w1[0][1], w1[1][0], w1[1][1], w1[2][0], w1[2][1], w1[3][0], w1[3][1]};
+                            acc_h = mfma(xh, wa, acc_h);
+                            acc_l = mfma(xl, wb, acc_l);
+                            continue;
+                        }
                         const half8_t wh = {w0[0][0], w0[0][1], w0[3][0], w0[3][1], w1[0][0], w1[0][1], w1[3][0], w1[3][1]};
                         const half8_t wl = {w0[1][0], w0[1][1], w0[2][0], w0[2][1], w1[1][0], w1[1][1], w1[2][0], w1[2][1]};
-                        acc_h = __builtin_amdgcn_mfma_f32_16x16x32_f16(xh, wh, acc_h, 0, 0, 0);
-                        acc_l = __builtin_amdgcn_mfma_f32_16x16x32_f16(xl, wl, acc_l, 0, 0, 0);
+                        acc_h = mfma(xh, wh, acc_h);
+                        acc_l = mfma(xl, wl, acc_l);
                     }
                     if (kb < nkb_ph) {
                         floatx4 sx, sx30;
@@ -587,7 +616,7 @@ __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restr
                         }
 #pragma unroll
                         for (int r = 0; r < 4; ++r)
-                            ysum[r] += sc * ((acc_h[r] + 16.f * acc_l[r] - sx30[r]) - bi * sx[r]);
+                            ysum[r] += sc * ((BF ? acc_h[r] + acc_l[r] : acc_h[r] + 16.f * acc_l[r] - sx30[r]) - bi * sx[r]);
                     }
                 }
                 cph = nph;
@@ -647,7 +676,7 @@ __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restr
                         s += red[(((s_rb & 1) * W + w) * kMaxM + min(m + SLOT * gg, kMaxM - 1)) * kBlockRows + n];
                 const int64_t row = (rb0 + s_rb) * kBlockRows + n;
                 if (FUSED && fu.residual && m < M && row < N) s += (float)fu.residual[(int64_t)m * N + row];
-                if (m < M && row < N) Y[(int64_t)m * N + row] = (half_t)s;
+                if (m < M && row < N) Y[(int64_t)m * N + row] = out_value(s);
             }
             // no second barrier: row block s_rb + 1 uses the other half of `red`, and nobody writes this
             // half again before passing the barrier of s_rb + 1, which the readers above reach after reading
@@ -676,7 +705,7 @@ __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restr
             const int64_t col = (rb0 + u) * kBlockRows + n;
             if (col < n_out) {
                 if (FUSED && fu.residual) v += (float)fu.residual[(int64_t)m * n_out + col];
-                Y[(int64_t)m * n_out + col] = (half_t)v;
+                Y[(int64_t)m * n_out + col] = out_value(v);
             }
         }
     }
@@ -785,18 +814,18 @@ bool make_mfma_plan(int64_t M, int64_t N, int64_t K, MfmaPlan& p, int unit = 1, 
     return true;
 }
 
-template <int W, bool FUSED, bool XREG, bool E8, bool PHASED, int GS, bool KEEP>
+template <int W, bool FUSED, bool XREG, bool E8, bool PHASED, int GS, bool KEEP, bool BF = false>
 int launch_mfma_keep(const MfmaPlan& p, const void* X, int64_t M, const void* packed, int64_t N, int64_t K, void* Y,
                   hipStream_t stream, const GemvFusion& fu)
 {
     if (PHASED != (p.kb_phase > 0) || (PHASED && !p.late) || p.lds_bytes > (size_t)kLdsLimitBytes) return E0M4_ERR_SHAPE;
     static std::atomic<uint64_t> lds_allowed{0};
-    const int arc = allow_dynamic_lds(reinterpret_cast<const void*>(&gemv_mfma_kernel<W, FUSED, XREG, E8, PHASED, GS, KEEP>),
+    const int arc = allow_dynamic_lds(reinterpret_cast<const void*>(&gemv_mfma_kernel<W, FUSED, XREG, E8, PHASED, GS, KEEP, BF>),
                                       kLdsLimitBytes, lds_allowed);
     if (arc != E0M4_OK) return arc;
     // (M: rows per chunk; fu.m_total: all rows, when there are several chunks)
     const unsigned chunks = fu.m_total > 0 ? (unsigned)((fu.m_total + M - 1) / M) : 1u;
-    hipLaunchKernelGGL((gemv_mfma_kernel<W, FUSED, XREG, E8, PHASED, GS, KEEP>), dim3((unsigned)p.grid, chunks), dim3(W * 64),
+    hipLaunchKernelGGL((gemv_mfma_kernel<W, FUSED, XREG, E8, PHASED, GS, KEEP, BF>), dim3((unsigned)p.grid, chunks), dim3(W * 64),
                        p.lds_bytes, stream, static_cast<const half_t*>(X), static_cast<const uint4*>(packed),
                        static_cast<half_t*>(Y), (int)M, (uint32_t)N, (uint32_t)K, p.step_slots, p.step_item, p.rb_base,
                        p.rb_rem, p.late, p.pieces_magic, p.kb_phase, p.ph_stage, p.pieces_magic_last, fu);
@@ -872,6 +901,43 @@ bool gemv_mfma_supported(int64_t M, int64_t N, int64_t K, int group)
         return false;
     MfmaPlan p;
     return make_mfma_plan(M, N, K, p, 1, false, groups_per_block(group));
+}
+
+namespace {
+template <int W, int GS>
+int launch_mfma_bf16(const MfmaPlan& p, const void* X, int64_t M, const void* packed, int64_t N, int64_t K, void* Y, hipStream_t stream)
+{
+    const GemvFusion fu{};
+    if constexpr (W >= 8) {
+        if (p.kb_phase > 0) return launch_mfma_keep<W, false, false, false, true, GS, false, true>(p, X, M, packed, N, K, Y, stream, fu);
+    }
+    if constexpr (W <= 8 && GS == 1) {
+        if (p.step_item == 0 && knob("gemv_mfma") != 2)
+            return launch_mfma_keep<W, false, true, false, false, GS, false, true>(p, X, M, packed, N, K, Y, stream, fu);
+    }
+    return launch_mfma_keep<W, false, false, false, false, GS, false, true>(p, X, M, packed, N, K, Y, stream, fu);
+}
+template <int GS>
+int launch_mfma_bf16_waves(const MfmaPlan& p, const void* X, int64_t M, const void* packed, int64_t N, int64_t K, void* Y, hipStream_t stream)
+{
+    switch (p.waves) {
+        case 4: return launch_mfma_bf16<4, GS>(p, X, M, packed, N, K, Y, stream);
+        case 8: return launch_mfma_bf16<8, GS>(p, X, M, packed, N, K, Y, stream);
+        default: return launch_mfma_bf16<16, GS>(p, X, M, packed, N, K, Y, stream);
+    }
+}
+}  // namespace
+
+// bfloat16: the sizes of gemv_mfma_supported.
+int launch_gemv_mfma_bf16(const void* X, int64_t M, const void* packed, int64_t N, int64_t K, int group, void* Y, hipStream_t stream)
+{
+    MfmaPlan p;
+    if (!gemv_mfma_supported(M, N, K, group) || !make_mfma_plan(M, N, K, p, 1, false, groups_per_block(group))) return E0M4_ERR_SHAPE;
+    switch (group) {
+        case 128: return launch_mfma_bf16_waves<1>(p, X, M, packed, N, K, Y, stream);
+        case 64: return launch_mfma_bf16_waves<2>(p, X, M, packed, N, K, Y, stream);
+        default: return launch_mfma_bf16_waves<4>(p, X, M, packed, N, K, Y, stream);
+    }
 }
 
 // Rows per chunk when M rows go out in `chunks` equal chunks (the last may be shorter; never fewer than two rows for

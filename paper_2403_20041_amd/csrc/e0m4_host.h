@@ -72,6 +72,8 @@ bool gemv_mfma_groups_pay(int64_t M, int64_t N, int64_t K, int group);
 // `chunks` > 1: M (17 ... 64) rows in that many equal chunks of at most 16 rows, dealt to the y dimension of one launch
 int launch_gemv_mfma(const void* X, int64_t M, const void* packed, int64_t N, int64_t K, void* Y, hipStream_t stream,
                      int chunks = 1, int group = 128);
+// 4-bit codes on bfloat16, the same sizes
+int launch_gemv_mfma_bf16(const void* X, int64_t M, const void* packed, int64_t N, int64_t K, int group, void* Y, hipStream_t stream);
 bool gemv_mfma_fused_supported(const Fusion& f, int64_t M, int64_t N, int64_t K, int group);
 // ... and all M rows of X fit the LDS at once (no phases along K)
 // (`workgroups`: the launch's grid, when it is)

@@ -122,6 +122,29 @@ def test_bf16_decode_shapes_and_wavefront_counts(e0m4, oracle, N, K, G, waves):
     assert torch.equal(Y.view(torch.int16), Y2.view(torch.int16))           # deterministic
 
 
+@pytest.mark.parametrize("waves,target", [(0, 0), (4, 0), (8, 3), (16, 0), (16, 3)])
+@pytest.mark.parametrize("M,N,K,G", [(2, 16, 128, 128), (8, 203, 4096, 128), (5, 333, 2176, 128), (7, 130, 16384, 128), (8, 70, 448, 64),
+                                     (6, 203, 5120, 64), (8, 100, 12800, 64), (3, 130, 160, 32), (4, 203, 13696, 32)])
+def test_bf16_decode_matrix_core_kernel(e0m4, oracle, M, N, K, G, waves, target):
+    # k blocks in registers and from LDS, K in phases, k blocks that K does not fill, one and several row blocks per workgroup;
+    # the vector kernel (1) on the same problem
+    codes, What, _ = assert_bf16_quantize_exact(e0m4, oracle, synth_inputs.weights_bf16(N, K, seed=3260 + N + K), G)
+    X = synth_inputs.activations_bf16(M, K, seed=3270 + M)
+    Yref, absdot = oracle.bf16_matmul(X, What)
+    e0m4.e0m4_set_knob("gemv_waves", waves)
+    e0m4.e0m4_set_knob("gemv_workgroups", target)
+    try:
+        for mode in (6, 1):
+            e0m4.e0m4_set_knob("gemv_mfma", mode)
+            Y = e0m4.e0m4_bf16_matmul(bf_dev(X), codes, N, K, G)
+            Y2 = e0m4.e0m4_bf16_matmul(bf_dev(X), codes, N, K, G)
+            check_bf16_matmul(oracle, Y, Yref, absdot, "bf16 few rows M=%d N=%d K=%d G=%d mode %d" % (M, N, K, G, mode))
+            assert torch.equal(Y.view(torch.int16), Y2.view(torch.int16))
+    finally:
+        for knob in ("gemv_mfma", "gemv_waves", "gemv_workgroups"):
+            e0m4.e0m4_set_knob(knob, 0)
+
+
 @pytest.mark.parametrize("M,N,K,G", [(9, 203, 1664, 128), (64, 256, 512, 32), (200, 520, 1024, 64), (300, 1040, 2080, 32),
                                      (1024, 1280, 4096, 128), (130, 64, 128, 128), (17, 4608, 416, 32)])
 def test_bf16_gemm(e0m4, oracle, M, N, K, G):
