@@ -101,11 +101,17 @@ struct SkArgs {
 // would compute many rows that do not exist or leave compute units without a tile; 128 x 128 with 2 x 2 wavefronts
 // (forced launches only).
 //
+// SHORT: M leaves 96 rows or fewer in the last row tile of 128.  Those tiles are computed in the 32-row blocks that exist (two
+// at least: below that the dequantisation is all there is to do) and are numbered last on every XCD, so that they fill the gaps
+// at the end: gated 317 x 32768 x 2048 in groups of 32 (256 whole tiles and 128 of 61 rows) 57.3 -> 49 us, two such blocks at M =
+// 317 277 -> 262 us per pass.  In instances of its own: the three forms of the K loop cost the others 2 % (1024 rows, two 6B
+// blocks 899 -> 916 us).
+//
 // E8 selects the 8-bit format E0M8 (e0m8_pack.hip; G is then 128, the group of its 4-bit slots): a K slice
 // of 64 is one block, a lane reads two 16-byte chunks of 16 weights per slice, and MFMA number s takes
 // words 2(s%2) and 2(s%2)+1 of chunk s/2, each of which one mask-or (and one more after a rotation) turns
 // into four binade values.
-template <int G, int WGM, int WGN, bool FUSED, int BM, int BN, bool E8 = false, bool BF = false, int KS = 1>
+template <int G, int WGM, int WGN, bool FUSED, int BM, int BN, bool E8 = false, bool BF = false, int KS = 1, bool SHORT = false>
 __global__ __launch_bounds__(64 * WGM * WGN * KS, 2) void gemm_pipe_kernel(const half_t* __restrict__ X, int64_t M,
                                                              const uint4* __restrict__ packed, int64_t N, int64_t K,
                                                              half_t* __restrict__ Y, int m_tiles, int n_tiles,
@@ -129,12 +135,21 @@ __global__ __launch_bounds__(64 * WGM * WGN * KS, 2) void gemm_pipe_kernel(const
     // neighbouring tiles and share operands in its L2; each XCD takes a contiguous run.
     // (even scheduling exists in the instance the launcher uses it with; elsewhere the segment loop below folds away)
     static_assert(!BF || (!FUSED && !E8), "the bfloat16 member has the plain 4-bit kernel only");
+    static_assert(!SHORT || (WGM == 1 && BM == 128 && KS == 1), "short last row tiles: of 128 rows");
     static_assert(KS == 1 || (KS == 2 && BM == 64 && !FUSED), "K halves inside a workgroup: the flat tile, unfused");
     constexpr bool kSk = !FUSED && !E8 && !BF && BM == 256 && BN == 256;
     const bool sk_on = kSk && sk.enabled;
     const int total = m_tiles * n_tiles * splits;
     const int per_xcd = (total + kNumXcd - 1) / kNumXcd;
-    const int item = (blockIdx.x % kNumXcd) * per_xcd + blockIdx.x / kNumXcd;
+    int item = (blockIdx.x % kNumXcd) * per_xcd + blockIdx.x / kNumXcd;
+    int tiles_m = m_tiles;                              // row tiles of the numbering
+    if (SHORT) {                                        // (splits == 1, two row tiles at least)
+        const int full = (m_tiles - 1) * n_tiles, pf = (full + kNumXcd - 1) / kNumXcd, pr = (n_tiles + kNumXcd - 1) / kNumXcd;
+        const int xcd = blockIdx.x % kNumXcd, j = blockIdx.x / kNumXcd;
+        item = j < pf ? xcd * pf + j : full + xcd * pr + (j - pf);
+        if (j < pf ? item >= full : item >= total) return;
+        tiles_m = m_tiles - 1;
+    }
     if (!sk_on && item >= total) return;
     const int KT_all = (int)(K / BK);
     // Even scheduling: this workgroup's position (consecutive positions on one XCD: they share weight rows in
@@ -231,10 +246,13 @@ __global__ __launch_bounds__(64 * WGM * WGN * KS, 2) void gemm_pipe_kernel(const
     // Tiles are numbered down the rows of a panel of `panel` row tiles, column after column, panel after panel: the
     // workgroups that run together on an XCD (consecutive numbers) then cover a block of panel x (their number / panel)
     // tiles and share both operands through its L2, instead of one or two whole columns of tiles.
-    int tile_m = tile % m_tiles, tile_n = tile / m_tiles;
-    if (!sk_on && fu.panel > 0 && fu.panel < m_tiles) {
+    int tile_m = tile % tiles_m, tile_n = tile / tiles_m;
+    if (SHORT && tile >= tiles_m * n_tiles) {          // (a column of the last row tile)
+        tile_m = tiles_m;
+        tile_n = tile - tiles_m * n_tiles;
+    } else if (!sk_on && fu.panel > 0 && fu.panel < tiles_m) {
         const int per_panel = fu.panel * n_tiles, pn = tile / per_panel;
-        const int rows_p = min(fu.panel, m_tiles - pn * fu.panel), t_in = tile - pn * per_panel;
+        const int rows_p = min(fu.panel, tiles_m - pn * fu.panel), t_in = tile - pn * per_panel;
         tile_m = pn * fu.panel + t_in % rows_p;
         tile_n = t_in / rows_p;
     }
@@ -305,10 +323,10 @@ __global__ __launch_bounds__(64 * WGM * WGN * KS, 2) void gemm_pipe_kernel(const
     uint32_t pwset[PD][TN];
     half8_t fa[2][TM], fb[2][TN];
 
-    auto load_a = [&](int kt, int set) {
+    auto load_a = [&](auto pa_c, int kt, int set) {
         const uint32_t k0 = (uint32_t)min(kt, KT - 1) * BK;
 #pragma unroll
-        for (int p = 0; p < PA; ++p)
+        for (int p = 0; p < decltype(pa_c)::value; ++p)
             a_reg[set][p] = __builtin_amdgcn_raw_buffer_load_b128(a_rsrc, (int)a_pass_off[p], (int)(k0 * 2), 0);
     };
     auto load_b = [&](int kt, int set) {
@@ -327,15 +345,15 @@ __global__ __launch_bounds__(64 * WGM * WGN * KS, 2) void gemm_pipe_kernel(const
             pwset[set][j] = __builtin_amdgcn_raw_buffer_load_b32(b_param_rsrc, (int)b_param_off[j], param_soff, 0);
         }
     };
-    auto store_a = [&](uint32_t stage_off, int set) {
+    auto store_a = [&](auto pa_c, uint32_t stage_off, int set) {
 #pragma unroll
-        for (int p = 0; p < PA; ++p)
+        for (int p = 0; p < decltype(pa_c)::value; ++p)
             *reinterpret_cast<u32x4*>(smem + stage_off + a_lds_off + p * RP * kRowBytes) = a_reg[set][p];
     };
-    auto read_frags = [&](uint32_t stage_off, int s, half8_t (&dst)[TM]) {
+    auto read_frags = [&](auto tm_c, uint32_t stage_off, int s, half8_t (&dst)[TM]) {
         const unsigned char* base = smem + stage_off + frag_off[s];
 #pragma unroll
-        for (int i = 0; i < TM; ++i) dst[i] = *reinterpret_cast<const half8_t*>(base + i * 32 * kRowBytes);
+        for (int i = 0; i < decltype(tm_c)::value; ++i) dst[i] = *reinterpret_cast<const half8_t*>(base + i * 32 * kRowBytes);
     };
     auto dequant_frags = [&](int set, int s, half8_t (&dst)[TN]) {
 #pragma unroll
@@ -390,9 +408,9 @@ __global__ __launch_bounds__(64 * WGM * WGN * KS, 2) void gemm_pipe_kernel(const
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-    auto mfma_block = [&](const half8_t (&a)[TM], const half8_t (&b)[TN]) {
+    auto mfma_block = [&](auto tm_c, const half8_t (&a)[TM], const half8_t (&b)[TN]) {
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+        for (int i = 0; i < decltype(tm_c)::value; ++i)
 #pragma unroll
             for (int j = 0; j < TN; ++j)
                 acc[i][j] = BF ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a[i]),
@@ -403,67 +421,69 @@ __global__ __launch_bounds__(64 * WGM * WGN * KS, 2) void gemm_pipe_kernel(const
     // Instruction order inside one sub-step: after every MFMA a few of the vector instructions that
     // prepare the next sub-step's operands, so that a single wavefront keeps the matrix pipe busy
     // (an MFMA of this shape occupies it for 32 cycles, its issue only for 4).
-    auto interleave = [&](auto dsw, auto vmem) {
-        constexpr int kMfma = TM * TN;
+    auto interleave = [&](auto tm_c, auto dsw, auto vmem) {
+        constexpr int TMX = decltype(tm_c)::value, kMfma = TMX * TN;
 #pragma unroll
         for (int i = 0; i < kMfma; ++i) {
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);          // one MFMA
-            if (i < TM) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);      // one LDS fragment read
+            if (i < TMX) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);      // one LDS fragment read
             __builtin_amdgcn_sched_group_barrier(0x002, kMfma >= 8 ? 5 : 9, 0);     // vector ALU
             if (i < decltype(dsw)::value) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);    // LDS write
             if (i < decltype(vmem)::value) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);   // global load
         }
     };
     using I0 = std::integral_constant<int, 0>;
-    using IPA = std::integral_constant<int, PA>;
     using ITN2 = std::integral_constant<int, (1 + NCH) * TN>;      // loads issued by load_b
 
+    // The K range on TMX of the wavefront's TM row blocks (all of them, but in a last row tile)
+    auto k_loop = [&](auto tm_c) {
+    using IPA = std::integral_constant<int, SHORT ? decltype(tm_c)::value * 32 / RP : PA>;
     // One K slice.  On entry: stage `cur` holds slice kt; fa[0], fb[0] hold its sub-step 0 operands;
     // bset[set] holds its codes; the next PD - 1 slices' codes and the next AD slices' activations are in flight.
     auto step = [&](int kt, int set, uint32_t cur, uint32_t nxt) {
         // sub-step 0: operands of sub-step 1; publish slice kt+1's activations and, the staging
         // registers being free again, request those of slice kt+1+AD at once
-        read_frags(cur, 1, fa[1]);
+        read_frags(tm_c, cur, 1, fa[1]);
         dequant_frags(set, 1, fb[1]);
-        store_a(nxt, (set + 1) % AD);
-        load_a(kt + 1 + AD, (set + 1) % AD);
-        mfma_block(fa[0], fb[0]);
-        interleave(IPA{}, IPA{});
+        store_a(IPA{}, nxt, (set + 1) % AD);
+        load_a(IPA{}, kt + 1 + AD, (set + 1) % AD);
+        mfma_block(tm_c, fa[0], fb[0]);
+        interleave(tm_c, IPA{}, IPA{});
         __builtin_amdgcn_sched_barrier(0);
         // sub-step 1: operands of sub-step 2
-        read_frags(cur, 2, fa[0]);
+        read_frags(tm_c, cur, 2, fa[0]);
         dequant_frags(set, 2, fb[0]);
-        mfma_block(fa[1], fb[1]);
-        interleave(I0{}, I0{});
+        mfma_block(tm_c, fa[1], fb[1]);
+        interleave(tm_c, I0{}, I0{});
         __builtin_amdgcn_sched_barrier(0);
         __syncthreads();                // slice kt+1 is complete in stage `nxt`
         __builtin_amdgcn_sched_barrier(0);
         // sub-step 2: operands of sub-step 3 (last use of this slice's codes)
-        read_frags(cur, 3, fa[1]);
+        read_frags(tm_c, cur, 3, fa[1]);
         dequant_frags(set, 3, fb[1]);
-        mfma_block(fa[0], fb[0]);
-        interleave(I0{}, I0{});
+        mfma_block(tm_c, fa[0], fb[0]);
+        interleave(tm_c, I0{}, I0{});
         __builtin_amdgcn_sched_barrier(0);
         // sub-step 3: operands of the next slice's sub-step 0; this slice's code registers are free,
         // so the codes of slice kt+PD are requested into them
         load_b(kt + PD, set);
-        read_frags(nxt, 0, fa[0]);
+        read_frags(tm_c, nxt, 0, fa[0]);
         dequant_frags((set + 1) % PD, 0, fb[0]);
-        mfma_block(fa[1], fb[1]);
-        interleave(I0{}, ITN2{});
+        mfma_block(tm_c, fa[1], fb[1]);
+        interleave(tm_c, I0{}, ITN2{});
         __builtin_amdgcn_sched_barrier(0);
     };
 
     // ---- prologue
-    load_a(kt_begin, 0);
+    load_a(IPA{}, kt_begin, 0);
 #pragma unroll
     for (int d = 0; d < PD; ++d) load_b(kt_begin + d, d);
     const uint32_t ring = KS == 2 ? (uint32_t)half * kStages * kStageBytes : 0u;
-    store_a(ring, 0);
+    store_a(IPA{}, ring, 0);
 #pragma unroll
-    for (int d = 1; d <= AD; ++d) load_a(kt_begin + d, d % AD);
+    for (int d = 1; d <= AD; ++d) load_a(IPA{}, kt_begin + d, d % AD);
     __syncthreads();
-    read_frags(ring, 0, fa[0]);
+    read_frags(tm_c, ring, 0, fa[0]);
     dequant_frags(0, 0, fb[0]);
 
     uint32_t s0 = ring, s1 = ring + kStageBytes, s2 = ring + 2 * kStageBytes;     // current, next, the one after
@@ -483,6 +503,16 @@ __global__ __launch_bounds__(64 * WGM * WGN * KS, 2) void gemm_pipe_kernel(const
             step(kt + 3, 3 % PD, s1, s2);
             advance_ring();
         }
+    }
+    };
+    if constexpr (SHORT) {
+        static_assert(PA * RP == TM * 32, "a loader pass is whole row blocks");
+        const int blocks = (int)((min((int64_t)BM, M - m0) + 31) / 32);
+        if (blocks == TM) k_loop(std::integral_constant<int, TM>{});
+        else if (blocks == 3) k_loop(std::integral_constant<int, 3>{});
+        else k_loop(std::integral_constant<int, 2>{});
+    } else {
+        k_loop(std::integral_constant<int, TM>{});
     }
     if (KS == 2) {
         // The upper half's sums are added to the lower half's, through LDS.  An odd number of pairs of slices gives the
@@ -1050,6 +1080,8 @@ int launch_pipe(const half_t* x, int64_t M, const uint4* c, int64_t N, int64_t K
     }
     SkArgs sk{0, 0, 0, 0, nullptr, nullptr};
     unsigned grid = (unsigned)(per_xcd * kNumXcd);
+    const bool last_short = BM == 128 && BN == 256 && splits == 1 && m_tiles > 1 && M % BM != 0 && M % BM <= BM - 32;
+    if (last_short) grid = (unsigned)((((m_tiles - 1) * n_tiles + kNumXcd - 1) / kNumXcd + (n_tiles + kNumXcd - 1) / kNumXcd) * kNumXcd);
     if (skp.on) {
         if (workspace == nullptr || workspace_bytes < skp.workspace_bytes) return E0M4_ERR_WORKSPACE;
         sk.enabled = 1;
@@ -1065,13 +1097,19 @@ int launch_pipe(const half_t* x, int64_t M, const uint4* c, int64_t N, int64_t K
     }
     // 96 KiB for the large tile: above the default limit.  (KS = 2: two rings; one half's sums, afterwards.)
     constexpr size_t lds = std::max((size_t)KS * kStages * BM * kRowBytes, KS == 2 ? (size_t)BM * BN * sizeof(float) : 0);
+    auto launch = [&](auto kernel, std::atomic<uint64_t>& lds_allowed) -> int {
+        const int arc = allow_dynamic_lds(reinterpret_cast<const void*>(kernel), (int)lds, lds_allowed);
+        if (arc != E0M4_OK) return arc;
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(64 * WGM * WGN * KS), lds, stream, x, M, c, N, K, y, (int)m_tiles, (int)n_tiles, splits,
+                           partial, fu, sk);
+        return check_launch();
+    };
+    if constexpr (BM == 128 && BN == 256) {
+        static std::atomic<uint64_t> lds_allowed{0};
+        if (last_short) return launch(&gemm_pipe_kernel<G, WGM, WGN, FUSED, BM, BN, E8, BF, KS, true>, lds_allowed);
+    }
     static std::atomic<uint64_t> lds_allowed{0};
-    const int arc = allow_dynamic_lds(reinterpret_cast<const void*>(&gemm_pipe_kernel<G, WGM, WGN, FUSED, BM, BN, E8, BF, KS>),
-                                      (int)lds, lds_allowed);
-    if (arc != E0M4_OK) return arc;
-    hipLaunchKernelGGL((gemm_pipe_kernel<G, WGM, WGN, FUSED, BM, BN, E8, BF, KS>), dim3(grid), dim3(64 * WGM * WGN * KS), lds, stream, x,
-                       M, c, N, K, y, (int)m_tiles, (int)n_tiles, splits, partial, fu, sk);
-    int rc = check_launch();
+    const int rc = launch(&gemm_pipe_kernel<G, WGM, WGN, FUSED, BM, BN, E8, BF, KS>, lds_allowed);
     if (rc != E0M4_OK || splits == 1) return rc;
     if (FUSED) {
         const int64_t n_out = f.swiglu ? N / 2 : N;
