@@ -1,19 +1,21 @@
-// Small batch on long rows: Y[M,N] = X[M,K] * dequant(packed)^T (+ residual) for 2 <= M <= 16, groups of 128, where M rows of X
-// exceed the LDS and every workgroup has one row block (16 weight rows).  Paper: section "Operator and lagging optimizations"
-// (vector-matrix product of the decoding stage, bound by memory bandwidth) with the dequantisation of section "E0M4 FP4
-// quantization" fused in registers.
+// Small batch with X taken block by block: Y[M,N] = X[M,K] * dequant(packed)^T (+ residual) for few rows of X (16, 8 and 4 with
+// groups of 128, 64 and 32) and one or two row blocks (of 16 weight rows) per workgroup.  Paper: section "Operator and lagging
+// optimizations" (vector-matrix product of the decoding stage, bound by memory bandwidth) with the dequantisation of section
+// "E0M4 FP4 quantization" fused in registers.
 //
-// The same products and sums, in the same order, as gemv_mfma_kernel (e0m4_gemv_mfma.hip) walking K in phases, to the bit:
-// exact code values on v_mfma_f32_16x16x32_f16 with the two kinds of code pairs apart, the group's affine map per k block, one
-// sum per work item of four k blocks; the items of one place in all phases are added first, then the places.  What differs is
-// how X comes in.  There a phase stages 128 KiB of X behind two barriers, with half of the wavefronts idle, since a phase is
-// eight items long and there are sixteen of them.  Here nothing is shared before the end and no barrier stands in the loop: a
-// wavefront takes the items w, w + 8, ..., loads the rows of X of its own k blocks two ahead and turns them into operand order
-// in a piece of LDS of its own, and parks an item's sums in LDS.
+// The same products and sums, in the same order, as gemv_mfma_kernel (e0m4_gemv_mfma.hip), to the bit: exact code values on
+// v_mfma_f32_16x16x32_f16 with the two kinds of code pairs apart, the group's affine map per k block, one running sum per
+// wavefront of that kernel and phase of K ("unit": of the work items of four k blocks r, r + W, ... of phase p, for every row
+// block), the phases' sums of a wavefront added first, then the wavefronts'.  What differs is how X comes in.  There a
+// workgroup stages M rows of X, or as much of K as fits the LDS, behind barriers, a piece of work that does not shrink with
+// the row blocks that share it.  Here nothing is shared before the end and no barrier stands in the loop: a wavefront takes the
+// units w, w + 8, ..., loads the rows of X of its own k blocks two ahead, turns them into operand order in a piece of LDS of its
+// own and parks a unit's sums in LDS.
 //
-// What bounds it: X from L2 (every workgroup needs all 2 M K bytes: at M = 16 512 KiB for 136 KiB of weights).  With a
-// residual, in phases and here (us): 2048 x 16384 at M = 16 19.8 -> 11.6, at M = 6 13.1 -> 9.5; 4096 x 13696 20.2 -> 14.5 and
-// 14.7 -> 11.1; 4096 x 24576 30.0 -> 22.7 and, at M = 8, 22.0 -> 17.1.
+// What bounds it: X from L2 (every workgroup needs all 2 M K bytes: at M = 16 and K = 16384 512 KiB for 136 KiB of weights).
+// With a residual, X staged and here (us): 4096 x 13696 at M = 16 20.6 -> 11.8, at M = 6 14.0 -> 10.4; 2048 x 16384 20.1 -> 12.4
+// and 13.4 -> 10.5; two row blocks: 5120 x 13696 27.0 -> 18.9, 5120 x 5120 14.0 -> 9.2; groups of 64 at M = 8: 5120 x 13696
+// 21.5 -> 16.1, 2560 x 8192 10.5 -> 7.8; groups of 32 at M = 4: 5120 x 5120 10.9 -> 8.5.
 #include "e0m4_device.h"
 #include "e0m4_host.h"
 
@@ -28,27 +30,38 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 constexpr int kItemWaves = 8;
 constexpr int kItemThreads = kItemWaves * 64;
 constexpr int kItemBlocks = 4;                  // k blocks of 128 per work item
-constexpr int kMaxItems = 96;                   // their sums (1 KiB each) and the wavefronts' X (4 KiB each) share the LDS
+constexpr int kMaxSums = 96;                    // of units and row blocks: 1 KiB each, beside the wavefronts' X (4 KiB each)
+constexpr int kZeroBytes = 64;                  // several groups per block: the zeros of a k-group that is not the row's
 constexpr int kItemXBytes = 16 * kBlockK * 2;   // sixteen rows of a k block
 
 // XE: loads of X per k block, four rows each (calls of up to 4 and 8 rows make one and two; the other rows of the tile stay
-// what LDS held, and so do their sums, which nobody stores)
-template <int XE>
+// what LDS held, and so do their sums, which nobody stores).  R: row blocks per workgroup.  GS: groups per k block; a row of X
+// is then GS rows of the MFMA, with zeros for the k-groups of the other groups.
+template <int XE, int R, int GS>
 __global__ __launch_bounds__(kItemThreads, 2) void gemv_items_kernel(const half_t* __restrict__ X, const uint4* __restrict__ packed,
                                                                      half_t* __restrict__ Y, const half_t* __restrict__ residual,
-                                                                     int M, uint32_t N32, uint32_t K32, int items_ph)
+                                                                     int M, uint32_t N32, uint32_t K32, int rb_base, int rb_rem,
+                                                                     int order_waves, int items_ph)
 {
+    constexpr int SLOT = 16 / GS;
+    constexpr uint32_t kFirstX = GS > 1 ? kZeroBytes : 0;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int64_t N = N32;
     const int nkb = (int)(K32 / kBlockK), items = (nkb + kItemBlocks - 1) / kItemBlocks;
+    const int n_ph = (items + items_ph - 1) / items_ph, items_end = items - (n_ph - 1) * items_ph;
+    const int units_ph = min(order_waves, items_ph);
     const int t = threadIdx.x;
     const int lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int n_l = lane & 15, g_l = lane >> 4;         // weight row and chunk of this lane; also (row of X, k-group)
     const uint32_t fmask = frac_mask_vgpr(), fmask_low = frac_mask_low_vgpr();
-    unsigned char* xl = smem + wave * kItemXBytes;
-    float* red = reinterpret_cast<float*>(smem + kItemWaves * kItemXBytes);     // [items][16 m][16 n]
-    const char* base = reinterpret_cast<const char*>(packed) + (size_t)blockIdx.x * ((size_t)nkb * block_bytes(128));
+    unsigned char* xl = smem + kFirstX + wave * kItemXBytes;
+    float* red = reinterpret_cast<float*>(smem + kFirstX + kItemWaves * kItemXBytes);   // [units][R][16 m][16 n]
+    const uint32_t rb_stride = (uint32_t)nkb * block_bytes(128 / GS);
+    const int64_t rb0 = (int64_t)blockIdx.x * rb_base + min((int)blockIdx.x, rb_rem);
+    const int n_rb = rb_base + ((int)blockIdx.x < rb_rem ? 1 : 0);
+    const char* base = reinterpret_cast<const char*>(packed) + (size_t)rb0 * rb_stride;
+    const uint32_t rb_next = n_rb > 1 ? rb_stride : 0;  // (no second row block: the first again, its sums are not used)
 
     // X: load number e brings rows 4 e .. 4 e + 3 of the k block, 16 bytes per lane.  A piece of eight activations (of one code
     // word) is two halves, those of the pairs that read 2 + c/8 and those that read 2 + c/128; unit u = 4 q + 2 (w / 2) + half
@@ -66,7 +79,14 @@ __global__ __launch_bounds__(kItemThreads, 2) void gemv_items_kernel(const half_
 #pragma unroll
     for (int wp = 0; wp < 2; ++wp)
 #pragma unroll
-        for (int hl = 0; hl < 2; ++hl) x_rd[wp][hl] = (uint32_t)(n_l * kBlockK * 2 + (((g_l * 4 + wp * 2 + hl) ^ n_l) << 4));
+        for (int hl = 0; hl < 2; ++hl) {
+            const int row = n_l % SLOT;
+            const bool own = GS == 1 || n_l / SLOT == g_l * GS / 4;
+            x_rd[wp][hl] = own ? kFirstX + (uint32_t)(wave * kItemXBytes + row * kBlockK * 2 + (((g_l * 4 + wp * 2 + hl) ^ row) << 4)) : 0u;
+        }
+    if (GS > 1) {                                       // (every wavefront before its own reads, with the same zeros)
+        if (lane < kZeroBytes / 4) reinterpret_cast<uint32_t*>(smem)[lane] = 0;
+    }
 
     // (a k block beyond the last is requested through a resource of no bytes: zeros, without an access to memory)
     auto rsrc_if = [](const void* p, bool in) -> __amdgpu_buffer_rsrc_t {
@@ -76,57 +96,99 @@ __global__ __launch_bounds__(kItemThreads, 2) void gemv_items_kernel(const half_
         void* q = reinterpret_cast<void*>(((uint64_t)hi << 32) | lo);
         return __builtin_amdgcn_make_buffer_rsrc(q, 0, __builtin_amdgcn_readfirstlane(in ? 0x7fffffff : 0), 0x00020000);
     };
-    u32x4 c[kItemBlocks], xr[2][XE];
-    uint32_t pw[kItemBlocks];
-    const uint32_t param_voff = (uint32_t)nkb * kBlockCodeBytes + 4 * n_l;
+    u32x4 c[kItemBlocks][R], xr[2][XE];
+    uint32_t pw[kItemBlocks][R];
+    const uint32_t param_voff = (uint32_t)nkb * kBlockCodeBytes + 4 * ((g_l * GS / 4) * kBlockRows + n_l);
     auto load_w = [&](int kb, int d) {
         const __amdgpu_buffer_rsrc_t rsrc = rsrc_if(base, kb < nkb);
-        c[d] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane * 16, kb * kBlockCodeBytes, 0);
-        pw[d] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)param_voff, kb * (4 * kBlockRows), 0);
+#pragma unroll
+        for (int s = 0; s < R; ++s) {
+            c[d][s] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane * 16, (int)(s * rb_next + (uint32_t)kb * kBlockCodeBytes), 0);
+            pw[d][s] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)param_voff, (int)(s * rb_next + (uint32_t)kb * (4 * kBlockRows * GS)), 0);
+        }
     };
     auto load_x = [&](int kb, int d) {
         const __amdgpu_buffer_rsrc_t rsrc = rsrc_if(X, kb < nkb);
 #pragma unroll
         for (int e = 0; e < XE; ++e) xr[d][e] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)x_voff[e], kb * (kBlockK * 2), 0);
     };
+    // Units in the order u = p * units_ph + r, dealt round the wavefronts; where that gives a wavefront the same units of every
+    // phase, `turn` on from phase to phase, the number of units with one item more than the others.  Item i of phase p is item p * items_ph + i of all.  Past the last unit (in a last
+    // phase of fewer items than units_ph, too) the item is one without k blocks.
+    struct Place {
+        int ph, r, i;
+    };
+    auto items_of = [&](int p) -> int { return p == n_ph - 1 ? items_end : items_ph; };
+    auto there = [&](const Place& q) -> bool { return q.ph < n_ph && q.r < items_of(q.ph); };
+    auto item_of = [&](const Place& q) -> int { return there(q) ? q.ph * items_ph + q.i : items; };
+    const int turn = units_ph % kItemWaves == 0 ? items_ph % order_waves : 0;
+    auto settle = [&](Place q) -> Place {
+        while (q.r >= units_ph) {
+            q.r -= units_ph;
+            if (units_ph % kItemWaves == 0) q.r = (q.r - turn) & (kItemWaves - 1);
+            ++q.ph;
+        }
+        q.i = q.r;
+        return q;
+    };
+    auto after = [&](Place q) -> Place {
+        if (q.i + order_waves < items_of(q.ph)) {
+            q.i += order_waves;
+            return q;
+        }
+        q.r += kItemWaves;
+        return settle(q);
+    };
+    Place at = settle(Place{0, wave, 0});
     // (in the order of use: a wait for one request is a wait for all before it)
 #pragma unroll
     for (int j = 0; j < kItemBlocks; ++j) {
-        if (j < 2) load_x(wave * kItemBlocks + j, j);
-        load_w(wave * kItemBlocks + j, j);
+        if (j < 2) load_x(item_of(at) * kItemBlocks + j, j);
+        load_w(item_of(at) * kItemBlocks + j, j);
     }
 
     const floatx4 zero4 = {0.f, 0.f, 0.f, 0.f};
     const half_t one = (half_t)1.f;
     const half8_t ones8 = {one, one, one, one, one, one, one, one};
     auto mfma = [](const half8_t& a, const half8_t& b, const floatx4& v) -> floatx4 { return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, v, 0, 0, 0); };
-    for (int item = wave; item < items; item += kItemWaves) {
-        floatx4 ysum = zero4;
+    floatx4 ysum[R];
+#pragma unroll
+    for (int s = 0; s < R; ++s) ysum[s] = zero4;
+    while (there(at)) {
+        const Place next = after(at);
+        const int kb_at = item_of(at) * kItemBlocks, kb_next = item_of(next) * kItemBlocks;
 #pragma unroll
         for (int j = 0; j < kItemBlocks; ++j) {
-            const int kb = item * kItemBlocks + j;
 #pragma unroll
             for (int e = 0; e < XE; ++e) {
                 const half8_t v = __builtin_bit_cast(half8_t, xr[j & 1][e]);
                 *reinterpret_cast<half4_t*>(xl + x_wr[e][0]) = half4_t{v[0], v[1], v[6], v[7]};
                 *reinterpret_cast<half4_t*>(xl + x_wr[e][1]) = half4_t{v[2], v[3], v[4], v[5]};
             }
-            load_x(j < 2 ? kb + 2 : kb - 2 + kItemWaves * kItemBlocks, j & 1);
+            load_x(j < 2 ? kb_at + j + 2 : kb_next + j - 2, j & 1);
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");     // read back by the wavefront that wrote it
             __builtin_amdgcn_wave_barrier();
             half8_t xh[2], xs[2];
 #pragma unroll
             for (int wp = 0; wp < 2; ++wp) {
-                xh[wp] = *reinterpret_cast<const half8_t*>(xl + x_rd[wp][0]);
-                xs[wp] = *reinterpret_cast<const half8_t*>(xl + x_rd[wp][1]);
+                xh[wp] = *reinterpret_cast<const half8_t*>(smem + x_rd[wp][0]);
+                xs[wp] = *reinterpret_cast<const half8_t*>(smem + x_rd[wp][1]);
             }
+            floatx4 sh = zero4, sl = zero4;
+#pragma unroll
+            for (int wp = 0; wp < 2; ++wp) {
+                sh = mfma(xh[wp], ones8, sh);
+                sl = mfma(xs[wp], ones8, sl);
+            }
+            const floatx4 sx = sh + sl, sx30 = 30.f * sl;
+#pragma unroll
+            for (int s = 0; s < R; ++s) {
             half2_t p[4][4];
 #pragma unroll
-            for (int w = 0; w < 4; ++w) w1_pairs_mixed(c[j][w], fmask, fmask_low, p[w]);
-            const float sc = (float)param_scale(pw[j]);
-            const float bi = (float)param_bias(pw[j]);
-            load_w(kb + kItemWaves * kItemBlocks, j);
-            floatx4 acc_h = zero4, acc_l = zero4, sh = zero4, sl = zero4;
+            for (int w = 0; w < 4; ++w) w1_pairs_mixed(c[j][s][w], fmask, fmask_low, p[w]);
+            const float sc = (float)param_scale(pw[j][s]);
+            const float bi = (float)param_bias(pw[j][s]);
+            floatx4 acc_h = zero4, acc_l = zero4;
 #pragma unroll
             for (int wp = 0; wp < 2; ++wp) {
                 const half2_t* w0 = p[2 * wp];
@@ -135,72 +197,124 @@ __global__ __launch_bounds__(kItemThreads, 2) void gemv_items_kernel(const half_
                 const half8_t wl = {w0[1][0], w0[1][1], w0[2][0], w0[2][1], w1[1][0], w1[1][1], w1[2][0], w1[2][1]};
                 acc_h = mfma(xh[wp], wh, acc_h);
                 acc_l = mfma(xs[wp], wl, acc_l);
-                sh = mfma(xh[wp], ones8, sh);
-                sl = mfma(xs[wp], ones8, sl);
             }
-            const floatx4 sx = sh + sl, sx30 = 30.f * sl;
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-                ysum[r] += sc * ((acc_h[r] + 16.f * acc_l[r] - sx30[r]) - bi * sx[r]);
+                ysum[s][r] += sc * ((acc_h[r] + 16.f * acc_l[r] - sx30[r]) - bi * sx[r]);
+            }
+            load_w(kb_next + j, j);
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             __builtin_amdgcn_wave_barrier();            // X is read before the next block's is written
         }
+        if (next.ph != at.ph || next.r != at.r) {       // the unit is complete
 #pragma unroll
-        for (int r = 0; r < 4; ++r) red[(item * 16 + 4 * g_l + r) * kBlockRows + n_l] = ysum[r];
+            for (int s = 0; s < R; ++s) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) red[(((at.ph * units_ph + at.r) * R + s) * 16 + 4 * g_l + r) * kBlockRows + n_l] = ysum[s][r];
+                ysum[s] = zero4;
+            }
+        }
+        at = next;
+    }
+    // The sums of all phases per wavefront of the order, then (in LDS that X has left) the wavefronts' in their order: the items i
+    // of row block s that wavefront v has are those with (s * items of the phase + i) % W = v, the first of them r below.  (In one
+    // pass over both, each sum a chain of dependent reads: 2048 x 16384 at M = 16 15.2 us, in two 12.4.)
+    __syncthreads();
+    float* cells = reinterpret_cast<float*>(smem + kFirstX);        // [W][R][16 m][16 n]
+    for (int c0 = wave >> 2; c0 < order_waves * R; c0 += kItemWaves / 4) {
+        const int v = c0 / R, s = c0 % R, at_cell = t & 255;
+        const int r_all = (v - s * items_ph) & (order_waves - 1), r_end = (v - s * items_end) & (order_waves - 1);
+        float cell = 0.f;
+        if (r_all < items_ph)
+            for (int p = 0; p < n_ph - 1; ++p) cell += red[((p * units_ph + r_all) * R + s) * (16 * kBlockRows) + at_cell];
+        if (r_end < items_end) cell += red[(((n_ph - 1) * units_ph + r_end) * R + s) * (16 * kBlockRows) + at_cell];
+        cells[c0 * (16 * kBlockRows) + at_cell] = cell;
     }
     __syncthreads();
-    if (t < 16 * kBlockRows) {
-        const int m = t >> 4;
-        const int64_t col = (int64_t)blockIdx.x * kBlockRows + (t & 15);
-        float s = 0.f;
-        for (int i = 0; i < min(items_ph, items); ++i) {
-            float cell = red[i * (16 * kBlockRows) + t];
-            for (int g = i + items_ph; g < items; g += items_ph) cell += red[g * (16 * kBlockRows) + t];
-            s += cell;
+    const int s = t >> 8, m = (t >> 4) & 15;
+    if (s < n_rb) {
+        const int64_t col = (rb0 + s) * kBlockRows + (t & 15);
+        float y = 0.f;
+        for (int v0 = 0; v0 < order_waves; v0 += 8) {
+            float cell[8][GS];
+#pragma unroll
+            for (int v = 0; v < 8; ++v)
+#pragma unroll
+                for (int gg = 0; gg < GS; ++gg)
+                    cell[v][gg] = cells[(((v0 + v) * R + s) * 16 + min(m + SLOT * gg, 15)) * kBlockRows + (t & 15)];
+#pragma unroll
+            for (int v = 0; v < 8; ++v)
+#pragma unroll
+                for (int gg = 0; gg < GS; ++gg) y += cell[v][gg];
         }
         if (m < M && col < N) {
-            if (residual) s += (float)residual[(int64_t)m * N + col];
-            Y[(int64_t)m * N + col] = (half_t)s;
+            if (residual) y += (float)residual[(int64_t)m * N + col];
+            Y[(int64_t)m * N + col] = (half_t)y;
         }
     }
 }
 
-template <int XE>
-int launch_items(const half_t* X, int64_t M, const uint4* packed, int64_t N, int64_t K, int items_ph, half_t* Y, const half_t* residual,
-                 hipStream_t stream)
+static_assert(kItemWaves * kItemXBytes >= 16 * 2 * 16 * kBlockRows * (int)sizeof(float), "the wavefronts' sums take the place of X");
+
+int order_units(int64_t K, int items_ph, int waves)
 {
-    const int items = (int)((K / kBlockK + kItemBlocks - 1) / kItemBlocks);
-    const int lds = kItemWaves * kItemXBytes + items * 16 * kBlockRows * (int)sizeof(float);
+    const int items = (int)((K / kBlockK + kItemBlocks - 1) / kItemBlocks), n_ph = (items + items_ph - 1) / items_ph;
+    return n_ph * std::min(waves, items_ph);
+}
+
+template <int XE, int R, int GS>
+int launch_items(const ItemsPlan& p, const half_t* X, int64_t M, const uint4* packed, int64_t N, int64_t K, half_t* Y,
+                 const half_t* residual, hipStream_t stream)
+{
+    constexpr int kFixed = (GS > 1 ? kZeroBytes : 0) + kItemWaves * kItemXBytes, kSum = 16 * kBlockRows * (int)sizeof(float);
+    const int lds = kFixed + order_units(K, p.items_ph, p.waves) * R * kSum;
     static std::atomic<uint64_t> lds_allowed{0};
-    const int arc = allow_dynamic_lds(reinterpret_cast<const void*>(&gemv_items_kernel<XE>),
-                                      kItemWaves * kItemXBytes + kMaxItems * 16 * kBlockRows * (int)sizeof(float), lds_allowed);
+    const int arc = allow_dynamic_lds(reinterpret_cast<const void*>(&gemv_items_kernel<XE, R, GS>), kFixed + kMaxSums * kSum, lds_allowed);
     if (arc != E0M4_OK) return arc;
-    hipLaunchKernelGGL(gemv_items_kernel<XE>, dim3((unsigned)row_blocks(N)), dim3(kItemThreads), lds, stream, X, packed, Y, residual,
-                       (int)M, (uint32_t)N, (uint32_t)K, items_ph);
+    hipLaunchKernelGGL((gemv_items_kernel<XE, R, GS>), dim3((unsigned)p.grid), dim3(kItemThreads), lds, stream, X, packed, Y, residual,
+                       (int)M, (uint32_t)N, (uint32_t)K, p.rb_base, p.rb_rem, p.waves, p.items_ph);
     return check_launch();
+}
+
+template <int R>
+int launch_items_m(const ItemsPlan& p, const half_t* x, int64_t M, const uint4* c, int64_t N, int64_t K, int group, half_t* y,
+                   const half_t* r, hipStream_t stream)
+{
+    if (group == 32) return launch_items<1, R, 4>(p, x, M, c, N, K, y, r, stream);
+    if (group == 64) return M <= 4 ? launch_items<1, R, 2>(p, x, M, c, N, K, y, r, stream) : launch_items<2, R, 2>(p, x, M, c, N, K, y, r, stream);
+    if (M <= 4) return launch_items<1, R, 1>(p, x, M, c, N, K, y, r, stream);
+    if (M <= 8) return launch_items<2, R, 1>(p, x, M, c, N, K, y, r, stream);
+    return launch_items<4, R, 1>(p, x, M, c, N, K, y, r, stream);
 }
 
 }  // namespace
 
-// `items_ph`: work items per phase of the order of the sums, `waves` the wavefronts of that order: an item per wavefront and
-// phase at most, or a wavefront's items of a phase would be one sum.
-bool gemv_items_supported(int64_t M, int64_t K, int items_ph, int waves)
+bool gemv_items_supported(const ItemsPlan& p, int64_t M, int64_t N, int64_t K, int group)
 {
-    return M >= 2 && M <= 16 && K > 0 && K % kBlockK == 0 && items_ph > 0 && items_ph <= waves &&
-           (K / kBlockK + kItemBlocks - 1) / kItemBlocks <= kMaxItems;
+    if (M < 2 || M > 16 * group / 128 || N <= 0 || K <= 0 || K % kBlockK != 0 || p.items_ph <= 0 || (p.waves != 8 && p.waves != 16)) return false;
+    const int most = p.rb_base + (p.rb_rem > 0 ? 1 : 0);
+    return p.rb_base >= 1 && most <= 2 && order_units(K, p.items_ph, p.waves) * most <= kMaxSums;
 }
 
-int launch_gemv_items(const void* X, int64_t M, const void* packed, int64_t N, int64_t K, int items_ph, int waves, void* Y,
+// Where it is the faster one (both sides with a residual, cold weights): nearly everywhere; not for two rows (2048 x 16384 9.7 and
+// 9.8 us, 8192 x 8192 12.5 and 11.6), nor for up to four with two row blocks and rows that take sixteen wavefronts to stage (5120 x
+// 13696 at M = 4 16.1 and 14.8; M = 6 16.0 and 18.5).
+bool gemv_items_pays(const ItemsPlan& p, int64_t M, int group)
+{
+    const bool two = p.rb_base + (p.rb_rem > 0 ? 1 : 0) > 1;
+    return group != 128 || M >= (two && p.waves == 16 ? 5 : 3);
+}
+
+int launch_gemv_items(const ItemsPlan& p, const void* X, int64_t M, const void* packed, int64_t N, int64_t K, int group, void* Y,
                       const void* residual, hipStream_t stream)
 {
-    if (!gemv_items_supported(M, K, items_ph, waves) || N <= 0) return E0M4_ERR_SHAPE;
+    if (!gemv_items_supported(p, M, N, K, group)) return E0M4_ERR_SHAPE;
     const half_t* x = static_cast<const half_t*>(X);
     const uint4* c = static_cast<const uint4*>(packed);
     half_t* y = static_cast<half_t*>(Y);
     const half_t* r = static_cast<const half_t*>(residual);
-    if (M <= 4) return launch_items<1>(x, M, c, N, K, items_ph, y, r, stream);
-    if (M <= 8) return launch_items<2>(x, M, c, N, K, items_ph, y, r, stream);
-    return launch_items<4>(x, M, c, N, K, items_ph, y, r, stream);
+    return p.rb_base + (p.rb_rem > 0 ? 1 : 0) == 1 ? launch_items_m<1>(p, x, M, c, N, K, group, y, r, stream)
+                                                   : launch_items_m<2>(p, x, M, c, N, K, group, y, r, stream);
 }
 
 }  // namespace e0m4

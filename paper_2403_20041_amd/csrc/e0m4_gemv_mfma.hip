@@ -883,11 +883,14 @@ template <int W, bool FUSED>
 int launch_mfma(const MfmaPlan& p, const void* X, int64_t M, const void* packed, int64_t N, int64_t K, void* Y,
                 hipStream_t stream, const GemvFusion& fu = GemvFusion{}, int gs = 1)
 {
-    // one row block per workgroup: the kernel without phases gives the same bits (gemv_mfma 2: not)
-    const int items_ph = p.kb_phase / kSuper;
-    if (gs == 1 && p.kb_phase > 0 && p.rb_base == 1 && p.rb_rem == 0 && !fu.gamma && !fu.swiglu && fu.m_total == 0 &&
-        knob("gemv_mfma") != 2 && gemv_items_supported(M, K, items_ph, W))
-        return launch_gemv_items(X, M, packed, N, K, items_ph, W, Y, fu.residual, stream);
+    if constexpr (W >= 8) {
+        const int items = (int)((k_blocks(K) + kSuper - 1) / kSuper);
+        const ItemsPlan ip{p.grid, p.rb_base, p.rb_rem, W, p.kb_phase > 0 ? p.kb_phase / kSuper : items};
+        const bool xreg = gs == 1 && W <= 8 && p.kb_phase == 0 && p.step_item == 0;
+        if (!fu.gamma && !fu.swiglu && fu.m_total == 0 && !xreg && knob("gemv_mfma") != 2 && knob("gemv_mfma") != 3 &&
+            gemv_items_supported(ip, M, N, K, kG / gs) && gemv_items_pays(ip, M, kG / gs))
+            return launch_gemv_items(ip, X, M, packed, N, K, kG / gs, Y, fu.residual, stream);
+    }
     if (gs == 2) return launch_mfma_groups<W, FUSED, 2>(p, X, M, packed, N, K, Y, stream, fu);
     if (gs == 4) return launch_mfma_groups<W, FUSED, 4>(p, X, M, packed, N, K, Y, stream, fu);
     if (p.kb_phase > 0) return launch_mfma_phased<W, FUSED, false>(p, X, M, packed, N, K, Y, stream, fu);

@@ -81,9 +81,16 @@ bool gemv_mfma_whole_rows(const Fusion& f, int64_t M, int64_t N, int64_t K, int 
 bool gemv_mfma8_whole_rows(const Fusion& f, int64_t M, int64_t N, int64_t K);
 int launch_gemv_mfma_fused(const Fusion& f, const void* X, int64_t M, const void* packed, int64_t N, int64_t K, void* Y,
                            hipStream_t stream, int chunks = 1, int group = 128);
-// Its plain and residual calls with K in phases and one row block per workgroup (e0m4_gemv_items.hip)
-bool gemv_items_supported(int64_t M, int64_t K, int items_ph, int waves);
-int launch_gemv_items(const void* X, int64_t M, const void* packed, int64_t N, int64_t K, int items_ph, int waves, void* Y,
+// Its plain and residual calls with one or two row blocks per workgroup, where X block by block is the faster way, to the same bits
+// (e0m4_gemv_items.hip).  The plan is that kernel's: wavefronts and work items per phase give the order of the sums.
+struct ItemsPlan {
+    int64_t grid;
+    int rb_base, rb_rem;
+    int waves, items_ph;
+};
+bool gemv_items_supported(const ItemsPlan& p, int64_t M, int64_t N, int64_t K, int group);
+bool gemv_items_pays(const ItemsPlan& p, int64_t M, int group);
+int launch_gemv_items(const ItemsPlan& p, const void* X, int64_t M, const void* packed, int64_t N, int64_t K, int group, void* Y,
                       const void* residual, hipStream_t stream);
 // Small-batch path with the weight operand dequantised in registers: 2 <= M <= 128, any group (e0m4_gemv_dq.hip).
 // (`pays`: it is expected to beat the GEMM)

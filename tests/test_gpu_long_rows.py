@@ -1,5 +1,5 @@
-"""Few rows of X on long rows of weights (2 <= M <= 16, X larger than the LDS, one row block per workgroup): the kernel that takes
-X block by block gives the bits of the one that stages it in phases, and both are the oracle's within its bar."""
+"""Few rows of X with one or two row blocks per workgroup: the kernel that takes X block by block gives the bits of the one that
+stages it, whole or in phases, and both are the oracle's within its bar."""
 import numpy as np
 import pytest
 
@@ -13,18 +13,34 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("N,K", [(130, 16384), (17, 9728), (203, 13696), (64, 24704), (48, 49152)])
 def test_same_bits_as_in_phases(e0m4, oracle, M, N, K):
     # (24704: 49 work items, the last of one block; 49152: the most items that the kernel takes)
-    (codes, _, _), What = assert_quantize_exact(e0m4, oracle, synth_inputs.weights(N, K, seed=5000 + N), 128)
+    same_bits(e0m4, oracle, M, N, K, 128, 0)
+
+
+# three workgroups asked for: two row blocks in some of them, one in others; items that leave a remainder over eight and sixteen
+# wavefronts, phases with and without one, a last phase of fewer items
+@pytest.mark.parametrize("N,target", [(80, 3), (96, 3), (17, 0)])
+@pytest.mark.parametrize("K", [1536, 2560, 5120, 5248, 8192, 13696, 16512])
+@pytest.mark.parametrize("M,G", [(3, 128), (5, 128), (16, 128), (3, 64), (4, 64), (6, 64), (8, 64), (3, 32), (4, 32)])
+def test_same_bits_as_staged(e0m4, oracle, M, G, K, N, target):
+    same_bits(e0m4, oracle, M, N, K, G, target)
+
+
+def same_bits(e0m4, oracle, M, N, K, G, target):
+    (codes, _, _), What = assert_quantize_exact(e0m4, oracle, synth_inputs.weights(N, K, seed=5000 + N), G)
     X = synth_inputs.activations(M, K, seed=5100 + M, outlier_frac=0.01)
     R = synth_inputs.activations(M, N, seed=5200 + M)
     Y, YR = [], []
+    e0m4.e0m4_set_knob("gemv_workgroups", target)
     try:
-        for mode in (0, 2):
+        for mode in (0 if G == 128 else 6, 2):          # (6: groups of 64 and 32 on these kernels wherever they can run)
             e0m4.e0m4_set_knob("gemv_mfma", mode)
-            Y.append(e0m4.e0m4_matmul(to_dev(X), codes, None, None, N, K, 128))
-            YR.append(e0m4.e0m4_matmul_fused(to_dev(X), codes, N, K, 128, residual=to_dev(R)))
+            Y.append(e0m4.e0m4_matmul(to_dev(X), codes, None, None, N, K, G))
+            YR.append(e0m4.e0m4_matmul_fused(to_dev(X), codes, N, K, G, residual=to_dev(R)))
     finally:
         e0m4.e0m4_set_knob("gemv_mfma", 0)
+        e0m4.e0m4_set_knob("gemv_workgroups", 0)
     Yref, absdot = oracle.matmul(X, What)
     check_matmul(Y[0], Yref, absdot, "M=%d K=%d" % (M, K))
-    assert torch.equal(Y[0].view(torch.int16), Y[1].view(torch.int16))
+    if G == 128:                                        # (other groups: 2 leaves the plain call to another kernel)
+        assert torch.equal(Y[0].view(torch.int16), Y[1].view(torch.int16))
     assert torch.equal(YR[0].view(torch.int16), YR[1].view(torch.int16))
