@@ -24,7 +24,7 @@ thread_local Knob g_knobs[] = {
     {"gemv_workgroups", 0},            // target number of workgroups of the small-M kernel
     // the matrix-core small-batch kernels: 1 neither; 2 activations staged in LDS always read from there; 3 their wavefront sums
     // reduced per row block; 4 plain matmuls on dequantised operands wherever that can run, 5 never; 6 staged also for groups of
-    // 64 and 32 wherever that can run
+    // 64 and 32 wherever that can run; 7 plain matmuls on exact codes without staging wherever that can run, 8 never
     {"gemv_mfma", 0},
     {"gemv_xreg", 0},                  // M = 1 kernel, a wavefront's activations in registers: 2 never
     {"gemm_variant", 0},               // 1: small-tile kernel; pipelined kernel with tiles of 2: 256 x 256, 3: 128 x 128, 4: 64 x 256, 5: 128 x 256
@@ -145,6 +145,16 @@ bool use_gemv_mfma_bf16(int64_t M, int64_t N, int64_t K, int group)
     const int k = knob("gemv_mfma");
     return M <= kGemvMaxM && k != 1 && (group == 128 || M >= 3 || k == 6) && gemv_mfma_supported(M, N, K, group);
 }
+// The kernel of use_gemv_dq on exact codes, which multiplies unrounded weights, for plain matmuls (gemv_mfma 7 forces it wherever it
+// can run; any other value but 0 leaves its calls to the kernels that have them otherwise).
+bool use_gemv_exact(int64_t M, int64_t N, int64_t K, int group, DqFormat format)
+{
+    const int k = knob("gemv_mfma");
+    if ((k != 0 && k != 7) || !gemv_exact_supported(M, N, K, group)) return false;
+    if (k == 7) return true;
+    if (gemm_steered() || N > (int64_t)1 << 24) return false;
+    return gemv_exact_pays(M, N, K, format, format == kDqFormatFp16 && small_batch_in_chunks(Fusion{}, M, N, K, group));
+}
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 // Shape rules shared by all entry points.
@@ -214,6 +224,7 @@ size_t e0m4_params_elems(int64_t N, int64_t K, int group)
 size_t e0m4_workspace_bytes(int64_t M, int64_t N, int64_t K, int group)
 {
     if (check_shape(N, K, group) != E0M4_OK || M <= 0 || N == 0 || K == 0) return 0;             // invalid or empty: nothing runs
+    if (use_gemv_exact(M, N, K, group, kDqFormatFp16)) return 0;
     if (small_m_on_vector(M, N, K)) return 0;           // the small-M kernels need none
     if (use_gemv_dq4(M, N, K, group)) return 0;
     if (use_gemv_mfma(M, N, K, group) || small_batch_in_chunks(Fusion{}, M, N, K, group)) return 0;
@@ -225,10 +236,11 @@ size_t e0m4_workspace_bytes(int64_t M, int64_t N, int64_t K, int group)
 static size_t norm_bytes(int64_t M, int64_t K) { return ((size_t)M * (size_t)K * 2 + 255) & ~(size_t)255; }
 
 // Which kernel family serves a fused matmul: 0 the decode kernel, 2 the small-batch kernel on the matrix
-// cores (both: everything in one launch), 3 that kernel on two chunks of rows, 1 the GEMM kernels (rms-norm,
-// if any, as a launch of its own before them).
+// cores (both: everything in one launch), 3 that kernel on chunks of rows, 4 (no operators) the kernel on exact codes, 1 the GEMM
+// kernels (rms-norm, if any, as a launch of its own before them).
 static int fused_path(const Fusion& f, int64_t M, int64_t N, int64_t K, int group)
 {
+    if (!f.any() && use_gemv_exact(M, N, K, group, kDqFormatFp16)) return 4;
     // (groups of 64 and 32 from three rows on: 1.1 - 2 x the vector kernel and the GEMM there, 10 - 25 % slower than the
     // vector kernel at two rows)
     if (knob("gemv_mfma") != 1 && gemv_mfma_fused_supported(f, M, N, K, group) &&
@@ -244,6 +256,7 @@ size_t e0m4_fused_workspace_bytes(int64_t M, int64_t N, int64_t K, int group, in
     if (epilogue != E0M4_EPILOGUE_NONE && epilogue != E0M4_EPILOGUE_SWIGLU) return 0;
     Fusion f;
     f.swiglu = epilogue == E0M4_EPILOGUE_SWIGLU;
+    f.residual = &f;                                    // (a call without any operator needs no more than one with a residual)
     if (fused_path(f, M, N, K, group) != 1) return 0;
     return (with_rmsnorm ? norm_bytes(M, K) : 0) + gemm_workspace_bytes(M, N, K, f.swiglu, true);
 }
@@ -358,6 +371,8 @@ int e0m4_matmul(const void* X, int64_t M, const void* codes, const void* scales,
     }
     if (!X || !codes) return E0M4_ERR_NULL;
     if (!aligned16(X) || !aligned16(codes)) return E0M4_ERR_ALIGN;
+    if (use_gemv_exact(M, N, K, group, kDqFormatFp16))
+        return launch_gemv_exact(X, M, codes, N, K, kDqFormatFp16, Y, (hipStream_t)stream);
     if (use_gemv_dq4(M, N, K, group))
         return launch_gemv_dq(X, M, codes, N, K, group, kDqFormatFp16, Y, (hipStream_t)stream);
     if (use_gemv_mfma(M, N, K, group)) return launch_gemv_mfma(X, M, codes, N, K, Y, (hipStream_t)stream, 1, group);
@@ -407,6 +422,7 @@ int e0m4_matmul_fused(const void* X, int64_t M, const void* rms_gamma, float rms
     const int path = fused_path(f, M, N, K, group);
     if (path == 2) return launch_gemv_mfma_fused(f, X, M, codes, N, K, Y, st, 1, group);
     if (path == 0) return launch_gemv_fused(f, X, M, codes, N, K, group, Y, st);
+    if (path == 4) return launch_gemv_exact(X, M, codes, N, K, kDqFormatFp16, Y, st);
     if (path == 3) return launch_gemv_mfma_fused(f, X, M, codes, N, K, Y, st, row_chunks(M), group);      // rows are independent
     if (N > (int64_t)1 << 24) return E0M4_ERR_SHAPE;    // 32-bit offsets in the GEMM epilogue
     const size_t nb = rms_gamma ? norm_bytes(M, K) : 0;
@@ -497,6 +513,8 @@ int e0m4_bf16_matmul(const void* X, int64_t M, const void* codes, int64_t N, int
     }
     if (!X || !codes) return E0M4_ERR_NULL;
     if (!aligned16(X) || !aligned16(codes)) return E0M4_ERR_ALIGN;
+    if (use_gemv_exact(M, N, K, group, kDqFormatBf16))
+        return launch_gemv_exact(X, M, codes, N, K, kDqFormatBf16, Y, (hipStream_t)stream);
     if ((knob("gemv_mfma") == 4 || !gemm_steered()) && use_gemv_dq(M, N, K, group, kDqFormatBf16))
         return launch_gemv_dq(X, M, codes, N, K, group, kDqFormatBf16, Y, (hipStream_t)stream);
     if (use_gemv_mfma_bf16(M, N, K, group)) return launch_gemv_mfma_bf16(X, M, codes, N, K, group, Y, (hipStream_t)stream);

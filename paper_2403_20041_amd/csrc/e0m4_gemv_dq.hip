@@ -69,11 +69,17 @@ __device__ inline __amdgpu_buffer_rsrc_t rsrc_if(const void* p, bool in)
 // XE: loads of X per tile and k block.  A load brings a quarter of the tile's rows (8-bit codes: half); calls of up to 4 and 8
 // rows make one and two of them, the other rows of the tile stay what LDS held and so do their sums, which nobody stores.
 // Groups of 32 at 4096 x 4096: M = 3 6.0 -> 5.3 us with one load for four, M = 8 6.1 -> 5.5 with two.
-template <DqFormat FMT, int MT, int R, int XE>
+// EX (4-bit codes, groups of 128, i.e. one group per k block): the codes' exact values 2 + c/8 are multiplied, not rounded
+// weights, and scale and bias are applied to the sums of a k block in fp32, as in the kernels of e0m4_gemv.hip and
+// e0m4_gemv_mfma.hip.  The sum of a k block's activations that the bias multiplies comes from MFMAs of the same X operands
+// with an all-ones weight operand, once for all row blocks.  28 vector instructions per weight operand and 8 per tile of X,
+// where the dequantisation takes 60 (bfloat16 76).
+template <DqFormat FMT, int MT, int R, int XE, bool EX>
 __global__ __launch_bounds__(kDqThreads, 2) void gemv_dq_kernel(const half_t* __restrict__ X, const uint4* __restrict__ packed,
                                                                 half_t* __restrict__ Y, int m_total, uint32_t N32, uint32_t K32,
                                                                 int rb_base, int rb_rem, int wk_shift, int group_shift)
 {
+    static_assert(!EX || FMT != kDqFormatE8, "exact codes: 4 bits");
     constexpr int NP = FMT == kDqFormatE8 ? 2 : 4;            // pieces of X (and MFMAs) per k block
     static_assert(XE == NP || (XE < NP && MT == 1), "a part of the rows: of a single tile");
     constexpr int BLK = NP * 32;                        // weights of a row per k block
@@ -98,7 +104,7 @@ __global__ __launch_bounds__(kDqThreads, 2) void gemv_dq_kernel(const half_t* __
     const int n_l = lane & 15, g_l = lane >> 4;         // weight row and chunk of this lane; also (row of X, k-group)
     const int wk_n = 1 << wk_shift;                     // wavefronts per group
     const int wr = wave >> wk_shift, wk = wave & (wk_n - 1);
-    const uint32_t fmask = frac_mask_vgpr();
+    const uint32_t fmask = EX && FMT == kDqFormatBf16 ? frac_mask_bf16_vgpr() : frac_mask_vgpr();
     const int64_t rb0 = (int64_t)blockIdx.x * rb_base + min((int)blockIdx.x, rb_rem);
     const int n_rb = rb_base + ((int)blockIdx.x < rb_rem ? 1 : 0);
     const char* wg_base = reinterpret_cast<const char*>(packed) + (size_t)rb0 * rb_stride;
@@ -199,6 +205,30 @@ __global__ __launch_bounds__(kDqThreads, 2) void gemv_dq_kernel(const half_t* __
         return *reinterpret_cast<const half8_t*>(o);
     };
 
+    // word p of the chunk as eight exact code values
+    auto codes = [&](const u32x4& cc, int p) -> half8_t {
+        uint32_t o[4];
+        if (FMT == kDqFormatBf16) {
+            o[0] = ((cc[p] >> 3) & fmask) | kExpBits2;
+            o[1] = ((cc[p] << 1) & fmask) | kExpBits2;
+            o[2] = ((cc[p] >> 7) & fmask) | kExpBits2;
+            o[3] = (__builtin_amdgcn_alignbit(cc[p], cc[p], 11) & fmask) | kExpBits2;
+        } else {
+            o[0] = w1_pair_bits<0>(cc[p], fmask);
+            o[1] = w1_pair_bits<1>(cc[p], fmask);
+            o[2] = w1_pair_bits<2>(cc[p], fmask);
+            o[3] = w1_pair_bits<3>(cc[p], fmask);
+        }
+        return *reinterpret_cast<const half8_t*>(o);
+    };
+    auto mfma = [](const half8_t& a, const half8_t& b, const floatx4& v) -> floatx4 {
+        if constexpr (FMT == kDqFormatBf16)
+            return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), v, 0, 0, 0);
+        else return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, v, 0, 0, 0);
+    };
+    const half_t one = FMT == kDqFormatBf16 ? __builtin_bit_cast(half_t, (uint16_t)0x3F80) : (half_t)1.f;
+    const half8_t ones8 = {one, one, one, one, one, one, one, one};
+
     floatx4 acc[R][MT];
 #pragma unroll
     for (int r = 0; r < R; ++r)
@@ -220,6 +250,36 @@ __global__ __launch_bounds__(kDqThreads, 2) void gemv_dq_kernel(const half_t* __
         load_x(kb + XD * wk_n, xd);
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");     // read back by the wavefront that wrote it
         __builtin_amdgcn_wave_barrier();
+        if constexpr (EX) {
+            half8_t xa[NP][MT];
+            floatx4 sx[MT];
+#pragma unroll
+            for (int i = 0; i < MT; ++i) sx[i] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int p = 0; p < NP; ++p)
+#pragma unroll
+                for (int i = 0; i < MT; ++i) {
+                    xa[p][i] = *reinterpret_cast<const half8_t*>(xl + i * (16 * RB) + x_rd[p]);
+                    sx[i] = mfma(xa[p][i], ones8, sx[i]);
+                }
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                floatx4 a[MT];
+#pragma unroll
+                for (int p = 0; p < NP; ++p) {
+                    const half8_t w = codes(c[u % DW][r], p);
+#pragma unroll
+                    for (int i = 0; i < MT; ++i) a[i] = mfma(xa[p][i], w, p == 0 ? floatx4{0.f, 0.f, 0.f, 0.f} : a[i]);
+                }
+                const uint32_t pw1 = pwd[u % DW][r];
+                const float sc = FMT == kDqFormatBf16 ? __builtin_bit_cast(float, pw1 << 16) : (float)param_scale(pw1);
+                const float bi = FMT == kDqFormatBf16 ? __builtin_bit_cast(float, pw1 & 0xFFFF0000u) : (float)param_bias(pw1);
+#pragma unroll
+                for (int i = 0; i < MT; ++i)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[r][i][e] += sc * (a[i][e] - bi * sx[i][e]);
+            }
+        } else
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
             half8_t xa[MT];
@@ -230,10 +290,7 @@ __global__ __launch_bounds__(kDqThreads, 2) void gemv_dq_kernel(const half_t* __
                 const half8_t w = dequant(c[u % DW][r], pwd[u % DW][r], p);
 #pragma unroll
                 for (int i = 0; i < MT; ++i)
-                    acc[r][i] = FMT == kDqFormatBf16
-                                    ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, xa[i]),
-                                                                              __builtin_bit_cast(bf16x8_t, w), acc[r][i], 0, 0, 0)
-                                    : __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[i], w, acc[r][i], 0, 0, 0);
+                    acc[r][i] = mfma(xa[i], w, acc[r][i]);
             }
             if (MT >= 3) __builtin_amdgcn_sched_barrier(0);         // (or all operands of the block are read first, and spilled)
         }
@@ -278,7 +335,8 @@ __global__ __launch_bounds__(kDqThreads, 2) void gemv_dq_kernel(const half_t* __
 
 // One workgroup per compute unit where the row blocks allow it (its eight wavefronts fill the unit's registers): with more
 // than 256 x 16 of them, as few whole rounds as possible.
-bool make_dq_plan(int64_t M, int64_t N, int64_t K, DqPlan& p)
+// (`exact`: the registers of four tiles of X and their sums leave room for two row blocks per wavefront)
+bool make_dq_plan(int64_t M, int64_t N, int64_t K, DqPlan& p, bool exact = false)
 {
     if (M < 2 || M > kDqMaxParts * kDqMaxM || N <= 0 || K <= 0) return false;
     p.parts = M > kDqMaxM ? kDqMaxParts : 1;
@@ -291,54 +349,59 @@ bool make_dq_plan(int64_t M, int64_t N, int64_t K, DqPlan& p)
     p.rb_base = (int)(nrb / p.grid);
     p.rb_rem = (int)(nrb % p.grid);
     p.wr = 1;
-    while (p.wr * kDqMaxR < most) p.wr *= 2;
+    const int max_r = exact && (M + p.parts - 1) / p.parts > 48 ? 2 : kDqMaxR;
+    while (p.wr * max_r < most) p.wr *= 2;
     p.r = (int)((most + p.wr - 1) / p.wr);
     return true;
 }
 
-template <DqFormat FMT, int MT, int R, int XE>
+template <DqFormat FMT, int MT, int R, int XE, bool EX>
 int launch_dq(const DqPlan& p, const void* X, int64_t M, const void* packed, int64_t N, int64_t K,
               int group, void* Y, hipStream_t stream)
 {
     constexpr int lds = std::max(kDqWaves * R * MT * 64 * 16, kDqWaves * MT * 16 * (FMT == kDqFormatE8 ? 128 : 256));
     static std::atomic<uint64_t> lds_allowed{0};
-    const int arc = allow_dynamic_lds(reinterpret_cast<const void*>(&gemv_dq_kernel<FMT, MT, R, XE>), lds, lds_allowed);
+    const int arc = allow_dynamic_lds(reinterpret_cast<const void*>(&gemv_dq_kernel<FMT, MT, R, XE, EX>), lds, lds_allowed);
     if (arc != E0M4_OK) return arc;
     int wk_shift = 0;                                   // log2 of the wavefronts in a group
     while ((p.wr << (wk_shift + 1)) <= kDqWaves) ++wk_shift;
     const int group_shift = FMT == kDqFormatE8 || group == 128 ? 7 : group == 64 ? 6 : 5;
-    hipLaunchKernelGGL((gemv_dq_kernel<FMT, MT, R, XE>), dim3((unsigned)p.grid, (unsigned)p.parts), dim3(kDqThreads), lds, stream,
+    hipLaunchKernelGGL((gemv_dq_kernel<FMT, MT, R, XE, EX>), dim3((unsigned)p.grid, (unsigned)p.parts), dim3(kDqThreads), lds, stream,
                        static_cast<const half_t*>(X), static_cast<const uint4*>(packed), static_cast<half_t*>(Y), (int)M,
                        (uint32_t)N, (uint32_t)K, p.rb_base, p.rb_rem, wk_shift, group_shift);
     return check_launch();
 }
 
-template <DqFormat FMT, int MT, int XE = FMT == kDqFormatE8 ? 2 : 4>
+template <DqFormat FMT, int MT, int XE, bool EX>
 int launch_dq_r(const DqPlan& p, const void* X, int64_t M, const void* packed, int64_t N, int64_t K,
                 int group, void* Y, hipStream_t stream)
 {
     switch (p.r) {
-        case 1: return launch_dq<FMT, MT, 1, XE>(p, X, M, packed, N, K, group, Y, stream);
-        case 2: return launch_dq<FMT, MT, 2, XE>(p, X, M, packed, N, K, group, Y, stream);
-        case 3: return launch_dq<FMT, MT, 3, XE>(p, X, M, packed, N, K, group, Y, stream);
-        case 4: return launch_dq<FMT, MT, 4, XE>(p, X, M, packed, N, K, group, Y, stream);
-        default: return E0M4_ERR_SHAPE;
+        case 1: return launch_dq<FMT, MT, 1, XE, EX>(p, X, M, packed, N, K, group, Y, stream);
+        case 2: return launch_dq<FMT, MT, 2, XE, EX>(p, X, M, packed, N, K, group, Y, stream);
+        default: break;
     }
+    if constexpr (!EX || MT < 4) {
+        if (p.r == 3) return launch_dq<FMT, MT, 3, XE, EX>(p, X, M, packed, N, K, group, Y, stream);
+        if (p.r == 4) return launch_dq<FMT, MT, 4, XE, EX>(p, X, M, packed, N, K, group, Y, stream);
+    }
+    return E0M4_ERR_SHAPE;
 }
 
-template <DqFormat FMT>
+template <DqFormat FMT, bool EX = false>
 int launch_dq_m(const DqPlan& p, const void* X, int64_t M, const void* packed, int64_t N, int64_t K,
                 int group, void* Y, hipStream_t stream)
 {
-    if constexpr (FMT == kDqFormatFp16) {               // (the other formats come here with nine rows or more)
-        if (M <= 4) return launch_dq_r<FMT, 1, 1>(p, X, M, packed, N, K, group, Y, stream);
-        if (M <= 8) return launch_dq_r<FMT, 1, 2>(p, X, M, packed, N, K, group, Y, stream);
+    constexpr int XE = FMT == kDqFormatE8 ? 2 : 4;
+    if constexpr (FMT == kDqFormatFp16 || EX) {         // (the other formats come here with nine rows or more)
+        if (M <= 4) return launch_dq_r<FMT, 1, 1, EX>(p, X, M, packed, N, K, group, Y, stream);
+        if (M <= 8) return launch_dq_r<FMT, 1, 2, EX>(p, X, M, packed, N, K, group, Y, stream);
     }
     switch (((M + p.parts - 1) / p.parts + 15) / 16) {
-        case 1: return launch_dq_r<FMT, 1>(p, X, M, packed, N, K, group, Y, stream);
-        case 2: return launch_dq_r<FMT, 2>(p, X, M, packed, N, K, group, Y, stream);
-        case 3: return launch_dq_r<FMT, 3>(p, X, M, packed, N, K, group, Y, stream);
-        case 4: return launch_dq_r<FMT, 4>(p, X, M, packed, N, K, group, Y, stream);
+        case 1: return launch_dq_r<FMT, 1, XE, EX>(p, X, M, packed, N, K, group, Y, stream);
+        case 2: return launch_dq_r<FMT, 2, XE, EX>(p, X, M, packed, N, K, group, Y, stream);
+        case 3: return launch_dq_r<FMT, 3, XE, EX>(p, X, M, packed, N, K, group, Y, stream);
+        case 4: return launch_dq_r<FMT, 4, XE, EX>(p, X, M, packed, N, K, group, Y, stream);
         default: return E0M4_ERR_SHAPE;
     }
 }
@@ -375,6 +438,37 @@ bool gemv_dq_pays(int64_t M, int64_t N, int64_t K, int group, DqFormat format)
     if (M > kDqMaxM) return false;
     if (M > 16) return NK <= (format == kDqFormatE8 ? 1e8 : 7e7) && (M <= 48 || (K >= 256 && K <= 9216));
     return format == kDqFormatFp16 && group != 128;
+}
+
+bool gemv_exact_supported(int64_t M, int64_t N, int64_t K, int group)
+{
+    DqPlan p;
+    return group == 128 && make_dq_plan(M, N, K, p, true);
+}
+
+// Where exact codes are faster than the kernels of unrounded weights that have the call otherwise (us, cold weights, the other and
+// this one).  Calls of kernels that round the weights are not taken, though some would gain (27392 x 4096 at M = 24 27.6 and 22.2):
+// against the dequantised weights they would be further off.
+//   bfloat16, 3 to 8 rows: the staging kernel (4608 x 4096 at M = 5 6.6 and 6.2, 4096 x 13696 at M = 8 13.9 and 10.8), but not where
+//     row blocks do not fill the wavefronts' (27392 x 4096, seven of eight: 15.1 and 16.0).
+//   fp16, 17 to 64 rows: the staging kernel in chunks (4608 x 4096 at M = 24 12.2 and 9.1, at M = 64 17.8 and 14.1, 4096 x 4096 at M =
+//     45 15.4 and 11.8).
+// Plain calls only.  With fused operators (one 6B block's residual call at M = 45 18.9 -> 14.3 us) a stack of blocks would sum in
+// another order and differ by up to 2.4 % of the largest value after four blocks.
+bool gemv_exact_pays(int64_t M, int64_t N, int64_t K, DqFormat format, bool in_chunks)
+{
+    DqPlan p;
+    if (M < 3 || !make_dq_plan(M, N, K, p, true)) return false;
+    if (format == kDqFormatBf16) return M <= kGemvMaxM && p.wr * p.r == p.rb_base + (p.rb_rem > 0 ? 1 : 0);
+    return in_chunks && M <= kDqMaxM;
+}
+
+int launch_gemv_exact(const void* X, int64_t M, const void* packed, int64_t N, int64_t K, DqFormat format, void* Y, hipStream_t stream)
+{
+    DqPlan p;
+    if (format == kDqFormatE8 || N <= 0 || !make_dq_plan(M, N, K, p, true)) return E0M4_ERR_SHAPE;
+    if (format == kDqFormatBf16) return launch_dq_m<kDqFormatBf16, true>(p, X, M, packed, N, K, 128, Y, stream);
+    return launch_dq_m<kDqFormatFp16, true>(p, X, M, packed, N, K, 128, Y, stream);
 }
 
 int launch_gemv_dq(const void* X, int64_t M, const void* packed, int64_t N, int64_t K, int group, DqFormat format, void* Y,

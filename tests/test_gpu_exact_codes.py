@@ -1,0 +1,62 @@
+"""The small-batch kernel on exact codes (groups of 128, 2 to 128 rows) against the oracle: last tiles of rows and columns, fewer k
+blocks than wavefronts, remainders of the unrolled loop, one to sixteen row blocks per workgroup, and calls that reach it by
+default."""
+import numpy as np
+import pytest
+
+import synth_inputs
+from test_gpu_bf16_e0m3 import assert_bf16_quantize_exact, bf_bits, bf_dev, check_bf16_matmul
+from test_gpu_parity import assert_quantize_exact, check_matmul, e0m4, to_dev, torch  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture
+def forced(e0m4):
+    e0m4.e0m4_set_knob("gemv_mfma", 7)
+    yield
+    e0m4.e0m4_set_knob("gemv_mfma", 0)
+    e0m4.e0m4_set_knob("gemv_workgroups", 0)
+
+
+# N, K, workgroups aimed at: 1, 2, 3 and 4 row blocks per wavefront, one, two and four groups of wavefronts
+@pytest.mark.parametrize("N,K,workgroups", [(17, 128, 0), (203, 1152, 0), (333, 2176, 12), (520, 1664, 4), (260, 640, 1), (1000, 4224, 9)])
+@pytest.mark.parametrize("M", [2, 4, 5, 8, 9, 16, 17, 33, 48, 49, 64, 65, 128])
+@pytest.mark.parametrize("fmt", ["e0m4", "bf16"])
+def test_plain(e0m4, oracle, forced, fmt, M, N, K, workgroups):
+    e0m4.e0m4_set_knob("gemv_workgroups", workgroups)
+    if fmt == "bf16":
+        codes, What, (oc, os_, ob) = assert_bf16_quantize_exact(e0m4, oracle, synth_inputs.weights_bf16(N, K, seed=7000 + N), 128)
+        X = synth_inputs.activations_bf16(M, K, seed=7100 + M)
+        X[0] = 0
+        X[0, 77] = 0x3FC0                               # one row with a single 1.5: 1.5 scale (w1 - bias), rounded once
+        Y = e0m4.e0m4_bf16_matmul(bf_dev(X), codes, N, K, 128)
+        Yref, absdot = oracle.bf16_matmul(X, What)
+        check_bf16_matmul(oracle, Y, Yref, absdot, "bf16 M=%d" % M)
+        exact = 1.5 * oracle.bf16_to_float64(os_[:, 0]) * (2 + oc[:, 77] / 8.0 - oracle.bf16_to_float64(ob[:, 0]))
+        assert np.array_equal(bf_bits(Y)[0] & 0x7FFF, synth_inputs.to_bf16_bits(exact.astype(np.float32)) & 0x7FFF)
+        return
+    (codes, _, _), What = assert_quantize_exact(e0m4, oracle, synth_inputs.weights(N, K, seed=7000 + N), 128)
+    X = synth_inputs.activations(M, K, seed=7100 + M, outlier_frac=0.01)
+    Y, Y2 = (e0m4.e0m4_matmul(to_dev(X), codes, None, None, N, K, 128) for _ in range(2))
+    Yref, absdot = oracle.matmul(X, What)
+    check_matmul(Y, Yref, absdot, "M=%d" % M)
+    assert torch.equal(Y, Y2)
+
+
+@pytest.mark.parametrize("N,K", [(448, 1664), (1088, 4096), (27392, 256)])
+@pytest.mark.parametrize("M", [3, 17, 24, 33, 48, 49, 64])
+def test_default_choice(e0m4, oracle, M, N, K):
+    # the fused entry point without operators gives the same bits (where the plain call does not multiply rounded weights, as with
+    # 27392 x 256), and with a residual it has the workspace that it needs
+    (codes, _, _), What = assert_quantize_exact(e0m4, oracle, synth_inputs.weights(N, K, seed=7400), 128)
+    X = synth_inputs.activations(M, K, seed=7500 + M)
+    Y = e0m4.e0m4_matmul(to_dev(X), codes, None, None, N, K, 128)
+    Y2 = e0m4.e0m4_matmul_fused(to_dev(X), codes, N, K, 128)
+    assert N > 2000 or torch.equal(Y, Y2)
+    Yref, absdot = oracle.matmul(X, What)
+    check_matmul(Y, Yref, absdot, "M=%d" % M)
+    R = to_dev(synth_inputs.activations(M, N, seed=7600 + M))
+    YR = e0m4.e0m4_matmul_fused(to_dev(X), codes, N, K, 128, residual=R).float().cpu().numpy()
+    want = Yref.astype(np.float64) + R.cpu().numpy()
+    assert (np.abs(YR - want) <= 1e-2 * np.maximum(1.0, absdot) + 2.0 ** -10 * np.abs(want)).all()
