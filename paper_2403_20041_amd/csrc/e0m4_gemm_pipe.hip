@@ -101,11 +101,13 @@ struct SkArgs {
 // would compute many rows that do not exist or leave compute units without a tile; 128 x 128 with 2 x 2 wavefronts
 // (forced launches only).
 //
-// SHORT: M leaves 96 rows or fewer in the last row tile of 128.  Those tiles are computed in the 32-row blocks that exist (two
-// at least: below that the dequantisation is all there is to do) and are numbered last on every XCD, so that they fill the gaps
-// at the end: gated 317 x 32768 x 2048 in groups of 32 (256 whole tiles and 128 of 61 rows) 57.3 -> 49 us, two such blocks at M =
-// 317 277 -> 262 us per pass.  In instances of its own: the three forms of the K loop cost the others 2 % (1024 rows, two 6B
-// blocks 899 -> 916 us).
+// SHORT: M leaves 64 rows or fewer in the last row tile of 128.  Those tiles are computed in two of their four 32-row blocks
+// (one block would take as long: below that the dequantisation is all there is to do) and are numbered last on every XCD, so
+// that they fill the gaps at the end: gated 317 x 32768 x 2048 in groups of 32 (256 whole tiles and 128 of 61 rows) 57.3 -> 49
+// us.  In instances of its own: another form of the K loop beside it costs the usual one 2 % (1024 rows, two 6B blocks 899 ->
+// 916 us), which is also why it takes six row tiles at most and as many tiles as compute units, or nobody waits for the whole
+// ones: gated 27392 x 4096 at M = 300 98.7 -> 85.4 us (bfloat16 95.1 -> 84.1), 15360 x 5120 at M = 576 116 -> 102, 32768 x 2048 at
+// M = 140 37.7 -> 35.4; but 7424 x 2688 at M = 700 (174 tiles) 38.0 and 40.3.
 //
 // E8 selects the 8-bit format E0M8 (e0m8_pack.hip; G is then 128, the group of its 4-bit slots): a K slice
 // of 64 is one block, a lane reads two 16-byte chunks of 16 weights per slice, and MFMA number s takes
@@ -507,9 +509,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KS, 2) void gemm_pipe_kernel(const
     };
     if constexpr (SHORT) {
         static_assert(PA * RP == TM * 32, "a loader pass is whole row blocks");
-        const int blocks = (int)((min((int64_t)BM, M - m0) + 31) / 32);
-        if (blocks == TM) k_loop(std::integral_constant<int, TM>{});
-        else if (blocks == 3) k_loop(std::integral_constant<int, 3>{});
+        if (M - m0 > 64) k_loop(std::integral_constant<int, TM>{});
         else k_loop(std::integral_constant<int, 2>{});
     } else {
         k_loop(std::integral_constant<int, TM>{});
@@ -1044,6 +1044,8 @@ int64_t pipe_tiles(const PipeTile& t, int64_t M, int64_t N, bool swiglu)
     return ((M + t.bm - 1) / t.bm) * n_tiles;
 }
 
+constexpr int64_t kShortMaxTiles = 6;                   // row tiles of a launch with a short last one (see the kernel)
+
 // (`whole_tiles`: neither a K split nor the even scheduling, hence no workspace)
 template <int G, int WGM, int WGN, bool FUSED, int BM, int BN, bool E8 = false, bool BF = false, int KS = 1>
 int launch_pipe(const half_t* x, int64_t M, const uint4* c, int64_t N, int64_t K, half_t* y, void* workspace,
@@ -1080,7 +1082,7 @@ int launch_pipe(const half_t* x, int64_t M, const uint4* c, int64_t N, int64_t K
     }
     SkArgs sk{0, 0, 0, 0, nullptr, nullptr};
     unsigned grid = (unsigned)(per_xcd * kNumXcd);
-    const bool last_short = BM == 128 && BN == 256 && splits == 1 && m_tiles > 1 && M % BM != 0 && M % BM <= BM - 32;
+    const bool last_short = BM == 128 && BN == 256 && splits == 1 && m_tiles > 1 && m_tiles <= kShortMaxTiles && tiles >= kComputeUnits && M % BM != 0 && M % BM <= 64;
     if (last_short) grid = (unsigned)((((m_tiles - 1) * n_tiles + kNumXcd - 1) / kNumXcd + (n_tiles + kNumXcd - 1) / kNumXcd) * kNumXcd);
     if (skp.on) {
         if (workspace == nullptr || workspace_bytes < skp.workspace_bytes) return E0M4_ERR_WORKSPACE;
