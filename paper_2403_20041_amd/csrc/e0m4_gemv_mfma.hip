@@ -107,10 +107,11 @@ __device__ inline int x_unit_off(int q, int w, int hl) { return ((q * 4 + (w >> 
 // PHASED: M rows of X do not fit the LDS.  K is walked in phases of kb_phase blocks: every phase visits all row blocks of
 // the workgroup and adds to the wavefront sums, which stay in LDS (`late`) until the last phase; X is staged for ph_stage
 // phases at a time.  The weights are still read exactly once.
+// XF: the first weights are requested behind the first X (see x_first).
 // KEEP: with an rms-norm, X stays in registers from the pass over its squares (keeps_x below).
 // BF: 4-bit codes on bfloat16 (no fused operators).  Brought to fraction bits 6..3 by one shift or rotation per pair, all eight
 // codes of a word read 2 + c/8, so one MFMA takes one word and X as it lies in memory, and a block needs the plain sum of X only.
-template <int W, bool FUSED, bool XREG, bool E8 = false, bool PHASED = false, int GS = 1, bool KEEP = false, bool BF = false>
+template <int W, bool FUSED, bool XREG, bool E8 = false, bool PHASED = false, int GS = 1, bool KEEP = false, bool BF = false, bool XF = false>
 __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restrict__ X,
                                                            const uint4* __restrict__ packed, half_t* __restrict__ Y,
                                                            int M, uint32_t N32, uint32_t K32, int step_slots_arg,
@@ -133,6 +134,7 @@ __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restr
     }
     static_assert(!(PHASED && XREG), "a wavefront meets other k blocks in every phase");
     static_assert(!KEEP || (FUSED && W <= 8 && !PHASED && GS == 1 && !(XREG && E8)), "instances that keep X");
+    static_assert(!XF || !PHASED, "X first: K in one piece");
     static_assert(!BF || (!FUSED && !E8), "bfloat16: 4-bit codes, plain matmuls");
     static_assert(GS == 1 || ((GS == 2 || GS == 4) && !E8 && !XREG), "several groups per block: 4-bit codes, X from LDS");
     constexpr int kThreads = W * 64;
@@ -234,9 +236,12 @@ __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restr
     nslot = slot;
     nitem = si;
     advance(nph, nslot, nitem);
-    fetch_params(0, slot, si);
+    auto first_item = [&]() {
+        fetch_params(0, slot, si);
 #pragma unroll
-    for (int j = 0; j < kSuper; ++j) fetch_code(j, 0, slot, si);
+        for (int j = 0; j < kSuper; ++j) fetch_code(j, 0, slot, si);
+    };
+    if (!XF) first_item();
 
     // ---- stage X in pieces of 8 elements (k = 8*pc .. 8*pc+7 of row m); no piece index needs a division
     const int pieces = nkb * (XBB / 16);
@@ -262,6 +267,7 @@ __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restr
             if (m < M && in_k) keep[m] = *reinterpret_cast<const half8_t*>(X + (int64_t)m * K + (int64_t)pc_own * 8);
         }
         if (in_k) g_own = *reinterpret_cast<const half8_t*>(fu.gamma + (int64_t)pc_own * 8);
+        if (XF) first_item();
 #pragma unroll
         for (int m0 = 0; m0 < kMaxM; m0 += 8) {         // eight rows' reductions at a time (their latencies overlap)
             if (m0 >= M) break;
@@ -305,6 +311,7 @@ __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restr
             }
             if (in_k) g_keep[c0] = *reinterpret_cast<const half8_t*>(fu.gamma + k);
         }
+        if (XF) first_item();
 #pragma unroll
         for (int m0 = 0; m0 < KM; m0 += 8) {
             if (m0 >= M) break;
@@ -343,11 +350,11 @@ __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restr
         // kNormRows rows at a time: their loads are in flight together and their wavefront reductions (chains of
         // cross-lane steps, each with the latency of an LDS access) overlap instead of running row after row
         constexpr int kNormRows = 8;
-        for (int m0 = 0; m0 < M; m0 += kNormRows) {
+        auto square_rows = [&](int m0, auto first_c) {
             float sq[kNormRows];
 #pragma unroll
             for (int r = 0; r < kNormRows; ++r) sq[r] = 0.f;
-            for (int c0 = 0; c0 < cpr; ++c0) {
+            auto chunk = [&](int c0, auto first_chunk_c) {
                 const int pc = c0 * kThreads + t;
                 const int64_t k = (int64_t)pc * 8;
                 half8_t vb[kNormRows];
@@ -356,6 +363,7 @@ __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restr
                     vb[r] = zero8;
                     if (m0 + r < M && pc < pieces && k < K) vb[r] = *reinterpret_cast<const half8_t*>(X + (int64_t)(m0 + r) * K + k);
                 }
+                if constexpr (decltype(first_chunk_c)::value) first_item();
 #pragma unroll
                 for (int r = 0; r < kNormRows; ++r) {
                     const half8_t v = vb[r];
@@ -365,7 +373,9 @@ __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restr
                     d = __builtin_amdgcn_fdot2(x2, x2, d, false);
                     sq[r] = __builtin_amdgcn_fdot2(x3, x3, d, false);
                 }
-            }
+            };
+            if (XF) chunk(0, first_c);
+            for (int c0 = XF ? 1 : 0; c0 < cpr; ++c0) chunk(c0, std::false_type{});
 #pragma unroll
             for (int d = 1; d < 64; d <<= 1)
 #pragma unroll
@@ -375,7 +385,9 @@ __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restr
                 for (int r = 0; r < kNormRows; ++r)
                     if (m0 + r < M) norm_part[wave * kMaxM + m0 + r] = sq[r];
             }
-        }
+        };
+        if (XF) square_rows(0, std::true_type{});
+        for (int m0 = XF ? kNormRows : 0; m0 < M; m0 += kNormRows) square_rows(m0, std::false_type{});
     }
     if (normed) {                                       // the wavefronts' sums, in wavefront order, then the row scales
         __syncthreads();
@@ -449,7 +461,7 @@ __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restr
                 __syncthreads();
             }
         } else if (own_x) {
-            for (int i0 = 0; i0 < M * kItemPieces; i0 += kStageBatch * 64) {
+            auto own_batch = [&](int i0, auto first_c) {
                 half8_t vb[kStageBatch];
 #pragma unroll
                 for (int u = 0; u < kStageBatch; ++u) {
@@ -458,13 +470,16 @@ __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restr
                     vb[u] = zero8;
                     if (m < M && pc < pieces && (int64_t)pc * 8 < K) vb[u] = *reinterpret_cast<const half8_t*>(X + (int64_t)m * K + (int64_t)pc * 8);
                 }
+                if constexpr (decltype(first_c)::value) first_item();
 #pragma unroll
                 for (int u = 0; u < kStageBatch; ++u) {
                     const int idx = i0 + u * 64 + lane;
                     const int m = idx / kItemPieces, pc = si * kItemPieces + idx % kItemPieces;
                     store_piece(m, pc, m < M && pc < pieces, vb[u], zero8);     // (a last work item may reach beyond the row's blocks)
                 }
-            }
+            };
+            if (XF) own_batch(0, std::true_type{});
+            for (int i0 = XF ? kStageBatch * 64 : 0; i0 < M * kItemPieces; i0 += kStageBatch * 64) own_batch(i0, std::false_type{});
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");     // read back by the wavefront that wrote it
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -475,7 +490,7 @@ __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restr
             const int ph_pieces = PHASED ? min(nkb_lds, nkb - kb_lo) * (XBB / 16) : pieces;
             const int pc_lo = PHASED ? kb_lo * (XBB / 16) : 0;
             const uint32_t pieces_magic = PHASED && kb_lo + nkb_lds >= nkb ? pieces_magic_last : pieces_magic_arg;
-            for (int base = 0; base < M * ph_pieces; base += kStageBatch * kThreads) {
+            auto batch = [&](int base, auto first_c) {
                 half8_t vb[kStageBatch], gb[kStageBatch];
 #pragma unroll
                 for (int u = 0; u < kStageBatch; ++u) {
@@ -489,13 +504,19 @@ __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restr
                         if (normed) gb[u] = *reinterpret_cast<const half8_t*>(fu.gamma + k);
                     }
                 }
+                if constexpr (decltype(first_c)::value) first_item();
 #pragma unroll
                 for (int u = 0; u < kStageBatch; ++u) {
                     const int idx = base + u * kThreads + t;
                     const int m = (int)__umulhi((uint32_t)idx, pieces_magic), pc = idx - m * ph_pieces;
                     store_piece(m, pc, idx < M * ph_pieces, vb[u], gb[u]);     // (pc: inside the staged part of the row)
                 }
+            };
+            if (XF) {
+                if (normed) batch(0, std::false_type{});
+                else batch(0, std::true_type{});
             }
+            for (int base = XF ? kStageBatch * kThreads : 0; base < M * ph_pieces; base += kStageBatch * kThreads) batch(base, std::false_type{});
             __syncthreads();
         }
 
@@ -814,18 +835,36 @@ bool make_mfma_plan(int64_t M, int64_t N, int64_t K, MfmaPlan& p, int unit = 1, 
     return true;
 }
 
-template <int W, bool FUSED, bool XREG, bool E8, bool PHASED, int GS, bool KEEP, bool BF = false>
+// Whether a wavefront requests X before its first weights.  A wait for one request is a wait for all before it, and X, which
+// stands in a cache, is what every wavefront needs first.  With rms-norm, weights first and X first (us): 15360 x 5120 at M = 4
+// 15.0 -> 13.7, gated 32768 x 2048 at M = 16 15.4 -> 14.7, groups of 64 4096 x 4096 at M = 5 10.1 -> 9.1, 8-bit codes 9.7 -> 9.0 at
+// M = 4; with a residual 8-bit 4096 x 4096 7.7 -> 7.3; bfloat16 4096 x 4096 at M = 8 6.7 -> 6.2.
+// Not with K in phases, where X is many loads per thread (4096 x 13696 with norm at M = 16 32.2 and 35.2).  With X in registers and 4-bit
+// codes not where wavefronts stage their own X of more than eight rows (4608 x 4096 at M = 16 8.3 and 8.6), for the same reason, nor
+// where there are fewer work items than wavefronts (2560 x 2048 at M = 2 with norm 6.8 and 7.0).
+bool x_first(const MfmaPlan& p, int64_t M, int64_t K, bool normed, bool gated)
+{
+    const int64_t nsi = (k_blocks(K) + kSuper - 1) / kSuper;
+    if (p.rb_base * (gated ? 2 : 1) * nsi < p.waves) return !normed && M > 4;
+    return normed || p.step_slots != 1 || M <= 8;
+}
+
+template <int W, bool FUSED, bool XREG, bool E8, bool PHASED, int GS, bool KEEP, bool BF = false, bool XF = !PHASED && !(XREG && !E8)>
 int launch_mfma_keep(const MfmaPlan& p, const void* X, int64_t M, const void* packed, int64_t N, int64_t K, void* Y,
                   hipStream_t stream, const GemvFusion& fu)
 {
+    if constexpr (XREG && !E8 && !XF) {
+        if (x_first(p, M, K, fu.gamma != nullptr, fu.swiglu != 0))
+            return launch_mfma_keep<W, FUSED, XREG, E8, PHASED, GS, KEEP, BF, true>(p, X, M, packed, N, K, Y, stream, fu);
+    }
     if (PHASED != (p.kb_phase > 0) || (PHASED && !p.late) || p.lds_bytes > (size_t)kLdsLimitBytes) return E0M4_ERR_SHAPE;
     static std::atomic<uint64_t> lds_allowed{0};
-    const int arc = allow_dynamic_lds(reinterpret_cast<const void*>(&gemv_mfma_kernel<W, FUSED, XREG, E8, PHASED, GS, KEEP, BF>),
+    const int arc = allow_dynamic_lds(reinterpret_cast<const void*>(&gemv_mfma_kernel<W, FUSED, XREG, E8, PHASED, GS, KEEP, BF, XF>),
                                       kLdsLimitBytes, lds_allowed);
     if (arc != E0M4_OK) return arc;
     // (M: rows per chunk; fu.m_total: all rows, when there are several chunks)
     const unsigned chunks = fu.m_total > 0 ? (unsigned)((fu.m_total + M - 1) / M) : 1u;
-    hipLaunchKernelGGL((gemv_mfma_kernel<W, FUSED, XREG, E8, PHASED, GS, KEEP, BF>), dim3((unsigned)p.grid, chunks), dim3(W * 64),
+    hipLaunchKernelGGL((gemv_mfma_kernel<W, FUSED, XREG, E8, PHASED, GS, KEEP, BF, XF>), dim3((unsigned)p.grid, chunks), dim3(W * 64),
                        p.lds_bytes, stream, static_cast<const half_t*>(X), static_cast<const uint4*>(packed),
                        static_cast<half_t*>(Y), (int)M, (uint32_t)N, (uint32_t)K, p.step_slots, p.step_item, p.rb_base,
                        p.rb_rem, p.late, p.pieces_magic, p.kb_phase, p.ph_stage, p.pieces_magic_last, fu);
