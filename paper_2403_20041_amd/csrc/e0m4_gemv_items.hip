@@ -15,7 +15,8 @@
 // What bounds it: X from L2 (every workgroup needs all 2 M K bytes: at M = 16 and K = 16384 512 KiB for 136 KiB of weights).
 // With a residual, X staged and here (us): 4096 x 13696 at M = 16 20.6 -> 11.8, at M = 6 14.0 -> 10.4; 2048 x 16384 20.1 -> 12.4
 // and 13.4 -> 10.5; two row blocks: 5120 x 13696 27.0 -> 18.9, 5120 x 5120 14.0 -> 9.2; groups of 64 at M = 8: 5120 x 13696
-// 21.5 -> 16.1, 2560 x 8192 10.5 -> 7.8; groups of 32 at M = 4: 5120 x 5120 10.9 -> 8.5.
+// 21.5 -> 16.1, 2560 x 8192 10.5 -> 7.8; groups of 32 at M = 4: 5120 x 5120 10.9 -> 8.5. 8-bit codes: 4096 x 4096 at M =
+// 16 9.6 -> 7.0, at M = 8 8.1 -> 6.8, 4096 x 13696 at M = 16 23.4 -> 19.7.
 #include "e0m4_device.h"
 #include "e0m4_host.h"
 
@@ -32,22 +33,26 @@ constexpr int kItemThreads = kItemWaves * 64;
 constexpr int kItemBlocks = 4;                  // k blocks of 128 per work item
 constexpr int kMaxSums = 96;                    // of units and row blocks: 1 KiB each, beside the wavefronts' X (4 KiB each)
 constexpr int kZeroBytes = 64;                  // several groups per block: the zeros of a k-group that is not the row's
-constexpr int kItemXBytes = 16 * kBlockK * 2;   // sixteen rows of a k block
+constexpr int kItemXBytes = 16 * kBlockK * 2;   // sixteen rows of a k block (8-bit codes: half of that)
 
 // XE: loads of X per k block, four rows each (calls of up to 4 and 8 rows make one and two; the other rows of the tile stay
-// what LDS held, and so do their sums, which nobody stores).  R: row blocks per workgroup.  GS: groups per k block; a row of X
-// is then GS rows of the MFMA, with zeros for the k-groups of the other groups.
-template <int XE, int R, int GS>
+// what LDS held, and so do their sums, which nobody stores; 8-bit codes: eight rows a load).  R: row blocks per workgroup.  GS: groups per k block; a row of X
+// is then GS rows of the MFMA, with zeros for the k-groups of the other groups.  E8: 8-bit codes, k blocks of 64 weights, a single
+// kind of code slot.
+template <int XE, int R, int GS, bool E8>
 __global__ __launch_bounds__(kItemThreads, 2) void gemv_items_kernel(const half_t* __restrict__ X, const uint4* __restrict__ packed,
                                                                      half_t* __restrict__ Y, const half_t* __restrict__ residual,
                                                                      int M, uint32_t N32, uint32_t K32, int rb_base, int rb_rem,
                                                                      int order_waves, int items_ph)
 {
+    static_assert(!E8 || GS == 1, "8-bit codes: a parameter word per block");
     constexpr int SLOT = 16 / GS;
+    constexpr int BLK = E8 ? kBlockK / 2 : kBlockK, ROWB = BLK * 2;     // weights of a row per k block, bytes of X
+    constexpr int PPR = ROWB / 16, RPI = 64 / PPR;                      // 16-byte pieces per row, rows per load
     constexpr uint32_t kFirstX = GS > 1 ? kZeroBytes : 0;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int64_t N = N32;
-    const int nkb = (int)(K32 / kBlockK), items = (nkb + kItemBlocks - 1) / kItemBlocks;
+    const int nkb = (int)(K32 / BLK), items = (nkb + kItemBlocks - 1) / kItemBlocks;
     const int n_ph = (items + items_ph - 1) / items_ph, items_end = items - (n_ph - 1) * items_ph;
     const int units_ph = min(order_waves, items_ph);
     const int t = threadIdx.x;
@@ -66,15 +71,16 @@ __global__ __launch_bounds__(kItemThreads, 2) void gemv_items_kernel(const half_
     // X: load number e brings rows 4 e .. 4 e + 3 of the k block, 16 bytes per lane.  A piece of eight activations (of one code
     // word) is two halves, those of the pairs that read 2 + c/8 and those that read 2 + c/128; unit u = 4 q + 2 (w / 2) + half
     // of a row lies at 16 (u ^ row): the sixteen rows of an operand read fall into sixteen different bank groups.
-    const int x_a = lane >> 4, x_q = (lane >> 2) & 3, x_w = lane & 3;
+    // (8-bit codes: a piece is a unit, at 16 (u ^ row / 2))
+    const int x_a = lane / PPR, x_j = lane % PPR, x_q = (lane >> 2) & 3, x_w = lane & 3;
     uint32_t x_voff[XE], x_wr[XE][2], x_rd[2][2];
 #pragma unroll
     for (int e = 0; e < XE; ++e) {
-        const int row = 4 * e + x_a;
-        x_voff[e] = ((uint32_t)min(row, M - 1) * K32 + (uint32_t)((lane & 15) * 8)) * 2;
+        const int row = RPI * e + x_a;
+        x_voff[e] = ((uint32_t)min(row, M - 1) * K32 + (uint32_t)(x_j * 8)) * 2;
 #pragma unroll
         for (int hl = 0; hl < 2; ++hl)
-            x_wr[e][hl] = (uint32_t)(row * kBlockK * 2 + (((x_q * 4 + (x_w >> 1) * 2 + hl) ^ row) << 4) + ((x_w & 1) << 3));
+            x_wr[e][hl] = E8 ? (uint32_t)(row * ROWB + ((x_j ^ ((row >> 1) & 7)) << 4)) : (uint32_t)(row * ROWB + (((x_q * 4 + (x_w >> 1) * 2 + hl) ^ row) << 4) + ((x_w & 1) << 3));
     }
 #pragma unroll
     for (int wp = 0; wp < 2; ++wp)
@@ -82,7 +88,8 @@ __global__ __launch_bounds__(kItemThreads, 2) void gemv_items_kernel(const half_
         for (int hl = 0; hl < 2; ++hl) {
             const int row = n_l % SLOT;
             const bool own = GS == 1 || n_l / SLOT == g_l * GS / 4;
-            x_rd[wp][hl] = own ? kFirstX + (uint32_t)(wave * kItemXBytes + row * kBlockK * 2 + (((g_l * 4 + wp * 2 + hl) ^ row) << 4)) : 0u;
+            if (E8) x_rd[wp][hl] = (uint32_t)(wave * kItemXBytes + row * ROWB + (((g_l * 2 + wp) ^ ((row >> 1) & 7)) << 4));
+            else x_rd[wp][hl] = own ? kFirstX + (uint32_t)(wave * kItemXBytes + row * ROWB + (((g_l * 4 + wp * 2 + hl) ^ row) << 4)) : 0u;
         }
     if (GS > 1) {                                       // (every wavefront before its own reads, with the same zeros)
         if (lane < kZeroBytes / 4) reinterpret_cast<uint32_t*>(smem)[lane] = 0;
@@ -110,7 +117,7 @@ __global__ __launch_bounds__(kItemThreads, 2) void gemv_items_kernel(const half_
     auto load_x = [&](int kb, int d) {
         const __amdgpu_buffer_rsrc_t rsrc = rsrc_if(X, kb < nkb);
 #pragma unroll
-        for (int e = 0; e < XE; ++e) xr[d][e] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)x_voff[e], kb * (kBlockK * 2), 0);
+        for (int e = 0; e < XE; ++e) xr[d][e] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)x_voff[e], kb * ROWB, 0);
     };
     // Units in the order u = p * units_ph + r, dealt round the wavefronts; where that gives a wavefront the same units of every
     // phase, `turn` on from phase to phase, the number of units with one item more than the others.  Item i of phase p is item p * items_ph + i of all.  Past the last unit (in a last
@@ -162,6 +169,10 @@ __global__ __launch_bounds__(kItemThreads, 2) void gemv_items_kernel(const half_
 #pragma unroll
             for (int e = 0; e < XE; ++e) {
                 const half8_t v = __builtin_bit_cast(half8_t, xr[j & 1][e]);
+                if (E8) {
+                    *reinterpret_cast<half8_t*>(xl + x_wr[e][0]) = v;
+                    continue;
+                }
                 *reinterpret_cast<half4_t*>(xl + x_wr[e][0]) = half4_t{v[0], v[1], v[6], v[7]};
                 *reinterpret_cast<half4_t*>(xl + x_wr[e][1]) = half4_t{v[2], v[3], v[4], v[5]};
             }
@@ -172,20 +183,28 @@ __global__ __launch_bounds__(kItemThreads, 2) void gemv_items_kernel(const half_
 #pragma unroll
             for (int wp = 0; wp < 2; ++wp) {
                 xh[wp] = *reinterpret_cast<const half8_t*>(smem + x_rd[wp][0]);
-                xs[wp] = *reinterpret_cast<const half8_t*>(smem + x_rd[wp][1]);
+                xs[wp] = E8 ? xh[wp] : *reinterpret_cast<const half8_t*>(smem + x_rd[wp][1]);
             }
             floatx4 sh = zero4, sl = zero4;
 #pragma unroll
             for (int wp = 0; wp < 2; ++wp) {
                 sh = mfma(xh[wp], ones8, sh);
-                sl = mfma(xs[wp], ones8, sl);
+                if (!E8) sl = mfma(xs[wp], ones8, sl);
             }
             const floatx4 sx = sh + sl, sx30 = 30.f * sl;
 #pragma unroll
             for (int s = 0; s < R; ++s) {
             half2_t p[4][4];
 #pragma unroll
-            for (int w = 0; w < 4; ++w) w1_pairs_mixed(c[j][s][w], fmask, fmask_low, p[w]);
+            for (int w = 0; w < 4; ++w) {
+                if (E8) {                               // (w1_0, w1_1) and, after the rotation, (w1_2, w1_3)
+                    const uint32_t m8 = fmask | fmask_low, word = c[j][s][w];
+                    p[w][0] = __builtin_bit_cast(half2_t, (word & m8) | kExpBits2);
+                    p[w][1] = __builtin_bit_cast(half2_t, (__builtin_amdgcn_alignbit(word, word, 8) & m8) | kExpBits2);
+                } else {
+                    w1_pairs_mixed(c[j][s][w], fmask, fmask_low, p[w]);
+                }
+            }
             const float sc = (float)param_scale(pw[j][s]);
             const float bi = (float)param_bias(pw[j][s]);
             floatx4 acc_h = zero4, acc_l = zero4;
@@ -193,6 +212,11 @@ __global__ __launch_bounds__(kItemThreads, 2) void gemv_items_kernel(const half_
             for (int wp = 0; wp < 2; ++wp) {
                 const half2_t* w0 = p[2 * wp];
                 const half2_t* w1 = p[2 * wp + 1];
+                if (E8) {
+                    const half8_t w8 = {w0[0][0], w0[0][1], w0[1][0], w0[1][1], w1[0][0], w1[0][1], w1[1][0], w1[1][1]};
+                    acc_h = mfma(xh[wp], w8, acc_h);
+                    continue;
+                }
                 const half8_t wh = {w0[0][0], w0[0][1], w0[3][0], w0[3][1], w1[0][0], w1[0][1], w1[3][0], w1[3][1]};
                 const half8_t wl = {w0[1][0], w0[1][1], w0[2][0], w0[2][1], w1[1][0], w1[1][1], w1[2][0], w1[2][1]};
                 acc_h = mfma(xh[wp], wh, acc_h);
@@ -256,23 +280,24 @@ __global__ __launch_bounds__(kItemThreads, 2) void gemv_items_kernel(const half_
 
 static_assert(kItemWaves * kItemXBytes >= 16 * 2 * 16 * kBlockRows * (int)sizeof(float), "the wavefronts' sums take the place of X");
 
+// (K in 4-bit slots, two per 8-bit code)
 int order_units(int64_t K, int items_ph, int waves)
 {
     const int items = (int)((K / kBlockK + kItemBlocks - 1) / kItemBlocks), n_ph = (items + items_ph - 1) / items_ph;
     return n_ph * std::min(waves, items_ph);
 }
 
-template <int XE, int R, int GS>
+template <int XE, int R, int GS, bool E8 = false>
 int launch_items(const ItemsPlan& p, const half_t* X, int64_t M, const uint4* packed, int64_t N, int64_t K, half_t* Y,
                  const half_t* residual, hipStream_t stream)
 {
     constexpr int kFixed = (GS > 1 ? kZeroBytes : 0) + kItemWaves * kItemXBytes, kSum = 16 * kBlockRows * (int)sizeof(float);
     const int lds = kFixed + order_units(K, p.items_ph, p.waves) * R * kSum;
     static std::atomic<uint64_t> lds_allowed{0};
-    const int arc = allow_dynamic_lds(reinterpret_cast<const void*>(&gemv_items_kernel<XE, R, GS>), kFixed + kMaxSums * kSum, lds_allowed);
+    const int arc = allow_dynamic_lds(reinterpret_cast<const void*>(&gemv_items_kernel<XE, R, GS, E8>), kFixed + kMaxSums * kSum, lds_allowed);
     if (arc != E0M4_OK) return arc;
-    hipLaunchKernelGGL((gemv_items_kernel<XE, R, GS>), dim3((unsigned)p.grid), dim3(kItemThreads), lds, stream, X, packed, Y, residual,
-                       (int)M, (uint32_t)N, (uint32_t)K, p.rb_base, p.rb_rem, p.waves, p.items_ph);
+    hipLaunchKernelGGL((gemv_items_kernel<XE, R, GS, E8>), dim3((unsigned)p.grid), dim3(kItemThreads), lds, stream, X, packed, Y, residual,
+                       (int)M, (uint32_t)N, (uint32_t)(E8 ? K / 2 : K), p.rb_base, p.rb_rem, p.waves, p.items_ph);
     return check_launch();
 }
 
@@ -280,6 +305,7 @@ template <int R>
 int launch_items_m(const ItemsPlan& p, const half_t* x, int64_t M, const uint4* c, int64_t N, int64_t K, int group, half_t* y,
                    const half_t* r, hipStream_t stream)
 {
+    if (p.e8) return M <= 8 ? launch_items<1, R, 1, true>(p, x, M, c, N, K, y, r, stream) : launch_items<2, R, 1, true>(p, x, M, c, N, K, y, r, stream);
     if (group == 32) return launch_items<1, R, 4>(p, x, M, c, N, K, y, r, stream);
     if (group == 64) return M <= 4 ? launch_items<1, R, 2>(p, x, M, c, N, K, y, r, stream) : launch_items<2, R, 2>(p, x, M, c, N, K, y, r, stream);
     if (M <= 4) return launch_items<1, R, 1>(p, x, M, c, N, K, y, r, stream);

@@ -87,6 +87,7 @@ struct ItemsPlan {
     int64_t grid;
     int rb_base, rb_rem;
     int waves, items_ph;
+    bool e8;                                            // 8-bit codes (group 128, K in 4-bit slots, two per code)
 };
 bool gemv_items_supported(const ItemsPlan& p, int64_t M, int64_t N, int64_t K, int group);
 bool gemv_items_pays(const ItemsPlan& p, int64_t M, int group);

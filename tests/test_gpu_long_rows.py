@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 
 import synth_inputs
+import test_gpu_e0m8
 from test_gpu_parity import assert_quantize_exact, check_matmul, e0m4, to_dev, torch  # noqa: F401
 
 pytestmark = pytest.mark.gpu
@@ -43,4 +44,28 @@ def same_bits(e0m4, oracle, M, N, K, G, target):
     check_matmul(Y[0], Yref, absdot, "M=%d K=%d" % (M, K))
     if G == 128:                                        # (other groups: 2 leaves the plain call to another kernel)
         assert torch.equal(Y[0].view(torch.int16), Y[1].view(torch.int16))
+    assert torch.equal(YR[0].view(torch.int16), YR[1].view(torch.int16))
+
+
+# 8-bit codes: k blocks of 64 weights, the same order of sums
+@pytest.mark.parametrize("N,target", [(80, 3), (17, 0)])
+@pytest.mark.parametrize("K", [768, 1344, 2560, 4096, 5184, 8192, 13696])
+@pytest.mark.parametrize("M", [3, 5, 8, 9, 16])
+def test_same_bits_as_staged_8bit(e0m4, oracle, M, K, N, target):
+    codes, What = test_gpu_e0m8.assert_quantize_exact(e0m4, oracle, synth_inputs.weights(N, K, seed=5300 + N), 64)
+    X = synth_inputs.activations(M, K, seed=5400 + M, outlier_frac=0.01)
+    R = synth_inputs.activations(M, N, seed=5500 + M)
+    Y, YR = [], []
+    e0m4.e0m4_set_knob("gemv_workgroups", target)
+    try:
+        for mode in (0, 2):
+            e0m4.e0m4_set_knob("gemv_mfma", mode)
+            Y.append(e0m4.e0m8_matmul(to_dev(X), codes, N, K, 64))
+            YR.append(e0m4.e0m8_matmul_fused(to_dev(X), codes, N, K, 64, residual=to_dev(R)))
+    finally:
+        e0m4.e0m4_set_knob("gemv_mfma", 0)
+        e0m4.e0m4_set_knob("gemv_workgroups", 0)
+    Yref, absdot = oracle.matmul(X, What)
+    check_matmul(Y[0], Yref, absdot, "M=%d K=%d" % (M, K))
+    assert torch.equal(Y[0].view(torch.int16), Y[1].view(torch.int16))
     assert torch.equal(YR[0].view(torch.int16), YR[1].view(torch.int16))
