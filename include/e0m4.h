@@ -129,7 +129,9 @@ int e0m4_unpack_codes(const void* codes, int64_t N, int64_t K, int group, void* 
  *            the LDS), else a matrix-core kernel that dequantises the weight
  *            operand in registers.
  *   17 <= M <= 64, group 128, N * K <= 7e7, a chunk of X within the LDS:
- *            that kernel on equal chunks of at most 16 rows in one launch,
+ *            that kernel (in fused calls on equal chunks of at most 16 rows
+ *            in one launch, in plain ones the dequantising kernel's form on
+ *            exact codes),
  *            when its workgroups make at most two rounds on the compute
  *            units (three on small weights); otherwise, any group, N * K <= 7e7 (and
  *            256 <= K <= 9216 for M > 48), the dequantising kernel.
@@ -302,8 +304,10 @@ int e0m3_unpack_codes(const void* codes, int64_t N, int64_t K, int group, void* 
  * are bfloat16 (16-bit patterns, round to nearest even); accumulation is fp32.
  * `codes` has the E0M4 layout and size (e0m4_codes_bytes; e0m4_unpack_codes
  * reads it), its embedded parameter words hold bfloat16 pairs.
- *   e0m4_bf16_matmul: M <= 8 the decode kernel with bfloat16 dot products
- *   (a shift and a mask-or per pair of codes; scale and bias in fp32); larger M
+ *   e0m4_bf16_matmul: one row (two, with groups of 64 and 32) the decode kernel
+ *   with bfloat16 dot products (a shift and a mask-or per pair of codes; scale
+ *   and bias in fp32), up to 8 rows (4 with groups of 32) the small-batch
+ *   matrix-core kernels on the codes' exact values; larger M
  *   with the weights dequantised in registers (fp32 fused multiply-add, one
  *   rounding to bfloat16): up to 64 rows, and 128 on small weights (not on the
  *   shortest rows), the dequantising kernel of e0m4_matmul, beyond that its pipelined MFMA kernel

@@ -991,11 +991,9 @@ int launch_gemv_mfma_bf16(const void* X, int64_t M, const void* packed, int64_t 
 // the M and chunk counts the callers use: 17 ... 64 rows in ceil(M / 16) chunks).
 int64_t chunk_rows(int64_t M, int chunks) { return (M + chunks - 1) / chunks; }
 
-// Groups of 64 and 32 stage every row of X two or four times (16 rows of LDS traffic whatever M is), which the
-// kernel with dequantised operands (e0m4_gemv_dq.hip) does not.  This one takes the calls where a workgroup has several
-// row blocks to spend its staging on, or (group 64) the staged rows fit the LDS at once: 15360 x 5120 at M = 4 12.4 us,
-// 27392 x 5120 at M = 8 22.6, 5120 x 5120 at M = 4 7.5; in phases 5120 x 5120 at M = 8 11.1, 5120 x 13696 at M = 4 18.9.
-// It works with unrounded weights, the other kernel with weights rounded to fp16: the line stays where it is, also where
+// Groups of 64 and 32: where this kernel (or e0m4_gemv_items.hip for it) takes plain calls from the kernel with dequantised
+// operands (e0m4_gemv_dq.hip): with several row blocks per workgroup, or (group 64) K in one phase.  15360 x 5120 at M = 4 12.4
+// us, 27392 x 5120 at M = 8 22.6, 5120 x 5120 at M = 4 7.5.  It works with unrounded weights, the other kernel with weights rounded to fp16: the line stays where it is, also where
 // the other kernel is by now the faster one.  At M = 2 the vector kernel is as fast or faster.
 bool gemv_mfma_groups_pay(int64_t M, int64_t N, int64_t K, int group)
 {
