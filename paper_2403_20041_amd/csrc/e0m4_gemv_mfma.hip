@@ -922,6 +922,7 @@ template <int W, bool FUSED>
 int launch_mfma(const MfmaPlan& p, const void* X, int64_t M, const void* packed, int64_t N, int64_t K, void* Y,
                 hipStream_t stream, const GemvFusion& fu = GemvFusion{}, int gs = 1)
 {
+    // one or two row blocks per workgroup: X block by block, to the same bits (gemv_mfma 2 and 3: the kernel above)
     if constexpr (W >= 8) {
         const int items = (int)((k_blocks(K) + kSuper - 1) / kSuper);
         const ItemsPlan ip{p.grid, p.rb_base, p.rb_rem, W, p.kb_phase > 0 ? p.kb_phase / kSuper : items, false};
