@@ -38,10 +38,10 @@ constexpr int kItemXBytes = 16 * kBlockK * 2;   // sixteen rows of a k block (8-
 // XE: loads of X per k block, four rows each (calls of up to 4 and 8 rows make one and two; the other rows of the tile stay
 // what LDS held, and so do their sums, which nobody stores; 8-bit codes: eight rows a load).  R: row blocks per workgroup.  GS: groups per k block; a row of X
 // is then GS rows of the MFMA, with zeros for the k-groups of the other groups.  E8: 8-bit codes, k blocks of 64 weights, a single
-// kind of code slot.
+// kind of code slot.  `residual` may be Y: neither is declared free of aliases.
 template <int XE, int R, int GS, bool E8>
 __global__ __launch_bounds__(kItemThreads, 2) void gemv_items_kernel(const half_t* __restrict__ X, const uint4* __restrict__ packed,
-                                                                     half_t* __restrict__ Y, const half_t* __restrict__ residual,
+                                                                     half_t* Y, const half_t* residual,
                                                                      int M, uint32_t N32, uint32_t K32, int rb_base, int rb_rem,
                                                                      int order_waves, int items_ph)
 {

@@ -5,6 +5,7 @@ import pytest
 
 import synth_inputs
 import test_gpu_e0m8
+from test_gpu_fused import run_fused
 from test_gpu_parity import assert_quantize_exact, check_matmul, e0m4, to_dev, torch  # noqa: F401
 
 pytestmark = pytest.mark.gpu
@@ -45,6 +46,19 @@ def same_bits(e0m4, oracle, M, N, K, G, target):
     if G == 128:                                        # (other groups: 2 leaves the plain call to another kernel)
         assert torch.equal(Y[0].view(torch.int16), Y[1].view(torch.int16))
     assert torch.equal(YR[0].view(torch.int16), YR[1].view(torch.int16))
+
+
+# The residual may be the output's own buffer (two row blocks in some workgroups with three asked for, one with none).
+@pytest.mark.parametrize("bits", [4, 8])
+@pytest.mark.parametrize("N,target,K", [(80, 3, 2560), (17, 0, 2560), (203, 0, 13696)])
+@pytest.mark.parametrize("M", [5, 16])
+def test_residual_in_place(e0m4, oracle, M, N, target, K, bits):
+    e0m4.e0m4_set_knob("gemv_workgroups", target)
+    try:
+        Y, Y2 = (run_fused(e0m4, oracle, M, N, K, 128, seed=5600 + M, res=True, in_place=i, bits=bits) for i in (False, True))
+    finally:
+        e0m4.e0m4_set_knob("gemv_workgroups", 0)
+    assert torch.equal(Y.view(torch.int16), Y2.view(torch.int16))
 
 
 # 8-bit codes: k blocks of 64 weights, the same order of sums
