@@ -24,7 +24,8 @@ thread_local Knob g_knobs[] = {
     {"gemv_workgroups", 0},            // target number of workgroups of the small-M kernel
     // the matrix-core small-batch kernels: 1 neither; 2 activations staged in LDS always read from there; 3 their wavefront sums
     // reduced per row block; 4 plain matmuls on dequantised operands wherever that can run, 5 never; 6 staged also for groups of
-    // 64 and 32 wherever that can run; 7 plain matmuls on exact codes without staging wherever that can run, 8 never
+    // 64 and 32 wherever that can run; 7 plain matmuls on exact codes without staging wherever that can run, 8 never; 9 as 6, and
+    // X block by block wherever that can run
     {"gemv_mfma", 0},
     {"gemv_xreg", 0},                  // M = 1 kernel, a wavefront's activations in registers: 2 never
     {"gemm_variant", 0},               // 1: small-tile kernel; pipelined kernel with tiles of 2: 256 x 256, 3: 128 x 128, 4: 64 x 256, 5: 128 x 256
@@ -72,13 +73,13 @@ __global__ void zero_fill_kernel(half_t* y, int64_t count)
 }
 
 bool group_ok(int group) { return group == 32 || group == 64 || group == 128; }
-// The small-batch kernel that stages X in LDS, for plain matmuls (gemv_mfma 1: off; 6: also for groups of 64 and 32 wherever
+// The small-batch kernel that stages X in LDS, for plain matmuls (gemv_mfma 1: off; 6 and 9: also for groups of 64 and 32 wherever
 // it can run, which by default it does where it pays).
 bool use_gemv_mfma(int64_t M, int64_t N, int64_t K, int group)
 {
     const int k = knob("gemv_mfma");
     if (k == 1 || !gemv_mfma_supported(M, N, K, group)) return false;
-    return group == 128 || k == 6 || gemv_mfma_groups_pay(M, N, K, group);
+    return group == 128 || k == 6 || k == 9 || gemv_mfma_groups_pay(M, N, K, group);
 }
 // M <= kGemvMaxM rows take the vector decode kernel, whose time grows with M, unless the matrix-core GEMM
 // (64 x 256 tile, time nearly independent of M) is faster: measured crossover at about M * N * K = 3.8e8
@@ -244,7 +245,7 @@ static int fused_path(const Fusion& f, int64_t M, int64_t N, int64_t K, int grou
     // (groups of 64 and 32 from three rows on: 1.1 - 2 x the vector kernel and the GEMM there, 10 - 25 % slower than the
     // vector kernel at two rows)
     if (knob("gemv_mfma") != 1 && gemv_mfma_fused_supported(f, M, N, K, group) &&
-        (group == 128 || M >= 3 || knob("gemv_mfma") == 6))
+        (group == 128 || M >= 3 || knob("gemv_mfma") == 6 || knob("gemv_mfma") == 9))
         return 2;
     if (small_batch_in_chunks(f, M, N, K, group)) return 3;
     return (small_m_on_vector(M, N, K) && gemv_fused_supported(f, M, N, K)) ? 0 : 1;

@@ -922,13 +922,13 @@ template <int W, bool FUSED>
 int launch_mfma(const MfmaPlan& p, const void* X, int64_t M, const void* packed, int64_t N, int64_t K, void* Y,
                 hipStream_t stream, const GemvFusion& fu = GemvFusion{}, int gs = 1)
 {
-    // one or two row blocks per workgroup: X block by block, to the same bits (gemv_mfma 2 and 3: the kernel above)
+    // one or two row blocks per workgroup: X block by block, to the same bits (gemv_mfma 2 and 3: the kernel above, 9: wherever it can)
     if constexpr (W >= 8) {
         const int items = (int)((k_blocks(K) + kSuper - 1) / kSuper);
-        const ItemsPlan ip{p.grid, p.rb_base, p.rb_rem, W, p.kb_phase > 0 ? p.kb_phase / kSuper : items, false};
+        const ItemsPlan ip{p.grid, p.rb_base, p.rb_rem, W, p.kb_phase > 0 ? p.kb_phase / kSuper : items, p.kb_phase > 0, false};
         const bool xreg = gs == 1 && W <= 8 && p.kb_phase == 0 && p.step_item == 0;
         if (!fu.gamma && !fu.swiglu && fu.m_total == 0 && !xreg && knob("gemv_mfma") != 2 && knob("gemv_mfma") != 3 &&
-            gemv_items_supported(ip, M, N, K, kG / gs) && gemv_items_pays(ip, M, kG / gs))
+            gemv_items_supported(ip, M, N, K, kG / gs) && (knob("gemv_mfma") == 9 || gemv_items_pays(ip, M, kG / gs, FUSED)))
             return launch_gemv_items(ip, X, M, packed, N, K, kG / gs, Y, fu.residual, stream);
     }
     if (gs == 2) return launch_mfma_groups<W, FUSED, 2>(p, X, M, packed, N, K, Y, stream, fu);
@@ -1036,9 +1036,9 @@ int launch_mfma8(const MfmaPlan& p, const GemvFusion& fu, const void* X, int64_t
                  int64_t K, void* Y, hipStream_t stream)
 {
     const int items = (int)((k_blocks(2 * K) + kSuper - 1) / kSuper);
-    const ItemsPlan ip{p.grid, p.rb_base, p.rb_rem, p.waves, p.kb_phase > 0 ? p.kb_phase / kSuper : items, true};
+    const ItemsPlan ip{p.grid, p.rb_base, p.rb_rem, p.waves, p.kb_phase > 0 ? p.kb_phase / kSuper : items, p.kb_phase > 0, true};
     if (!fu.gamma && !fu.swiglu && fu.m_total == 0 && (p.kb_phase > 0 || p.step_item != 0) && knob("gemv_mfma") != 2 &&
-        knob("gemv_mfma") != 3 && gemv_items_supported(ip, M, N, 2 * K, 128) && gemv_items_pays(ip, M, 128))
+        knob("gemv_mfma") != 3 && gemv_items_supported(ip, M, N, 2 * K, 128) && (knob("gemv_mfma") == 9 || gemv_items_pays(ip, M, 128, FUSED)))
         return launch_gemv_items(ip, X, M, packed, N, 2 * K, 128, Y, fu.residual, stream);
     if (p.kb_phase > 0)
         return p.waves == 8 ? launch_mfma_phased<8, FUSED, true>(p, X, M, packed, N, K, Y, stream, fu)

@@ -87,10 +87,11 @@ struct ItemsPlan {
     int64_t grid;
     int rb_base, rb_rem;
     int waves, items_ph;
+    bool phased;                                        // X does not fit that kernel's LDS at once
     bool e8;                                            // 8-bit codes (group 128, K in 4-bit slots, two per code)
 };
 bool gemv_items_supported(const ItemsPlan& p, int64_t M, int64_t N, int64_t K, int group);
-bool gemv_items_pays(const ItemsPlan& p, int64_t M, int group);
+bool gemv_items_pays(const ItemsPlan& p, int64_t M, int group, bool fused);
 int launch_gemv_items(const ItemsPlan& p, const void* X, int64_t M, const void* packed, int64_t N, int64_t K, int group, void* Y,
                       const void* residual, hipStream_t stream);
 // Small-batch path with the weight operand dequantised in registers: 2 <= M <= 128, any group (e0m4_gemv_dq.hip).

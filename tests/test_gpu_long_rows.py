@@ -1,11 +1,10 @@
 """Few rows of X with one or two row blocks per workgroup: the kernel that takes X block by block gives the bits of the one that
 stages it, whole or in phases, and both are the oracle's within its bar."""
-import numpy as np
 import pytest
 
 import synth_inputs
 import test_gpu_e0m8
-from test_gpu_fused import run_fused
+from test_gpu_fused import check_fused, run_fused
 from test_gpu_parity import assert_quantize_exact, check_matmul, e0m4, to_dev, torch  # noqa: F401
 
 pytestmark = pytest.mark.gpu
@@ -31,21 +30,32 @@ def same_bits(e0m4, oracle, M, N, K, G, target):
     (codes, _, _), What = assert_quantize_exact(e0m4, oracle, synth_inputs.weights(N, K, seed=5000 + N), G)
     X = synth_inputs.activations(M, K, seed=5100 + M, outlier_frac=0.01)
     R = synth_inputs.activations(M, N, seed=5200 + M)
-    Y, YR = [], []
+
+    def plain(x):
+        return e0m4.e0m4_matmul(x, codes, None, None, N, K, G)
+
+    def fused(x, **residual):
+        return e0m4.e0m4_matmul_fused(x, codes, N, K, G, **residual)
+
+    compare(e0m4, oracle, plain, fused, X, What, R, target)
+
+
+def compare(e0m4, oracle, plain, fused, X, What, R, target):
     e0m4.e0m4_set_knob("gemv_workgroups", target)
     try:
-        for mode in (0 if G == 128 else 6, 2):          # (6: groups of 64 and 32 on these kernels wherever they can run)
-            e0m4.e0m4_set_knob("gemv_mfma", mode)
-            Y.append(e0m4.e0m4_matmul(to_dev(X), codes, None, None, N, K, G))
-            YR.append(e0m4.e0m4_matmul_fused(to_dev(X), codes, N, K, G, residual=to_dev(R)))
+        e0m4.e0m4_set_knob("gemv_mfma", 9)              # block by block wherever that can run, also where it does not pay
+        Y, YR = plain(to_dev(X)), fused(to_dev(X), residual=to_dev(R))
+        e0m4.e0m4_set_knob("gemv_mfma", 2)              # staged (plain calls in groups of 64 and 32 only through the fused entry point)
+        Y2, YR2 = fused(to_dev(X)), fused(to_dev(X), residual=to_dev(R))
     finally:
         e0m4.e0m4_set_knob("gemv_mfma", 0)
         e0m4.e0m4_set_knob("gemv_workgroups", 0)
-    Yref, absdot = oracle.matmul(X, What)
-    check_matmul(Y[0], Yref, absdot, "M=%d K=%d" % (M, K))
-    if G == 128:                                        # (other groups: 2 leaves the plain call to another kernel)
-        assert torch.equal(Y[0].view(torch.int16), Y[1].view(torch.int16))
-    assert torch.equal(YR[0].view(torch.int16), YR[1].view(torch.int16))
+    Yref, info = oracle.matmul_fused(X, What)
+    check_matmul(Y, Yref, info["absdot"], "plain")
+    YRref, info = oracle.matmul_fused(X, What, residual=R)
+    check_fused(YR, YRref, info, False, False, "residual")
+    assert torch.equal(Y.view(torch.int16), Y2.view(torch.int16))
+    assert torch.equal(YR.view(torch.int16), YR2.view(torch.int16))
 
 
 # The residual may be the output's own buffer (two row blocks in some workgroups with three asked for, one with none).
@@ -54,9 +64,11 @@ def same_bits(e0m4, oracle, M, N, K, G, target):
 @pytest.mark.parametrize("M", [5, 16])
 def test_residual_in_place(e0m4, oracle, M, N, target, K, bits):
     e0m4.e0m4_set_knob("gemv_workgroups", target)
+    e0m4.e0m4_set_knob("gemv_mfma", 9)
     try:
         Y, Y2 = (run_fused(e0m4, oracle, M, N, K, 128, seed=5600 + M, res=True, in_place=i, bits=bits) for i in (False, True))
     finally:
+        e0m4.e0m4_set_knob("gemv_mfma", 0)
         e0m4.e0m4_set_knob("gemv_workgroups", 0)
     assert torch.equal(Y.view(torch.int16), Y2.view(torch.int16))
 
@@ -69,17 +81,11 @@ def test_same_bits_as_staged_8bit(e0m4, oracle, M, K, N, target):
     codes, What = test_gpu_e0m8.assert_quantize_exact(e0m4, oracle, synth_inputs.weights(N, K, seed=5300 + N), 64)
     X = synth_inputs.activations(M, K, seed=5400 + M, outlier_frac=0.01)
     R = synth_inputs.activations(M, N, seed=5500 + M)
-    Y, YR = [], []
-    e0m4.e0m4_set_knob("gemv_workgroups", target)
-    try:
-        for mode in (0, 2):
-            e0m4.e0m4_set_knob("gemv_mfma", mode)
-            Y.append(e0m4.e0m8_matmul(to_dev(X), codes, N, K, 64))
-            YR.append(e0m4.e0m8_matmul_fused(to_dev(X), codes, N, K, 64, residual=to_dev(R)))
-    finally:
-        e0m4.e0m4_set_knob("gemv_mfma", 0)
-        e0m4.e0m4_set_knob("gemv_workgroups", 0)
-    Yref, absdot = oracle.matmul(X, What)
-    check_matmul(Y[0], Yref, absdot, "M=%d K=%d" % (M, K))
-    assert torch.equal(Y[0].view(torch.int16), Y[1].view(torch.int16))
-    assert torch.equal(YR[0].view(torch.int16), YR[1].view(torch.int16))
+
+    def plain(x):
+        return e0m4.e0m8_matmul(x, codes, N, K, 64)
+
+    def fused(x, **residual):
+        return e0m4.e0m8_matmul_fused(x, codes, N, K, 64, **residual)
+
+    compare(e0m4, oracle, plain, fused, X, What, R, target)
