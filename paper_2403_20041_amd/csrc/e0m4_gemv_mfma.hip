@@ -162,10 +162,6 @@ __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restr
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int n_l = lane & 15, g_l = lane >> 4;         // weight row / k-group of this lane; also (row of X, k-group)
     const uint32_t fmask = BF ? frac_mask_bf16_vgpr() : frac_mask_vgpr(), fmask_low = frac_mask_low_vgpr();
-    auto mfma = [](const half8_t& a, const half8_t& b, const floatx4& c_) -> floatx4 {
-        if constexpr (BF) return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c_, 0, 0, 0);
-        else return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c_, 0, 0, 0);
-    };
     auto out_value = [](float v) -> half_t {
         if constexpr (BF) return __builtin_bit_cast(half_t, (__bf16)v);
         else return (half_t)v;
@@ -549,8 +545,13 @@ __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restr
             floatx4 sh = zero4, sl = zero4;
 #pragma unroll
             for (int wp = 0; wp < 2; ++wp) {
-                sh = mfma(xh[wp], ones8, sh);
-                if (!E8) sl = mfma(xl[wp], ones8, sl);
+                if constexpr (BF) {
+                    sh = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, xh[wp]), __builtin_bit_cast(bf16x8_t, ones8), sh, 0, 0, 0);
+                    sl = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, xl[wp]), __builtin_bit_cast(bf16x8_t, ones8), sl, 0, 0, 0);
+                } else {
+                    sh = __builtin_amdgcn_mfma_f32_16x16x32_f16(xh[wp], ones8, sh, 0, 0, 0);
+                    if (!E8) sl = __builtin_amdgcn_mfma_f32_16x16x32_f16(xl[wp], ones8, sl, 0, 0, 0);
+                }
             }
             sx = sh + sl;
             sx30 = 30.f * sl;
@@ -609,7 +610,7 @@ __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restr
                             const half2_t* w0 = p[2 * wp];
                             const half2_t* w1 = p[2 * wp + 1];
                             const half8_t w8 = {w0[0][0], w0[0][1], w0[1][0], w0[1][1], w1[0][0], w1[0][1], w1[1][0], w1[1][1]};
-                            acc_h = mfma(xh2[wp], w8, acc_h);
+                            acc_h = __builtin_amdgcn_mfma_f32_16x16x32_f16(xh2[wp], w8, acc_h, 0, 0, 0);
                             continue;
                         }
                         const half8_t xh = xh2[wp], xl = xl2[wp];
@@ -618,14 +619,14 @@ __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restr
                         if (BF) {
                             const half8_t wa = {w0[0][0], w0[0][1], w0[1][0], w0[1][1], w0[2][0], w0[2][1], w0[3][0], w0[3][1]};
                             const half8_t wb = {w1[0][0], w1[0][1], w1[1][0], w1[1][1], w1[2][0], w1[2][1], w1[3][0], w1[3][1]};
-                            acc_h = mfma(xh, wa, acc_h);
-                            acc_l = mfma(xl, wb, acc_l);
+                            acc_h = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, xh), __builtin_bit_cast(bf16x8_t, wa), acc_h, 0, 0, 0);
+                            acc_l = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, xl), __builtin_bit_cast(bf16x8_t, wb), acc_l, 0, 0, 0);
                             continue;
                         }
                         const half8_t wh = {w0[0][0], w0[0][1], w0[3][0], w0[3][1], w1[0][0], w1[0][1], w1[3][0], w1[3][1]};
                         const half8_t wl = {w0[1][0], w0[1][1], w0[2][0], w0[2][1], w1[1][0], w1[1][1], w1[2][0], w1[2][1]};
-                        acc_h = mfma(xh, wh, acc_h);
-                        acc_l = mfma(xl, wl, acc_l);
+                        acc_h = __builtin_amdgcn_mfma_f32_16x16x32_f16(xh, wh, acc_h, 0, 0, 0);
+                        acc_l = __builtin_amdgcn_mfma_f32_16x16x32_f16(xl, wl, acc_l, 0, 0, 0);
                     }
                     if (kb < nkb_ph) {
                         floatx4 sx, sx30;
@@ -839,22 +840,40 @@ bool make_mfma_plan(int64_t M, int64_t N, int64_t K, MfmaPlan& p, int unit = 1, 
 // stands in a cache, is what every wavefront needs first.  With rms-norm, weights first and X first (us): 15360 x 5120 at M = 4
 // 15.0 -> 13.7, gated 32768 x 2048 at M = 16 15.4 -> 14.7, groups of 64 4096 x 4096 at M = 5 10.1 -> 9.1, 8-bit codes 9.7 -> 9.0 at
 // M = 4; with a residual 8-bit 4096 x 4096 7.7 -> 7.3; bfloat16 4096 x 4096 at M = 8 6.7 -> 6.2.
-// Not with K in phases, where X is many loads per thread (4096 x 13696 with norm at M = 16 32.2 and 35.2).  With X in registers and 4-bit
-// codes not where wavefronts stage their own X of more than eight rows (4608 x 4096 at M = 16 8.3 and 8.6), for the same reason, nor
-// where there are fewer work items than wavefronts (2560 x 2048 at M = 2 with norm 6.8 and 7.0).
-bool x_first(const MfmaPlan& p, int64_t M, int64_t K, bool normed, bool gated)
+// Not with K in phases, where X is many loads per thread (4096 x 13696 with norm at M = 16 32.2 and 35.2).  Of the instances below
+// there are two, and of the others the one that is faster nearly everywhere:
+//   4-bit codes, X in registers: not where wavefronts stage their own X of more than eight rows (4608 x 4096 at M = 16 8.3 and 8.6),
+//     which is as many loads again, nor where there are fewer work items than wavefronts (2560 x 2048 at M = 2 with norm 6.8 and 7.0;
+//     gated, also where there are as many: 7.0 and 7.15).
+//   8-bit codes, X in registers, fused: not with the gated product (2560 x 2048 at M = 3 7.45 and 7.65).
+//   Eight wavefronts, X from LDS, plain: from nine rows on always (0.92 - 1.0 of the time on 250 problems), from five where there are
+//     at least as many work items as wavefronts (0.94 - 1.04; 6144 x 1536, six items, 1.03), in 4-bit codes with more than twelve work
+//     items also below (0.95 - 1.02; with up to twelve 0.97 - 1.07, 8-bit codes 0.98 - 1.07).
+//   Sixteen wavefronts, fused: with rms-norm only (residual, 5120 x 13696 at M = 4 14.1 and 14.5, 8-bit 2560 x 8192 at M = 4 8.85 and 9.1).
+constexpr bool x_first_by_plan(int W, bool FUSED, bool XREG, bool E8, bool PHASED, int GS, bool BF)
+{
+    if (PHASED) return false;
+    if (XREG) return !E8 || (FUSED && W == 8);
+    return !BF && (FUSED ? W == 16 && GS == 1 : W == 8);
+}
+bool x_first(const MfmaPlan& p, int64_t M, int64_t K, bool xreg, bool e8, bool fused, const GemvFusion& fu)
 {
     const int64_t nsi = (k_blocks(K) + kSuper - 1) / kSuper;
-    if (p.rb_base * (gated ? 2 : 1) * nsi < p.waves) return !normed && M > 4;
+    const bool normed = fu.gamma != nullptr, gated = fu.swiglu != 0;
+    const int64_t items = p.rb_base * (gated ? 2 : 1) * nsi;
+    if (!xreg) return fused ? normed : M > 8 || (M > 4 && items >= p.waves) || (!e8 && 2 * items > 3 * p.waves);
+    if (e8) return !gated;
+    if (items < p.waves || (gated && items == p.waves)) return !normed && M > 4;
     return normed || p.step_slots != 1 || M <= 8;
 }
 
-template <int W, bool FUSED, bool XREG, bool E8, bool PHASED, int GS, bool KEEP, bool BF = false, bool XF = !PHASED && !(XREG && !E8)>
+template <int W, bool FUSED, bool XREG, bool E8, bool PHASED, int GS, bool KEEP, bool BF = false,
+          bool XF = !PHASED && !x_first_by_plan(W, FUSED, XREG, E8, PHASED, GS, BF)>
 int launch_mfma_keep(const MfmaPlan& p, const void* X, int64_t M, const void* packed, int64_t N, int64_t K, void* Y,
                   hipStream_t stream, const GemvFusion& fu)
 {
-    if constexpr (XREG && !E8 && !XF) {
-        if (x_first(p, M, K, fu.gamma != nullptr, fu.swiglu != 0))
+    if constexpr (x_first_by_plan(W, FUSED, XREG, E8, PHASED, GS, BF) && !XF) {
+        if (x_first(p, M, E8 ? 2 * K : K, XREG, E8, FUSED, fu))
             return launch_mfma_keep<W, FUSED, XREG, E8, PHASED, GS, KEEP, BF, true>(p, X, M, packed, N, K, Y, stream, fu);
     }
     if (PHASED != (p.kb_phase > 0) || (PHASED && !p.late) || p.lds_bytes > (size_t)kLdsLimitBytes) return E0M4_ERR_SHAPE;
