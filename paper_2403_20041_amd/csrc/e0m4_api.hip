@@ -138,13 +138,19 @@ bool use_gemv_dq4(int64_t M, int64_t N, int64_t K, int group)
     return use_gemv_dq(M, N, K, group, kDqFormatFp16);
 }
 // bfloat16 of up to eight rows: the small-batch kernel, which multiplies the codes' exact values as the vector kernel does but
-// whose time hardly grows with the rows (27392 x 5120 at M = 5 32 -> 18.3 us; M = 2 21.5 -> 18.4, 4096 x 4096 5.8 -> 5.7, 2560 x
-// 2048 4.4 and 4.5).  In groups of 64 and 32 from three rows on: 2560 x 2048 at M = 2 4.4 against 4.8, at M = 3 5.6 against 4.8.
+// whose time hardly grows with the rows (27392 x 5120 at M = 5 32 -> 18.3 us; M = 2 21.5 -> 18.4).  In groups of 64 and 32 from three
+// rows on: 2560 x 2048 at M = 2 4.4 against 4.8, at M = 3 5.6 against 4.8.  Two rows in groups of 128 on 117 problems: 0.79 - 0.93 of
+// the vector kernel's time with more than six work items (of 512 weights) per row of weights, and with five or six where
+// workgroups have one row block each; else 0.95 - 1.15 (2560 x 2048 4.2 and 4.6 us, 7680 x 2560 5.8 and 6.4), but 0.79 - 1.04 with more
+// than five row blocks per workgroup and more than three work items.
 // (gemv_mfma 1: the vector kernel, 6: this one from two rows on)
 bool use_gemv_mfma_bf16(int64_t M, int64_t N, int64_t K, int group)
 {
     const int k = knob("gemv_mfma");
-    return M <= kGemvMaxM && k != 1 && (group == 128 || M >= 3 || k == 6) && gemv_mfma_supported(M, N, K, group);
+    if (M > kGemvMaxM || k == 1 || !gemv_mfma_supported(M, N, K, group)) return false;
+    if (M > 2 || k == 6) return true;
+    const int64_t items = (k_blocks(K) + 3) / 4, rb = (row_blocks(N) + 255) / 256;
+    return group == 128 && (items > 6 || (items > 4 && rb == 1) || (items > 3 && rb > 5));
 }
 // The kernel of use_gemv_dq on exact codes, which multiplies unrounded weights, for plain matmuls (gemv_mfma 7 forces it wherever it
 // can run; any other value but 0 leaves its calls to the kernels that have them otherwise).
