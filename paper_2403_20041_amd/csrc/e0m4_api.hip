@@ -157,7 +157,7 @@ bool use_gemv_mfma_bf16(int64_t M, int64_t N, int64_t K, int group)
 bool use_gemv_exact(int64_t M, int64_t N, int64_t K, int group, DqFormat format)
 {
     const int k = knob("gemv_mfma");
-    if ((k != 0 && k != 7) || !gemv_exact_supported(M, N, K, group)) return false;
+    if ((k != 0 && k != 7) || !gemv_exact_supported(M, N, K, group, format)) return false;
     if (k == 7) return true;
     if (gemm_steered() || N > (int64_t)1 << 24) return false;
     return gemv_exact_pays(M, N, K, format, format == kDqFormatFp16 && small_batch_in_chunks(Fusion{}, M, N, K, group));

@@ -39,7 +39,7 @@ typedef float floatx2 __attribute__((ext_vector_type(2)));
 constexpr int kDqWaves = 8;
 constexpr int kDqThreads = kDqWaves * 64;
 constexpr int kDqMaxR = 4;                      // row blocks per wavefront
-constexpr int kDqMaxSlots = 16;                 // row blocks per workgroup (so that at least two wavefronts share a row block)
+constexpr int kDqMaxSlots = 16;                 // row blocks per workgroup (so that two wavefronts at least share a row block; one, with R at most two)
 constexpr int kDqMaxM = 64;                     // rows of X per workgroup
 constexpr int kDqMaxParts = 2;
 constexpr int kTargetWorkgroups = 256;          // one workgroup per compute unit
@@ -393,17 +393,24 @@ int launch_dq_m(const DqPlan& p, const void* X, int64_t M, const void* packed, i
                 int group, void* Y, hipStream_t stream)
 {
     constexpr int XE = FMT == kDqFormatE8 ? 2 : 4;
-    if constexpr (FMT == kDqFormatFp16 || EX) {         // (the other formats come here with nine rows or more)
+    // (calls of up to eight rows: fp16 with rounded weights, bfloat16 with exact codes)
+    if constexpr (EX == (FMT == kDqFormatBf16) && FMT != kDqFormatE8) {
         if (M <= 4) return launch_dq_r<FMT, 1, 1, EX>(p, X, M, packed, N, K, group, Y, stream);
         if (M <= 8) return launch_dq_r<FMT, 1, 2, EX>(p, X, M, packed, N, K, group, Y, stream);
     }
-    switch (((M + p.parts - 1) / p.parts + 15) / 16) {
-        case 1: return launch_dq_r<FMT, 1, XE, EX>(p, X, M, packed, N, K, group, Y, stream);
-        case 2: return launch_dq_r<FMT, 2, XE, EX>(p, X, M, packed, N, K, group, Y, stream);
-        case 3: return launch_dq_r<FMT, 3, XE, EX>(p, X, M, packed, N, K, group, Y, stream);
-        case 4: return launch_dq_r<FMT, 4, XE, EX>(p, X, M, packed, N, K, group, Y, stream);
-        default: return E0M4_ERR_SHAPE;
+    if constexpr (!(EX && FMT == kDqFormatBf16)) {
+        const int64_t tiles = ((M + p.parts - 1) / p.parts + 15) / 16;
+        if constexpr (!EX) {
+            if (tiles == 1) return launch_dq_r<FMT, 1, XE, EX>(p, X, M, packed, N, K, group, Y, stream);
+        }
+        switch (tiles) {
+            case 2: return launch_dq_r<FMT, 2, XE, EX>(p, X, M, packed, N, K, group, Y, stream);
+            case 3: return launch_dq_r<FMT, 3, XE, EX>(p, X, M, packed, N, K, group, Y, stream);
+            case 4: return launch_dq_r<FMT, 4, XE, EX>(p, X, M, packed, N, K, group, Y, stream);
+            default: break;
+        }
     }
+    return E0M4_ERR_SHAPE;
 }
 
 }  // namespace
@@ -440,10 +447,12 @@ bool gemv_dq_pays(int64_t M, int64_t N, int64_t K, int group, DqFormat format)
     return format == kDqFormatFp16 && group != 128;
 }
 
-bool gemv_exact_supported(int64_t M, int64_t N, int64_t K, int group)
+// (the row counts of the calls below; the kernel is not compiled for others)
+bool gemv_exact_supported(int64_t M, int64_t N, int64_t K, int group, DqFormat format)
 {
     DqPlan p;
-    return group == 128 && make_dq_plan(M, N, K, p, true);
+    const bool rows = format == kDqFormatBf16 ? M <= 8 : format == kDqFormatFp16 && M > 16 && M <= kDqMaxM;
+    return rows && group == 128 && make_dq_plan(M, N, K, p, true);
 }
 
 // Where exact codes are faster than the kernels of unrounded weights that have the call otherwise (us, cold weights, the other and
@@ -458,15 +467,15 @@ bool gemv_exact_supported(int64_t M, int64_t N, int64_t K, int group)
 bool gemv_exact_pays(int64_t M, int64_t N, int64_t K, DqFormat format, bool in_chunks)
 {
     DqPlan p;
-    if (M < 3 || !make_dq_plan(M, N, K, p, true)) return false;
-    if (format == kDqFormatBf16) return M <= kGemvMaxM && p.wr * p.r == p.rb_base + (p.rb_rem > 0 ? 1 : 0);
-    return in_chunks && M <= kDqMaxM;
+    if (M < 3 || !gemv_exact_supported(M, N, K, 128, format) || !make_dq_plan(M, N, K, p, true)) return false;
+    if (format == kDqFormatBf16) return p.wr * p.r == p.rb_base + (p.rb_rem > 0 ? 1 : 0);
+    return in_chunks;
 }
 
 int launch_gemv_exact(const void* X, int64_t M, const void* packed, int64_t N, int64_t K, DqFormat format, void* Y, hipStream_t stream)
 {
     DqPlan p;
-    if (format == kDqFormatE8 || N <= 0 || !make_dq_plan(M, N, K, p, true)) return E0M4_ERR_SHAPE;
+    if (!gemv_exact_supported(M, N, K, 128, format) || !make_dq_plan(M, N, K, p, true)) return E0M4_ERR_SHAPE;
     if (format == kDqFormatBf16) return launch_dq_m<kDqFormatBf16, true>(p, X, M, packed, N, K, 128, Y, stream);
     return launch_dq_m<kDqFormatFp16, true>(p, X, M, packed, N, K, 128, Y, stream);
 }

@@ -101,9 +101,9 @@ bool gemv_dq_supported(int64_t M, int64_t N, int64_t K, int group);
 bool gemv_dq_pays(int64_t M, int64_t N, int64_t K, int group, DqFormat format);
 int launch_gemv_dq(const void* X, int64_t M, const void* packed, int64_t N, int64_t K, int group, DqFormat format, void* Y,
                    hipStream_t stream);
-// The same kernel on exact code values (4-bit codes, groups of 128).
+// The same kernel on exact code values (4-bit codes, groups of 128; bfloat16 of up to 8 rows, fp16 of 17 to 64).
 // (`pays`: it is expected to beat the kernels that have the call otherwise; `in_chunks`: launch_gemv_mfma in chunks would)
-bool gemv_exact_supported(int64_t M, int64_t N, int64_t K, int group);
+bool gemv_exact_supported(int64_t M, int64_t N, int64_t K, int group, DqFormat format);
 bool gemv_exact_pays(int64_t M, int64_t N, int64_t K, DqFormat format, bool in_chunks);
 int launch_gemv_exact(const void* X, int64_t M, const void* packed, int64_t N, int64_t K, DqFormat format, void* Y, hipStream_t stream);
 // INT4 twin of the M = 1 kernel: same layout and work decomposition, codes turned into numbers with

@@ -1,4 +1,4 @@
-"""The small-batch kernel on exact codes (groups of 128, 2 to 128 rows) against the oracle: last tiles of rows and columns, fewer k
+"""The small-batch kernel on exact codes (groups of 128; bfloat16 of 2 to 8 rows, fp16 of 17 to 64) against the oracle: last tiles of rows and columns, fewer k
 blocks than wavefronts, remainders of the unrolled loop, one to sixteen row blocks per workgroup, and calls that reach it by
 default."""
 import numpy as np
@@ -6,6 +6,7 @@ import pytest
 
 import synth_inputs
 from test_gpu_bf16_e0m3 import assert_bf16_quantize_exact, bf_bits, bf_dev, check_bf16_matmul
+from test_gpu_fused import check_fused
 from test_gpu_parity import assert_quantize_exact, check_matmul, e0m4, to_dev, torch  # noqa: F401
 
 pytestmark = pytest.mark.gpu
@@ -21,8 +22,7 @@ def forced(e0m4):
 
 # N, K, workgroups aimed at: 1, 2, 3 and 4 row blocks per wavefront, one, two and four groups of wavefronts
 @pytest.mark.parametrize("N,K,workgroups", [(17, 128, 0), (203, 1152, 0), (333, 2176, 12), (520, 1664, 4), (260, 640, 1), (1000, 4224, 9)])
-@pytest.mark.parametrize("M", [2, 4, 5, 8, 9, 16, 17, 33, 48, 49, 64, 65, 128])
-@pytest.mark.parametrize("fmt", ["e0m4", "bf16"])
+@pytest.mark.parametrize("fmt,M", [("bf16", M) for M in (2, 4, 5, 8)] + [("e0m4", M) for M in (17, 32, 33, 48, 49, 64)])
 def test_plain(e0m4, oracle, forced, fmt, M, N, K, workgroups):
     e0m4.e0m4_set_knob("gemv_workgroups", workgroups)
     if fmt == "bf16":
@@ -56,7 +56,7 @@ def test_default_choice(e0m4, oracle, M, N, K):
     assert N > 2000 or torch.equal(Y, Y2)
     Yref, absdot = oracle.matmul(X, What)
     check_matmul(Y, Yref, absdot, "M=%d" % M)
-    R = to_dev(synth_inputs.activations(M, N, seed=7600 + M))
-    YR = e0m4.e0m4_matmul_fused(to_dev(X), codes, N, K, 128, residual=R).float().cpu().numpy()
-    want = Yref.astype(np.float64) + R.cpu().numpy()
-    assert (np.abs(YR - want) <= 1e-2 * np.maximum(1.0, absdot) + 2.0 ** -10 * np.abs(want)).all()
+    R = synth_inputs.activations(M, N, seed=7600 + M)
+    YR = e0m4.e0m4_matmul_fused(to_dev(X), codes, N, K, 128, residual=to_dev(R))
+    YRref, info = oracle.matmul_fused(X, What, residual=R)
+    check_fused(YR, YRref, info, False, False, "residual M=%d" % M)
