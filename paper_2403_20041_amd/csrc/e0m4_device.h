@@ -252,6 +252,16 @@ __device__ inline __amdgpu_buffer_rsrc_t make_rsrc(const void* p)
     return __builtin_amdgcn_make_buffer_rsrc(q, 0, 0x7fffffff, 0x00020000);
 }
 
+// make_rsrc, or a resource of no bytes, whose loads return zeros without an access to memory (`in` is wavefront-uniform).
+__device__ inline __amdgpu_buffer_rsrc_t rsrc_if(const void* p, bool in)
+{
+    const uint64_t a = reinterpret_cast<uint64_t>(p);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
+    void* q = reinterpret_cast<void*>(((uint64_t)hi << 32) | lo);
+    return __builtin_amdgcn_make_buffer_rsrc(q, 0, __builtin_amdgcn_readfirstlane(in ? 0x7fffffff : 0), 0x00020000);
+}
+
 // Operators folded into the decode kernels (e0m4_matmul_fused; paper: section "Operator and lagging
 // optimizations", fusion of rms-norm and of element-wise operators into their neighbours):
 //   gamma    : the rows of X are rms-normalised while they are staged (x * rsqrt(mean x^2 + eps) * gamma,

@@ -439,73 +439,73 @@ __global__ __launch_bounds__(64 * WGM * WGN * KS, 2) void gemm_pipe_kernel(const
 
     // The K range on TMX of the wavefront's TM row blocks (all of them, but in a last row tile)
     auto k_loop = [&](auto tm_c) {
-    using IPA = std::integral_constant<int, SHORT ? decltype(tm_c)::value * 32 / RP : PA>;
-    // One K slice.  On entry: stage `cur` holds slice kt; fa[0], fb[0] hold its sub-step 0 operands;
-    // bset[set] holds its codes; the next PD - 1 slices' codes and the next AD slices' activations are in flight.
-    auto step = [&](int kt, int set, uint32_t cur, uint32_t nxt) {
-        // sub-step 0: operands of sub-step 1; publish slice kt+1's activations and, the staging
-        // registers being free again, request those of slice kt+1+AD at once
-        read_frags(tm_c, cur, 1, fa[1]);
-        dequant_frags(set, 1, fb[1]);
-        store_a(IPA{}, nxt, (set + 1) % AD);
-        load_a(IPA{}, kt + 1 + AD, (set + 1) % AD);
-        mfma_block(tm_c, fa[0], fb[0]);
-        interleave(tm_c, IPA{}, IPA{});
-        __builtin_amdgcn_sched_barrier(0);
-        // sub-step 1: operands of sub-step 2
-        read_frags(tm_c, cur, 2, fa[0]);
-        dequant_frags(set, 2, fb[0]);
-        mfma_block(tm_c, fa[1], fb[1]);
-        interleave(tm_c, I0{}, I0{});
-        __builtin_amdgcn_sched_barrier(0);
-        __syncthreads();                // slice kt+1 is complete in stage `nxt`
-        __builtin_amdgcn_sched_barrier(0);
-        // sub-step 2: operands of sub-step 3 (last use of this slice's codes)
-        read_frags(tm_c, cur, 3, fa[1]);
-        dequant_frags(set, 3, fb[1]);
-        mfma_block(tm_c, fa[0], fb[0]);
-        interleave(tm_c, I0{}, I0{});
-        __builtin_amdgcn_sched_barrier(0);
-        // sub-step 3: operands of the next slice's sub-step 0; this slice's code registers are free,
-        // so the codes of slice kt+PD are requested into them
-        load_b(kt + PD, set);
-        read_frags(tm_c, nxt, 0, fa[0]);
-        dequant_frags((set + 1) % PD, 0, fb[0]);
-        mfma_block(tm_c, fa[1], fb[1]);
-        interleave(tm_c, I0{}, ITN2{});
-        __builtin_amdgcn_sched_barrier(0);
-    };
+        using IPA = std::integral_constant<int, SHORT ? decltype(tm_c)::value * 32 / RP : PA>;
+        // One K slice.  On entry: stage `cur` holds slice kt; fa[0], fb[0] hold its sub-step 0 operands;
+        // bset[set] holds its codes; the next PD - 1 slices' codes and the next AD slices' activations are in flight.
+        auto step = [&](int kt, int set, uint32_t cur, uint32_t nxt) {
+            // sub-step 0: operands of sub-step 1; publish slice kt+1's activations and, the staging
+            // registers being free again, request those of slice kt+1+AD at once
+            read_frags(tm_c, cur, 1, fa[1]);
+            dequant_frags(set, 1, fb[1]);
+            store_a(IPA{}, nxt, (set + 1) % AD);
+            load_a(IPA{}, kt + 1 + AD, (set + 1) % AD);
+            mfma_block(tm_c, fa[0], fb[0]);
+            interleave(tm_c, IPA{}, IPA{});
+            __builtin_amdgcn_sched_barrier(0);
+            // sub-step 1: operands of sub-step 2
+            read_frags(tm_c, cur, 2, fa[0]);
+            dequant_frags(set, 2, fb[0]);
+            mfma_block(tm_c, fa[1], fb[1]);
+            interleave(tm_c, I0{}, I0{});
+            __builtin_amdgcn_sched_barrier(0);
+            __syncthreads();                // slice kt+1 is complete in stage `nxt`
+            __builtin_amdgcn_sched_barrier(0);
+            // sub-step 2: operands of sub-step 3 (last use of this slice's codes)
+            read_frags(tm_c, cur, 3, fa[1]);
+            dequant_frags(set, 3, fb[1]);
+            mfma_block(tm_c, fa[0], fb[0]);
+            interleave(tm_c, I0{}, I0{});
+            __builtin_amdgcn_sched_barrier(0);
+            // sub-step 3: operands of the next slice's sub-step 0; this slice's code registers are free,
+            // so the codes of slice kt+PD are requested into them
+            load_b(kt + PD, set);
+            read_frags(tm_c, nxt, 0, fa[0]);
+            dequant_frags((set + 1) % PD, 0, fb[0]);
+            mfma_block(tm_c, fa[1], fb[1]);
+            interleave(tm_c, I0{}, ITN2{});
+            __builtin_amdgcn_sched_barrier(0);
+        };
 
-    // ---- prologue
-    load_a(IPA{}, kt_begin, 0);
+        // ---- prologue
+        load_a(IPA{}, kt_begin, 0);
 #pragma unroll
-    for (int d = 0; d < PD; ++d) load_b(kt_begin + d, d);
-    const uint32_t ring = KS == 2 ? (uint32_t)half * kStages * kStageBytes : 0u;
-    store_a(IPA{}, ring, 0);
+        for (int d = 0; d < PD; ++d) load_b(kt_begin + d, d);
+        const uint32_t ring = KS == 2 ? (uint32_t)half * kStages * kStageBytes : 0u;
+        store_a(IPA{}, ring, 0);
 #pragma unroll
-    for (int d = 1; d <= AD; ++d) load_a(IPA{}, kt_begin + d, d % AD);
-    __syncthreads();
-    read_frags(tm_c, ring, 0, fa[0]);
-    dequant_frags(0, 0, fb[0]);
+        for (int d = 1; d <= AD; ++d) load_a(IPA{}, kt_begin + d, d % AD);
+        __syncthreads();
+        read_frags(tm_c, ring, 0, fa[0]);
+        dequant_frags(0, 0, fb[0]);
 
-    uint32_t s0 = ring, s1 = ring + kStageBytes, s2 = ring + 2 * kStageBytes;     // current, next, the one after
-    auto advance_ring = [&]() {                         // by two slices
-        const uint32_t tmp = s0;
-        s0 = s2;
-        s2 = s1;
-        s1 = tmp;
-    };
-    for (int kt = kt_begin; kt < kt_end; kt += PD) {
-        step(kt, 0, s0, s1);
-        step(kt + 1, 1, s1, s2);
-        advance_ring();
-        if (PD == 4) {                                  // (K ranges are whole pairs of slices)
-            if (kt + 2 >= kt_end) break;
-            step(kt + 2, 2 % PD, s0, s1);
-            step(kt + 3, 3 % PD, s1, s2);
+        uint32_t s0 = ring, s1 = ring + kStageBytes, s2 = ring + 2 * kStageBytes;     // current, next, the one after
+        auto advance_ring = [&]() {                         // by two slices
+            const uint32_t tmp = s0;
+            s0 = s2;
+            s2 = s1;
+            s1 = tmp;
+        };
+        for (int kt = kt_begin; kt < kt_end; kt += PD) {
+            step(kt, 0, s0, s1);
+            step(kt + 1, 1, s1, s2);
             advance_ring();
+            if (PD == 4) {                                  // (K ranges are whole pairs of slices)
+                if (kt + 2 >= kt_end) break;
+                step(kt + 2, 2 % PD, s0, s1);
+                step(kt + 3, 3 % PD, s1, s2);
+                advance_ring();
+            }
         }
-    }
     };
     if constexpr (SHORT) {
         static_assert(PA * RP == TM * 32, "a loader pass is whole row blocks");
@@ -1082,7 +1082,8 @@ int launch_pipe(const half_t* x, int64_t M, const uint4* c, int64_t N, int64_t K
     }
     SkArgs sk{0, 0, 0, 0, nullptr, nullptr};
     unsigned grid = (unsigned)(per_xcd * kNumXcd);
-    const bool last_short = BM == 128 && BN == 256 && splits == 1 && m_tiles > 1 && m_tiles <= kShortMaxTiles && tiles >= kComputeUnits && M % BM != 0 && M % BM <= 64;
+    const bool last_short = BM == 128 && BN == 256 && splits == 1 && m_tiles > 1 && m_tiles <= kShortMaxTiles &&
+                            tiles >= kComputeUnits && M % BM != 0 && M % BM <= 64;
     if (last_short) grid = (unsigned)((((m_tiles - 1) * n_tiles + kNumXcd - 1) / kNumXcd + (n_tiles + kNumXcd - 1) / kNumXcd) * kNumXcd);
     if (skp.on) {
         if (workspace == nullptr || workspace_bytes < skp.workspace_bytes) return E0M4_ERR_WORKSPACE;

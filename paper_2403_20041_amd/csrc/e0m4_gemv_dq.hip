@@ -39,7 +39,8 @@ typedef float floatx2 __attribute__((ext_vector_type(2)));
 constexpr int kDqWaves = 8;
 constexpr int kDqThreads = kDqWaves * 64;
 constexpr int kDqMaxR = 4;                      // row blocks per wavefront
-constexpr int kDqMaxSlots = 16;                 // row blocks per workgroup (so that two wavefronts at least share a row block; one, with R at most two)
+// row blocks per workgroup (so that two wavefronts at least share a row block; one, where R is two at most)
+constexpr int kDqMaxSlots = 16;
 constexpr int kDqMaxM = 64;                     // rows of X per workgroup
 constexpr int kDqMaxParts = 2;
 constexpr int kTargetWorkgroups = 256;          // one workgroup per compute unit
@@ -54,16 +55,6 @@ struct DqPlan {
 __device__ inline half2_t dq_pair(half2_t w1, half2_t bias2, half2_t scale2)
 {
     return (w1 - bias2) * scale2;               // difference exact, product rounded once
-}
-
-// make_rsrc, or a resource of no bytes, whose loads return zeros (`in` is wavefront-uniform)
-__device__ inline __amdgpu_buffer_rsrc_t rsrc_if(const void* p, bool in)
-{
-    const uint64_t a = reinterpret_cast<uint64_t>(p);
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a);
-    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
-    void* q = reinterpret_cast<void*>(((uint64_t)hi << 32) | lo);
-    return __builtin_amdgcn_make_buffer_rsrc(q, 0, __builtin_amdgcn_readfirstlane(in ? 0x7fffffff : 0), 0x00020000);
 }
 
 // XE: loads of X per tile and k block.  A load brings a quarter of the tile's rows (8-bit codes: half); calls of up to 4 and 8

@@ -36,9 +36,9 @@ constexpr int kZeroBytes = 64;                  // several groups per block: the
 constexpr int kItemXBytes = 16 * kBlockK * 2;   // sixteen rows of a k block (8-bit codes: half of that)
 
 // XE: loads of X per k block, four rows each (calls of up to 4 and 8 rows make one and two; the other rows of the tile stay
-// what LDS held, and so do their sums, which nobody stores; 8-bit codes: eight rows a load).  R: row blocks per workgroup.  GS: groups per k block; a row of X
-// is then GS rows of the MFMA, with zeros for the k-groups of the other groups.  E8: 8-bit codes, k blocks of 64 weights, a single
-// kind of code slot.  `residual` may be Y: neither is declared free of aliases.
+// what LDS held, and so do their sums, which nobody stores; 8-bit codes: eight rows a load).  R: row blocks per workgroup.
+// GS: groups per k block; a row of X is then GS rows of the MFMA, with zeros for the k-groups of the other groups.  E8: 8-bit codes,
+// k blocks of 64 weights, a single kind of code slot.  `residual` may be Y: neither is declared free of aliases.
 template <int XE, int R, int GS, bool E8>
 __global__ __launch_bounds__(kItemThreads, 2) void gemv_items_kernel(const half_t* __restrict__ X, const uint4* __restrict__ packed,
                                                                      half_t* Y, const half_t* residual,
@@ -80,7 +80,8 @@ __global__ __launch_bounds__(kItemThreads, 2) void gemv_items_kernel(const half_
         x_voff[e] = ((uint32_t)min(row, M - 1) * K32 + (uint32_t)(x_j * 8)) * 2;
 #pragma unroll
         for (int hl = 0; hl < 2; ++hl)
-            x_wr[e][hl] = E8 ? (uint32_t)(row * ROWB + ((x_j ^ ((row >> 1) & 7)) << 4)) : (uint32_t)(row * ROWB + (((x_q * 4 + (x_w >> 1) * 2 + hl) ^ row) << 4) + ((x_w & 1) << 3));
+            x_wr[e][hl] = (uint32_t)(row * ROWB) + (uint32_t)(E8 ? (x_j ^ ((row >> 1) & 7)) << 4
+                                                                 : (((x_q * 4 + (x_w >> 1) * 2 + hl) ^ row) << 4) + ((x_w & 1) << 3));
     }
 #pragma unroll
     for (int wp = 0; wp < 2; ++wp)
@@ -96,13 +97,6 @@ __global__ __launch_bounds__(kItemThreads, 2) void gemv_items_kernel(const half_
     }
 
     // (a k block beyond the last is requested through a resource of no bytes: zeros, without an access to memory)
-    auto rsrc_if = [](const void* p, bool in) -> __amdgpu_buffer_rsrc_t {
-        const uint64_t a = reinterpret_cast<uint64_t>(p);
-        const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a);
-        const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
-        void* q = reinterpret_cast<void*>(((uint64_t)hi << 32) | lo);
-        return __builtin_amdgcn_make_buffer_rsrc(q, 0, __builtin_amdgcn_readfirstlane(in ? 0x7fffffff : 0), 0x00020000);
-    };
     u32x4 c[kItemBlocks][R], xr[2][XE];
     uint32_t pw[kItemBlocks][R];
     const uint32_t param_voff = (uint32_t)nkb * kBlockCodeBytes + 4 * ((g_l * GS / 4) * kBlockRows + n_l);
@@ -111,7 +105,8 @@ __global__ __launch_bounds__(kItemThreads, 2) void gemv_items_kernel(const half_
 #pragma unroll
         for (int s = 0; s < R; ++s) {
             c[d][s] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane * 16, (int)(s * rb_next + (uint32_t)kb * kBlockCodeBytes), 0);
-            pw[d][s] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)param_voff, (int)(s * rb_next + (uint32_t)kb * (4 * kBlockRows * GS)), 0);
+            pw[d][s] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)param_voff,
+                                                            (int)(s * rb_next + (uint32_t)kb * (4 * kBlockRows * GS)), 0);
         }
     };
     auto load_x = [&](int kb, int d) {
@@ -120,8 +115,9 @@ __global__ __launch_bounds__(kItemThreads, 2) void gemv_items_kernel(const half_
         for (int e = 0; e < XE; ++e) xr[d][e] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)x_voff[e], kb * ROWB, 0);
     };
     // Units in the order u = p * units_ph + r, dealt round the wavefronts; where that gives a wavefront the same units of every
-    // phase, `turn` on from phase to phase, the number of units with one item more than the others.  Item i of phase p is item p * items_ph + i of all.  Past the last unit (in a last
-    // phase of fewer items than units_ph, too) the item is one without k blocks.
+    // phase, `turn` on from phase to phase, the number of units with one item more than the others.  Item i of phase p is item
+    // p * items_ph + i of all.  Past the last unit (in a last phase of fewer items than units_ph, too) the item is one without
+    // k blocks.
     struct Place {
         int ph, r, i;
     };
@@ -157,7 +153,9 @@ __global__ __launch_bounds__(kItemThreads, 2) void gemv_items_kernel(const half_
     const floatx4 zero4 = {0.f, 0.f, 0.f, 0.f};
     const half_t one = (half_t)1.f;
     const half8_t ones8 = {one, one, one, one, one, one, one, one};
-    auto mfma = [](const half8_t& a, const half8_t& b, const floatx4& v) -> floatx4 { return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, v, 0, 0, 0); };
+    auto mfma = [](const half8_t& a, const half8_t& b, const floatx4& v) -> floatx4 {
+        return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, v, 0, 0, 0);
+    };
     floatx4 ysum[R];
 #pragma unroll
     for (int s = 0; s < R; ++s) ysum[s] = zero4;
@@ -194,37 +192,37 @@ __global__ __launch_bounds__(kItemThreads, 2) void gemv_items_kernel(const half_
             const floatx4 sx = sh + sl, sx30 = 30.f * sl;
 #pragma unroll
             for (int s = 0; s < R; ++s) {
-            half2_t p[4][4];
+                half2_t p[4][4];
 #pragma unroll
-            for (int w = 0; w < 4; ++w) {
-                if (E8) {                               // (w1_0, w1_1) and, after the rotation, (w1_2, w1_3)
-                    const uint32_t m8 = fmask | fmask_low, word = c[j][s][w];
-                    p[w][0] = __builtin_bit_cast(half2_t, (word & m8) | kExpBits2);
-                    p[w][1] = __builtin_bit_cast(half2_t, (__builtin_amdgcn_alignbit(word, word, 8) & m8) | kExpBits2);
-                } else {
-                    w1_pairs_mixed(c[j][s][w], fmask, fmask_low, p[w]);
+                for (int w = 0; w < 4; ++w) {
+                    if (E8) {                               // (w1_0, w1_1) and, after the rotation, (w1_2, w1_3)
+                        const uint32_t m8 = fmask | fmask_low, word = c[j][s][w];
+                        p[w][0] = __builtin_bit_cast(half2_t, (word & m8) | kExpBits2);
+                        p[w][1] = __builtin_bit_cast(half2_t, (__builtin_amdgcn_alignbit(word, word, 8) & m8) | kExpBits2);
+                    } else {
+                        w1_pairs_mixed(c[j][s][w], fmask, fmask_low, p[w]);
+                    }
                 }
-            }
-            const float sc = (float)param_scale(pw[j][s]);
-            const float bi = (float)param_bias(pw[j][s]);
-            floatx4 acc_h = zero4, acc_l = zero4;
+                const float sc = (float)param_scale(pw[j][s]);
+                const float bi = (float)param_bias(pw[j][s]);
+                floatx4 acc_h = zero4, acc_l = zero4;
 #pragma unroll
-            for (int wp = 0; wp < 2; ++wp) {
-                const half2_t* w0 = p[2 * wp];
-                const half2_t* w1 = p[2 * wp + 1];
-                if (E8) {
-                    const half8_t w8 = {w0[0][0], w0[0][1], w0[1][0], w0[1][1], w1[0][0], w1[0][1], w1[1][0], w1[1][1]};
-                    acc_h = mfma(xh[wp], w8, acc_h);
-                    continue;
+                for (int wp = 0; wp < 2; ++wp) {
+                    const half2_t* w0 = p[2 * wp];
+                    const half2_t* w1 = p[2 * wp + 1];
+                    if (E8) {
+                        const half8_t w8 = {w0[0][0], w0[0][1], w0[1][0], w0[1][1], w1[0][0], w1[0][1], w1[1][0], w1[1][1]};
+                        acc_h = mfma(xh[wp], w8, acc_h);
+                        continue;
+                    }
+                    const half8_t wh = {w0[0][0], w0[0][1], w0[3][0], w0[3][1], w1[0][0], w1[0][1], w1[3][0], w1[3][1]};
+                    const half8_t wl = {w0[1][0], w0[1][1], w0[2][0], w0[2][1], w1[1][0], w1[1][1], w1[2][0], w1[2][1]};
+                    acc_h = mfma(xh[wp], wh, acc_h);
+                    acc_l = mfma(xs[wp], wl, acc_l);
                 }
-                const half8_t wh = {w0[0][0], w0[0][1], w0[3][0], w0[3][1], w1[0][0], w1[0][1], w1[3][0], w1[3][1]};
-                const half8_t wl = {w0[1][0], w0[1][1], w0[2][0], w0[2][1], w1[1][0], w1[1][1], w1[2][0], w1[2][1]};
-                acc_h = mfma(xh[wp], wh, acc_h);
-                acc_l = mfma(xs[wp], wl, acc_l);
-            }
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
-                ysum[s][r] += sc * ((acc_h[r] + 16.f * acc_l[r] - sx30[r]) - bi * sx[r]);
+                for (int r = 0; r < 4; ++r)
+                    ysum[s][r] += sc * ((acc_h[r] + 16.f * acc_l[r] - sx30[r]) - bi * sx[r]);
             }
             load_w(kb_next + j, j);
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -294,7 +292,8 @@ int launch_items(const ItemsPlan& p, const half_t* X, int64_t M, const uint4* pa
     constexpr int kFixed = (GS > 1 ? kZeroBytes : 0) + kItemWaves * kItemXBytes, kSum = 16 * kBlockRows * (int)sizeof(float);
     const int lds = kFixed + order_units(K, p.items_ph, p.waves) * R * kSum;
     static std::atomic<uint64_t> lds_allowed{0};
-    const int arc = allow_dynamic_lds(reinterpret_cast<const void*>(&gemv_items_kernel<XE, R, GS, E8>), kFixed + kMaxSums * kSum, lds_allowed);
+    const int arc = allow_dynamic_lds(reinterpret_cast<const void*>(&gemv_items_kernel<XE, R, GS, E8>), kFixed + kMaxSums * kSum,
+                                      lds_allowed);
     if (arc != E0M4_OK) return arc;
     hipLaunchKernelGGL((gemv_items_kernel<XE, R, GS, E8>), dim3((unsigned)p.grid), dim3(kItemThreads), lds, stream, X, packed, Y, residual,
                        (int)M, (uint32_t)N, (uint32_t)(E8 ? K / 2 : K), p.rb_base, p.rb_rem, p.waves, p.items_ph);
@@ -305,9 +304,15 @@ template <int R>
 int launch_items_m(const ItemsPlan& p, const half_t* x, int64_t M, const uint4* c, int64_t N, int64_t K, int group, half_t* y,
                    const half_t* r, hipStream_t stream)
 {
-    if (p.e8) return M <= 8 ? launch_items<1, R, 1, true>(p, x, M, c, N, K, y, r, stream) : launch_items<2, R, 1, true>(p, x, M, c, N, K, y, r, stream);
+    if (p.e8) {
+        if (M <= 8) return launch_items<1, R, 1, true>(p, x, M, c, N, K, y, r, stream);
+        return launch_items<2, R, 1, true>(p, x, M, c, N, K, y, r, stream);
+    }
     if (group == 32) return launch_items<1, R, 4>(p, x, M, c, N, K, y, r, stream);
-    if (group == 64) return M <= 4 ? launch_items<1, R, 2>(p, x, M, c, N, K, y, r, stream) : launch_items<2, R, 2>(p, x, M, c, N, K, y, r, stream);
+    if (group == 64) {
+        if (M <= 4) return launch_items<1, R, 2>(p, x, M, c, N, K, y, r, stream);
+        return launch_items<2, R, 2>(p, x, M, c, N, K, y, r, stream);
+    }
     if (M <= 4) return launch_items<1, R, 1>(p, x, M, c, N, K, y, r, stream);
     if (M <= 8) return launch_items<2, R, 1>(p, x, M, c, N, K, y, r, stream);
     return launch_items<4, R, 1>(p, x, M, c, N, K, y, r, stream);
@@ -317,7 +322,8 @@ int launch_items_m(const ItemsPlan& p, const half_t* x, int64_t M, const uint4* 
 
 bool gemv_items_supported(const ItemsPlan& p, int64_t M, int64_t N, int64_t K, int group)
 {
-    if (M < 2 || M > 16 * group / 128 || N <= 0 || K <= 0 || K % kBlockK != 0 || p.items_ph <= 0 || (p.waves != 8 && p.waves != 16)) return false;
+    if (M < 2 || M > 16 * group / 128 || N <= 0 || K <= 0 || K % kBlockK != 0) return false;
+    if (p.items_ph <= 0 || (p.waves != 8 && p.waves != 16)) return false;
     const int most = p.rb_base + (p.rb_rem > 0 ? 1 : 0);
     return p.rb_base >= 1 && most <= 2 && order_units(K, p.items_ph, p.waves) * most <= kMaxSums;
 }

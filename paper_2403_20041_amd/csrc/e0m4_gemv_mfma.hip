@@ -51,6 +51,7 @@ namespace {
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+__device__ inline bf16x8_t as_bf16x8(half8_t v) { return __builtin_bit_cast(bf16x8_t, v); }
 
 constexpr int kSuper = 4;                       // weight blocks (of 128 k) per work item
 constexpr int kG = 128;                         // group size: one group per block
@@ -111,7 +112,8 @@ __device__ inline int x_unit_off(int q, int w, int hl) { return ((q * 4 + (w >> 
 // KEEP: with an rms-norm, X stays in registers from the pass over its squares (keeps_x below).
 // BF: 4-bit codes on bfloat16 (no fused operators).  Brought to fraction bits 6..3 by one shift or rotation per pair, all eight
 // codes of a word read 2 + c/8, so one MFMA takes one word and X as it lies in memory, and a block needs the plain sum of X only.
-template <int W, bool FUSED, bool XREG, bool E8 = false, bool PHASED = false, int GS = 1, bool KEEP = false, bool BF = false, bool XF = false>
+template <int W, bool FUSED, bool XREG, bool E8 = false, bool PHASED = false, int GS = 1, bool KEEP = false, bool BF = false,
+          bool XF = false>
 __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restrict__ X,
                                                            const uint4* __restrict__ packed, half_t* __restrict__ Y,
                                                            int M, uint32_t N32, uint32_t K32, int step_slots_arg,
@@ -464,7 +466,8 @@ __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restr
                     const int idx = i0 + u * 64 + lane;
                     const int m = idx / kItemPieces, pc = si * kItemPieces + idx % kItemPieces;
                     vb[u] = zero8;
-                    if (m < M && pc < pieces && (int64_t)pc * 8 < K) vb[u] = *reinterpret_cast<const half8_t*>(X + (int64_t)m * K + (int64_t)pc * 8);
+                    if (m < M && pc < pieces && (int64_t)pc * 8 < K)
+                        vb[u] = *reinterpret_cast<const half8_t*>(X + (int64_t)m * K + (int64_t)pc * 8);
                 }
                 if constexpr (decltype(first_c)::value) first_item();
 #pragma unroll
@@ -512,7 +515,8 @@ __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restr
                 if (normed) batch(0, std::false_type{});
                 else batch(0, std::true_type{});
             }
-            for (int base = XF ? kStageBatch * kThreads : 0; base < M * ph_pieces; base += kStageBatch * kThreads) batch(base, std::false_type{});
+            for (int base = XF ? kStageBatch * kThreads : 0; base < M * ph_pieces; base += kStageBatch * kThreads)
+                batch(base, std::false_type{});
             __syncthreads();
         }
 
@@ -546,8 +550,8 @@ __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restr
 #pragma unroll
             for (int wp = 0; wp < 2; ++wp) {
                 if constexpr (BF) {
-                    sh = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, xh[wp]), __builtin_bit_cast(bf16x8_t, ones8), sh, 0, 0, 0);
-                    sl = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, xl[wp]), __builtin_bit_cast(bf16x8_t, ones8), sl, 0, 0, 0);
+                    sh = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(xh[wp]), as_bf16x8(ones8), sh, 0, 0, 0);
+                    sl = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(xl[wp]), as_bf16x8(ones8), sl, 0, 0, 0);
                 } else {
                     sh = __builtin_amdgcn_mfma_f32_16x16x32_f16(xh[wp], ones8, sh, 0, 0, 0);
                     if (!E8) sl = __builtin_amdgcn_mfma_f32_16x16x32_f16(xl[wp], ones8, sl, 0, 0, 0);
@@ -575,7 +579,8 @@ __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restr
                 fetch_params(nph, nslot, nitem);
 #pragma unroll
                 for (int j = 0; j < kSuper; ++j) {
-                    const int kb = si * kSuper + j;         // (inside the phase) may lie beyond K in the last item: such a block is left out below
+                    // (inside the phase; may lie beyond K in the last item: such a block is left out below)
+                    const int kb = si * kSuper + j;
                     const float sc = BF ? __builtin_bit_cast(float, pwj[j] << 16) : (float)param_scale(pwj[j]);
                     const float bi = BF ? __builtin_bit_cast(float, pwj[j] & 0xFFFF0000u) : (float)param_bias(pwj[j]);
                     const uint32_t words[4] = {c[j].x, c[j].y, c[j].z, c[j].w};
@@ -619,8 +624,8 @@ __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restr
                         if (BF) {
                             const half8_t wa = {w0[0][0], w0[0][1], w0[1][0], w0[1][1], w0[2][0], w0[2][1], w0[3][0], w0[3][1]};
                             const half8_t wb = {w1[0][0], w1[0][1], w1[1][0], w1[1][1], w1[2][0], w1[2][1], w1[3][0], w1[3][1]};
-                            acc_h = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, xh), __builtin_bit_cast(bf16x8_t, wa), acc_h, 0, 0, 0);
-                            acc_l = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, xl), __builtin_bit_cast(bf16x8_t, wb), acc_l, 0, 0, 0);
+                            acc_h = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(xh), as_bf16x8(wa), acc_h, 0, 0, 0);
+                            acc_l = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(xl), as_bf16x8(wb), acc_l, 0, 0, 0);
                             continue;
                         }
                         const half8_t wh = {w0[0][0], w0[0][1], w0[3][0], w0[3][1], w1[0][0], w1[0][1], w1[3][0], w1[3][1]};
@@ -743,7 +748,8 @@ bool make_phased_plan(int64_t M, int64_t mfma_rows, int64_t nrb, int64_t nkb, Mf
     const int64_t nsi = (nkb + kSuper - 1) / kSuper;
     const size_t xbb = e8 ? kXBlockBytes / 2 : kXBlockBytes;
     auto plan = [&](int w) -> bool {
-        int64_t most = (nrb + std::min<int64_t>(nrb, target) - 1) / std::min<int64_t>(nrb, target);    // row blocks (or pairs) of a workgroup
+        // row blocks (or pairs) of a workgroup
+        int64_t most = (nrb + std::min<int64_t>(nrb, target) - 1) / std::min<int64_t>(nrb, target);
         const size_t per_item = (size_t)mfma_rows * kSuper * xbb, other = kNormBytes + (size_t)mfma_rows * kRowPadBytes;
         const size_t min_x = other + (size_t)std::min<int64_t>(kPhasedMinItems, nsi) * per_item;
         const size_t room = (size_t)kLdsLimitBytes > min_x ? (size_t)kLdsLimitBytes - min_x : 0;    // for the sums
@@ -985,7 +991,8 @@ int launch_mfma_bf16(const MfmaPlan& p, const void* X, int64_t M, const void* pa
     return launch_mfma_keep<W, false, false, false, false, GS, false, true>(p, X, M, packed, N, K, Y, stream, fu);
 }
 template <int GS>
-int launch_mfma_bf16_waves(const MfmaPlan& p, const void* X, int64_t M, const void* packed, int64_t N, int64_t K, void* Y, hipStream_t stream)
+int launch_mfma_bf16_waves(const MfmaPlan& p, const void* X, int64_t M, const void* packed, int64_t N, int64_t K, void* Y,
+                           hipStream_t stream)
 {
     switch (p.waves) {
         case 4: return launch_mfma_bf16<4, GS>(p, X, M, packed, N, K, Y, stream);
@@ -1013,8 +1020,8 @@ int64_t chunk_rows(int64_t M, int chunks) { return (M + chunks - 1) / chunks; }
 
 // Groups of 64 and 32: where this kernel (or e0m4_gemv_items.hip for it) takes plain calls from the kernel with dequantised
 // operands (e0m4_gemv_dq.hip): with several row blocks per workgroup, or (group 64) K in one phase.  15360 x 5120 at M = 4 12.4
-// us, 27392 x 5120 at M = 8 22.6, 5120 x 5120 at M = 4 7.5.  It works with unrounded weights, the other kernel with weights rounded to fp16: the line stays where it is, also where
-// the other kernel is by now the faster one.  At M = 2 the vector kernel is as fast or faster.
+// us, 27392 x 5120 at M = 8 22.6, 5120 x 5120 at M = 4 7.5.  It works with unrounded weights, the other kernel with weights rounded
+// to fp16: the line stays where it is, also where the other kernel is by now the faster one.  At M = 2 the vector kernel is as fast or faster.
 bool gemv_mfma_groups_pay(int64_t M, int64_t N, int64_t K, int group)
 {
     const int gs = groups_per_block(group);
@@ -1057,7 +1064,8 @@ int launch_mfma8(const MfmaPlan& p, const GemvFusion& fu, const void* X, int64_t
     const int items = (int)((k_blocks(2 * K) + kSuper - 1) / kSuper);
     const ItemsPlan ip{p.grid, p.rb_base, p.rb_rem, p.waves, p.kb_phase > 0 ? p.kb_phase / kSuper : items, p.kb_phase > 0, true};
     if (!fu.gamma && !fu.swiglu && fu.m_total == 0 && (p.kb_phase > 0 || p.step_item != 0) && knob("gemv_mfma") != 2 &&
-        knob("gemv_mfma") != 3 && gemv_items_supported(ip, M, N, 2 * K, 128) && (knob("gemv_mfma") == 9 || gemv_items_pays(ip, M, 128, FUSED)))
+        knob("gemv_mfma") != 3 && gemv_items_supported(ip, M, N, 2 * K, 128) &&
+        (knob("gemv_mfma") == 9 || gemv_items_pays(ip, M, 128, FUSED)))
         return launch_gemv_items(ip, X, M, packed, N, 2 * K, 128, Y, fu.residual, stream);
     if (p.kb_phase > 0)
         return p.waves == 8 ? launch_mfma_phased<8, FUSED, true>(p, X, M, packed, N, K, Y, stream, fu)
