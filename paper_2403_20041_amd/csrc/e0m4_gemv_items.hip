@@ -333,20 +333,22 @@ bool gemv_items_supported(const ItemsPlan& p, int64_t M, int64_t N, int64_t K, i
 // format and row count).  From three rows on:
 //   K in phases: 0.57 - 0.95.  But 8-bit codes with two row blocks and sixteen wavefronts lie between 0.84 and 1.12, above one where
 //     workgroups leave a good part of the compute units idle (4416 x 12416 at M = 9 1.10).
-//   Whole rows, one row block: 0.68 - 0.97 with eight wavefronts.  With sixteen, X is staged in half the time: 4-bit codes 1.00 -
-//     1.08 at three rows (fused 0.90 - 1.00) and 0.90 - 0.98 at four, 8-bit codes 0.94 - 1.06 at six (fused 0.89 - 1.03), 1.0 - 1.17
-//     below, 0.91 - 1.0 from eight on.
+//   Whole rows, one row block: 0.68 - 0.97 with eight wavefronts.  With sixteen, X is staged in half the time: 4-bit codes 0.94 -
+//     1.08 at three rows (fused 0.90 - 1.00) and 0.90 - 0.98 at four; 8-bit codes plain 0.96 - 1.17 up to six rows, 0.91 - 1.03 from
+//     eight on, fused 0.89 - 1.03 from six on and, where three quarters of the compute units have a workgroup, from three (0.92 -
+//     1.03; 4096 x 13696 at M = 3 15.6 and 15.3 us, but 2048 x 16384 12.7 and 14.1).
 //   Whole rows, two row blocks share what is staged: fused 0.80 - 1.05 with eight wavefronts (0.94 on average), plain 1.0 - 1.15
 //     (5120 x 5120 at M = 4 7.1 and 7.4 us, 8-bit at M = 12 10.1 and 11.2), but 0.88 - 0.98 where X is too large for sixteen
 //     wavefronts' sums beside it, and with thirteen rows or more in 4-bit codes; with sixteen wavefronts 1.0 - 1.15.
 // Groups of 64 and 32: plain calls with two row blocks 0.97 - 1.12, everything else 0.67 - 0.98.
-constexpr int64_t kPhased8MinGrid = 192;
+constexpr int64_t kBusyGrid8 = 192;
 bool gemv_items_pays(const ItemsPlan& p, int64_t M, int group, bool fused)
 {
     const bool two = p.rb_base + (p.rb_rem > 0 ? 1 : 0) > 1;
     if (group == 128 && M < 3) return false;
-    if (p.phased) return !(p.e8 && two && p.waves == 16) || p.grid >= kPhased8MinGrid;
-    if (!two) return p.waves == 8 || M >= (p.e8 ? (fused ? 6 : 8) : (fused ? 3 : 4));
+    if (p.phased) return !(p.e8 && two && p.waves == 16) || p.grid >= kBusyGrid8;
+    if (!two && p.waves == 16) return p.e8 ? (fused ? M >= 6 || p.grid >= kBusyGrid8 : M >= 8) : M >= (fused ? 3 : 4);
+    if (!two) return true;
     return p.waves == 8 && (fused || p.items_ph > 16 || (!p.e8 && M > 12));
 }
 
