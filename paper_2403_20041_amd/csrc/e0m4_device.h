@@ -269,7 +269,8 @@ __device__ inline __amdgpu_buffer_rsrc_t rsrc_if(const void* p, bool in)
 //   swiglu   : weight row j (gate) is paired with row N/2 + j (up) and Y[m, j] = silu(gate) * up; a
 //              workgroup then owns pairs of row blocks, slot 2p the gate block and slot 2p + 1 the up block
 //              of pair p, `half_bytes` apart in the packed buffer;
-//   residual : added to the result before its one rounding.
+//   residual : added to the result before its one rounding.  It may be Y (an element is read and written by one thread), so the
+//              kernels that take one declare neither free of aliases.
 struct GemvFusion {
     const half_t* gamma;
     const half_t* residual;

@@ -46,6 +46,7 @@ __device__ inline int tile_off(int row, int piece) { return row * kRowBytes + ((
 // Epilogue operators of e0m4_matmul_fused (FUSED).  Gated: the tile covers BN/2 output columns; of the
 // two 32-row operand blocks of a wavefront the first holds gate rows o .. o+31 and the second the up rows
 // N/2 + o .. N/2 + o+31, and the lane that holds both values of an output element writes silu(gate) * up.
+// (The residual may be Y, so neither is declared free of aliases.)
 struct TileFusion {
     const half_t* residual;
     int swiglu;
@@ -65,7 +66,7 @@ __device__ inline uint32_t bf16_pair_bits(float lo, float hi)     // two fp32 ->
 template <int G, int BM, int BN, bool FUSED, bool BF = false>
 __global__ __launch_bounds__(kThreads) void gemm_kernel(const half_t* __restrict__ X, int64_t M,
                                                         const uint4* __restrict__ packed, int64_t N, int64_t K,
-                                                        half_t* __restrict__ Y, int m_tiles, int n_tiles, TileFusion fu)
+                                                        half_t* Y, int m_tiles, int n_tiles, TileFusion fu)
 {
     constexpr int TM = BM / 64, TN = BN / 64;           // 32x32 MFMA blocks per wavefront along m and n
     constexpr int PA = BM / 32, PB = BN / 128;          // loader passes
@@ -231,7 +232,7 @@ __global__ __launch_bounds__(kThreads) void gemm_kernel(const half_t* __restrict
 
     // accumulator layout of a 32x32 block: register r of lane l is row 8*(r/4) + 4*(l/32) + r%4, column l%32
     // (tile-local offsets fit 32 bits: at most 256 rows of N elements)
-    half_t* __restrict__ Yt = Y + m0 * N + n0;
+    half_t* Yt = Y + m0 * N + n0;
     const uint32_t n32 = (uint32_t)N;
     const int rows_left = (int)min((int64_t)BM, M - m0), cols_left = (int)min((int64_t)BN, N - n0);
     const int row0 = wm + 4 * (lane >> 5), col0 = wn + (lane & 31);
@@ -241,8 +242,8 @@ __global__ __launch_bounds__(kThreads) void gemm_kernel(const half_t* __restrict
             const int ocols_left = (int)min((int64_t)(BN / 2), fu.n_half - n0);
             const int ocol = (wave & 1) * 32 + (lane & 31);
             const uint32_t nh32 = (uint32_t)fu.n_half;
-            half_t* __restrict__ yt = Y + m0 * fu.n_half + n0;
-            const half_t* __restrict__ rt = fu.residual ? fu.residual + m0 * fu.n_half + n0 : nullptr;
+            half_t* yt = Y + m0 * fu.n_half + n0;
+            const half_t* rt = fu.residual ? fu.residual + m0 * fu.n_half + n0 : nullptr;
             const uint32_t o0 = (uint32_t)row0 * nh32 + (uint32_t)ocol;
             if (ocol < ocols_left) {
 #pragma unroll
@@ -260,7 +261,7 @@ __global__ __launch_bounds__(kThreads) void gemm_kernel(const half_t* __restrict
             return;
         }
         if (fu.residual) {
-            const half_t* __restrict__ rt = fu.residual + m0 * N + n0;
+            const half_t* rt = fu.residual + m0 * N + n0;
 #pragma unroll
             for (int j = 0; j < TN; ++j) {
                 if (col0 + 32 * j < cols_left) {

@@ -63,7 +63,8 @@ __device__ inline T out_value(float v)                 // one rounding to the ou
 // epilogue a tile covers 128 output columns: the first operand block of a wavefront holds 32 gate rows
 // o .. o+31 and its second the up rows N/2 + o .. N/2 + o+31, so that a lane finds the gate and the up
 // value of an output element in the same register of its two accumulator blocks and writes
-// silu(gate) * up.  The residual is added before the one rounding.
+// silu(gate) * up.  The residual is added before the one rounding.  It may be Y, so neither is declared free of
+// aliases.
 struct PipeFusion {
     const half_t* residual;
     int swiglu;
@@ -116,7 +117,7 @@ struct SkArgs {
 template <int G, int WGM, int WGN, bool FUSED, int BM, int BN, bool E8 = false, bool BF = false, int KS = 1, bool SHORT = false>
 __global__ __launch_bounds__(64 * WGM * WGN * KS, 2) void gemm_pipe_kernel(const half_t* __restrict__ X, int64_t M,
                                                              const uint4* __restrict__ packed, int64_t N, int64_t K,
-                                                             half_t* __restrict__ Y, int m_tiles, int n_tiles,
+                                                             half_t* Y, int m_tiles, int n_tiles,
                                                              int splits, float* __restrict__ partial, PipeFusion fu,
                                                              SkArgs sk)
 {
@@ -693,7 +694,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KS, 2) void gemm_pipe_kernel(const
         // The last sharer: the tile's slabs (its own among them) added in K order, a quarter of the registers at a
         // time -- the accumulators are not needed any more, and this way the code shares nothing with the other
         // epilogues.  The loads are device-coherent: the other sharers ran on other XCDs, whose L2 this one cannot see.
-        half_t* __restrict__ yt = Y + m0 * N + n0;
+        half_t* yt = Y + m0 * N + n0;
         // (one of the wavefront's TM row blocks at a time: two at a time measured twice as slow)
         constexpr int kAtOnce = 1;
 #pragma unroll 1
@@ -760,8 +761,8 @@ __global__ __launch_bounds__(64 * WGM * WGN * KS, 2) void gemm_pipe_kernel(const
             continue;
         }
         if (out_mode != 1 && fu.residual && (n32 & 7u) != 0) {
-            const half_t* __restrict__ rt = fu.residual + m0 * N + n0;
-            half_t* __restrict__ yt = Y + m0 * N + n0;
+            const half_t* rt = fu.residual + m0 * N + n0;
+            half_t* yt = Y + m0 * N + n0;
 #pragma unroll
             for (int j = 0; j < TN; ++j) {
                 if (col0 + 32 * j < cols_left) {
@@ -796,7 +797,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KS, 2) void gemm_pipe_kernel(const
 template <int V>
 __global__ __launch_bounds__(256) void splitk_reduce_fused_kernel(const float* __restrict__ partial, int splits,
                                                                   int64_t M, int64_t N, int64_t n_out,
-                                                                  half_t* __restrict__ Y, PipeFusion fu)
+                                                                  half_t* Y, PipeFusion fu)
 {
     typedef float fvec __attribute__((ext_vector_type(V)));
     typedef _Float16 hvec __attribute__((ext_vector_type(V)));

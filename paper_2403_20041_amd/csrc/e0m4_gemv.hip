@@ -159,7 +159,7 @@ __device__ inline half_t out_value(float s)
 // lane queue up ahead of the weights.)
 template <int G, int M, int W, int DEQ = kDeqE0M4, bool FUSED = false, bool XREG = false>
 __global__ __launch_bounds__(W * 64) void gemv_kernel(const half_t* __restrict__ X, const uint4* __restrict__ packed,
-                                                      half_t* __restrict__ Y, uint32_t N32, uint32_t K32, int seg_items,
+                                                      half_t* Y, uint32_t N32, uint32_t K32, int seg_items,
                                                       int step_slots, int step_item, int rb_base, int rb_rem, int own_items,
                                                       GemvFusion fu)
 {

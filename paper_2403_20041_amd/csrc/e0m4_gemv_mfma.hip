@@ -115,7 +115,7 @@ __device__ inline int x_unit_off(int q, int w, int hl) { return ((q * 4 + (w >> 
 template <int W, bool FUSED, bool XREG, bool E8 = false, bool PHASED = false, int GS = 1, bool KEEP = false, bool BF = false,
           bool XF = false>
 __global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(const half_t* __restrict__ X,
-                                                           const uint4* __restrict__ packed, half_t* __restrict__ Y,
+                                                           const uint4* __restrict__ packed, half_t* Y,
                                                            int M, uint32_t N32, uint32_t K32, int step_slots_arg,
                                                            int step_item_arg, int rb_base, int rb_rem, int late,
                                                            uint32_t pieces_magic_arg, int kb_phase, int ph_stage,
