@@ -102,12 +102,13 @@ bool small_m_on_vector(int64_t M, int64_t N, int64_t K)
 constexpr int64_t kChunkRows = 16, kChunkedMaxM = 64, kChunked8MaxM = 32;
 int row_chunks(int64_t M) { return (int)((M + kChunkRows - 1) / kChunkRows); }
 int64_t rows_per_chunk(int64_t M) { return (M + row_chunks(M) - 1) / row_chunks(M); }
-bool small_batch_in_chunks(const Fusion& f, int64_t M, int64_t N, int64_t K, int group)
+bool small_batch_in_chunks(const Fusion& f, int64_t M, int64_t N, int64_t K, int group, WholeRowsPlan* plan = nullptr)
 {
     if (M <= kChunkRows || M > kChunkedMaxM || knob("gemv_mfma") == 1 || (double)N * (double)K > 7e7) return false;
-    int64_t wgs = 0;
-    if (!gemv_mfma_whole_rows(f, rows_per_chunk(M), N, K, group, &wgs)) return false;
-    const int64_t rounds = (row_chunks(M) * wgs + 255) / 256;
+    WholeRowsPlan p;
+    if (!gemv_mfma_whole_rows(f, rows_per_chunk(M), N, K, group, &p)) return false;
+    if (plan) *plan = p;
+    const int64_t rounds = (row_chunks(M) * p.workgroups + 255) / 256;
     return rounds <= 2 || (rounds == 3 && (double)N * (double)K <= 2e7);
 }
 // Any of the GEMM's knobs is set: it keeps the calls that are its own without the kernel below.
@@ -160,7 +161,9 @@ bool use_gemv_exact(int64_t M, int64_t N, int64_t K, int group, DqFormat format)
     if ((k != 0 && k != 7) || !gemv_exact_supported(M, N, K, group, format)) return false;
     if (k == 7) return true;
     if (gemm_steered() || N > (int64_t)1 << 24) return false;
-    return gemv_exact_pays(M, N, K, format, format == kDqFormatFp16 && small_batch_in_chunks(Fusion{}, M, N, K, group));
+    if (format == kDqFormatBf16) return gemv_exact_pays_bf16(M, N, K);
+    WholeRowsPlan p;
+    return small_batch_in_chunks(Fusion{}, M, N, K, group, &p) && gemv_exact_pays_chunks(M, row_chunks(M), p);
 }
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 

@@ -20,8 +20,8 @@
 // Against the GEMM at 4096 x 4096, 27392 x 4096, 4096 x 13696 (us): bfloat16 at M = 16 35.0 -> 6.5, 38.6 -> 19.6, 102 -> 13.7;
 // groups of 64 at M = 16 15.1 -> 6.3, 27.3 -> 18.0, 30.7 -> 13.4; 8-bit codes at M = 45 17.6 -> 11.0, (not used), 33.3 -> 28.4.
 //
-// Every weight is rounded to 16 bits before the product, as it is in the GEMM.  The kernels that keep code values exact and
-// apply scale and bias in fp32 (e0m4_gemv.hip, e0m4_gemv_mfma.hip) are not replaced by this one.
+// Every weight is rounded to 16 bits before the product, as it is in the GEMM, but in the instances on exact codes (EX below),
+// which apply scale and bias in fp32 as e0m4_gemv.hip and e0m4_gemv_mfma.hip do.  Calls of those two go to EX instances only.
 #include "e0m4_device.h"
 #include "e0m4_host.h"
 
@@ -414,9 +414,8 @@ bool gemv_dq_supported(int64_t M, int64_t N, int64_t K, int group)
 }
 
 // Where this kernel is faster than the GEMM, which rounds the weights as it does.  (The callers keep the calls of the kernels
-// that multiply unrounded weights away from here, faster or not: bfloat16 4096 x 13696 at M = 5 takes the vector kernel 19.2 us
-// and this one 11.8.)  The other side's time over this kernel's, on 166 problems with cold weights
-// (profiles/small_batch_dequantised_operands_vs_gemm.txt):
+// that multiply unrounded weights away from here, faster or not; the instances on exact codes are chosen below.)  The other
+// side's time over this kernel's, on 166 problems with cold weights (profiles/small_batch_dequantised_operands_vs_gemm.txt):
 //   bfloat16: up to 64 rows always (1.1 - 7.8: the GEMM has whole tiles only).  65 to 128 rows in two parts, against 64 x 256
 //     tiles with K halves, where a workgroup has few row blocks: 1.2 - 3.1; at M = 100 4096 x 4096 34.8 -> 21.1 us, 4096 x 13696
 //     102 -> 52, but 32768 x 2048 (8 row blocks) 25 -> 37, 27392 x 4096 43 -> 63.
@@ -448,19 +447,37 @@ bool gemv_exact_supported(int64_t M, int64_t N, int64_t K, int group, DqFormat f
 
 // Where exact codes are faster than the kernels of unrounded weights that have the call otherwise (us, cold weights, the other and
 // this one).  Calls of kernels that round the weights are not taken, though some would gain (27392 x 4096 at M = 24 27.6 and 22.2):
-// against the dequantised weights they would be further off.
-//   bfloat16, 3 to 8 rows: the staging kernel (4608 x 4096 at M = 5 6.6 and 6.2, 4096 x 13696 at M = 8 13.9 and 10.8), but not where
+// against the dequantised weights they would be further off.  Plain calls only: a form with fused operators is not built (a
+// residual call of 4096 x 4096 at M = 45 would go from 18.9 to 14.3 us).  Errors against float64 on the unrounded weights are those
+// of the other kernels (fp16 2.072e-4 on both sides, bfloat16 1.656e-3).
+//   bfloat16, 3 to 8 rows: the staging kernel (4608 x 4096 at M = 5 6.0 and 5.8, 4096 x 13696 at M = 8 13.9 and 10.2), but not where
 //     row blocks do not fill the wavefronts' (27392 x 4096, seven of eight: 15.1 and 16.0).
-//   fp16, 17 to 64 rows: the staging kernel in chunks (4608 x 4096 at M = 24 12.2 and 9.1, at M = 64 17.8 and 14.1, 4096 x 4096 at M =
-//     45 15.4 and 11.8).
-// Plain calls only.  With fused operators (one 6B block's residual call at M = 45 18.9 -> 14.3 us) a stack of blocks would sum in
-// another order and differ by up to 2.4 % of the largest value after four blocks.
-bool gemv_exact_pays(int64_t M, int64_t N, int64_t K, DqFormat format, bool in_chunks)
+bool gemv_exact_pays_bf16(int64_t M, int64_t N, int64_t K)
 {
     DqPlan p;
-    if (M < 3 || !gemv_exact_supported(M, N, K, 128, format) || !make_dq_plan(M, N, K, p, true)) return false;
-    if (format == kDqFormatBf16) return p.wr * p.r == p.rb_base + (p.rb_rem > 0 ? 1 : 0);
-    return in_chunks;
+    return M >= 3 && gemv_exact_supported(M, N, K, 128, kDqFormatBf16) && make_dq_plan(M, N, K, p, true) &&
+           p.wr * p.r == p.rb_base + (p.rb_rem > 0 ? 1 : 0);
+}
+
+//   fp16, 17 to 64 rows: the staging kernel in chunks of equal rows, by the workgroups of all chunks (this kernel's time over its on
+//     1 400 calls of 17 to 64 rows, 480 to 9 000 x 1536 to 12 000).
+//     More than one row block per workgroup: 0.55 - 0.98 (4608 x 4096 at M = 24 11.6 and 8.9).
+//     A compute unit for each workgroup of a chunk: 1.02 - 1.79 (840 x 4096 at M = 59 6.3 and 11.3); but two chunks with five to
+//       seven work items for eight wavefronts 0.92 - 0.98 beyond 28 rows and, with most units taken, beyond 24 (1904 x 3328 at M =
+//       28 6.4 and 6.0).
+//     Two of them on a compute unit at once: with two chunks 0.85 - 0.92, with more 1.04 - 1.17 (1816 x 2688 at M = 35 6.7 and 7.6).
+//     Else 0.51 - 1.02 (2376 x 1920 at M = 64 11.0 and 7.3; 1056 x 5120 at M = 49, eight workgroups beyond a round, 1.11), but with four
+//       chunks in two rounds whose wavefronts each stage their own X (as many work items as wavefronts) 1.00 - 1.18 (2040 x 4096 at
+//       M = 51 9.8 and 11.5).
+bool gemv_exact_pays_chunks(int64_t M, int chunks, const WholeRowsPlan& plan)
+{
+    if (plan.row_blocks > 1) return true;
+    const int64_t wgs = plan.workgroups * chunks;
+    if (wgs <= kTargetWorkgroups)
+        return chunks == 2 && plan.items > 4 && plan.items < 8 && (M > 28 || (M > 24 && wgs > kTargetWorkgroups * 3 / 4));
+    if (chunks == 2) return true;
+    if (wgs <= kTargetWorkgroups * plan.resident) return false;
+    return !(chunks == 4 && plan.x_in_registers && plan.items == plan.waves && wgs <= 2 * kTargetWorkgroups);
 }
 
 int launch_gemv_exact(const void* X, int64_t M, const void* packed, int64_t N, int64_t K, DqFormat format, void* Y, hipStream_t stream)

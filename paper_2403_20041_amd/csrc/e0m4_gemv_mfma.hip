@@ -1021,7 +1021,8 @@ int64_t chunk_rows(int64_t M, int chunks) { return (M + chunks - 1) / chunks; }
 // Groups of 64 and 32: where this kernel (or e0m4_gemv_items.hip for it) takes plain calls from the kernel with dequantised
 // operands (e0m4_gemv_dq.hip): with several row blocks per workgroup, or (group 64) K in one phase.  15360 x 5120 at M = 4 12.4
 // us, 27392 x 5120 at M = 8 22.6, 5120 x 5120 at M = 4 7.5.  It works with unrounded weights, the other kernel with weights rounded
-// to fp16: the line stays where it is, also where the other kernel is by now the faster one.  At M = 2 the vector kernel is as fast or faster.
+// to fp16: the line stays where it is, also where the other kernel is by now the faster one.  At M = 2 the vector kernel is as
+// fast or faster.
 bool gemv_mfma_groups_pay(int64_t M, int64_t N, int64_t K, int group)
 {
     const int gs = groups_per_block(group);
@@ -1132,13 +1133,18 @@ bool gemv_mfma_fused_supported(const Fusion& f, int64_t M, int64_t N, int64_t K,
     return make_mfma_plan(M, N, K, p, 2, false, groups_per_block(group));
 }
 
-bool gemv_mfma_whole_rows(const Fusion& f, int64_t M, int64_t N, int64_t K, int group, int64_t* workgroups)
+bool gemv_mfma_whole_rows(const Fusion& f, int64_t M, int64_t N, int64_t K, int group, WholeRowsPlan* plan)
 {
     MfmaPlan p;
     if (!gemv_mfma_fused_supported(f, M, N, K, group) ||
         !make_mfma_plan(M, N, K, p, f.swiglu ? 2 : 1, false, groups_per_block(group)) || p.kb_phase != 0)
         return false;
-    if (workgroups) *workgroups = p.grid;
+    if (plan) {
+        const bool xreg = groups_per_block(group) == 1 && p.waves <= 8 && p.step_item == 0;     // (154 registers: one per unit)
+        const int by_lds = (int)((size_t)160 * 1024 / p.lds_bytes);
+        *plan = {p.grid, p.rb_base + (p.rb_rem > 0 ? 1 : 0), xreg || p.waves > 8 ? 1 : std::min(2, by_lds),
+                 (int)((k_blocks(K) + kSuper - 1) / kSuper), p.waves, xreg};
+    }
     return true;
 }
 

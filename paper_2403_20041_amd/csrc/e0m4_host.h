@@ -76,8 +76,14 @@ int launch_gemv_mfma(const void* X, int64_t M, const void* packed, int64_t N, in
 int launch_gemv_mfma_bf16(const void* X, int64_t M, const void* packed, int64_t N, int64_t K, int group, void* Y, hipStream_t stream);
 bool gemv_mfma_fused_supported(const Fusion& f, int64_t M, int64_t N, int64_t K, int group);
 // ... and all M rows of X fit the LDS at once (no phases along K)
-// (`workgroups`: the launch's grid, when it is)
-bool gemv_mfma_whole_rows(const Fusion& f, int64_t M, int64_t N, int64_t K, int group, int64_t* workgroups = nullptr);
+struct WholeRowsPlan {
+    int64_t workgroups;
+    int row_blocks;                                     // of a workgroup (pairs of them with the gated product), at most
+    int resident;                                       // workgroups of a plain call that a compute unit holds at once
+    int items, waves;                                   // work items per row block
+    bool x_in_registers;
+};
+bool gemv_mfma_whole_rows(const Fusion& f, int64_t M, int64_t N, int64_t K, int group, WholeRowsPlan* plan = nullptr);
 bool gemv_mfma8_whole_rows(const Fusion& f, int64_t M, int64_t N, int64_t K);
 int launch_gemv_mfma_fused(const Fusion& f, const void* X, int64_t M, const void* packed, int64_t N, int64_t K, void* Y,
                            hipStream_t stream, int chunks = 1, int group = 128);
@@ -102,9 +108,11 @@ bool gemv_dq_pays(int64_t M, int64_t N, int64_t K, int group, DqFormat format);
 int launch_gemv_dq(const void* X, int64_t M, const void* packed, int64_t N, int64_t K, int group, DqFormat format, void* Y,
                    hipStream_t stream);
 // The same kernel on exact code values (4-bit codes, groups of 128; bfloat16 of up to 8 rows, fp16 of 17 to 64).
-// (`pays`: it is expected to beat the kernels that have the call otherwise; `in_chunks`: launch_gemv_mfma in chunks would)
+// (`pays`: it is expected to beat the kernels that have the call otherwise: the small-batch kernel, fp16 in `chunks` launches of
+// `plan` side by side)
 bool gemv_exact_supported(int64_t M, int64_t N, int64_t K, int group, DqFormat format);
-bool gemv_exact_pays(int64_t M, int64_t N, int64_t K, DqFormat format, bool in_chunks);
+bool gemv_exact_pays_bf16(int64_t M, int64_t N, int64_t K);
+bool gemv_exact_pays_chunks(int64_t M, int chunks, const WholeRowsPlan& plan);
 int launch_gemv_exact(const void* X, int64_t M, const void* packed, int64_t N, int64_t K, DqFormat format, void* Y, hipStream_t stream);
 // INT4 twin of the M = 1 kernel: same layout and work decomposition, codes turned into numbers with
 // integer-to-float conversion instructions.

@@ -1,6 +1,6 @@
-"""The small-batch kernel on exact codes (groups of 128; bfloat16 of 2 to 8 rows, fp16 of 17 to 64) against the oracle: last tiles of rows and columns, fewer k
-blocks than wavefronts, remainders of the unrolled loop, one to sixteen row blocks per workgroup, and calls that reach it by
-default."""
+"""The small-batch kernel on exact codes (groups of 128; bfloat16 of 2 to 8 rows, fp16 of 17 to 64) against the oracle: last tiles
+of rows and columns, fewer k blocks than wavefronts, remainders of the unrolled loop, one to sixteen row blocks per workgroup, and
+calls that reach it by default."""
 import numpy as np
 import pytest
 
@@ -60,3 +60,25 @@ def test_default_choice(e0m4, oracle, M, N, K):
     YR = e0m4.e0m4_matmul_fused(to_dev(X), codes, N, K, 128, residual=to_dev(R))
     YRref, info = oracle.matmul_fused(X, What, residual=R)
     check_fused(YR, YRref, info, False, False, "residual M=%d" % M)
+
+
+# calls whose chunks have a compute unit (or a place on one) each stay on them, to the bit, as in the last case four chunks in two
+# rounds; the others take exact codes
+@pytest.mark.parametrize("M,N,K,exact", [(59, 840, 4096, False), (17, 1550, 6144, False), (24, 904, 2688, False), (32, 576, 2304, True),
+                                         (28, 1904, 3328, True), (28, 800, 3328, False),
+                                         (35, 1816, 2688, False), (20, 2856, 2432, True), (47, 2376, 1920, True), (24, 4608, 1536, True),
+                                         (51, 2040, 4096, False), (64, 2832, 3712, True)])
+def test_chunks_where_they_are_faster(e0m4, oracle, M, N, K, exact):
+    (codes, _, _), What = assert_quantize_exact(e0m4, oracle, synth_inputs.weights(N, K, seed=7700), 128)
+    X = synth_inputs.activations(M, K, seed=7800 + M, outlier_frac=0.01)
+    Y = {}
+    try:
+        for mode in (0, 7, 8):
+            e0m4.e0m4_set_knob("gemv_mfma", mode)
+            Y[mode] = e0m4.e0m4_matmul(to_dev(X), codes, None, None, N, K, 128)
+    finally:
+        e0m4.e0m4_set_knob("gemv_mfma", 0)
+    Yref, absdot = oracle.matmul(X, What)
+    check_matmul(Y[0], Yref, absdot, "M=%d" % M)
+    assert not torch.equal(Y[7], Y[8])                  # (two orders of the sums)
+    assert torch.equal(Y[0], Y[7 if exact else 8])
