@@ -451,12 +451,18 @@ bool gemv_exact_supported(int64_t M, int64_t N, int64_t K, int group, DqFormat f
 // residual call of 4096 x 4096 at M = 45 would go from 18.9 to 14.3 us).  Errors against float64 on the unrounded weights are those
 // of the other kernels (fp16 2.072e-4 on both sides, bfloat16 1.656e-3).
 //   bfloat16, 3 to 8 rows: the staging kernel (4608 x 4096 at M = 5 6.0 and 5.8, 4096 x 13696 at M = 8 13.9 and 10.2), but not where
-//     row blocks do not fill the wavefronts' (27392 x 4096, seven of eight: 15.1 and 16.0).
+//     row blocks do not fill the wavefronts' (27392 x 4096, seven of eight: 15.1 and 16.0), nor where a wavefront walks three or four
+//     row blocks that lie almost a multiple of 16 KiB apart, on the same few memory channels: rows of 1920, 3840, 5760 and 7680
+//     weights, 16384 of them at M = 5 7.0 and 7.8, 9.6 and 11.9, 14.0 and 15.1, 17.6 and 19.0 (of 1792 and 2048 6.9 and 6.5, 7.0
+//     and 6.75; of 9600 as fast); with three 12288 x 3840 8.3 and 9.4, but x 7680 15.2 and 14.7; with two never slower.
+constexpr int64_t kChannelBytes = 16 * 1024;
 bool gemv_exact_pays_bf16(int64_t M, int64_t N, int64_t K)
 {
     DqPlan p;
-    return M >= 3 && gemv_exact_supported(M, N, K, 128, kDqFormatBf16) && make_dq_plan(M, N, K, p, true) &&
-           p.wr * p.r == p.rb_base + (p.rb_rem > 0 ? 1 : 0);
+    if (M < 3 || !gemv_exact_supported(M, N, K, 128, kDqFormatBf16) || !make_dq_plan(M, N, K, p, true)) return false;
+    const int64_t beyond = k_blocks(K) * block_bytes(128) % kChannelBytes, off = std::min(beyond, kChannelBytes - beyond);
+    if (p.r >= 3 && off <= 64 * p.r) return false;
+    return p.wr * p.r == p.rb_base + (p.rb_rem > 0 ? 1 : 0);
 }
 
 //   fp16, 17 to 64 rows: the staging kernel in chunks of equal rows, by the workgroups of all chunks (this kernel's time over its on

@@ -82,3 +82,26 @@ def test_chunks_where_they_are_faster(e0m4, oracle, M, N, K, exact):
     check_matmul(Y[0], Yref, absdot, "M=%d" % M)
     assert not torch.equal(Y[7], Y[8])                  # (two orders of the sums)
     assert torch.equal(Y[0], Y[7 if exact else 8])
+
+
+# bfloat16: with three and four row blocks per wavefront not where these lie almost a multiple of 16 KiB apart (to the bits of the
+# staging kernel there)
+@pytest.mark.parametrize("workgroups,N,K,exact", [(3, 190, 1920, False), (3, 190, 1792, True), (2, 96, 3840, False), (2, 96, 7680, True),
+                                                  (3, 96, 1920, True), (1, 128, 5760, False)])
+def test_bf16_row_blocks_on_the_same_channels(e0m4, oracle, workgroups, N, K, exact):
+    W, X, half = synth_inputs.weights_bf16(N, K, seed=7900), synth_inputs.activations_bf16(5, K, seed=7950), K // 256 * 128
+    W[:, half:2 * half], X[:, half:2 * half], X[:, 2 * half:] = W[:, :half], X[:, :half] ^ 0x8000, 0
+    codes, What, _ = assert_bf16_quantize_exact(e0m4, oracle, W, 128)       # (sums that cancel: what is left shows their order)
+    Y = {}
+    e0m4.e0m4_set_knob("gemv_workgroups", workgroups)
+    try:
+        for mode in (0, 7, 8):
+            e0m4.e0m4_set_knob("gemv_mfma", mode)
+            Y[mode] = e0m4.e0m4_bf16_matmul(bf_dev(X), codes, N, K, 128)
+    finally:
+        e0m4.e0m4_set_knob("gemv_mfma", 0)
+        e0m4.e0m4_set_knob("gemv_workgroups", 0)
+    Yref, absdot = oracle.bf16_matmul(X, What)
+    check_bf16_matmul(oracle, Y[0], Yref, absdot, "K=%d" % K)
+    assert torch.equal(Y[0].view(torch.int16), Y[7 if exact else 8].view(torch.int16))
+    assert not torch.equal(Y[7].view(torch.int16), Y[8].view(torch.int16))
