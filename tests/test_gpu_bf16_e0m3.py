@@ -145,6 +145,29 @@ def test_bf16_decode_matrix_core_kernel(e0m4, oracle, M, N, K, G, waves, target)
             e0m4.e0m4_set_knob(knob, 0)
 
 
+# three and four rows in groups of 64 and 32: the vector kernel's bits with K in phases and on short rows, the matrix-core kernel's else
+# (sums that cancel: what is left shows their order)
+@pytest.mark.parametrize("M,N,K,G,vector", [(3, 2704, 5120, 32, True), (4, 1664, 6016, 32, True), (4, 800, 6144, 64, True),
+                                            (3, 7368, 2048, 32, True), (3, 11136, 1536, 64, True), (3, 4800, 1280, 32, False),
+                                            (3, 2000, 4096, 32, False), (3, 2000, 6016, 64, False), (3, 1000, 6912, 32, False),
+                                            (4, 7368, 2048, 32, False)])
+def test_bf16_few_rows_where_the_vector_kernel_is_faster(e0m4, oracle, M, N, K, G, vector):
+    W, X, half = synth_inputs.weights_bf16(N, K, seed=3280), synth_inputs.activations_bf16(M, K, seed=3290), K // 256 * 128
+    W[:, half:2 * half], X[:, half:2 * half], X[:, 2 * half:] = W[:, :half], X[:, :half] ^ 0x8000, 0
+    codes, What, _ = assert_bf16_quantize_exact(e0m4, oracle, W, G)
+    Y = {}
+    try:
+        for mode in (0, 1, 6):
+            e0m4.e0m4_set_knob("gemv_mfma", mode)
+            Y[mode] = e0m4.e0m4_bf16_matmul(bf_dev(X), codes, N, K, G).view(torch.int16)
+    finally:
+        e0m4.e0m4_set_knob("gemv_mfma", 0)
+    Yref, absdot = oracle.bf16_matmul(X, What)
+    check_bf16_matmul(oracle, Y[0].view(torch.bfloat16), Yref, absdot, "M=%d N=%d K=%d G=%d" % (M, N, K, G))
+    assert torch.equal(Y[0], Y[1 if vector else 6])
+    assert not torch.equal(Y[1], Y[6])
+
+
 @pytest.mark.parametrize("M,N,K,G", [(9, 203, 1664, 128), (64, 256, 512, 32), (200, 520, 1024, 64), (300, 1040, 2080, 32),
                                      (1024, 1280, 4096, 128), (130, 64, 128, 128), (17, 4608, 416, 32)])
 def test_bf16_gemm(e0m4, oracle, M, N, K, G):
