@@ -122,19 +122,21 @@ int e0m4_unpack_codes(const void* codes, int64_t N, int64_t K, int group, void* 
  *            the matrix cores so the cost stays near the weight stream for
  *            every such M.  X is staged in the LDS of the compute unit, all
  *            of it (about M * K * 2 <= 140 KiB) or one part of K after the
- *            other; the weights are read once either way.
- *   3 <= M <= 16, group 32 or 64: the same kernel with every row of X staged
- *            once per group of a block (M <= 8 at group 64, M <= 4 at group 32,
- *            where a workgroup has several row blocks or the staged rows fit
- *            the LDS), else a matrix-core kernel that dequantises the weight
- *            operand in registers.
- *   17 <= M <= 64, group 128, N * K <= 7e7, a chunk of X within the LDS:
- *            that kernel (in fused calls on equal chunks of at most 16 rows
- *            in one launch, in plain ones the dequantising kernel's form on
- *            exact codes),
- *            when its workgroups make at most two rounds on the compute
- *            units (three on small weights); otherwise, any group, N * K <= 7e7 (and
- *            256 <= K <= 9216 for M > 48), the dequantising kernel.
+ *            other, or, with one or two blocks of output rows per workgroup,
+ *            brought in block by block as the weights are (the same sums in the
+ *            same order); the weights are read once either way.
+ *   3 <= M <= 16, group 32 or 64: the same kernels (M <= 8 at group 64, M <= 4
+ *            at group 32, where a workgroup has several blocks of output rows or
+ *            the rows of X fit the LDS), else a matrix-core kernel that
+ *            dequantises the weight operand in registers.
+ *   17 <= M <= 64, group 128, N * K <= 7e7, a chunk of X within the LDS,
+ *            where equal chunks of at most 16 rows make at most two rounds of
+ *            workgroups on the compute units (three on small weights): the
+ *            small-batch kernel on those chunks in one launch or, in plain calls
+ *            and mostly where they make more than one round, the dequantising
+ *            kernel's form on exact codes; otherwise, plain calls, any group,
+ *            N * K <= 7e7 (and 256 <= K <= 9216 for M > 48), the dequantising
+ *            kernel.
  *   M >= 9 otherwise, and 2 <= M <= 8 when M * N * K is about 3.8e8 or
  *            more (the vector kernel's time grows with M): MFMA GEMM path
  *            (tiles of 64 x 256, 128 x 256 or 256 x 256 outputs, whichever
@@ -143,8 +145,8 @@ int e0m4_unpack_codes(const void* codes, int64_t N, int64_t K, int group, void* 
  *            tiles shared out evenly when the estimate favours that).
  *            e0m4_workspace_bytes() tells when a workspace is needed.
  * The dequantising kernel and the GEMM round every weight to fp16 as
- * e0m4_dequant does; the other kernels work on the codes' exact values and
- * apply scale and bias in fp32.
+ * e0m4_dequant does; the form on exact codes and the other kernels multiply the
+ * codes' exact values and apply scale and bias in fp32.
  * `scales_f16`/`bias_f16` may be NULL (see `codes` above); `workspace` may be
  * NULL when e0m4_workspace_bytes() is 0, else it is device memory of at least
  * that many bytes, 16-byte aligned, owned by the caller, overwritten by the
@@ -304,15 +306,15 @@ int e0m3_unpack_codes(const void* codes, int64_t N, int64_t K, int group, void* 
  * are bfloat16 (16-bit patterns, round to nearest even); accumulation is fp32.
  * `codes` has the E0M4 layout and size (e0m4_codes_bytes; e0m4_unpack_codes
  * reads it), its embedded parameter words hold bfloat16 pairs.
- *   e0m4_bf16_matmul: one row (two, with groups of 64 and 32) the decode kernel
- *   with bfloat16 dot products (a shift and a mask-or per pair of codes; scale
- *   and bias in fp32), up to 8 rows (4 with groups of 32) the small-batch
- *   matrix-core kernels on the codes' exact values; larger M
- *   with the weights dequantised in registers (fp32 fused multiply-add, one
- *   rounding to bfloat16): up to 64 rows, and 128 on small weights (not on the
- *   shortest rows), the dequantising kernel of e0m4_matmul, beyond that its pipelined MFMA kernel
- *   in whole tiles (no workspace, so no split along K but for two halves inside
- *   a workgroup); when K is not a multiple of 128 an MFMA kernel with
+ *   e0m4_bf16_matmul: one row (and two to four where that is faster: two in
+ *   groups of 64 and 32 and on short rows of weights, three and four seldom) the
+ *   decode kernel with bfloat16 dot products (a shift and a mask-or per pair of
+ *   codes; scale and bias in fp32), up to 8 rows (4 with groups of 32) the small-batch matrix-core kernels on the codes' exact
+ *   values; larger M with the weights dequantised in registers (fp32 fused
+ *   multiply-add, one rounding to bfloat16): up to 64 rows, and 128 on small
+ *   weights (not on the shortest rows), the dequantising kernel of e0m4_matmul,
+ *   beyond that its pipelined MFMA kernel in whole tiles (no workspace, so no
+ *   split along K but for two halves inside a workgroup); when K is not a multiple of 128 an MFMA kernel with
  *   128 x 128 tiles that dequantises into LDS.
  * Shape, pointer, stream and error rules as for the E0M4 entry points.
  */

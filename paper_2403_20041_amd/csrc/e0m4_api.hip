@@ -141,10 +141,11 @@ bool use_gemv_dq4(int64_t M, int64_t N, int64_t K, int group)
 // bfloat16 of up to eight rows: the small-batch kernel, which multiplies the codes' exact values as the vector kernel does but
 // whose time hardly grows with the rows (27392 x 5120 at M = 5 32 -> 18.3 us; M = 2 21.5 -> 18.4).  Its time over the vector kernel's:
 //   Groups of 64 and 32 from three rows on (2560 x 2048 at M = 2 4.4 us there and 4.8 here, at M = 3 5.6 and 4.8), 0.37 - 1.02 on 1 100
-//     calls (rows of up to 1024 weights to 1.07, of 512 at four rows to 1.12).  But 1.03 - 1.21 with K in phases on one row block per workgroup and up to
-//     twelve work items (of 512 weights) per row, at three and four rows (2704 x 5120 in groups of 32 at M = 3 6.8 and 8.2); and 0.97 -
-//     1.17 at three rows with up to four work items per row where a workgroup of several row blocks has up to four or eight to twelve
-//     in all, which the vector kernel's wavefronts divide evenly (16000 x 1536 6.9 and 7.6, 7368 x 2048 5.6 and 6.3).
+//     calls (rows of up to 1024 weights to 1.07, of 512 at four rows to 1.12).  But 1.03 - 1.21 with K in phases on one row block per
+//     workgroup and up to twelve work items (of 512 weights) per row, at three and four rows (2704 x 5120 in groups of 32 at M = 3
+//     6.8 and 8.2); and 0.97 - 1.17 at three rows with up to four work items per row where a workgroup of several row blocks has up
+//     to four or eight to twelve in all, which the vector kernel's wavefronts divide evenly (16000 x 1536 6.9 and 7.6, 7368 x 2048 5.6
+//     and 6.3).
 //   Two rows in groups of 128 on 117 problems: 0.79 - 0.93 with more than six work items per row, and with five or six where
 //     workgroups have one row block each; else 0.95 - 1.15 (2560 x 2048 4.2 and 4.6, 7680 x 2560 5.8 and 6.4), but 0.79 - 1.04 with more
 //     than five row blocks per workgroup and more than three work items.

@@ -104,11 +104,15 @@ struct SkArgs {
 //
 // SHORT: M leaves 64 rows or fewer in the last row tile of 128.  Those tiles are computed in two of their four 32-row blocks
 // (one block would take as long: below that the dequantisation is all there is to do) and are numbered last on every XCD, so
-// that they fill the gaps at the end: gated 317 x 32768 x 2048 in groups of 32 (256 whole tiles and 128 of 61 rows) 57.3 -> 49
-// us.  In instances of its own: another form of the K loop beside it costs the usual one 2 % (1024 rows, two 6B blocks 899 ->
-// 916 us), which is also why it takes six row tiles at most and as many tiles as compute units, or nobody waits for the whole
-// ones: gated 27392 x 4096 at M = 300 98.7 -> 85.4 us (bfloat16 95.1 -> 84.1), 15360 x 5120 at M = 576 116 -> 102, 32768 x 2048 at
-// M = 140 37.7 -> 35.4; but 7424 x 2688 at M = 700 (174 tiles) 38.0 and 40.3.
+// that they fill the gaps at the end.  In instances of its own: another form of the K loop beside it costs the usual one 2 %
+// (1024 rows, two 6B blocks 899 -> 916 us).  It takes as many tiles as compute units, or nobody waits for the whole ones (7424 x
+// 2688 at M = 700, 174 tiles, 38.0 and 40.3 us), and six row tiles at most.  Short over whole with this tile forced, 3 to 13 row
+// tiles with 20 and 60 rows left, 4-bit 27392 x 4096 and 32768 x 2048 gated and 15360 x 5120, bfloat16 27392 x 4096 and 11008 x
+// 4096, 8-bit 22016 x 3072: up to six row tiles 0.81 - 1.00, the least where the last round of workgroups is nearly empty (gated
+// 27392 x 4096 at M = 316 97.6 -> 84.7 us, bfloat16 95.3 -> 84.1, gated 32768 x 2048 in groups of 32 57.5 -> 50.6, 15360 x 5120 at
+// M = 572 116 -> 101; at six row tiles 0.97 - 1.00, but 0.87 and 0.90 with 258 and 516 tiles); beyond, 0.90 - 1.02: 4-bit codes still
+// gain (27392 x 4096 at M = 828 177 -> 173), 8-bit codes and bfloat16 of fewer columns lose (22016 x 3072 at M = 788 128.6 -> 131.1,
+// 11008 x 4096 93.9 -> 95.0).
 //
 // E8 selects the 8-bit format E0M8 (e0m8_pack.hip; G is then 128, the group of its 4-bit slots): a K slice
 // of 64 is one block, a lane reads two 16-byte chunks of 16 weights per slice, and MFMA number s takes

@@ -13,10 +13,10 @@
 // own and parks a unit's sums in LDS.
 //
 // What bounds it: X from L2 (every workgroup needs all 2 M K bytes: at M = 16 and K = 16384 512 KiB for 136 KiB of weights).
-// With a residual, X staged and here (us): 4096 x 13696 at M = 16 20.6 -> 11.8, at M = 6 14.0 -> 10.4; 2048 x 16384 20.1 -> 12.4
-// and 13.4 -> 10.5; two row blocks: 5120 x 13696 27.0 -> 18.9, 5120 x 5120 14.0 -> 9.2; groups of 64 at M = 8: 5120 x 13696
-// 21.5 -> 16.1, 2560 x 8192 10.5 -> 7.8; groups of 32 at M = 4: 5120 x 5120 10.9 -> 8.5. 8-bit codes: 4096 x 4096 at M =
-// 16 9.6 -> 7.0, at M = 8 8.1 -> 6.8, 4096 x 13696 at M = 16 23.4 -> 19.7.
+// With a residual and cold weights, X staged and here (us): 4096 x 13696 at M = 16 20.1 -> 14.7, at M = 8 15.2 -> 11.7; 2048 x 16384
+// 19.4 -> 14.8 and 13.9 -> 11.6 (with the weights in the last-level cache 11.0 at M = 16); two row blocks: 5120 x 13696 26.7 -> 18.3,
+// 5120 x 5120 13.5 -> 9.7; groups of 64 at M = 8: 5120 x 13696 21.2 -> 15.5, 5120 x 5120 11.3 -> 8.5; 8-bit codes: 4096 x 4096 at M =
+// 16 9.1 -> 7.3, at M = 8 7.4 -> 6.6, 4096 x 13696 at M = 16 23.2 -> 18.9.  Where it is not the faster one: gemv_items_pays.
 #include "e0m4_device.h"
 #include "e0m4_host.h"
 
@@ -240,7 +240,7 @@ __global__ __launch_bounds__(kItemThreads, 2) void gemv_items_kernel(const half_
     }
     // The sums of all phases per wavefront of the order, then (in LDS that X has left) the wavefronts' in their order: the items i
     // of row block s that wavefront v has are those with (s * items of the phase + i) % W = v, the first of them r below.  (In one
-    // pass over both, each sum a chain of dependent reads: 2048 x 16384 at M = 16 15.2 us, in two 12.4.)
+    // pass over both, each sum a chain of dependent reads, 2048 x 16384 at M = 16 took 2.8 us longer.)
     __syncthreads();
     float* cells = reinterpret_cast<float*>(smem + kFirstX);        // [W][R][16 m][16 n]
     for (int c0 = wave >> 2; c0 < order_waves * R; c0 += kItemWaves / 4) {

@@ -38,7 +38,10 @@
 // for as many phases at a time as fit (ph_stage: one, but with several groups per block, whose phases are cut as
 // if LDS held GS times the rows, so that the order of the sums does not depend on what it does hold).  The weight
 // stream is the same, each byte once, and runs on from phase to phase: replacing X costs a barrier and the loads (2048 x
-// 16384 at M = 16, four phases: 20.6 us with the weights' prefetch started anew in every phase, now 19.8).
+// 16384 with a residual at M = 16, four phases: 20.6 us with the weights' prefetch started anew in every phase, then 19.8).
+// Calls without rms-norm and gated product on one or two row blocks per workgroup have left for e0m4_gemv_items.hip where that
+// kernel is the faster one; in phases remain those with a norm or a gated product and those with more row blocks (27392 x 8192
+// at M = 9 and 16 31.7 and 35.2 us).
 #include "e0m4_device.h"
 #include "e0m4_host.h"
 

@@ -1,5 +1,6 @@
 """Prompts whose last row tile of 128 holds 64 rows or fewer: those tiles are computed in two blocks of 32 rows and numbered behind
-the whole ones (32776 and, gated, 32768 columns: as many tiles as compute units; 11016 with six row tiles likewise; 200: too few for that)."""
+the whole ones (32776 and, gated, 32768 columns: as many tiles as compute units; 11016 with six row tiles likewise; 200: too
+few for that)."""
 import numpy as np
 import pytest
 
