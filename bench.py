@@ -65,17 +65,17 @@ def profile_traffic(key):
 # rocprofv3 summaries
 
 def _short_kernel_name(n):
-    m = re.search(r"(gemv_kernel|gemv_mfma_kernel|gemv_dq_kernel|splitk_reduce_fused_kernel|gemm_pipe_kernel|gemm_kernel|quantize_kernel|"
-                  r"dequant_kernel|unpack_kernel|splitk_reduce_kernel|zero_fill_kernel|rmsnorm_kernel|kv_append_kernel|"
-                  r"quantize8_kernel)I((?:L[ib]\d+E)+)E", n)
+    m = re.search(r"(gemv_kernel|gemv_mfma_kernel|gemv_items_kernel|gemv_dq_kernel|splitk_reduce_fused_kernel|gemm_pipe_kernel|"
+                  r"gemm_kernel|quantize_kernel|dequant_kernel|unpack_kernel|splitk_reduce_kernel|zero_fill_kernel|rmsnorm_kernel|"
+                  r"kv_append_kernel|quantize8_kernel)I((?:L(?:[ib]|NS_8DqFormatE)\d+E)+)E", n)
     if m:
-        return "%s<%s>" % (m.group(1), ",".join(re.findall(r"L[ib](\d+)", m.group(2))))
-    n = re.sub(r"^void ", "", n)
-    m = re.search(r"(Cijk_\w{0,40}|__amd_rocclr_\w+|\w+_kernel\w*)", n)
-    return (m.group(1) if m else n)[:60]
+        return "%s<%s>" % (m.group(1), ",".join(re.findall(r"L(?:[ib]|NS_8DqFormatE)(\d+)", m.group(2))))
+    n = re.sub(r"^void |^_ZN4e0m412_GLOBAL__N_1\d\d", "", n)
+    m = re.search(r"^(\w+_kernel)EP|(Cijk_\w{0,40}|__amd_rocclr_\w+|\w+_kernel\w*)", n)
+    return (m.group(1) or m.group(2) if m else n)[:60]
 
 
-OUR_KERNELS = (r"gemv_kernel|gemv_mfma_kernel|gemv_dq_kernel|gemm_pipe_kernel|gemm_kernel|splitk_reduce|rmsnorm_kernel|"
+OUR_KERNELS = (r"gemv_kernel|gemv_mfma_kernel|gemv_items_kernel|gemv_dq_kernel|gemm_pipe_kernel|gemm_kernel|splitk_reduce|rmsnorm_kernel|"
                r"quantize_kernel|dequant_kernel|kv_append_kernel|zero_u32_kernel")
 
 
@@ -127,7 +127,7 @@ def summarize(directory, last):
     rows = [r for r in con.execute("select name,grid_x,workgroup_x,start,end from kernels order by start")
             if re.search(OUR_KERNELS, r[0])]
     if last:
-        rows = [r for r in rows if re.search(r"gemv_kernel|gemv_mfma_kernel|gemv_dq_kernel|gemm_pipe_kernel|gemm_kernel|splitk_reduce", r[0])][-last:]
+        rows = [r for r in rows if re.search(r"gemv_\w*kernel|gemm_\w*kernel|splitk_reduce", r[0])][-last:]
         print("last %d dispatches of the matmul kernels (the timed graph replays): %.3f ms of kernel time, "
               "%.3f ms from the first start to the last end" % (len(rows), sum(r[4] - r[3] for r in rows) / 1e6,
                                                                  (rows[-1][4] - rows[0][3]) / 1e6))
