@@ -262,6 +262,20 @@ __device__ inline __amdgpu_buffer_rsrc_t rsrc_if(const void* p, bool in)
     return __builtin_amdgcn_make_buffer_rsrc(q, 0, __builtin_amdgcn_readfirstlane(in ? 0x7fffffff : 0), 0x00020000);
 }
 
+// 16 bytes per lane from memory to LDS without a register in between: lane l's arrive at `lds` + 16 l (`lds` is wavefront-uniform).
+// Nothing waits for them by itself: wait_loads<N> waits until at most N of the wavefront's loads are under way, of either kind,
+// which come back in the order of the requests.
+__device__ inline void load_to_lds_b128(__amdgpu_buffer_rsrc_t rsrc, unsigned char* lds, uint32_t voff, uint32_t soff)
+{
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void*)lds, 16, (int)voff, (int)soff, 0, 0);
+}
+template <int N>
+__device__ inline void wait_loads()
+{
+    static_assert(N >= 0 && N < 64, "vmcnt has six bits");
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
 // Operators folded into the decode kernels (e0m4_matmul_fused; paper: section "Operator and lagging
 // optimizations", fusion of rms-norm and of element-wise operators into their neighbours):
 //   gamma    : the rows of X are rms-normalised while they are staged (x * rsqrt(mean x^2 + eps) * gamma,

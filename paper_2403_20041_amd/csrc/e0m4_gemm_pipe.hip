@@ -8,15 +8,22 @@
 // registers per lane each, which leaves two wavefronts per SIMD at most: little but a wavefront's own
 // instruction stream can hide latency.  The stream is therefore laid out by hand, per K slice of 64
 // (= 4 MFMA sub-steps of 16):
-//   - activations: global -> registers (issued two slices ahead) -> LDS ring of three stages ->
-//     16-byte fragments, read one sub-step ahead of their use;
+//   - activations: global -> LDS ring of four stages, without a register in between, requested two and a half
+//     slices ahead -> 16-byte fragments, read one sub-step ahead of their use;
 //   - weights: never touch LDS.  Lane (n = l%32, h = l/32) reads the 16-byte chunk of row n with
-//     k = 32h..32h+31 of the slice (two slices ahead), and word s of that chunk is dequantised
+//     k = 32h..32h+31 of the slice (three slices ahead), and word s of that chunk is dequantised
 //     (shift, mask-or exponent, minus bias, times scale; packed fp16, bit-identical to
 //     e0m4_dequant) one sub-step ahead of MFMA number s, whose K set is {8s..8s+7} u
 //     {32+8s..32+8s+7}; the activation fragment of the same MFMA is piece 4h+s of the row.
-//   - one barrier per slice, placed after sub-step 1, separates the LDS write of slice kt+1 from
-//     the fragment reads that start in sub-step 3.
+//   - one barrier per slice, placed after sub-step 1: before it a wavefront waits for its own requests of slice
+//     kt+1, whose fragment reads start in sub-step 3; behind it the stage of slice kt-1 is free for slice kt+3.
+// Through registers the activations could be requested one slice ahead, and the weights too: less than a memory latency
+// where a wavefront has a SIMD to itself.  Time of a pair of slices (K = 8192 against 2048), then and now: 64 x 256 tiles on
+// 64, 256 and 512 workgroups 1.24 -> 0.85, 1.82 -> 1.47 and 2.56 -> 2.41 us; 128 x 256 tiles on 64, 256 and 512 1.43 -> 1.15, 1.95 ->
+// 1.86 and 3.62 -> 3.54; 256 x 256 tiles on 256 3.53 -> 3.39.  With all compute units at work the clock that the chip holds
+// is the bound: the same launch on zero operands takes 0.56 of the time, without the dequantisation 0.86 of it, with
+// activation fragments that are read once 0.94, with neither 0.68 (128 x 256 tiles).  A wavefront that owns all 256 rows of the
+// large tile (accumulators in the AGPRs, each weight dequantised once) gains 3 % per pair and loses 3 us per tile.
 // The LDS tile is 128-byte rows whose eight 16-byte pieces are XOR-swizzled with (row / 2) % 8: the
 // LDS of gfx950 serves a 16-byte-per-lane read 16 lanes (256 bytes, two rows of the tile) at a time,
 // so 16 consecutive rows have to land in 16 different 16-byte bank groups (swizzling with row % 8, the
@@ -33,7 +40,7 @@ namespace {
 
 constexpr int BK = 64;
 constexpr int kRowBytes = BK * 2;
-constexpr int kStages = 3;
+constexpr int kStages = 4;
 constexpr int kNumXcd = 8;
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
@@ -127,11 +134,9 @@ __global__ __launch_bounds__(64 * WGM * WGN * KS, 2) void gemm_pipe_kernel(const
 {
     constexpr int kThreads = 64 * WGM * WGN;            // per K half
     constexpr int kStageBytes = BM * kRowBytes;
-    // K slices of weights in flight, and of activations in registers.  Twice as many where one workgroup has a compute unit to
-    // itself (K halves: 4096 x 13696 at M = 300 112 -> 103 us); with a second one beside it the longer start costs more than it
-    // gives (fp16 4096 x 13696 at M = 128 in K splits 29.4 -> 31.4, bfloat16 22784 x 5120 at M = 180, 267 tiles, 77 -> 79).
-    constexpr int PD = KS == 2 ? 4 : 2;
-    constexpr int AD = KS == 2 ? 2 : 1;
+    // Slices of weights in registers (8-bit codes: twice the registers per slice), stages of activations in LDS, and how many
+    // slices ahead those are requested.
+    constexpr int PD = E8 && BM > 64 ? 2 : 4, S = kStages, L = S - 1;
     constexpr int TM = BM / (32 * WGM), TN = BN / (32 * WGN);      // 32x32 MFMA blocks per wavefront
     constexpr int RP = kThreads / 8;                    // rows covered by one activation loader pass
     constexpr int PA = BM / RP;                         // activation loader passes
@@ -279,8 +284,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KS, 2) void gemm_pipe_kernel(const
     const PackedLayout<G> lay(E8 ? 2 * K : K);
     const int64_t nrb = row_blocks(N);
     const int wm = (wave / WGN) * (BM / WGM), wn = (wave % WGN) * (BN / WGN);
-    const int KT = KT_all;                              // K % 128 == 0 is required by the launcher: KT is even
-    // this segment's K slices [kt_begin, kt_end): whole pairs of slices
+    // this segment's K slices [kt_begin, kt_end): whole pairs of slices (K % 128 == 0 is required by the launcher)
     const int kt_begin = __builtin_amdgcn_readfirstlane(seg_kb);
     const int kt_end = __builtin_amdgcn_readfirstlane(seg_ke);
 
@@ -289,21 +293,20 @@ __global__ __launch_bounds__(64 * WGM * WGN * KS, 2) void gemm_pipe_kernel(const
     // Global reads are buffer loads: a wavefront-uniform resource (base of this tile's data, in
     // scalar registers), a scalar offset that advances with the K slice, and a 32-bit per-lane
     // offset that never changes -- no vector address arithmetic inside the K loop.
-    const int a_row = t >> 3, a_piece = t & 7;
-    const __amdgpu_buffer_rsrc_t a_rsrc = make_rsrc(X + m0 * K);
+    const int a_row = t >> 3, a_piece = (t & 7) ^ ((a_row >> 1) & 7);
+    const half_t* a_base = X + m0 * K;
     uint32_t a_pass_off[PA];
 #pragma unroll
     for (int p = 0; p < PA; ++p)
         a_pass_off[p] = (uint32_t)((min((int64_t)(a_row + RP * p), M - 1 - m0) * K + a_piece * 8) * 2);
-    // LDS write position of this thread's piece (pass p adds RP rows)
-    const uint32_t a_lds_off = (uint32_t)(a_row * kRowBytes + ((a_piece ^ ((a_row >> 1) & 7)) << 4));
+    // LDS position of this wavefront's eight rows (pass p adds RP rows); lane l fills the 16 bytes at 16 l
+    const uint32_t a_lds_off = (uint32_t)(wave * 8 * kRowBytes);
 
     // ---- weight loader: operand block j of this wavefront covers rows n0 + wn + 32j .. +31
     const int b_h = lane >> 5, b_r = lane & 15;
     const int64_t rb_tile = n0 / kBlockRows;            // first row block of the tile (exists: n0 < N)
-    const __amdgpu_buffer_rsrc_t b_code_rsrc = make_rsrc(packed + lay.code_index(rb_tile, 0));
-    const __amdgpu_buffer_rsrc_t b_param_rsrc =
-        make_rsrc(reinterpret_cast<const uint32_t*>(packed) + lay.param_index(rb_tile, 0));
+    const uint4* b_codes = packed + lay.code_index(rb_tile, 0);
+    const uint32_t* b_params = reinterpret_cast<const uint32_t*>(packed) + lay.param_index(rb_tile, 0);
     const uint32_t rb_stride = (uint32_t)lay.nkb * block_bytes(G);
     uint32_t b_code_off[TN], b_param_off[TN];           // row blocks beyond N are clamped (never stored)
 #pragma unroll
@@ -324,20 +327,22 @@ __global__ __launch_bounds__(64 * WGM * WGN * KS, 2) void gemm_pipe_kernel(const
     for (int s = 0; s < 4; ++s)
         frag_off[s] = (uint32_t)((wm + (lane & 31)) * kRowBytes + (((4 * b_h + s) ^ ((lane >> 1) & 7)) << 4));
 
-    u32x4 a_reg[AD][PA];
     constexpr int NCH = E8 ? 2 : 1;                     // 16-byte chunks per lane, slice and operand block
     u32x4 bset[PD][TN][NCH];
     uint32_t pwset[PD][TN];
     half8_t fa[2][TM], fb[2][TN];
 
-    auto load_a = [&](auto pa_c, int kt, int set) {
-        const uint32_t k0 = (uint32_t)min(kt, KT - 1) * BK;
+    // (slices beyond the range are requested through a resource of no bytes: the number of requests stays, memory is not read)
+    auto load_a = [&](auto pa_c, int kt, uint32_t stage_off) {
+        const __amdgpu_buffer_rsrc_t a_rsrc = rsrc_if(a_base, kt < kt_end);
+        const uint32_t k0 = (uint32_t)kt * BK;
 #pragma unroll
         for (int p = 0; p < decltype(pa_c)::value; ++p)
-            a_reg[set][p] = __builtin_amdgcn_raw_buffer_load_b128(a_rsrc, (int)a_pass_off[p], (int)(k0 * 2), 0);
+            load_to_lds_b128(a_rsrc, smem + stage_off + a_lds_off + p * RP * kRowBytes, a_pass_off[p], k0 * 2);
     };
     auto load_b = [&](int kt, int set) {
-        const uint32_t k0 = (uint32_t)min(kt, KT - 1) * BK;
+        const __amdgpu_buffer_rsrc_t b_code_rsrc = rsrc_if(b_codes, kt < kt_end), b_param_rsrc = rsrc_if(b_params, kt < kt_end);
+        const uint32_t k0 = (uint32_t)kt * BK;
         // chunk (k0/32) of the row block's codes starts (k0/32)*256 bytes in; the parameter words of
         // group k0/G start (k0/G)*64 bytes into the row block's parameters
         // (8-bit: the slice is block k0/64 of 1 KiB with 16 parameter words)
@@ -351,11 +356,6 @@ __global__ __launch_bounds__(64 * WGM * WGN * KS, 2) void gemm_pipe_kernel(const
                                                                         code_soff, 0);
             pwset[set][j] = __builtin_amdgcn_raw_buffer_load_b32(b_param_rsrc, (int)b_param_off[j], param_soff, 0);
         }
-    };
-    auto store_a = [&](auto pa_c, uint32_t stage_off, int set) {
-#pragma unroll
-        for (int p = 0; p < decltype(pa_c)::value; ++p)
-            *reinterpret_cast<u32x4*>(smem + stage_off + a_lds_off + p * RP * kRowBytes) = a_reg[set][p];
     };
     auto read_frags = [&](auto tm_c, uint32_t stage_off, int s, half8_t (&dst)[TM]) {
         const unsigned char* base = smem + stage_off + frag_off[s];
@@ -428,14 +428,13 @@ __global__ __launch_bounds__(64 * WGM * WGN * KS, 2) void gemm_pipe_kernel(const
     // Instruction order inside one sub-step: after every MFMA a few of the vector instructions that
     // prepare the next sub-step's operands, so that a single wavefront keeps the matrix pipe busy
     // (an MFMA of this shape occupies it for 32 cycles, its issue only for 4).
-    auto interleave = [&](auto tm_c, auto dsw, auto vmem) {
+    auto interleave = [&](auto tm_c, auto vmem) {
         constexpr int TMX = decltype(tm_c)::value, kMfma = TMX * TN;
 #pragma unroll
         for (int i = 0; i < kMfma; ++i) {
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);          // one MFMA
             if (i < TMX) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);      // one LDS fragment read
             __builtin_amdgcn_sched_group_barrier(0x002, kMfma >= 8 ? 5 : 9, 0);     // vector ALU
-            if (i < decltype(dsw)::value) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);    // LDS write
             if (i < decltype(vmem)::value) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);   // global load
         }
     };
@@ -445,72 +444,89 @@ __global__ __launch_bounds__(64 * WGM * WGN * KS, 2) void gemm_pipe_kernel(const
     // The K range on TMX of the wavefront's TM row blocks (all of them, but in a last row tile)
     auto k_loop = [&](auto tm_c) {
         using IPA = std::integral_constant<int, SHORT ? decltype(tm_c)::value * 32 / RP : PA>;
+        constexpr int PAX = IPA::value, NB = ITN2::value;
         // One K slice.  On entry: stage `cur` holds slice kt; fa[0], fb[0] hold its sub-step 0 operands;
-        // bset[set] holds its codes; the next PD - 1 slices' codes and the next AD slices' activations are in flight.
-        auto step = [&](int kt, int set, uint32_t cur, uint32_t nxt) {
-            // sub-step 0: operands of sub-step 1; publish slice kt+1's activations and, the staging
-            // registers being free again, request those of slice kt+1+AD at once
+        // bset[set] holds its codes; the next PD - 1 slices' codes and the next L - 1 slices' activations are in flight.
+        // (REST: one of the range's last two slices, which request nothing)
+        auto step = [&](auto rest_c, int kt, int set, uint32_t cur, uint32_t nxt, uint32_t last) {
+            constexpr bool REST = decltype(rest_c)::value;
+            // sub-step 0: operands of sub-step 1
             read_frags(tm_c, cur, 1, fa[1]);
             dequant_frags(set, 1, fb[1]);
-            store_a(IPA{}, nxt, (set + 1) % AD);
-            load_a(IPA{}, kt + 1 + AD, (set + 1) % AD);
             mfma_block(tm_c, fa[0], fb[0]);
-            interleave(tm_c, IPA{}, IPA{});
+            interleave(tm_c, I0{});
             __builtin_amdgcn_sched_barrier(0);
             // sub-step 1: operands of sub-step 2
             read_frags(tm_c, cur, 2, fa[0]);
             dequant_frags(set, 2, fb[0]);
             mfma_block(tm_c, fa[1], fb[1]);
-            interleave(tm_c, I0{}, I0{});
+            interleave(tm_c, I0{});
             __builtin_amdgcn_sched_barrier(0);
-            __syncthreads();                // slice kt+1 is complete in stage `nxt`
+            wait_loads<REST ? 0 : (L - 1) * NB + (L - 2) * PAX>();
+            __builtin_amdgcn_s_barrier();   // slice kt+1 is complete in stage `nxt`, and nobody reads slice kt-1 any more
+            asm volatile("" ::: "memory");
             __builtin_amdgcn_sched_barrier(0);
-            // sub-step 2: operands of sub-step 3 (last use of this slice's codes)
+            // sub-step 2: operands of sub-step 3 (last use of this slice's codes); activations into the stage of slice kt-1
             read_frags(tm_c, cur, 3, fa[1]);
             dequant_frags(set, 3, fb[1]);
+            if (!REST) load_a(IPA{}, kt + L, last);
             mfma_block(tm_c, fa[0], fb[0]);
-            interleave(tm_c, I0{}, I0{});
+            interleave(tm_c, I0{});
             __builtin_amdgcn_sched_barrier(0);
             // sub-step 3: operands of the next slice's sub-step 0; this slice's code registers are free,
             // so the codes of slice kt+PD are requested into them
-            load_b(kt + PD, set);
+            if (!REST) load_b(kt + PD, set);
             read_frags(tm_c, nxt, 0, fa[0]);
             dequant_frags((set + 1) % PD, 0, fb[0]);
             mfma_block(tm_c, fa[1], fb[1]);
-            interleave(tm_c, I0{}, ITN2{});
+            interleave(tm_c, ITN2{});
             __builtin_amdgcn_sched_barrier(0);
         };
 
         // ---- prologue
-        load_a(IPA{}, kt_begin, 0);
+        const uint32_t ring = KS == 2 ? (uint32_t)half * S * kStageBytes : 0u;
+        // (in the order that the loop keeps up: slice kt requests activations L slices on, then codes PD slices on)
 #pragma unroll
-        for (int d = 0; d < PD; ++d) load_b(kt_begin + d, d);
-        const uint32_t ring = KS == 2 ? (uint32_t)half * kStages * kStageBytes : 0u;
-        store_a(IPA{}, ring, 0);
-#pragma unroll
-        for (int d = 1; d <= AD; ++d) load_a(IPA{}, kt_begin + d, d % AD);
-        __syncthreads();
+        for (int d = -(PD > L ? PD : L); d < 0; ++d) {
+            if (d + L >= 0) load_a(IPA{}, kt_begin + d + L, ring + (d + L) * kStageBytes);
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_sched_barrier(0);
+            if (d + PD >= 0) load_b(kt_begin + d + PD, d + PD);
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        wait_loads<(L - 1) * PAX + (PD < L ? PD : L) * NB>();
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
         read_frags(tm_c, ring, 0, fa[0]);
         dequant_frags(0, 0, fb[0]);
 
-        uint32_t s0 = ring, s1 = ring + kStageBytes, s2 = ring + 2 * kStageBytes;     // current, next, the one after
+        uint32_t so[S];                                     // stages of slices kt, kt + 1, ..., kt - 1
+#pragma unroll
+        for (int i = 0; i < S; ++i) so[i] = ring + i * kStageBytes;
         auto advance_ring = [&]() {                         // by two slices
-            const uint32_t tmp = s0;
-            s0 = s2;
-            s2 = s1;
-            s1 = tmp;
+            uint32_t tmp[S];
+#pragma unroll
+            for (int i = 0; i < S; ++i) tmp[i] = so[(i + 2) % S];
+#pragma unroll
+            for (int i = 0; i < S; ++i) so[i] = tmp[i];
         };
-        for (int kt = kt_begin; kt < kt_end; kt += PD) {
-            step(kt, 0, s0, s1);
-            step(kt + 1, 1, s1, s2);
-            advance_ring();
-            if (PD == 4) {                                  // (K ranges are whole pairs of slices)
-                if (kt + 2 >= kt_end) break;
-                step(kt + 2, 2 % PD, s0, s1);
-                step(kt + 3, 3 % PD, s1, s2);
+        // (K ranges are whole pairs of slices)
+        int kt = kt_begin;
+        for (; kt + PD <= kt_end; kt += PD) {
+#pragma unroll
+            for (int d = 0; d < PD; d += 2) {
+                step(std::false_type{}, kt + d, d, so[0], so[1], so[S - 1]);
+                step(std::false_type{}, kt + d + 1, d + 1, so[1], so[2], so[0]);
                 advance_ring();
             }
         }
+        if (PD == 4 && kt < kt_end) {
+            step(std::true_type{}, kt, 0, so[0], so[1], so[S - 1]);
+            step(std::true_type{}, kt + 1, 1, so[1], so[2], so[0]);
+        }
+        // (what was requested beyond the range has arrived before the stages are used otherwise)
+        wait_loads<0>();
     };
     if constexpr (SHORT) {
         static_assert(PA * RP == TM * 32, "a loader pass is whole row blocks");
