@@ -11,14 +11,17 @@
 // dequant entry points produce, and the activations of row l%16 of a tile of 16 rows of X at the same k.  One dequantised
 // operand serves MT tiles of X, and one set of activation registers R row blocks.
 //
-// What bounds it: the weights come from memory and X (2 M K bytes, of which every workgroup needs all) from L2.  X as the
-// matrix core takes it, 16 rows at a stride of 2 K bytes per load, comes at 13 bytes per clock and compute unit (4096 x
-// 13696 at M = 16: 21.7 us); loads of whole rows of a k block, turned around in LDS, bring that to 13.9 us.  After that it
-// is the arithmetic of the dequantisation, 15 vector instructions per word of eight weights (bfloat16: 19), which is why
-// one operand should serve many rows.  In flight per wavefront are two k blocks of weights (four where it has a single row
-// block) and two of X, or one where registers are short (XD); four of both, and sixteen wavefronts, took up to 15 % longer.
-// Against the GEMM at 4096 x 4096, 27392 x 4096, 4096 x 13696 (us): bfloat16 at M = 16 35.0 -> 6.5, 38.6 -> 19.6, 102 -> 13.7;
-// groups of 64 at M = 16 15.1 -> 6.3, 27.3 -> 18.0, 30.7 -> 13.4; 8-bit codes at M = 45 17.6 -> 11.0, (not used), 33.3 -> 28.4.
+// What bounds it: the weights come from memory and X (2 M K bytes, of which every workgroup needs all) from L2, and what a
+// wavefront waits for, dequantises and multiplies does not overlap well with eight wavefronts on a compute unit.  27392 x 4096 at M =
+// 45 takes 26 us; without X 24, without X and the dequantisation 23, the weights alone 16.  X as the matrix core takes it, 16 rows
+// at a stride of 2 K bytes per load, comes at 13 bytes per clock and compute unit (4096 x 13696 at M = 16: 21.7 us), so whole rows
+// of a k block are loaded and turned around in LDS.  From nine rows on they go there without a register in between, one k block
+// ahead: 4096 x 4096 at M = 16, 24, 45 and 64 6.7 -> 6.2, 8.6 -> 7.2, 11.1 -> 8.8 and 12.3 -> 10.0 us (bfloat16); two and four k blocks
+// of X in flight were 0 - 10 % slower than one, as were three and four of weights.  Up to eight rows, which are one or two loads
+// per k block, registers in between are 2 - 8 % faster.  An operand is dequantised by 15 vector instructions (bfloat16: 19), so one
+// should serve many rows.
+// Against the GEMM at 4096 x 4096, 27392 x 4096, 4096 x 13696 (us): bfloat16 at M = 16 35.0 -> 6.2, 38.6 -> 20.3, 102 -> 13.1;
+// groups of 64 at M = 16 15.1 -> 6.2, 27.3 -> 18.0, 30.7 -> 13.4; 8-bit codes at M = 45 17.6 -> 10.1, (not used), 33.3 -> 28.0.
 //
 // Every weight is rounded to 16 bits before the product, as it is in the GEMM, but in the instances on exact codes (EX below),
 // which apply scale and bias in fp32 as e0m4_gemv.hip and e0m4_gemv_mfma.hip do.  Calls of those two go to EX instances only.
@@ -26,6 +29,7 @@
 #include "e0m4_host.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace e0m4 {
 
@@ -38,12 +42,18 @@ typedef float floatx2 __attribute__((ext_vector_type(2)));
 
 constexpr int kDqWaves = 8;
 constexpr int kDqThreads = kDqWaves * 64;
-constexpr int kDqMaxR = 4;                      // row blocks per wavefront
-// row blocks per workgroup (so that two wavefronts at least share a row block; one, where R is two at most)
+// Row blocks per wavefront, for so many tiles of X: as many as the registers hold (exact codes keep a k block's sums beside the
+// others), but not more than five.  Five in place of two groups of wavefronts of three: 20000 x 3072 at M = 32 15.2 -> 14.0 us; seven and
+// eight in place of two groups of four 32768 x 2048 17.6 and 21.9.
+constexpr int dq_max_r(int MT, bool exact) { return exact ? (MT == 4 ? 3 : 4) : MT == 4 ? 4 : 5; }
+// row blocks per workgroup (so that two wavefronts at least share a row block)
 constexpr int kDqMaxSlots = 16;
 constexpr int kDqMaxM = 64;                     // rows of X per workgroup
 constexpr int kDqMaxParts = 2;
 constexpr int kTargetWorkgroups = 256;          // one workgroup per compute unit
+
+// k blocks of weights that a wavefront has under way (a round of the loop)
+constexpr int dq_weights_ahead(int R) { return R == 1 ? 4 : 2; }
 
 struct DqPlan {
     int64_t grid;
@@ -51,6 +61,15 @@ struct DqPlan {
     int parts;                                  // of the rows of X
     int wr, r;                                  // groups of wavefronts, row blocks per group
 };
+
+template <int N, int I = 0, typename F>
+__device__ inline void for_each_of(F&& f)               // f(0), ..., f(N - 1), the numbers as constants
+{
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        for_each_of<N, I + 1>(f);
+    }
+}
 
 __device__ inline half2_t dq_pair(half2_t w1, half2_t bias2, half2_t scale2)
 {
@@ -74,9 +93,10 @@ __global__ __launch_bounds__(kDqThreads, 2) void gemv_dq_kernel(const half_t* __
     constexpr int NP = FMT == kDqFormatE8 ? 2 : 4;            // pieces of X (and MFMAs) per k block
     static_assert(XE == NP || (XE < NP && MT == 1), "a part of the rows: of a single tile");
     constexpr int BLK = NP * 32;                        // weights of a row per k block
-    constexpr int DW = R == 1 ? 4 : 2;
-    constexpr int XD = MT <= 2 || (MT == 3 && R <= 2) || FMT == kDqFormatE8 ? 2 : 1;
-    constexpr int U = DW > XD ? DW : XD;                // k blocks per unrolled round of the loop
+    constexpr int DW = dq_weights_ahead(R);
+    constexpr bool kFew = XE < NP;                      // X through registers, XD k blocks ahead
+    constexpr int XD = 2;
+    static_assert(DW >= XD, "a round of the loop is DW k blocks");
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int64_t N = N32;
     const int K = (int)K32;
@@ -108,33 +128,32 @@ __global__ __launch_bounds__(kDqThreads, 2) void gemv_dq_kernel(const half_t* __
     const uint32_t code_voff = lane * 16;
     const uint32_t param_voff = (uint32_t)nkb * kBlockCodeBytes + 4 * (((g_l * kCodesPerChunk) >> group_shift) * kBlockRows + n_l);
     const uint32_t pb = 4 * pw;
-    // X on its way to the matrix core: load number e of a tile brings RPI whole rows of the k block, 16 bytes per lane; the
-    // wavefront writes them to a piece of LDS of its own and reads them back as operands.  (row, piece) lies at row * RB +
-    // 16 * (piece ^ swizzle(row)): the 16 rows of an operand read fall into 16 different bank groups.
+    // X on its way to the matrix core: load number e of a tile brings RPI whole rows of the k block, 16 bytes per lane, to a piece
+    // of LDS of the wavefront's own, where lane l's come to lie at 16 l; the wavefront reads them back as operands.  (row, piece)
+    // lies at row * RB + 16 * (piece ^ swizzle(row)), by the choice of the piece that a lane loads: the 16 rows of an operand read
+    // fall into 16 different bank groups.
     constexpr int PPR = NP * 4, RPI = 64 / PPR, RB = PPR * 16;
     unsigned char* xl = smem + wave * (MT * 16 * RB);
-    const int x_a = lane / PPR, x_j = lane % PPR;
     auto swizzle = [](int row) -> int { return FMT == kDqFormatE8 ? (row >> 1) & 7 : row & 15; };
     // A last k block that K does not fill (groups of 32 and 64): instead of chunks of X that do not exist the block's first
     // is read, and zeroed before use; their codes and parameters are stored as zeros.
     const int tail_kb = (K % BLK) != 0 ? nkb - 1 : -1;
-    const bool in_tail = (nkb - 1) * BLK + x_j * 8 < K;
-    const uint32_t x_tail_back = in_tail ? 0u : (uint32_t)((x_j / NP) * NP * 16);
-    uint32_t x_voff[MT][XE];
-    uint32_t x_wr[XE], x_rd[NP];
+    const bool none = (nkb - 1) * BLK + g_l * (NP * 8) >= K;
+    uint32_t x_voff[MT][XE], x_back[XE];
+    uint32_t x_rd[NP];
 #pragma unroll
     for (int e = 0; e < XE; ++e) {
-        const int row = e * RPI + x_a;
+        const int row = e * RPI + lane / PPR, j = (lane % PPR) ^ swizzle(row);
 #pragma unroll
-        for (int i = 0; i < MT; ++i) x_voff[i][e] = ((uint32_t)min(16 * i + row, M - 1) * K32 + (uint32_t)(x_j * 8)) * 2;
-        x_wr[e] = (uint32_t)(row * RB + ((x_j ^ swizzle(row)) << 4));
+        for (int i = 0; i < MT; ++i) x_voff[i][e] = ((uint32_t)min(16 * i + row, M - 1) * K32 + (uint32_t)(j * 8)) * 2;
+        x_back[e] = (nkb - 1) * BLK + j * 8 < K ? 0u : (uint32_t)((j / NP) * NP * 16);
     }
 #pragma unroll
     for (int e = 0; e < NP; ++e) x_rd[e] = (uint32_t)(n_l * RB + (((g_l * NP + e) ^ swizzle(n_l)) << 4));
 
     u32x4 c[DW][R];
     uint32_t pwd[DW][R];
-    u32x4 xr[XD][MT][XE];
+    u32x4 xr[kFew ? XD : 1][XE];
     // (a k block beyond the last is requested through a resource of no bytes: zeros, without an access to memory)
     auto load_w = [&](int kb, int d) {
         const __amdgpu_buffer_rsrc_t rsrc = rsrc_if(wg_base, kb < nkb);
@@ -146,18 +165,24 @@ __global__ __launch_bounds__(kDqThreads, 2) void gemv_dq_kernel(const half_t* __
     };
     auto load_x = [&](int kb, int d) {
         const __amdgpu_buffer_rsrc_t rsrc = rsrc_if(X, kb < nkb);
-        const uint32_t back = kb == tail_kb ? x_tail_back : 0u;
 #pragma unroll
         for (int i = 0; i < MT; ++i)
 #pragma unroll
-            for (int e = 0; e < XE; ++e)
-                xr[d][i][e] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)(x_voff[i][e] - back), kb * RB, 0);
+            for (int e = 0; e < XE; ++e) {
+                const uint32_t voff = kb == tail_kb ? x_voff[i][e] - x_back[e] : x_voff[i][e];
+                if constexpr (kFew) xr[d][e] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)voff, kb * RB, 0);
+                else load_to_lds_b128(rsrc, xl + (i * 16 + e * RPI) * RB, voff, (uint32_t)kb * RB);
+            }
     };
     // (in the order of use: a wait for one request is a wait for all before it)
 #pragma unroll
-    for (int d = 0; d < U; ++d) {
-        if (d < XD) load_x(wk + d * wk_n, d);
-        if (d < DW) load_w(wk + d * wk_n, d);
+    for (int d = 0; d < DW; ++d) {
+        if (d < (kFew ? XD : 1)) load_x(wk + d * wk_n, d);
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        load_w(wk + d * wk_n, d);
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
     }
 
     // the weight operand of MFMA p: word p of the chunk (8-bit codes: words 2p and 2p + 1)
@@ -226,33 +251,49 @@ __global__ __launch_bounds__(kDqThreads, 2) void gemv_dq_kernel(const half_t* __
 #pragma unroll
         for (int i = 0; i < MT; ++i) acc[r][i] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-    // one k block (number u of a round), with everything it frees requested again DW or XD of this wavefront's blocks on
-    auto block = [&](int kb, int u) {
-        const int xd = u % XD;
-        const bool none = kb == tail_kb && !in_tail;
+    // One k block (number u of a round).  Its X goes from LDS to registers, whereupon this wavefront's next block's is requested into
+    // the same place; its weights' registers are requested again for DW of this wavefront's blocks on.
+    // (REST: one of the blocks after the last whole round, whose own requests for weights nobody uses and the compiler may leave out)
+    auto block = [&](auto rest_c, int kb, auto u_c) {
+        constexpr int u = decltype(u_c)::value;
+        if constexpr (kFew) {
 #pragma unroll
-        for (int i = 0; i < MT; ++i)
+            for (int e = 0; e < XE; ++e) *reinterpret_cast<u32x4*>(xl + e * (RPI * RB) + lane * 16) = xr[u % XD][e];
+            load_x(kb + XD * wk_n, u % XD);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");     // read back by the wavefront that wrote it
+            __builtin_amdgcn_wave_barrier();
+        } else {
+            // (behind this block's X, requested in the block before, come only that block's weights; behind the first block's all
+            // of the prologue's)
+            if (u == 0 && kb < wk_n) wait_loads<DW * 2 * R>();
+            else wait_loads<(decltype(rest_c)::value && u > 0) ? 0 : 2 * R>();
+        }
+        half8_t xa[NP][MT];
 #pragma unroll
-            for (int e = 0; e < XE; ++e) {
-                half8_t v = __builtin_bit_cast(half8_t, xr[xd][i][e]);
-                if (none) v = half8_t{0, 0, 0, 0, 0, 0, 0, 0};
-                *reinterpret_cast<half8_t*>(xl + i * (16 * RB) + x_wr[e]) = v;
-            }
-        load_x(kb + XD * wk_n, xd);
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");     // read back by the wavefront that wrote it
-        __builtin_amdgcn_wave_barrier();
+        for (int p = 0; p < NP; ++p)
+#pragma unroll
+            for (int i = 0; i < MT; ++i) xa[p][i] = *reinterpret_cast<const half8_t*>(xl + i * (16 * RB) + x_rd[p]);
+        if constexpr (!kFew) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");          // read before it is written again
+            __builtin_amdgcn_sched_barrier(0);
+            load_x(kb + wk_n, 0);
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (kb == tail_kb && none) {
+#pragma unroll
+            for (int p = 0; p < NP; ++p)
+#pragma unroll
+                for (int i = 0; i < MT; ++i) xa[p][i] = half8_t{0, 0, 0, 0, 0, 0, 0, 0};
+        }
         if constexpr (EX) {
-            half8_t xa[NP][MT];
             floatx4 sx[MT];
 #pragma unroll
             for (int i = 0; i < MT; ++i) sx[i] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int p = 0; p < NP; ++p)
 #pragma unroll
-                for (int i = 0; i < MT; ++i) {
-                    xa[p][i] = *reinterpret_cast<const half8_t*>(xl + i * (16 * RB) + x_rd[p]);
-                    sx[i] = mfma(xa[p][i], ones8, sx[i]);
-                }
+                for (int i = 0; i < MT; ++i) sx[i] = mfma(xa[p][i], ones8, sx[i]);
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 floatx4 a[MT];
@@ -273,34 +314,33 @@ __global__ __launch_bounds__(kDqThreads, 2) void gemv_dq_kernel(const half_t* __
         } else
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
-            half8_t xa[MT];
-#pragma unroll
-            for (int i = 0; i < MT; ++i) xa[i] = *reinterpret_cast<const half8_t*>(xl + i * (16 * RB) + x_rd[p]);
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 const half8_t w = dequant(c[u % DW][r], pwd[u % DW][r], p);
 #pragma unroll
                 for (int i = 0; i < MT; ++i)
-                    acc[r][i] = mfma(xa[i], w, acc[r][i]);
+                    acc[r][i] = mfma(xa[p][i], w, acc[r][i]);
             }
-            if (MT >= 3) __builtin_amdgcn_sched_barrier(0);         // (or all operands of the block are read first, and spilled)
         }
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
         load_w(kb + DW * wk_n, u % DW);
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();                // X is read before the next block's is written
+        asm volatile("" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);              // (or blocks are mixed, and registers spilled)
     };
     int kb = wk;
-    for (; kb + (U - 1) * wk_n < nkb; kb += U * wk_n) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) block(kb + u * wk_n, u);
+    for (; kb + (DW - 1) * wk_n < nkb; kb += DW * wk_n) {
+        for_each_of<DW>([&](auto u_c) { block(std::false_type{}, kb + decltype(u_c)::value * wk_n, u_c); });
     }
-#pragma unroll
-    for (int u = 0; u < U - 1; ++u)
-        if (kb + u * wk_n < nkb) block(kb + u * wk_n, u);
+    for_each_of<DW - 1>([&](auto u_c) {
+        if (kb + decltype(u_c)::value * wk_n < nkb) block(std::true_type{}, kb + decltype(u_c)::value * wk_n, u_c);
+    });
 
     // The wavefronts' sums, added in wavefront order: lane l holds rows 4 (l/16) .. + 3 of every tile, weight row l%16
     floatx4* red = reinterpret_cast<floatx4*>(smem);    // [wavefronts][R][MT][64]
+    wait_loads<0>();                                    // (what was requested beyond the last block has arrived)
     __syncthreads();                                    // every wavefront has finished with its X
 #pragma unroll
     for (int r = 0; r < R; ++r)
@@ -326,7 +366,6 @@ __global__ __launch_bounds__(kDqThreads, 2) void gemv_dq_kernel(const half_t* __
 
 // One workgroup per compute unit where the row blocks allow it (its eight wavefronts fill the unit's registers): with more
 // than 256 x 16 of them, as few whole rounds as possible.
-// (`exact`: the registers of four tiles of X and their sums leave room for two row blocks per wavefront)
 bool make_dq_plan(int64_t M, int64_t N, int64_t K, DqPlan& p, bool exact = false)
 {
     if (M < 2 || M > kDqMaxParts * kDqMaxM || N <= 0 || K <= 0) return false;
@@ -340,7 +379,7 @@ bool make_dq_plan(int64_t M, int64_t N, int64_t K, DqPlan& p, bool exact = false
     p.rb_base = (int)(nrb / p.grid);
     p.rb_rem = (int)(nrb % p.grid);
     p.wr = 1;
-    const int max_r = exact && (M + p.parts - 1) / p.parts > 48 ? 2 : kDqMaxR;
+    const int max_r = dq_max_r((int)(((M + p.parts - 1) / p.parts + 15) / 16), exact);
     while (p.wr * max_r < most) p.wr *= 2;
     p.r = (int)((most + p.wr - 1) / p.wr);
     return true;
@@ -363,20 +402,20 @@ int launch_dq(const DqPlan& p, const void* X, int64_t M, const void* packed, int
     return check_launch();
 }
 
+template <DqFormat FMT, int MT, int R, int XE, bool EX>
+int launch_dq_at_r(const DqPlan& p, const void* X, int64_t M, const void* packed, int64_t N, int64_t K,
+                   int group, void* Y, hipStream_t stream)
+{
+    if (p.r == R) return launch_dq<FMT, MT, R, XE, EX>(p, X, M, packed, N, K, group, Y, stream);
+    if constexpr (R < dq_max_r(MT, EX)) return launch_dq_at_r<FMT, MT, R + 1, XE, EX>(p, X, M, packed, N, K, group, Y, stream);
+    return E0M4_ERR_SHAPE;
+}
+
 template <DqFormat FMT, int MT, int XE, bool EX>
 int launch_dq_r(const DqPlan& p, const void* X, int64_t M, const void* packed, int64_t N, int64_t K,
                 int group, void* Y, hipStream_t stream)
 {
-    switch (p.r) {
-        case 1: return launch_dq<FMT, MT, 1, XE, EX>(p, X, M, packed, N, K, group, Y, stream);
-        case 2: return launch_dq<FMT, MT, 2, XE, EX>(p, X, M, packed, N, K, group, Y, stream);
-        default: break;
-    }
-    if constexpr (!EX || MT < 4) {
-        if (p.r == 3) return launch_dq<FMT, MT, 3, XE, EX>(p, X, M, packed, N, K, group, Y, stream);
-        if (p.r == 4) return launch_dq<FMT, MT, 4, XE, EX>(p, X, M, packed, N, K, group, Y, stream);
-    }
-    return E0M4_ERR_SHAPE;
+    return launch_dq_at_r<FMT, MT, 1, XE, EX>(p, X, M, packed, N, K, group, Y, stream);
 }
 
 template <DqFormat FMT, bool EX = false>

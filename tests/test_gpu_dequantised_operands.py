@@ -86,3 +86,33 @@ def test_few_rows_of_a_tile(e0m4, oracle, M, N, K, G, workgroups):
     Yref, absdot = oracle.matmul(X[:M], What)
     check_matmul(Y, Yref, absdot, "M=%d" % M)
     assert torch.equal(Y, Y16[:M])
+
+
+# five row blocks per wavefront (three with exact codes and four tiles of X), one to seven k blocks per wavefront and a last one
+# that K does not fill
+@pytest.mark.parametrize("fmt,M", [("e0m4", 16), ("e0m4", 48), ("bf16", 17), ("bf16", 33), ("e0m8", 48), ("exact", 49), ("exact", 64)])
+@pytest.mark.parametrize("K", [256, 1088, 2176, 3200, 6272])
+def test_most_row_blocks_per_wavefront(e0m4, oracle, fmt, M, K):
+    N, workgroups, G = (380, 5, 64) if fmt != "exact" else (333, 7, 128)
+    if K % G:
+        pytest.skip("K is not whole groups")
+    e0m4.e0m4_set_knob("gemv_mfma", 7 if fmt == "exact" else 4)
+    e0m4.e0m4_set_knob("gemv_workgroups", workgroups)
+    try:
+        if fmt == "bf16":
+            codes, What, _ = assert_bf16_quantize_exact(e0m4, oracle, synth_inputs.weights_bf16(N, K, seed=4970 + K), G)
+            X = synth_inputs.activations_bf16(M, K, seed=4980 + M)
+            Y = e0m4.e0m4_bf16_matmul(bf_dev(X), codes, N, K, G)
+            check_bf16_matmul(oracle, Y, *oracle.bf16_matmul(X, What), "bf16")
+            return
+        X, W = synth_inputs.activations(M, K, seed=4980 + M, outlier_frac=0.01), synth_inputs.weights(N, K, seed=4970 + K)
+        if fmt == "e0m8":
+            codes, What = test_gpu_e0m8.assert_quantize_exact(e0m4, oracle, W, G)
+            Y = e0m4.e0m8_matmul(to_dev(X), codes, N, K, G)
+        else:
+            (codes, _, _), What = assert_quantize_exact(e0m4, oracle, W, G)
+            Y = e0m4.e0m4_matmul(to_dev(X), codes, None, None, N, K, G)
+        check_matmul(Y, *oracle.matmul(X, What), fmt)
+    finally:
+        e0m4.e0m4_set_knob("gemv_mfma", 0)
+        e0m4.e0m4_set_knob("gemv_workgroups", 0)
