@@ -134,9 +134,9 @@ int e0m4_unpack_codes(const void* codes, int64_t N, int64_t K, int group, void* 
  *            workgroups on the compute units (three on small weights): the
  *            small-batch kernel on those chunks in one launch or, in plain calls
  *            and mostly where they make more than one round, the dequantising
- *            kernel's form on exact codes; otherwise, plain calls, any group,
- *            N * K <= 7e7 (and 256 <= K <= 9216 for M > 48), the dequantising
- *            kernel.
+ *            kernel's form on exact codes; otherwise, any group, the
+ *            dequantising kernel (M > 32: K <= 12800, M > 48: 256 <= K <= 7680
+ *            and N * K <= 1e8).
  *   M >= 9 otherwise, and 2 <= M <= 8 when M * N * K is about 3.8e8 or
  *            more (the vector kernel's time grows with M): MFMA GEMM path
  *            (tiles of 64 x 256, 128 x 256 or 256 x 256 outputs, whichever
@@ -204,7 +204,9 @@ int e0m4_matmul_static(const void* X_f16, int64_t M, const void* codes, int64_t 
  * On the decode paths (M <= 8, and the small-batch path of e0m4_matmul up to
  * M = 16) everything happens inside the one kernel; for larger M the epilogue
  * runs inside the GEMM kernels (or the kernel that adds the K splits) and the
- * rms-norm is a launch of its own that writes x' to the workspace.
+ * rms-norm is a launch of its own that writes x' to the workspace; up to M = 64
+ * the dequantising kernel of e0m4_matmul follows it where no other operator is
+ * selected.
  * Workspace: e0m4_fused_workspace_bytes() bytes, same rules as e0m4_matmul.
  * With no operator selected the result is that of e0m4_matmul (up to the order of
  * the fp32 additions and the rounding of the weights: the two may choose different
@@ -261,8 +263,9 @@ int e0m4_kv_append(void* cache_f16, int64_t max_seq, int64_t row_elems,
  *     (and N <= 2^24): the MFMA GEMM kernels, workspace of
  *     e0m8_workspace_bytes() bytes under the rules of e0m4_matmul (17 <= M <=
  *     32 with K <= 2048 and N * K <= 1e7: the matrix-core variant on two
- *     chunks of rows in one launch instead; otherwise M <= 64 with N * K <= 1e8,
- *     and 256 <= K <= 9216 for M > 48: the dequantising kernel of e0m4_matmul).  Other M > 16:
+ *     chunks of rows in one launch instead; otherwise M <= 64, with K <= 8192 for
+ *     M > 32 and 256 <= K <= 6144 and N * K <= 1.2e8 for M > 48: the dequantising
+ *     kernel of e0m4_matmul).  Other M > 16:
  *     the decode kernel on 8 rows of X at a time (needs N % 8 == 0).
  * Pointer, alignment, stream and error rules as for the E0M4 entry points.
  */

@@ -254,19 +254,37 @@ size_t e0m4_workspace_bytes(int64_t M, int64_t N, int64_t K, int group)
 // rounded up to 256 bytes, then the partial sums of the split along K.
 static size_t norm_bytes(int64_t M, int64_t K) { return ((size_t)M * (size_t)K * 2 + 255) & ~(size_t)255; }
 
-// Which kernel family serves a fused matmul: 0 the decode kernel, 2 the small-batch kernel on the matrix
-// cores (both: everything in one launch), 3 that kernel on chunks of rows, 4 (no operators) the kernel on exact codes, 1 the GEMM
-// kernels (rms-norm, if any, as a launch of its own before them).
-static int fused_path(const Fusion& f, int64_t M, int64_t N, int64_t K, int group)
+// Which kernel family serves a fused matmul.
+enum FusedPath {
+    kFusedNone = -1,
+    kFusedVector,                                       // the decode kernel, everything in one launch
+    kFusedGemm,                                         // (this and the last: an rms-norm is a launch of its own before it)
+    kFusedSmallBatch,                                   // the small-batch kernel on the matrix cores, everything in one launch
+    kFusedChunks,                                       // that kernel on chunks of rows
+    kFusedExact,                                        // no operators: the kernel on exact codes
+    kFusedDq,                                           // an rms-norm alone or nothing: the kernel with dequantised operands
+};
+// An rms-norm alone (a projection into q, k and v, or to the vocabulary) and calls without operators may go where the plain call
+// goes.  Calls with a residual or the gated product keep the GEMM and its order of the sums, though the kernel with dequantised
+// operands would be faster: a stack of blocks amplifies the rounding of a residual stream that is summed in another order.
+static bool as_plain(const Fusion& f) { return !f.residual && !f.swiglu; }
+static FusedPath fused_path(const Fusion& f, int64_t M, int64_t N, int64_t K, int group)
 {
-    if (!f.any() && use_gemv_exact(M, N, K, group, kDqFormatFp16)) return 4;
+    if (!f.any() && use_gemv_exact(M, N, K, group, kDqFormatFp16)) return kFusedExact;
     // (groups of 64 and 32 from three rows on: 1.1 - 2 x the vector kernel and the GEMM there, 10 - 25 % slower than the
     // vector kernel at two rows)
-    if (knob("gemv_mfma") != 1 && gemv_mfma_fused_supported(f, M, N, K, group) &&
-        (group == 128 || M >= 3 || knob("gemv_mfma") == 6 || knob("gemv_mfma") == 9))
-        return 2;
-    if (small_batch_in_chunks(f, M, N, K, group)) return 3;
-    return (small_m_on_vector(M, N, K) && gemv_fused_supported(f, M, N, K)) ? 0 : 1;
+    const int k = knob("gemv_mfma");
+    if (k != 1 && gemv_mfma_fused_supported(f, M, N, K, group) && (group == 128 || M >= 3 || k == 6 || k == 9)) return kFusedSmallBatch;
+    if (small_batch_in_chunks(f, M, N, K, group)) return kFusedChunks;
+    if (small_m_on_vector(M, N, K) && gemv_fused_supported(f, M, N, K)) return kFusedVector;
+    return as_plain(f) && !gemm_steered() && N <= (int64_t)1 << 24 && use_gemv_dq(M, N, K, group, kDqFormatFp16) ? kFusedDq : kFusedGemm;
+}
+
+// What the launches of a path need of the workspace: the normalised X, the GEMM's partial sums behind it.
+static size_t fused_need(FusedPath path, bool normed, int64_t M, int64_t K, size_t gemm_bytes)
+{
+    if (path != kFusedGemm && path != kFusedDq) return 0;
+    return (normed ? norm_bytes(M, K) : 0) + (path == kFusedGemm ? gemm_bytes : 0);
 }
 
 size_t e0m4_fused_workspace_bytes(int64_t M, int64_t N, int64_t K, int group, int with_rmsnorm, int epilogue)
@@ -275,9 +293,8 @@ size_t e0m4_fused_workspace_bytes(int64_t M, int64_t N, int64_t K, int group, in
     if (epilogue != E0M4_EPILOGUE_NONE && epilogue != E0M4_EPILOGUE_SWIGLU) return 0;
     Fusion f;
     f.swiglu = epilogue == E0M4_EPILOGUE_SWIGLU;
-    f.residual = &f;                                    // (a call without any operator needs no more than one with a residual)
-    if (fused_path(f, M, N, K, group) != 1) return 0;
-    return (with_rmsnorm ? norm_bytes(M, K) : 0) + gemm_workspace_bytes(M, N, K, f.swiglu, true);
+    f.residual = &f;                                    // (a call without a residual needs no more than one with it)
+    return fused_need(fused_path(f, M, N, K, group), with_rmsnorm != 0, M, K, gemm_workspace_bytes(M, N, K, f.swiglu, true));
 }
 
 int e0m4_set_knob(const char* name, int value)
@@ -438,14 +455,14 @@ int e0m4_matmul_fused(const void* X, int64_t M, const void* rms_gamma, float rms
         (residual && !aligned16(residual)))
         return E0M4_ERR_ALIGN;
     hipStream_t st = (hipStream_t)stream;
-    const int path = fused_path(f, M, N, K, group);
-    if (path == 2) return launch_gemv_mfma_fused(f, X, M, codes, N, K, Y, st, 1, group);
-    if (path == 0) return launch_gemv_fused(f, X, M, codes, N, K, group, Y, st);
-    if (path == 4) return launch_gemv_exact(X, M, codes, N, K, kDqFormatFp16, Y, st);
-    if (path == 3) return launch_gemv_mfma_fused(f, X, M, codes, N, K, Y, st, row_chunks(M), group);      // rows are independent
+    const FusedPath path = fused_path(f, M, N, K, group);
+    if (path == kFusedSmallBatch) return launch_gemv_mfma_fused(f, X, M, codes, N, K, Y, st, 1, group);
+    if (path == kFusedVector) return launch_gemv_fused(f, X, M, codes, N, K, group, Y, st);
+    if (path == kFusedExact) return launch_gemv_exact(X, M, codes, N, K, kDqFormatFp16, Y, st);
+    if (path == kFusedChunks) return launch_gemv_mfma_fused(f, X, M, codes, N, K, Y, st, row_chunks(M), group);      // rows are independent
     if (N > (int64_t)1 << 24) return E0M4_ERR_SHAPE;    // 32-bit offsets in the GEMM epilogue
     const size_t nb = rms_gamma ? norm_bytes(M, K) : 0;
-    const size_t need = nb + gemm_workspace_bytes(M, N, K, f.swiglu, true);
+    const size_t need = fused_need(path, rms_gamma != nullptr, M, K, gemm_workspace_bytes(M, N, K, f.swiglu, true));
     if (need > 0) {
         if (!workspace) return E0M4_ERR_NULL;
         if (!aligned16(workspace)) return E0M4_ERR_ALIGN;
@@ -458,6 +475,7 @@ int e0m4_matmul_fused(const void* X, int64_t M, const void* rms_gamma, float rms
         x = workspace;
         f.gamma = nullptr;
     }
+    if (path == kFusedDq) return launch_gemv_dq(x, M, codes, N, K, group, kDqFormatFp16, Y, st);
     return launch_gemm_fused(f, x, M, codes, N, K, group, Y, static_cast<char*>(workspace) + nb,
                              workspace_bytes - nb, st);
 }
@@ -656,13 +674,14 @@ int e0m8_matmul(const void* X, int64_t M, const void* codes, int64_t N, int64_t 
     return E0M4_OK;
 }
 
-// Fused matmul on 8-bit codes: 2 the small-batch kernel, 0 the decode kernel, 1 the GEMM kernels (K % 128 == 0), -1 none.
-static int fused_path8(const Fusion& f, int64_t M, int64_t N, int64_t K)
+// Fused matmul on 8-bit codes (the GEMM kernels need K % 128 == 0).
+static FusedPath fused_path8(const Fusion& f, int64_t M, int64_t N, int64_t K)
 {
-    if (knob("gemv_mfma") != 1 && gemv_mfma8_fused_supported(f, M, N, K)) return 2;
-    if (small_batch8_in_chunks(f, M, N, K)) return 3;
-    if (small_m_on_vector(M, N, K) && gemv_fused_supported(f, M, N, 2 * K)) return 0;
-    return gemm_pipe_supported(K) && N <= (int64_t)1 << 24 ? 1 : -1;
+    if (knob("gemv_mfma") != 1 && gemv_mfma8_fused_supported(f, M, N, K)) return kFusedSmallBatch;
+    if (small_batch8_in_chunks(f, M, N, K)) return kFusedChunks;
+    if (small_m_on_vector(M, N, K) && gemv_fused_supported(f, M, N, 2 * K)) return kFusedVector;
+    if (!gemm_pipe_supported(K) || N > (int64_t)1 << 24) return kFusedNone;
+    return as_plain(f) && !gemm_steered() && use_gemv_dq(M, N, K, 128, kDqFormatE8) ? kFusedDq : kFusedGemm;
 }
 
 size_t e0m8_fused_workspace_bytes(int64_t M, int64_t N, int64_t K, int group, int with_rmsnorm, int epilogue)
@@ -671,8 +690,8 @@ size_t e0m8_fused_workspace_bytes(int64_t M, int64_t N, int64_t K, int group, in
     if (epilogue != E0M4_EPILOGUE_NONE && epilogue != E0M4_EPILOGUE_SWIGLU) return 0;
     Fusion f;
     f.swiglu = epilogue == E0M4_EPILOGUE_SWIGLU;
-    if (fused_path8(f, M, N, K) != 1) return 0;
-    return (with_rmsnorm ? norm_bytes(M, K) : 0) + gemm_pipe_workspace_bytes(M, N, K, f.swiglu, true);
+    f.residual = &f;                                    // (as in e0m4_fused_workspace_bytes)
+    return fused_need(fused_path8(f, M, N, K), with_rmsnorm != 0, M, K, gemm_pipe_workspace_bytes(M, N, K, f.swiglu, true));
 }
 
 int e0m8_matmul_fused(const void* X, int64_t M, const void* rms_gamma, float rms_eps, const void* codes, int64_t N,
@@ -696,13 +715,13 @@ int e0m8_matmul_fused(const void* X, int64_t M, const void* rms_gamma, float rms
         (residual && !aligned16(residual)))
         return E0M4_ERR_ALIGN;
     hipStream_t st = (hipStream_t)stream;
-    const int path = fused_path8(f, M, N, K);
-    if (path == 2) return launch_gemv_mfma8_fused(f, X, M, codes, N, K, Y, st);
-    if (path == 0) return launch_gemv8_fused(f, X, M, codes, N, K, Y, st);
-    if (path == 3) return launch_gemv_mfma8_fused(f, X, M, codes, N, K, Y, st, row_chunks(M));
-    if (path != 1) return E0M4_ERR_SHAPE;               // larger M needs K % 128 == 0 (GEMM kernels)
+    const FusedPath path = fused_path8(f, M, N, K);
+    if (path == kFusedSmallBatch) return launch_gemv_mfma8_fused(f, X, M, codes, N, K, Y, st);
+    if (path == kFusedVector) return launch_gemv8_fused(f, X, M, codes, N, K, Y, st);
+    if (path == kFusedChunks) return launch_gemv_mfma8_fused(f, X, M, codes, N, K, Y, st, row_chunks(M));
+    if (path == kFusedNone) return E0M4_ERR_SHAPE;      // larger M needs K % 128 == 0 (GEMM kernels)
     const size_t nb = rms_gamma ? norm_bytes(M, K) : 0;
-    const size_t need = nb + gemm_pipe_workspace_bytes(M, N, K, f.swiglu, true);
+    const size_t need = fused_need(path, rms_gamma != nullptr, M, K, gemm_pipe_workspace_bytes(M, N, K, f.swiglu, true));
     if (need > 0) {
         if (!workspace) return E0M4_ERR_NULL;
         if (!aligned16(workspace)) return E0M4_ERR_ALIGN;
@@ -715,6 +734,7 @@ int e0m8_matmul_fused(const void* X, int64_t M, const void* rms_gamma, float rms
         x = workspace;
         f.gamma = nullptr;
     }
+    if (path == kFusedDq) return launch_gemv_dq(x, M, codes, N, K, 128, kDqFormatE8, Y, st);
     return launch_gemm_pipe8_fused(f, x, M, codes, N, K, Y, static_cast<char*>(workspace) + nb, workspace_bytes - nb, st);
 }
 

@@ -454,15 +454,18 @@ bool gemv_dq_supported(int64_t M, int64_t N, int64_t K, int group)
 
 // Where this kernel is faster than the GEMM, which rounds the weights as it does.  (The callers keep the calls of the kernels
 // that multiply unrounded weights away from here, faster or not; the instances on exact codes are chosen below.)  The other
-// side's time over this kernel's, on 166 problems with cold weights (profiles/small_batch_dequantised_operands_vs_gemm.txt):
+// side's time over this kernel's, with cold weights:
 //   bfloat16: up to 64 rows always (1.1 - 7.8: the GEMM has whole tiles only).  65 to 128 rows in two parts, against 64 x 256
-//     tiles with K halves, where a workgroup has few row blocks: 1.2 - 3.1; at M = 100 4096 x 4096 34.8 -> 21.1 us, 4096 x 13696
-//     102 -> 52, but 32768 x 2048 (8 row blocks) 25 -> 37, 27392 x 4096 43 -> 63.
+//     tiles with K halves, where a workgroup has few row blocks: 1.2 - 3.1; at M = 100 4096 x 4096 34.8 -> 16.7 us, 4096 x 13696
+//     102 -> 43, but 32768 x 2048 (8 row blocks) 25 -> 37, 27392 x 4096 43 -> 41.
 //   On the shortest rows most wavefronts have no k block of their own, and many rows of X cost the others time: M = 64, 16384 x
 //     128 6.0 us against 4.9; in two parts M = 128, 8192 x 256 7.7 against 6.2, 8192 x 512 7.9 against 8.3.
 //   Groups of 32 and 64 up to 16 rows: always (1.3 - 3.1, the vector kernel's calls among them).
-//   17 to 64 rows, against K splits: 1.1 - 2.7 while the weights are few enough that reading X again in every workgroup is
-//     the smaller part; beyond the lines below 0.9 - 1.4, the more the fewer the rows.
+//   17 to 64 rows, against K splits, on 181 problems in 4-bit codes and 240 in 8-bit codes: up to 48
+//     rows 1.0 - 2.9 (27392 x 4096 at M = 24 29.7 -> 21.5, 4096 x 13696 at M = 30 26.8 -> 18.9) but for the longest rows, of which a
+//     workgroup reads all of X (7872 x 13824 at M = 41 28.2 and 30.3).  With more rows 1.0 - 1.9 within the lines below, beyond them 0.8
+//     - 1.1 (26272 x 3968 at M = 54 32.7 and 34.2, 17376 x 6912 at M = 64 37.0 and 42.6); in 8-bit codes, whose rows are twice as
+//     long, 3392 x 9088 at M = 56 20.1 and 23.2, 18560 x 6656 at M = 63 45.3 and 52.0.
 bool gemv_dq_pays(int64_t M, int64_t N, int64_t K, int group, DqFormat format)
 {
     DqPlan p;
@@ -472,8 +475,9 @@ bool gemv_dq_pays(int64_t M, int64_t N, int64_t K, int group, DqFormat format)
         return M > kGemvMaxM && N <= (int64_t)1 << 24 &&
                (M <= 48 || (M <= kDqMaxM ? K >= 256 : K >= 512 && NK <= 7e7 && p.wr * p.r <= 2));
     if (M > kDqMaxM) return false;
-    if (M > 16) return NK <= (format == kDqFormatE8 ? 1e8 : 7e7) && (M <= 48 || (K >= 256 && K <= 9216));
-    return format == kDqFormatFp16 && group != 128;
+    if (format == kDqFormatE8) return M > 16 && (M <= 32 || (M <= 48 ? K <= 8192 : K >= 256 && K <= 6144 && NK <= 1.2e8));
+    if (M > 16) return M <= 32 || (M <= 48 ? K <= 12800 : K >= 256 && K <= 7680 && NK <= 1e8);
+    return group != 128;
 }
 
 // (the row counts of the calls below; the kernel is not compiled for others)
