@@ -206,7 +206,10 @@ int e0m4_matmul_static(const void* X_f16, int64_t M, const void* codes, int64_t 
  * runs inside the GEMM kernels (or the kernel that adds the K splits) and the
  * rms-norm is a launch of its own that writes x' to the workspace; up to M = 64
  * the dequantising kernel of e0m4_matmul follows it where no other operator is
- * selected.
+ * selected.  Where e0m4_matmul would go in chunks of rows (17 <= M <= 64), a
+ * kernel with all rows in a workgroup gives the same sums in the same order; its
+ * rms-norm is a launch of its own, and calls with one that bring less than
+ * e0m4_fused_workspace_bytes() of workspace go in chunks, which need none.
  * Workspace: e0m4_fused_workspace_bytes() bytes, same rules as e0m4_matmul.
  * With no operator selected the result is that of e0m4_matmul (up to the order of
  * the fp32 additions and the rounding of the weights: the two may choose different

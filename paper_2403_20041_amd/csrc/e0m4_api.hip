@@ -258,9 +258,10 @@ static size_t norm_bytes(int64_t M, int64_t K) { return ((size_t)M * (size_t)K *
 enum FusedPath {
     kFusedNone = -1,
     kFusedVector,                                       // the decode kernel, everything in one launch
-    kFusedGemm,                                         // (this and the last: an rms-norm is a launch of its own before it)
+    kFusedGemm,                                         // (this and the last two: an rms-norm is a launch of its own before them)
     kFusedSmallBatch,                                   // the small-batch kernel on the matrix cores, everything in one launch
     kFusedChunks,                                       // that kernel on chunks of rows
+    kFusedTiles,                                        // the same sums with all rows in a workgroup (an rms-norm is a launch before it)
     kFusedExact,                                        // no operators: the kernel on exact codes
     kFusedDq,                                           // an rms-norm alone or nothing: the kernel with dequantised operands
 };
@@ -268,14 +269,21 @@ enum FusedPath {
 // goes.  Calls with a residual or the gated product keep the GEMM and its order of the sums, though the kernel with dequantised
 // operands would be faster: a stack of blocks amplifies the rounding of a residual stream that is summed in another order.
 static bool as_plain(const Fusion& f) { return !f.residual && !f.swiglu; }
-static FusedPath fused_path(const Fusion& f, int64_t M, int64_t N, int64_t K, int group)
+static FusedPath fused_path(const Fusion& f, int64_t M, int64_t N, int64_t K, int group, TilesPlan* tiles = nullptr)
 {
     if (!f.any() && use_gemv_exact(M, N, K, group, kDqFormatFp16)) return kFusedExact;
     // (groups of 64 and 32 from three rows on: 1.1 - 2 x the vector kernel and the GEMM there, 10 - 25 % slower than the
     // vector kernel at two rows)
     const int k = knob("gemv_mfma");
     if (k != 1 && gemv_mfma_fused_supported(f, M, N, K, group) && (group == 128 || M >= 3 || k == 6 || k == 9)) return kFusedSmallBatch;
-    if (small_batch_in_chunks(f, M, N, K, group)) return kFusedChunks;
+    if (small_batch_in_chunks(f, M, N, K, group)) {
+        TilesPlan p;
+        const bool can = f.any() && group == 128 && (k == 0 || k == 7) && gemv_tiles_plan(f, M, row_chunks(M), N, K, &p) &&
+                         gemv_tiles_supported(p, M, K);
+        if (!can || (k == 0 && !gemv_tiles_pays(f, p, row_chunks(M)))) return kFusedChunks;
+        if (tiles) *tiles = p;
+        return kFusedTiles;
+    }
     if (small_m_on_vector(M, N, K) && gemv_fused_supported(f, M, N, K)) return kFusedVector;
     return as_plain(f) && !gemm_steered() && N <= (int64_t)1 << 24 && use_gemv_dq(M, N, K, group, kDqFormatFp16) ? kFusedDq : kFusedGemm;
 }
@@ -283,7 +291,7 @@ static FusedPath fused_path(const Fusion& f, int64_t M, int64_t N, int64_t K, in
 // What the launches of a path need of the workspace: the normalised X, the GEMM's partial sums behind it.
 static size_t fused_need(FusedPath path, bool normed, int64_t M, int64_t K, size_t gemm_bytes)
 {
-    if (path != kFusedGemm && path != kFusedDq) return 0;
+    if (path != kFusedGemm && path != kFusedDq && path != kFusedTiles) return 0;
     return (normed ? norm_bytes(M, K) : 0) + (path == kFusedGemm ? gemm_bytes : 0);
 }
 
@@ -455,13 +463,16 @@ int e0m4_matmul_fused(const void* X, int64_t M, const void* rms_gamma, float rms
         (residual && !aligned16(residual)))
         return E0M4_ERR_ALIGN;
     hipStream_t st = (hipStream_t)stream;
-    const FusedPath path = fused_path(f, M, N, K, group);
+    TilesPlan tiles;
+    FusedPath path = fused_path(f, M, N, K, group, &tiles);
+    const size_t nb = rms_gamma ? norm_bytes(M, K) : 0;
+    // (chunks need no workspace: calls without one stay there)
+    if (path == kFusedTiles && nb > 0 && (!workspace || !aligned16(workspace) || workspace_bytes < nb)) path = kFusedChunks;
     if (path == kFusedSmallBatch) return launch_gemv_mfma_fused(f, X, M, codes, N, K, Y, st, 1, group);
     if (path == kFusedVector) return launch_gemv_fused(f, X, M, codes, N, K, group, Y, st);
     if (path == kFusedExact) return launch_gemv_exact(X, M, codes, N, K, kDqFormatFp16, Y, st);
     if (path == kFusedChunks) return launch_gemv_mfma_fused(f, X, M, codes, N, K, Y, st, row_chunks(M), group);      // rows are independent
     if (N > (int64_t)1 << 24) return E0M4_ERR_SHAPE;    // 32-bit offsets in the GEMM epilogue
-    const size_t nb = rms_gamma ? norm_bytes(M, K) : 0;
     const size_t need = fused_need(path, rms_gamma != nullptr, M, K, gemm_workspace_bytes(M, N, K, f.swiglu, true));
     if (need > 0) {
         if (!workspace) return E0M4_ERR_NULL;
@@ -470,11 +481,12 @@ int e0m4_matmul_fused(const void* X, int64_t M, const void* rms_gamma, float rms
     }
     const void* x = X;
     if (rms_gamma) {
-        rc = launch_rmsnorm(X, M, K, rms_gamma, rms_eps, workspace, st);
+        rc = launch_rmsnorm(X, M, K, rms_gamma, rms_eps, workspace, st, path == kFusedTiles ? tiles.waves : 4);
         if (rc != E0M4_OK) return rc;
         x = workspace;
         f.gamma = nullptr;
     }
+    if (path == kFusedTiles) return launch_gemv_tiles(f, tiles, x, M, codes, N, K, Y, st);
     if (path == kFusedDq) return launch_gemv_dq(x, M, codes, N, K, group, kDqFormatFp16, Y, st);
     return launch_gemm_fused(f, x, M, codes, N, K, group, Y, static_cast<char*>(workspace) + nb,
                              workspace_bytes - nb, st);

@@ -1151,6 +1151,17 @@ bool gemv_mfma_whole_rows(const Fusion& f, int64_t M, int64_t N, int64_t K, int 
     return true;
 }
 
+bool gemv_tiles_plan(const Fusion& f, int64_t M, int chunks, int64_t N, int64_t K, TilesPlan* plan)
+{
+    MfmaPlan p;
+    const int unit = f.swiglu ? 2 : 1;
+    const int64_t mc = chunk_rows(M, chunks);
+    if (!gemv_mfma_fused_supported(f, mc, N, K, kG) || !make_mfma_plan(mc, N, K, p, unit) || p.kb_phase != 0) return false;
+    *plan = {p.grid, p.rb_base, p.rb_rem, (p.rb_base + (p.rb_rem > 0 ? 1 : 0)) * unit, p.waves,
+             (int)((k_blocks(K) + kSuper - 1) / kSuper), p.waves <= 8 && p.step_item == 0};
+    return true;
+}
+
 int launch_gemv_mfma_fused(const Fusion& f, const void* X, int64_t M, const void* packed, int64_t N, int64_t K, void* Y,
                            hipStream_t stream, int chunks, int group)
 {

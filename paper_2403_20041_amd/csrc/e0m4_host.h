@@ -100,6 +100,18 @@ bool gemv_items_supported(const ItemsPlan& p, int64_t M, int64_t N, int64_t K, i
 bool gemv_items_pays(const ItemsPlan& p, int64_t M, int group, bool fused);
 int launch_gemv_items(const ItemsPlan& p, const void* X, int64_t M, const void* packed, int64_t N, int64_t K, int group, void* Y,
                       const void* residual, hipStream_t stream);
+// Fused calls of 17 to 64 rows with all rows in a workgroup, to the bits of that kernel on chunks of rows (e0m4_gemv_tiles.hip).
+struct TilesPlan {
+    int64_t grid;
+    int rb_base, rb_rem;                                // even deal of row blocks, or of pairs
+    int slots, waves, items;                            // row blocks of a workgroup, at most; wavefronts and work items of the order
+    bool x_in_registers;                                // in that kernel
+};
+bool gemv_tiles_plan(const Fusion& f, int64_t M, int chunks, int64_t N, int64_t K, TilesPlan* plan);
+bool gemv_tiles_supported(const TilesPlan& p, int64_t M, int64_t K);
+bool gemv_tiles_pays(const Fusion& f, const TilesPlan& p, int chunks);
+int launch_gemv_tiles(const Fusion& f, const TilesPlan& p, const void* X, int64_t M, const void* packed, int64_t N, int64_t K, void* Y,
+                      hipStream_t stream);
 // Small-batch path with the weight operand dequantised in registers: 2 <= M <= 128, any group (e0m4_gemv_dq.hip).
 // (`pays`: it is expected to beat the GEMM)
 enum DqFormat { kDqFormatFp16 = 0, kDqFormatE8 = 1, kDqFormatBf16 = 2 };     // 4-bit codes, 8-bit codes, 4-bit codes on bfloat16
@@ -135,7 +147,8 @@ int launch_gemm_fused(const Fusion& f, const void* X, int64_t M, const void* pac
 int launch_gemm_pipe_fused(const Fusion& f, const void* X, int64_t M, const void* packed, int64_t N, int64_t K, int group,
                            void* Y, void* workspace, size_t workspace_bytes, hipStream_t stream);
 // Row-wise rms-norm of X [M, K] into X_out (fp16): the prologue of e0m4_matmul_fused for the GEMM path.
-int launch_rmsnorm(const void* X, int64_t M, int64_t K, const void* gamma, float eps, void* X_out, hipStream_t stream);
+// (`waves` per row, which give the order of its sum of squares: 4 or 8)
+int launch_rmsnorm(const void* X, int64_t M, int64_t K, const void* gamma, float eps, void* X_out, hipStream_t stream, int waves = 4);
 // Software-pipelined 256 x 256 tile kernel (needs K % 128 == 0).  Problems with too few tiles to
 // fill the chip are split along K; the fp32 partial sums ([splits][M][N]) live in the caller's
 // workspace of gemm_pipe_workspace_bytes() bytes and a second kernel adds them.

@@ -10,13 +10,13 @@ namespace e0m4 {
 
 namespace {
 
-constexpr int kNormThreads = 256;
-
-__global__ __launch_bounds__(kNormThreads) void rmsnorm_kernel(const half_t* __restrict__ X, int64_t K,
+template <int WAVES>
+__global__ __launch_bounds__(WAVES * 64) void rmsnorm_kernel(const half_t* __restrict__ X, int64_t K,
                                                                const half_t* __restrict__ gamma, float eps,
                                                                half_t* __restrict__ out)
 {
-    __shared__ float part[kNormThreads / 64];
+    constexpr int kNormThreads = WAVES * 64;
+    __shared__ float part[WAVES];
     const half_t* __restrict__ x = X + (int64_t)blockIdx.x * K;
     half_t* __restrict__ o = out + (int64_t)blockIdx.x * K;
     const int t = threadIdx.x;
@@ -36,7 +36,7 @@ __global__ __launch_bounds__(kNormThreads) void rmsnorm_kernel(const half_t* __r
     __syncthreads();
     float total = 0.f;
 #pragma unroll
-    for (int w = 0; w < kNormThreads / 64; ++w) total += part[w];
+    for (int w = 0; w < WAVES; ++w) total += part[w];
     const float r = 1.f / sqrtf(total / (float)K + eps);
     for (int pc = t; pc < pieces; pc += kNormThreads) {
         const half8_t v = *reinterpret_cast<const half8_t*>(x + (int64_t)pc * 8);
@@ -50,12 +50,19 @@ __global__ __launch_bounds__(kNormThreads) void rmsnorm_kernel(const half_t* __r
 
 }  // namespace
 
-int launch_rmsnorm(const void* X, int64_t M, int64_t K, const void* gamma, float eps, void* X_out, hipStream_t stream)
+int launch_rmsnorm(const void* X, int64_t M, int64_t K, const void* gamma, float eps, void* X_out, hipStream_t stream, int waves)
 {
     if (M <= 0 || K <= 0) return E0M4_OK;
-    hipLaunchKernelGGL(rmsnorm_kernel, dim3((unsigned)M), dim3(kNormThreads), 0, stream, static_cast<const half_t*>(X), K,
-                       static_cast<const half_t*>(gamma), eps, static_cast<half_t*>(X_out));
-    return check_launch();
+    auto launch = [&](auto kernel) -> int {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)M), dim3((unsigned)waves * 64), 0, stream, static_cast<const half_t*>(X), K,
+                           static_cast<const half_t*>(gamma), eps, static_cast<half_t*>(X_out));
+        return check_launch();
+    };
+    switch (waves) {
+        case 4: return launch(&rmsnorm_kernel<4>);
+        case 8: return launch(&rmsnorm_kernel<8>);
+        default: return E0M4_ERR_SHAPE;
+    }
 }
 
 }  // namespace e0m4

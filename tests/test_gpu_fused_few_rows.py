@@ -1,10 +1,56 @@
-"""Fused matmuls of up to 64 rows by default routes against the oracle: an rms-norm alone runs before the kernel with dequantised
-operands, other operators on chunks of rows or the GEMM."""
+"""Fused matmuls of up to 64 rows: all rows in a workgroup, to the bits of the small-batch kernel on chunks of rows, with every
+operator, over last tiles of rows and columns, one to four row blocks per workgroup, work items that wavefronts of the order have in
+other row blocks and that end before their fourth k block; the calls that have no workspace for the normalised activations; and
+calls by default routes against the oracle."""
+import ctypes
+
+import numpy as np
 import pytest
 
-from test_gpu_fused import COMBOS, e0m4, run_fused  # noqa: F401
+import synth_inputs
+from test_gpu_fused import COMBOS, e0m4, quantized, run_fused, to_dev, torch  # noqa: F401
 
 pytestmark = pytest.mark.gpu
+
+
+def call(e0m4, mode, X, codes, N, K, gamma, swiglu, residual):
+    e0m4.e0m4_set_knob("gemv_mfma", mode)
+    try:
+        return e0m4.e0m4_matmul_fused(X, codes, N, K, 128, rms_gamma=gamma, rms_eps=1e-5, residual=residual,
+                                      epilogue=e0m4.E0M4_EPILOGUE_SWIGLU if swiglu else e0m4.E0M4_EPILOGUE_NONE)
+    finally:
+        e0m4.e0m4_set_knob("gemv_mfma", 0)
+
+
+# N, K, workgroups aimed at: 1 to 4 and 7 row blocks per workgroup (gated: 2, 4 and 8); 1, 3, 4, 8, 9 and 14 work items
+@pytest.mark.parametrize("N,K,workgroups", [(192, 128, 0), (448, 1664, 0), (320, 1152, 10), (1088, 2048, 34), (576, 4096, 12), (448, 1536, 7),
+                                            (320, 4480, 20), (192, 7040, 6), (1728, 2304, 16)])
+@pytest.mark.parametrize("M", [17, 32, 41, 48, 49, 64])
+def test_bits_of_the_chunks(e0m4, oracle, M, N, K, workgroups):
+    codes, What = quantized(e0m4, oracle, N, K, 128, seed=900 + N)
+    gamma_h = synth_inputs.norm_weight(K, 902)
+    X_h = synth_inputs.activations(M, K, seed=901 + M, outlier_frac=0.01)
+    X, gamma = to_dev(X_h), to_dev(gamma_h)
+    e0m4.e0m4_set_knob("gemv_workgroups", workgroups)
+    try:
+        for norm, swiglu, res in COMBOS + [(False, True, True), (True, True, False)]:
+            R_h = synth_inputs.residual(M, N // 2 if swiglu else N, 903)
+            Y, Yc = (call(e0m4, mode, X, codes, N, K, gamma if norm else None, swiglu, to_dev(R_h) if res else None) for mode in (7, 8))
+            assert torch.equal(Y, Yc), (norm, swiglu, res)
+            if res:                                     # the residual updated in place
+                Z = to_dev(R_h)
+                e0m4.e0m4_set_knob("gemv_mfma", 7)
+                e0m4.e0m4_matmul_fused(X, codes, N, K, 128, rms_gamma=gamma if norm else None, rms_eps=1e-5, residual=Z, out=Z,
+                                       epilogue=e0m4.E0M4_EPILOGUE_SWIGLU if swiglu else e0m4.E0M4_EPILOGUE_NONE)
+                e0m4.e0m4_set_knob("gemv_mfma", 0)
+                assert torch.equal(Z, Yc), (norm, swiglu)
+        # (a matrix that ends in the middle of a row block)
+        codes, _ = quantized(e0m4, oracle, N - 21, K, 128, seed=904 + N)
+        R = to_dev(synth_inputs.residual(M, N - 21, 905))
+        assert torch.equal(*(call(e0m4, mode, X, codes, N - 21, K, None, False, R) for mode in (7, 8)))
+    finally:
+        e0m4.e0m4_set_knob("gemv_mfma", 0)
+        e0m4.e0m4_set_knob("gemv_workgroups", 0)
 
 
 @pytest.mark.parametrize("norm,swiglu,res", COMBOS)
@@ -12,3 +58,18 @@ pytestmark = pytest.mark.gpu
                                           (48, 832, 160, 32, 4), (64, 4608, 1152, 128, 4), (30, 4608, 2304, 128, 8), (64, 2048, 1152, 64, 8)])
 def test_by_default(e0m4, oracle, M, N, K, G, bits, norm, swiglu, res):
     run_fused(e0m4, oracle, M, N, K, G, seed=950 + M, norm=norm, swiglu=swiglu, res=res, outliers=True, bits=bits)
+
+
+def test_without_a_workspace(e0m4, oracle):
+    M, N, K = 45, 4608, 2048
+    codes, _ = quantized(e0m4, oracle, N, K, 128, seed=970)
+    X, gamma = to_dev(synth_inputs.activations(M, K, seed=971)), to_dev(synth_inputs.norm_weight(K, 972))
+    need = e0m4.e0m4_fused_workspace_bytes(M, N, K, 128, True, 0)
+    assert need >= M * K * 2
+    room = torch.full((need + 16,), 255, dtype=torch.uint8, device=X.device)
+    for ws, nbytes in ((0, 0), (0, need), (room.data_ptr(), need - 1), (room.data_ptr() + 8, need)):
+        Y = torch.empty((M, N), dtype=torch.float16, device=X.device)
+        rc = e0m4.lib().e0m4_matmul_fused(X.data_ptr(), M, gamma.data_ptr(), ctypes.c_float(1e-5), codes.data_ptr(), N, K, 128, 0, 0,
+                                          Y.data_ptr(), ws, nbytes, torch.cuda.current_stream().cuda_stream)
+        assert rc == 0 and torch.equal(Y, call(e0m4, 8, X, codes, N, K, gamma, False, None))
+    assert np.all(room.cpu().numpy() == 255)            # (nothing was written there)
