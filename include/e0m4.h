@@ -136,7 +136,8 @@ int e0m4_unpack_codes(const void* codes, int64_t N, int64_t K, int group, void* 
  *            and mostly where they make more than one round, the dequantising
  *            kernel's form on exact codes; otherwise, any group, the
  *            dequantising kernel (M > 32: K <= 12800, M > 48: 256 <= K <= 7680
- *            and N * K <= 1e8).
+ *            and N * K <= 1e8, or up to 9216 and 7e7; beyond N * K = 7e7 the
+ *            GEMM's workspace is asked for, though it uses none).
  *   M >= 9 otherwise, and 2 <= M <= 8 when M * N * K is about 3.8e8 or
  *            more (the vector kernel's time grows with M): MFMA GEMM path
  *            (tiles of 64 x 256, 128 x 256 or 256 x 256 outputs, whichever
@@ -209,8 +210,10 @@ int e0m4_matmul_static(const void* X_f16, int64_t M, const void* codes, int64_t 
  * selected.  Where e0m4_matmul would go in chunks of rows (17 <= M <= 64), a
  * kernel with all rows in a workgroup gives the same sums in the same order; its
  * rms-norm is a launch of its own, and calls with one that bring less than
- * e0m4_fused_workspace_bytes() of workspace go in chunks, which need none.
- * Workspace: e0m4_fused_workspace_bytes() bytes, same rules as e0m4_matmul.
+ * e0m4_fused_workspace_best_bytes() of workspace go in chunks, which need none.
+ * Workspace: e0m4_fused_workspace_bytes() bytes, same rules as e0m4_matmul;
+ * with e0m4_fused_workspace_best_bytes(), which is as many or more, every call
+ * has its fastest kernel.
  * With no operator selected the result is that of e0m4_matmul (up to the order of
  * the fp32 additions and the rounding of the weights: the two may choose different
  * kernels).  K == 0 is
@@ -219,6 +222,7 @@ int e0m4_matmul_static(const void* X_f16, int64_t M, const void* codes, int64_t 
 #define E0M4_EPILOGUE_NONE   0
 #define E0M4_EPILOGUE_SWIGLU 1
 size_t e0m4_fused_workspace_bytes(int64_t M, int64_t N, int64_t K, int group, int with_rmsnorm, int epilogue);
+size_t e0m4_fused_workspace_best_bytes(int64_t M, int64_t N, int64_t K, int group, int with_rmsnorm, int epilogue);
 int e0m4_matmul_fused(const void* X_f16, int64_t M, const void* rms_gamma_f16, float rms_eps,
                       const void* codes, int64_t N, int64_t K, int group,
                       int epilogue, const void* residual_f16,

@@ -65,6 +65,8 @@ def lib() -> ctypes.CDLL:
     L.e0m4_matmul_static.argtypes = [vp, i64, vp, i64, i64, ci, vp, vp]
     L.e0m4_fused_workspace_bytes.restype = sz
     L.e0m4_fused_workspace_bytes.argtypes = [i64, i64, i64, ci, ci, ci]
+    L.e0m4_fused_workspace_best_bytes.restype = sz
+    L.e0m4_fused_workspace_best_bytes.argtypes = [i64, i64, i64, ci, ci, ci]
     L.e0m4_matmul_fused.restype = ci
     L.e0m4_matmul_fused.argtypes = [vp, i64, vp, ctypes.c_float, vp, i64, i64, ci, ci, vp, vp, vp, sz, vp]
     L.e0m8_codes_bytes.restype = sz
@@ -271,9 +273,10 @@ def e0m4_matmul_fused(X, codes, N: int, K: int, group: int, rms_gamma=None, rms_
         out = _empty((M, n_out), torch.float16, X.device, stream, "out")
     else:
         _need(out, torch.float16, (M, n_out), "out")
-    need = e0m4_fused_workspace_bytes(M, N, K, group, rms_gamma is not None, epilogue)
-    if workspace is None and need > 0:
-        workspace = _empty(need, torch.uint8, X.device, stream, "workspace")
+    if workspace is None:
+        need = lib().e0m4_fused_workspace_best_bytes(M, N, K, group, 1 if rms_gamma is not None else 0, epilogue)
+        if need > 0:
+            workspace = _empty(need, torch.uint8, X.device, stream, "workspace")
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     _check(lib().e0m4_matmul_fused(_ptr(X), M, _ptr(rms_gamma), float(rms_eps), _ptr(codes), N, K, group, epilogue,
                                    _ptr(residual), _ptr(out), _ptr(workspace), ws_bytes, _stream(stream)),

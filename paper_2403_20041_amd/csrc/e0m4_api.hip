@@ -245,7 +245,7 @@ size_t e0m4_workspace_bytes(int64_t M, int64_t N, int64_t K, int group)
     if (check_shape(N, K, group) != E0M4_OK || M <= 0 || N == 0 || K == 0) return 0;             // invalid or empty: nothing runs
     if (use_gemv_exact(M, N, K, group, kDqFormatFp16)) return 0;
     if (small_m_on_vector(M, N, K)) return 0;           // the small-M kernels need none
-    if (use_gemv_dq4(M, N, K, group)) return 0;
+    if (use_gemv_dq4(M, N, K, group) && (knob("gemv_mfma") == 4 || gemv_dq_free(M, N, K, group, kDqFormatFp16))) return 0;
     if (use_gemv_mfma(M, N, K, group) || small_batch_in_chunks(Fusion{}, M, N, K, group)) return 0;
     return gemm_workspace_bytes(M, N, K);       // partial tiles of the split-K GEMM, if it splits
 }
@@ -258,12 +258,12 @@ static size_t norm_bytes(int64_t M, int64_t K) { return ((size_t)M * (size_t)K *
 enum FusedPath {
     kFusedNone = -1,
     kFusedVector,                                       // the decode kernel, everything in one launch
-    kFusedGemm,                                         // (this and the last two: an rms-norm is a launch of its own before them)
+    kFusedGemm,                                         // (an rms-norm is a launch of its own before it)
     kFusedSmallBatch,                                   // the small-batch kernel on the matrix cores, everything in one launch
     kFusedChunks,                                       // that kernel on chunks of rows
     kFusedTiles,                                        // the same sums with all rows in a workgroup (an rms-norm is a launch before it)
     kFusedExact,                                        // no operators: the kernel on exact codes
-    kFusedDq,                                           // an rms-norm alone or nothing: the kernel with dequantised operands
+    kFusedDq,                                           // an rms-norm alone or nothing, as for the GEMM: the kernel with dequantised operands
 };
 // An rms-norm alone (a projection into q, k and v, or to the vocabulary) and calls without operators may go where the plain call
 // goes.  Calls with a residual or the gated product keep the GEMM and its order of the sums, though the kernel with dequantised
@@ -288,21 +288,33 @@ static FusedPath fused_path(const Fusion& f, int64_t M, int64_t N, int64_t K, in
     return as_plain(f) && !gemm_steered() && N <= (int64_t)1 << 24 && use_gemv_dq(M, N, K, group, kDqFormatFp16) ? kFusedDq : kFusedGemm;
 }
 
-// What the launches of a path need of the workspace: the normalised X, the GEMM's partial sums behind it.
+// The workspace that a call has to bring: the normalised X, the GEMM's partial sums behind it.  (Calls of the kernel with
+// dequantised operands have the same to bring as when they were the GEMM's; calls in tiles may do without, in chunks.)
 static size_t fused_need(FusedPath path, bool normed, int64_t M, int64_t K, size_t gemm_bytes)
 {
-    if (path != kFusedGemm && path != kFusedDq && path != kFusedTiles) return 0;
-    return (normed ? norm_bytes(M, K) : 0) + (path == kFusedGemm ? gemm_bytes : 0);
+    return path == kFusedGemm || path == kFusedDq ? (normed ? norm_bytes(M, K) : 0) + gemm_bytes : 0;
 }
 
-size_t e0m4_fused_workspace_bytes(int64_t M, int64_t N, int64_t K, int group, int with_rmsnorm, int epilogue)
+static size_t fused_bytes(int64_t M, int64_t N, int64_t K, int group, bool normed, int epilogue, bool best)
 {
     if (check_shape(N, K, group) != E0M4_OK || M <= 0 || N == 0 || K == 0) return 0;
     if (epilogue != E0M4_EPILOGUE_NONE && epilogue != E0M4_EPILOGUE_SWIGLU) return 0;
     Fusion f;
     f.swiglu = epilogue == E0M4_EPILOGUE_SWIGLU;
     f.residual = &f;                                    // (a call without a residual needs no more than one with it)
-    return fused_need(fused_path(f, M, N, K, group), with_rmsnorm != 0, M, K, gemm_workspace_bytes(M, N, K, f.swiglu, true));
+    const FusedPath path = fused_path(f, M, N, K, group);
+    if (best && path == kFusedTiles && normed) return norm_bytes(M, K);
+    return fused_need(path, normed, M, K, gemm_workspace_bytes(M, N, K, f.swiglu, true));
+}
+
+size_t e0m4_fused_workspace_bytes(int64_t M, int64_t N, int64_t K, int group, int with_rmsnorm, int epilogue)
+{
+    return fused_bytes(M, N, K, group, with_rmsnorm != 0, epilogue, false);
+}
+
+size_t e0m4_fused_workspace_best_bytes(int64_t M, int64_t N, int64_t K, int group, int with_rmsnorm, int epilogue)
+{
+    return fused_bytes(M, N, K, group, with_rmsnorm != 0, epilogue, true);
 }
 
 int e0m4_set_knob(const char* name, int value)
@@ -397,6 +409,14 @@ int e0m4_unpack_codes(const void* codes, int64_t N, int64_t K, int group, void* 
     return launch_unpack(codes, N, K, group, out, (hipStream_t)stream);
 }
 
+// a workspace that a plain call has to bring, whether its kernel uses it or not
+static int check_workspace(size_t need, const void* workspace, size_t bytes)
+{
+    if (need == 0) return E0M4_OK;
+    if (bytes > 0 && (!workspace || !aligned16(workspace))) return workspace ? E0M4_ERR_ALIGN : E0M4_ERR_NULL;
+    return bytes < need ? E0M4_ERR_WORKSPACE : E0M4_OK;
+}
+
 int e0m4_matmul(const void* X, int64_t M, const void* codes, const void* scales, const void* bias, int64_t N, int64_t K,
                 int group, void* Y, void* workspace, size_t workspace_bytes, void* stream)
 {
@@ -417,8 +437,10 @@ int e0m4_matmul(const void* X, int64_t M, const void* codes, const void* scales,
     if (!aligned16(X) || !aligned16(codes)) return E0M4_ERR_ALIGN;
     if (use_gemv_exact(M, N, K, group, kDqFormatFp16))
         return launch_gemv_exact(X, M, codes, N, K, kDqFormatFp16, Y, (hipStream_t)stream);
-    if (use_gemv_dq4(M, N, K, group))
-        return launch_gemv_dq(X, M, codes, N, K, group, kDqFormatFp16, Y, (hipStream_t)stream);
+    if (use_gemv_dq4(M, N, K, group)) {
+        rc = check_workspace(e0m4_workspace_bytes(M, N, K, group), workspace, workspace_bytes);
+        return rc != E0M4_OK ? rc : launch_gemv_dq(X, M, codes, N, K, group, kDqFormatFp16, Y, (hipStream_t)stream);
+    }
     if (use_gemv_mfma(M, N, K, group)) return launch_gemv_mfma(X, M, codes, N, K, Y, (hipStream_t)stream, 1, group);
     if (small_m_on_vector(M, N, K)) return launch_gemv(X, M, codes, N, K, group, Y, (hipStream_t)stream);
     if (small_batch_in_chunks(Fusion{}, M, N, K, group))
@@ -643,11 +665,13 @@ static bool e0m8_use_gemv_dq(int64_t M, int64_t N, int64_t K)
     return (knob("gemv_mfma") == 4 || (e0m8_gemm_or_dq(M, N, K) && !gemm_steered())) && use_gemv_dq(M, N, K, 128, kDqFormatE8);
 }
 static bool e0m8_use_gemm(int64_t M, int64_t N, int64_t K) { return e0m8_gemm_or_dq(M, N, K) && !e0m8_use_gemv_dq(M, N, K); }
+static bool e0m8_dq_free(int64_t M, int64_t N, int64_t K) { return knob("gemv_mfma") == 4 || gemv_dq_free(M, N, K, 128, kDqFormatE8); }
 
 size_t e0m8_workspace_bytes(int64_t M, int64_t N, int64_t K, int group)
 {
     if (check_shape8(N, K, group) != E0M4_OK || M <= 0 || N == 0 || K == 0) return 0;
-    return e0m8_use_gemm(M, N, K) ? gemm_pipe_workspace_bytes(M, N, K, false, true) : 0;
+    if (!e0m8_gemm_or_dq(M, N, K) || (e0m8_use_gemv_dq(M, N, K) && e0m8_dq_free(M, N, K))) return 0;
+    return gemm_pipe_workspace_bytes(M, N, K, false, true);
 }
 
 int e0m8_matmul(const void* X, int64_t M, const void* codes, int64_t N, int64_t K, int group, void* Y, void* workspace,
@@ -667,7 +691,11 @@ int e0m8_matmul(const void* X, int64_t M, const void* codes, int64_t N, int64_t 
     }
     if (!X || !codes) return E0M4_ERR_NULL;
     if (!aligned16(X) || !aligned16(codes)) return E0M4_ERR_ALIGN;
-    if (e0m8_use_gemv_dq(M, N, K)) return launch_gemv_dq(X, M, codes, N, K, 128, kDqFormatE8, Y, (hipStream_t)stream);
+    if (e0m8_use_gemv_dq(M, N, K)) {
+        rc = check_workspace(e0m8_workspace_bytes(M, N, K, group), workspace, workspace_bytes);
+        if (rc != E0M4_OK) return rc;
+        return launch_gemv_dq(X, M, codes, N, K, 128, kDqFormatE8, Y, (hipStream_t)stream);
+    }
     if (e0m8_use_mfma_decode(M, N, K)) return launch_gemv_mfma8(X, M, codes, N, K, Y, (hipStream_t)stream);
     if (small_batch8_in_chunks(Fusion{}, M, N, K))
         return launch_gemv_mfma8(X, M, codes, N, K, Y, (hipStream_t)stream, row_chunks(M));

@@ -464,8 +464,16 @@ bool gemv_dq_supported(int64_t M, int64_t N, int64_t K, int group)
 //   17 to 64 rows, against K splits, on 181 problems in 4-bit codes and 240 in 8-bit codes: up to 48
 //     rows 1.0 - 2.9 (27392 x 4096 at M = 24 29.7 -> 21.5, 4096 x 13696 at M = 30 26.8 -> 18.9) but for the longest rows, of which a
 //     workgroup reads all of X (7872 x 13824 at M = 41 28.2 and 30.3).  With more rows 1.0 - 1.9 within the lines below, beyond them 0.8
-//     - 1.1 (26272 x 3968 at M = 54 32.7 and 34.2, 17376 x 6912 at M = 64 37.0 and 42.6); in 8-bit codes, whose rows are twice as
+//     - 1.1 (but they stay here within the lines of gemv_dq_free; 26272 x 3968 at M = 54 32.7 and 34.2, 17376 x 6912 at M = 64 37.0 and 42.6); in 8-bit codes, whose rows are twice as
 //     long, 3392 x 9088 at M = 56 20.1 and 23.2, 18560 x 6656 at M = 63 45.3 and 52.0.
+//   (gemv_dq_free: calls that need no workspace.  Callers of the others, up to 64 rows, bring the GEMM's; those lines stay
+//   where they are, so that a size that was asked for once is enough for good.)
+bool gemv_dq_free(int64_t M, int64_t N, int64_t K, int group, DqFormat format)
+{
+    if (format == kDqFormatBf16 || M > kDqMaxM) return format == kDqFormatBf16;
+    if (M > 16) return (double)N * (double)K <= (format == kDqFormatE8 ? 1e8 : 7e7) && (M <= 48 || (K >= 256 && K <= 9216));
+    return format == kDqFormatFp16 && group != 128;
+}
 bool gemv_dq_pays(int64_t M, int64_t N, int64_t K, int group, DqFormat format)
 {
     DqPlan p;
@@ -475,9 +483,9 @@ bool gemv_dq_pays(int64_t M, int64_t N, int64_t K, int group, DqFormat format)
         return M > kGemvMaxM && N <= (int64_t)1 << 24 &&
                (M <= 48 || (M <= kDqMaxM ? K >= 256 : K >= 512 && NK <= 7e7 && p.wr * p.r <= 2));
     if (M > kDqMaxM) return false;
+    if (gemv_dq_free(M, N, K, group, format)) return true;
     if (format == kDqFormatE8) return M > 16 && (M <= 32 || (M <= 48 ? K <= 8192 : K >= 256 && K <= 6144 && NK <= 1.2e8));
-    if (M > 16) return M <= 32 || (M <= 48 ? K <= 12800 : K >= 256 && K <= 7680 && NK <= 1e8);
-    return group != 128;
+    return M > 16 && (M <= 32 || (M <= 48 ? K <= 12800 : K >= 256 && K <= 7680 && NK <= 1e8));
 }
 
 // (the row counts of the calls below; the kernel is not compiled for others)
