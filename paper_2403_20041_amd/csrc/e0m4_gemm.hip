@@ -318,7 +318,7 @@ int launch_tile(const half_t* x, int64_t M, const uint4* c, int64_t N, int64_t K
     return check_launch();
 }
 
-// The pipelined kernel runs whenever it can (K a multiple of 128): with its three tiles and the K split it was
+// The pipelined kernel runs whenever it can (K a multiple of 128): with its tiles and the K split it was
 // never slower than the kernel of this file on any measured shape, and up to 2.7x faster on small ones
 // (M = 17..96, 2048 x 2048: 12 us against 31).  gemm_variant 1 forces the kernel of this file.
 bool use_pipe(int64_t M, int64_t N, int64_t K, bool swiglu = false)

@@ -1,8 +1,7 @@
 // Software-pipelined tile of the prefill GEMM (paper: section "Operator and lagging optimizations",
 // matrix-matrix product; dequantisation of section "E0M4 FP4 quantization" fused in registers), built
-// for 256 x 256 outputs, for 128 x 256 and 64 x 256 outputs (four wavefronts side by side, two workgroups
-// per compute unit) and for 128 x 128 outputs (four wavefronts 2 x 2); pipe_tile() below chooses.  The
-// description is that of the large tile.
+// for 256 x 256 outputs and, with four wavefronts side by side, for 128 x 256, 64 x 256, 128 x 128 (two workgroups
+// per compute unit) and 64 x 128 outputs (four); shortest() below chooses.  The description is that of the large tile.
 //
 // Eight wavefronts (2 x 4, two per SIMD) share the tile, 128 x 64 outputs and 128 fp32 accumulator
 // registers per lane each, which leaves two wavefronts per SIMD at most: little but a wavefront's own
@@ -106,8 +105,10 @@ struct SkArgs {
 //
 // The tile is BM x BN: 256 x 256 with 2 x 4 wavefronts; 128 x 256 with 1 x 4 wavefronts (the same 128 x 64 per
 // wavefront, two independent workgroups per compute unit); 64 x 256 with 1 x 4 wavefronts, where the taller tiles
-// would compute many rows that do not exist or leave compute units without a tile; 128 x 128 with 2 x 2 wavefronts
-// (forced launches only).
+// would compute many rows that do not exist or leave compute units without a tile; 128 x 128 and 64 x 128 with 1 x 4
+// wavefronts of 32 columns (TN = 1), which take half of those wavefronts' registers and time per slice, where tiles are few.  Gated,
+// such wavefronts alternate: an even one holds the gate's columns, the next one the same columns of the up projection, and
+// hands its sums over in LDS. 
 //
 // SHORT: M leaves 64 rows or fewer in the last row tile of 128.  Those tiles are computed in two of their four 32-row blocks
 // (one block would take as long: below that the dequantisation is all there is to do) and are numbered last on every XCD, so
@@ -313,8 +314,8 @@ __global__ __launch_bounds__(64 * WGM * WGN * KS, 2) void gemm_pipe_kernel(const
     for (int j = 0; j < TN; ++j) {
         int64_t rb = min(rb_tile + wn / kBlockRows + 2 * j + ((lane >> 4) & 1), nrb - 1) - rb_tile;
         if (gated) {                                    // block 0: gate rows, block 1: the up rows, N/2 further
-            const int64_t nrbh = fu.n_half / kBlockRows;
-            rb = min(rb_tile + (wave % WGN) * 2 + ((lane >> 4) & 1), nrbh - 1) - rb_tile + j * nrbh;
+            const int64_t nrbh = fu.n_half / kBlockRows;    // (TN = 1: those of an odd wavefront)
+            rb = min(rb_tile + (TN == 2 ? wave % WGN : wave >> 1) * 2 + ((lane >> 4) & 1), nrbh - 1) - rb_tile + (TN == 2 ? j : wave & 1) * nrbh;
         }
         // 4-bit: chunk b_h of the slice; 8-bit: chunks 2 b_h and 2 b_h + 1 of the block (the second 256 bytes on)
         b_code_off[j] = (uint32_t)rb * rb_stride + (uint32_t)((E8 ? 2 * b_h : b_h) * kBlockRows + b_r) * 16;
@@ -434,7 +435,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KS, 2) void gemm_pipe_kernel(const
         for (int i = 0; i < kMfma; ++i) {
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);          // one MFMA
             if (i < TMX) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);      // one LDS fragment read
-            __builtin_amdgcn_sched_group_barrier(0x002, kMfma >= 8 ? 5 : 9, 0);     // vector ALU
+            __builtin_amdgcn_sched_group_barrier(0x002, TMX >= 4 ? 5 : 9, 0);       // vector ALU
             if (i < decltype(vmem)::value) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);   // global load
         }
     };
@@ -575,8 +576,9 @@ __global__ __launch_bounds__(64 * WGM * WGN * KS, 2) void gemm_pipe_kernel(const
     // through the K loop: a hundred registers more, and spills in the large tile)
     uint32_t n32 = (uint32_t)N;
     asm volatile("" : "+s"(n32));
-    // (KS = 2: the upper half has no rows to write)
+    // (KS = 2: the upper half has no rows to write; gated with TN = 1, the odd wavefronts have none of their own)
     const int rows_left = KS == 2 && half == 1 ? 0 : (int)min((int64_t)BM, M - m0), cols_left = (int)min((int64_t)BN, N - n0);
+    const int rows_mine = TN == 1 && gated && (wave & 1) ? 0 : rows_left;
     const int row0 = wm + 4 * (lane >> 5), col0 = wn + (lane & 31);
     const uint32_t off0 = (uint32_t)row0 * n32 + (uint32_t)col0;
     auto store_tile = [&](auto* __restrict__ dst) {     // dst: element (m0, n0) of a row-major [M, N] array
@@ -628,7 +630,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KS, 2) void gemm_pipe_kernel(const
         const int prow = lane / PPR, pcol = (lane % PPR) * 8;
         const bool col_ok = wcol + pcol < cols_valid;
         const uint32_t o0 = (uint32_t)(wm + prow) * ld + (uint32_t)(wcol + pcol);
-        const int my_rows = col_ok ? rows_left - wm - prow : 0;     // rows from this lane's first on that exist
+        const int my_rows = col_ok ? rows_mine - wm - prow : 0;     // rows from this lane's first on that exist
         half8_t rs[2][2];
         auto load_res = [&](int ch) {
 #pragma unroll
@@ -749,10 +751,10 @@ __global__ __launch_bounds__(64 * WGM * WGN * KS, 2) void gemm_pipe_kernel(const
     // Split K in a fixed number of ranges: this work item's fp32 partial sums go to slab `split` of the workspace
     // (row-major [splits][M][N]); a second kernel adds the slabs in split order and rounds to fp16.
     if (FUSED) {
-        static_assert(!FUSED || TN == 2, "the gated epilogue pairs the two operand blocks of a wavefront");
+        static_assert(!FUSED || TN == 2 || (TN == 1 && WGM == 1), "the gated epilogue pairs operand blocks of a wavefront, or two wavefronts");
         if (gated) {
             const int ocols_left = (int)min((int64_t)(BN / 2), fu.n_half - n0);
-            const int ocol = (wave % WGN) * 32 + (lane & 31);
+            const int wcol = (TN == 2 ? wave % WGN : wave >> 1) * 32, ocol = wcol + (lane & 31);
             if (ocol < ocols_left) {
                 if (out_mode == 1) {                    // partial sums keep the [M, N] layout of the weight rows
                     float* __restrict__ pg = partial + ((size_t)split * (size_t)M + (size_t)m0) * (size_t)N + (size_t)n0;
@@ -764,8 +766,12 @@ __global__ __launch_bounds__(64 * WGM * WGN * KS, 2) void gemm_pipe_kernel(const
                         for (int r = 0; r < 16; ++r) {
                             const int dr = 32 * i + 8 * (r >> 2) + (r & 3);
                             if (row0 + dr < rows_left) {
-                                pg[o0 + (uint32_t)dr * n32] = acc[i][0][r];
-                                pu[o0 + (uint32_t)dr * n32] = acc[i][1][r];
+                                if constexpr (TN == 2) {
+                                    pg[o0 + (uint32_t)dr * n32] = acc[i][0][r];
+                                    pu[o0 + (uint32_t)dr * n32] = acc[i][1][r];
+                                } else {
+                                    (wave & 1 ? pu : pg)[o0 + (uint32_t)dr * n32] = acc[i][0][r];
+                                }
                             }
                         }
                 }
@@ -773,10 +779,34 @@ __global__ __launch_bounds__(64 * WGM * WGN * KS, 2) void gemm_pipe_kernel(const
             if (out_mode != 1) {
                 uint32_t nh32 = (uint32_t)fu.n_half;    // (a multiple of 32)
                 asm volatile("" : "+s"(nh32));          // (opaque, like n32)
+                if constexpr (TN == 1) {                // the up sums of an odd wavefront to the even one before it
+                    floatx4* sums = reinterpret_cast<floatx4*>(smem) + (wave >> 1) * (TM * 4 * 64) + lane;
+                    __syncthreads();                    // every wavefront has left the K loop's stages
+                    if (wave & 1) {
+#pragma unroll
+                        for (int i = 0; i < TM; ++i)
+#pragma unroll
+                            for (int q = 0; q < 4; ++q)
+                                sums[(i * 4 + q) * 64] = floatx4{acc[i][0][4 * q], acc[i][0][4 * q + 1], acc[i][0][4 * q + 2], acc[i][0][4 * q + 3]};
+                    }
+                    __syncthreads();
+                    if (!(wave & 1)) {
+#pragma unroll
+                        for (int i = 0; i < TM; ++i)
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) {
+                                const floatx4 up = sums[(i * 4 + q) * 64];
+#pragma unroll
+                                for (int e = 0; e < 4; ++e) acc[i][0][4 * q + e] = silu_f32(acc[i][0][4 * q + e]) * up[e];
+                            }
+                    }
+                    write_rows(std::integral_constant<int, 32>{}, [&](int i, int r, int) { return acc[i][0][r]; }, Y + m0 * fu.n_half + n0,
+                               fu.residual ? fu.residual + m0 * fu.n_half + n0 : nullptr, nh32, wcol, ocols_left);
+                } else
                 write_rows(std::integral_constant<int, 32>{},
                            [&](int i, int r, int) { return silu_f32(acc[i][0][r]) * acc[i][1][r]; },
                            Y + m0 * fu.n_half + n0, fu.residual ? fu.residual + m0 * fu.n_half + n0 : nullptr, nh32,
-                           (wave % WGN) * 32, ocols_left);
+                           wcol, ocols_left);
             }
             continue;
         }
@@ -804,7 +834,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KS, 2) void gemm_pipe_kernel(const
     if (out_mode == 1)
         store_tile(partial + ((size_t)split * (size_t)M + (size_t)m0) * (size_t)N + (size_t)n0);
     else if ((n32 & 7u) == 0 && (KS == 2 || (FUSED && fu.residual) || M - m0 < BM || N - n0 < BN))
-        write_rows(std::integral_constant<int, 64>{}, [&](int i, int r, int j) { return acc[i][j][r]; }, yt,
+        write_rows(std::integral_constant<int, TN * 32>{}, [&](int i, int r, int j) { return acc[i][j][r]; }, yt,
                    FUSED && fu.residual ? fu.residual + m0 * N + n0 : nullptr, n32, wn, cols_left);
     else
         store_tile(yt);
@@ -862,17 +892,19 @@ constexpr int kComputeUnits = 256;
 constexpr int kMinPairsPerSplit = 4;
 constexpr int kMaxSplits = 8;
 
-// The tile a problem gets (gemm_variant 2, 3, 4, 5 force the 256 x 256, 128 x 128, 64 x 256 and 128 x 256 tile) and
+// The tile a problem gets (gemm_variant 2, 3, 4, 5, 6 force the 256 x 256, 128 x 128, 64 x 256, 128 x 256 and 64 x 128 tile) and
 // whether the large tile runs with even scheduling (SkArgs; gemm_sk 1 forces it whenever the last round is partly
-// filled, 2 forbids it) are decided by an estimate of the launch's duration.  Up to 64 rows only the 64 x 256 tile
-// (four wavefronts side by side, every weight dequantised once per workgroup) makes sense; the 128 x 128 tile never
-// won.  The 128 x 256 tile has the large tile's wavefront (128 x 64, 3.75 vector instructions per MFMA) in workgroups
+// filled, 2 forbids it) are decided by an estimate of the launch's duration.  Up to 64 rows only the tiles of 64 rows
+// make sense.  The 128 x 256 tile has the large tile's wavefront (128 x 64, 3.75 vector instructions per MFMA) in workgroups
 // of four, two to a compute unit, that start and finish independently: it pads fewer rows than the large tile,
 // dequantises half as often as the flat one and leaves a shorter tail (354 x 13056 x 10368: 111 us against 138 and
-// 146; 2048 x 27392 x 4096: 397 against 421 with even scheduling).
+// 146; 2048 x 27392 x 4096: 397 against 421 with even scheduling).  The tiles of 128 columns have wavefronts of half the width
+// (64 x 32 and 128 x 32, an operand of X read for every MFMA): twice as many workgroups where tiles are few, each with half the
+// work per slice, so that fewer splits do or none (317 x 2560 x 2048 on 64 x 256 tiles in splits 16.9 us, on 64 x 128 tiles unsplit 12.9;
+// 1024 x 4096 x 4096 on 128 x 256 in two splits 45.7, on 128 x 128 unsplit 39.7; 64 x 4096 x 13696 in eight splits 27.3 and 19.1).
 //
 // The estimate counts rounds: the work items (tiles times K splits) run `cap` at a time (one 256 x 256 tile per
-// compute unit, two of the others), a full round takes  pairs-of-K-slices * a(1) + b  and the last, partly filled
+// compute unit, two of the others, four of the smallest), a full round takes  pairs-of-K-slices * a(1) + b  and the last, partly filled
 // one  pairs * a(fill) + b  with a() piecewise linear in the fill -- a compute unit is slower the more of them run
 // (one round of 160 large tiles with K = 5120 takes 112 us, one of 256 tiles 152 us, whether the workgroups read
 // different tiles or all the same one: it is not the memory side), which is why filling idle units buys much less
@@ -881,19 +913,15 @@ constexpr int kMaxSplits = 8;
 // one with the shortest estimate; even scheduling runs its whole rounds like whole tiles and the shared-out rest on
 // every unit at the full rate, and adds the slabs' cost, of which the part per sharer of a tile is serial (the last
 // arriver reads them all).
-// The constants are a least-squares fit (logarithm of the ratio to the measurement, rms 5.8 %) to 1301 timings of 321
-// problems -- M = 65 .. 8192, N = 1024 .. 256000, K = 1024 .. 16384, groups of 32, 64 and 128, random and layer shapes
-// of 2B to 14B models -- each timed with the three tiles and with even scheduling, 18 of them also with one to eight K
-// splits per tile, on weights out of cache.  Choosing by the estimate costs 0.8 % over always choosing the measured
-// best (geometric mean; 0.6 - 0.9 % with the fit made on two thirds and tested on the rest; 3.6 % on the 18 problems
-// with their 15 candidates each; the timings themselves repeat within about 3 %).  tune_gemm_estimate.py of the Python
-// package times and fits in this way.
+// The constants are a least-squares fit (logarithm of the ratio to the measurement, rms 4.1 %) to 3010 timings of 181
+// problems -- M = 65 .. 8192, N = 1024 .. 20480, K = 1024 .. 14336, random ones and the layer shapes of 6B and 14B models -- each timed
+// with the five tiles, one to eight K splits, and with even scheduling, on weights out of cache.  Choosing by the estimate
+// costs 0.9 % over always choosing the measured best (geometric mean); without the tiles of 128 columns the best would be
+// 2.4 % slower (5.2 % up to 384 rows).  tune_gemm_estimate.py of the Python package times and fits in this way.
 struct PipeTile {
     int bm, bn;
-    int slots;                                          // (128 x 128 tile) work items wanted before K is split no further
 };
-constexpr PipeTile kFlatTile{64, 256, 2 * kComputeUnits}, kMidTile{128, 128, kComputeUnits + kComputeUnits / 2},
-    kBigTile{256, 256, kComputeUnits}, kHalfTile{128, 256, 2 * kComputeUnits};
+constexpr PipeTile kFlatTile{64, 256}, kMidTile{128, 128}, kBigTile{256, 256}, kHalfTile{128, 256}, kNarrowTile{64, 128};
 constexpr int kFlatOnlyMaxM = 64;
 
 struct TileCost {
@@ -902,11 +930,27 @@ struct TileCost {
     double b;                                           // us per round: prologue and epilogue of a work item
     int cap;                                            // work items per round
 };
-constexpr TileCost kFlatCost{{0.809, 1.173, 1.302, 1.456}, {1.601, 2.034, 1.971}, 4.39, 2 * kComputeUnits};
-constexpr TileCost kHalfCost{{1.427, 1.531, 1.573, 1.894}, {2.592, 3.118, 3.411}, 5.92, 2 * kComputeUnits};
-constexpr TileCost kBigCost{{2.052, 2.302, 2.454, 2.523}, {2.445, 2.908, 3.461}, 9.34, kComputeUnits};
-constexpr double kReduceUs = 4.87, kReduceUsPerMB = 0.176;      // reduction kernel of a K split
-constexpr double kSkUs = 34.7, kSkUsPerSharer = 0.68;           // even scheduling: slabs, and the serial part per sharer
+constexpr TileCost kFlatCost{{0.800, 0.868, 0.905, 1.150}, {1.662, 1.908, 2.013}, 2.99, 2 * kComputeUnits};
+constexpr TileCost kHalfCost{{1.125, 1.183, 1.243, 1.817}, {2.587, 3.045, 3.491}, 5.67, 2 * kComputeUnits};
+constexpr TileCost kBigCost{{2.020, 2.049, 2.081, 2.238}, {2.220, 2.910, 3.533}, 7.54, kComputeUnits};
+constexpr TileCost kNarrowCost{{0.551, 0.515, 0.747, 1.243}, {1.388, 1.925, 2.255}, 2.73, 4 * kComputeUnits};
+constexpr TileCost kMidCost{{0.709, 0.737, 0.782, 1.046}, {1.472, 1.730, 1.981}, 3.52, 2 * kComputeUnits};
+constexpr double kReduceUs = 4.38, kReduceUsPerMB = 0.184;      // reduction kernel of a K split
+constexpr double kSkUs = 38.4, kSkUsPerSharer = 0.52;           // even scheduling: slabs, and the serial part per sharer
+struct Estimate {
+    TileCost flat, half, big;
+    double reduce_us, reduce_us_per_mb, sk_us, sk_us_per_sharer;
+    bool all_tiles;                                     // with the tiles of 128 columns, and a short last row tile counted as such
+};
+constexpr Estimate kNow{kFlatCost, kHalfCost, kBigCost, kReduceUs, kReduceUsPerMB, kSkUs, kSkUsPerSharer, true};
+// The workspace that callers are asked for, and with it the most K splits that a launch may have, come from an estimate with
+// constants that stay as they are, whatever becomes of the kernel: a size once asked for is enough for good.  Fused calls of up to
+// 64 rows have exactly its number of splits: with another one their sums, and the residual streams that they feed, would be
+// rounded otherwise.
+constexpr Estimate kSizes{{{0.809, 1.173, 1.302, 1.456}, {1.601, 2.034, 1.971}, 4.39, 2 * kComputeUnits},
+                          {{1.427, 1.531, 1.573, 1.894}, {2.592, 3.118, 3.411}, 5.92, 2 * kComputeUnits},
+                          {{2.052, 2.302, 2.454, 2.523}, {2.445, 2.908, 3.461}, 9.34, kComputeUnits},
+                          4.87, 0.176, 34.7, 0.68, false};
 constexpr int kSplitMajorMinPairs = 16;
 constexpr int kSkMinTiles = 128;                        // fewer tiles: the fixed K split (the fit holds no such launch)
 
@@ -928,38 +972,37 @@ double rounds_us(const TileCost& c, int64_t items, double pairs_per_item)
 }
 
 // `tiles` whole tiles (splits = 1), or each in `splits` K ranges followed by the reduction kernel
-double split_launch_us(const TileCost& c, int64_t tiles, int splits, int64_t M, int64_t N, int64_t K)
+double split_launch_us(const Estimate& e, const TileCost& c, int64_t tiles, int splits, int64_t M, int64_t N, int64_t K)
 {
     double us = rounds_us(c, tiles * splits, (double)(K / (2 * BK)) / splits);
-    if (splits > 1) us += kReduceUs + kReduceUsPerMB * (double)splits * (double)M * (double)N * 4e-6;
+    if (splits > 1) us += e.reduce_us + e.reduce_us_per_mb * (double)splits * (double)M * (double)N * 4e-6;
     return us;
 }
 
-const TileCost* cost_of(const PipeTile& t)
+const TileCost& cost_of(const Estimate& e, const PipeTile& t)
 {
-    return t.bm == 64 ? &kFlatCost : t.bm == 256 ? &kBigCost : t.bn == 256 ? &kHalfCost : nullptr;
+    if (t.bn == 128) return t.bm == 64 ? kNarrowCost : kMidCost;
+    return t.bm == 64 ? e.flat : t.bm == 256 ? e.big : e.half;
 }
 
-// The number of K splits of a launch with the tile `t` (gemm_splits forces one).  Which number pays depends on the
+// The number of K splits of a launch with the tile `t`, at most `most` (gemm_splits forces one).  Which number pays depends on the
 // tile count as much as on K: 1024 x 4096 x 4096 on 128 tiles of 128 x 256 takes 56 us unsplit, 44.6 in two splits
 // (one work item per compute unit) and 53 in four; 256 x 4096 x 13696 on 32 such tiles 177, 95, 55 and 41 us in one,
 // two, four and eight.
-int choose_splits(const PipeTile& t, int64_t tiles, int64_t M, int64_t N, int64_t K)
+int choose_splits(const Estimate& e, const PipeTile& t, int64_t tiles, int64_t M, int64_t N, int64_t K, int64_t most)
 {
     const int forced = knob("gemm_splits");
     const int64_t pairs = K / (2 * BK);
     if (forced > 0) return (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(forced, pairs), kMaxSplits));   // tests: down to one pair per split
-    // every compute unit already has a tile: the partial sums and their reduction cost more than a second
-    // workgroup per unit gains
-    if (tiles >= kComputeUnits || tiles <= 0) return 1;
-    const int max_splits = (int)std::max<int64_t>(1, std::min<int64_t>(pairs / kMinPairsPerSplit, kMaxSplits));
-    const TileCost* c = cost_of(t);
-    if (c == nullptr)                                   // (the 128 x 128 tile, forced launches only: as many as fill its slots)
-        return (int)std::max<int64_t>(1, std::min<int64_t>(t.slots / tiles, max_splits));
+    // every compute unit already has a tile (of the smallest, two): the partial sums and their reduction cost more than further
+    // workgroups per unit gain
+    const TileCost& c = cost_of(e, t);
+    if (tiles >= std::max(kComputeUnits, c.cap / 2) || tiles <= 0) return 1;
+    const int max_splits = (int)std::min<int64_t>(std::min<int64_t>(pairs / kMinPairsPerSplit, kMaxSplits), most);
     int best = 1;
-    double best_us = split_launch_us(*c, tiles, 1, M, N, K);
+    double best_us = split_launch_us(e, c, tiles, 1, M, N, K);
     for (int sp = 2; sp <= max_splits; ++sp) {
-        const double us = split_launch_us(*c, tiles, sp, M, N, K);
+        const double us = split_launch_us(e, c, tiles, sp, M, N, K);
         if (us < best_us) {
             best_us = us;
             best = sp;
@@ -968,20 +1011,31 @@ int choose_splits(const PipeTile& t, int64_t tiles, int64_t M, int64_t N, int64_
     return best;
 }
 
-// whole tiles, or the K split that the estimate puts ahead, with its reduction kernel
-double tile_launch_us(const PipeTile& t, const TileCost& c, int64_t M, int64_t N, int64_t K, bool whole_tiles)
+// (gated calls have as many: halves of bn / 2 columns of the N / 2, and N is even)
+int64_t pipe_tiles(const PipeTile& t, int64_t M, int64_t N) { return ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn); }
+
+constexpr int64_t kShortMaxTiles = 6;                   // row tiles of a launch with a short last one (see the kernel)
+bool short_last(const PipeTile& t, int64_t M, int64_t tiles, int splits)
 {
-    const int64_t tiles = ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
-    return split_launch_us(c, tiles, whole_tiles ? 1 : choose_splits(t, tiles, M, N, K), M, N, K);
+    const int64_t m_tiles = (M + t.bm - 1) / t.bm;
+    return t.bm == 128 && t.bn == 256 && splits == 1 && m_tiles > 1 && m_tiles <= kShortMaxTiles && tiles >= kComputeUnits &&
+           M % t.bm != 0 && M % t.bm <= 64;
+}
+
+// whole tiles (a short last row tile counts as 0.6), or `splits` K ranges of each and the reduction kernel
+double tile_launch_us(const Estimate& e, const PipeTile& t, int splits, int64_t M, int64_t N, int64_t K)
+{
+    int64_t tiles = pipe_tiles(t, M, N);
+    if (e.all_tiles && short_last(t, M, tiles, splits)) tiles -= tiles / ((M + t.bm - 1) / t.bm) * 2 / 5;
+    return split_launch_us(e, cost_of(e, t), tiles, splits, M, N, K);
 }
 
 // even scheduling of `tiles` large tiles, of which `rem` are shared out
-double sk_launch_us(int64_t tiles, int64_t rem, int64_t pairs)
+double sk_launch_us(const Estimate& e, int64_t tiles, int64_t rem, int64_t pairs)
 {
     const double sharers = std::min<double>((double)kComputeUnits / (double)rem + 1.0, (double)pairs);
-    const double whole_rounds = (double)(tiles / kComputeUnits) * ((double)pairs * kBigCost.hi[2] + kBigCost.b);
-    return whole_rounds + (double)rem * (double)pairs / kComputeUnits * kBigCost.hi[2] + kBigCost.b + kSkUs +
-           kSkUsPerSharer * sharers;
+    const double whole_rounds = (double)(tiles / kComputeUnits) * ((double)pairs * e.big.hi[2] + e.big.b);
+    return whole_rounds + (double)rem * (double)pairs / kComputeUnits * e.big.hi[2] + e.big.b + e.sk_us + e.sk_us_per_sharer * sharers;
 }
 
 constexpr size_t kSkCounterBytes = 1024;                // 255 counters at most, then the slabs (16-byte aligned)
@@ -995,22 +1049,22 @@ struct SkPlan {
 // With M = 2048, G = 128: N = 27392, K = 5120 (856 tiles) 547 -> 525 us; N = 5120, K = 13696 (160 tiles) 293 -> 275 us;
 // but N = 5120, K = 5120 (160 tiles) 113 -> 133 us and N = 15360, K = 5120 (480 tiles) 286 -> 316 us.  (Shared tiles
 // taken row by row, see the kernel; column by column the first two were 525 and 284.)
-SkPlan sk_plan(int64_t tiles, int64_t K, int bm, int bn, bool allowed)
+SkPlan sk_plan(const Estimate& e, const PipeTile& t, int64_t tiles, int64_t K, size_t room)
 {
     SkPlan p{false, 0, 0, 0, 0, 0.0};
     const int forced = knob("gemm_sk");
-    if (!allowed || forced == 2 || bm != 256 || bn != 256 || tiles <= 0) return p;
+    if (room == 0 || forced == 2 || t.bm != 256 || tiles <= 0) return p;
     p.rounds_dp = (int)(tiles / kComputeUnits);
     p.rem_tiles = (int)(tiles % kComputeUnits);
     p.pairs = (int)(K / (2 * BK));
     if (p.rem_tiles == 0 || tiles > 0x3fffffffLL || p.pairs > 8192) return p;      // (the kernel's unit arithmetic is 32-bit)
-    p.us = sk_launch_us(tiles, p.rem_tiles, p.pairs);
+    p.us = sk_launch_us(e, tiles, p.rem_tiles, p.pairs);
     if (forced != 1) {
         if (tiles < kSkMinTiles) return p;
-        if (p.us >= rounds_us(kBigCost, tiles, (double)p.pairs)) return p;
+        if (p.us >= rounds_us(e.big, tiles, (double)p.pairs)) return p;
     }
-    p.on = true;
-    p.workspace_bytes = kSkCounterBytes + (size_t)(kComputeUnits + p.rem_tiles) * (size_t)bm * bn * sizeof(float);
+    p.workspace_bytes = kSkCounterBytes + (size_t)(kComputeUnits + p.rem_tiles) * (size_t)t.bm * t.bn * sizeof(float);
+    p.on = p.workspace_bytes <= room;
     return p;
 }
 
@@ -1024,34 +1078,101 @@ SkPlan sk_plan(int64_t tiles, int64_t K, int bm, int bn, bool allowed)
 constexpr int64_t kHalvesMinK = 18 * BK;
 bool k_halves(const PipeTile& t, int64_t M, int64_t N, int64_t K)
 {
-    return t.bm == 64 && K >= kHalvesMinK && ((M + 63) / 64) * ((N + 255) / 256) <= kComputeUnits;
+    return t.bm == 64 && t.bn == 256 && K >= kHalvesMinK && ((M + 63) / 64) * ((N + 255) / 256) <= kComputeUnits;
 }
 // (the cases above within 12 %, whatever the number of tiles: a compute unit has two wavefronts per SIMD or none)
 constexpr double kHalvesUsPerPair = 1.1;                // us per pair of K slices of the whole K
 
-// Up to 64 rows the flat tile; above, the tile with the shortest estimate.
-// (`sk_allowed`: the launch may use even scheduling; `whole_tiles`: it has no workspace, so neither that nor a K split)
-PipeTile pipe_tile(int64_t M, int64_t N, int64_t K, bool sk_allowed, bool whole_tiles = false)
+size_t partial_bytes(int splits, int64_t M, int64_t N) { return (size_t)splits * (size_t)M * (size_t)N * sizeof(float); }
+
+PipeTile tile_of(int bm, int bn)
 {
-    const int v = knob("gemm_variant");
-    if (v == 4) return kFlatTile;
-    if (v == 3) return kMidTile;
-    if (v == 2) return kBigTile;
-    if (v == 5) return kHalfTile;
-    if (M <= kFlatOnlyMaxM || N <= 0 || K < 2 * BK) return kFlatTile;
-    const double flat_us = whole_tiles && k_halves(kFlatTile, M, N, K) ? (double)(K / (2 * BK)) * kHalvesUsPerPair + kFlatCost.b
-                                                                       : tile_launch_us(kFlatTile, kFlatCost, M, N, K, whole_tiles);
-    const double half_us = tile_launch_us(kHalfTile, kHalfCost, M, N, K, whole_tiles);
-    double big_us = tile_launch_us(kBigTile, kBigCost, M, N, K, whole_tiles);
-    const SkPlan skp = sk_plan(((M + 255) / 256) * ((N + 255) / 256), K, 256, 256, sk_allowed && !whole_tiles);
-    if (skp.on) big_us = std::min(big_us, skp.us);
-    if (half_us < flat_us && half_us <= big_us) return kHalfTile;
-    return flat_us <= big_us ? kFlatTile : kBigTile;
+    if (bm == 64) return bn == 128 ? kNarrowTile : kFlatTile;
+    return bm == 256 ? kBigTile : bn == 256 ? kHalfTile : kMidTile;
 }
 
-PipeTile tile_of(int bm, int bn) { return bm == 64 ? kFlatTile : bm == 256 ? kBigTile : bn == 256 ? kHalfTile : kMidTile; }
+struct PipePlan {
+    PipeTile tile;
+    int splits;
+    SkPlan sk;
+    size_t room;                                        // workspace that the call has to bring
+    size_t bytes(int64_t M, int64_t N) const { return sk.on ? sk.workspace_bytes : splits > 1 ? partial_bytes(splits, M, N) : 0; }
+};
 
-size_t partial_bytes(int splits, int64_t M, int64_t N) { return (size_t)splits * (size_t)M * (size_t)N * sizeof(float); }
+// What a call's launch is: whole tiles without a workspace, else at most `splits` K splits (`exactly`: that many), the even
+// scheduling in `sk_room` bytes or not at all (0).
+struct PipeRules {
+    bool whole_tiles, exactly;
+    int64_t splits;
+    size_t sk_room;
+};
+
+// The tile with the shortest estimate, up to 64 rows one of 64 rows.
+PipePlan shortest(const Estimate& e, int64_t M, int64_t N, int64_t K, const PipeRules& r)
+{
+    auto splits_of = [&](const PipeTile& t) -> int {
+        if (r.whole_tiles) return 1;
+        if (r.exactly && knob("gemm_splits") == 0) return (int)r.splits;
+        return choose_splits(e, t, pipe_tiles(t, M, N), M, N, K, r.splits);
+    };
+    auto plan_of = [&](const PipeTile& t) -> PipePlan {
+        PipePlan p{t, 1, sk_plan(e, t, pipe_tiles(t, M, N), K, r.sk_room), 0};
+        if (!p.sk.on) p.splits = splits_of(t);
+        return p;
+    };
+    switch (knob("gemm_variant")) {
+        case 2: return plan_of(kBigTile);
+        case 3: return plan_of(kMidTile);
+        case 4: return plan_of(kFlatTile);
+        case 5: return plan_of(kHalfTile);
+        case 6: return plan_of(kNarrowTile);
+        default: break;
+    }
+    if (N <= 0 || K < 2 * BK) return plan_of(kFlatTile);
+    PipeTile best = kFlatTile;
+    double best_us = r.whole_tiles && k_halves(kFlatTile, M, N, K) ? (double)(K / (2 * BK)) * kHalvesUsPerPair + e.flat.b
+                                                                   : tile_launch_us(e, kFlatTile, splits_of(kFlatTile), M, N, K);
+    auto consider = [&](const PipeTile& t) {
+        const double us = tile_launch_us(e, t, splits_of(t), M, N, K);
+        if (us < best_us) {
+            best = t;
+            best_us = us;
+        }
+    };
+    if (e.all_tiles) consider(kNarrowTile);
+    if (M > kFlatOnlyMaxM) {
+        if (e.all_tiles) consider(kMidTile);
+        consider(kHalfTile);
+        consider(kBigTile);
+        const SkPlan sk = sk_plan(e, kBigTile, pipe_tiles(kBigTile, M, N), K, r.sk_room);
+        if (sk.on && sk.us < best_us) best = kBigTile;
+    }
+    return plan_of(best);
+}
+
+// (fused matmuls and the 8-bit format have whole tiles or the fixed K split, `sk` false.  With a knob set a launch has what it asks
+// for, and the room for it.)
+size_t pipe_room(int64_t M, int64_t N, int64_t K, bool sk, PipePlan* plan)
+{
+    const bool steered = knob("gemm_variant") || knob("gemm_splits") || knob("gemm_sk");
+    const PipePlan p = shortest(steered ? kNow : kSizes, M, N, K, PipeRules{false, false, kMaxSplits, sk ? ~(size_t)0 : 0});
+    if (plan) *plan = p;
+    return p.bytes(M, N);
+}
+
+PipePlan pipe_plan(int64_t M, int64_t N, int64_t K, bool fused, bool sk)
+{
+    PipePlan p;
+    const size_t room = pipe_room(M, N, K, sk, &p);
+    const bool steered = knob("gemm_variant") || knob("gemm_splits") || knob("gemm_sk");
+    if (!steered) {
+        const bool exactly = fused && M <= kFlatOnlyMaxM;
+        p = shortest(kNow, M, N, K, PipeRules{false, exactly, exactly ? p.splits : std::max<int64_t>(1, (int64_t)(room / partial_bytes(1, M, N))),
+                                              sk ? room : 0});
+    }
+    p.room = room;
+    return p;
+}
 
 __global__ void zero_u32_kernel(unsigned int* p, int n)
 {
@@ -1059,18 +1180,9 @@ __global__ void zero_u32_kernel(unsigned int* p, int n)
     if (i < n) p[i] = 0u;
 }
 
-int64_t pipe_tiles(const PipeTile& t, int64_t M, int64_t N, bool swiglu)
-{
-    const int64_t n_tiles = swiglu ? (N / 2 + t.bn / 2 - 1) / (t.bn / 2) : (N + t.bn - 1) / t.bn;
-    return ((M + t.bm - 1) / t.bm) * n_tiles;
-}
-
-constexpr int64_t kShortMaxTiles = 6;                   // row tiles of a launch with a short last one (see the kernel)
-
-// (`whole_tiles`: neither a K split nor the even scheduling, hence no workspace)
 template <int G, int WGM, int WGN, bool FUSED, int BM, int BN, bool E8 = false, bool BF = false, int KS = 1>
 int launch_pipe(const half_t* x, int64_t M, const uint4* c, int64_t N, int64_t K, half_t* y, void* workspace,
-                size_t workspace_bytes, hipStream_t stream, const Fusion& f, bool whole_tiles = false)
+                size_t workspace_bytes, hipStream_t stream, const Fusion& f, const PipePlan& plan)
 {
     PipeFusion fu;
     fu.residual = static_cast<const half_t*>(f.residual);
@@ -1085,9 +1197,9 @@ int launch_pipe(const half_t* x, int64_t M, const uint4* c, int64_t N, int64_t K
     fu.n_half = N / 2;
     const PipeTile shape = tile_of(BM, BN);
     const int64_t m_tiles = (M + BM - 1) / BM;
-    const int64_t tiles = pipe_tiles(shape, M, N, f.swiglu), n_tiles = tiles / m_tiles;
-    const SkPlan skp = sk_plan(tiles, K, BM, BN, !FUSED && !E8 && !BF && !whole_tiles);
-    const int splits = skp.on || whole_tiles ? 1 : choose_splits(shape, tiles, M, N, K);
+    const int64_t tiles = pipe_tiles(shape, M, N), n_tiles = tiles / m_tiles;
+    const SkPlan& skp = plan.sk;
+    const int splits = plan.splits;
     if (tiles * splits > 0x3fffffffLL) return E0M4_ERR_SHAPE;
     // Long K ranges gain from the order by split (1024 x 4096 x 13696 in four splits 122 -> 116 us, 512 x 2048 x 16384
     // in eight 46.9 -> 44.6), short ones lose (128 x 4608 x 4096 in eight splits of four pairs 19.6 -> 21.6, 1024 x 4608
@@ -1097,17 +1209,13 @@ int launch_pipe(const half_t* x, int64_t M, const uint4* c, int64_t N, int64_t K
     const int total = (int)(tiles * splits);
     const int per_xcd = (total + kNumXcd - 1) / kNumXcd;
     float* partial = nullptr;
-    if (splits > 1) {
-        if (workspace == nullptr || workspace_bytes < partial_bytes(splits, M, N)) return E0M4_ERR_WORKSPACE;
-        partial = static_cast<float*>(workspace);
-    }
+    if (plan.room > 0 && (workspace == nullptr || workspace_bytes < plan.room)) return E0M4_ERR_WORKSPACE;
+    if (splits > 1) partial = static_cast<float*>(workspace);
     SkArgs sk{0, 0, 0, 0, nullptr, nullptr};
     unsigned grid = (unsigned)(per_xcd * kNumXcd);
-    const bool last_short = BM == 128 && BN == 256 && splits == 1 && m_tiles > 1 && m_tiles <= kShortMaxTiles &&
-                            tiles >= kComputeUnits && M % BM != 0 && M % BM <= 64;
+    const bool last_short = short_last(shape, M, tiles, splits);
     if (last_short) grid = (unsigned)((((m_tiles - 1) * n_tiles + kNumXcd - 1) / kNumXcd + (n_tiles + kNumXcd - 1) / kNumXcd) * kNumXcd);
     if (skp.on) {
-        if (workspace == nullptr || workspace_bytes < skp.workspace_bytes) return E0M4_ERR_WORKSPACE;
         sk.enabled = 1;
         sk.rounds_dp = skp.rounds_dp;
         sk.rem_tiles = skp.rem_tiles;
@@ -1159,43 +1267,40 @@ int launch_pipe(const half_t* x, int64_t M, const uint4* c, int64_t N, int64_t K
 
 bool gemm_pipe_supported(int64_t K) { return K >= 128 && (K % (2 * BK)) == 0; }
 
-// (`fused`: the call comes from a fused matmul or the 8-bit format, whose kernels keep whole tiles or the fixed K split)
 size_t gemm_pipe_workspace_bytes(int64_t M, int64_t N, int64_t K, bool swiglu, bool fused)
 {
-    const PipeTile shape = pipe_tile(M, N, K, !fused && !swiglu);
-    const int64_t tiles = pipe_tiles(shape, M, N, swiglu);
-    if (tiles == 0 || !gemm_pipe_supported(K)) return 0;
-    const SkPlan skp = sk_plan(tiles, K, shape.bm, shape.bn, !fused && !swiglu);
-    if (skp.on) return skp.workspace_bytes;
-    const int splits = choose_splits(shape, tiles, M, N, K);
-    return splits > 1 ? partial_bytes(splits, M, N) : 0;
+    if (M <= 0 || N <= 0 || !gemm_pipe_supported(K)) return 0;
+    return pipe_room(M, N, K, !fused && !swiglu, nullptr);
 }
 
 namespace {
 
 // the kernel instance of a tile
 template <int G, bool FUSED, bool E8 = false, bool BF = false>
-int launch_pipe_as(const PipeTile& t, const half_t* x, int64_t M, const uint4* c, int64_t N, int64_t K, half_t* y,
-                   void* workspace, size_t workspace_bytes, hipStream_t stream, const Fusion& f, bool whole_tiles = false)
+int launch_pipe_as(const PipePlan& p, const half_t* x, int64_t M, const uint4* c, int64_t N, int64_t K, half_t* y,
+                   void* workspace, size_t workspace_bytes, hipStream_t stream, const Fusion& f)
 {
+    const PipeTile& t = p.tile;
     if constexpr (BF) {
         if (k_halves(t, M, N, K))
-            return launch_pipe<G, 1, 4, FUSED, 64, 256, E8, BF, 2>(x, M, c, N, K, y, workspace, workspace_bytes, stream, f, whole_tiles);
+            return launch_pipe<G, 1, 4, FUSED, 64, 256, E8, BF, 2>(x, M, c, N, K, y, workspace, workspace_bytes, stream, f, p);
     }
+    if (t.bm == 64 && t.bn == 128)
+        return launch_pipe<G, 1, 4, FUSED, 64, 128, E8, BF>(x, M, c, N, K, y, workspace, workspace_bytes, stream, f, p);
     if (t.bm == 64)
-        return launch_pipe<G, 1, 4, FUSED, 64, 256, E8, BF>(x, M, c, N, K, y, workspace, workspace_bytes, stream, f, whole_tiles);
+        return launch_pipe<G, 1, 4, FUSED, 64, 256, E8, BF>(x, M, c, N, K, y, workspace, workspace_bytes, stream, f, p);
     if (t.bm == 128 && t.bn == 256)
-        return launch_pipe<G, 1, 4, FUSED, 128, 256, E8, BF>(x, M, c, N, K, y, workspace, workspace_bytes, stream, f, whole_tiles);
+        return launch_pipe<G, 1, 4, FUSED, 128, 256, E8, BF>(x, M, c, N, K, y, workspace, workspace_bytes, stream, f, p);
     if (t.bm == 128)
-        return launch_pipe<G, 2, 2, FUSED, 128, 128, E8, BF>(x, M, c, N, K, y, workspace, workspace_bytes, stream, f, whole_tiles);
-    return launch_pipe<G, 2, 4, FUSED, 256, 256, E8, BF>(x, M, c, N, K, y, workspace, workspace_bytes, stream, f, whole_tiles);
+        return launch_pipe<G, 1, 4, FUSED, 128, 128, E8, BF>(x, M, c, N, K, y, workspace, workspace_bytes, stream, f, p);
+    return launch_pipe<G, 2, 4, FUSED, 256, 256, E8, BF>(x, M, c, N, K, y, workspace, workspace_bytes, stream, f, p);
 }
 
 template <int G, bool FUSED>
 int launch_pipe_tile(const half_t* x, int64_t M, const uint4* c, int64_t N, int64_t K, half_t* y, void* workspace,
                      size_t workspace_bytes, hipStream_t stream, const Fusion& f)
 {
-    return launch_pipe_as<G, FUSED>(pipe_tile(M, N, K, !FUSED), x, M, c, N, K, y, workspace, workspace_bytes, stream, f);
+    return launch_pipe_as<G, FUSED>(pipe_plan(M, N, K, FUSED, !FUSED), x, M, c, N, K, y, workspace, workspace_bytes, stream, f);
 }
 
 }  // namespace
@@ -1207,7 +1312,7 @@ int launch_gemm_pipe8(const void* X, int64_t M, const void* packed, int64_t N, i
     const half_t* x = static_cast<const half_t*>(X);
     const uint4* c = static_cast<const uint4*>(packed);
     half_t* y = static_cast<half_t*>(Y);
-    return launch_pipe_as<128, false, true>(pipe_tile(M, N, K, false), x, M, c, N, K, y, workspace, workspace_bytes, stream,
+    return launch_pipe_as<128, false, true>(pipe_plan(M, N, K, false, false), x, M, c, N, K, y, workspace, workspace_bytes, stream,
                                             Fusion{});
 }
 
@@ -1218,7 +1323,7 @@ int launch_gemm_pipe8_fused(const Fusion& f, const void* X, int64_t M, const voi
     const uint4* c = static_cast<const uint4*>(packed);
     half_t* y = static_cast<half_t*>(Y);
     if (f.swiglu && (N % (2 * kBlockRows) != 0 || gated_half_bytes(N, 2 * K, 128) > kMaxHalfBytes)) return E0M4_ERR_SHAPE;
-    return launch_pipe_as<128, true, true>(pipe_tile(M, N, K, false), x, M, c, N, K, y, workspace, workspace_bytes, stream, f);
+    return launch_pipe_as<128, true, true>(pipe_plan(M, N, K, true, false), x, M, c, N, K, y, workspace, workspace_bytes, stream, f);
 }
 
 int launch_gemm_pipe(const void* X, int64_t M, const void* packed, int64_t N, int64_t K, int group, void* Y,
@@ -1242,8 +1347,8 @@ namespace {
 template <int G>
 int launch_pipe_bf16(const half_t* x, int64_t M, const uint4* c, int64_t N, int64_t K, half_t* y, hipStream_t stream)
 {
-    return launch_pipe_as<G, false, false, true>(pipe_tile(M, N, K, false, true), x, M, c, N, K, y, nullptr, 0, stream,
-                                                 Fusion{}, true);
+    const PipePlan p = shortest(kNow, M, N, K, PipeRules{true, false, 1, 0});
+    return launch_pipe_as<G, false, false, true>(p, x, M, c, N, K, y, nullptr, 0, stream, Fusion{});
 }
 }  // namespace
 

@@ -1,11 +1,11 @@
 """Re-fit the constants of the prefill GEMM's launch-time estimate (csrc/e0m4_gemm_pipe.hip: kFlatCost, kHalfCost,
-kBigCost, kReduceUs, kReduceUsPerMB, kSkUs, kSkUsPerSharer) on the GPU at hand.
+kBigCost, kNarrowCost, kMidCost, kReduceUs, kReduceUsPerMB, kSkUs, kSkUsPerSharer) on the GPU at hand.
 
     python -m paper_2403_20041_amd.tune_gemm_estimate time  timings.txt [--problems 120] [--seed 7]
     python -m paper_2403_20041_amd.tune_gemm_estimate fit   timings.txt [more.txt ...]
 
 `time` draws seeded problems (M = 65 .. 8192, N and K multiples of 128, plus the layer shapes of synth_inputs) and
-times e0m4_matmul on each with every tile forced (knob gemm_variant 4, 5, 2), one to eight K splits (gemm_splits)
+times e0m4_matmul on each with every tile forced (knob gemm_variant 4, 5, 2, 6, 3), one to eight K splits (gemm_splits)
 and, where the large tile leaves a partly filled last round of at least 128 tiles, even scheduling (gemm_sk 1): us
 per launch in a HIP graph over rotating weight copies, so that the weights come from HBM.  `fit` minimises the squared
 logarithm of estimate / measurement over all timings, prints the constants in the order of the C++ initialisers and
@@ -22,11 +22,14 @@ import re
 import sys
 
 CU = 256
-TILES = {"f": (64, 256, 2 * CU, 0), "h": (128, 256, 2 * CU, 1), "b": (256, 256, CU, 2)}   # rows, columns, items per round
-VARIANT = {"f": 4, "h": 5, "b": 2}
+TILES = {"f": (64, 256, 2 * CU, 0), "h": (128, 256, 2 * CU, 1), "b": (256, 256, CU, 2),    # rows, columns, items per round
+         "n": (64, 128, 4 * CU, 3), "m": (128, 128, 2 * CU, 4)}
+VARIANT = {"f": 4, "h": 5, "b": 2, "n": 6, "m": 3}
 NP = 8                                                      # constants per tile: four low knots, three high, b
 START = [0.8, 1.2, 1.3, 1.45, 1.6, 2.0, 2.0, 4.4, 1.4, 1.5, 1.6, 1.9, 2.6, 3.1, 3.4, 5.9,
-         2.0, 2.3, 2.45, 2.5, 2.45, 2.9, 3.5, 9.3, 4.9, 0.18, 35.0, 0.7]
+         2.0, 2.3, 2.45, 2.5, 2.45, 2.9, 3.5, 9.3, 0.5, 0.6, 0.7, 1.1, 1.3, 1.7, 2.2, 4.4,
+         0.7, 0.8, 0.9, 1.1, 1.3, 1.6, 1.9, 5.0, 4.9, 0.18, 35.0, 0.7]
+NT = len(TILES)
 
 
 def interp(x, xs, ys):
@@ -40,7 +43,7 @@ def estimate(p, M, N, K, tile, splits):
     """The launch time in us as rounds_us / split_launch_us / sk_launch_us compute it; splits = 'sk': even scheduling."""
     bm, bn, cap, i = TILES[tile]
     lo, hi, b = p[NP * i:NP * i + 4], p[NP * i + 4:NP * i + 7], p[NP * i + 7]
-    r0, r1, c0, c1 = p[3 * NP:3 * NP + 4]
+    r0, r1, c0, c1 = p[NT * NP:NT * NP + 4]
     tiles, pairs = -(-M // bm) * -(-N // bn), K // 128
     if splits == "sk":
         full, rem = divmod(tiles, CU)
@@ -62,7 +65,7 @@ def read_timings(paths):
     groups = {}
     for path in paths:
         for line in open(path):
-            m = re.match(r"(\d+) (\d+) (\d+) ([fhb]) (\d+|sk) ([0-9.]+)\s*$", line)
+            m = re.match(r"(\d+) (\d+) (\d+) ([fhbnm]) (\d+|sk) ([0-9.]+)\s*$", line)
             if m:
                 M, N, K = int(m.group(1)), int(m.group(2)), int(m.group(3))
                 s = m.group(5) if m.group(5) == "sk" else int(m.group(5))
@@ -76,8 +79,8 @@ def fit(paths):
 
     groups = read_timings(paths)
     pts = [(M, N, K, t, s, us) for (M, N, K), c in groups.items() for t, s, us in c]
-    lo = ([0.01] * 7 + [0.0]) * 3 + [0.0] * 4
-    hi = ([8.0] * 7 + [40.0]) * 3 + [50.0, 5.0, 100.0, 10.0]
+    lo = ([0.01] * 7 + [0.0]) * NT + [0.0] * 4
+    hi = ([8.0] * 7 + [40.0]) * NT + [50.0, 5.0, 100.0, 10.0]
 
     def resid(p):
         return [math.log(estimate(p, M, N, K, t, s) / us) for M, N, K, t, s, us in pts]
@@ -89,10 +92,10 @@ def fit(paths):
     print("%d timings of %d problems; rms of log(estimate / measured) %.3f" % (len(pts), len(groups), r.std()))
     print("choice by the estimate over the measured best: geometric mean %.4f, worst %.3f"
           % (math.exp(sum(math.log(x) for x in regret) / len(regret)), max(regret)))
-    for name, i in (("kFlatCost", 0), ("kHalfCost", 1), ("kBigCost", 2)):
+    for name, i in (("kFlatCost", 0), ("kHalfCost", 1), ("kBigCost", 2), ("kNarrowCost", 3), ("kMidCost", 4)):
         q = p[NP * i:NP * i + NP]
         print("%s{{%.3f, %.3f, %.3f, %.3f}, {%.3f, %.3f, %.3f}, %.2f, ...}" % ((name,) + tuple(q)))
-    print("kReduceUs = %.2f, kReduceUsPerMB = %.3f, kSkUs = %.1f, kSkUsPerSharer = %.2f" % tuple(p[3 * NP:3 * NP + 4]))
+    print("kReduceUs = %.2f, kReduceUsPerMB = %.3f, kSkUs = %.1f, kSkUsPerSharer = %.2f" % tuple(p[NT * NP:NT * NP + 4]))
 
 
 def time_problems(out_path, n_problems, seed):
@@ -124,7 +127,7 @@ def time_problems(out_path, n_problems, seed):
             cands = []
             for tile, (bm, bn, cap, _) in TILES.items():
                 tiles = -(-M // bm) * -(-N // bn)
-                for s in ((1,) if tiles >= CU else [s for s in (1, 2, 3, 4, 6, 8) if s == 1 or pairs // s >= 4]):
+                for s in ((1,) if tiles >= max(CU, cap // 2) else [s for s in (1, 2, 3, 4, 6, 8) if s == 1 or pairs // s >= 4]):
                     cands.append((tile, s))
             big = -(-M // 256) * -(-N // 256)
             if big >= 128 and big % CU:

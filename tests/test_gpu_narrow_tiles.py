@@ -1,0 +1,65 @@
+"""GEMM tiles of 128 columns, whose wavefronts hold one block of 32 columns: last tiles of rows and columns, row lengths that are no
+multiple of 8, the gated product of two wavefronts' sums in whole tiles and in K splits, a K range shorter than the pipeline, every
+group and format; the same bits as the tiles of 256 columns in the same number of splits; and the number of K splits, hence the
+bits, of fused calls of up to 64 rows by default routes."""
+import pytest
+
+import synth_inputs
+from test_gpu_bf16_e0m3 import assert_bf16_quantize_exact, bf_dev, check_bf16_matmul
+from test_gpu_fused import COMBOS, e0m4, quantized, run_fused, to_dev, torch  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+def with_knobs(e0m4, fn, **knobs):
+    for k, v in knobs.items():
+        e0m4.e0m4_set_knob(k, v)
+    try:
+        return fn()
+    finally:
+        for k in knobs:
+            e0m4.e0m4_set_knob(k, 0)
+
+
+@pytest.mark.parametrize("variant", [3, 6])
+@pytest.mark.parametrize("splits", [1, 3])
+@pytest.mark.parametrize("norm,swiglu,res", COMBOS)
+def test_against_the_oracle(e0m4, oracle, variant, splits, norm, swiglu, res):
+    for M, N, K, G, bits in ((300, 640, 1024, 128, 4), (9, 192, 384, 64, 4), (130, 1088, 512, 32, 4), (65, 128, 128, 128, 4), (129, 704, 640, 128, 8)):
+        with_knobs(e0m4, lambda: run_fused(e0m4, oracle, M, N, K, G, seed=1400 + M, norm=norm, swiglu=swiglu, res=res, outliers=True, bits=bits),
+                   gemm_variant=variant, gemm_splits=splits, gemv_mfma=1)
+
+
+@pytest.mark.parametrize("M,N,K", [(64, 192, 1024), (200, 327, 640), (257, 576, 2048), (129, 1152, 128)])
+def test_bits_of_the_wide_tiles(e0m4, oracle, M, N, K):
+    codes, _ = quantized(e0m4, oracle, N, K, 128, seed=1420 + N)
+    X = to_dev(synth_inputs.activations(M, K, seed=1421 + M, outlier_frac=0.01))
+    for swiglu in (False, True):
+        if swiglu and N % 64:
+            continue
+        R = to_dev(synth_inputs.residual(M, N // 2 if swiglu else N, 1422))
+        for splits in (1, 2):
+            Y = [with_knobs(e0m4, lambda: e0m4.e0m4_matmul_fused(X, codes, N, K, 128, residual=R, epilogue=1 if swiglu else 0),
+                            gemm_variant=v, gemm_splits=splits, gemv_mfma=1) for v in (4, 6, 3)]
+            assert torch.equal(Y[0], Y[1]) and torch.equal(Y[0], Y[2]), (swiglu, splits)
+
+
+# (K splits as by 64 x 256 tiles: the most, fewer, and as many tiles as compute units)
+@pytest.mark.parametrize("N,K,splits", [(1536, 5888, 8), (4096, 13696, 8), (9216, 3072, 6), (27392, 4096, 4), (65536, 1024, 1)])
+def test_fused_calls_of_few_rows_keep_their_splits(e0m4, N, K, splits):
+    M = 45
+    codes = e0m4.e0m4_quantize(to_dev(synth_inputs.weights(256, K, seed=1431)).repeat(N // 256, 1), 128)[0]
+    X, R = to_dev(synth_inputs.activations(M, K, seed=1432)), to_dev(synth_inputs.residual(M, N, 1433))
+    forced = with_knobs(e0m4, lambda: e0m4.e0m4_matmul_fused(X, codes, N, K, 128, residual=R), gemm_variant=4, gemm_splits=splits, gemv_mfma=1)
+    by_default = with_knobs(e0m4, lambda: e0m4.e0m4_matmul_fused(X, codes, N, K, 128, residual=R), gemv_mfma=1)
+    assert torch.equal(forced, by_default)
+
+
+@pytest.mark.parametrize("variant", [3, 6])
+@pytest.mark.parametrize("M,N,K,G", [(300, 600, 1024, 128), (129, 272, 384, 32), (65, 203, 2048, 64), (64, 128, 128, 64)])
+def test_bf16(e0m4, oracle, variant, M, N, K, G):
+    codes, What, _ = assert_bf16_quantize_exact(e0m4, oracle, synth_inputs.weights_bf16(N, K, seed=1440 + N + K), G)
+    X = synth_inputs.activations_bf16(M, K, seed=1441 + M)
+    Y = with_knobs(e0m4, lambda: e0m4.e0m4_bf16_matmul(bf_dev(X), codes, N, K, G), gemm_variant=variant)
+    Yref, absdot = oracle.bf16_matmul(X, What)
+    check_bf16_matmul(oracle, Y, Yref, absdot, "bf16 gemm variant %d M=%d N=%d K=%d" % (variant, M, N, K))
