@@ -28,7 +28,7 @@ thread_local Knob g_knobs[] = {
     // X block by block wherever that can run
     {"gemv_mfma", 0},
     {"gemv_xreg", 0},                  // M = 1 kernel, a wavefront's activations in registers: 2 never
-    {"gemm_variant", 0},               // 1: small-tile kernel; pipelined kernel with tiles of 2: 256 x 256, 3: 128 x 128, 4: 64 x 256, 5: 128 x 256, 6: 64 x 128
+    {"gemm_variant", 0},               // 1: small-tile kernel; pipelined kernel with tiles of 2: 256 x 256, 3: 128 x 128, 4: 64 x 256, 5: 128 x 256, 6: 64 x 128, 7: that with K quarters
     {"gemm_splits", 0},                // force the number of K splits of the pipelined GEMM kernel
     {"gemm_sk", 0},                    // even scheduling of the 256 x 256 tiles over the compute units: 1 whenever the last round is partly filled, 2 never
     {"gemm_panel", 0},                 // row tiles per panel of the pipelined GEMM's tile numbering (0: the default, -1: whole columns)

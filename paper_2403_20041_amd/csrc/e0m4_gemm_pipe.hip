@@ -133,7 +133,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KS, 2) void gemm_pipe_kernel(const
                                                              int splits, float* __restrict__ partial, PipeFusion fu,
                                                              SkArgs sk)
 {
-    constexpr int kThreads = 64 * WGM * WGN;            // per K half
+    constexpr int kThreads = 64 * WGM * WGN;            // per K part
     constexpr int kStageBytes = BM * kRowBytes;
     // Slices of weights in registers (8-bit codes: twice the registers per slice), stages of activations in LDS, and how many
     // slices ahead those are requested.
@@ -149,7 +149,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KS, 2) void gemm_pipe_kernel(const
     // (even scheduling exists in the instance the launcher uses it with; elsewhere the segment loop below folds away)
     static_assert(!BF || (!FUSED && !E8), "the bfloat16 member has the plain 4-bit kernel only");
     static_assert(!SHORT || (WGM == 1 && BM == 128 && KS == 1), "short last row tiles: of 128 rows");
-    static_assert(KS == 1 || (KS == 2 && BM == 64 && !FUSED), "K halves inside a workgroup: the flat tile, unfused");
+    static_assert(KS == 1 || BM == 64, "K parts inside a workgroup: tiles of 64 rows");
     constexpr bool kSk = !FUSED && !E8 && !BF && BM == 256 && BN == 256;
     const bool sk_on = kSk && sk.enabled;
     const int total = m_tiles * n_tiles * splits;
@@ -196,9 +196,9 @@ __global__ __launch_bounds__(64 * WGM * WGN * KS, 2) void gemm_pipe_kernel(const
     const int all_tiles = m_tiles * n_tiles;
     const int plain_tile = __builtin_amdgcn_readfirstlane(fu.split_major ? item % all_tiles : item / splits);
     const int plain_split = __builtin_amdgcn_readfirstlane(fu.split_major ? item / all_tiles : item % splits);
-    // (KS = 2: no K split of the launch; the two halves of the workgroup's wavefronts take one half of K each)
-    const int half = KS == 2 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / kThreads) : 0;
-    const int k_part = KS == 2 ? half : plain_split, k_parts = KS == 2 ? 2 : splits;
+    // (KS > 1: no K split of the launch; the workgroup's wavefronts take a part of K each)
+    const int part = KS > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / kThreads) : 0;
+    const int k_part = KS > 1 ? part : plain_split, k_parts = KS > 1 ? KS : splits;
     const int plain_kb = __builtin_amdgcn_readfirstlane(2 * (int)((int64_t)(KT_all / 2) * k_part / k_parts));
     const int plain_ke = __builtin_amdgcn_readfirstlane(2 * (int)((int64_t)(KT_all / 2) * (k_part + 1) / k_parts));
   for (int seg = 0; seg < n_segments; ++seg) {
@@ -277,7 +277,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KS, 2) void gemm_pipe_kernel(const
     // (the thread number is made opaque to the optimiser in every segment: what is derived from it -- loader
     // offsets, epilogue rows and masks -- is then computed where it is used, not ahead of the segment loop, where it
     // would hold registers through the K loop)
-    int t = KS == 2 ? (int)threadIdx.x % kThreads : (int)threadIdx.x;
+    int t = KS > 1 ? (int)threadIdx.x % kThreads : (int)threadIdx.x;
     asm volatile("" : "+v"(t));
     const int lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -485,7 +485,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KS, 2) void gemm_pipe_kernel(const
         };
 
         // ---- prologue
-        const uint32_t ring = KS == 2 ? (uint32_t)half * S * kStageBytes : 0u;
+        const uint32_t ring = (uint32_t)part * S * kStageBytes;
         // (in the order that the loop keeps up: slice kt requests activations L slices on, then codes PD slices on)
 #pragma unroll
         for (int d = -(PD > L ? PD : L); d < 0; ++d) {
@@ -536,37 +536,40 @@ __global__ __launch_bounds__(64 * WGM * WGN * KS, 2) void gemm_pipe_kernel(const
     } else {
         k_loop(std::integral_constant<int, TM>{});
     }
-    if (KS == 2) {
-        // The upper half's sums are added to the lower half's, through LDS.  An odd number of pairs of slices gives the
-        // upper half one more, so the lower half waits at the barriers of its last two steps.
-        if (half == 0 && ((KT_all / 2) & 1)) {
+    if (KS > 1) {
+        // The parts' sums are added to the first's, in the order of K, through LDS.  Parts of one pair of slices fewer wait at the
+        // barriers of two steps more.
+        if (kt_end - kt_begin < 2 * ((KT_all / 2 + KS - 1) / KS)) {
             __syncthreads();
             __syncthreads();
         }
         __syncthreads();                                // every wavefront has left the K loop's stages
         floatx4* sums = reinterpret_cast<floatx4*>(smem);
-        if (half == 1) {
+        constexpr int kPart = TM * TN * 4 * kThreads;
+        if (part > 0) {
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
                 for (int j = 0; j < TN; ++j)
 #pragma unroll
                     for (int q = 0; q < 4; ++q)
-                        sums[((i * TN + j) * 4 + q) * kThreads + t] =
+                        sums[(part - 1) * kPart + ((i * TN + j) * 4 + q) * kThreads + t] =
                             floatx4{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
         }
         __syncthreads();
-        if (half == 0) {
+        if (part == 0) {
 #pragma unroll
-            for (int i = 0; i < TM; ++i)
+            for (int s = 0; s < KS - 1; ++s)
 #pragma unroll
-                for (int j = 0; j < TN; ++j)
+                for (int i = 0; i < TM; ++i)
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const floatx4 v = sums[((i * TN + j) * 4 + q) * kThreads + t];
+                    for (int j = 0; j < TN; ++j)
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) acc[i][j][4 * q + e] += v[e];
-                    }
+                        for (int q = 0; q < 4; ++q) {
+                            const floatx4 v = sums[s * kPart + ((i * TN + j) * 4 + q) * kThreads + t];
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) acc[i][j][4 * q + e] += v[e];
+                        }
         }
     }
 
@@ -576,8 +579,8 @@ __global__ __launch_bounds__(64 * WGM * WGN * KS, 2) void gemm_pipe_kernel(const
     // through the K loop: a hundred registers more, and spills in the large tile)
     uint32_t n32 = (uint32_t)N;
     asm volatile("" : "+s"(n32));
-    // (KS = 2: the upper half has no rows to write; gated with TN = 1, the odd wavefronts have none of their own)
-    const int rows_left = KS == 2 && half == 1 ? 0 : (int)min((int64_t)BM, M - m0), cols_left = (int)min((int64_t)BN, N - n0);
+    // (KS > 1: the first part's wavefronts write the rows; gated with TN = 1, the odd wavefronts have none of their own)
+    const int rows_left = KS > 1 && part > 0 ? 0 : (int)min((int64_t)BM, M - m0), cols_left = (int)min((int64_t)BN, N - n0);
     const int rows_mine = TN == 1 && gated && (wave & 1) ? 0 : rows_left;
     const int row0 = wm + 4 * (lane >> 5), col0 = wn + (lane & 31);
     const uint32_t off0 = (uint32_t)row0 * n32 + (uint32_t)col0;
@@ -626,7 +629,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KS, 2) void gemm_pipe_kernel(const
         constexpr int COLS = decltype(cols_c)::value, ROWS = 1024 / COLS, kChunks = TM * 32 / ROWS;
         constexpr int PPR = COLS / 8, RPP = 64 / PPR;   // 16-byte pieces per row, rows per pass (two passes per chunk)
         constexpr int kStride = COLS + 4, NJ = COLS / 32, NR = 16 / NJ;
-        float* turn = reinterpret_cast<float*>(smem + (half * WGM * WGN + wave) * kTurnBytes);
+        float* turn = reinterpret_cast<float*>(smem + (part * WGM * WGN + wave) * kTurnBytes);
         const int prow = lane / PPR, pcol = (lane % PPR) * 8;
         const bool col_ok = wcol + pcol < cols_valid;
         const uint32_t o0 = (uint32_t)(wm + prow) * ld + (uint32_t)(wcol + pcol);
@@ -833,7 +836,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KS, 2) void gemm_pipe_kernel(const
     out_t* yt = reinterpret_cast<out_t*>(Y) + m0 * N + n0;
     if (out_mode == 1)
         store_tile(partial + ((size_t)split * (size_t)M + (size_t)m0) * (size_t)N + (size_t)n0);
-    else if ((n32 & 7u) == 0 && (KS == 2 || (FUSED && fu.residual) || M - m0 < BM || N - n0 < BN))
+    else if ((n32 & 7u) == 0 && (KS > 1 || (FUSED && fu.residual) || M - m0 < BM || N - n0 < BN))
         write_rows(std::integral_constant<int, TN * 32>{}, [&](int i, int r, int j) { return acc[i][j][r]; }, yt,
                    FUSED && fu.residual ? fu.residual + m0 * N + n0 : nullptr, n32, wn, cols_left);
     else
@@ -1083,6 +1086,23 @@ bool k_halves(const PipeTile& t, int64_t M, int64_t N, int64_t K)
 // (the cases above within 12 %, whatever the number of tiles: a compute unit has two wavefronts per SIMD or none)
 constexpr double kHalvesUsPerPair = 1.1;                // us per pair of K slices of the whole K
 
+// Fused calls of up to 64 rows in four K splits, to the same bits without partial sums in memory: workgroups of eight wavefronts on
+// 64 x 128 tiles, a pair of wavefronts to a quarter of K each, whose sums are added in LDS in the order of the splits.  One
+// workgroup fits a compute unit, so there have to be nearly as many tiles as units, and not more.  Against the splits, gated, at M = 20, 33, 45
+// and 64 (us): 27392 x 4096 30.5, 33.4, 33.9, 36.9 -> 29.3, 30.2, 29.9, 30.7; 32768 x 2048 25.7, 25.0, 26.7, 30.8 -> 17.8, 22.2, 22.6, 22.8;
+// 30720 x 11008 66.0, 67.5, 69.5, 72.8 -> 64.4, 65.8, 66.6, 66.9.  With fewer tiles 64 x 128 tiles in splits are the
+// better ones (128 tiles, 16384 x 2048 at M = 64 18.5 and 16.8), with more the second round (288 tiles, 36864 x 3072, 1.2 - 1.35 x the splits' time).
+// Rows of Y that are no multiple of 8 long are written by a quarter of the wavefronts element by element (27356 x 4096 at M = 45 33.5
+// -> 36.5), and 8-bit codes gain nothing up to 48 rows (27392 x 4096 at M = 30 37.1 and 38.2): both keep the splits.
+// gemm_variant 7 takes these tiles whatever their number.
+constexpr int64_t kQuartersMinTiles = 160;
+bool k_quarters(int splits, int64_t M, int64_t N)
+{
+    const int64_t tiles = pipe_tiles(kNarrowTile, M, N);
+    const int v = knob("gemm_variant");
+    return splits == 4 && N % 8 == 0 && (v == 7 || (v == 0 && tiles >= kQuartersMinTiles && tiles <= kComputeUnits));
+}
+
 size_t partial_bytes(int splits, int64_t M, int64_t N) { return (size_t)splits * (size_t)M * (size_t)N * sizeof(float); }
 
 PipeTile tile_of(int bm, int bn)
@@ -1096,6 +1116,7 @@ struct PipePlan {
     int splits;
     SkPlan sk;
     size_t room;                                        // workspace that the call has to bring
+    bool quarters;                                      // four K parts in each workgroup
     size_t bytes(int64_t M, int64_t N) const { return sk.on ? sk.workspace_bytes : splits > 1 ? partial_bytes(splits, M, N) : 0; }
 };
 
@@ -1116,7 +1137,7 @@ PipePlan shortest(const Estimate& e, int64_t M, int64_t N, int64_t K, const Pipe
         return choose_splits(e, t, pipe_tiles(t, M, N), M, N, K, r.splits);
     };
     auto plan_of = [&](const PipeTile& t) -> PipePlan {
-        PipePlan p{t, 1, sk_plan(e, t, pipe_tiles(t, M, N), K, r.sk_room), 0};
+        PipePlan p{t, 1, sk_plan(e, t, pipe_tiles(t, M, N), K, r.sk_room), 0, false};
         if (!p.sk.on) p.splits = splits_of(t);
         return p;
     };
@@ -1154,21 +1175,27 @@ PipePlan shortest(const Estimate& e, int64_t M, int64_t N, int64_t K, const Pipe
 // for, and the room for it.)
 size_t pipe_room(int64_t M, int64_t N, int64_t K, bool sk, PipePlan* plan)
 {
-    const bool steered = knob("gemm_variant") || knob("gemm_splits") || knob("gemm_sk");
+    const bool steered = (knob("gemm_variant") && knob("gemm_variant") != 7) || knob("gemm_splits") || knob("gemm_sk");
     const PipePlan p = shortest(steered ? kNow : kSizes, M, N, K, PipeRules{false, false, kMaxSplits, sk ? ~(size_t)0 : 0});
     if (plan) *plan = p;
     return p.bytes(M, N);
 }
 
-PipePlan pipe_plan(int64_t M, int64_t N, int64_t K, bool fused, bool sk)
+PipePlan pipe_plan(int64_t M, int64_t N, int64_t K, bool fused, bool e8)
 {
     PipePlan p;
+    const bool sk = !fused && !e8;
     const size_t room = pipe_room(M, N, K, sk, &p);
-    const bool steered = knob("gemm_variant") || knob("gemm_splits") || knob("gemm_sk");
+    const bool steered = (knob("gemm_variant") && knob("gemm_variant") != 7) || knob("gemm_splits") || knob("gemm_sk");
     if (!steered) {
         const bool exactly = fused && M <= kFlatOnlyMaxM;
         p = shortest(kNow, M, N, K, PipeRules{false, exactly, exactly ? p.splits : std::max<int64_t>(1, (int64_t)(room / partial_bytes(1, M, N))),
                                               sk ? room : 0});
+    }
+    if (fused && !e8 && M <= kFlatOnlyMaxM && k_quarters(p.splits, M, N)) {
+        p.tile = kNarrowTile;
+        p.splits = 1;
+        p.quarters = true;
     }
     p.room = room;
     return p;
@@ -1227,8 +1254,8 @@ int launch_pipe(const half_t* x, int64_t M, const uint4* c, int64_t N, int64_t K
         const int zrc = check_launch();
         if (zrc != E0M4_OK) return zrc;
     }
-    // 96 KiB for the large tile: above the default limit.  (KS = 2: two rings; one half's sums, afterwards.)
-    constexpr size_t lds = std::max((size_t)KS * kStages * BM * kRowBytes, KS == 2 ? (size_t)BM * BN * sizeof(float) : 0);
+    // 96 KiB for the large tile: above the default limit.  (KS > 1: as many rings; the other parts' sums, afterwards.)
+    constexpr size_t lds = std::max((size_t)KS * kStages * BM * kRowBytes, (size_t)(KS - 1) * BM * BN * sizeof(float));
     auto launch = [&](auto kernel, std::atomic<uint64_t>& lds_allowed) -> int {
         const int arc = allow_dynamic_lds(reinterpret_cast<const void*>(kernel), (int)lds, lds_allowed);
         if (arc != E0M4_OK) return arc;
@@ -1285,6 +1312,9 @@ int launch_pipe_as(const PipePlan& p, const half_t* x, int64_t M, const uint4* c
         if (k_halves(t, M, N, K))
             return launch_pipe<G, 1, 4, FUSED, 64, 256, E8, BF, 2>(x, M, c, N, K, y, workspace, workspace_bytes, stream, f, p);
     }
+    if constexpr (FUSED && !E8) {
+        if (p.quarters) return launch_pipe<G, 1, 2, FUSED, 64, 128, E8, BF, 4>(x, M, c, N, K, y, workspace, workspace_bytes, stream, f, p);
+    }
     if (t.bm == 64 && t.bn == 128)
         return launch_pipe<G, 1, 4, FUSED, 64, 128, E8, BF>(x, M, c, N, K, y, workspace, workspace_bytes, stream, f, p);
     if (t.bm == 64)
@@ -1300,7 +1330,7 @@ template <int G, bool FUSED>
 int launch_pipe_tile(const half_t* x, int64_t M, const uint4* c, int64_t N, int64_t K, half_t* y, void* workspace,
                      size_t workspace_bytes, hipStream_t stream, const Fusion& f)
 {
-    return launch_pipe_as<G, FUSED>(pipe_plan(M, N, K, FUSED, !FUSED), x, M, c, N, K, y, workspace, workspace_bytes, stream, f);
+    return launch_pipe_as<G, FUSED>(pipe_plan(M, N, K, FUSED, false), x, M, c, N, K, y, workspace, workspace_bytes, stream, f);
 }
 
 }  // namespace
@@ -1312,7 +1342,7 @@ int launch_gemm_pipe8(const void* X, int64_t M, const void* packed, int64_t N, i
     const half_t* x = static_cast<const half_t*>(X);
     const uint4* c = static_cast<const uint4*>(packed);
     half_t* y = static_cast<half_t*>(Y);
-    return launch_pipe_as<128, false, true>(pipe_plan(M, N, K, false, false), x, M, c, N, K, y, workspace, workspace_bytes, stream,
+    return launch_pipe_as<128, false, true>(pipe_plan(M, N, K, false, true), x, M, c, N, K, y, workspace, workspace_bytes, stream,
                                             Fusion{});
 }
 
@@ -1323,7 +1353,7 @@ int launch_gemm_pipe8_fused(const Fusion& f, const void* X, int64_t M, const voi
     const uint4* c = static_cast<const uint4*>(packed);
     half_t* y = static_cast<half_t*>(Y);
     if (f.swiglu && (N % (2 * kBlockRows) != 0 || gated_half_bytes(N, 2 * K, 128) > kMaxHalfBytes)) return E0M4_ERR_SHAPE;
-    return launch_pipe_as<128, true, true>(pipe_plan(M, N, K, true, false), x, M, c, N, K, y, workspace, workspace_bytes, stream, f);
+    return launch_pipe_as<128, true, true>(pipe_plan(M, N, K, true, true), x, M, c, N, K, y, workspace, workspace_bytes, stream, f);
 }
 
 int launch_gemm_pipe(const void* X, int64_t M, const void* packed, int64_t N, int64_t K, int group, void* Y,

@@ -1,6 +1,6 @@
 """GEMM tiles of 128 columns, whose wavefronts hold one block of 32 columns: last tiles of rows and columns, row lengths that are no
 multiple of 8, the gated product of two wavefronts' sums in whole tiles and in K splits, a K range shorter than the pipeline, every
-group and format; the same bits as the tiles of 256 columns in the same number of splits; and the number of K splits, hence the
+group and format; K quarters inside a workgroup; the same bits as the tiles of 256 columns in the same number of splits; and the number of K splits, hence the
 bits, of fused calls of up to 64 rows by default routes."""
 import pytest
 
@@ -63,3 +63,19 @@ def test_bf16(e0m4, oracle, variant, M, N, K, G):
     Y = with_knobs(e0m4, lambda: e0m4.e0m4_bf16_matmul(bf_dev(X), codes, N, K, G), gemm_variant=variant)
     Yref, absdot = oracle.bf16_matmul(X, What)
     check_bf16_matmul(oracle, Y, Yref, absdot, "bf16 gemm variant %d M=%d N=%d K=%d" % (variant, M, N, K))
+
+
+# (calls with four K splits; quarters of equal and unequal length, ragged last tiles, every group)
+@pytest.mark.parametrize("N,K,G", [(11392, 2048, 128), (12352, 2176, 128), (14400, 2048, 32), (12224, 2304, 64)])
+@pytest.mark.parametrize("M", [33, 64])
+def test_bits_of_k_quarters(e0m4, M, N, K, G):
+    codes = e0m4.e0m4_quantize(to_dev(synth_inputs.weights(64, K, seed=1450)).repeat((N + 63) // 64, 1)[:N].contiguous(), G)[0]
+    X = to_dev(synth_inputs.activations(M, K, seed=1451 + M, outlier_frac=0.01))
+    assert with_knobs(e0m4, lambda: e0m4.e0m4_fused_workspace_bytes(M, N, K, G, False, 0), gemv_mfma=1) == 4 * M * N * 4
+    for swiglu, res in ((True, False), (False, True), (True, True)):
+        if swiglu and N % 64:
+            continue
+        R = to_dev(synth_inputs.residual(M, N // 2 if swiglu else N, 1452)) if res else None
+        Y = [with_knobs(e0m4, lambda: e0m4.e0m4_matmul_fused(X, codes, N, K, G, residual=R, epilogue=1 if swiglu else 0), gemv_mfma=1, **k)
+             for k in ({"gemm_variant": 4, "gemm_splits": 4}, {"gemm_variant": 7})]
+        assert torch.equal(*Y), (swiglu, res)
