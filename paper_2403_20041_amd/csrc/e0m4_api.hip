@@ -15,25 +15,22 @@ thread_local char g_hip_error[256] = "";
 
 // Diagnostic knobs belong to the calling thread: a size query and the call it sizes, made from one thread,
 // always see the same values, and a thread that never sets a knob always gets the built-in heuristics.
-struct Knob {
-    const char* name;
-    int value;
-};
-thread_local Knob g_knobs[] = {
-    {"gemv_waves", 0},                 // wavefronts per workgroup of the small-M kernel (4, 8 or 16)
-    {"gemv_workgroups", 0},            // target number of workgroups of the small-M kernel
+const char* const kKnobNames[] = {      // in the order of Knob
+    "gemv_waves",                 // wavefronts per workgroup of the small-M kernel (4, 8 or 16)
+    "gemv_workgroups",            // target number of workgroups of the small-M kernel
     // the matrix-core small-batch kernels: 1 neither; 2 activations staged in LDS always read from there; 3 their wavefront sums
     // reduced per row block; 4 plain matmuls on dequantised operands wherever that can run, 5 never; 6 staged also for groups of
     // 64 and 32 wherever that can run; 7 plain matmuls on exact codes without staging wherever that can run, 8 never; 9 as 6, and
     // X block by block wherever that can run
-    {"gemv_mfma", 0},
-    {"gemv_xreg", 0},                  // M = 1 kernel, a wavefront's activations in registers: 2 never
-    {"gemm_variant", 0},               // 1: small-tile kernel; pipelined kernel with tiles of 2: 256 x 256, 3: 128 x 128, 4: 64 x 256, 5: 128 x 256, 6: 64 x 128, 7: that with K quarters
-    {"gemm_splits", 0},                // force the number of K splits of the pipelined GEMM kernel
-    {"gemm_sk", 0},                    // even scheduling of the 256 x 256 tiles over the compute units: 1 whenever the last round is partly filled, 2 never
-    {"gemm_panel", 0},                 // row tiles per panel of the pipelined GEMM's tile numbering (0: the default, -1: whole columns)
-    {"gemm_split_order", 0},           // work items of a K-split launch: 1 by tile, 2 by split (0: by the length of a split)
+    "gemv_mfma",
+    "gemv_xreg",                  // M = 1 kernel, a wavefront's activations in registers: 2 never
+    "gemm_variant",               // 1: small-tile kernel; pipelined kernel with tiles of 2: 256 x 256, 3: 128 x 128, 4: 64 x 256, 5: 128 x 256, 6: 64 x 128, 7: that with K quarters
+    "gemm_splits",                // force the number of K splits of the pipelined GEMM kernel
+    "gemm_sk",                    // even scheduling of the 256 x 256 tiles over the compute units: 1 whenever the last round is partly filled, 2 never
+    "gemm_panel",                 // row tiles per panel of the pipelined GEMM's tile numbering (0: the default, -1: whole columns)
+    "gemm_split_order",           // work items of a K-split launch: 1 by tile, 2 by split (0: by the length of a split)
 };
+static_assert(sizeof(kKnobNames) / sizeof(kKnobNames[0]) == (size_t)Knob::count, "a name for each");
 
 // Scratch of e0m4_matmul_static: the split-K partial sums that e0m4_matmul keeps in the caller's workspace.
 // Every GPU the library runs on holds its own copy of the array, at its own address, until the process ends.
@@ -77,7 +74,7 @@ bool group_ok(int group) { return group == 32 || group == 64 || group == 128; }
 // it can run, which by default it does where it pays).
 bool use_gemv_mfma(int64_t M, int64_t N, int64_t K, int group)
 {
-    const int k = knob("gemv_mfma");
+    const int k = knob(Knob::gemv_mfma);
     if (k == 1 || !gemv_mfma_supported(M, N, K, group)) return false;
     return group == 128 || k == 6 || k == 9 || gemv_mfma_groups_pay(M, N, K, group);
 }
@@ -104,7 +101,7 @@ int row_chunks(int64_t M) { return (int)((M + kChunkRows - 1) / kChunkRows); }
 int64_t rows_per_chunk(int64_t M) { return (M + row_chunks(M) - 1) / row_chunks(M); }
 bool small_batch_in_chunks(const Fusion& f, int64_t M, int64_t N, int64_t K, int group, WholeRowsPlan* plan = nullptr)
 {
-    if (M <= kChunkRows || M > kChunkedMaxM || knob("gemv_mfma") == 1 || (double)N * (double)K > 7e7) return false;
+    if (M <= kChunkRows || M > kChunkedMaxM || knob(Knob::gemv_mfma) == 1 || (double)N * (double)K > 7e7) return false;
     WholeRowsPlan p;
     if (!gemv_mfma_whole_rows(f, rows_per_chunk(M), N, K, group, &p)) return false;
     if (plan) *plan = p;
@@ -114,7 +111,7 @@ bool small_batch_in_chunks(const Fusion& f, int64_t M, int64_t N, int64_t K, int
 // Any of the GEMM's knobs is set: it keeps the calls that are its own without the kernel below.
 bool gemm_steered()
 {
-    return knob("gemm_variant") || knob("gemm_splits") || knob("gemm_sk") || knob("gemm_panel") || knob("gemm_split_order");
+    return knob(Knob::gemm_variant) || knob(Knob::gemm_splits) || knob(Knob::gemm_sk) || knob(Knob::gemm_panel) || knob(Knob::gemm_split_order);
 }
 // The small-batch kernel with dequantised weight operands, for plain matmuls.  It rounds every weight to 16 bits before the
 // product, as the GEMM does; the kernels above work on the codes' exact values and apply scale and bias in fp32.  So it never
@@ -122,14 +119,14 @@ bool gemm_steered()
 // 64, what use_gemv_mfma leaves.  gemv_mfma 4 forces it wherever it can run (2 <= M <= 128), 1 and 5 switch it off.
 bool use_gemv_dq(int64_t M, int64_t N, int64_t K, int group, DqFormat format)
 {
-    const int k = knob("gemv_mfma");
+    const int k = knob(Knob::gemv_mfma);
     if (k == 1 || k == 5 || !gemv_dq_supported(M, N, K, group)) return false;
     return k == 4 || gemv_dq_pays(M, N, K, group, format);
 }
 bool use_gemv_dq4(int64_t M, int64_t N, int64_t K, int group)
 {
     if (M < 2) return false;
-    if (knob("gemv_mfma") != 4) {
+    if (knob(Knob::gemv_mfma) != 4) {
         if (use_gemv_mfma(M, N, K, group) || small_batch_in_chunks(Fusion{}, M, N, K, group)) return false;
         const bool fits = M <= kGemvMaxM || (M <= 16 && M * (k_blocks(K) * 256 + 16) <= 140 * 1024);
         if (group != 128 && M >= 3 && fits) return use_gemv_dq(M, N, K, group, kDqFormatFp16);
@@ -152,7 +149,7 @@ bool use_gemv_dq4(int64_t M, int64_t N, int64_t K, int group)
 // (gemv_mfma 1: the vector kernel, 6: this one from two rows on)
 bool use_gemv_mfma_bf16(int64_t M, int64_t N, int64_t K, int group)
 {
-    const int k = knob("gemv_mfma");
+    const int k = knob(Knob::gemv_mfma);
     if (M > kGemvMaxM || k == 1 || !gemv_mfma_supported(M, N, K, group)) return false;
     if (k == 6 || (M > 2 && group == 128)) return true;
     const int64_t items = (k_blocks(K) + 3) / 4, rb = (row_blocks(N) + 255) / 256;
@@ -166,7 +163,7 @@ bool use_gemv_mfma_bf16(int64_t M, int64_t N, int64_t K, int group)
 // can run; any other value but 0 leaves its calls to the kernels that have them otherwise).
 bool use_gemv_exact(int64_t M, int64_t N, int64_t K, int group, DqFormat format)
 {
-    const int k = knob("gemv_mfma");
+    const int k = knob(Knob::gemv_mfma);
     if ((k != 0 && k != 7) || !gemv_exact_supported(M, N, K, group, format)) return false;
     if (k == 7) return true;
     if (gemm_steered() || N > (int64_t)1 << 24) return false;
@@ -197,12 +194,7 @@ int record_hip_error(hipError_t e)
 
 int check_launch() { return record_hip_error(hipGetLastError()); }
 
-int knob(const char* name)
-{
-    for (auto& k : g_knobs)
-        if (strcmp(k.name, name) == 0) return k.value;
-    return 0;
-}
+__thread int g_knobs[(int)Knob::count] = {};
 
 }  // namespace e0m4
 
@@ -245,7 +237,7 @@ size_t e0m4_workspace_bytes(int64_t M, int64_t N, int64_t K, int group)
     if (check_shape(N, K, group) != E0M4_OK || M <= 0 || N == 0 || K == 0) return 0;             // invalid or empty: nothing runs
     if (use_gemv_exact(M, N, K, group, kDqFormatFp16)) return 0;
     if (small_m_on_vector(M, N, K)) return 0;           // the small-M kernels need none
-    if (use_gemv_dq4(M, N, K, group) && (knob("gemv_mfma") == 4 || gemv_dq_free(M, N, K, group, kDqFormatFp16))) return 0;
+    if (use_gemv_dq4(M, N, K, group) && (knob(Knob::gemv_mfma) == 4 || gemv_dq_free(M, N, K, group, kDqFormatFp16))) return 0;
     if (use_gemv_mfma(M, N, K, group) || small_batch_in_chunks(Fusion{}, M, N, K, group)) return 0;
     return gemm_workspace_bytes(M, N, K);       // partial tiles of the split-K GEMM, if it splits
 }
@@ -274,7 +266,7 @@ static FusedPath fused_path(const Fusion& f, int64_t M, int64_t N, int64_t K, in
     if (!f.any() && use_gemv_exact(M, N, K, group, kDqFormatFp16)) return kFusedExact;
     // (groups of 64 and 32 from three rows on: 1.1 - 2 x the vector kernel and the GEMM there, 10 - 25 % slower than the
     // vector kernel at two rows)
-    const int k = knob("gemv_mfma");
+    const int k = knob(Knob::gemv_mfma);
     if (k != 1 && gemv_mfma_fused_supported(f, M, N, K, group) && (group == 128 || M >= 3 || k == 6 || k == 9)) return kFusedSmallBatch;
     if (small_batch_in_chunks(f, M, N, K, group)) {
         TilesPlan p;
@@ -289,12 +281,7 @@ static FusedPath fused_path(const Fusion& f, int64_t M, int64_t N, int64_t K, in
 }
 
 // The workspace that a call has to bring: the normalised X, the GEMM's partial sums behind it.  (Calls of the kernel with
-// dequantised operands have the same to bring as when they were the GEMM's; calls in tiles may do without, in chunks.)
-static size_t fused_need(FusedPath path, bool normed, int64_t M, int64_t K, size_t gemm_bytes)
-{
-    return path == kFusedGemm || path == kFusedDq ? (normed ? norm_bytes(M, K) : 0) + gemm_bytes : 0;
-}
-
+// dequantised operands have the same to bring as when they were the GEMM's; calls in tiles may do without, in chunks: `best`.)
 static size_t fused_bytes(int64_t M, int64_t N, int64_t K, int group, bool normed, int epilogue, bool best)
 {
     if (check_shape(N, K, group) != E0M4_OK || M <= 0 || N == 0 || K == 0) return 0;
@@ -304,7 +291,8 @@ static size_t fused_bytes(int64_t M, int64_t N, int64_t K, int group, bool norme
     f.residual = &f;                                    // (a call without a residual needs no more than one with it)
     const FusedPath path = fused_path(f, M, N, K, group);
     if (best && path == kFusedTiles && normed) return norm_bytes(M, K);
-    return fused_need(path, normed, M, K, gemm_workspace_bytes(M, N, K, f.swiglu, true));
+    if (path != kFusedGemm) return 0;                   // (with a residual it is never the kernel with dequantised operands)
+    return (normed ? norm_bytes(M, K) : 0) + gemm_workspace_bytes(M, N, K, f.swiglu, true);
 }
 
 size_t e0m4_fused_workspace_bytes(int64_t M, int64_t N, int64_t K, int group, int with_rmsnorm, int epilogue)
@@ -320,9 +308,9 @@ size_t e0m4_fused_workspace_best_bytes(int64_t M, int64_t N, int64_t K, int grou
 int e0m4_set_knob(const char* name, int value)
 {
     if (!name) return E0M4_ERR_NULL;
-    for (auto& k : g_knobs)
-        if (strcmp(k.name, name) == 0) {
-            k.value = value;
+    for (int k = 0; k < (int)Knob::count; ++k)
+        if (strcmp(kKnobNames[k], name) == 0) {
+            g_knobs[k] = value;
             return E0M4_OK;
         }
     return E0M4_ERR_SHAPE;
@@ -495,7 +483,7 @@ int e0m4_matmul_fused(const void* X, int64_t M, const void* rms_gamma, float rms
     if (path == kFusedExact) return launch_gemv_exact(X, M, codes, N, K, kDqFormatFp16, Y, st);
     if (path == kFusedChunks) return launch_gemv_mfma_fused(f, X, M, codes, N, K, Y, st, row_chunks(M), group);      // rows are independent
     if (N > (int64_t)1 << 24) return E0M4_ERR_SHAPE;    // 32-bit offsets in the GEMM epilogue
-    const size_t need = fused_need(path, rms_gamma != nullptr, M, K, gemm_workspace_bytes(M, N, K, f.swiglu, true));
+    const size_t need = path == kFusedTiles ? 0 : nb + gemm_workspace_bytes(M, N, K, f.swiglu, true);
     if (need > 0) {
         if (!workspace) return E0M4_ERR_NULL;
         if (!aligned16(workspace)) return E0M4_ERR_ALIGN;
@@ -586,7 +574,7 @@ int e0m4_bf16_matmul(const void* X, int64_t M, const void* codes, int64_t N, int
     if (!aligned16(X) || !aligned16(codes)) return E0M4_ERR_ALIGN;
     if (use_gemv_exact(M, N, K, group, kDqFormatBf16))
         return launch_gemv_exact(X, M, codes, N, K, kDqFormatBf16, Y, (hipStream_t)stream);
-    if ((knob("gemv_mfma") == 4 || !gemm_steered()) && use_gemv_dq(M, N, K, group, kDqFormatBf16))
+    if ((knob(Knob::gemv_mfma) == 4 || !gemm_steered()) && use_gemv_dq(M, N, K, group, kDqFormatBf16))
         return launch_gemv_dq(X, M, codes, N, K, group, kDqFormatBf16, Y, (hipStream_t)stream);
     if (use_gemv_mfma_bf16(M, N, K, group)) return launch_gemv_mfma_bf16(X, M, codes, N, K, group, Y, (hipStream_t)stream);
     if (M <= kGemvMaxM) return launch_gemv_bf16(X, M, codes, N, K, group, Y, (hipStream_t)stream);
@@ -642,7 +630,7 @@ int e0m8_unpack_codes(const void* codes, int64_t N, int64_t K, int group, void* 
 // The pipelined GEMM serves M > 8 when K is a multiple of 128 (its K slices come in pairs).
 static bool e0m8_use_mfma_decode(int64_t M, int64_t N, int64_t K)
 {
-    return knob("gemv_mfma") != 1 && gemv_mfma8_supported(M, N, K);
+    return knob(Knob::gemv_mfma) != 1 && gemv_mfma8_supported(M, N, K);
 }
 
 // The 8-bit form of small_batch_in_chunks.  Twice the weight bytes per launch: the two launches only win on
@@ -650,7 +638,7 @@ static bool e0m8_use_mfma_decode(int64_t M, int64_t N, int64_t K)
 // 512 x 4096 and larger weights 5 - 20 % slower).
 static bool small_batch8_in_chunks(const Fusion& f, int64_t M, int64_t N, int64_t K)
 {
-    return M > kChunkRows && M <= kChunked8MaxM && knob("gemv_mfma") != 1 && K <= 2048 && (double)N * (double)K <= 1e7 &&
+    return M > kChunkRows && M <= kChunked8MaxM && knob(Knob::gemv_mfma) != 1 && K <= 2048 && (double)N * (double)K <= 1e7 &&
            gemv_mfma8_whole_rows(f, rows_per_chunk(M), N, K);
 }
 
@@ -662,10 +650,10 @@ static bool e0m8_gemm_or_dq(int64_t M, int64_t N, int64_t K)
 }
 static bool e0m8_use_gemv_dq(int64_t M, int64_t N, int64_t K)
 {
-    return (knob("gemv_mfma") == 4 || (e0m8_gemm_or_dq(M, N, K) && !gemm_steered())) && use_gemv_dq(M, N, K, 128, kDqFormatE8);
+    return (knob(Knob::gemv_mfma) == 4 || (e0m8_gemm_or_dq(M, N, K) && !gemm_steered())) && use_gemv_dq(M, N, K, 128, kDqFormatE8);
 }
 static bool e0m8_use_gemm(int64_t M, int64_t N, int64_t K) { return e0m8_gemm_or_dq(M, N, K) && !e0m8_use_gemv_dq(M, N, K); }
-static bool e0m8_dq_free(int64_t M, int64_t N, int64_t K) { return knob("gemv_mfma") == 4 || gemv_dq_free(M, N, K, 128, kDqFormatE8); }
+static bool e0m8_dq_free(int64_t M, int64_t N, int64_t K) { return knob(Knob::gemv_mfma) == 4 || gemv_dq_free(M, N, K, 128, kDqFormatE8); }
 
 size_t e0m8_workspace_bytes(int64_t M, int64_t N, int64_t K, int group)
 {
@@ -717,7 +705,7 @@ int e0m8_matmul(const void* X, int64_t M, const void* codes, int64_t N, int64_t 
 // Fused matmul on 8-bit codes (the GEMM kernels need K % 128 == 0).
 static FusedPath fused_path8(const Fusion& f, int64_t M, int64_t N, int64_t K)
 {
-    if (knob("gemv_mfma") != 1 && gemv_mfma8_fused_supported(f, M, N, K)) return kFusedSmallBatch;
+    if (knob(Knob::gemv_mfma) != 1 && gemv_mfma8_fused_supported(f, M, N, K)) return kFusedSmallBatch;
     if (small_batch8_in_chunks(f, M, N, K)) return kFusedChunks;
     if (small_m_on_vector(M, N, K) && gemv_fused_supported(f, M, N, 2 * K)) return kFusedVector;
     if (!gemm_pipe_supported(K) || N > (int64_t)1 << 24) return kFusedNone;
@@ -731,7 +719,8 @@ size_t e0m8_fused_workspace_bytes(int64_t M, int64_t N, int64_t K, int group, in
     Fusion f;
     f.swiglu = epilogue == E0M4_EPILOGUE_SWIGLU;
     f.residual = &f;                                    // (as in e0m4_fused_workspace_bytes)
-    return fused_need(fused_path8(f, M, N, K), with_rmsnorm != 0, M, K, gemm_pipe_workspace_bytes(M, N, K, f.swiglu, true));
+    if (fused_path8(f, M, N, K) != kFusedGemm) return 0;
+    return (with_rmsnorm ? norm_bytes(M, K) : 0) + gemm_pipe_workspace_bytes(M, N, K, f.swiglu, true);
 }
 
 int e0m8_matmul_fused(const void* X, int64_t M, const void* rms_gamma, float rms_eps, const void* codes, int64_t N,
@@ -761,7 +750,7 @@ int e0m8_matmul_fused(const void* X, int64_t M, const void* rms_gamma, float rms
     if (path == kFusedChunks) return launch_gemv_mfma8_fused(f, X, M, codes, N, K, Y, st, row_chunks(M));
     if (path == kFusedNone) return E0M4_ERR_SHAPE;      // larger M needs K % 128 == 0 (GEMM kernels)
     const size_t nb = rms_gamma ? norm_bytes(M, K) : 0;
-    const size_t need = fused_need(path, rms_gamma != nullptr, M, K, gemm_pipe_workspace_bytes(M, N, K, f.swiglu, true));
+    const size_t need = nb + gemm_pipe_workspace_bytes(M, N, K, f.swiglu, true);
     if (need > 0) {
         if (!workspace) return E0M4_ERR_NULL;
         if (!aligned16(workspace)) return E0M4_ERR_ALIGN;

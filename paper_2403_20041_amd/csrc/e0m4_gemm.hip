@@ -324,7 +324,7 @@ int launch_tile(const half_t* x, int64_t M, const uint4* c, int64_t N, int64_t K
 bool use_pipe(int64_t M, int64_t N, int64_t K, bool swiglu = false)
 {
     (void)M; (void)N; (void)swiglu;
-    return gemm_pipe_supported(K) && knob("gemm_variant") != 1;
+    return gemm_pipe_supported(K) && knob(Knob::gemm_variant) != 1;
 }
 
 }  // namespace
@@ -355,7 +355,7 @@ int launch_gemm(const void* X, int64_t M, const void* packed, int64_t N, int64_t
 int launch_gemm_bf16(const void* X, int64_t M, const void* packed, int64_t N, int64_t K, int group, void* Y,
                      hipStream_t stream)
 {
-    if (knob("gemm_variant") != 1 && gemm_pipe_bf16_pays(M, N, K))
+    if (knob(Knob::gemm_variant) != 1 && gemm_pipe_bf16_pays(M, N, K))
         return launch_gemm_pipe_bf16(X, M, packed, N, K, group, Y, stream);
     const half_t* x = static_cast<const half_t*>(X);
     const uint4* c = static_cast<const uint4*>(packed);

@@ -994,7 +994,7 @@ const TileCost& cost_of(const Estimate& e, const PipeTile& t)
 // two, four and eight.
 int choose_splits(const Estimate& e, const PipeTile& t, int64_t tiles, int64_t M, int64_t N, int64_t K, int64_t most)
 {
-    const int forced = knob("gemm_splits");
+    const int forced = knob(Knob::gemm_splits);
     const int64_t pairs = K / (2 * BK);
     if (forced > 0) return (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(forced, pairs), kMaxSplits));   // tests: down to one pair per split
     // every compute unit already has a tile (of the smallest, two): the partial sums and their reduction cost more than further
@@ -1055,7 +1055,7 @@ struct SkPlan {
 SkPlan sk_plan(const Estimate& e, const PipeTile& t, int64_t tiles, int64_t K, size_t room)
 {
     SkPlan p{false, 0, 0, 0, 0, 0.0};
-    const int forced = knob("gemm_sk");
+    const int forced = knob(Knob::gemm_sk);
     if (room == 0 || forced == 2 || t.bm != 256 || tiles <= 0) return p;
     p.rounds_dp = (int)(tiles / kComputeUnits);
     p.rem_tiles = (int)(tiles % kComputeUnits);
@@ -1099,7 +1099,7 @@ constexpr int64_t kQuartersMinTiles = 160;
 bool k_quarters(int splits, int64_t M, int64_t N)
 {
     const int64_t tiles = pipe_tiles(kNarrowTile, M, N);
-    const int v = knob("gemm_variant");
+    const int v = knob(Knob::gemm_variant);
     return splits == 4 && N % 8 == 0 && (v == 7 || (v == 0 && tiles >= kQuartersMinTiles && tiles <= kComputeUnits));
 }
 
@@ -1133,7 +1133,7 @@ PipePlan shortest(const Estimate& e, int64_t M, int64_t N, int64_t K, const Pipe
 {
     auto splits_of = [&](const PipeTile& t) -> int {
         if (r.whole_tiles) return 1;
-        if (r.exactly && knob("gemm_splits") == 0) return (int)r.splits;
+        if (r.exactly && knob(Knob::gemm_splits) == 0) return (int)r.splits;
         return choose_splits(e, t, pipe_tiles(t, M, N), M, N, K, r.splits);
     };
     auto plan_of = [&](const PipeTile& t) -> PipePlan {
@@ -1141,7 +1141,7 @@ PipePlan shortest(const Estimate& e, int64_t M, int64_t N, int64_t K, const Pipe
         if (!p.sk.on) p.splits = splits_of(t);
         return p;
     };
-    switch (knob("gemm_variant")) {
+    switch (knob(Knob::gemm_variant)) {
         case 2: return plan_of(kBigTile);
         case 3: return plan_of(kMidTile);
         case 4: return plan_of(kFlatTile);
@@ -1175,7 +1175,7 @@ PipePlan shortest(const Estimate& e, int64_t M, int64_t N, int64_t K, const Pipe
 // for, and the room for it.)
 size_t pipe_room(int64_t M, int64_t N, int64_t K, bool sk, PipePlan* plan)
 {
-    const bool steered = (knob("gemm_variant") && knob("gemm_variant") != 7) || knob("gemm_splits") || knob("gemm_sk");
+    const bool steered = (knob(Knob::gemm_variant) && knob(Knob::gemm_variant) != 7) || knob(Knob::gemm_splits) || knob(Knob::gemm_sk);
     const PipePlan p = shortest(steered ? kNow : kSizes, M, N, K, PipeRules{false, false, kMaxSplits, sk ? ~(size_t)0 : 0});
     if (plan) *plan = p;
     return p.bytes(M, N);
@@ -1186,7 +1186,7 @@ PipePlan pipe_plan(int64_t M, int64_t N, int64_t K, bool fused, bool e8)
     PipePlan p;
     const bool sk = !fused && !e8;
     const size_t room = pipe_room(M, N, K, sk, &p);
-    const bool steered = (knob("gemm_variant") && knob("gemm_variant") != 7) || knob("gemm_splits") || knob("gemm_sk");
+    const bool steered = (knob(Knob::gemm_variant) && knob(Knob::gemm_variant) != 7) || knob(Knob::gemm_splits) || knob(Knob::gemm_sk);
     if (!steered) {
         const bool exactly = fused && M <= kFlatOnlyMaxM;
         p = shortest(kNow, M, N, K, PipeRules{false, exactly, exactly ? p.splits : std::max<int64_t>(1, (int64_t)(room / partial_bytes(1, M, N))),
@@ -1218,7 +1218,7 @@ int launch_pipe(const half_t* x, int64_t M, const uint4* c, int64_t N, int64_t K
     // 128 x 256 tiles: 504 -> 488 us, 2048 x 32768 x 2048: 269 -> 251; on 64 x 256 tiles 601 -> 569 and 318 -> 285; on
     // the large tile 550 -> 541 and 270 -> 254); heights of 2 to 6 tiles of 128 rows measured alike.
     // gemm_panel forces a height, -1 whole columns.
-    const int panel_knob = knob("gemm_panel");
+    const int panel_knob = knob(Knob::gemm_panel);
     fu.panel = panel_knob > 0 ? panel_knob : panel_knob < 0 ? 0 : BM == 256 ? 2 : 4;
     fu.split_major = 0;
     fu.n_half = N / 2;
@@ -1231,7 +1231,7 @@ int launch_pipe(const half_t* x, int64_t M, const uint4* c, int64_t N, int64_t K
     // Long K ranges gain from the order by split (1024 x 4096 x 13696 in four splits 122 -> 116 us, 512 x 2048 x 16384
     // in eight 46.9 -> 44.6), short ones lose (128 x 4608 x 4096 in eight splits of four pairs 19.6 -> 21.6, 1024 x 4608
     // x 4096 in three of ten or eleven 56.9 -> 58.5); gemm_split_order 1 forces the order by tile, 2 the order by split.
-    const int order_knob = knob("gemm_split_order");
+    const int order_knob = knob(Knob::gemm_split_order);
     fu.split_major = splits > 1 && (order_knob == 2 || (order_knob == 0 && K / (2 * BK) / splits >= kSplitMajorMinPairs)) ? 1 : 0;
     const int total = (int)(tiles * splits);
     const int per_xcd = (total + kNumXcd - 1) / kNumXcd;

@@ -66,7 +66,7 @@ GemvPlan make_plan(int64_t M, int64_t N, int64_t K, int unit = 1, bool* single_s
     GemvPlan p;
     const int64_t nrb = row_blocks(N) / unit, nkb = k_blocks(K);
     const int64_t nsi = (nkb + kSuper - 1) / kSuper;           // work items per row block
-    int w = knob("gemv_waves");
+    int w = knob(Knob::gemv_waves);
     if (w == 16 && M > 4) w = 8;                // 16 wavefronts leave too few registers for that many accumulators
     const bool forced = w == 4 || w == 8 || w == 16;
     // 16 wavefronts when K is long, or when a workgroup has many work items of a medium K; 8 otherwise
@@ -78,7 +78,7 @@ GemvPlan make_plan(int64_t M, int64_t N, int64_t K, int unit = 1, bool* single_s
     // (K = 5120, 6144, 7168: 10, 12 or 14 work items per row block get as many wavefronts, for the same reason;
     // 10 and 14 load the four SIMDs unevenly, which costs more than it gains when a workgroup has only one or
     // two row blocks: 5120 x 5120 takes 6.1 us against 5.7)
-    if (!forced && M == 1 && nkb % kSuper == 0 && knob("gemv_xreg") != 2) {
+    if (!forced && M == 1 && nkb % kSuper == 0 && knob(Knob::gemv_xreg) != 2) {
         if (8 % nsi == 0) w = 8;
         else if (more_waves && (nsi == 12 || ((nsi == 10 || nsi == 14) && unit * t_guess >= 3))) w = (int)nsi;
     }
@@ -92,7 +92,7 @@ GemvPlan make_plan(int64_t M, int64_t N, int64_t K, int unit = 1, bool* single_s
         const int64_t red_budget = std::min<int64_t>(kRedBudgetBytes, kLdsLimitBytes - x_bytes);
         int64_t t_max = red_budget / ((int64_t)unit * w * M * kBlockRows * sizeof(float));
         if (t_max < 1) t_max = 1;
-        int target = knob("gemv_workgroups");
+        int target = knob(Knob::gemv_workgroups);
         if (target <= 0) target = kTargetWorkgroups;
         t = (nrb + target - 1) / target;
         if (t > t_max) t = t_max;
@@ -601,7 +601,7 @@ int launch_one(const GemvPlan& p, const void* X, const void* packed, int64_t N, 
         // every wavefront stays on its own k blocks, all of X in one segment, and a work item that exists
         const int64_t nkb = k_blocks(DEQ == kDeqE0M8 ? 2 * K : K);     // (8-bit codes: blocks of 64 weights)
         const int64_t nsi = (nkb + kSuper - 1) / kSuper;
-        if (knob("gemv_xreg") != 2 && p.step_item == 0 && p.seg_items >= nsi && W >= nsi &&       // (2: never)
+        if (knob(Knob::gemv_xreg) != 2 && p.step_item == 0 && p.seg_items >= nsi && W >= nsi &&       // (2: never)
             nkb % kSuper == 0)
             return launch_one<G, M, W, DEQ, FUSED, true>(p, X, packed, N, K, Y, stream, fu);
     }

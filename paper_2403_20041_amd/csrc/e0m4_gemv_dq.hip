@@ -371,7 +371,7 @@ bool make_dq_plan(int64_t M, int64_t N, int64_t K, DqPlan& p, bool exact = false
     if (M < 2 || M > kDqMaxParts * kDqMaxM || N <= 0 || K <= 0) return false;
     p.parts = M > kDqMaxM ? kDqMaxParts : 1;
     const int64_t nrb = row_blocks(N);
-    int target = knob("gemv_workgroups");
+    int target = knob(Knob::gemv_workgroups);
     if (target <= 0) target = kTargetWorkgroups;
     const int64_t rounds = (nrb + target * kDqMaxSlots - 1) / (target * kDqMaxSlots);
     const int64_t most = (nrb + target * rounds - 1) / (target * rounds);

@@ -806,7 +806,7 @@ bool make_mfma_plan(int64_t M, int64_t N, int64_t K, MfmaPlan& p, int unit = 1, 
 {
     const int64_t nrb = row_blocks(N) / unit, nkb = k_blocks(K);
     const int64_t nsi = (nkb + kSuper - 1) / kSuper;
-    int w = knob("gemv_waves");
+    int w = knob(Knob::gemv_waves);
     // (sixteen wavefronts for more than 16 work items per row block; with exactly 16 eight are faster: 8192 x 8192
     // at M = 4 takes 10.5 us, 12.1 with sixteen; 8-bit 4096 x 4096 at M = 2 5.9 against 6.7)
     const int w_knob = (w == 4 || w == 8 || w == 16) ? w : 0;
@@ -815,13 +815,13 @@ bool make_mfma_plan(int64_t M, int64_t N, int64_t K, MfmaPlan& p, int unit = 1, 
     // (several groups per block: plans are made for the rows of the MFMA, of which LDS holds a part)
     const int64_t rows = mfma_rows(M, gs);
     while (w > 4 && lds_need(rows, nkb, w, e8) > (size_t)kLdsLimitBytes) w /= 2;    // (smaller buffers for the wavefront sums)
-    int target = knob("gemv_workgroups");
+    int target = knob(Knob::gemv_workgroups);
     if (target <= 0) target = kTargetWorkgroups;
     p.kb_phase = p.ph_stage = 0;
     p.pieces_magic_last = 0;
     // X does not fit beside the sums of eight wavefronts: K in phases rather than all of X with four wavefronts
     // (36864 x 7168 at M = 10: 33 us against 52)
-    if (w < 8 && w_wanted >= 8 && knob("gemv_mfma") != 3 && make_phased_plan(M, rows, nrb, nkb, p, unit, e8, w_knob, target))
+    if (w < 8 && w_wanted >= 8 && knob(Knob::gemv_mfma) != 3 && make_phased_plan(M, rows, nrb, nkb, p, unit, e8, w_knob, target))
         return true;
     if (lds_need(rows, nkb, w, e8) > (size_t)kLdsLimitBytes) return false;
     p.grid = std::min<int64_t>(nrb, target);
@@ -840,7 +840,7 @@ bool make_mfma_plan(int64_t M, int64_t N, int64_t K, MfmaPlan& p, int unit = 1, 
     p.pieces_magic = (uint32_t)(((1ull << 32) + row_pieces - 1) / row_pieces);
     const size_t per_rb = 2 * (size_t)w * kMaxM * kBlockRows * sizeof(float);
     const size_t late_bytes = late_red_bytes(rows, (p.rb_base + 1) * unit, w);
-    p.late = knob("gemv_mfma") != 3 && p.lds_bytes - per_rb + late_bytes <= (size_t)kLdsLimitBytes;
+    p.late = knob(Knob::gemv_mfma) != 3 && p.lds_bytes - per_rb + late_bytes <= (size_t)kLdsLimitBytes;
     if (p.late) p.lds_bytes = p.lds_bytes - per_rb + std::max(late_bytes, (size_t)16);
     return true;
 }
@@ -955,15 +955,15 @@ int launch_mfma(const MfmaPlan& p, const void* X, int64_t M, const void* packed,
         const int items = (int)((k_blocks(K) + kSuper - 1) / kSuper);
         const ItemsPlan ip{p.grid, p.rb_base, p.rb_rem, W, p.kb_phase > 0 ? p.kb_phase / kSuper : items, p.kb_phase > 0, false};
         const bool xreg = gs == 1 && W <= 8 && p.kb_phase == 0 && p.step_item == 0;
-        if (!fu.gamma && !fu.swiglu && fu.m_total == 0 && !xreg && knob("gemv_mfma") != 2 && knob("gemv_mfma") != 3 &&
-            gemv_items_supported(ip, M, N, K, kG / gs) && (knob("gemv_mfma") == 9 || gemv_items_pays(ip, M, kG / gs, FUSED)))
+        if (!fu.gamma && !fu.swiglu && fu.m_total == 0 && !xreg && knob(Knob::gemv_mfma) != 2 && knob(Knob::gemv_mfma) != 3 &&
+            gemv_items_supported(ip, M, N, K, kG / gs) && (knob(Knob::gemv_mfma) == 9 || gemv_items_pays(ip, M, kG / gs, FUSED)))
             return launch_gemv_items(ip, X, M, packed, N, K, kG / gs, Y, fu.residual, stream);
     }
     if (gs == 2) return launch_mfma_groups<W, FUSED, 2>(p, X, M, packed, N, K, Y, stream, fu);
     if (gs == 4) return launch_mfma_groups<W, FUSED, 4>(p, X, M, packed, N, K, Y, stream, fu);
     if (p.kb_phase > 0) return launch_mfma_phased<W, FUSED, false>(p, X, M, packed, N, K, Y, stream, fu);
     if constexpr (W <= 8) {
-        if (p.step_item == 0 && knob("gemv_mfma") != 2)
+        if (p.step_item == 0 && knob(Knob::gemv_mfma) != 2)
             return launch_mfma_x<W, FUSED, true>(p, X, M, packed, N, K, Y, stream, fu);
     }
     return launch_mfma_x<W, FUSED, false>(p, X, M, packed, N, K, Y, stream, fu);
@@ -988,7 +988,7 @@ int launch_mfma_bf16(const MfmaPlan& p, const void* X, int64_t M, const void* pa
         if (p.kb_phase > 0) return launch_mfma_keep<W, false, false, false, true, GS, false, true>(p, X, M, packed, N, K, Y, stream, fu);
     }
     if constexpr (W <= 8 && GS == 1) {
-        if (p.step_item == 0 && knob("gemv_mfma") != 2)
+        if (p.step_item == 0 && knob(Knob::gemv_mfma) != 2)
             return launch_mfma_keep<W, false, true, false, false, GS, false, true>(p, X, M, packed, N, K, Y, stream, fu);
     }
     return launch_mfma_keep<W, false, false, false, false, GS, false, true>(p, X, M, packed, N, K, Y, stream, fu);
@@ -1067,14 +1067,14 @@ int launch_mfma8(const MfmaPlan& p, const GemvFusion& fu, const void* X, int64_t
 {
     const int items = (int)((k_blocks(2 * K) + kSuper - 1) / kSuper);
     const ItemsPlan ip{p.grid, p.rb_base, p.rb_rem, p.waves, p.kb_phase > 0 ? p.kb_phase / kSuper : items, p.kb_phase > 0, true};
-    if (!fu.gamma && !fu.swiglu && fu.m_total == 0 && (p.kb_phase > 0 || p.step_item != 0) && knob("gemv_mfma") != 2 &&
-        knob("gemv_mfma") != 3 && gemv_items_supported(ip, M, N, 2 * K, 128) &&
-        (knob("gemv_mfma") == 9 || gemv_items_pays(ip, M, 128, FUSED)))
+    if (!fu.gamma && !fu.swiglu && fu.m_total == 0 && (p.kb_phase > 0 || p.step_item != 0) && knob(Knob::gemv_mfma) != 2 &&
+        knob(Knob::gemv_mfma) != 3 && gemv_items_supported(ip, M, N, 2 * K, 128) &&
+        (knob(Knob::gemv_mfma) == 9 || gemv_items_pays(ip, M, 128, FUSED)))
         return launch_gemv_items(ip, X, M, packed, N, 2 * K, 128, Y, fu.residual, stream);
     if (p.kb_phase > 0)
         return p.waves == 8 ? launch_mfma_phased<8, FUSED, true>(p, X, M, packed, N, K, Y, stream, fu)
                             : launch_mfma_phased<16, FUSED, true>(p, X, M, packed, N, K, Y, stream, fu);
-    const bool xreg = p.step_item == 0 && knob("gemv_mfma") != 2;
+    const bool xreg = p.step_item == 0 && knob(Knob::gemv_mfma) != 2;
     switch (p.waves) {
         case 4:
             return xreg ? launch_mfma_x<4, FUSED, true, true>(p, X, M, packed, N, K, Y, stream, fu)

@@ -31,8 +31,11 @@ inline int allow_dynamic_lds(const void* kernel, int bytes, std::atomic<uint64_t
     return E0M4_OK;
 }
 
-// Tuning knobs (0 = use the heuristic).
-int knob(const char* name);
+// Tuning knobs of the calling thread (0 = use the heuristic), by index: a plan asks for dozens of them, and compared by name they
+// were half of its time.  Names and meanings stand at kKnobNames.
+enum class Knob { gemv_waves, gemv_workgroups, gemv_mfma, gemv_xreg, gemm_variant, gemm_splits, gemm_sk, gemm_panel, gemm_split_order, count };
+extern __thread int g_knobs[(int)Knob::count];
+inline int knob(Knob k) { return g_knobs[(int)k]; }
 
 // Operators folded into a matmul (e0m4_matmul_fused).  All-zero is the plain matmul.
 struct Fusion {
