@@ -125,8 +125,8 @@ struct SkArgs {
 // E8 selects the 8-bit format E0M8 (e0m8_pack.hip; G is then 128, the group of its 4-bit slots): a K slice
 // of 64 is one block, a lane reads two 16-byte chunks of 16 weights per slice, and MFMA number s takes
 // words 2(s%2) and 2(s%2)+1 of chunk s/2, each of which one mask-or (and one more after a rotation) turns
-// into four binade values.
-template <int G, int WGM, int WGN, bool FUSED, int BM, int BN, bool E8 = false, bool BF = false, int KS = 1, bool SHORT = false>
+// into four binade values.  DEPTH: slices of codes in registers, where it is not the default.
+template <int G, int WGM, int WGN, bool FUSED, int BM, int BN, bool E8 = false, bool BF = false, int KS = 1, bool SHORT = false, int DEPTH = 0>
 __global__ __launch_bounds__(64 * WGM * WGN * KS, 2) void gemm_pipe_kernel(const half_t* __restrict__ X, int64_t M,
                                                              const uint4* __restrict__ packed, int64_t N, int64_t K,
                                                              half_t* Y, int m_tiles, int n_tiles,
@@ -137,7 +137,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KS, 2) void gemm_pipe_kernel(const
     constexpr int kStageBytes = BM * kRowBytes;
     // Slices of weights in registers (8-bit codes: twice the registers per slice), stages of activations in LDS, and how many
     // slices ahead those are requested.
-    constexpr int PD = E8 && BM > 64 ? 2 : 4, S = kStages, L = S - 1;
+    constexpr int PD = DEPTH > 0 ? DEPTH : E8 && BM > 64 ? 2 : 4, S = kStages, L = S - 1;
     constexpr int TM = BM / (32 * WGM), TN = BN / (32 * WGN);      // 32x32 MFMA blocks per wavefront
     constexpr int RP = kThreads / 8;                    // rows covered by one activation loader pass
     constexpr int PA = BM / RP;                         // activation loader passes
@@ -1268,7 +1268,17 @@ int launch_pipe(const half_t* x, int64_t M, const uint4* c, int64_t N, int64_t K
         if (last_short) return launch(&gemm_pipe_kernel<G, WGM, WGN, FUSED, BM, BN, E8, BF, KS, true>, lds_allowed);
     }
     static std::atomic<uint64_t> lds_allowed{0};
-    const int rc = launch(&gemm_pipe_kernel<G, WGM, WGN, FUSED, BM, BN, E8, BF, KS>, lds_allowed);
+    int rc = E0M4_OK;
+    // 8-bit codes of up to 64 rows in splits that make a work item per compute unit or fewer: codes two slices ahead instead of four,
+    // a shorter start (gated 16384 x 2048 at M = 20 and 64 20.6 -> 18.4 and 24.0 -> 21.9 us, 8192 x 8192 28.7 -> 26.2; with more items the
+    // longer lead is the better one, 22016 x 3072 at M = 50 28.5 and 30.1).
+    bool two_ahead = false;
+    if constexpr (E8 && FUSED && BM == 64 && BN == 256) {
+        static std::atomic<uint64_t> allowed{0};
+        two_ahead = M <= kFlatOnlyMaxM && splits > 1 && total <= kComputeUnits;
+        if (two_ahead) rc = launch(&gemm_pipe_kernel<G, WGM, WGN, FUSED, BM, BN, E8, BF, KS, false, 2>, allowed);
+    }
+    if (!two_ahead) rc = launch(&gemm_pipe_kernel<G, WGM, WGN, FUSED, BM, BN, E8, BF, KS>, lds_allowed);
     if (rc != E0M4_OK || splits == 1) return rc;
     if (FUSED) {
         const int64_t n_out = f.swiglu ? N / 2 : N;

@@ -79,3 +79,14 @@ def test_bits_of_k_quarters(e0m4, M, N, K, G):
         Y = [with_knobs(e0m4, lambda: e0m4.e0m4_matmul_fused(X, codes, N, K, G, residual=R, epilogue=1 if swiglu else 0), gemv_mfma=1, **k)
              for k in ({"gemm_variant": 4, "gemm_splits": 4}, {"gemm_variant": 7})]
         assert torch.equal(*Y), (swiglu, res)
+
+
+# (8-bit codes, up to 64 rows, at most a work item per compute unit: splits of one pair of K slices and more, equal and unequal)
+@pytest.mark.parametrize("N,K,splits", [(832, 512, 4), (600, 1152, 2), (320, 2176, 8), (64, 384, 3)])
+@pytest.mark.parametrize("swiglu,res", [(True, False), (False, True), (True, True)])
+def test_8bit_codes_two_slices_ahead(e0m4, oracle, N, K, splits, swiglu, res):
+    if swiglu and N % 64:
+        N -= N % 64
+    for M in (19, 64):
+        with_knobs(e0m4, lambda: run_fused(e0m4, oracle, M, N, K, 128, seed=1460 + M, norm=False, swiglu=swiglu, res=res, outliers=True, bits=8),
+                   gemm_variant=4, gemm_splits=splits, gemv_mfma=1)
