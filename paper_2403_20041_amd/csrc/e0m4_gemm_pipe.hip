@@ -1382,8 +1382,8 @@ int launch_gemm_pipe(const void* X, int64_t M, const void* packed, int64_t N, in
 
 namespace {
 // Whole tiles only (no workspace to split K into); the tile by the same estimate as for fp16, whose timings those of
-// this member follow, flat tiles as K halves where k_halves says so.  M = 1024: 4608 x 4096 (288 flat tiles) 61 us, 27392 x
-// 4096 (428 large ones) 226, 4096 x 13696 (256 flat tiles in halves) 131, whole 154.
+// this member follow, flat tiles as K halves where k_halves says so.  Before the tiles of 128 columns and now: M = 700, 4608 x 4096 39.6
+// and 32.7 us, 4096 x 13696 108 and 92; M = 1024, 4096 x 13696 (256 flat tiles in halves) 128 and 112; M = 100, 27392 x 4096 43 and 34.
 template <int G>
 int launch_pipe_bf16(const half_t* x, int64_t M, const uint4* c, int64_t N, int64_t K, half_t* y, hipStream_t stream)
 {
