@@ -123,20 +123,23 @@ def _stream(stream) -> int:
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
+def _can_allocate(device, stream) -> bool:
+    """Whether _empty can make a buffer for `stream`."""
+    return stream is None or hasattr(stream, "cuda_stream") or int(stream) == torch.cuda.current_stream(device).cuda_stream
+
+
 def _empty(shape, dtype, device, stream, what: str):
     """torch.empty for a buffer that the kernels enqueued on `stream` will use.  The caching allocator ties a
     block to the stream that was current when it was allocated, so the buffer is allocated with `stream`
     current; a raw stream handle that is not the current stream cannot be made current here, and the caller
     must then own the buffer."""
-    if stream is None:
-        return torch.empty(shape, dtype=dtype, device=device)
-    if hasattr(stream, "cuda_stream"):
+    if not _can_allocate(device, stream):
+        raise ValueError("%s: pass a caller-owned tensor when `stream` is a raw handle other than torch's current stream"
+                         % what)
+    if stream is not None and hasattr(stream, "cuda_stream"):
         with torch.cuda.stream(stream):
             return torch.empty(shape, dtype=dtype, device=device)
-    if int(stream) == torch.cuda.current_stream(device).cuda_stream:
-        return torch.empty(shape, dtype=dtype, device=device)
-    raise ValueError("%s: pass a caller-owned tensor when `stream` is a raw handle other than torch's current stream"
-                     % what)
+    return torch.empty(shape, dtype=dtype, device=device)
 
 
 def _ptr(t) -> int:
@@ -275,6 +278,8 @@ def e0m4_matmul_fused(X, codes, N: int, K: int, group: int, rms_gamma=None, rms_
         _need(out, torch.float16, (M, n_out), "out")
     if workspace is None:
         need = lib().e0m4_fused_workspace_best_bytes(M, N, K, group, 1 if rms_gamma is not None else 0, epilogue)
+        if need > 0 and not _can_allocate(X.device, stream):        # (calls that can do without one run without)
+            need = e0m4_fused_workspace_bytes(M, N, K, group, rms_gamma is not None, epilogue)
         if need > 0:
             workspace = _empty(need, torch.uint8, X.device, stream, "workspace")
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()

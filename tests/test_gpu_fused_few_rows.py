@@ -73,3 +73,19 @@ def test_without_a_workspace(e0m4, oracle):
                                           Y.data_ptr(), ws, nbytes, torch.cuda.current_stream().cuda_stream)
         assert rc == 0 and torch.equal(Y, call(e0m4, 8, X, codes, N, K, gamma, False, None))
     assert np.all(room.cpu().numpy() == 255)            # (nothing was written there)
+
+
+def test_on_a_raw_stream_that_is_not_the_current_one(e0m4, oracle):
+    """A workspace cannot be allocated for such a stream: calls that need none are served without, others say what is missing."""
+    M, N, K = 45, 4608, 2048
+    codes, _ = quantized(e0m4, oracle, N, K, 128, seed=980)
+    X, gamma = to_dev(synth_inputs.activations(M, K, seed=981)), to_dev(synth_inputs.norm_weight(K, 982))
+    side = torch.cuda.Stream()
+    Y = torch.empty((M, N), dtype=torch.float16, device=X.device)
+    side.wait_stream(torch.cuda.current_stream())
+    e0m4.e0m4_matmul_fused(X, codes, N, K, 128, rms_gamma=gamma, rms_eps=1e-5, out=Y, stream=side.cuda_stream)
+    side.synchronize()
+    assert torch.equal(Y, e0m4.e0m4_matmul_fused(X, codes, N, K, 128, rms_gamma=gamma, rms_eps=1e-5))
+    X = to_dev(synth_inputs.activations(200, K, seed=983))
+    with pytest.raises(ValueError, match="workspace"):
+        e0m4.e0m4_matmul_fused(X, codes, N, K, 128, rms_gamma=gamma, rms_eps=1e-5, out=X.new_empty((200, N)), stream=side.cuda_stream)
