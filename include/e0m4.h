@@ -208,12 +208,15 @@ int e0m4_matmul_static(const void* X_f16, int64_t M, const void* codes, int64_t 
  * rms-norm is a launch of its own that writes x' to the workspace; up to M = 64
  * the dequantising kernel of e0m4_matmul follows it where no other operator is
  * selected.  Where e0m4_matmul would go in chunks of rows (17 <= M <= 64), a
- * kernel with all rows in a workgroup gives the same sums in the same order; its
- * rms-norm is a launch of its own, and calls with one that bring less than
- * e0m4_fused_workspace_best_bytes() of workspace go in chunks, which need none.
- * Workspace: e0m4_fused_workspace_bytes() bytes, same rules as e0m4_matmul;
- * with e0m4_fused_workspace_best_bytes(), which is as many or more, every call
- * has its fastest kernel.
+ * kernel with all rows in a workgroup gives the same sums in the same order.  Its
+ * rms-norm is a launch of its own that needs room for x', which chunks do not:
+ * calls with one go there through e0m4_matmul_fused_best.
+ * Workspace: e0m4_fused_workspace_bytes() bytes, same rules as e0m4_matmul; one
+ * that is brought where this is 0 is not touched.
+ * e0m4_matmul_fused_best is the same call, to the same bits, with a workspace of
+ * e0m4_fused_workspace_best_bytes() bytes, which is as many or more: with it
+ * every call has its fastest kernel.  With less, e0m4_fused_workspace_bytes() at
+ * least, it does what e0m4_matmul_fused does.
  * With no operator selected the result is that of e0m4_matmul (up to the order of
  * the fp32 additions and the rounding of the weights: the two may choose different
  * kernels).  K == 0 is
@@ -227,6 +230,10 @@ int e0m4_matmul_fused(const void* X_f16, int64_t M, const void* rms_gamma_f16, f
                       const void* codes, int64_t N, int64_t K, int group,
                       int epilogue, const void* residual_f16,
                       void* Y_f16, void* workspace, size_t workspace_bytes, void* stream);
+int e0m4_matmul_fused_best(const void* X_f16, int64_t M, const void* rms_gamma_f16, float rms_eps,
+                           const void* codes, int64_t N, int64_t K, int group,
+                           int epilogue, const void* residual_f16,
+                           void* Y_f16, void* workspace, size_t workspace_bytes, void* stream);
 
 /*
  * In-place KV-cache append (paper: section "KV cache copy optimization").  The

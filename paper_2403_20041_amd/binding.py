@@ -67,8 +67,9 @@ def lib() -> ctypes.CDLL:
     L.e0m4_fused_workspace_bytes.argtypes = [i64, i64, i64, ci, ci, ci]
     L.e0m4_fused_workspace_best_bytes.restype = sz
     L.e0m4_fused_workspace_best_bytes.argtypes = [i64, i64, i64, ci, ci, ci]
-    L.e0m4_matmul_fused.restype = ci
-    L.e0m4_matmul_fused.argtypes = [vp, i64, vp, ctypes.c_float, vp, i64, i64, ci, ci, vp, vp, vp, sz, vp]
+    for name in ("e0m4_matmul_fused", "e0m4_matmul_fused_best"):
+        getattr(L, name).restype = ci
+        getattr(L, name).argtypes = [vp, i64, vp, ctypes.c_float, vp, i64, i64, ci, ci, vp, vp, vp, sz, vp]
     L.e0m8_codes_bytes.restype = sz
     L.e0m8_codes_bytes.argtypes = [i64, i64, ci]
     L.e0m8_quantize.restype = ci
@@ -276,16 +277,17 @@ def e0m4_matmul_fused(X, codes, N: int, K: int, group: int, rms_gamma=None, rms_
         out = _empty((M, n_out), torch.float16, X.device, stream, "out")
     else:
         _need(out, torch.float16, (M, n_out), "out")
+    call = lib().e0m4_matmul_fused                      # (which writes to a caller's workspace only where one is needed)
     if workspace is None:
         need = lib().e0m4_fused_workspace_best_bytes(M, N, K, group, 1 if rms_gamma is not None else 0, epilogue)
         if need > 0 and not _can_allocate(X.device, stream):        # (calls that can do without one run without)
             need = e0m4_fused_workspace_bytes(M, N, K, group, rms_gamma is not None, epilogue)
         if need > 0:
             workspace = _empty(need, torch.uint8, X.device, stream, "workspace")
+            call = lib().e0m4_matmul_fused_best
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(lib().e0m4_matmul_fused(_ptr(X), M, _ptr(rms_gamma), float(rms_eps), _ptr(codes), N, K, group, epilogue,
-                                   _ptr(residual), _ptr(out), _ptr(workspace), ws_bytes, _stream(stream)),
-           "e0m4_matmul_fused")
+    _check(call(_ptr(X), M, _ptr(rms_gamma), float(rms_eps), _ptr(codes), N, K, group, epilogue, _ptr(residual), _ptr(out),
+                _ptr(workspace), ws_bytes, _stream(stream)), "e0m4_matmul_fused")
     return out
 
 

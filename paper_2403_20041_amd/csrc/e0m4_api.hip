@@ -451,9 +451,10 @@ int e0m4_matmul_static(const void* X, int64_t M, const void* codes, int64_t N, i
     return e0m4_matmul(X, M, codes, nullptr, nullptr, N, K, group, Y, ws, need, stream);
 }
 
-int e0m4_matmul_fused(const void* X, int64_t M, const void* rms_gamma, float rms_eps, const void* codes, int64_t N,
-                      int64_t K, int group, int epilogue, const void* residual, void* Y, void* workspace,
-                      size_t workspace_bytes, void* stream)
+// (`best`: a workspace of e0m4_fused_workspace_best_bytes may be written, else one of e0m4_fused_workspace_bytes)
+static int matmul_fused(const void* X, int64_t M, const void* rms_gamma, float rms_eps, const void* codes, int64_t N, int64_t K,
+                        int group, int epilogue, const void* residual, void* Y, void* workspace, size_t workspace_bytes, bool best,
+                        void* stream)
 {
     int rc = check_shape(N, K, group);
     if (rc != E0M4_OK) return rc;
@@ -477,7 +478,7 @@ int e0m4_matmul_fused(const void* X, int64_t M, const void* rms_gamma, float rms
     FusedPath path = fused_path(f, M, N, K, group, &tiles);
     const size_t nb = rms_gamma ? norm_bytes(M, K) : 0;
     // (chunks need no workspace: calls without one stay there)
-    if (path == kFusedTiles && nb > 0 && (!workspace || !aligned16(workspace) || workspace_bytes < nb)) path = kFusedChunks;
+    if (path == kFusedTiles && nb > 0 && (!best || !workspace || !aligned16(workspace) || workspace_bytes < nb)) path = kFusedChunks;
     if (path == kFusedSmallBatch) return launch_gemv_mfma_fused(f, X, M, codes, N, K, Y, st, 1, group);
     if (path == kFusedVector) return launch_gemv_fused(f, X, M, codes, N, K, group, Y, st);
     if (path == kFusedExact) return launch_gemv_exact(X, M, codes, N, K, kDqFormatFp16, Y, st);
@@ -500,6 +501,20 @@ int e0m4_matmul_fused(const void* X, int64_t M, const void* rms_gamma, float rms
     if (path == kFusedDq) return launch_gemv_dq(x, M, codes, N, K, group, kDqFormatFp16, Y, st);
     return launch_gemm_fused(f, x, M, codes, N, K, group, Y, static_cast<char*>(workspace) + nb,
                              workspace_bytes - nb, st);
+}
+
+int e0m4_matmul_fused(const void* X, int64_t M, const void* rms_gamma, float rms_eps, const void* codes, int64_t N,
+                      int64_t K, int group, int epilogue, const void* residual, void* Y, void* workspace,
+                      size_t workspace_bytes, void* stream)
+{
+    return matmul_fused(X, M, rms_gamma, rms_eps, codes, N, K, group, epilogue, residual, Y, workspace, workspace_bytes, false, stream);
+}
+
+int e0m4_matmul_fused_best(const void* X, int64_t M, const void* rms_gamma, float rms_eps, const void* codes, int64_t N,
+                           int64_t K, int group, int epilogue, const void* residual, void* Y, void* workspace,
+                           size_t workspace_bytes, void* stream)
+{
+    return matmul_fused(X, M, rms_gamma, rms_eps, codes, N, K, group, epilogue, residual, Y, workspace, workspace_bytes, true, stream);
 }
 
 // ---- E0M3: the 3-bit member of the family, stored in 4-bit slots ---------------------------------------

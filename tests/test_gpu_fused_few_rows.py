@@ -89,3 +89,24 @@ def test_on_a_raw_stream_that_is_not_the_current_one(e0m4, oracle):
     X = to_dev(synth_inputs.activations(200, K, seed=983))
     with pytest.raises(ValueError, match="workspace"):
         e0m4.e0m4_matmul_fused(X, codes, N, K, 128, rms_gamma=gamma, rms_eps=1e-5, out=X.new_empty((200, N)), stream=side.cuda_stream)
+
+
+def test_a_workspace_that_is_not_needed_is_not_touched(e0m4, oracle):
+    """A buffer that several calls share stays as it is where the call's stated need is 0."""
+    M, N, K = 45, 4608, 2048
+    codes, _ = quantized(e0m4, oracle, N, K, 128, seed=990)
+    X, gamma = to_dev(synth_inputs.activations(M, K, seed=991)), to_dev(synth_inputs.norm_weight(K, 992))
+    room = torch.full((M * K * 2 + 256,), 255, dtype=torch.uint8, device=X.device)
+    L, stream = e0m4.lib(), torch.cuda.current_stream().cuda_stream
+    Y = torch.empty((2, M, N), dtype=torch.float16, device=X.device)
+
+    def args(y):
+        return (X.data_ptr(), M, gamma.data_ptr(), ctypes.c_float(1e-5), codes.data_ptr(), N, K, 128, 0, 0, y.data_ptr(),
+                room.data_ptr(), room.numel(), stream)
+
+    assert e0m4.e0m4_fused_workspace_bytes(M, N, K, 128, True, 0) == 0
+    assert L.e0m4_matmul_fused(*args(Y[0])) == 0
+    e0m4.e0m4_matmul_fused(X, codes, N, K, 128, rms_gamma=gamma, rms_eps=1e-5, workspace=room)
+    assert np.all(room.cpu().numpy() == 255)
+    assert L.e0m4_matmul_fused_best(*args(Y[1])) == 0 and torch.equal(Y[0], Y[1])
+    assert np.any(room.cpu().numpy() != 255)            # (the normalised activations)
