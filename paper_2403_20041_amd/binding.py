@@ -262,6 +262,22 @@ def e0m4_fused_workspace_bytes(M: int, N: int, K: int, group: int, with_rmsnorm:
     return lib().e0m4_fused_workspace_bytes(M, N, K, group, 1 if with_rmsnorm else 0, epilogue)
 
 
+def _capturing(stream) -> bool:
+    if stream is not None and hasattr(stream, "cuda_stream"):
+        with torch.cuda.stream(stream):
+            return torch.cuda.is_current_stream_capturing()
+    return torch.cuda.is_current_stream_capturing()
+
+
+def _chunks_are_shorter(M: int, n_out: int, K: int) -> bool:
+    """Of a call with an rms-norm that is issued by itself and may do without a workspace: with one it is shorter on the GPU, and
+    by a launch and an allocation 3 - 4 us longer on the host.  In row chunks it takes 8 - 10 us where these (one for 16 rows and
+    16 columns) are no more than the compute units and rows of X not long, less than the host does then (M = 20, 2048 x 2048 8.3
+    and 10.1 - 12.8 us, replayed in a graph 8.5 and 7.1); else 12 - 35 (M = 45, 4608 x 4096 19.7 and 11.9; M = 18, gated 2304 x 6272
+    15.7 and 12.5)."""
+    return 17 <= M <= 64 and -(-M // 16) * -(-n_out // 16) <= 256 and K <= 4608
+
+
 def e0m4_matmul_fused(X, codes, N: int, K: int, group: int, rms_gamma=None, rms_eps: float = 0.0,
                       epilogue: int = E0M4_EPILOGUE_NONE, residual=None, out=None, workspace=None, stream=None):
     """The matmul with rms-norm on X, the SiLU-gated product of the two output halves and a residual add
@@ -280,8 +296,9 @@ def e0m4_matmul_fused(X, codes, N: int, K: int, group: int, rms_gamma=None, rms_
     call = lib().e0m4_matmul_fused                      # (which writes to a caller's workspace only where one is needed)
     if workspace is None:
         need = lib().e0m4_fused_workspace_best_bytes(M, N, K, group, 1 if rms_gamma is not None else 0, epilogue)
-        if need > 0 and not _can_allocate(X.device, stream):        # (calls that can do without one run without)
-            need = e0m4_fused_workspace_bytes(M, N, K, group, rms_gamma is not None, epilogue)
+        if need > 0 and (not _can_allocate(X.device, stream)
+                         or (rms_gamma is not None and _chunks_are_shorter(M, n_out, K) and not _capturing(stream))):
+            need = e0m4_fused_workspace_bytes(M, N, K, group, rms_gamma is not None, epilogue)     # (0 if it can do without)
         if need > 0:
             workspace = _empty(need, torch.uint8, X.device, stream, "workspace")
             call = lib().e0m4_matmul_fused_best

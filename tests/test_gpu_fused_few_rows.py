@@ -110,3 +110,58 @@ def test_a_workspace_that_is_not_needed_is_not_touched(e0m4, oracle):
     assert np.all(room.cpu().numpy() == 255)
     assert L.e0m4_matmul_fused_best(*args(Y[1])) == 0 and torch.equal(Y[0], Y[1])
     assert np.any(room.cpu().numpy() != 255)            # (the normalised activations)
+
+
+@pytest.mark.parametrize("M,N,K,swiglu,brings", [(24, 2048, 2048, True, False), (26, 4096, 4608, True, False), (26, 4096, 4736, True, True),
+                                                 (32, 4096, 1024, True, False), (32, 4160, 1024, True, True), (45, 4608, 2048, False, True)])
+def test_calls_issued_one_by_one_allocate_only_where_that_is_the_faster_way(e0m4, oracle, M, N, K, swiglu, brings):
+    codes = e0m4.e0m4_quantize(to_dev(synth_inputs.weights(64, K, seed=1000)).repeat(N // 64, 1), 128)[0]
+    X, gamma = to_dev(synth_inputs.activations(M, K, seed=1001, outlier_frac=0.01)), to_dev(synth_inputs.norm_weight(K, 1002))
+    n_out = N // 2 if swiglu else N
+    Y, Z = (torch.empty((M, n_out), dtype=torch.float16, device=X.device) for _ in range(2))
+
+    def run(out, stream=None):
+        e0m4.e0m4_matmul_fused(X, codes, N, K, 128, rms_gamma=gamma, rms_eps=1e-5, epilogue=1 if swiglu else 0, out=out, stream=stream)
+
+    def allocations():
+        return torch.cuda.memory_stats(X.device)["allocation.all.allocated"]
+
+    before = allocations()
+    run(Y)
+    assert allocations() - before == (1 if brings else 0)
+    graph = torch.cuda.CUDAGraph()                      # in a graph always, to the same bits
+    with torch.cuda.graph(graph):
+        before = allocations()
+        run(Z)
+        run(Z, torch.cuda.current_stream())
+        assert allocations() - before == 2
+    for _ in range(3):
+        Z.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(Y, Z)
+
+
+# the shapes of test_bits_of_the_chunks with an rms-norm, whose calls from Python go in chunks where these are few
+@pytest.mark.parametrize("N,K,workgroups", [(192, 128, 0), (448, 1664, 0), (320, 1152, 10), (1088, 2048, 34), (576, 4096, 12), (448, 1536, 7),
+                                            (320, 4480, 20), (192, 7040, 6), (1728, 2304, 16)])
+@pytest.mark.parametrize("M", [17, 32, 41, 48, 49, 64])
+def test_bits_of_the_chunks_with_an_rms_norm(e0m4, oracle, M, N, K, workgroups):
+    codes, _ = quantized(e0m4, oracle, N, K, 128, seed=900 + N)
+    X, gamma = to_dev(synth_inputs.activations(M, K, seed=901 + M, outlier_frac=0.01)), to_dev(synth_inputs.norm_weight(K, 902))
+    e0m4.e0m4_set_knob("gemv_workgroups", workgroups)
+    try:
+        room = torch.empty(M * K * 2 + 256 + e0m4.e0m4_fused_workspace_bytes(M, N, K, 128, True, 0), dtype=torch.uint8, device=X.device)
+        for swiglu, res in ((False, False), (False, True), (True, False), (True, True)):
+            n_out = N // 2 if swiglu else N
+            R = to_dev(synth_inputs.residual(M, n_out, 903)) if res else None
+            Yc = call(e0m4, 8, X, codes, N, K, gamma, swiglu, R)
+            Y = R.clone() if res else torch.empty_like(Yc)                     # (the residual updated in place)
+            e0m4.e0m4_set_knob("gemv_mfma", 7)
+            rc = e0m4.lib().e0m4_matmul_fused_best(X.data_ptr(), M, gamma.data_ptr(), ctypes.c_float(1e-5), codes.data_ptr(), N, K, 128,
+                                                   1 if swiglu else 0, Y.data_ptr() if res else 0, Y.data_ptr(), room.data_ptr(), room.numel(),
+                                                   torch.cuda.current_stream().cuda_stream)
+            assert rc == 0 and torch.equal(Y, Yc), (swiglu, res)
+    finally:
+        e0m4.e0m4_set_knob("gemv_mfma", 0)
+        e0m4.e0m4_set_knob("gemv_workgroups", 0)
