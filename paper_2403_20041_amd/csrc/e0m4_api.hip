@@ -289,6 +289,7 @@ static size_t fused_bytes(int64_t M, int64_t N, int64_t K, int group, bool norme
     Fusion f;
     f.swiglu = epilogue == E0M4_EPILOGUE_SWIGLU;
     f.residual = &f;                                    // (a call without a residual needs no more than one with it)
+    if (best && normed) f.gamma = &f;                   // (which of the kernels without a need is the fastest depends on the rms-norm)
     const FusedPath path = fused_path(f, M, N, K, group);
     if (best && path == kFusedTiles && normed) return norm_bytes(M, K);
     if (path != kFusedGemm) return 0;                   // (with a residual it is never the kernel with dequantised operands)

@@ -165,3 +165,20 @@ def test_bits_of_the_chunks_with_an_rms_norm(e0m4, oracle, M, N, K, workgroups):
     finally:
         e0m4.e0m4_set_knob("gemv_mfma", 0)
         e0m4.e0m4_set_knob("gemv_workgroups", 0)
+
+
+# (two, three and four chunks, on either side of as many chunks as compute units)
+@pytest.mark.parametrize("M,N,swiglu", [(20, 2048, False), (30, 2048, False), (45, 1024, False), (48, 1360, False), (48, 1376, False), (51, 1024, False),
+                                        (64, 1024, False), (64, 1040, False), (24, 2048, True), (45, 1024, True), (45, 4096, True)])
+def test_the_best_workspace_is_asked_for_where_it_is_used(e0m4, oracle, M, N, swiglu):
+    K, epilogue = 1152, 1 if swiglu else 0
+    codes, _ = quantized(e0m4, oracle, N, K, 128, seed=1010)
+    X, gamma = to_dev(synth_inputs.activations(M, K, seed=1011)), to_dev(synth_inputs.norm_weight(K, 1012))
+    room = torch.full((M * K * 2 + 256,), 255, dtype=torch.uint8, device=X.device)
+    best = e0m4.lib().e0m4_fused_workspace_best_bytes(M, N, K, 128, 1, epilogue)
+    assert best in (0, (M * K * 2 + 255) // 256 * 256) and e0m4.e0m4_fused_workspace_bytes(M, N, K, 128, True, epilogue) == 0
+    Y = torch.empty((M, N // 2 if swiglu else N), dtype=torch.float16, device=X.device)
+    rc = e0m4.lib().e0m4_matmul_fused_best(X.data_ptr(), M, gamma.data_ptr(), ctypes.c_float(1e-5), codes.data_ptr(), N, K, 128, epilogue, 0,
+                                           Y.data_ptr(), room.data_ptr(), room.numel(), torch.cuda.current_stream().cuda_stream)
+    assert rc == 0 and bool((room != 255).any()) == (best > 0)
+    assert torch.equal(Y, call(e0m4, 8, X, codes, N, K, gamma, swiglu, None))

@@ -230,6 +230,35 @@ def test_fused_matmul_validation_and_workspace(L):
     assert w(1024, 4096, 4096, 128, 1, 5) == 0
 
 
+def test_best_workspace_of_fused_calls(L):
+    """Room for the normalised activations wherever a call with an rms-norm has a kernel for all rows in a workgroup that is
+    faster than row chunks; else what the call has to bring."""
+    best, need = L.e0m4_fused_workspace_best_bytes, L.e0m4_fused_workspace_bytes
+    NONE, SWIGLU = 0, 1
+
+    def norm(M, K):
+        return (2 * M * K + 255) // 256 * 256
+
+    # chunks that leave compute units free: with an rms-norm two of them, three without the gated product, never four
+    for M, N, K, epilogue, tiles in ((17, 2048, 2048, NONE, True), (20, 512, 2048, NONE, True), (30, 2048, 2048, NONE, True),
+                                     (32, 1536, 1024, NONE, True), (45, 512, 2048, NONE, True), (45, 1024, 2048, NONE, True),
+                                     (51, 1024, 2048, NONE, False), (64, 512, 2048, NONE, False), (24, 2048, 2048, SWIGLU, True),
+                                     (45, 1024, 2048, SWIGLU, False)):
+        assert best(M, N, K, 128, 1, epilogue) == (norm(M, K) if tiles else 0), (M, N, K, epilogue)
+        assert need(M, N, K, 128, 1, epilogue) == 0 and best(M, N, K, 128, 0, epilogue) == 0, (M, N, K, epilogue)
+    # on either side of as many chunks as compute units, three and four to a row block
+    assert best(48, 1360, 2048, 128, 1, NONE) == norm(48, 2048) and best(64, 1024, 2048, 128, 1, NONE) == 0
+    assert best(64, 1040, 2048, 128, 1, NONE) == norm(64, 2048)
+    for M in (1, 8, 16, 17, 33, 48, 64, 65, 300):
+        for N in (64, 320, 2048, 4096, 27392):
+            for K in (128, 1152, 4096, 13696):
+                for group in (64, 128):
+                    for normed in (0, 1):
+                        for epilogue in (NONE, SWIGLU):
+                            b, n = best(M, N, K, group, normed, epilogue), need(M, N, K, group, normed, epilogue)
+                            assert b == n or (b == norm(M, K) and n == 0 and normed and group == 128), (M, N, K, group, normed, epilogue)
+
+
 def test_kv_append_validation(L):
     L.e0m4_kv_append.restype = ctypes.c_int
     L.e0m4_kv_append.argtypes = [ctypes.c_void_p, ctypes.c_int64, ctypes.c_int64, ctypes.c_void_p, ctypes.c_int64,
