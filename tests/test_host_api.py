@@ -242,6 +242,7 @@ def test_best_workspace_of_fused_calls(L):
     # chunks that leave compute units free: with an rms-norm two of them, three without the gated product, never four
     for M, N, K, epilogue, tiles in ((17, 2048, 2048, NONE, True), (20, 512, 2048, NONE, True), (30, 2048, 2048, NONE, True),
                                      (32, 1536, 1024, NONE, True), (45, 512, 2048, NONE, True), (45, 1024, 2048, NONE, True),
+                                     (45, 1024, 3584, NONE, True), (45, 1024, 3712, NONE, False), (45, 1024, 4096, NONE, False), (45, 1024, 4224, NONE, True),
                                      (51, 1024, 2048, NONE, False), (64, 512, 2048, NONE, False), (24, 2048, 2048, SWIGLU, True),
                                      (45, 1024, 2048, SWIGLU, False)):
         assert best(M, N, K, 128, 1, epilogue) == (norm(M, K) if tiles else 0), (M, N, K, epilogue)
