@@ -135,6 +135,11 @@ bool use_gemv_dq4(int64_t M, int64_t N, int64_t K, int group)
     }
     return use_gemv_dq(M, N, K, group, kDqFormatFp16);
 }
+// (whether such calls have no workspace to bring)
+bool dq4_free(int64_t M, int64_t N, int64_t K, int group)
+{
+    return knob(Knob::gemv_mfma) == 4 || gemv_dq_free(M, N, K, group, kDqFormatFp16);
+}
 // bfloat16 of up to eight rows: the small-batch kernel, which multiplies the codes' exact values as the vector kernel does but
 // whose time hardly grows with the rows (27392 x 5120 at M = 5 32 -> 18.3 us; M = 2 21.5 -> 18.4).  Its time over the vector kernel's:
 //   Groups of 64 and 32 from three rows on (2560 x 2048 at M = 2 4.4 us there and 4.8 here, at M = 3 5.6 and 4.8), 0.37 - 1.02 on 1 100
@@ -237,7 +242,7 @@ size_t e0m4_workspace_bytes(int64_t M, int64_t N, int64_t K, int group)
     if (check_shape(N, K, group) != E0M4_OK || M <= 0 || N == 0 || K == 0) return 0;             // invalid or empty: nothing runs
     if (use_gemv_exact(M, N, K, group, kDqFormatFp16)) return 0;
     if (small_m_on_vector(M, N, K)) return 0;           // the small-M kernels need none
-    if (use_gemv_dq4(M, N, K, group) && (knob(Knob::gemv_mfma) == 4 || gemv_dq_free(M, N, K, group, kDqFormatFp16))) return 0;
+    if (use_gemv_dq4(M, N, K, group) && dq4_free(M, N, K, group)) return 0;
     if (use_gemv_mfma(M, N, K, group) || small_batch_in_chunks(Fusion{}, M, N, K, group)) return 0;
     return gemm_workspace_bytes(M, N, K);       // partial tiles of the split-K GEMM, if it splits
 }
@@ -398,10 +403,9 @@ int e0m4_unpack_codes(const void* codes, int64_t N, int64_t K, int group, void* 
     return launch_unpack(codes, N, K, group, out, (hipStream_t)stream);
 }
 
-// a workspace that a plain call has to bring, whether its kernel uses it or not
+// the workspace of a plain call that the GEMM would have otherwise, by the GEMM's rules: refused also where nobody uses it
 static int check_workspace(size_t need, const void* workspace, size_t bytes)
 {
-    if (need == 0) return E0M4_OK;
     if (bytes > 0 && (!workspace || !aligned16(workspace))) return workspace ? E0M4_ERR_ALIGN : E0M4_ERR_NULL;
     return bytes < need ? E0M4_ERR_WORKSPACE : E0M4_OK;
 }
@@ -427,7 +431,7 @@ int e0m4_matmul(const void* X, int64_t M, const void* codes, const void* scales,
     if (use_gemv_exact(M, N, K, group, kDqFormatFp16))
         return launch_gemv_exact(X, M, codes, N, K, kDqFormatFp16, Y, (hipStream_t)stream);
     if (use_gemv_dq4(M, N, K, group)) {
-        rc = check_workspace(e0m4_workspace_bytes(M, N, K, group), workspace, workspace_bytes);
+        if (!dq4_free(M, N, K, group)) rc = check_workspace(e0m4_workspace_bytes(M, N, K, group), workspace, workspace_bytes);
         return rc != E0M4_OK ? rc : launch_gemv_dq(X, M, codes, N, K, group, kDqFormatFp16, Y, (hipStream_t)stream);
     }
     if (use_gemv_mfma(M, N, K, group)) return launch_gemv_mfma(X, M, codes, N, K, Y, (hipStream_t)stream, 1, group);
@@ -696,7 +700,7 @@ int e0m8_matmul(const void* X, int64_t M, const void* codes, int64_t N, int64_t 
     if (!X || !codes) return E0M4_ERR_NULL;
     if (!aligned16(X) || !aligned16(codes)) return E0M4_ERR_ALIGN;
     if (e0m8_use_gemv_dq(M, N, K)) {
-        rc = check_workspace(e0m8_workspace_bytes(M, N, K, group), workspace, workspace_bytes);
+        if (!e0m8_dq_free(M, N, K)) rc = check_workspace(e0m8_workspace_bytes(M, N, K, group), workspace, workspace_bytes);
         if (rc != E0M4_OK) return rc;
         return launch_gemv_dq(X, M, codes, N, K, 128, kDqFormatE8, Y, (hipStream_t)stream);
     }

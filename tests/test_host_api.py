@@ -132,6 +132,21 @@ def test_more_columns_than_the_gemm_serves_are_refused(L):
         assert L.e0m4_bf16_matmul(p, M, p, N, K, group, p, None) == -2, (M, K, group)
 
 
+def test_a_workspace_that_is_no_buffer_is_refused_where_nobody_uses_it(L):
+    """Plain calls of up to 64 rows on large weights, the GEMM's or the small-batch kernel's by which is the faster: a misaligned
+    workspace, or none with a size, is refused on either side of the line, also where 0 bytes are needed."""
+    p, odd = ctypes.c_void_p(0x1000), ctypes.c_void_p(0x1008)
+    L.e0m8_matmul.argtypes = [ctypes.c_void_p, ctypes.c_int64, ctypes.c_void_p, ctypes.c_int64, ctypes.c_int64, ctypes.c_int,
+                              ctypes.c_void_p, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p]
+    for M, N, K in ((17, 71000, 1024), (24, 65536, 4096), (31, 89472, 5376), (40, 131072, 4096), (64, 200000, 4096), (100, 65536, 4096)):
+        assert L.e0m4_workspace_bytes(M, N, K, 128) == 0
+        assert L.e0m4_matmul(p, M, p, p, p, N, K, 128, p, odd, 4096, None) == -4, (M, N, K)
+        assert L.e0m4_matmul(p, M, p, p, p, N, K, 128, p, None, 4096, None) == -1, (M, N, K)
+        if N * K > 1e8:
+            assert L.e0m8_matmul(p, M, p, N, K, 128, p, odd, 4096, None) == -4, (M, N, K)
+            assert L.e0m8_matmul(p, M, p, N, K, 128, p, None, 4096, None) == -1, (M, N, K)
+
+
 def test_error_codes_before_any_launch(L):
     p = ctypes.c_void_p(0x1000)         # aligned, never dereferenced: every call below fails validation first
     odd = ctypes.c_void_p(0x1008)
