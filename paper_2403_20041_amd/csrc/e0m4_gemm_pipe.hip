@@ -1306,7 +1306,7 @@ bool gemm_pipe_supported(int64_t K) { return K >= 128 && (K % (2 * BK)) == 0; }
 
 size_t gemm_pipe_workspace_bytes(int64_t M, int64_t N, int64_t K, bool swiglu, bool fused)
 {
-    if (M <= 0 || N <= 0 || !gemm_pipe_supported(K)) return 0;
+    if (M <= 0 || N <= 0 || (swiglu && N < 2) || !gemm_pipe_supported(K)) return 0;
     return pipe_room(M, N, K, !fused && !swiglu, nullptr);
 }
 

@@ -88,6 +88,11 @@ def test_size_queries_of_empty_and_invalid_problems(L):
     assert L.e0m8_codes_bytes(0, 128, 128) == 0
 
 
+def test_no_partial_sums_for_a_gated_call_without_columns(L):
+    for M, K in ((51, 8320), (597, 3072), (100, 5888)):
+        assert L.e0m4_fused_workspace_bytes(M, 1, K, 128, 0, 1) == 0 and L.e0m8_fused_workspace_bytes(M, 1, K, 128, 0, 1) == 0
+
+
 def test_knobs_belong_to_the_calling_thread(L):
     """A diagnostic knob set by one thread changes neither the size queries nor the dispatch of another."""
     import threading
