@@ -150,6 +150,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KS, 2) void gemm_pipe_kernel(const
     static_assert(!BF || (!FUSED && !E8), "the bfloat16 member has the plain 4-bit kernel only");
     static_assert(!SHORT || (WGM == 1 && BM == 128 && KS == 1), "short last row tiles: of 128 rows");
     static_assert(KS == 1 || BM == 64, "K parts inside a workgroup: tiles of 64 rows");
+    static_assert(!FUSED || KS == 1 || TN == 2, "the exchange of gated sums between wavefronts has no place for more than one K part");
     constexpr bool kSk = !FUSED && !E8 && !BF && BM == 256 && BN == 256;
     const bool sk_on = kSk && sk.enabled;
     const int total = m_tiles * n_tiles * splits;
@@ -1254,8 +1255,10 @@ int launch_pipe(const half_t* x, int64_t M, const uint4* c, int64_t N, int64_t K
         const int zrc = check_launch();
         if (zrc != E0M4_OK) return zrc;
     }
-    // 96 KiB for the large tile: above the default limit.  (KS > 1: as many rings; the other parts' sums, afterwards.)
+    // 128 KiB for the large tile: above the default limit.  (KS > 1: as many rings; the other parts' sums, afterwards.)
     constexpr size_t lds = std::max((size_t)KS * kStages * BM * kRowBytes, (size_t)(KS - 1) * BM * BN * sizeof(float));
+    constexpr int per_unit = KS > 1 || BM == 256 ? 1 : BM == 64 && BN == 128 ? 4 : 2;      // as TileCost::cap counts on
+    static_assert(lds * per_unit <= 160 * 1024, "LDS of a compute unit");
     auto launch = [&](auto kernel, std::atomic<uint64_t>& lds_allowed) -> int {
         const int arc = allow_dynamic_lds(reinterpret_cast<const void*>(kernel), (int)lds, lds_allowed);
         if (arc != E0M4_OK) return arc;
