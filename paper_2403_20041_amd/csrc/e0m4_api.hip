@@ -123,6 +123,13 @@ bool use_gemv_dq(int64_t M, int64_t N, int64_t K, int group, DqFormat format)
     if (k == 1 || k == 5 || !gemv_dq_supported(M, N, K, group)) return false;
     return k == 4 || gemv_dq_pays(M, N, K, group, format);
 }
+// The same for fused calls that would be the GEMM's, with an rms-norm alone or without operators.
+bool use_gemv_dq_fused(int64_t M, int64_t N, int64_t K, int group, DqFormat format)
+{
+    const int k = knob(Knob::gemv_mfma);
+    if (k == 1 || k == 5 || !gemv_dq_supported(M, N, K, group)) return false;
+    return k == 4 || gemv_dq_beats_gemm(M, N, K, group, format);
+}
 bool use_gemv_dq4(int64_t M, int64_t N, int64_t K, int group)
 {
     if (M < 2) return false;
@@ -282,7 +289,7 @@ static FusedPath fused_path(const Fusion& f, int64_t M, int64_t N, int64_t K, in
         return kFusedTiles;
     }
     if (small_m_on_vector(M, N, K) && gemv_fused_supported(f, M, N, K)) return kFusedVector;
-    return as_plain(f) && !gemm_steered() && N <= (int64_t)1 << 24 && use_gemv_dq(M, N, K, group, kDqFormatFp16) ? kFusedDq : kFusedGemm;
+    return as_plain(f) && !gemm_steered() && N <= (int64_t)1 << 24 && use_gemv_dq_fused(M, N, K, group, kDqFormatFp16) ? kFusedDq : kFusedGemm;
 }
 
 // The workspace that a call has to bring: the normalised X, the GEMM's partial sums behind it.  (Calls of the kernel with
@@ -729,7 +736,7 @@ static FusedPath fused_path8(const Fusion& f, int64_t M, int64_t N, int64_t K)
     if (small_batch8_in_chunks(f, M, N, K)) return kFusedChunks;
     if (small_m_on_vector(M, N, K) && gemv_fused_supported(f, M, N, 2 * K)) return kFusedVector;
     if (!gemm_pipe_supported(K) || N > (int64_t)1 << 24) return kFusedNone;
-    return as_plain(f) && !gemm_steered() && use_gemv_dq(M, N, K, 128, kDqFormatE8) ? kFusedDq : kFusedGemm;
+    return as_plain(f) && !gemm_steered() && use_gemv_dq_fused(M, N, K, 128, kDqFormatE8) ? kFusedDq : kFusedGemm;
 }
 
 size_t e0m8_fused_workspace_bytes(int64_t M, int64_t N, int64_t K, int group, int with_rmsnorm, int epilogue)

@@ -461,11 +461,7 @@ bool gemv_dq_supported(int64_t M, int64_t N, int64_t K, int group)
 //   On the shortest rows most wavefronts have no k block of their own, and many rows of X cost the others time: M = 64, 16384 x
 //     128 6.0 us against 4.9; in two parts M = 128, 8192 x 256 7.7 against 6.2, 8192 x 512 7.9 against 8.3.
 //   Groups of 32 and 64 up to 16 rows: always (1.3 - 3.1, the vector kernel's calls among them).
-//   17 to 64 rows, against K splits, on 181 problems in 4-bit codes and 240 in 8-bit codes: up to 48
-//     rows 1.0 - 2.9 (27392 x 4096 at M = 24 29.7 -> 21.5, 4096 x 13696 at M = 30 26.8 -> 18.9) but for the longest rows, of which a
-//     workgroup reads all of X (7872 x 13824 at M = 41 28.2 and 30.3).  With more rows 1.0 - 1.9 within the lines below, beyond them 0.8
-//     - 1.1 (but they stay here within the lines of gemv_dq_free; 26272 x 3968 at M = 54 32.7 and 34.2, 17376 x 6912 at M = 64 37.0 and 42.6); in 8-bit codes, whose rows are twice as
-//     long, 3392 x 9088 at M = 56 20.1 and 23.2, 18560 x 6656 at M = 63 45.3 and 52.0.
+//   17 to 64 rows: gemv_dq_beats_gemm, but plain calls within the lines of gemv_dq_free stay here whatever the GEMM has become.
 //   (gemv_dq_free: calls that need no workspace.  Callers of the others, up to 64 rows, bring the GEMM's; those lines stay
 //   where they are, so that a size that was asked for once is enough for good.)
 bool gemv_dq_free(int64_t M, int64_t N, int64_t K, int group, DqFormat format)
@@ -474,18 +470,40 @@ bool gemv_dq_free(int64_t M, int64_t N, int64_t K, int group, DqFormat format)
     if (M > 16) return (double)N * (double)K <= (format == kDqFormatE8 ? 1e8 : 7e7) && (M <= 48 || (K >= 256 && K <= 9216));
     return format == kDqFormatFp16 && group != 128;
 }
+// fp16, on 840 calls with 640 to 260 000 columns and 256 to 14 000 weights a row, by the row blocks that a compute unit has: every
+// workgroup reads all of X, and beyond sixteen row blocks of its own the workgroups come in rounds.  The GEMM's time over this kernel's:
+//   4-bit codes.  17 to 32 rows: 1.1 - 1.8 up to six row blocks, 1.0 - 1.3 up to twelve, up to 24 on rows of 1536 weights and more 0.97 -
+//   1.15; on shorter ones 0.79 - 0.94 (65984 x 512 at M = 22 10.8 and 13.5 us), beyond 24 0.6 - 0.92 (201088 x 384 at M = 22 0.62).
+//   33 to 48 rows: 1.0 - 2.0 up to six, 0.84 - 0.93 with seven and eight (the last of two groups of wavefronts is half empty), 1.09 - 1.14
+//   with nine and ten, beyond 0.6 - 0.96 (209792 x 1152 at M = 38 48.5 and 71.3).  49 to 64 rows: 1.0 - 1.4 up to four, on rows of 640
+//   weights and fewer 0.85 - 0.95; 0.75 - 1.25 with five and six (where the GEMM's tiles are just more than the compute units it is the
+//   slower one), beyond 0.55 - 1.0 (59328 x 1280 at M = 64 19.3 and 25.6).  The longest rows, of which a workgroup reads all of X: 0.9 - 1.0.
+//   8-bit codes.  17 to 32 rows: 0.96 - 1.5 up to thirteen, beyond 0.82 - 1.03; 33 to 48: 1.0 - 1.3 up to four, and up to ten on rows of
+//   1024 weights and more, else 0.7 - 0.96; 49 to 64: 1.0 - 1.4 up to four, beyond 0.7 - 1.1 (78720 x 1280 at M = 53 31.2 and 40.9).
+//   Up to sixteen rows: groups of 32 and 64, up to 60 row blocks (1.04 - 1.9).
+bool gemv_dq_beats_gemm(int64_t M, int64_t N, int64_t K, int group, DqFormat format)
+{
+    DqPlan p;
+    if (M < 3 || M > kDqMaxM || !make_dq_plan(M, N, K, p)) return false;
+    if (M <= 16) return format == kDqFormatFp16 && group != 128;
+    const int64_t rb = (row_blocks(N) + kTargetWorkgroups - 1) / kTargetWorkgroups;
+    if (format == kDqFormatE8) {
+        if (M <= 32) return rb <= 13;
+        if (M <= 48) return (rb <= 4 || (rb <= 10 && K >= 1024)) && K <= 8192;
+        return rb <= 4 && K >= 256 && K <= 6144;
+    }
+    if (M <= 32) return rb <= 6 || (rb <= 12 && K >= 768) || (rb <= 24 && K >= 1536);
+    if (M <= 48) return (rb <= 6 || (rb >= 9 && rb <= 10 && K >= 512)) && K <= 12800;
+    return rb <= 4 && K >= 768 && K <= 7680;
+}
 bool gemv_dq_pays(int64_t M, int64_t N, int64_t K, int group, DqFormat format)
 {
     DqPlan p;
     if (M < 3 || !make_dq_plan(M, N, K, p)) return false;
-    const double NK = (double)N * (double)K;
     if (format == kDqFormatBf16)
         return M > kGemvMaxM && N <= (int64_t)1 << 24 &&
-               (M <= 48 || (M <= kDqMaxM ? K >= 256 : K >= 512 && NK <= 7e7 && p.wr * p.r <= 2));
-    if (M > kDqMaxM) return false;
-    if (gemv_dq_free(M, N, K, group, format)) return true;
-    if (format == kDqFormatE8) return M > 16 && (M <= 32 || (M <= 48 ? K <= 8192 : K >= 256 && K <= 6144 && NK <= 1.2e8));
-    return M > 16 && (M <= 32 || (M <= 48 ? K <= 12800 : K >= 256 && K <= 7680 && NK <= 1e8));
+               (M <= 48 || (M <= kDqMaxM ? K >= 256 : K >= 512 && (double)N * (double)K <= 7e7 && p.wr * p.r <= 2));
+    return gemv_dq_free(M, N, K, group, format) || (M > 16 && gemv_dq_beats_gemm(M, N, K, group, format));
 }
 
 // (the row counts of the calls below; the kernel is not compiled for others)

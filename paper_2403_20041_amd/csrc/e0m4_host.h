@@ -116,10 +116,12 @@ bool gemv_tiles_pays(const Fusion& f, const TilesPlan& p, int chunks);
 int launch_gemv_tiles(const Fusion& f, const TilesPlan& p, const void* X, int64_t M, const void* packed, int64_t N, int64_t K, void* Y,
                       hipStream_t stream);
 // Small-batch path with the weight operand dequantised in registers: 2 <= M <= 128, any group (e0m4_gemv_dq.hip).
-// (`pays`: it is expected to beat the GEMM; `free`: such calls need no workspace, the others as much as the GEMM)
+// (`beats_gemm`: it is expected to be the faster one; `free`: plain calls that need no workspace, the others as much as the GEMM;
+// `pays`: plain calls that it has)
 enum DqFormat { kDqFormatFp16 = 0, kDqFormatE8 = 1, kDqFormatBf16 = 2 };     // 4-bit codes, 8-bit codes, 4-bit codes on bfloat16
 bool gemv_dq_supported(int64_t M, int64_t N, int64_t K, int group);
 bool gemv_dq_pays(int64_t M, int64_t N, int64_t K, int group, DqFormat format);
+bool gemv_dq_beats_gemm(int64_t M, int64_t N, int64_t K, int group, DqFormat format);
 bool gemv_dq_free(int64_t M, int64_t N, int64_t K, int group, DqFormat format);
 int launch_gemv_dq(const void* X, int64_t M, const void* packed, int64_t N, int64_t K, int group, DqFormat format, void* Y,
                    hipStream_t stream);

@@ -116,3 +116,32 @@ def test_most_row_blocks_per_wavefront(e0m4, oracle, fmt, M, K):
     finally:
         e0m4.e0m4_set_knob("gemv_mfma", 0)
         e0m4.e0m4_set_knob("gemv_workgroups", 0)
+
+
+# (wide weights: on either side of the number of row blocks per compute unit up to which this kernel is faster than the GEMM)
+@pytest.mark.parametrize("fmt,M,N,K,norm,here", [
+    ("e0m4", 32, 24576, 512, True, True), ("e0m4", 32, 24592, 512, True, False), ("e0m4", 17, 49152, 768, True, True),
+    ("e0m4", 32, 49168, 1408, True, False), ("e0m4", 32, 49168, 1536, False, True), ("e0m4", 24, 98320, 1536, False, False),
+    ("e0m4", 48, 24576, 512, True, True), ("e0m4", 33, 24592, 512, True, False), ("e0m4", 48, 40960, 512, True, True),
+    ("e0m4", 40, 40976, 2048, False, False), ("e0m4", 64, 16384, 768, True, True), ("e0m4", 64, 16400, 768, True, False),
+    ("e0m8", 32, 53248, 256, True, True), ("e0m8", 32, 53264, 256, True, False), ("e0m8", 40, 16400, 896, True, False),
+    ("e0m8", 40, 40960, 1024, True, True), ("e0m8", 40, 40976, 2560, False, False), ("e0m8", 64, 16384, 256, True, True),
+    ("e0m8", 64, 16400, 256, True, False)])
+def test_wide_weights_go_where_they_are_faster(e0m4, fmt, M, N, K, norm, here):
+    G = 64 if fmt == "e0m4" else 128
+    quantize = e0m4.e0m4_quantize if fmt == "e0m4" else e0m4.e0m8_quantize
+    codes = quantize(to_dev(synth_inputs.weights(512, K, seed=5000)).repeat(-(-N // 512), 1)[:N].contiguous(), G)[0]
+    X, gamma = to_dev(synth_inputs.activations(M, K, seed=5001, outlier_frac=0.01)), to_dev(synth_inputs.norm_weight(K, 5002))
+
+    def run(mode):
+        e0m4.e0m4_set_knob("gemv_mfma", mode)
+        try:
+            if norm:
+                return (e0m4.e0m4_matmul_fused if fmt == "e0m4" else e0m4.e0m8_matmul_fused)(X, codes, N, K, G, rms_gamma=gamma, rms_eps=1e-5)
+            return e0m4.e0m4_matmul(X, codes, None, None, N, K, G) if fmt == "e0m4" else e0m4.e0m8_matmul(X, codes, N, K, G)
+        finally:
+            e0m4.e0m4_set_knob("gemv_mfma", 0)
+
+    by_default, small_batch, gemm = run(0), run(4), run(5)
+    assert not torch.equal(small_batch, gemm)           # (they add in different orders)
+    assert torch.equal(by_default, small_batch if here else gemm)
