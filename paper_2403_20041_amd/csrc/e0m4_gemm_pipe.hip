@@ -912,16 +912,19 @@ constexpr int kMaxSplits = 8;
 // one  pairs * a(fill) + b  with a() piecewise linear in the fill -- a compute unit is slower the more of them run
 // (one round of 160 large tiles with K = 5120 takes 112 us, one of 256 tiles 152 us, whether the workgroups read
 // different tiles or all the same one: it is not the memory side), which is why filling idle units buys much less
-// than their number suggests; a() has a step at half fill, where the first compute units get a second workgroup.
+// than their number suggests; a() has a step where the first compute units get a second workgroup, at half fill (at a quarter for the
+// 64 x 128 tile: gated 297 x 6656 x 6656, 260 such tiles, 50.7 us, on 128 x 256 tiles 41.1).
 // A K split adds its reduction kernel (a fixed part and one per MB of partial sums), and the number of splits is the
 // one with the shortest estimate; even scheduling runs its whole rounds like whole tiles and the shared-out rest on
 // every unit at the full rate, and adds the slabs' cost, of which the part per sharer of a tile is serial (the last
 // arriver reads them all).
-// The constants are a least-squares fit (logarithm of the ratio to the measurement, rms 4.1 %) to 3010 timings of 181
-// problems -- M = 65 .. 8192, N = 1024 .. 20480, K = 1024 .. 14336, random ones and the layer shapes of 6B and 14B models -- each timed
-// with the five tiles, one to eight K splits, and with even scheduling, on weights out of cache.  Choosing by the estimate
-// costs 0.9 % over always choosing the measured best (geometric mean); without the tiles of 128 columns the best would be
-// 2.4 % slower (5.2 % up to 384 rows).  tune_gemm_estimate.py of the Python package times and fits in this way.
+// The constants are a least-squares fit (logarithm of the ratio to the measurement, rms 5.1 %) to 12893 timings of 608
+// problems -- M = 17 .. 8192, N = 1024 .. 20480, K = 1024 .. 14336, groups of 128, random ones and the layer shapes of 6B and 14B models --
+// on two cards, each timed with the five tiles, one to eight K splits, and with even scheduling, on weights out of cache.  Choosing by
+// the estimate costs 0.6 % over always choosing the measured best on the one card and 1.4 - 2.1 % on the other (geometric means), where
+// split launches on tiles of 128 columns take up to 28 % longer than on the first; up to 64 rows 6 %, above 384 0.5 %.  Without the tiles of 128
+// columns the best would be 2.3 - 4.0 % slower (up to 64 rows 11 - 16 %).  tune_gemm_estimate.py of the Python package times and fits in
+// this way.
 struct PipeTile {
     int bm, bn;
 };
@@ -930,31 +933,38 @@ constexpr int kFlatOnlyMaxM = 64;
 
 struct TileCost {
     double lo[4];                                       // us per pair of K slices at fill 0, 1/8, 1/4, 1/2 of a round ...
+    double past;                                        // ... just above 1/4 ...
     double hi[3];                                       // ... and just above 1/2, at 3/4 and 1
     double b;                                           // us per round: prologue and epilogue of a work item
     int cap;                                            // work items per round
 };
-constexpr TileCost kFlatCost{{0.800, 0.868, 0.905, 1.150}, {1.662, 1.908, 2.013}, 2.99, 2 * kComputeUnits};
-constexpr TileCost kHalfCost{{1.125, 1.183, 1.243, 1.817}, {2.587, 3.045, 3.491}, 5.67, 2 * kComputeUnits};
-constexpr TileCost kBigCost{{2.020, 2.049, 2.081, 2.238}, {2.220, 2.910, 3.533}, 7.54, kComputeUnits};
-constexpr TileCost kNarrowCost{{0.551, 0.515, 0.747, 1.243}, {1.388, 1.925, 2.255}, 2.73, 4 * kComputeUnits};
-constexpr TileCost kMidCost{{0.709, 0.737, 0.782, 1.046}, {1.472, 1.730, 1.981}, 3.52, 2 * kComputeUnits};
-constexpr double kReduceUs = 4.38, kReduceUsPerMB = 0.184;      // reduction kernel of a K split
-constexpr double kSkUs = 38.4, kSkUsPerSharer = 0.52;           // even scheduling: slabs, and the serial part per sharer
+constexpr TileCost kFlatCost{{0.821, 0.866, 0.887, 1.113}, 0.887, {1.604, 1.867, 1.868}, 3.74, 2 * kComputeUnits};
+constexpr TileCost kHalfCost{{1.114, 1.174, 1.222, 1.713}, 1.222, {2.513, 2.919, 3.212}, 6.07, 2 * kComputeUnits};
+constexpr TileCost kBigCost{{2.008, 2.046, 2.094, 2.227}, 2.094, {2.220, 2.730, 3.313}, 7.35, kComputeUnits};
+constexpr TileCost kNarrowCost{{0.505, 0.549, 0.628, 1.162}, 0.847, {1.393, 1.858, 2.078}, 3.33, 4 * kComputeUnits};
+constexpr TileCost kMidCost{{0.683, 0.726, 0.761, 0.988}, 0.761, {1.391, 1.660, 1.840}, 4.29, 2 * kComputeUnits};
+constexpr double kReduceUs = 4.23, kReduceUsPerMB = 0.211;      // reduction kernel of a K split
+constexpr double kSkUs = 39.1, kSkUsPerSharer = 0.86;           // even scheduling: slabs, and the serial part per sharer
 struct Estimate {
-    TileCost flat, half, big;
+    TileCost flat, half, big, narrow, mid;
     double reduce_us, reduce_us_per_mb, sk_us, sk_us_per_sharer;
     bool all_tiles;                                     // with the tiles of 128 columns, and a short last row tile counted as such
 };
-constexpr Estimate kNow{kFlatCost, kHalfCost, kBigCost, kReduceUs, kReduceUsPerMB, kSkUs, kSkUsPerSharer, true};
+constexpr Estimate kNow{kFlatCost, kHalfCost, kBigCost, kNarrowCost, kMidCost, kReduceUs, kReduceUsPerMB, kSkUs, kSkUsPerSharer, true};
 // The workspace that callers are asked for, and with it the most K splits that a launch may have, come from an estimate with
 // constants that stay as they are, whatever becomes of the kernel: a size once asked for is enough for good.  Fused calls of up to
 // 64 rows have exactly its number of splits: with another one their sums, and the residual streams that they feed, would be
 // rounded otherwise.
-constexpr Estimate kSizes{{{0.809, 1.173, 1.302, 1.456}, {1.601, 2.034, 1.971}, 4.39, 2 * kComputeUnits},
-                          {{1.427, 1.531, 1.573, 1.894}, {2.592, 3.118, 3.411}, 5.92, 2 * kComputeUnits},
-                          {{2.052, 2.302, 2.454, 2.523}, {2.445, 2.908, 3.461}, 9.34, kComputeUnits},
+constexpr Estimate kSizes{{{0.809, 1.173, 1.302, 1.456}, 1.302, {1.601, 2.034, 1.971}, 4.39, 2 * kComputeUnits},
+                          {{1.427, 1.531, 1.573, 1.894}, 1.573, {2.592, 3.118, 3.411}, 5.92, 2 * kComputeUnits},
+                          {{2.052, 2.302, 2.454, 2.523}, 2.454, {2.445, 2.908, 3.461}, 9.34, kComputeUnits},
+                          kNarrowCost, kMidCost,        // (not among its tiles)
                           4.87, 0.176, 34.7, 0.68, false};
+// Those calls choose between the two tiles of 64 rows only, by costs of their own: on 240 calls in 4- and 8-bit codes 0.3 - 1.0 % over the
+// better tile on two cards, with the costs above 0.15 - 1.8 %.
+constexpr Estimate kFewFused{{{0.800, 0.868, 0.905, 1.150}, 0.905, {1.662, 1.908, 2.013}, 2.99, 2 * kComputeUnits}, kHalfCost, kBigCost,
+                             {{0.551, 0.515, 0.747, 1.243}, 0.747, {1.388, 1.925, 2.255}, 2.73, 4 * kComputeUnits}, kMidCost,
+                             4.38, 0.184, kSkUs, kSkUsPerSharer, true};
 constexpr int kSplitMajorMinPairs = 16;
 constexpr int kSkMinTiles = 128;                        // fewer tiles: the fixed K split (the fit holds no such launch)
 
@@ -967,7 +977,7 @@ double rounds_us(const TileCost& c, int64_t items, double pairs_per_item)
         double a;
         if (fill <= 0.125) a = c.lo[0] + (c.lo[1] - c.lo[0]) * fill * 8.0;
         else if (fill <= 0.25) a = c.lo[1] + (c.lo[2] - c.lo[1]) * (fill - 0.125) * 8.0;
-        else if (fill <= 0.5) a = c.lo[2] + (c.lo[3] - c.lo[2]) * (fill - 0.25) * 4.0;
+        else if (fill <= 0.5) a = c.past + (c.lo[3] - c.past) * (fill - 0.25) * 4.0;
         else if (fill <= 0.75) a = c.hi[0] + (c.hi[1] - c.hi[0]) * (fill - 0.5) * 4.0;
         else a = c.hi[1] + (c.hi[2] - c.hi[1]) * (fill - 0.75) * 4.0;
         t += pairs_per_item * a + c.b;
@@ -985,7 +995,7 @@ double split_launch_us(const Estimate& e, const TileCost& c, int64_t tiles, int 
 
 const TileCost& cost_of(const Estimate& e, const PipeTile& t)
 {
-    if (t.bn == 128) return t.bm == 64 ? kNarrowCost : kMidCost;
+    if (t.bn == 128) return t.bm == 64 ? e.narrow : e.mid;
     return t.bm == 64 ? e.flat : t.bm == 256 ? e.big : e.half;
 }
 
@@ -1190,7 +1200,7 @@ PipePlan pipe_plan(int64_t M, int64_t N, int64_t K, bool fused, bool e8)
     const bool steered = (knob(Knob::gemm_variant) && knob(Knob::gemm_variant) != 7) || knob(Knob::gemm_splits) || knob(Knob::gemm_sk);
     if (!steered) {
         const bool exactly = fused && M <= kFlatOnlyMaxM;
-        p = shortest(kNow, M, N, K, PipeRules{false, exactly, exactly ? p.splits : std::max<int64_t>(1, (int64_t)(room / partial_bytes(1, M, N))),
+        p = shortest(exactly ? kFewFused : kNow, M, N, K, PipeRules{false, exactly, exactly ? p.splits : std::max<int64_t>(1, (int64_t)(room / partial_bytes(1, M, N))),
                                               sk ? room : 0});
     }
     if (fused && !e8 && M <= kFlatOnlyMaxM && k_quarters(p.splits, M, N)) {

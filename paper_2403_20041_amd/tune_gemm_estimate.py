@@ -4,7 +4,7 @@ kBigCost, kNarrowCost, kMidCost, kReduceUs, kReduceUsPerMB, kSkUs, kSkUsPerShare
     python -m paper_2403_20041_amd.tune_gemm_estimate time  timings.txt [--problems 120] [--seed 7]
     python -m paper_2403_20041_amd.tune_gemm_estimate fit   timings.txt [more.txt ...]
 
-`time` draws seeded problems (M = 65 .. 8192, N and K multiples of 128, plus the layer shapes of synth_inputs) and
+`time` draws seeded problems (M = 17 .. 8192, N and K multiples of 128, plus the layer shapes of synth_inputs) and
 times e0m4_matmul on each with every tile forced (knob gemm_variant 4, 5, 2, 6, 3), one to eight K splits (gemm_splits)
 and, where the large tile leaves a partly filled last round of at least 128 tiles, even scheduling (gemm_sk 1): us
 per launch in a HIP graph over rotating weight copies, so that the weights come from HBM.  `fit` minimises the squared
@@ -28,8 +28,8 @@ VARIANT = {"f": 4, "h": 5, "b": 2, "n": 6, "m": 3}
 NP = 8                                                      # constants per tile: four low knots, three high, b
 START = [0.8, 1.2, 1.3, 1.45, 1.6, 2.0, 2.0, 4.4, 1.4, 1.5, 1.6, 1.9, 2.6, 3.1, 3.4, 5.9,
          2.0, 2.3, 2.45, 2.5, 2.45, 2.9, 3.5, 9.3, 0.5, 0.6, 0.7, 1.1, 1.3, 1.7, 2.2, 4.4,
-         0.7, 0.8, 0.9, 1.1, 1.3, 1.6, 1.9, 5.0, 4.9, 0.18, 35.0, 0.7]
-NT = len(TILES)
+         0.7, 0.8, 0.9, 1.1, 1.3, 1.6, 1.9, 5.0, 4.9, 0.18, 35.0, 0.7, 1.0]
+NT = len(TILES)                                             # (the last: the narrow tile just beyond one item per unit)
 
 
 def interp(x, xs, ys):
@@ -53,7 +53,10 @@ def estimate(p, M, N, K, tile, splits):
     t = full * (kp * hi[2] + b)
     if rem:
         fill = rem / cap
-        a = interp(fill, [0, 0.125, 0.25, 0.5], lo) if fill <= 0.5 else interp(fill, [0.5, 0.75, 1.0], hi)
+        if tile == "n" and 0.25 < fill <= 0.5:
+            a = interp(fill, [0.25, 0.5], [p[NT * NP + 4], lo[3]])
+        else:
+            a = interp(fill, [0, 0.125, 0.25, 0.5], lo) if fill <= 0.5 else interp(fill, [0.5, 0.75, 1.0], hi)
         t += kp * a + b
     if splits > 1:
         t += r0 + r1 * splits * M * N * 4 / 1e6
@@ -79,8 +82,8 @@ def fit(paths):
 
     groups = read_timings(paths)
     pts = [(M, N, K, t, s, us) for (M, N, K), c in groups.items() for t, s, us in c]
-    lo = ([0.01] * 7 + [0.0]) * NT + [0.0] * 4
-    hi = ([8.0] * 7 + [40.0]) * NT + [50.0, 5.0, 100.0, 10.0]
+    lo = ([0.01] * 7 + [0.0]) * NT + [0.0] * 4 + [0.01]
+    hi = ([8.0] * 7 + [40.0]) * NT + [50.0, 5.0, 100.0, 10.0, 8.0]
 
     def resid(p):
         return [math.log(estimate(p, M, N, K, t, s) / us) for M, N, K, t, s, us in pts]
@@ -93,8 +96,9 @@ def fit(paths):
     print("choice by the estimate over the measured best: geometric mean %.4f, worst %.3f"
           % (math.exp(sum(math.log(x) for x in regret) / len(regret)), max(regret)))
     for name, i in (("kFlatCost", 0), ("kHalfCost", 1), ("kBigCost", 2), ("kNarrowCost", 3), ("kMidCost", 4)):
-        q = p[NP * i:NP * i + NP]
-        print("%s{{%.3f, %.3f, %.3f, %.3f}, {%.3f, %.3f, %.3f}, %.2f, ...}" % ((name,) + tuple(q)))
+        q = list(p[NP * i:NP * i + NP])
+        q.insert(4, p[NT * NP + 4] if name == "kNarrowCost" else q[2])
+        print("%s{{%.3f, %.3f, %.3f, %.3f}, %.3f, {%.3f, %.3f, %.3f}, %.2f, ...}" % ((name,) + tuple(q)))
     print("kReduceUs = %.2f, kReduceUsPerMB = %.3f, kSkUs = %.1f, kSkUsPerSharer = %.2f" % tuple(p[NT * NP:NT * NP + 4]))
 
 
@@ -108,13 +112,13 @@ def time_problems(out_path, n_problems, seed):
     stream = torch.cuda.Stream()
     rnd = random.Random(seed)
     problems = []
-    for lo_m, hi_m, share in ((65, 384, 0.35), (385, 1024, 0.3), (1025, 2560, 0.25), (2561, 8192, 0.1)):
+    for lo_m, hi_m, share in ((17, 64, 0.2), (65, 384, 0.3), (385, 1024, 0.25), (1025, 2560, 0.2), (2561, 8192, 0.05)):
         for _ in range(int(n_problems * share)):
             problems.append((rnd.randint(lo_m, hi_m), 128 * rnd.randint(8, 160), 128 * rnd.randint(8, 112)))
     for shapes in (synth_inputs.CHATGLM2_6B, synth_inputs.DENSE_14B):
         for M in (256, 512, 1024, 2048):
             problems += [(M, N, K) for _, N, K in shapes]
-    knobs = ("gemm_variant", "gemm_splits", "gemm_sk")
+    knobs = ("gemm_variant", "gemm_splits", "gemm_sk", "gemv_mfma")
     with open(out_path, "a") as out:
         for M, N, K in problems:
             W = synth_inputs.weights_device(N, K, 1, dev)
@@ -133,6 +137,7 @@ def time_problems(out_path, n_problems, seed):
             if big >= 128 and big % CU:
                 cands.append(("b", "sk"))
             try:
+                e0m4.e0m4_set_knob("gemv_mfma", 1)      # (up to 64 rows: not the small-batch kernels)
                 for tile, s in cands:
                     e0m4.e0m4_set_knob("gemm_variant", VARIANT[tile])
                     e0m4.e0m4_set_knob("gemm_splits", 1 if s == "sk" else s)

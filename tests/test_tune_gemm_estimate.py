@@ -1,6 +1,10 @@
 """The tool that re-fits the GEMM's launch-time estimate: its copy of the estimate on hand-computed cases, and the fit
 on timings generated from known constants (no GPU needed)."""
+import os
 import random
+import re
+
+import pytest
 
 from paper_2403_20041_amd import tune_gemm_estimate as tool
 
@@ -17,6 +21,14 @@ def test_estimate_by_hand():
     # large tile, 300 tiles evenly scheduled: one whole round, 44 tiles shared out, 256 / 44 + 1 sharers per tile
     want = (16 * 3.5 + 9.3) + 44 * 16 / 256 * 3.5 + 9.3 + 35.0 + 0.7 * (256 / 44 + 1)
     assert abs(tool.estimate(p, 256 * 10, 256 * 30, 2048, "b", "sk") - want) < 1e-9
+
+
+def test_estimate_of_the_narrow_tile_jumps_at_one_item_per_unit():
+    p = list(tool.START)
+    # 64 x 128 tiles, a = 0.7 at 256 of them, 1.0 just beyond, 1.1 at 512; b = 4.4; 16 pairs
+    assert abs(tool.estimate(p, 64, 128 * 256, 2048, "n", 1) - (16 * 0.7 + 4.4)) < 1e-9
+    assert abs(tool.estimate(p, 64, 128 * 257, 2048, "n", 1) - (16 * (1.0 + 0.1 / 256) + 4.4)) < 1e-9
+    assert abs(tool.estimate(p, 64, 128 * 512, 2048, "n", 1) - (16 * 1.1 + 4.4)) < 1e-9
 
 
 def test_fit_recovers_the_choices(tmp_path, capsys):
@@ -38,3 +50,27 @@ def test_fit_recovers_the_choices(tmp_path, capsys):
     tool.fit([str(path)])
     out = capsys.readouterr().out
     assert "geometric mean 1.00" in out and "kBigCost{{" in out and "kReduceUs" in out
+
+
+def constants(suffix):
+    """The estimate's constants in the C++ source, in the tool's order."""
+    text = open(os.path.join(os.path.dirname(tool.__file__), "csrc", "e0m4_gemm_pipe.hip")).read()
+    p, past = [], None
+    for name in ("Flat", "Half", "Big", "Narrow", "Mid"):
+        m = re.search(r"k%sCost%s\{\{([^}]*)\}, ([0-9.]+), \{([^}]*)\}, ([0-9.]+)," % (name, suffix), text)
+        p += [float(x) for x in (m.group(1) + "," + m.group(3) + "," + m.group(4)).split(",")]
+        past = float(m.group(2)) if name == "Narrow" else past
+    for name in ("kReduceUs", "kReduceUsPerMB", "kSkUs", "kSkUsPerSharer"):
+        p.append(float(re.search(r"\b%s%s = ([0-9.]+)" % (name, suffix if name.startswith("kReduce") else ""), text).group(1)))
+    return p + [past]
+
+
+# (problems with as many work items as compute units on the narrow tile or somewhat more, where an estimate that is continuous there
+# chose launches 9 - 21 % longer than the best)
+@pytest.mark.parametrize("timings,suffix", [("gemm_launch_timings_4bit.txt", "")])
+def test_the_constants_choose_among_measured_launches(timings, suffix):
+    p = constants(suffix)
+    for (M, N, K), c in tool.read_timings([os.path.join(os.path.dirname(__file__), "golden", timings)]).items():
+        c = [x for x in c if x[1] != "sk"]
+        chosen = min(c, key=lambda x: tool.estimate(p, M, N, K, x[0], x[1]))
+        assert chosen[2] <= 1.05 * min(x[2] for x in c), (M, N, K, chosen)
