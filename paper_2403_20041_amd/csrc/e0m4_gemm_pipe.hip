@@ -945,12 +945,23 @@ constexpr TileCost kNarrowCost{{0.505, 0.549, 0.628, 1.162}, 0.847, {1.393, 1.85
 constexpr TileCost kMidCost{{0.683, 0.726, 0.761, 0.988}, 0.761, {1.391, 1.660, 1.840}, 4.29, 2 * kComputeUnits};
 constexpr double kReduceUs = 4.23, kReduceUsPerMB = 0.211;      // reduction kernel of a K split
 constexpr double kSkUs = 39.1, kSkUsPerSharer = 0.86;           // even scheduling: slabs, and the serial part per sharer
+// 8-bit codes, twice the registers per slice and twice the bytes: 128-row tiles request codes two slices ahead instead of four, and those of
+// 128 columns, a wavefront to a SIMD, wait for them.  A fit of their own to 13181 timings of 622 problems (rms 6.7 %): the choice
+// costs 1.0 - 2.4 % over the best, by the costs of 4-bit codes 2.4 - 4.2 % (gated 192 x 11712 x 7808, 184 tiles of 128 x 128, 79.8 us, on
+// 64 x 256 tiles 61.9).
+constexpr TileCost kFlatCost8{{0.789, 0.877, 0.917, 1.203}, 0.917, {1.773, 2.006, 2.045}, 4.88, 2 * kComputeUnits};
+constexpr TileCost kHalfCost8{{1.266, 1.351, 1.392, 1.898}, 1.392, {2.739, 3.236, 3.436}, 5.85, 2 * kComputeUnits};
+constexpr TileCost kBigCost8{{2.225, 2.287, 2.356, 2.515}, 2.356, {2.499, 2.965, 3.553}, 5.99, kComputeUnits};
+constexpr TileCost kNarrowCost8{{0.518, 0.598, 0.698, 1.326}, 1.053, {1.570, 2.062, 2.250}, 3.75, 4 * kComputeUnits};
+constexpr TileCost kMidCost8{{0.988, 1.134, 1.163, 1.244}, 1.163, {1.487, 1.892, 1.981}, 4.21, 2 * kComputeUnits};
+constexpr double kReduceUs8 = 4.42, kReduceUsPerMB8 = 0.245;
 struct Estimate {
     TileCost flat, half, big, narrow, mid;
     double reduce_us, reduce_us_per_mb, sk_us, sk_us_per_sharer;
     bool all_tiles;                                     // with the tiles of 128 columns, and a short last row tile counted as such
 };
 constexpr Estimate kNow{kFlatCost, kHalfCost, kBigCost, kNarrowCost, kMidCost, kReduceUs, kReduceUsPerMB, kSkUs, kSkUsPerSharer, true};
+constexpr Estimate kNow8{kFlatCost8, kHalfCost8, kBigCost8, kNarrowCost8, kMidCost8, kReduceUs8, kReduceUsPerMB8, kSkUs, kSkUsPerSharer, true};
 // The workspace that callers are asked for, and with it the most K splits that a launch may have, come from an estimate with
 // constants that stay as they are, whatever becomes of the kernel: a size once asked for is enough for good.  Fused calls of up to
 // 64 rows have exactly its number of splits: with another one their sums, and the residual streams that they feed, would be
@@ -1200,7 +1211,7 @@ PipePlan pipe_plan(int64_t M, int64_t N, int64_t K, bool fused, bool e8)
     const bool steered = (knob(Knob::gemm_variant) && knob(Knob::gemm_variant) != 7) || knob(Knob::gemm_splits) || knob(Knob::gemm_sk);
     if (!steered) {
         const bool exactly = fused && M <= kFlatOnlyMaxM;
-        p = shortest(exactly ? kFewFused : kNow, M, N, K, PipeRules{false, exactly, exactly ? p.splits : std::max<int64_t>(1, (int64_t)(room / partial_bytes(1, M, N))),
+        p = shortest(exactly ? kFewFused : e8 ? kNow8 : kNow, M, N, K, PipeRules{false, exactly, exactly ? p.splits : std::max<int64_t>(1, (int64_t)(room / partial_bytes(1, M, N))),
                                               sk ? room : 0});
     }
     if (fused && !e8 && M <= kFlatOnlyMaxM && k_quarters(p.splits, M, N)) {

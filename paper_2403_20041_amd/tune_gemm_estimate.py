@@ -1,13 +1,14 @@
 """Re-fit the constants of the prefill GEMM's launch-time estimate (csrc/e0m4_gemm_pipe.hip: kFlatCost, kHalfCost,
 kBigCost, kNarrowCost, kMidCost, kReduceUs, kReduceUsPerMB, kSkUs, kSkUsPerSharer) on the GPU at hand.
 
-    python -m paper_2403_20041_amd.tune_gemm_estimate time  timings.txt [--problems 120] [--seed 7]
+    python -m paper_2403_20041_amd.tune_gemm_estimate time  timings.txt [--format e0m8] [--problems 120] [--seed 7]
     python -m paper_2403_20041_amd.tune_gemm_estimate fit   timings.txt [more.txt ...]
 
 `time` draws seeded problems (M = 17 .. 8192, N and K multiples of 128, plus the layer shapes of synth_inputs) and
 times e0m4_matmul on each with every tile forced (knob gemm_variant 4, 5, 2, 6, 3), one to eight K splits (gemm_splits)
 and, where the large tile leaves a partly filled last round of at least 128 tiles, even scheduling (gemm_sk 1): us
-per launch in a HIP graph over rotating weight copies, so that the weights come from HBM.  `fit` minimises the squared
+per launch in a HIP graph over rotating weight copies, so that the weights come from HBM.  With --format e0m8 it times
+e0m8_matmul, which has no even scheduling: the fit then gives the costs of 8-bit codes (names that end in 8).  `fit` minimises the squared
 logarithm of estimate / measurement over all timings, prints the constants in the order of the C++ initialisers and
 says how much slower than the measured best the estimate's choice is (geometric mean over the problems).  The knobs
 are diagnostic and belong to the calling thread; nothing here changes the library's defaults: paste the constants
@@ -102,7 +103,7 @@ def fit(paths):
     print("kReduceUs = %.2f, kReduceUsPerMB = %.3f, kSkUs = %.1f, kSkUsPerSharer = %.2f" % tuple(p[NT * NP:NT * NP + 4]))
 
 
-def time_problems(out_path, n_problems, seed):
+def time_problems(out_path, n_problems, seed, fmt="e0m4"):
     import torch
 
     import paper_2403_20041_amd as e0m4
@@ -111,6 +112,9 @@ def time_problems(out_path, n_problems, seed):
     dev = torch.device("cuda:0")
     stream = torch.cuda.Stream()
     rnd = random.Random(seed)
+    quantize, matmul, workspace_bytes = (
+        (e0m4.e0m8_quantize, lambda x, c, N, K, **kw: e0m4.e0m8_matmul(x, c, N, K, 128, **kw), e0m4.e0m8_workspace_bytes) if fmt == "e0m8"
+        else (e0m4.e0m4_quantize, lambda x, c, N, K, **kw: e0m4.e0m4_matmul(x, c, None, None, N, K, 128, **kw), e0m4.e0m4_workspace_bytes))
     problems = []
     for lo_m, hi_m, share in ((17, 64, 0.2), (65, 384, 0.3), (385, 1024, 0.25), (1025, 2560, 0.2), (2561, 8192, 0.05)):
         for _ in range(int(n_problems * share)):
@@ -122,7 +126,7 @@ def time_problems(out_path, n_problems, seed):
     with open(out_path, "a") as out:
         for M, N, K in problems:
             W = synth_inputs.weights_device(N, K, 1, dev)
-            first = e0m4.e0m4_quantize(W, 128)[0]
+            first = quantize(W, 128)[0]
             del W
             copies = [first] + [first.clone() for _ in range(max(2, min(40, int(4e8 // first.numel()))) - 1)]
             x = synth_inputs.activations_device(M, K, 2, dev)
@@ -134,7 +138,7 @@ def time_problems(out_path, n_problems, seed):
                 for s in ((1,) if tiles >= max(CU, cap // 2) else [s for s in (1, 2, 3, 4, 6, 8) if s == 1 or pairs // s >= 4]):
                     cands.append((tile, s))
             big = -(-M // 256) * -(-N // 256)
-            if big >= 128 and big % CU:
+            if big >= 128 and big % CU and fmt == "e0m4":
                 cands.append(("b", "sk"))
             try:
                 e0m4.e0m4_set_knob("gemv_mfma", 1)      # (up to 64 rows: not the small-batch kernels)
@@ -142,15 +146,15 @@ def time_problems(out_path, n_problems, seed):
                     e0m4.e0m4_set_knob("gemm_variant", VARIANT[tile])
                     e0m4.e0m4_set_knob("gemm_splits", 1 if s == "sk" else s)
                     e0m4.e0m4_set_knob("gemm_sk", 1 if s == "sk" else 2)
-                    ws = torch.empty(max(16, e0m4.e0m4_workspace_bytes(M, N, K, 128)), dtype=torch.uint8, device=dev)
+                    ws = torch.empty(max(16, workspace_bytes(M, N, K, 128)), dtype=torch.uint8, device=dev)
                     with torch.cuda.stream(stream):
                         for c in copies[:2]:
-                            e0m4.e0m4_matmul(x, c, None, None, N, K, 128, out=y, workspace=ws, stream=stream)
+                            matmul(x, c, N, K, out=y, workspace=ws, stream=stream)
                         stream.synchronize()
                         g = torch.cuda.CUDAGraph()
                         with torch.cuda.graph(g, stream=stream):
                             for c in copies:
-                                e0m4.e0m4_matmul(x, c, None, None, N, K, 128, out=y, workspace=ws, stream=stream)
+                                matmul(x, c, N, K, out=y, workspace=ws, stream=stream)
                         best = None
                         for _ in range(3):
                             g.replay()
@@ -179,9 +183,10 @@ def main():
     ap.add_argument("files", nargs="+")
     ap.add_argument("--problems", type=int, default=120)
     ap.add_argument("--seed", type=int, default=7)
+    ap.add_argument("--format", choices=("e0m4", "e0m8"), default="e0m4")
     args = ap.parse_args()
     if args.mode == "time":
-        time_problems(args.files[0], args.problems, args.seed)
+        time_problems(args.files[0], args.problems, args.seed, args.format)
     else:
         fit(args.files)
 
