@@ -963,9 +963,9 @@ struct Estimate {
 constexpr Estimate kNow{kFlatCost, kHalfCost, kBigCost, kNarrowCost, kMidCost, kReduceUs, kReduceUsPerMB, kSkUs, kSkUsPerSharer, true};
 constexpr Estimate kNow8{kFlatCost8, kHalfCost8, kBigCost8, kNarrowCost8, kMidCost8, kReduceUs8, kReduceUsPerMB8, kSkUs, kSkUsPerSharer, true};
 // The workspace that callers are asked for, and with it the most K splits that a launch may have, come from an estimate with
-// constants that stay as they are, whatever becomes of the kernel: a size once asked for is enough for good.  Fused calls of up to
-// 64 rows have exactly its number of splits: with another one their sums, and the residual streams that they feed, would be
-// rounded otherwise.
+// constants that stay as they are, whatever becomes of the kernel: a size once asked for is enough for good.  Calls of up to 64 rows
+// with a residual or the gated product have exactly its number of splits: with another one their sums, and the residual streams that
+// they feed, would be rounded otherwise.
 constexpr Estimate kSizes{{{0.809, 1.173, 1.302, 1.456}, 1.302, {1.601, 2.034, 1.971}, 4.39, 2 * kComputeUnits},
                           {{1.427, 1.531, 1.573, 1.894}, 1.573, {2.592, 3.118, 3.411}, 5.92, 2 * kComputeUnits},
                           {{2.052, 2.302, 2.454, 2.523}, 2.454, {2.445, 2.908, 3.461}, 9.34, kComputeUnits},
@@ -1203,14 +1203,14 @@ size_t pipe_room(int64_t M, int64_t N, int64_t K, bool sk, PipePlan* plan)
     return p.bytes(M, N);
 }
 
-PipePlan pipe_plan(int64_t M, int64_t N, int64_t K, bool fused, bool e8)
+PipePlan pipe_plan(const Fusion& f, int64_t M, int64_t N, int64_t K, bool fused, bool e8)
 {
     PipePlan p;
     const bool sk = !fused && !e8;
     const size_t room = pipe_room(M, N, K, sk, &p);
     const bool steered = (knob(Knob::gemm_variant) && knob(Knob::gemm_variant) != 7) || knob(Knob::gemm_splits) || knob(Knob::gemm_sk);
     if (!steered) {
-        const bool exactly = fused && M <= kFlatOnlyMaxM;
+        const bool exactly = fused && M <= kFlatOnlyMaxM && (f.residual || f.swiglu);
         p = shortest(exactly ? kFewFused : e8 ? kNow8 : kNow, M, N, K, PipeRules{false, exactly, exactly ? p.splits : std::max<int64_t>(1, (int64_t)(room / partial_bytes(1, M, N))),
                                               sk ? room : 0});
     }
@@ -1364,7 +1364,7 @@ template <int G, bool FUSED>
 int launch_pipe_tile(const half_t* x, int64_t M, const uint4* c, int64_t N, int64_t K, half_t* y, void* workspace,
                      size_t workspace_bytes, hipStream_t stream, const Fusion& f)
 {
-    return launch_pipe_as<G, FUSED>(pipe_plan(M, N, K, FUSED, false), x, M, c, N, K, y, workspace, workspace_bytes, stream, f);
+    return launch_pipe_as<G, FUSED>(pipe_plan(f, M, N, K, FUSED, false), x, M, c, N, K, y, workspace, workspace_bytes, stream, f);
 }
 
 }  // namespace
@@ -1376,7 +1376,7 @@ int launch_gemm_pipe8(const void* X, int64_t M, const void* packed, int64_t N, i
     const half_t* x = static_cast<const half_t*>(X);
     const uint4* c = static_cast<const uint4*>(packed);
     half_t* y = static_cast<half_t*>(Y);
-    return launch_pipe_as<128, false, true>(pipe_plan(M, N, K, false, true), x, M, c, N, K, y, workspace, workspace_bytes, stream,
+    return launch_pipe_as<128, false, true>(pipe_plan(Fusion{}, M, N, K, false, true), x, M, c, N, K, y, workspace, workspace_bytes, stream,
                                             Fusion{});
 }
 
@@ -1387,7 +1387,7 @@ int launch_gemm_pipe8_fused(const Fusion& f, const void* X, int64_t M, const voi
     const uint4* c = static_cast<const uint4*>(packed);
     half_t* y = static_cast<half_t*>(Y);
     if (f.swiglu && (N % (2 * kBlockRows) != 0 || gated_half_bytes(N, 2 * K, 128) > kMaxHalfBytes)) return E0M4_ERR_SHAPE;
-    return launch_pipe_as<128, true, true>(pipe_plan(M, N, K, true, true), x, M, c, N, K, y, workspace, workspace_bytes, stream, f);
+    return launch_pipe_as<128, true, true>(pipe_plan(f, M, N, K, true, true), x, M, c, N, K, y, workspace, workspace_bytes, stream, f);
 }
 
 int launch_gemm_pipe(const void* X, int64_t M, const void* packed, int64_t N, int64_t K, int group, void* Y,

@@ -90,3 +90,17 @@ def test_8bit_codes_two_slices_ahead(e0m4, oracle, N, K, splits, swiglu, res):
     for M in (19, 64):
         with_knobs(e0m4, lambda: run_fused(e0m4, oracle, M, N, K, 128, seed=1460 + M, norm=False, swiglu=swiglu, res=res, outliers=True, bits=8),
                    gemm_variant=4, gemm_splits=splits, gemv_mfma=1)
+
+
+# (large weights whose work items would be more than the compute units in splits: whole 64 x 128 tiles, whose sums are in another order)
+@pytest.mark.parametrize("bits,M,N,K,splits", [(8, 63, 27456, 2816, 4), (4, 56, 26112, 2560, 5)])
+def test_calls_with_an_rms_norm_alone_choose_their_splits(e0m4, bits, M, N, K, splits):
+    quantize, fused = (e0m4.e0m8_quantize, e0m4.e0m8_matmul_fused) if bits == 8 else (e0m4.e0m4_quantize, e0m4.e0m4_matmul_fused)
+    codes = quantize(to_dev(synth_inputs.weights(192, K, seed=1470)).repeat(N // 192, 1), 128)[0]
+    X, gamma = to_dev(synth_inputs.activations(M, K, seed=1471, outlier_frac=0.01)), to_dev(synth_inputs.norm_weight(K, 1472))
+
+    def run(**knobs):
+        return with_knobs(e0m4, lambda: fused(X, codes, N, K, 128, rms_gamma=gamma, rms_eps=1e-5), **knobs)
+
+    by_default, whole, split = run(), run(gemm_variant=6, gemm_splits=1), run(gemm_variant=4, gemm_splits=splits)
+    assert torch.equal(by_default, whole) and not torch.equal(by_default, split)
