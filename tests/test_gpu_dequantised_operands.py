@@ -145,3 +145,33 @@ def test_wide_weights_go_where_they_are_faster(e0m4, fmt, M, N, K, norm, here):
     by_default, small_batch, gemm = run(0), run(4), run(5)
     assert not torch.equal(small_batch, gemm)           # (they add in different orders)
     assert torch.equal(by_default, small_batch if here else gemm)
+
+
+# rows of one to eight k blocks: one, two and four groups of wavefronts, the last with fewer row blocks than the others or none
+@pytest.mark.parametrize("fmt,K", [("e0m4", 96), ("e0m4", 256), ("e0m4", 512), ("e0m4", 640), ("bf16", 128), ("bf16", 384), ("bf16", 512),
+                                   ("e0m8", 64), ("e0m8", 128), ("e0m8", 256), ("e0m8", 320), ("exact", 128), ("exact", 256), ("exact", 512)])
+@pytest.mark.parametrize("M", [5, 17, 49, 64])
+def test_short_rows(e0m4, oracle, fmt, K, M):
+    G = 32 if K % 64 else 64 if fmt != "exact" else 128
+    if fmt == "exact" and M <= 16:
+        pytest.skip("17 rows and more")
+    for N, workgroups in ((16 * 9 - 3, 9), (333, 7), (16 * 25, 5), (16 * 13, 1)):
+        e0m4.e0m4_set_knob("gemv_mfma", 7 if fmt == "exact" else 4)
+        e0m4.e0m4_set_knob("gemv_workgroups", workgroups)
+        try:
+            if fmt == "bf16":
+                codes, What, _ = assert_bf16_quantize_exact(e0m4, oracle, synth_inputs.weights_bf16(N, K, seed=5010 + K), G)
+                X = synth_inputs.activations_bf16(M, K, seed=5020 + M)
+                check_bf16_matmul(oracle, e0m4.e0m4_bf16_matmul(bf_dev(X), codes, N, K, G), *oracle.bf16_matmul(X, What), "bf16")
+                continue
+            X, W = synth_inputs.activations(M, K, seed=5020 + M, outlier_frac=0.01), synth_inputs.weights(N, K, seed=5010 + K)
+            if fmt == "e0m8":
+                codes, What = test_gpu_e0m8.assert_quantize_exact(e0m4, oracle, W, G)
+                Y = e0m4.e0m8_matmul(to_dev(X), codes, N, K, G)
+            else:
+                (codes, _, _), What = assert_quantize_exact(e0m4, oracle, W, G)
+                Y = e0m4.e0m4_matmul(to_dev(X), codes, None, None, N, K, G)
+            check_matmul(Y, *oracle.matmul(X, What), fmt)
+        finally:
+            e0m4.e0m4_set_knob("gemv_mfma", 0)
+            e0m4.e0m4_set_knob("gemv_workgroups", 0)
