@@ -284,7 +284,7 @@ static FusedPath fused_path(const Fusion& f, int64_t M, int64_t N, int64_t K, in
         TilesPlan p;
         const bool can = f.any() && group == 128 && (k == 0 || k == 7) && gemv_tiles_plan(f, M, row_chunks(M), N, K, &p) &&
                          gemv_tiles_supported(p, M, K);
-        if (!can || (k == 0 && !gemv_tiles_pays(f, p, row_chunks(M)))) return kFusedChunks;
+        if (!can || (k == 0 && !gemv_tiles_pays(f, p, M, row_chunks(M)))) return kFusedChunks;
         if (tiles) *tiles = p;
         return kFusedTiles;
     }

@@ -257,15 +257,18 @@ bool gemv_tiles_supported(const TilesPlan& p, int64_t M, int64_t K)
     return p.waves == kTileWaves && p.slots <= max_slots((int)((M + 15) / 16));
 }
 
-// Where it is faster than chunks, on 360 calls of 128 to 20 000 columns: 1.15 - 2.4 where chunks need more than a compute unit each.
-// Else, with an rms-norm, which they do in every workgroup: two chunks 1.03 - 1.57 and, without the gated product, three 1.0 - 1.3, but
+// Where it is faster than chunks, on 800 calls of 64 to 20 000 columns: 1.15 - 2.4 where chunks need more than a compute unit each.
+// Else, with an rms-norm, which they do in every workgroup: two chunks 1.03 - 1.6 and, without the gated product, three 1.0 - 1.3, but
 // three with eight work items to a row, of which each of the chunk kernel's wavefronts has one, 0.93 - 0.96 (192 x 3968 at M = 36 9.1 and 9.7
-// us), four 0.89 - 1.02 (384 x 2816 at M = 51 9.8 and 10.6 us) and three with the gated product 0.86 - 1.04; with a residual alone 0.66 -
-// 1.03 (960 x 2176 at M = 37 5.5 and 6.2).
-bool gemv_tiles_pays(const Fusion& f, const TilesPlan& p, int chunks)
+// us), four 0.89 - 1.02 (384 x 2816 at M = 51 9.8 and 10.6 us) and three with the gated product 0.86 - 1.04.  With the gated product
+// alone two chunks 1.0 - 1.22, but 0.83 - 0.99 with eight work items (2944 x 3968 at M = 22 7.2 and 7.9), 0.94 - 1.02 on rows of one or
+// two, 0.96 - 0.98 on rows of four in sixteen workgroups, and 0.88 - 1.09 at 17 to 20 rows of up to seven (512 x 3072 at M = 17 6.1 and 6.9);
+// with a residual alone 0.66 - 1.03 (960 x 2176 at M = 37 5.5 and 6.2).
+bool gemv_tiles_pays(const Fusion& f, const TilesPlan& p, int64_t M, int chunks)
 {
     if (p.grid * chunks > 256) return true;
-    return (f.gamma || f.swiglu) && (chunks == 2 || (chunks == 3 && !f.swiglu && p.items != kTileWaves));
+    if (f.gamma) return chunks == 2 || (chunks == 3 && !f.swiglu && p.items != kTileWaves);
+    return f.swiglu && chunks == 2 && (p.items > kTileWaves || (p.items >= 4 && p.items < kTileWaves && M > 20 && (p.items > 4 || p.grid > 16)));
 }
 
 int launch_gemv_tiles(const Fusion& f, const TilesPlan& p, const void* X, int64_t M, const void* packed, int64_t N, int64_t K, void* Y,

@@ -112,7 +112,7 @@ struct TilesPlan {
 };
 bool gemv_tiles_plan(const Fusion& f, int64_t M, int chunks, int64_t N, int64_t K, TilesPlan* plan);
 bool gemv_tiles_supported(const TilesPlan& p, int64_t M, int64_t K);
-bool gemv_tiles_pays(const Fusion& f, const TilesPlan& p, int chunks);
+bool gemv_tiles_pays(const Fusion& f, const TilesPlan& p, int64_t M, int chunks);
 int launch_gemv_tiles(const Fusion& f, const TilesPlan& p, const void* X, int64_t M, const void* packed, int64_t N, int64_t K, void* Y,
                       hipStream_t stream);
 // Small-batch path with the weight operand dequantised in registers: 2 <= M <= 128, any group (e0m4_gemv_dq.hip).
