@@ -476,16 +476,18 @@ bool gemv_dq_free(int64_t M, int64_t N, int64_t K, int group, DqFormat format)
     if (M > 16) return (double)N * (double)K <= (format == kDqFormatE8 ? 1e8 : 7e7) && (M <= 48 || (K >= 256 && K <= 9216));
     return format == kDqFormatFp16 && group != 128;
 }
-// fp16, on 840 calls with 640 to 260 000 columns and 256 to 14 000 weights a row, by the row blocks that a compute unit has: every
+// fp16, on 1130 calls with 640 to 260 000 columns and 256 to 14 000 weights a row, by the row blocks that a compute unit has: every
 // workgroup reads all of X, and beyond sixteen row blocks of its own the workgroups come in rounds.  The GEMM's time over this kernel's:
-//   4-bit codes.  17 to 32 rows: 1.1 - 1.8 up to six row blocks, 1.0 - 1.3 up to twelve, up to 24 on rows of 1536 weights and more 0.97 -
-//   1.15; on shorter ones 0.79 - 0.94 (65984 x 512 at M = 22 10.8 and 13.5 us), beyond 24 0.6 - 0.92 (201088 x 384 at M = 22 0.62).
+//   4-bit codes.  17 to 32 rows: 1.1 - 1.8 up to six row blocks, 1.0 - 1.3 up to twelve, up to 24 on rows of 1024 weights and more 0.97 -
+//   1.2; on shorter ones 0.79 - 0.94 (65984 x 512 at M = 22 10.8 and 13.5 us), beyond 24 0.6 - 0.92 (201088 x 384 at M = 22 0.62).
 //   33 to 48 rows: 1.0 - 2.0 up to six, 0.84 - 0.93 with seven and eight (the last of two groups of wavefronts is half empty), 1.09 - 1.14
-//   with nine and ten, beyond 0.6 - 0.96 (209792 x 1152 at M = 38 48.5 and 71.3).  49 to 64 rows: 1.0 - 1.4 up to four, with
-//   three and four on rows of 640 weights and fewer 0.85 - 0.95; 0.75 - 1.25 with five and six (where the GEMM's tiles are just more than the compute units it is the
-//   slower one), beyond 0.55 - 1.0 (59328 x 1280 at M = 64 19.3 and 25.6).  The longest rows, of which a workgroup reads all of X: 0.9 - 1.0.
-//   8-bit codes.  17 to 32 rows: 0.96 - 1.5 up to thirteen, beyond 0.82 - 1.03; 33 to 48: 1.0 - 1.3 up to four, and up to ten on rows of
-//   1024 weights and more, else 0.7 - 0.96; 49 to 64: 1.0 - 1.4 up to four, beyond 0.7 - 1.1 (78720 x 1280 at M = 53 31.2 and 40.9).
+//   with nine and ten, beyond 0.6 - 0.96 (209792 x 1152 at M = 38 48.5 and 71.3).  49 to 64 rows: 1.0 - 1.4 up to four, with three and
+//   four on rows of 640 weights and fewer 0.85 - 0.95; 0.75 - 1.25 with five and six (where the GEMM's tiles are just more than the
+//   compute units it is the slower one), beyond 0.55 - 1.0 (59328 x 1280 at M = 64 19.3 and 25.6).  The longest rows, of which a workgroup
+//   reads all of X: 0.9 - 1.0.
+//   8-bit codes.  17 to 32 rows: 0.96 - 1.5 up to twenty, on rows of 384 weights beyond thirteen and on all beyond twenty 0.82 - 1.05; 33 to
+//   48: 1.0 - 1.3 up to four, and up to ten on rows of 1024 weights and more, else 0.7 - 0.96; 49 to 64: 1.0 - 1.4 up to four, beyond 0.7 -
+//   1.1 (78720 x 1280 at M = 53 31.2 and 40.9).
 //   Up to sixteen rows: groups of 32 and 64, up to 60 row blocks (1.04 - 1.9).
 bool gemv_dq_beats_gemm(int64_t M, int64_t N, int64_t K, int group, DqFormat format)
 {
@@ -494,11 +496,11 @@ bool gemv_dq_beats_gemm(int64_t M, int64_t N, int64_t K, int group, DqFormat for
     if (M <= 16) return format == kDqFormatFp16 && group != 128;
     const int64_t rb = (row_blocks(N) + kTargetWorkgroups - 1) / kTargetWorkgroups;
     if (format == kDqFormatE8) {
-        if (M <= 32) return rb <= 13;
+        if (M <= 32) return rb <= 13 || (rb <= 20 && K >= 512);
         if (M <= 48) return (rb <= 4 || (rb <= 10 && K >= 1024)) && K <= 8192;
         return rb <= 4 && K >= 256 && K <= 6144;
     }
-    if (M <= 32) return rb <= 6 || (rb <= 12 && K >= 768) || (rb <= 24 && K >= 1536);
+    if (M <= 32) return rb <= 6 || (rb <= 12 && K >= 768) || (rb <= 24 && K >= 1024);
     if (M <= 48) return (rb <= 6 || (rb >= 9 && rb <= 10 && K >= 512)) && K <= 12800;
     return rb <= 4 && K >= (rb <= 2 ? 256 : 768) && K <= 7680;
 }

@@ -121,10 +121,10 @@ def test_most_row_blocks_per_wavefront(e0m4, oracle, fmt, M, K):
 # (wide weights: on either side of the number of row blocks per compute unit up to which this kernel is faster than the GEMM)
 @pytest.mark.parametrize("fmt,M,N,K,norm,here", [
     ("e0m4", 32, 24576, 512, True, True), ("e0m4", 32, 24592, 512, True, False), ("e0m4", 17, 49152, 768, True, True),
-    ("e0m4", 32, 49168, 1408, True, False), ("e0m4", 32, 49168, 1536, False, True), ("e0m4", 24, 98320, 1536, False, False),
+    ("e0m4", 32, 49168, 896, True, False), ("e0m4", 32, 49168, 1536, False, True), ("e0m4", 20, 98304, 1024, True, True), ("e0m4", 24, 98320, 1536, False, False),
     ("e0m4", 48, 24576, 512, True, True), ("e0m4", 33, 24592, 512, True, False), ("e0m4", 48, 40960, 512, True, True),
     ("e0m4", 40, 40976, 2048, False, False), ("e0m4", 64, 16384, 768, True, True), ("e0m4", 64, 16400, 768, True, False),
-    ("e0m8", 32, 53248, 256, True, True), ("e0m8", 32, 53264, 256, True, False), ("e0m8", 40, 16400, 896, True, False),
+    ("e0m8", 32, 53248, 256, True, True), ("e0m8", 32, 53264, 384, True, False), ("e0m8", 32, 53264, 512, True, True), ("e0m8", 17, 81936, 512, True, False), ("e0m8", 40, 16400, 896, True, False),
     ("e0m8", 40, 40960, 1024, True, True), ("e0m8", 40, 40976, 2560, False, False), ("e0m8", 64, 16384, 256, True, True),
     ("e0m8", 64, 16400, 256, True, False)])
 def test_wide_weights_go_where_they_are_faster(e0m4, fmt, M, N, K, norm, here):
