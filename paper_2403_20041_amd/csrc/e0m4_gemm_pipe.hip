@@ -931,34 +931,40 @@ struct PipeTile {
 constexpr PipeTile kFlatTile{64, 256}, kMidTile{128, 128}, kBigTile{256, 256}, kHalfTile{128, 256}, kNarrowTile{64, 128};
 constexpr int kFlatOnlyMaxM = 64;
 
+// The gated product's epilogue takes longer than the plain one, the exchange of gate and up sums between wavefronts of 128-column tiles
+// longest: 1.4 and 2.4 us for every workgroup that a compute unit has, on tiles of 256 columns 0.6 - 1.6.  On 498 gated calls of 65 to 900 rows
+// and 256 to 5000 weights a row the choice among whole tiles costs 0.2 - 0.6 % over the best, without these costs 3.6 - 4.1 %
+// (683 x 9408 x 384 in 8-bit codes 14.5 us on 64 x 128 tiles, 11.8 on 64 x 256).
 struct TileCost {
     double lo[4];                                       // us per pair of K slices at fill 0, 1/8, 1/4, 1/2 of a round ...
     double past;                                        // ... just above 1/4 ...
     double hi[3];                                       // ... and just above 1/2, at 3/4 and 1
     double b;                                           // us per round: prologue and epilogue of a work item
     int cap;                                            // work items per round
+    double gated;                                       // us more per workgroup of a compute unit for the gated product's epilogue
 };
-constexpr TileCost kFlatCost{{0.821, 0.866, 0.887, 1.113}, 0.887, {1.604, 1.867, 1.868}, 3.74, 2 * kComputeUnits};
-constexpr TileCost kHalfCost{{1.114, 1.174, 1.222, 1.713}, 1.222, {2.513, 2.919, 3.212}, 6.07, 2 * kComputeUnits};
-constexpr TileCost kBigCost{{2.008, 2.046, 2.094, 2.227}, 2.094, {2.220, 2.730, 3.313}, 7.35, kComputeUnits};
-constexpr TileCost kNarrowCost{{0.505, 0.549, 0.628, 1.162}, 0.847, {1.393, 1.858, 2.078}, 3.33, 4 * kComputeUnits};
-constexpr TileCost kMidCost{{0.683, 0.726, 0.761, 0.988}, 0.761, {1.391, 1.660, 1.840}, 4.29, 2 * kComputeUnits};
+constexpr TileCost kFlatCost{{0.821, 0.866, 0.887, 1.113}, 0.887, {1.604, 1.867, 1.868}, 3.74, 2 * kComputeUnits, 1.0};
+constexpr TileCost kHalfCost{{1.114, 1.174, 1.222, 1.713}, 1.222, {2.513, 2.919, 3.212}, 6.07, 2 * kComputeUnits, 0.6};
+constexpr TileCost kBigCost{{2.008, 2.046, 2.094, 2.227}, 2.094, {2.220, 2.730, 3.313}, 7.35, kComputeUnits, 1.6};
+constexpr TileCost kNarrowCost{{0.505, 0.549, 0.628, 1.162}, 0.847, {1.393, 1.858, 2.078}, 3.33, 4 * kComputeUnits, 1.35};
+constexpr TileCost kMidCost{{0.683, 0.726, 0.761, 0.988}, 0.761, {1.391, 1.660, 1.840}, 4.29, 2 * kComputeUnits, 2.4};
 constexpr double kReduceUs = 4.23, kReduceUsPerMB = 0.211;      // reduction kernel of a K split
 constexpr double kSkUs = 39.1, kSkUsPerSharer = 0.86;           // even scheduling: slabs, and the serial part per sharer
 // 8-bit codes, twice the registers per slice and twice the bytes: 128-row tiles request codes two slices ahead instead of four, and those of
 // 128 columns, a wavefront to a SIMD, wait for them.  A fit of their own to 13181 timings of 622 problems (rms 6.7 %): the choice
 // costs 1.0 - 2.4 % over the best, by the costs of 4-bit codes 2.4 - 4.2 % (gated 192 x 11712 x 7808, 184 tiles of 128 x 128, 79.8 us, on
 // 64 x 256 tiles 61.9).
-constexpr TileCost kFlatCost8{{0.789, 0.877, 0.917, 1.203}, 0.917, {1.773, 2.006, 2.045}, 4.88, 2 * kComputeUnits};
-constexpr TileCost kHalfCost8{{1.266, 1.351, 1.392, 1.898}, 1.392, {2.739, 3.236, 3.436}, 5.85, 2 * kComputeUnits};
-constexpr TileCost kBigCost8{{2.225, 2.287, 2.356, 2.515}, 2.356, {2.499, 2.965, 3.553}, 5.99, kComputeUnits};
-constexpr TileCost kNarrowCost8{{0.518, 0.598, 0.698, 1.326}, 1.053, {1.570, 2.062, 2.250}, 3.75, 4 * kComputeUnits};
-constexpr TileCost kMidCost8{{0.988, 1.134, 1.163, 1.244}, 1.163, {1.487, 1.892, 1.981}, 4.21, 2 * kComputeUnits};
+constexpr TileCost kFlatCost8{{0.789, 0.877, 0.917, 1.203}, 0.917, {1.773, 2.006, 2.045}, 4.88, 2 * kComputeUnits, 0.9};
+constexpr TileCost kHalfCost8{{1.266, 1.351, 1.392, 1.898}, 1.392, {2.739, 3.236, 3.436}, 5.85, 2 * kComputeUnits, 0.8};
+constexpr TileCost kBigCost8{{2.225, 2.287, 2.356, 2.515}, 2.356, {2.499, 2.965, 3.553}, 5.99, kComputeUnits, 2.6};
+constexpr TileCost kNarrowCost8{{0.518, 0.598, 0.698, 1.326}, 1.053, {1.570, 2.062, 2.250}, 3.75, 4 * kComputeUnits, 1.35};
+constexpr TileCost kMidCost8{{0.988, 1.134, 1.163, 1.244}, 1.163, {1.487, 1.892, 1.981}, 4.21, 2 * kComputeUnits, 2.2};
 constexpr double kReduceUs8 = 4.42, kReduceUsPerMB8 = 0.245;
 struct Estimate {
     TileCost flat, half, big, narrow, mid;
     double reduce_us, reduce_us_per_mb, sk_us, sk_us_per_sharer;
     bool all_tiles;                                     // with the tiles of 128 columns, and a short last row tile counted as such
+    bool gated = false;                                 // for a call with the gated product
 };
 constexpr Estimate kNow{kFlatCost, kHalfCost, kBigCost, kNarrowCost, kMidCost, kReduceUs, kReduceUsPerMB, kSkUs, kSkUsPerSharer, true};
 constexpr Estimate kNow8{kFlatCost8, kHalfCost8, kBigCost8, kNarrowCost8, kMidCost8, kReduceUs8, kReduceUsPerMB8, kSkUs, kSkUsPerSharer, true};
@@ -966,15 +972,15 @@ constexpr Estimate kNow8{kFlatCost8, kHalfCost8, kBigCost8, kNarrowCost8, kMidCo
 // constants that stay as they are, whatever becomes of the kernel: a size once asked for is enough for good.  Calls of up to 64 rows
 // with a residual or the gated product have exactly its number of splits: with another one their sums, and the residual streams that
 // they feed, would be rounded otherwise.
-constexpr Estimate kSizes{{{0.809, 1.173, 1.302, 1.456}, 1.302, {1.601, 2.034, 1.971}, 4.39, 2 * kComputeUnits},
-                          {{1.427, 1.531, 1.573, 1.894}, 1.573, {2.592, 3.118, 3.411}, 5.92, 2 * kComputeUnits},
-                          {{2.052, 2.302, 2.454, 2.523}, 2.454, {2.445, 2.908, 3.461}, 9.34, kComputeUnits},
+constexpr Estimate kSizes{{{0.809, 1.173, 1.302, 1.456}, 1.302, {1.601, 2.034, 1.971}, 4.39, 2 * kComputeUnits, 0.0},
+                          {{1.427, 1.531, 1.573, 1.894}, 1.573, {2.592, 3.118, 3.411}, 5.92, 2 * kComputeUnits, 0.0},
+                          {{2.052, 2.302, 2.454, 2.523}, 2.454, {2.445, 2.908, 3.461}, 9.34, kComputeUnits, 0.0},
                           kNarrowCost, kMidCost,        // (not among its tiles)
                           4.87, 0.176, 34.7, 0.68, false};
 // Those calls choose between the two tiles of 64 rows only, by costs of their own: on 240 calls in 4- and 8-bit codes 0.3 - 1.0 % over the
 // better tile on two cards, with the costs above 0.15 - 1.8 %.
-constexpr Estimate kFewFused{{{0.800, 0.868, 0.905, 1.150}, 0.905, {1.662, 1.908, 2.013}, 2.99, 2 * kComputeUnits}, kHalfCost, kBigCost,
-                             {{0.551, 0.515, 0.747, 1.243}, 0.747, {1.388, 1.925, 2.255}, 2.73, 4 * kComputeUnits}, kMidCost,
+constexpr Estimate kFewFused{{{0.800, 0.868, 0.905, 1.150}, 0.905, {1.662, 1.908, 2.013}, 2.99, 2 * kComputeUnits, 0.0}, kHalfCost, kBigCost,
+                             {{0.551, 0.515, 0.747, 1.243}, 0.747, {1.388, 1.925, 2.255}, 2.73, 4 * kComputeUnits, 0.0}, kMidCost,
                              4.38, 0.184, kSkUs, kSkUsPerSharer, true};
 constexpr int kSplitMajorMinPairs = 16;
 constexpr int kSkMinTiles = 128;                        // fewer tiles: the fixed K split (the fit holds no such launch)
@@ -1001,6 +1007,7 @@ double split_launch_us(const Estimate& e, const TileCost& c, int64_t tiles, int 
 {
     double us = rounds_us(c, tiles * splits, (double)(K / (2 * BK)) / splits);
     if (splits > 1) us += e.reduce_us + e.reduce_us_per_mb * (double)splits * (double)M * (double)N * 4e-6;
+    else if (e.gated) us += c.gated * (double)(tiles / c.cap * (c.cap / kComputeUnits) + (tiles % c.cap + kComputeUnits - 1) / kComputeUnits);
     return us;
 }
 
@@ -1211,8 +1218,10 @@ PipePlan pipe_plan(const Fusion& f, int64_t M, int64_t N, int64_t K, bool fused,
     const bool steered = (knob(Knob::gemm_variant) && knob(Knob::gemm_variant) != 7) || knob(Knob::gemm_splits) || knob(Knob::gemm_sk);
     if (!steered) {
         const bool exactly = fused && M <= kFlatOnlyMaxM && (f.residual || f.swiglu);
-        p = shortest(exactly ? kFewFused : e8 ? kNow8 : kNow, M, N, K, PipeRules{false, exactly, exactly ? p.splits : std::max<int64_t>(1, (int64_t)(room / partial_bytes(1, M, N))),
-                                              sk ? room : 0});
+        Estimate e = exactly ? kFewFused : e8 ? kNow8 : kNow;
+        e.gated = f.swiglu;
+        p = shortest(e, M, N, K, PipeRules{false, exactly, exactly ? p.splits : std::max<int64_t>(1, (int64_t)(room / partial_bytes(1, M, N))),
+                                           sk ? room : 0});
     }
     if (fused && !e8 && M <= kFlatOnlyMaxM && k_quarters(p.splits, M, N)) {
         p.tile = kNarrowTile;

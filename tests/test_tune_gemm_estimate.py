@@ -75,3 +75,24 @@ def test_the_constants_choose_among_measured_launches(timings, suffix):
         c = [x for x in c if x[1] != "sk"]
         chosen = min(c, key=lambda x: tool.estimate(p, M, N, K, x[0], x[1]))
         assert chosen[2] <= 1.05 * min(x[2] for x in c), (M, N, K, chosen)
+
+
+def gated_costs(suffix):
+    text = open(os.path.join(os.path.dirname(tool.__file__), "csrc", "e0m4_gemm_pipe.hip")).read()
+    return {t: float(re.search(r"k%sCost%s\{\{[^;]*, ([0-9.]+)\};" % (name, suffix), text).group(1))
+            for t, name in zip("fhbnm", ("Flat", "Half", "Big", "Narrow", "Mid"))}
+
+
+# (whole tiles: calls with the gated product where the costs of plain calls chose launches 17 - 29 % longer)
+@pytest.mark.parametrize("timings,suffix", [("gated_launch_timings_4bit.txt", ""), ("gated_launch_timings_8bit.txt", "8")])
+def test_the_gated_costs_choose_among_measured_launches(timings, suffix):
+    p, g = constants(suffix), gated_costs(suffix)
+
+    def estimate(M, N, K, tile):
+        bm, bn, cap, _ = tool.TILES[tile]
+        full, rem = divmod(-(-M // bm) * -(-N // bn), cap)
+        return tool.estimate(p, M, N, K, tile, 1) + g[tile] * (full * (cap // tool.CU) + -(-rem // tool.CU))
+
+    for (M, N, K), c in tool.read_timings([os.path.join(os.path.dirname(__file__), "golden", timings)]).items():
+        chosen = min(c, key=lambda x: estimate(M, N, K, x[0]))
+        assert chosen[2] <= 1.04 * min(x[2] for x in c), (M, N, K, chosen)
