@@ -1054,11 +1054,16 @@ bool short_last(const PipeTile& t, int64_t M, int64_t tiles, int splits)
            M % t.bm != 0 && M % t.bm <= 64;
 }
 
-// whole tiles (a short last row tile counts as 0.6), or `splits` K ranges of each and the reduction kernel
+// whole tiles (a short last row tile counts as 0.6, but more tiles than compute units stay more: the first of them have two workgroups,
+// whatever the last one's rows; gated 288 x 23296 x 640, 273 tiles, 18.3 us, on 64 x 256 tiles 14.7), or `splits` K ranges of each and
+// the reduction kernel
 double tile_launch_us(const Estimate& e, const PipeTile& t, int splits, int64_t M, int64_t N, int64_t K)
 {
     int64_t tiles = pipe_tiles(t, M, N);
-    if (e.all_tiles && short_last(t, M, tiles, splits)) tiles -= tiles / ((M + t.bm - 1) / t.bm) * 2 / 5;
+    if (e.all_tiles && short_last(t, M, tiles, splits)) {
+        const int64_t less = tiles - tiles / ((M + t.bm - 1) / t.bm) * 2 / 5;
+        tiles = tiles > kComputeUnits ? std::max<int64_t>(less, kComputeUnits + 1) : less;
+    }
     return split_launch_us(e, cost_of(e, t), tiles, splits, M, N, K);
 }
 

@@ -2,6 +2,8 @@
 multiple of 8, the gated product of two wavefronts' sums in whole tiles and in K splits, a K range shorter than the pipeline, every
 group and format; K quarters inside a workgroup; the same bits as the tiles of 256 columns in the same number of splits; and the number of K splits, hence the
 bits, of fused calls of up to 64 rows by default routes."""
+import ctypes
+
 import pytest
 
 import synth_inputs
@@ -104,3 +106,49 @@ def test_calls_with_an_rms_norm_alone_choose_their_splits(e0m4, bits, M, N, K, s
 
     by_default, whole, split = run(), run(gemm_variant=6, gemm_splits=1), run(gemm_variant=4, gemm_splits=splits)
     assert torch.equal(by_default, whole) and not torch.equal(by_default, split)
+
+
+class Dim3(ctypes.Structure):
+    _fields_ = [("x", ctypes.c_uint32), ("y", ctypes.c_uint32), ("z", ctypes.c_uint32)]
+
+
+class KernelNodeParams(ctypes.Structure):
+    _fields_ = [("block", Dim3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p), ("grid", Dim3), ("params", ctypes.c_void_p),
+                ("shared", ctypes.c_uint)]
+
+
+def launches(fn):
+    """Workgroups, threads and LDS of the kernels that a call launches, which tell the GEMM's tiles apart."""
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    fn()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        fn()
+    hip, n = ctypes.CDLL("libamdhip64.so"), ctypes.c_size_t(0)
+    raw = ctypes.c_void_p(graph.raw_cuda_graph())
+    assert hip.hipGraphGetNodes(raw, None, ctypes.byref(n)) == 0
+    nodes = (ctypes.c_void_p * n.value)()
+    assert hip.hipGraphGetNodes(raw, nodes, ctypes.byref(n)) == 0
+    out = []
+    for node in nodes:
+        p = KernelNodeParams()
+        assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(p)) == 0
+        out.append((p.grid.x, p.block.x, p.shared))
+    return out
+
+
+# (the tile of a gated call by default: on tiles of 128 columns its epilogue takes longer; tiles of 128 x 256 that are more than the compute
+# units, the last row of them short)
+@pytest.mark.parametrize("bits,M,N,K,tiles", [(4, 609, 10816, 384, (4, 5)), (4, 222, 8640, 256, (4,)), (8, 732, 9600, 256, (4, 5)), (8, 121, 21056, 384, (4,)),
+                                              (4, 107, 10368, 768, (6,)), (4, 439, 17920, 2432, (4,)), (8, 391, 17344, 2944, (4,)), (4, 288, 23296, 640, (4,))])
+def test_tiles_of_gated_calls(e0m4, bits, M, N, K, tiles):
+    quantize, fused = (e0m4.e0m8_quantize, e0m4.e0m8_matmul_fused) if bits == 8 else (e0m4.e0m4_quantize, e0m4.e0m4_matmul_fused)
+    codes = quantize(to_dev(synth_inputs.weights(64, K, seed=1480)).repeat(-(-N // 64), 1)[:N].contiguous(), 128)[0]
+    X = to_dev(synth_inputs.activations(M, K, seed=1481))
+    Y = X.new_empty((M, N // 2))
+
+    def run(**knobs):
+        return with_knobs(e0m4, lambda: launches(lambda: fused(X, codes, N, K, 128, epilogue=1, out=Y)), **knobs)
+
+    by_default = run()
+    assert by_default in [run(gemm_variant=v, gemm_splits=1) for v in tiles], by_default
