@@ -978,9 +978,10 @@ constexpr Estimate kSizes{{{0.809, 1.173, 1.302, 1.456}, 1.302, {1.601, 2.034, 1
                           kNarrowCost, kMidCost,        // (not among its tiles)
                           4.87, 0.176, 34.7, 0.68, false};
 // Those calls choose between the two tiles of 64 rows only, by costs of their own: on 240 calls in 4- and 8-bit codes 0.3 - 1.0 % over the
-// better tile on two cards, with the costs above 0.15 - 1.8 %.
-constexpr Estimate kFewFused{{{0.800, 0.868, 0.905, 1.150}, 0.905, {1.662, 1.908, 2.013}, 2.99, 2 * kComputeUnits, 0.0}, kHalfCost, kBigCost,
-                             {{0.551, 0.515, 0.747, 1.243}, 0.747, {1.388, 1.925, 2.255}, 2.73, 4 * kComputeUnits, 0.0}, kMidCost,
+// better tile on two cards, with the costs above 0.15 - 1.8 %; on 202 gated ones in whole tiles, of 128 weights a row and more, 0.06 - 0.3 %, without the
+// gated costs 3.5 - 4.2 % (39 x 36096 x 128 7.2 us on 64 x 128 tiles, 5.8 on 64 x 256).
+constexpr Estimate kFewFused{{{0.800, 0.868, 0.905, 1.150}, 0.905, {1.662, 1.908, 2.013}, 2.99, 2 * kComputeUnits, 1.0}, kHalfCost, kBigCost,
+                             {{0.551, 0.515, 0.747, 1.243}, 0.747, {1.388, 1.925, 2.255}, 2.73, 4 * kComputeUnits, 1.35}, kMidCost,
                              4.38, 0.184, kSkUs, kSkUsPerSharer, true};
 constexpr int kSplitMajorMinPairs = 16;
 constexpr int kSkMinTiles = 128;                        // fewer tiles: the fixed K split (the fit holds no such launch)
