@@ -371,7 +371,9 @@ __global__ __launch_bounds__(kDqThreads, 2) void gemv_dq_kernel(const half_t* __
 // One workgroup per compute unit where the row blocks allow it (its eight wavefronts fill the unit's registers): with more
 // than 256 x 16 of them, as few whole rounds as possible.  (`nkb`: k blocks of a row; without it the plan's size only)
 // Rows shorter than a group of wavefronts has members are shared among more groups: 18848 x 512 (five row blocks per workgroup, four k
-// blocks) in bfloat16 at M = 45 6.6 us with four of eight wavefronts at work, 5.8 with all; at M = 16 4.8 and 4.1.
+// blocks) in bfloat16 at M = 45 6.6 us with four of eight wavefronts at work, 5.8 with all; at M = 16 4.8 and 4.1.  (Exact codes of up to
+// eight rows not with two row blocks, of which most workgroups then have one: 4816 x 384 at M = 5 3.2 us in one group, 3.4 in two; with X
+// straight to LDS, 7888 x 256 at M = 9, 3.8 and 3.6.)
 bool make_dq_plan(int64_t M, int64_t N, int64_t K, DqPlan& p, bool exact = false, int64_t nkb = kDqWaves)
 {
     if (M < 2 || M > kDqMaxParts * kDqMaxM || N <= 0 || K <= 0) return false;
@@ -386,7 +388,8 @@ bool make_dq_plan(int64_t M, int64_t N, int64_t K, DqPlan& p, bool exact = false
     p.rb_rem = (int)(nrb % p.grid);
     p.wr = 1;
     const int max_r = dq_max_r((int)(((M + p.parts - 1) / p.parts + 15) / 16), exact);
-    while (p.wr * max_r < most || (p.wr < kDqMaxGroups && p.wr * 2 <= most && p.wr * 2 * nkb <= kDqWaves)) p.wr *= 2;
+    const int fewest = exact && M <= 8 ? 3 : 2;             // row blocks to be shared by groups
+    while (p.wr * max_r < most || (most >= fewest && p.wr < kDqMaxGroups && p.wr * 2 <= most && p.wr * 2 * nkb <= kDqWaves)) p.wr *= 2;
     p.r = (int)((most + p.wr - 1) / p.wr);
     return true;
 }
