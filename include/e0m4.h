@@ -135,9 +135,13 @@ int e0m4_unpack_codes(const void* codes, int64_t N, int64_t K, int group, void* 
  *            small-batch kernel on those chunks in one launch or, in plain calls
  *            and mostly where they make more than one round, the dequantising
  *            kernel's form on exact codes; otherwise, any group, the
- *            dequantising kernel (M > 32: K <= 12800, M > 48: 256 <= K <= 7680
- *            and N * K <= 1e8, or up to 9216 and 7e7; beyond N * K = 7e7 the
- *            GEMM's workspace is asked for, though it uses none).
+ *            dequantising kernel, without a workspace where N * K <= 7e7 (M > 48:
+ *            and 256 <= K <= 9216), elsewhere by the number b of blocks of 16
+ *            output rows that a compute unit has, N / 4096 rounded up: M <= 32
+ *            b <= 6, K >= 768 b <= 12, K >= 1024 b <= 24; M <= 48, K <= 12800
+ *            b <= 6, K >= 512 b = 9 and 10; above, K <= 7680, K >= 256 b <= 2,
+ *            K >= 768 b <= 4 (the GEMM's workspace is asked for there, though
+ *            that kernel uses none).
  *   M >= 9 otherwise, and 2 <= M <= 8 when M * N * K is about 3.8e8 or
  *            more (the vector kernel's time grows with M): MFMA GEMM path
  *            (tiles of 64 x 128 to 256 x 256 outputs, whichever
@@ -207,7 +211,7 @@ int e0m4_matmul_static(const void* X_f16, int64_t M, const void* codes, int64_t 
  * runs inside the GEMM kernels (or the kernel that adds the K splits) and the
  * rms-norm is a launch of its own that writes x' to the workspace; up to M = 64
  * the dequantising kernel of e0m4_matmul follows it where no other operator is
- * selected.  Where e0m4_matmul would go in chunks of rows (17 <= M <= 64), a
+ * selected and that kernel is the faster one (by b as there, whatever N * K).  Where e0m4_matmul would go in chunks of rows (17 <= M <= 64), a
  * kernel with all rows in a workgroup gives the same sums in the same order.  Its
  * rms-norm is a launch of its own that needs room for x', which chunks do not:
  * calls with one go there through e0m4_matmul_fused_best.
@@ -277,9 +281,11 @@ int e0m4_kv_append(void* cache_f16, int64_t max_seq, int64_t row_elems,
  *     (and N <= 2^24): the MFMA GEMM kernels, workspace of
  *     e0m8_workspace_bytes() bytes under the rules of e0m4_matmul (17 <= M <=
  *     32 with K <= 2048 and N * K <= 1e7: the matrix-core variant on two
- *     chunks of rows in one launch instead; otherwise M <= 64, with K <= 8192 for
- *     M > 32 and 256 <= K <= 6144 and N * K <= 1.2e8 for M > 48: the dequantising
- *     kernel of e0m4_matmul).  Other M > 16:
+ *     chunks of rows in one launch instead; otherwise M <= 64: the dequantising
+ *     kernel of e0m4_matmul, without a workspace where N * K <= 1e8 (M > 48: and
+ *     256 <= K <= 9216), elsewhere, with b as there and the GEMM's workspace asked
+ *     for, M <= 32 with b <= 13, K >= 512 b <= 20; M <= 48, K <= 8192 with b <= 4,
+ *     K >= 1024 b <= 10; above, 256 <= K <= 6144 with b <= 4).  Other M > 16:
  *     the decode kernel on 8 rows of X at a time (needs N % 8 == 0).
  * Pointer, alignment, stream and error rules as for the E0M4 entry points.
  */
