@@ -20,8 +20,9 @@
 // of X in flight were 0 - 10 % slower than one, as were three and four of weights.  Up to eight rows, which are one or two loads
 // per k block, registers in between are 2 - 8 % faster.  An operand is dequantised by 15 vector instructions (bfloat16: 19), so one
 // should serve many rows.
-// Against the GEMM at 4096 x 4096, 27392 x 4096, 4096 x 13696 (us): bfloat16 at M = 16 35.0 -> 6.2, 38.6 -> 20.3, 102 -> 13.1;
-// groups of 64 at M = 16 15.1 -> 6.2, 27.3 -> 18.0, 30.7 -> 13.4; 8-bit codes at M = 45 17.6 -> 10.1, (not used), 33.3 -> 28.0.
+// The GEMM and this kernel at 4096 x 4096, 27392 x 4096, 4096 x 13696 (us): bfloat16 at M = 16 23.5 and 5.7, 28.2 and 19.6, 70 and 13.0;
+// groups of 64 at M = 16 10.7 and 5.5, 25.9 and 19.5, 17.9 and 13.2; 8-bit codes at M = 45 13.3 and 10.0, 32.3 and 35.4 (not used), 24.2 and
+// 28.1 (gemv_dq_free).
 //
 // Every weight is rounded to 16 bits before the product, as it is in the GEMM, but in the instances on exact codes (EX below),
 // which apply scale and bias in fp32 as e0m4_gemv.hip and e0m4_gemv_mfma.hip do.  Calls of those two go to EX instances only.
@@ -466,11 +467,13 @@ bool gemv_dq_supported(int64_t M, int64_t N, int64_t K, int group)
 // Where this kernel is faster than the GEMM, which rounds the weights as it does.  (The callers keep the calls of the kernels
 // that multiply unrounded weights away from here, faster or not; the instances on exact codes are chosen below.)  The other
 // side's time over this kernel's, with cold weights:
-//   bfloat16: up to 64 rows always (1.1 - 7.8: the GEMM has whole tiles only).  65 to 128 rows in two parts, against 64 x 256
-//     tiles with K halves, where a workgroup has few row blocks: 1.2 - 3.1; at M = 100 4096 x 4096 34.8 -> 16.7 us, 4096 x 13696
-//     102 -> 43, but 32768 x 2048 (8 row blocks) 25 -> 37, 27392 x 4096 43 -> 41.
+//   bfloat16: up to 64 rows always (1.0 - 5.4: the GEMM has whole tiles only).  65 to 128 rows in two parts, where a workgroup has one
+//     row block or two; on 248 calls with one row block and rows of 1024 weights and more 1.0 - 4.5, from 512 on 0.84 - 1.7; with two on
+//     4096 and more 1.2 - 1.7, from 1024 on 0.94 - 1.25, from 512 on, since there are 64 x 128 tiles, 0.77 - 0.84 (8192 x 512 at M = 128 6.5
+//     us and here 8.3); with more 0.5 - 1.3.  At M = 100 4096 x 4096 24.0 and 17.2, 4096 x 13696 71 and 43, but 32768 x 2048 (8 row blocks)
+//     21.6 and 35.4, 27392 x 4096 36 and 56.
 //   On the shortest rows most wavefronts have no k block of their own, and many rows of X cost the others time: M = 64, 16384 x
-//     128 6.0 us against 4.9; in two parts M = 128, 8192 x 256 7.7 against 6.2, 8192 x 512 7.9 against 8.3.
+//     128 4.5 us against 5.0; in two parts M = 128, 8192 x 256 5.3 against 7.9.
 //   Groups of 32 and 64 up to 16 rows: always (1.3 - 3.1, the vector kernel's calls among them).
 //   17 to 64 rows: gemv_dq_beats_gemm, but plain calls within the lines of gemv_dq_free stay here whatever the GEMM has become.
 //   (gemv_dq_free: calls that need no workspace.  Callers of the others, up to 64 rows, bring the GEMM's; those lines stay
@@ -557,6 +560,11 @@ bool gemv_exact_pays_bf16(int64_t M, int64_t N, int64_t K)
 //     Else 0.51 - 1.02 (2376 x 1920 at M = 64 11.0 and 7.3; 1056 x 5120 at M = 49, eight workgroups beyond a round, 1.11), but with four
 //       chunks in two rounds whose wavefronts each stage their own X (as many work items as wavefronts) 1.00 - 1.18 (2040 x 4096 at
 //       M = 51 9.8 and 11.5).
+//     These lines were drawn before X came straight to LDS.  Since then, on 500 calls: more than one row block 0.44 - 1.0, two chunks of
+//     more than a round 0.50 - 1.0, three and four of fewer than eight work items 0.41 - 1.0; but of the calls that the lines leave to chunks
+//     those of two with a compute unit each take 0.74 - 1.0 (1856 x 4736 at M = 27 8.4 and 6.5), of three 0.83 - 1.2, of four 0.90 - 1.27,
+//     and four with eight work items 0.78 - 0.87 (1864 x 4096 at M = 56 11.2 and 8.8).  The lines stand: calls beyond them keep the order
+//     of their sums.
 bool gemv_exact_pays_chunks(int64_t M, int chunks, const WholeRowsPlan& plan)
 {
     if (plan.row_blocks > 1) return true;
