@@ -14,7 +14,10 @@ benchmark set (the single 4096 x 4096 GEMV over rotating weight copies, the
 ChatGLM2-6B prefill GEMMs at M=1024, the Gemma-2B-shaped layers with the LM
 head, the 14B-shaped layers at groups 64 and 128, M=1 and M=2048); side
 sections (small batches, E0M4 against INT4, 8-bit codes, operator fusion,
-KV append); and the CPU oracle timed on bounded samples of the same work.
+KV append); and the CPU oracle timed on bounded samples of the same work.  The
+line has every section's figures, at most LINE_CHARS of them, since what
+keeps a run's output keeps so much of its end; the tables per shape behind them
+go to the file of --details.
 
 Sections can be selected with --only / --skip (names: decode, shapes, cfg1,
 prefill, gemma, d14b, small_batch, table1, e0m8, bf16, fusion, kv, cpu); the profiler
@@ -40,8 +43,47 @@ if ROOT not in sys.path:
 HBM_PEAK_GBPS = 8000.0          # MI355X published HBM3E bandwidth
 MFMA_F16_PEAK_TFLOPS = 2500.0   # MI355X published dense fp16 matrix peak
 GROUP = 128
+LINE_CHARS = 6000
 SECTIONS = ("decode", "shapes", "cfg1", "prefill", "gemma", "d14b", "small_batch", "table1", "e0m8", "bf16", "fusion",
             "kv", "dispatch", "cpu", "gemma_prefill", "d14b_prefill")
+
+
+def brief(out):
+    """The record as it is printed: roofline objects down to rate and share of the peak, tables down to the times."""
+    def roofline(r):
+        return {k: r[k] for k in ("achieved", "unit", "frac") if k in r}
+
+    def times(table):
+        return {shape: v["us"] for shape, v in table.items()}
+
+    line = {k: v for k, v in out.items() if k not in ("configs", "decode_per_shape", "dispatch", "small_batch", "small_batch_g64",
+                                                      "e0m8_decode", "e0m4_bf16", "table1_e0m4_vs_int4")}
+
+    def parts(cfg):
+        found = {}
+        for k, v in cfg.items():
+            if isinstance(v, dict) and "frac" in v:
+                found[k] = roofline(v)
+            elif isinstance(v, dict) and "layer" in v:
+                found[k] = roofline(v["layer"])
+            elif k.startswith("group_"):
+                found[k] = parts(v)
+        return found
+
+    line["configs"] = {name: parts(cfg) for name, cfg in out["configs"].items()}
+    if "decode_per_shape" in out:
+        line["decode_us"] = times(out["decode_per_shape"])
+    if "dispatch" in out:
+        line["dispatch"] = {k: v for k, v in out["dispatch"].items() if k.endswith("over_best")}
+    for k in ("small_batch", "small_batch_g64"):
+        if k in out:
+            line[k + "_us"] = {M: times(t) for M, t in out[k]["per_M"].items()}
+    for k in ("e0m8_decode", "e0m4_bf16"):
+        if k in out:
+            line[k] = {shape: {f: v[f] for f in ("us", "prefill_TFLOPs") if f in v} for shape, v in out[k]["per_shape"].items()}
+    if "table1_e0m4_vs_int4" in out:
+        line["table1_int4_over_e0m4"] = {k: v["int4_over_e0m4"] for k, v in out["table1_e0m4_vs_int4"]["shapes"].items()}
+    return line
 
 
 def algorithmic_bytes(M, N, K, G):
@@ -156,6 +198,7 @@ def main():
     ap.add_argument("--copy-probe", action="store_true",
                     help="first run three plain device copies of 1 GiB (calibration of HBM traffic counters)")
     ap.add_argument("--summarize", default=None, metavar="DIR", help="summarise a rocprofv3 output directory and exit")
+    ap.add_argument("--details", default=None, metavar="FILE", help="write the whole record, with its tables, to FILE")
     ap.add_argument("--last", type=int, default=0, help="with --summarize: only the last N matmul dispatches")
     args = ap.parse_args()
     if args.summarize:
@@ -864,7 +907,10 @@ def main():
             "sample": "dequant + fp64 matmul of an M=16 slice of the four M=1024 GEMMs (%.1f s); a full layer at this "
                       "rate would take %.0f s (extrapolated x64)" % (t16, t16 * 64)}
 
-    print(json.dumps(out))
+    if args.details:
+        with open(args.details, "w") as f:
+            json.dump(out, f)
+    print(json.dumps(brief(out)))
 
 
 if __name__ == "__main__":
