@@ -153,3 +153,15 @@ def test_tiles_of_gated_calls(e0m4, bits, M, N, K, tiles):
 
     by_default = run()
     assert by_default in [run(gemm_variant=v, gemm_splits=1) for v in tiles], by_default
+
+
+def test_a_tie_between_whole_tiles_and_splits_is_the_whole_tiles(e0m4):
+    M, N, K = 2048, 5120, 13696
+    codes = e0m4.e0m4_quantize(to_dev(synth_inputs.weights(64, K, seed=1490)).repeat(N // 64, 1), 64)[0]
+    X, R = to_dev(synth_inputs.activations(M, K, seed=1491)), to_dev(synth_inputs.residual(M, N, 1492))
+    Y = torch.empty_like(R)
+
+    def run(**knobs):
+        return with_knobs(e0m4, lambda: launches(lambda: e0m4.e0m4_matmul_fused(X, codes, N, K, 64, residual=R, out=Y)), **knobs)
+
+    assert run() == run(gemm_variant=2, gemm_splits=1)
