@@ -107,7 +107,7 @@ def profile_traffic(key):
 # rocprofv3 summaries
 
 def _short_kernel_name(n):
-    m = re.search(r"(gemv_kernel|gemv_mfma_kernel|gemv_items_kernel|gemv_dq_kernel|splitk_reduce_fused_kernel|gemm_pipe_kernel|"
+    m = re.search(r"(gemv_kernel|gemv_mfma_kernel|gemv_items_kernel|gemv_dq_kernel|gemv_tiles_kernel|splitk_reduce_fused_kernel|gemm_pipe_kernel|"
                   r"gemm_kernel|quantize_kernel|dequant_kernel|unpack_kernel|splitk_reduce_kernel|zero_fill_kernel|rmsnorm_kernel|"
                   r"kv_append_kernel|quantize8_kernel)I((?:L(?:[ib]|NS_8DqFormatE)\d+E)+)E", n)
     if m:
@@ -117,7 +117,7 @@ def _short_kernel_name(n):
     return (m.group(1) or m.group(2) if m else n)[:60]
 
 
-OUR_KERNELS = (r"gemv_kernel|gemv_mfma_kernel|gemv_items_kernel|gemv_dq_kernel|gemm_pipe_kernel|gemm_kernel|splitk_reduce|rmsnorm_kernel|"
+OUR_KERNELS = (r"gemv_kernel|gemv_mfma_kernel|gemv_items_kernel|gemv_dq_kernel|gemv_tiles_kernel|gemm_pipe_kernel|gemm_kernel|splitk_reduce|rmsnorm_kernel|"
                r"quantize_kernel|dequant_kernel|kv_append_kernel|zero_u32_kernel")
 
 

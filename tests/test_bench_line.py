@@ -1,6 +1,7 @@
 """The line that bench.py prints, made from the whole record of a run: short enough to be kept, with the fields that are read from it."""
 import json
 import os
+import re
 
 import bench
 
@@ -22,3 +23,16 @@ def test_sections_that_did_not_run_are_left_out():
     least = {k: record[k] for k in ("metric", "value", "unit", "config", "roofline", "quantize")}
     least["configs"] = {"cfg2_chatglm2_decode": {"workload": "w", "roofline": record["roofline"]}}
     assert set(bench.brief(least)) == set(least)
+
+
+def test_kernel_summaries_name_every_matmul_kernel():
+    csrc = os.path.join(os.path.dirname(bench.__file__), "paper_2403_20041_amd", "csrc")
+    names = set()
+    for f in os.listdir(csrc):
+        if f.endswith(".hip"):
+            names |= set(re.findall(r"\b((?:gemv|gemm|splitk)\w*_kernel)\(", open(os.path.join(csrc, f)).read()))
+    assert len(names) >= 7
+    for n in names:
+        assert re.search(bench.OUR_KERNELS, n), n
+        mangled = "_ZN4e0m412_GLOBAL__N_1%d%sILi3ELi2EEEvPKDF16_" % (len(n), n)
+        assert bench._short_kernel_name(mangled).startswith(n + "<3"), n
