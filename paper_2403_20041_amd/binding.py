@@ -134,10 +134,12 @@ def _empty(shape, dtype, device, stream, what: str):
     block to the stream that was current when it was allocated, so the buffer is allocated with `stream`
     current; a raw stream handle that is not the current stream cannot be made current here, and the caller
     must then own the buffer."""
+    if stream is None:
+        return torch.empty(shape, dtype=dtype, device=device)
     if not _can_allocate(device, stream):
         raise ValueError("%s: pass a caller-owned tensor when `stream` is a raw handle other than torch's current stream"
                          % what)
-    if stream is not None and hasattr(stream, "cuda_stream"):
+    if hasattr(stream, "cuda_stream"):
         with torch.cuda.stream(stream):
             return torch.empty(shape, dtype=dtype, device=device)
     return torch.empty(shape, dtype=dtype, device=device)
@@ -263,19 +265,19 @@ def e0m4_fused_workspace_bytes(M: int, N: int, K: int, group: int, with_rmsnorm:
 
 
 def _capturing(stream) -> bool:
-    if stream is not None and hasattr(stream, "cuda_stream"):
-        with torch.cuda.stream(stream):
-            return torch.cuda.is_current_stream_capturing()
-    return torch.cuda.is_current_stream_capturing()
+    if stream is None or not hasattr(stream, "cuda_stream"):
+        return torch.cuda.is_current_stream_capturing()
+    with torch.cuda.stream(stream):
+        return torch.cuda.is_current_stream_capturing()
 
 
 def _chunks_are_shorter(M: int, n_out: int, K: int) -> bool:
-    """Of a call with an rms-norm that is issued by itself and may do without a workspace: with one it is shorter on the GPU, and
+    """Of a call of 17 to 64 rows with an rms-norm that is issued by itself and may do without a workspace: with one it is shorter on the GPU, and
     by a launch and an allocation 3 - 4 us longer on the host.  In row chunks it takes 8 - 10 us where these (one for 16 rows and
     16 columns) are no more than the compute units and rows of X not long, less than the host does then (M = 20, 2048 x 2048 8.3
     and 10.1 - 12.8 us, replayed in a graph 8.5 and 7.1); else 12 - 35 (M = 45, 4608 x 4096 19.7 and 11.9; M = 18, gated 2304 x 6272
     15.7 and 12.5)."""
-    return 17 <= M <= 64 and -(-M // 16) * -(-n_out // 16) <= 256 and K <= 4608
+    return -(-M // 16) * -(-n_out // 16) <= 256 and K <= 4608
 
 
 def e0m4_matmul_fused(X, codes, N: int, K: int, group: int, rms_gamma=None, rms_eps: float = 0.0,
@@ -293,15 +295,17 @@ def e0m4_matmul_fused(X, codes, N: int, K: int, group: int, rms_gamma=None, rms_
         out = _empty((M, n_out), torch.float16, X.device, stream, "out")
     else:
         _need(out, torch.float16, (M, n_out), "out")
-    call = lib().e0m4_matmul_fused                      # (which writes to a caller's workspace only where one is needed)
+    L = lib()
+    normed = 0 if rms_gamma is None else 1
+    call = L.e0m4_matmul_fused                          # (which writes to a caller's workspace only where one is needed)
     if workspace is None:
-        need = lib().e0m4_fused_workspace_best_bytes(M, N, K, group, 1 if rms_gamma is not None else 0, epilogue)
-        if need > 0 and (not _can_allocate(X.device, stream)
-                         or (rms_gamma is not None and _chunks_are_shorter(M, n_out, K) and not _capturing(stream))):
-            need = e0m4_fused_workspace_bytes(M, N, K, group, rms_gamma is not None, epilogue)     # (0 if it can do without)
+        if not _can_allocate(X.device, stream) or (normed and 17 <= M <= 64 and _chunks_are_shorter(M, n_out, K) and not _capturing(stream)):
+            need = L.e0m4_fused_workspace_bytes(M, N, K, group, normed, epilogue)     # (0 if it can do without)
+        else:
+            need = L.e0m4_fused_workspace_best_bytes(M, N, K, group, normed, epilogue)
+            call = L.e0m4_matmul_fused_best
         if need > 0:
             workspace = _empty(need, torch.uint8, X.device, stream, "workspace")
-            call = lib().e0m4_matmul_fused_best
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     _check(call(_ptr(X), M, _ptr(rms_gamma), float(rms_eps), _ptr(codes), N, K, group, epilogue, _ptr(residual), _ptr(out),
                 _ptr(workspace), ws_bytes, _stream(stream)), "e0m4_matmul_fused")

@@ -273,7 +273,8 @@ enum FusedPath {
 // goes.  Calls with a residual or the gated product keep the GEMM and its order of the sums, though the kernel with dequantised
 // operands would be faster: a stack of blocks amplifies the rounding of a residual stream that is summed in another order.
 static bool as_plain(const Fusion& f) { return !f.residual && !f.swiglu; }
-static FusedPath fused_path(const Fusion& f, int64_t M, int64_t N, int64_t K, int group, TilesPlan* tiles = nullptr)
+// (`may_tiles`: the question is whether a call of the chunks goes in tiles)
+static FusedPath fused_path(const Fusion& f, int64_t M, int64_t N, int64_t K, int group, bool may_tiles, TilesPlan* tiles = nullptr)
 {
     if (!f.any() && use_gemv_exact(M, N, K, group, kDqFormatFp16)) return kFusedExact;
     // (groups of 64 and 32 from three rows on: 1.1 - 2 x the vector kernel and the GEMM there, 10 - 25 % slower than the
@@ -282,7 +283,7 @@ static FusedPath fused_path(const Fusion& f, int64_t M, int64_t N, int64_t K, in
     if (k != 1 && gemv_mfma_fused_supported(f, M, N, K, group) && (group == 128 || M >= 3 || k == 6 || k == 9)) return kFusedSmallBatch;
     if (small_batch_in_chunks(f, M, N, K, group)) {
         TilesPlan p;
-        const bool can = f.any() && group == 128 && (k == 0 || k == 7) && gemv_tiles_plan(f, M, row_chunks(M), N, K, &p) &&
+        const bool can = may_tiles && f.any() && group == 128 && (k == 0 || k == 7) && gemv_tiles_plan(f, M, row_chunks(M), N, K, &p) &&
                          gemv_tiles_supported(p, M, K);
         if (!can || (k == 0 && !gemv_tiles_pays(f, p, M, row_chunks(M)))) return kFusedChunks;
         if (tiles) *tiles = p;
@@ -302,7 +303,7 @@ static size_t fused_bytes(int64_t M, int64_t N, int64_t K, int group, bool norme
     f.swiglu = epilogue == E0M4_EPILOGUE_SWIGLU;
     f.residual = &f;                                    // (a call without a residual needs no more than one with it)
     if (best && normed) f.gamma = &f;                   // (which of the kernels without a need is the fastest depends on the rms-norm)
-    const FusedPath path = fused_path(f, M, N, K, group);
+    const FusedPath path = fused_path(f, M, N, K, group, best && normed);
     if (best && path == kFusedTiles && normed) return norm_bytes(M, K);
     if (path != kFusedGemm) return 0;                   // (with a residual it is never the kernel with dequantised operands)
     return (normed ? norm_bytes(M, K) : 0) + gemm_workspace_bytes(M, N, K, f.swiglu, true);
@@ -487,10 +488,10 @@ static int matmul_fused(const void* X, int64_t M, const void* rms_gamma, float r
         return E0M4_ERR_ALIGN;
     hipStream_t st = (hipStream_t)stream;
     TilesPlan tiles;
-    FusedPath path = fused_path(f, M, N, K, group, &tiles);
+    FusedPath path = fused_path(f, M, N, K, group, best || !rms_gamma, &tiles);
     const size_t nb = rms_gamma ? norm_bytes(M, K) : 0;
     // (chunks need no workspace: calls without one stay there)
-    if (path == kFusedTiles && nb > 0 && (!best || !workspace || !aligned16(workspace) || workspace_bytes < nb)) path = kFusedChunks;
+    if (path == kFusedTiles && nb > 0 && (!workspace || !aligned16(workspace) || workspace_bytes < nb)) path = kFusedChunks;
     if (path == kFusedSmallBatch) return launch_gemv_mfma_fused(f, X, M, codes, N, K, Y, st, 1, group);
     if (path == kFusedVector) return launch_gemv_fused(f, X, M, codes, N, K, group, Y, st);
     if (path == kFusedExact) return launch_gemv_exact(X, M, codes, N, K, kDqFormatFp16, Y, st);
