@@ -1347,8 +1347,13 @@ bool gemm_pipe_supported(int64_t K) { return K >= 128 && (K % (2 * BK)) == 0; }
 
 size_t gemm_pipe_workspace_bytes(int64_t M, int64_t N, int64_t K, bool swiglu, bool fused)
 {
-    if (M <= 0 || N <= 0 || (swiglu && N < 2) || !gemm_pipe_supported(K)) return 0;
-    return pipe_room(M, N, K, !fused && !swiglu, nullptr);
+    if (M <= 0 || N <= 0 || !gemm_pipe_supported(K)) return 0;
+    PipePlan p;
+    const size_t room = pipe_room(M, N, K, !fused && !swiglu, &p);
+    if (!swiglu || N % 2 == 0) return room;
+    // (such calls are refused; their size is that of splits of whole pairs of columns)
+    const int splits = choose_splits(kSizes, p.tile, pipe_tiles(p.tile, M, N - 1), M, N, K, kMaxSplits);
+    return splits > 1 ? partial_bytes(splits, M, N) : 0;
 }
 
 namespace {

@@ -93,6 +93,12 @@ def test_no_partial_sums_for_a_gated_call_without_columns(L):
         assert L.e0m4_fused_workspace_bytes(M, 1, K, 128, 0, 1) == 0 and L.e0m8_fused_workspace_bytes(M, 1, K, 128, 0, 1) == 0
 
 
+def test_partial_sums_of_a_gated_call_with_an_odd_number_of_columns(L):
+    assert L.e0m4_fused_workspace_bytes(163, 2561, 47104, 32, 1, 1) == 28714080
+    assert L.e0m4_fused_workspace_bytes(3942, 513, 6656, 64, 0, 1) == L.e0m8_fused_workspace_bytes(3942, 513, 6656, 64, 0, 1) == 32355936
+    assert L.e0m8_fused_workspace_bytes(1057, 7169, 11776, 64, 0, 1) == 0
+
+
 def test_knobs_belong_to_the_calling_thread(L):
     """A diagnostic knob set by one thread changes neither the size queries nor the dispatch of another."""
     import threading
