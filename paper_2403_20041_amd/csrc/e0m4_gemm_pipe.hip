@@ -964,10 +964,11 @@ struct Estimate {
     TileCost flat, half, big, narrow, mid;
     double reduce_us, reduce_us_per_mb, sk_us, sk_us_per_sharer;
     bool all_tiles;                                     // with the tiles of 128 columns, and a short last row tile counted as such
+    int short_rounds = 1 << 20;                         // rounds of a launch up to which a short row of tiles counts less than a whole one
     bool gated = false;                                 // for a call with the gated product
 };
 constexpr Estimate kNow{kFlatCost, kHalfCost, kBigCost, kNarrowCost, kMidCost, kReduceUs, kReduceUsPerMB, kSkUs, kSkUsPerSharer, true};
-constexpr Estimate kNow8{kFlatCost8, kHalfCost8, kBigCost8, kNarrowCost8, kMidCost8, kReduceUs8, kReduceUsPerMB8, kSkUs, kSkUsPerSharer, true};
+constexpr Estimate kNow8{kFlatCost8, kHalfCost8, kBigCost8, kNarrowCost8, kMidCost8, kReduceUs8, kReduceUsPerMB8, kSkUs, kSkUsPerSharer, true, 2};
 // The workspace that callers are asked for, and with it the most K splits that a launch may have, come from an estimate with
 // constants that stay as they are, whatever becomes of the kernel: a size once asked for is enough for good.  Calls of up to 64 rows
 // with a residual or the gated product have exactly its number of splits: with another one their sums, and the residual streams that
@@ -1057,12 +1058,14 @@ bool short_last(const PipeTile& t, int64_t M, int64_t tiles, int splits)
 }
 
 // whole tiles (a short last row tile counts as 0.6, but more tiles than compute units stay more: the first of them have two workgroups,
-// whatever the last one's rows; gated 288 x 23296 x 640, 273 tiles, 18.3 us, on 64 x 256 tiles 14.7), or `splits` K ranges of each and
-// the reduction kernel
+// whatever the last one's rows; gated 288 x 23296 x 640, 273 tiles, 18.3 us, on 64 x 256 tiles 14.7.  8-bit codes of more than two rounds
+// are bound by the codes, which a short tile reads as a whole one does: gated 142 x 200192 x 1920, 1564 tiles, 207 us, on 64 x 256 tiles
+// 182; on 114 calls with such a row the choice costs 1.3 % over the best whole tiles, 1.7 % without this line), or `splits` K ranges of
+// each and the reduction kernel
 double tile_launch_us(const Estimate& e, const PipeTile& t, int splits, int64_t M, int64_t N, int64_t K)
 {
     int64_t tiles = pipe_tiles(t, M, N);
-    if (e.all_tiles && short_last(t, M, tiles, splits)) {
+    if (e.all_tiles && short_last(t, M, tiles, splits) && tiles <= (int64_t)e.short_rounds * cost_of(e, t).cap) {
         const int64_t less = tiles - tiles / ((M + t.bm - 1) / t.bm) * 2 / 5;
         tiles = tiles > kComputeUnits ? std::max<int64_t>(less, kComputeUnits + 1) : less;
     }

@@ -141,7 +141,7 @@ def launches(fn):
 # units, the last row of them short)
 @pytest.mark.parametrize("bits,M,N,K,tiles", [(4, 609, 10816, 384, (4, 5)), (4, 222, 8640, 256, (4,)), (8, 732, 9600, 256, (4, 5)), (8, 121, 21056, 384, (4,)),
                                               (4, 107, 10368, 768, (6,)), (4, 439, 17920, 2432, (4,)), (8, 391, 17344, 2944, (4,)), (4, 288, 23296, 640, (4,)),
-                                              (4, 39, 36096, 128, (4,)), (4, 60, 33216, 256, (4,)), (8, 46, 37056, 128, (4,)), (8, 20, 44480, 256, (4,)), (4, 34, 32768, 384, (6,))])
+                                              (8, 142, 200192, 1920, (4,)), (4, 39, 36096, 128, (4,)), (4, 60, 33216, 256, (4,)), (8, 46, 37056, 128, (4,)), (8, 20, 44480, 256, (4,)), (4, 34, 32768, 384, (6,))])
 def test_tiles_of_gated_calls(e0m4, bits, M, N, K, tiles):
     quantize, fused = (e0m4.e0m8_quantize, e0m4.e0m8_matmul_fused) if bits == 8 else (e0m4.e0m4_quantize, e0m4.e0m4_matmul_fused)
     codes = quantize(to_dev(synth_inputs.weights(64, K, seed=1480)).repeat(-(-N // 64), 1)[:N].contiguous(), 128)[0]
