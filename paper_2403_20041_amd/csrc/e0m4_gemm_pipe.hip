@@ -1315,7 +1315,9 @@ int launch_pipe(const half_t* x, int64_t M, const uint4* c, int64_t N, int64_t K
     int rc = E0M4_OK;
     // 8-bit codes of up to 64 rows in splits that make a work item per compute unit or fewer: codes two slices ahead instead of four,
     // a shorter start (gated 16384 x 2048 at M = 20 and 64 20.6 -> 18.4 and 24.0 -> 21.9 us, 8192 x 8192 28.7 -> 26.2; with more items the
-    // longer lead is the better one, 22016 x 3072 at M = 50 28.5 and 30.1).
+    // longer lead is the better one, 22016 x 3072 at M = 50 28.5 and 30.1).  Above 64 rows, on 40 calls against the kernel that had two slices
+    // ahead everywhere, these tiles take 0.64 - 0.98 of its time on rows of 1536 weights and more; on rows of up to 768 with more tiles than compute units
+    // 1.02 - 1.07, but there other tiles are chosen and the calls take 0.75 - 1.04.
     bool two_ahead = false;
     if constexpr (E8 && FUSED && BM == 64 && BN == 256) {
         static std::atomic<uint64_t> allowed{0};
